@@ -141,12 +141,13 @@ size_t preft_workspace_bytes(int32_t T, int32_t S);
 
 /*
  * Bytes of a workspace that, beyond the schedule, has room for the intermediate z = A_i x of Eq. 2 of
- * every active row: LoRA calls of up to `rank` with up to n_proj outputs per call.  A LoRA call
- * (bf16, rank 20..64 in multiples of 4, d_in a multiple of 128, every d_out a multiple of 256) on a
- * batch of 8192 to 131 072 rows that is handed at least this many bytes runs its two sweeps as two
- * launches -- shrink into z, then the expand in 2-D tiles -- which measured 4 to 12 points of
- * bandwidth faster at that size (a batch of 38 416 rows, rank 32 and 64).  With fewer bytes, or
- * outside those limits, the same call runs as before.  The result is the same bit for bit.  The z area lies behind the schedule and is rewritten by every such call: calls that
+ * every active row: LoRA calls of up to `rank` with up to n_proj outputs per call.  A bf16 LoRA call of
+ * rank 1..64 (above rank 16: d_in and every d_out a multiple of 128) on a batch of more than 1024 rows that is
+ * handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the expand
+ * in 2-D tiles -- where that is faster: wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
+ * 1100), and every shape above rank 16 (up to 5x on 1100 rows).  With fewer bytes, or outside those limits,
+ * the same call runs as before, with the same result within the rounding of fp32 sums.
+ * The z area lies behind the schedule and is rewritten by every such call: calls that
  * share a workspace must be ordered on one stream, as they must be for the schedule already.
  * Returns 0 for a negative T or S, a rank outside 1..PREFT_MAX_RANK or n_proj outside
  * 1..PREFT_MAX_PACKED.

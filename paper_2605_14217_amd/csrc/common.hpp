@@ -75,6 +75,7 @@ typedef float  f32x2_t  __attribute__((ext_vector_type(2)));
 typedef float  f32x4_t  __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef int32_t  i32x4_t  __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf16_lo(uint32_t packed) { return __uint_as_float(packed << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t packed) { return __uint_as_float(packed & 0xffff0000u); }
@@ -100,6 +101,10 @@ __device__ __forceinline__ float wave_sum(float v)
 #define PREFT_GLOBAL __attribute__((address_space(1)))
 typedef const PREFT_GLOBAL char *gcptr_t;
 typedef PREFT_GLOBAL char *gptr_t;
+// The schedule and the pool tables do not change while an apply kernel runs: read through the constant address
+// space they come by scalar loads whatever the kernel stores in between.
+#define PREFT_CONST __attribute__((address_space(4)))
+template <typename T> __device__ __forceinline__ const PREFT_CONST T *as_const(const T *p) { return (const PREFT_CONST T *)p; }
 __device__ __forceinline__ gcptr_t as_global(const void *p) { return (gcptr_t)p; }
 __device__ __forceinline__ gptr_t as_global(void *p) { return (gptr_t)p; }
 
@@ -202,7 +207,10 @@ struct ApplyArgs {
     const int2         *shorts;
     const int4         *gtiles;
     void               *zws;             // z area of the workspace (two-launch LoRA), or null
+    int64_t             z_blocks;        // 16-row blocks the z area has room for
     int32_t             gathered_only;   // tile kernels: skip the chunks (another launch covers them)
+    int32_t             xcd_runs;        // expand launch: neighbouring tiles on one XCD
+    int32_t             chunks_only;     // expand launch: skip the gathered tiles (another launch covers them)
     int32_t             col_split;       // >= 1: workgroups per tile, each expanding its share of the columns
     // packed projections (LoRA only): further outputs computed from the same x, each with its
     // own factors; slice 0 is (y, ldy, d_out, A_pool, Bt_pool) above
@@ -226,12 +234,14 @@ struct ApplyArgs {
 // call's batch (same T, S, N and position set).  A caller that passes PREFT_SCHEDULE_READY with a
 // workspace built for something else would otherwise skip rows or apply the wrong position set
 // without any sign: such a launch does nothing and raises the mismatch flag of the header instead
-// (one ordinary vector store; preft_schedule_counts reports it).  Uniform: four scalar loads of
-// the cache line the kernel reads anyway.
+// (one ordinary vector store; preft_schedule_counts reports it).  Uniform: one trip to the cache line the
+// kernel reads anyway -- compared word by word behind && it was four dependent trips at the head of every kernel.
 __device__ __forceinline__ bool schedule_matches(const ApplyArgs &p)
 {
-    const bool ok = p.header[HDR_T] == p.T && p.header[HDR_S] == p.S && p.header[HDR_N] == p.N &&
-                    p.header[HDR_ALL] == p.all_tokens;
+    const PREFT_CONST i32x4_t *h = reinterpret_cast<const PREFT_CONST i32x4_t *>(as_const(p.header));
+    const i32x4_t lo = h[0], hi = h[1];
+    static_assert(HDR_ALL == 3 && HDR_T == 5 && HDR_S == 6 && HDR_N == 7, "words of the two vectors");
+    const bool ok = ((lo[3] ^ p.all_tokens) | (hi[1] ^ p.T) | (hi[2] ^ p.S) | (hi[3] ^ p.N)) == 0;
     if (!ok && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
         *reinterpret_cast<volatile int32_t *>(p.header + HDR_MISMATCH) = 1;
     return ok;
@@ -308,8 +318,9 @@ template <int R>
 __device__ __forceinline__ int tile_units(const ApplyArgs &p, int *n_chunk_units)
 {
     constexpr int UPG = R >= GTILE_ROWS ? 1 : GTILE_ROWS / R;
-    *n_chunk_units = p.gathered_only ? 0 : p.header[HDR_CHUNKS] * (CHUNK_ROWS / R);
-    return *n_chunk_units + p.header[HDR_GTILES] * UPG;
+    const PREFT_CONST int32_t *header = as_const(p.header);
+    *n_chunk_units = p.gathered_only ? 0 : header[HDR_CHUNKS] * (CHUNK_ROWS / R);
+    return *n_chunk_units + header[HDR_GTILES] * UPG;
 }
 
 }  // namespace preft

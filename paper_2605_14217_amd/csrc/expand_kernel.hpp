@@ -1,0 +1,218 @@
+// The expand sweep of LoRA as a launch of its own (bf16, z from the workspace):  y += s B z  (Eq. 2).
+//
+// A ZOUT launch of mfma_tile_kernel or mfma_wide_kernel has left z in the workspace in the form the MFMAs
+// below take it (scaled, split into bf16 head and remainder): 1 KB per 16-row block, output and rank block of
+// 16; lane l of a wavefront holds the 16-byte piece l (ranks 4 (l / 16) .. + 3 of row l % 16).
+//
+// Bound: HBM (y once in, once out).  What decides how much of it a kernel gets is the order in which the chip
+// walks the rows.  Measured with kernels that only move the bytes (read and write y, 89 600 rows of 28 672 bf16):
+// workgroups that loop over tiles or columns sustain 4.5-5.3 TB/s whatever they prefetch; the same tiles as
+// one workgroup each, ids in memory order, 6.0-6.6 (16 or 32 rows x 1 KB; a flat elementwise pass 5.95): the
+// hardware hands out workgroups in order, so the bytes in flight stay one narrow window of y.  Hence a
+// workgroup takes one tile of 16 MB rows x 512 columns and ends, tiles of a row block side by side, and every
+// request of the tile is issued before anything is computed.  A wavefront takes 128 columns and needs no barrier.
+//
+// The factors of its columns are contiguous in the [d_out, r] layout: they are fetched in whole lines and turned
+// through LDS, 32 columns at a time.  (Fetched in MFMA order, lanes of neighbouring columns, every lane is an
+// access of its own in the texture path: that path was busy 59 % of the time at rank 64, 1455 accesses per
+// wavefront, and the launch 5290 us instead of 4270.)  Two row blocks per wavefront halve the factor traffic; four
+// leave too few wavefronts in flight.
+// gate+up of the 8B layer, rank 16, 36 864 rows (4.2 GB of y): 700 us = 6.0 TB/s; the column sweeps of the
+// single launch 850.  70B layer, rank 64, 89 740 rows (20.6 GB): 4270 us = 4.8 TB/s (184 registers: two wavefronts
+// per SIMD); the barrier-and-stride panel kernel before this one 5180.
+#pragma once
+#include "common.hpp"
+#include "mfma_kernel.hpp"
+
+namespace preft {
+
+constexpr int EXPAND_WAVES = 4;                               // 128-column units (one per wavefront) of a workgroup
+
+// LDS of a wavefront: one 16-row turn buffer, and the factors of 32 columns.  A column's factors are padded by
+// 8 bytes so that the 16 columns of an MFMA operand read spread over all banks; ranks that are not multiples of 4
+// lie as in memory (a lane then shifts its four factors into place and may look one word past them).
+constexpr int expand_fac_bytes(int NB) { return 32 * (32 * NB + 8) + 16; }
+
+template <int NB, int MB, bool ODD>
+__global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(ApplyArgs p, int n_slices)
+{
+    constexpr int R = 16 * MB;
+    constexpr int TPC = CHUNK_ROWS / R;
+    static_assert(CHUNK_ROWS % R == 0, "tile height must divide the chunk height");
+    __shared__ u32x4_t turn[EXPAND_WAVES][16 * MFMA_TRS];
+    __shared__ __attribute__((aligned(16))) char fac[EXPAND_WAVES][expand_fac_bytes(NB)];
+
+    if (!schedule_matches(p)) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int rl = lane & 15, g = lane >> 4;                  // MFMA order
+    const int q = lane >> 4, c16 = lane & 15;                 // unit load order
+    const int r = p.rank;
+    u32x4_t *tr = turn[wave];
+    char *fw = fac[wave];
+
+    // column panels: those of the first output, then those of the others
+    auto panels_of = [](int d) { return (d + EXPAND_WAVES * 128 - 1) / (EXPAND_WAVES * 128); };
+    const int pan0 = panels_of(p.d_out);
+    const int pan1 = n_slices > 1 ? panels_of(p.more[0].d_out) : 0;
+    const int pan2 = n_slices > 2 ? panels_of(p.more[1].d_out) : 0;
+    const int panels = pan0 + pan1 + pan2;
+    const PREFT_CONST int32_t *header = as_const(p.header);
+    const int chunk_tiles = header[HDR_CHUNKS] * TPC;
+    const int n_tiles = chunk_tiles + (p.chunks_only ? 0 : header[HDR_GTILES]);
+    const uint32_t n_ids = (uint32_t)n_tiles * (uint32_t)panels;     // below 2^31 (host-checked)
+
+    const uint32_t per_xcd = (n_ids + 7) >> 3;
+    for (uint32_t slot = blockIdx.x; slot < n_ids + 7; slot += gridDim.x) {
+        const uint32_t id = p.xcd_runs ? (slot & 7) * per_xcd + (slot >> 3) : slot;
+        if (id >= n_ids || (p.xcd_runs && (slot >> 3) >= per_xcd)) continue;
+        const int tile_id = (int)(id / (uint32_t)panels);
+        int panel = (int)id - tile_id * panels;
+        const bool gathered = tile_id >= chunk_tiles;
+        const int row0 = gathered ? 0 : tile_id % TPC * R;    // within the chunk
+        const int4 entry = __builtin_bit_cast(int4, *reinterpret_cast<const PREFT_CONST i32x4_t *>(
+            gathered ? as_const(p.gtiles) + (tile_id - chunk_tiles) : as_const(p.chunks) + tile_id / TPC));
+        const int n_rows = min(R, entry.z - row0);
+        const int64_t block0 = gathered ? (int64_t)chunk_tiles * MB + (tile_id - chunk_tiles) : (int64_t)tile_id * MB;
+        if (n_rows <= 0 || block0 >= p.z_blocks) continue;    // (tables whose segments overlap can list more tiles than z has room for)
+        int sl = 0;
+        void *y = p.y;
+        int64_t ldy_b = p.ldy * 2;
+        int d_out = p.d_out;
+        const void *const *Bt_pool = p.Bt_pool;
+        if (panel >= pan0) {
+            sl = panel >= pan0 + pan1 ? 2 : 1;
+            panel -= sl == 2 ? pan0 + pan1 : pan0;
+            y = p.more[sl - 1].y; ldy_b = p.more[sl - 1].ldy * 2; d_out = p.more[sl - 1].d_out; Bt_pool = p.more[sl - 1].Bt_pool;
+        }
+        const int c0 = (panel * EXPAND_WAVES + __builtin_amdgcn_readfirstlane(wave)) * 128;   // this wavefront's first column
+        if (c0 >= d_out) continue;
+
+        // Every request of the tile at once, none of them conditional on the lane: row slots past the tile alias
+        // its last row, columns past the width the last ones, factor pieces past a column group's end its last
+        // piece.  Only the stores are masked.
+        int32_t row[MB][4];
+        const bool col_ok = c0 + c16 * 8 < d_out;             // d_out % 8 == 0: a lane's 8 columns exist or not
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) row[mb][i] = entry.y + row0 + min(mb * 16 + 4 * i + q, n_rows - 1);
+        if (gathered) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) row[mb][i] = p.shorts[row[mb][i]].y;
+        }
+        u32x4_t Y[MB][4];
+        gptr_t yc = as_global(y) + (int64_t)c0 * 2;           // uniform
+        const int y_col = (col_ok ? c16 * 8 : d_out - 8 - c0) * 2;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (mb * 16 < n_rows) Y[mb][i] = ld16_stream(yc + (row[mb][i] * ldy_b + y_col));
+        // factors of the 32 columns of step s: 4 r contiguous 16-byte pieces, of which this lane takes lane + 64 j
+        gcptr_t Wp = as_global(as_const(Bt_pool)[entry.x]);
+        const int w_last = (int)((int64_t)d_out * r / 8 - 1 - (int64_t)c0 * r / 8);      // last piece that exists, from this column on
+        Wp += (int64_t)c0 * r * 2;
+        constexpr int AHEAD = NB >= 4 ? 2 : 4;                // register budget
+        u32x4_t W[4][NB];
+        auto load_w = [&](int s) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) W[s][j] = ld16(Wp + (uint32_t)(min(s * 4 * r + lane + 64 * j, w_last) * 16));
+        };
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) load_w(s);
+        bf16x8_t zop[MB][NB];
+        gcptr_t zb = as_global(p.zws) + ((block0 * n_slices + sl) * NB * 64 + lane) * 16;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            if (mb * 16 < n_rows) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) zop[mb][b] = as_bf16x8(ld16(zb + (mb * n_slices * NB + b) * 1024));
+            }
+        }
+        // where the pieces land in LDS: two 8-byte halves, neither straddles a column (multiples of 4)
+        int w_dst[NB][2];
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                const int byte = (lane + 64 * j) * 16 + hh * 8;
+                w_dst[j][hh] = ODD ? byte : byte + byte / (2 * r) * 8;
+            }
+
+        // to MFMA order: lane (row rl, g) holds columns 8g .. 8g+7 of step s
+        u32x4_t yop[MB][4];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[mb][i];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) yop[mb][s] = tr[rl * MFMA_TRS + 4 * s + g];
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                if (lane + 64 * j < 4 * r) {
+                    if constexpr (ODD) {
+                        *reinterpret_cast<u32x4_t *>(fw + w_dst[j][0]) = W[s][j];
+                    } else {
+                        *reinterpret_cast<u32x2_t *>(fw + w_dst[j][0]) = u32x2_t{W[s][j][0], W[s][j][1]};
+                        *reinterpret_cast<u32x2_t *>(fw + w_dst[j][1]) = u32x2_t{W[s][j][2], W[s][j][3]};
+                    }
+                }
+            if (s + AHEAD < 4) load_w(s + AHEAD);
+            // MFMA e takes columns 2m + e of the step: lane (row, g) owns outputs 8g + 2v + e
+            u32x2_t w[2][NB];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const int rank0 = 16 * b + 4 * g, n = r - rank0;      // n: how many of the lane's four ranks exist
+                    if constexpr (ODD) {
+                        const uint32_t m01 = n >= 2 ? 0xffffffffu : n == 1 ? 0xffffu : 0u;
+                        const uint32_t m23 = n >= 4 ? 0xffffffffu : n == 3 ? 0xffffu : 0u;
+                        const int at = (2 * rl + e) * r + (n > 0 ? rank0 : 0);
+                        const uint32_t *w3 = reinterpret_cast<const uint32_t *>(fw) + (at >> 1);
+                        const uint32_t sh = (at & 1) * 16, d0 = w3[0], d1 = w3[1], d2 = w3[2];
+                        w[e][b] = u32x2_t{__builtin_amdgcn_alignbit(d1, d0, sh) & m01, __builtin_amdgcn_alignbit(d2, d1, sh) & m23};
+                    } else {
+                        w[e][b] = *reinterpret_cast<const u32x2_t *>(fw + (2 * rl + e) * (2 * r + 8) + (n > 0 ? rank0 : 0) * 2);
+                    }
+                }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                f32x4_t d[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    d[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        d[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[e][b][0], w[e][b][1], w[e][b][0], w[e][b][1]}),
+                                                                       zop[mb][b], d[e], 0, 0, 0);
+                }
+                const u32x4_t yv = yop[mb][s];
+                float out[8];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    out[2 * v]     = bf16_lo(yv[v]) + d[0][v];
+                    out[2 * v + 1] = bf16_hi(yv[v]) + d[1][v];
+                }
+                yop[mb][s] = Elem<bf16_tag>::pack(out);
+            }
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) tr[rl * MFMA_TRS + 4 * s + g] = yop[mb][s];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const u32x4_t o = tr[(4 * i + q) * MFMA_TRS + c16];
+                if (col_ok && mb * 16 + 4 * i + q < n_rows) st16_stream(yc + (row[mb][i] * ldy_b + c16 * 16), o);
+            }
+        }
+    }
+}
+
+}  // namespace preft

@@ -24,7 +24,7 @@ GROUPS = 7
 FAMILIES = {            # kernel template -> (header, rough relative compile cost)
     "preft::mfma_wide_kernel": ("mfma_wide_kernel.hpp", 3),
     "preft::mfma_wide_layers_kernel": ("mfma_wide_kernel.hpp", 3),
-    "preft::mfma_expand_panel_kernel": ("mfma_wide_kernel.hpp", 1),
+    "preft::mfma_expand_kernel": ("expand_kernel.hpp", 1),
     "preft::mfma_tile_kernel": ("mfma_kernel.hpp", 2),
     "preft::mfma_tile_layers_kernel": ("mfma_kernel.hpp", 2),
     "preft::valu_tile_kernel": ("valu_kernel.hpp", 1),

@@ -91,8 +91,11 @@ constexpr int mfma_min_waves(int NB, int MB, int WAVES, int HUNITS)
 // two bytes at a time, zero for the ranks past r.  ODD is the number of 16-byte pieces of that block a
 // lane carries: 2 up to rank 8, 4 up to rank 16.  In place with the tile in registers, the blocks of the
 // first two units are requested before the reduction of z and the next ones while a unit is finished.
+//
+// ZOUT: the shrink sweep alone.  z goes to the workspace in the form the expand's MFMAs take it, 1 KB per
+// 16-row block and rank block, and mfma_expand_kernel does the expand in a second launch.
 template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bool COLSPLIT = false, bool PARTIAL = false,
-          int ODD = 0>
+          int ODD = 0, bool ZOUT = false>
 __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 {
     static_assert(!PARTIAL || HUNITS > 0, "a partially resident tile keeps some units");
@@ -140,6 +143,9 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
         unit = xcd_unit(n_units);
     }
     if (unit < 0) return;
+    if constexpr (ZOUT) {
+        if (unit >= p.z_blocks) return;                       // only tables whose segments overlap list that many tiles
+    }
     TileRows tile;
     if (!tile_rows<R>(p, unit, n_chunk_units, tile)) return;   // uniform over the workgroup
     const int adapter = tile.adapter;
@@ -342,7 +348,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     // first output's y and factor is requested before the reduction of z, so that the sweep over
     // the output starts without a gap.  The addresses are those of the sweep.  (Measured: +1 to +3
     // points of bandwidth with one output, nothing with two, a loss with three.)
-    constexpr bool EARLY_UNIT = SLICES <= 2 && HUNITS == 0 && NB == 1 && MB == 1 && !ODD;
+    constexpr bool EARLY_UNIT = SLICES <= 2 && HUNITS == 0 && NB == 1 && MB == 1 && !ODD && !ZOUT;
     u32x4_t y_early[MB][4];
     u32x2_t w_early[4][2][NB];
     if constexpr (EARLY_UNIT) {
@@ -449,6 +455,14 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
             packed[3] = pack_bf16(rem_f[2], rem_f[3]);
             zop[b][mb] = as_bf16x8(packed);
         }
+    }
+
+    if constexpr (ZOUT) {                                     // every wavefront holds the same z: they share the writing
+        u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + (int64_t)unit * (NBT * 64) + lane;
+#pragma unroll
+        for (int b = 0; b < NBT; ++b)
+            if (b % WAVES == wave) zw[b * 64] = as_u32x4(zop[b][0]);
+        return;
     }
 
     // ---------------------------------------------------------------- expand (once per output)
@@ -687,10 +701,10 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 }
 
 template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bool COLSPLIT = false, bool PARTIAL = false,
-          int ODD = 0>
+          int ODD = 0, bool ZOUT = false>
 __global__ __launch_bounds__(WAVES * 64, mfma_min_waves(NB, MB, WAVES, HUNITS)) void mfma_tile_kernel(ApplyArgs p)
 {
-    mfma_tile_body<NB, MB, WAVES, HUNITS, DIREFT, SLICES, COLSPLIT, PARTIAL, ODD>(p);
+    mfma_tile_body<NB, MB, WAVES, HUNITS, DIREFT, SLICES, COLSPLIT, PARTIAL, ODD, ZOUT>(p);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer

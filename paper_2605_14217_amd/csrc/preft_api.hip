@@ -3,6 +3,7 @@
 #include "../../include/preft.h"
 
 #include "common.hpp"
+#include "expand_kernel.hpp"
 #include "mfma_kernel.hpp"
 #include "mfma_wide_kernel.hpp"
 #include "row_kernel.hpp"
@@ -243,32 +244,72 @@ inline bool wide_widths_ok(const ApplyArgs &a, int cw)
     return (a.d_in % m) == 0 && (a.d_out % m) == 0;
 }
 
-// LoRA at rank 20..64 with a z area in the workspace: the chunks' shrink sweep and expand sweep as two
-// launches, the expand in 2-D tiles of 64 rows x 256 columns (see mfma_expand_panel_kernel).  Measured on
-// the same buffers, % of peak, one launch -> two:
-//   8B-sized batch (38 416 rows): rank 64 q+k+v 37 -> 42, o 42-43 -> 51-53, gate+up 47 -> 59, down 46 -> 51;
-//     rank 32 q+k+v 52 -> 53, o 58 -> 62.5, gate+up 58 -> 66.5, down 62 -> 62 (a 64-row tile per workgroup
-//     leaves the chip 1.2 rounds of tiles; the expand launch has thousands of small workgroups);
-//   70B-sized batch (352 814 rows): rank 64 o and down +2 to +4 on one set of buffers, -2 on another (the
-//     one-launch kernel moves between 62 and 68 % with the placement of its buffers, the two launches stay
-//     at 62-66 %), packed q+k+v 57.8 -> 52, gate+up 61.8 -> 60.8 (the shrink launch of two or three outputs is
-//     bound by LDS reads and MFMA issue once no expand sweep of another workgroup runs beside it: 33 % of peak
-//     for q+k+v; 28 672-wide dense rows gain little from the tiling); rank 32 o 73.8 -> 74.2, down 71.9 -> 76.5,
-//     packed q+k+v 69 -> 61, gate+up 74 -> 68; skewed batch (836 609 rows), rank 32, 8192 -> 8192: 77.4 -> 73.9.
-// Hence: batches of 8192 to 131 072 rows.  PREFT_TEST_RESIDENT(1) takes this form wherever it exists,
-// PREFT_TEST_VARIANT(5) never.  Panels of 128 columns: -1 to -3 points; of 512: one workgroup per compute
-// unit, -15.
-template <int NB, int SLICES>
-bool launch_mfma_split(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
+// the expand launch of a call whose z is in the workspace: a workgroup per 16 MB rows x 512 columns
+template <int NB, int MB, bool ODD>
+bool launch_expand_shape(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
 {
-    constexpr int PU = 2;
-    if (!a.zws || k.variant == 5 || k.waves || k.rowblocks || k.colsplit) return false;
-    if (k.resident != 1 && (a.T < 8192 || a.T > 131072)) return false;
-    if ((a.d_in % 128) != 0 || (a.d_out % (128 * PU)) != 0) return false;
-    int max_d_out = a.d_out;
-    for (int i = 1; i < SLICES; ++i) {
-        if ((a.more[i - 1].d_out % (128 * PU)) != 0) return false;
-        if (a.more[i - 1].d_out > max_d_out) max_d_out = a.more[i - 1].d_out;
+    constexpr int COLS = EXPAND_WAVES * 128;
+    int64_t panels = (a.d_out + COLS - 1) / COLS;
+    for (int i = 1; i < n_slices; ++i) panels += (a.more[i - 1].d_out + COLS - 1) / COLS;
+    // more tiles than the batch's rows fill are likely to be empty: the kernel strides over what exceeds the grid
+    const int64_t bound = tile_grid(a, S, 16 * MB), likely = (int64_t)a.T / (16 * MB) * 5 / 4 + 64;
+    if (bound * panels >= ((int64_t)1 << 31)) return false;
+    hipLaunchKernelGGL((mfma_expand_kernel<NB, MB, ODD>), dim3((unsigned)((bound < likely ? bound : likely) * panels)),
+                       dim3(EXPAND_WAVES * 64), 0, stream, a, n_slices);
+    return true;
+}
+
+bool rows_off_lines(const ApplyArgs &a, int n_slices);
+
+template <int NB, bool ODD>
+bool launch_expand(ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
+{
+    a.xcd_runs = rows_off_lines(a, n_slices);
+    return launch_expand_shape<NB, 2, ODD>(a, S, n_slices, stream);
+}
+
+// Rows that do not start on 128-byte lines: neighbouring panels share lines, so they go to one XCD.
+bool rows_off_lines(const ApplyArgs &a, int n_slices)
+{
+    bool off = ((reinterpret_cast<uintptr_t>(a.y) | (uintptr_t)(a.ldy * 2)) & 127) != 0;
+    for (int i = 1; i < n_slices; ++i) off = off || ((reinterpret_cast<uintptr_t>(a.more[i - 1].y) | (uintptr_t)(a.more[i - 1].ldy * 2)) & 127) != 0;
+    return off;
+}
+
+// LoRA with a z area in the workspace: the shrink sweep leaves z there and the expand runs as a launch of its
+// own (mfma_expand_kernel).  Measured on the same buffers, one launch -> two, prompts of about 700 rows:
+//   rank 16, 4096 -> 2 x 14336: 1100 rows 67 -> 36 us, 8000 rows 247 -> 181, 37 000 rows 909 -> 789; 4096 -> 4096:
+//     15.3 -> 15.5, 48.6 -> 46.2, 167 -> 159; 500 rows (against four workgroups per tile): 10.9 -> 13.2;
+//     1024 -> 2728 (rows off 128-byte lines): 2000 rows 11.3 -> 13.6, 37 000 rows 114 -> 120; 2000 -> 3208:
+//     15.0 -> 14.4, 154 -> 148.  Ranks 1-15 alike (rank 1, 2 x 14336: 37 000 rows 967 -> 763).
+//   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 518 -> 454; rank 32 86 -> 48,
+//     105 -> 97, 355 -> 372.
+//   decode rows alone, 7 per adapter (gathered tiles), rank 16, 8192 -> 8192: 1200 rows 30 -> 35, 3584 rows 89 -> 89;
+//     one per adapter 87 -> 109.
+// Hence: above 1024 rows; up to rank 16 where the outputs are worth a second launch, and not for all-position
+// batches of mostly single rows.  PREFT_TEST_RESIDENT(1) takes this form wherever it exists, PREFT_TEST_VARIANT(5) never.
+bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
+{
+    if (!a.zws || (k.variant != 0 && k.variant != 4) || k.waves || k.rowblocks || k.colsplit) return false;
+    if (k.resident == 1) return true;
+    if (a.T <= 1024) return false;
+    if (a.rank > 16) return true;
+    if (a.all_tokens && a.T < 8 * S) return false;
+    int64_t width = a.d_out;
+    for (int i = 1; i < n_slices; ++i) width += a.more[i - 1].d_out;
+    return a.T * width >= 6000000 && (width >= 3072 || !rows_off_lines(a, n_slices));
+}
+
+// rank 17..64: the row-split kernel's shrink sweep of the chunks, then their expand launch
+template <int NB, int SLICES>
+bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream_t stream)
+{
+    if (!wants_split(a0, S, SLICES, k) || (a0.d_in % 128) != 0) return false;
+    ApplyArgs a = a0;
+    a.chunks_only = 1;
+    if (a.rank % 4) {
+        hipLaunchKernelGGL((mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, true>), dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
+        return launch_expand<NB, true>(a, S, SLICES, stream);
     }
     void (*shrink)(ApplyArgs) = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true>;
     int threads = 256;
@@ -276,11 +317,23 @@ bool launch_mfma_split(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_
         if ((a.d_in % 256) == 0) { shrink = mfma_wide_kernel<NB, 1, 4, 2, false, SLICES, true>; threads = 512; }
     }
     hipLaunchKernelGGL(shrink, dim3(chunk_grid(a, S, 64)), dim3(threads), 0, stream, a);
-    int64_t tiles = chunk_capacity(a.T, S) * (CHUNK_ROWS / 64) * (int64_t)(max_d_out / (128 * PU));
-    tiles = ((tiles + 7) / 8) * 8;
-    if (tiles > 8192) tiles = 8192;                         // the kernel strides over the rest
-    hipLaunchKernelGGL((mfma_expand_panel_kernel<NB, 4, PU>), dim3((unsigned)tiles, SLICES), dim3(256), 0, stream, a, SLICES);
-    return true;
+    return launch_expand<NB, false>(a, S, SLICES, stream);
+}
+
+// rank 1..16: the column-split kernel's shrink sweep, then the expand launch; chunks and gathered tiles alike
+template <int SLICES>
+bool launch_mfma_split16(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
+{
+    constexpr int WAVES = SLICES == 3 ? 4 : 8;
+    if (!wants_split(a, S, SLICES, k)) return false;
+    if (a.rank % 4) {
+        hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, false, 2, true>), dim3(tile_grid(a, S, 16)),
+                           dim3(WAVES * 64), 0, stream, a);
+        return launch_expand<1, true>(a, S, SLICES, stream);
+    }
+    hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, false, 0, true>), dim3(tile_grid(a, S, 16)),
+                       dim3(WAVES * 64), 0, stream, a);
+    return launch_expand<1, false>(a, S, SLICES, stream);
 }
 
 template <int NB, bool DIREFT>
@@ -342,6 +395,9 @@ void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t s
         }
     }
     if constexpr (!DIREFT) {
+        if constexpr (NB == 1) {
+            if (k.variant == 0 && launch_mfma_split16<1>(a, S, k, stream)) return;
+        }
         if (a.col_split > 1) {
             launch_mfma_colsplit<NB, 1>(a, S, stream);
             return;
@@ -363,6 +419,7 @@ void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t s
 template <int SLICES, int PIECES = 0>
 void launch_mfma_packed(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
+    if (k.variant == 0 && launch_mfma_split16<SLICES>(a, S, k, stream)) return;
     if (a.col_split > 1) {
         launch_mfma_colsplit<1, SLICES, PIECES>(a, S, stream);
         return;
@@ -387,11 +444,12 @@ void launch_rows(const ApplyArgs &a, int64_t S, bool chunks_too, hipStream_t str
 template <int NB>
 void launch_mfma_wide_packed(const ApplyArgs &a, int n_proj, int64_t S, const Knobs &k, hipStream_t stream)
 {
+    const bool split = n_proj == 2 ? launch_mfma_split<NB, 2>(a, S, k, stream) : launch_mfma_split<NB, 3>(a, S, k, stream);
     if (a.rank % 4) {
         // the any-rank form: the basic shape for the chunks, the per-row kernel for the gathered tiles
         void (*odd)(ApplyArgs) = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 1, false, 2, false, true>
                                              : mfma_wide_kernel<NB, 1, 4, 1, false, 3, false, true>;
-        hipLaunchKernelGGL(odd, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
+        if (!split) hipLaunchKernelGGL(odd, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
         for (int i = 0; i < n_proj; ++i) {
             ApplyArgs g = a;
             if (i > 0) {
@@ -402,7 +460,6 @@ void launch_mfma_wide_packed(const ApplyArgs &a, int n_proj, int64_t S, const Kn
         }
         return;
     }
-    const bool split = n_proj == 2 ? launch_mfma_split<NB, 2>(a, S, k, stream) : launch_mfma_split<NB, 3>(a, S, k, stream);
     // two column groups at rank 32 where every width allows it (see launch_mfma_nb)
     bool cw2 = NB <= 2 && (a.d_in % 256) == 0 && (a.d_out % 256) == 0;
     for (int i = 1; i < n_proj; ++i) cw2 = cw2 && (a.more[i - 1].d_out % 256) == 0;
@@ -451,8 +508,11 @@ void launch_mfma_odd_pieces(const ApplyArgs &a, int64_t S, hipStream_t stream)
 }
 
 template <bool DIREFT>
-void launch_mfma_odd(const ApplyArgs &a, int64_t S, hipStream_t stream)
+void launch_mfma_odd(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
+    if constexpr (!DIREFT) {
+        if (k.variant == 0 && launch_mfma_split16<1>(a, S, k, stream)) return;
+    }
     // a unit's [128 columns][rank] block of the expand factor is 16 * rank pieces of 16 bytes: 2 per lane
     // up to rank 8, 4 up to rank 16
     if (a.rank <= 8) launch_mfma_odd_pieces<DIREFT, 2>(a, S, stream);
@@ -463,10 +523,15 @@ void launch_mfma_odd(const ApplyArgs &a, int64_t S, hipStream_t stream)
 // form takes the chunks (its basic shape: 4 wavefronts x 16 rows, above rank 64 8 x 16), the per-row kernel
 // the gathered tiles (all-token mode: decode rows)
 template <bool DIREFT>
-void launch_mfma_odd_wide(const ApplyArgs &a, int64_t S, hipStream_t stream)
+void launch_mfma_odd_wide(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
     const int nb = (a.rank + 15) / 16;
-    if (nb <= 2)      launch_wide_shape<2, 1, 4, 1, DIREFT, true>(a, S, stream);
+    bool split = false;
+    if constexpr (!DIREFT) {
+        if (nb <= 4) split = nb <= 2 ? launch_mfma_split<2, 1>(a, S, k, stream) : launch_mfma_split<4, 1>(a, S, k, stream);
+    }
+    if (split)        {}
+    else if (nb <= 2)      launch_wide_shape<2, 1, 4, 1, DIREFT, true>(a, S, stream);
     else if (nb <= 4) launch_wide_shape<4, 1, 4, 1, DIREFT, true>(a, S, stream);
     else              launch_wide_shape<8, 1, 8, 1, DIREFT, true>(a, S, stream);
     launch_rows<bf16_tag, DIREFT>(a, S, false, stream);
@@ -476,8 +541,8 @@ template <bool DIREFT>
 void launch_mfma_rank(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
     const int nb = (a.rank + 15) / 16;
-    if ((a.rank % 4) && a.rank > 16) { launch_mfma_odd_wide<DIREFT>(a, S, stream); return; }   // widths: choose_path
-    if (a.rank % 4) { launch_mfma_odd<DIREFT>(a, S, stream); return; }      // rank <= 16 (choose_path)
+    if ((a.rank % 4) && a.rank > 16) { launch_mfma_odd_wide<DIREFT>(a, S, k, stream); return; }   // widths: choose_path
+    if (a.rank % 4) { launch_mfma_odd<DIREFT>(a, S, k, stream); return; }      // rank <= 16 (choose_path)
     if (nb <= 1)      launch_mfma_nb<1, DIREFT>(a, S, k, stream);
     else if (nb <= 2) launch_mfma_nb<2, DIREFT>(a, S, k, stream);
     else if (nb <= 4) launch_mfma_nb<4, DIREFT>(a, S, k, stream);
@@ -591,6 +656,9 @@ int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipSt
         break;
     }
     case Path::Valu:
+        if constexpr (!DIREFT) {
+            if (k.variant == 0 && launch_mfma_split16<1>(a, S, k, stream)) break;
+        }
         launch_valu_rank<DIREFT>(a, S, k, stream);
         break;
     default:
@@ -621,14 +689,16 @@ void bind_schedule(ApplyArgs &a, void *workspace, int32_t T, int32_t S, int32_t 
     const ScheduleView v = view_of(workspace, T, S);
     a.T = T; a.S = S; a.N = N; a.all_tokens = (mode & PREFT_ALL_TOKENS) ? 1 : 0;
     a.header = v.header; a.chunks = v.chunks; a.shorts = v.shorts; a.gtiles = v.gtiles;
-    a.gathered_only = 0; a.col_split = 1; a.zws = nullptr;
+    a.gathered_only = 0; a.chunks_only = 0; a.xcd_runs = 0; a.col_split = 1; a.zws = nullptr; a.z_blocks = 0;
 }
 
-// a workspace with room for z lets the LoRA calls of large batches run their sweeps as two launches
+// a workspace with room for z lets LoRA calls run their sweeps as two launches
 void bind_z(ApplyArgs &a, void *workspace, size_t bytes, int32_t T, int32_t S, int32_t rank, int32_t n_proj)
 {
-    if (T > 1024 && bytes >= z_offset(T, S) + z_bytes(T, S, rank, n_proj))
+    if (bytes >= z_offset(T, S) + z_bytes(T, S, rank, n_proj)) {
         a.zws = reinterpret_cast<char *>(workspace) + z_offset(T, S);
+        a.z_blocks = chunk_capacity(T, S) * (CHUNK_ROWS / 16);
+    }
 }
 
 int check_matrix(const void *p, int64_t ld, int32_t width, int dtype)
@@ -776,12 +846,12 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
     bind_schedule(a, workspace, T, S, N, mode);
     a.y = y[0]; a.x = x; a.ldy = ldy[0]; a.ldx = ldx; a.d_in = d_in; a.d_out = d_out[0];
     a.A_pool = A_pools[0]; a.Bt_pool = B_pools[0]; a.bias_pool = nullptr; a.rank = rank; a.scale = scale;
+    bind_z(a, workspace, bytes, T, S, rank, n_proj);
     for (int32_t i = 1; i < n_proj; ++i) {
         a.more[i - 1].y = y[i]; a.more[i - 1].ldy = ldy[i]; a.more[i - 1].d_out = d_out[i];
         a.more[i - 1].A_pool = A_pools[i]; a.more[i - 1].Bt_pool = B_pools[i];
     }
     if (fused_wide) {
-        bind_z(a, workspace, bytes, T, S, rank, n_proj);
         if (rank <= 32) launch_mfma_wide_packed<2>(a, n_proj, S, k, st);
         else            launch_mfma_wide_packed<4>(a, n_proj, S, k, st);
     } else if (fused_mfma) {
@@ -797,6 +867,7 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
             else                  launch_mfma_packed<3, 4>(a, S, k, st);
         }
     } else {
+        if (k.variant == 0 && (n_proj == 2 ? launch_mfma_split16<2>(a, S, k, st) : launch_mfma_split16<3>(a, S, k, st))) return check_launch();
         if (n_proj == 2) launch_valu_packed<2>(a, S, st);
         else             launch_valu_packed<3>(a, S, st);
     }

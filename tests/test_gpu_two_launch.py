@@ -1,0 +1,68 @@
+"""LoRA as two launches (shrink into the workspace's z area, then the expand in 2-D tiles): every rank class, at the
+edges of its tiles -- 32 rows x 512 columns, 128-column units, 32-column steps -- against the oracle, and bit for
+bit against the single launch where both sum in the same order (rank >= 4; ranks 1-3 otherwise take the vector-ALU
+kernel).  Bars of parity_util: row-wise 1e-2 for bf16 storage."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_14217_amd as preft
+from paper_2605_14217_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# prompts of 1, 15..17, 31..33, 127..129 rows between decode rows, and one empty segment
+LENS = [1, 15, 16, 17, 31, 32, 33, 5, 0, 127, 128, 129, 4, 560] + [1] * 40
+
+CASES = [(1, 512, (512,)), (3, 1000, (520, 8)), (4, 128, (128, 1032, 512)), (5, 264, (640,)), (7, 1000, (2728, 2728)),
+         (8, 136, (1544,)), (12, 520, (504, 512)), (16, 4104, (512,)), (16, 512, (1536, 256, 256)), (13, 384, (1288, 24, 512)),
+         (17, 128, (128,)), (20, 256, (512, 256)), (31, 384, (512, 128, 256)), (36, 128, (1152,)), (48, 256, (512,)),
+         (63, 256, (640, 512)), (64, 128, (128, 1664))]
+
+
+@pytest.mark.parametrize("pad", [0, 8])
+@pytest.mark.parametrize("rank,d_in,d_outs", CASES, ids=[f"r{c[0]}-{c[1]}-{'x'.join(map(str, c[2]))}" for c in CASES])
+def test_two_launches_match_the_oracle_and_the_single_launch(rank, d_in, d_outs, pad):
+    from oracle import preft_oracle as ora
+    from parity_util import bits, check_guards, compare, dev_tables, lora_pools_to_device, padded
+    N = 5
+    rng = np.random.Generator(np.random.PCG64(rank * 31 + d_in))
+    lens = np.array(LENS)
+    ids = rng.integers(-1, N + 1, size=len(lens))              # -1 and N: no adapter
+    tab = wl.from_lengths(lens, ids, np.where(np.arange(len(lens)) < 14, np.maximum(lens - (lens > 100), 0), 0))
+    T = tab.T
+    ss, sa, sp = dev_tables(tab)
+    x = wl.activations(T, d_in, "bf16", device="cuda", seed=1)
+    y0s = [wl.activations(T, n, "bf16", device="cuda", seed=2 + i) for i, n in enumerate(d_outs)]
+    pools = [wl.lora_pool(N, rank, d_in, n, "bf16", device="cuda", seed=9 + i) for i, n in enumerate(d_outs)]
+    tables = [lora_pools_to_device(pl) for pl in pools]
+    ws = preft.new_workspace(T, tab.S, z_rank=rank, z_proj=len(d_outs))
+
+    def call(mode, flags):
+        ws.fill_(0xa5)                                        # nothing in the workspace has to start at zero
+        bufs = [padded(y, pad, 7.0) for y in y0s]
+        prev = preft.set_test_flags(flags)
+        try:
+            preft.preft_lora_apply_packed([b[1] for b in bufs], x, ss, sa, sp, [t[0] for t in tables],
+                                          [t[1] for t in tables], rank, 2.0, mode, ws)
+        finally:
+            preft.set_test_flags(prev)
+        torch.cuda.synchronize()
+        for (buf, _), n in zip(bufs, d_outs):
+            check_guards(buf, T, n, 7.0)
+        return [b[1] for b in bufs]
+
+    for all_tokens in (False, True):
+        mode = preft.PREFT_ALL_TOKENS if all_tokens else preft.PREFT_PREFILL_ONLY
+        pos = ora.ALL_POSITIONS if all_tokens else ora.PROMPT_ONLY
+        owner = ora.positions(T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, pos)
+        two = call(mode, preft.test_flags(resident=1))
+        for y, y0, pl in zip(two, y0s, pools):
+            want = ora.lora(y0.cpu(), x.cpu(), tab.seg_start, tab.seg_adapter, tab.seg_prefill_len,
+                            [a.cpu() for a in pl.A], [b.cpu() for b in pl.B], rank, 2.0, pos)
+            compare(y, y0, want, owner, "bf16")
+        # the any-rank shape of the single launch sums 8 partial z also for three outputs
+        if rank >= 4 and not (rank < 16 and rank % 4 and len(d_outs) == 3):
+            one = call(mode, preft.test_flags(variant=5, colsplit=1))
+            for y, y1 in zip(two, one):
+                assert torch.equal(bits(y), bits(y1))
