@@ -62,9 +62,9 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
     const uint32_t n_ids = (uint32_t)n_tiles * (uint32_t)panels;     // below 2^31 (host-checked)
 
     const uint32_t per_xcd = (n_ids + 7) >> 3;
-    for (uint32_t slot = blockIdx.x; slot < n_ids + 7; slot += gridDim.x) {
+    for (uint32_t slot = blockIdx.x; slot < per_xcd * 8; slot += gridDim.x) {
         const uint32_t id = p.xcd_runs ? (slot & 7) * per_xcd + (slot >> 3) : slot;
-        if (id >= n_ids || (p.xcd_runs && (slot >> 3) >= per_xcd)) continue;
+        if (id >= n_ids) continue;
         const int tile_id = (int)(id / (uint32_t)panels);
         int panel = (int)id - tile_id * panels;
         const bool gathered = tile_id >= chunk_tiles;
@@ -108,17 +108,16 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (mb * 16 < n_rows) Y[mb][i] = ld16_stream(yc + (row[mb][i] * ldy_b + y_col));
+            for (int i = 0; i < 4; ++i) Y[mb][i] = ld16_stream(yc + (row[mb][i] * ldy_b + y_col));
         // factors of the 32 columns of step s: 4 r contiguous 16-byte pieces, of which this lane takes lane + 64 j
-        gcptr_t Wp = as_global(as_const(Bt_pool)[entry.x]);
-        const int w_last = (int)((int64_t)d_out * r / 8 - 1 - (int64_t)c0 * r / 8);      // last piece that exists, from this column on
-        Wp += (int64_t)c0 * r * 2;
+        // (lanes past them the last one)
+        gcptr_t Wp = as_global(as_const(Bt_pool)[entry.x]) + (int64_t)c0 * r * 2;
+        const int w_last = (d_out - c0) * r / 8 - 1;          // last piece that exists, from column c0 on
         constexpr int AHEAD = NB >= 4 ? 2 : 4;                // register budget
         u32x4_t W[4][NB];
         auto load_w = [&](int s) {
 #pragma unroll
-            for (int j = 0; j < NB; ++j) W[s][j] = ld16(Wp + (uint32_t)(min(s * 4 * r + lane + 64 * j, w_last) * 16));
+            for (int j = 0; j < NB; ++j) W[s][j] = ld16(Wp + (uint32_t)(min(s * 4 * r + min(lane + 64 * j, 4 * r - 1), w_last) * 16));
         };
 #pragma unroll
         for (int s = 0; s < AHEAD; ++s) load_w(s);
@@ -126,10 +125,9 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
         gcptr_t zb = as_global(p.zws) + ((block0 * n_slices + sl) * NB * 64 + lane) * 16;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            if (mb * 16 < n_rows) {
+            const int m = mb * 16 < n_rows ? mb : 0;          // row blocks past the tile: any z will do
 #pragma unroll
-                for (int b = 0; b < NB; ++b) zop[mb][b] = as_bf16x8(ld16(zb + (mb * n_slices * NB + b) * 1024));
-            }
+            for (int b = 0; b < NB; ++b) zop[mb][b] = as_bf16x8(ld16(zb + (m * n_slices * NB + b) * 1024));
         }
         // where the pieces land in LDS: two 8-byte halves, neither straddles a column (multiples of 4)
         int w_dst[NB][2];
@@ -137,7 +135,7 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
-                const int byte = (lane + 64 * j) * 16 + hh * 8;
+                const int byte = min(lane + 64 * j, 4 * r - 1) * 16 + hh * 8;
                 w_dst[j][hh] = ODD ? byte : byte + byte / (2 * r) * 8;
             }
 
@@ -153,15 +151,14 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
-                if (lane + 64 * j < 4 * r) {
-                    if constexpr (ODD) {
-                        *reinterpret_cast<u32x4_t *>(fw + w_dst[j][0]) = W[s][j];
-                    } else {
-                        *reinterpret_cast<u32x2_t *>(fw + w_dst[j][0]) = u32x2_t{W[s][j][0], W[s][j][1]};
-                        *reinterpret_cast<u32x2_t *>(fw + w_dst[j][1]) = u32x2_t{W[s][j][2], W[s][j][3]};
-                    }
+            for (int j = 0; j < NB; ++j) {
+                if constexpr (ODD) {
+                    *reinterpret_cast<u32x4_t *>(fw + w_dst[j][0]) = W[s][j];
+                } else {
+                    *reinterpret_cast<u32x2_t *>(fw + w_dst[j][0]) = u32x2_t{W[s][j][0], W[s][j][1]};
+                    *reinterpret_cast<u32x2_t *>(fw + w_dst[j][1]) = u32x2_t{W[s][j][2], W[s][j][3]};
                 }
+            }
             if (s + AHEAD < 4) load_w(s + AHEAD);
             // MFMA e takes columns 2m + e of the step: lane (row, g) owns outputs 8g + 2v + e
             u32x2_t w[2][NB];

@@ -15,14 +15,14 @@ template __global__ void preft::mfma_tile_kernel<2, 2, 4, 8, true, 1, false, tru
 template __global__ void preft::mfma_tile_kernel<8, 1, 4, 0, false, 1, true, false, 0, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_tile_layers_kernel<1, 1, 8, 0, false, 4>(preft::ApplyArgs);
 template __global__ void preft::mfma_tile_layers_kernel<2, 2, 4, 0, false, 0>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<1, 1, 8, 1, false, 1, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 1, true, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 3, true, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<2, 1, 4, 2, false, 2, true, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<2, 2, 4, 1, true, 1, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, false, 2, true, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, true, 1, false, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<8, 1, 4, 1, false, 1, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<1, 1, 8, 1, false, 1, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 1, true, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 3, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<2, 1, 4, 2, false, 1, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<2, 2, 4, 1, true, 1, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, false, 2, true, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, true, 1, false, true, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<8, 1, 4, 1, false, 1, false, false, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<1, 1, 4, 2, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<2, 2, 4, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<8, 1, 8, 1, false>(preft::ApplyArgs);

@@ -15,14 +15,14 @@ template __global__ void preft::mfma_tile_kernel<4, 1, 4, 0, false, 1, false, fa
 template __global__ void preft::mfma_tile_kernel<8, 1, 4, 0, true, 1, false, false, 0, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_tile_layers_kernel<1, 1, 8, 4, false, 0>(preft::ApplyArgs);
 template __global__ void preft::mfma_tile_layers_kernel<2, 2, 4, 8, true, 0>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<1, 1, 8, 1, true, 1, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 2, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 3, true, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<2, 1, 4, 2, false, 3, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, false, 1, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, false, 2, true, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<4, 1, 4, 2, false, 1, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<8, 1, 4, 1, true, 1, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<1, 1, 8, 1, true, 1, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 1, true, true, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 3, false, true, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<2, 1, 4, 2, false, 2, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, false, 1, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, false, 2, true, true, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<4, 1, 4, 2, false, 1, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<8, 1, 4, 1, true, 1, false, false, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<1, 1, 8, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<4, 1, 4, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<8, 1, 8, 1, true>(preft::ApplyArgs);

@@ -35,6 +35,8 @@
 #include "common.hpp"
 #include "mfma_kernel.hpp"
 
+#include <type_traits>
+
 namespace preft {
 
 constexpr int wide_fac_bytes(int NB, int CW)                   // one buffer of CW factor units
@@ -53,17 +55,22 @@ constexpr int wide_lds_bytes(int NB, int MB, int RW, int CW)
 // split into bf16 head and remainder, in lane order), goes to the z area of the workspace, 1 KB per
 // 16-row block and rank block, and mfma_expand_kernel does the expand in a second launch.
 //
+// EO (ZOUT only): even and odd units are summed apart and added at the end, as the two column groups of the
+// single launch do, so that both forms give the same bits.  The read-only sweep itself is faster without column
+// groups (rank 32, 14336 columns, 36 864 rows: 222 -> 199 us, 5.3 TB/s): more and shorter tiles per compute unit.
+//
 // ODD: ranks that are not multiples of 4 (17, 18, 19, 21, ...; nothing is padded in memory).  The shrink
 // needs nothing new (rank rows past r alias row r-1, their z is zeroed, here per element).  The expand's B
 // units go to LDS as they lie in memory, a column's r factors right behind the previous column's, and a
 // lane reads its four factors of a column as the three 32-bit words that hold them, shifts them into place
 // and masks the ranks past r (as the any-rank shape of mfma_tile_kernel does for rank 5..15).
-template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false>
+template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false, bool EO = false>
 __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
 {
     static_assert(!ODD || (MB == 1 && CW == 1), "the any-rank form: the basic shape");
     static_assert(SLICES == 1 || !DIREFT, "packed projections are a LoRA feature");
     static_assert(!ZOUT || (!DIREFT && MB == 1), "the two-launch form: LoRA, 16-row blocks per wavefront");
+    static_assert(!EO || (ZOUT && CW == 1), "one wavefront in place of two column groups");
     constexpr int WAVES = RW * CW;
     constexpr int NBT = NB * SLICES;                          // accumulator blocks of the shrink sweep
     constexpr int R = 16 * MB * RW;
@@ -130,11 +137,14 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
     };
 
     // ---------------------------------------------------------------- shrink
-    f32x4_t acc[NBT][MB];
+    f32x4_t acc_eo[EO ? 2 : 1][NBT][MB];
+    auto &acc = acc_eo[0];
 #pragma unroll
-    for (int b = 0; b < NBT; ++b)
+    for (int eo = 0; eo < (EO ? 2 : 1); ++eo)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[b][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < NBT; ++b)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) acc_eo[eo][b][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     // a step covers CW adjacent units: this wavefront's unit of step u is u * CW + cg
     const int k_steps = p.d_in / (128 * CW);                  // d_in % (128 CW) == 0 (host-checked)
@@ -164,8 +174,8 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
                 fa[(chunk >> 4) * A_UNIT + (piece / (16 * CW)) * MFMA_TRS + (chunk & 15)] = areg[i];
         }
     };
-    auto mfma_a = [&](const u32x4_t (&op)[MB][4], int buf, auto sl_tag) {
-        constexpr int SL = decltype(sl_tag)::value;
+    auto mfma_a = [&](const u32x4_t (&op)[MB][4], int buf, auto sl_tag, auto eo_tag) {
+        constexpr int SL = decltype(sl_tag)::value, E = decltype(eo_tag)::value;
         const u32x4_t *fa = reinterpret_cast<const u32x4_t *>(fac + buf * FAC) + cg * A_UNIT;
 #pragma unroll
         for (int s = 0; s < 4; ++s)
@@ -175,8 +185,8 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) {
                     const u32x4_t xo = op[mb][s];
-                    acc[SL * NB + b][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ao), as_bf16x8(xo),
-                                                                                  acc[SL * NB + b][mb], 0, 0, 0);
+                    acc_eo[E][SL * NB + b][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ao), as_bf16x8(xo),
+                                                                                        acc_eo[E][SL * NB + b][mb], 0, 0, 0);
                 }
             }
     };
@@ -195,8 +205,9 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
         // check which requests still exist.
         u32x4_t X[3][MB][4], op[MB][4], areg[SLICES][A_ITERS];
         int par = 0;                                          // LDS buffer of the current step
-        auto trip = [&](auto xi_tag, int u, auto guard_tag) {
-            constexpr int XI = decltype(xi_tag)::value;
+        auto trip = [&](auto ti_tag, int u, auto guard_tag) {   // trip ti of a round: u = ti modulo 3 (and 2, when EO)
+            constexpr int XI = decltype(ti_tag)::value % 3;
+            constexpr std::integral_constant<int, EO ? decltype(ti_tag)::value % 2 : 0> eo_tag{};
             constexpr bool GUARD = decltype(guard_tag)::value;
             const bool has1 = !GUARD || u + 1 < k_steps, has2 = !GUARD || u + 2 < k_steps;
             auto step = [&](auto sl_tag) {
@@ -211,7 +222,7 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
                     if (has2) load_x(X[(XI + 2) % 3], u + 2);
                     unit_to_mfma(X[XI], op);
                 }
-                mfma_a(op, par, sl_tag);
+                mfma_a(op, par, sl_tag, eo_tag);
                 if (SL + 1 < SLICES || has1) publish_a(areg[(SL + 1) % SLICES], par ^ 1);   // step t + 1 exists
                 __syncthreads();                              // the last one: the factor area is reused below
                 par ^= 1;
@@ -232,15 +243,41 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
         publish_a(areg[0], 0);
         __syncthreads();
         int u = 0;
-        for (; u + 5 <= k_steps; u += 3) {                    // steps u .. u + 4 exist
-            trip(b0, u, steady);
-            trip(b1, u + 1, steady);
-            trip(b2, u + 2, steady);
-        }
-        for (; u < k_steps; u += 3) {
-            trip(b0, u, guarded);
-            if (u + 1 < k_steps) trip(b1, u + 1, guarded);
-            if (u + 2 < k_steps) trip(b2, u + 2, guarded);
+        if constexpr (EO) {
+            constexpr std::integral_constant<int, 3> b3{};
+            constexpr std::integral_constant<int, 4> b4{};
+            constexpr std::integral_constant<int, 5> b5{};
+            for (; u + 8 <= k_steps; u += 6) {                // steps u .. u + 7 exist
+                trip(b0, u, steady);
+                trip(b1, u + 1, steady);
+                trip(b2, u + 2, steady);
+                trip(b3, u + 3, steady);
+                trip(b4, u + 4, steady);
+                trip(b5, u + 5, steady);
+            }
+            for (; u < k_steps; u += 6) {
+                trip(b0, u, guarded);
+                if (u + 1 < k_steps) trip(b1, u + 1, guarded);
+                if (u + 2 < k_steps) trip(b2, u + 2, guarded);
+                if (u + 3 < k_steps) trip(b3, u + 3, guarded);
+                if (u + 4 < k_steps) trip(b4, u + 4, guarded);
+                if (u + 5 < k_steps) trip(b5, u + 5, guarded);
+            }
+#pragma unroll
+            for (int b = 0; b < NBT; ++b)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[b][mb] += acc_eo[1][b][mb];
+        } else {
+            for (; u + 5 <= k_steps; u += 3) {                // steps u .. u + 4 exist
+                trip(b0, u, steady);
+                trip(b1, u + 1, steady);
+                trip(b2, u + 2, steady);
+            }
+            for (; u < k_steps; u += 3) {
+                trip(b0, u, guarded);
+                if (u + 1 < k_steps) trip(b1, u + 1, guarded);
+                if (u + 2 < k_steps) trip(b2, u + 2, guarded);
+            }
         }
     }
 
@@ -497,10 +534,10 @@ constexpr int wide_min_waves(int RW, int CW, int SLICES)
     return (RW * CW == 4 && SLICES > 1) ? 2 : 1;
 }
 
-template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false>
+template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false, bool EO = false>
 __global__ __launch_bounds__(RW * CW * 64, wide_min_waves(RW, CW, SLICES)) void mfma_wide_kernel(ApplyArgs p)
 {
-    mfma_wide_body<NB, MB, RW, CW, DIREFT, SLICES, ZOUT, ODD>(p);
+    mfma_wide_body<NB, MB, RW, CW, DIREFT, SLICES, ZOUT, ODD, EO>(p);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer

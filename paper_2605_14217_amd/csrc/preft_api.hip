@@ -312,11 +312,10 @@ bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream
         return launch_expand<NB, true>(a, S, SLICES, stream);
     }
     void (*shrink)(ApplyArgs) = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true>;
-    int threads = 256;
-    if constexpr (NB <= 2) {
-        if ((a.d_in % 256) == 0) { shrink = mfma_wide_kernel<NB, 1, 4, 2, false, SLICES, true>; threads = 512; }
+    if constexpr (NB <= 2) {                                // the single launch sums in two column groups then
+        if ((a.d_in % 256) == 0) shrink = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, false, true>;
     }
-    hipLaunchKernelGGL(shrink, dim3(chunk_grid(a, S, 64)), dim3(threads), 0, stream, a);
+    hipLaunchKernelGGL(shrink, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
     return launch_expand<NB, false>(a, S, SLICES, stream);
 }
 
