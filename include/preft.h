@@ -197,7 +197,7 @@ int preft_schedule(void *workspace, size_t workspace_bytes,
  * a few points below their neighbours), with one exception: a rank above 16 that is not a multiple
  * of 4 needs d_in and d_out to be multiples of 128 for that, and takes the slow per-row kernels
  * otherwise (an adapter of such a rank and such widths is served faster when its factors are
- * zero-padded to the next multiple of 4).  fp32 takes the per-row kernels.
+ * zero-padded to the next multiple of 4).  fp32 runs on the matrix cores too (fp32 products and sums).
  * Unless mode carries PREFT_SCHEDULE_READY the call first runs the scheduler into
  * `workspace` (>= preft_workspace_bytes(T, S) bytes).
  * T == 0 or S == 0 returns PREFT_OK without launching.

@@ -4,6 +4,7 @@
 
 #include "common.hpp"
 #include "expand_kernel.hpp"
+#include "f32_kernel.hpp"
 #include "mfma_kernel.hpp"
 #include "mfma_wide_kernel.hpp"
 #include "row_kernel.hpp"
@@ -628,11 +629,40 @@ void launch_rows(const ApplyArgs &a, int64_t S, bool chunks_too, hipStream_t str
     hipLaunchKernelGGL(short_kernel, dim3((unsigned)g, a.n_layers), dim3(ROW_THREADS), 0, stream, a);
 }
 
-enum class Path { Rows, Valu, Mfma };
-
-Path choose_path(int dtype, int rank, bool widths_128, const Knobs &k)
+// fp32: 8 wavefronts per 16-row tile; out of place, col_split workgroups per tile
+template <int NB, bool DIREFT>
+void launch_f32_nb(const ApplyArgs &a, int64_t S, hipStream_t stream)
 {
-    if (dtype != PREFT_BF16 || k.variant == 1) return Path::Rows;
+    void (*kernel)(ApplyArgs);
+    if constexpr (DIREFT) {
+        if (a.h_layers) kernel = (a.rank % 4) ? f32_tile_layers_kernel<NB, true> : f32_tile_layers_kernel<NB, false>;
+        else            kernel = (a.rank % 4) ? f32_tile_kernel<NB, true, true> : f32_tile_kernel<NB, true, false>;
+    } else {
+        kernel = (a.rank % 4) ? f32_tile_kernel<NB, false, true> : f32_tile_kernel<NB, false, false>;
+    }
+    hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, 16), a.n_layers), dim3(F32_WAVES * 64), 0, stream, a);
+}
+
+// Workgroups per tile out of place (rank 16, 4096 -> 4096, 1 / 2 / 4 / 8 of them): 300 rows 26 / 21 / 17 / 16 us, 2304
+// rows 34 / 40 / 47 / 75 (144 tiles keep the chip busy, and every further workgroup repeats the shrink).
+template <bool DIREFT>
+void launch_f32(ApplyArgs a, int64_t S, const Knobs &k, hipStream_t stream)
+{
+    if (!DIREFT) a.col_split = k.colsplit ? k.colsplit : a.T <= 512 ? 8 : a.T <= 1024 ? 4 : 1;
+    if (a.rank <= 16)      launch_f32_nb<1, DIREFT>(a, S, stream);
+    else if (a.rank <= 32) launch_f32_nb<2, DIREFT>(a, S, stream);
+    else if (a.rank <= 64) launch_f32_nb<4, DIREFT>(a, S, stream);
+    else                   launch_f32_nb<8, DIREFT>(a, S, stream);
+}
+
+enum class Path { Rows, Valu, Mfma, F32 };
+
+Path choose_path(int dtype, int32_t T, int rank, bool widths_128, bool narrow, const Knobs &k)
+{
+    if (k.variant == 1) return Path::Rows;
+    // fp32: a handful of rows at rank 1-4 has no use for the matrix cores (rank 1, 5 rows of 4872, in place: per-row
+    // kernel 15 us, tile kernel 24; rank 8, 32 rows of 4096: 26 and 21; rank 16, 2304 rows: 82 and 29)
+    if (dtype != PREFT_BF16) return narrow && (rank > 4 || T > 64) ? Path::F32 : Path::Rows;
     // matrix-core kernels: multiples of 4, every rank from 5 to 16 (the any-rank shape of the column-split
     // kernel) and, widths being multiples of 128, every rank above (the any-rank form of the row-split
     // kernel); ranks 1..3 are a vector-ALU matter
@@ -647,7 +677,11 @@ Path choose_path(int dtype, int rank, bool widths_128, const Knobs &k)
 template <bool DIREFT>
 int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipStream_t stream)
 {
-    switch (choose_path(dtype, a.rank, wide_widths_ok(a, 1), k)) {
+    const bool narrow = a.d_in <= (1 << 22) && a.d_out <= (1 << 22);     // byte offsets within a factor fit 32 bits
+    switch (choose_path(dtype, a.T, a.rank, wide_widths_ok(a, 1), narrow, k)) {
+    case Path::F32:
+        launch_f32<DIREFT>(a, S, k, stream);
+        break;
     case Path::Mfma: {                     // the tile kernels take chunks and gathered tiles alike
         ApplyArgs b = a;
         if (!DIREFT) b.col_split = choose_col_split(a.T, k);
