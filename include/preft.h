@@ -92,10 +92,10 @@ enum {
  *                            (any non-zero value also makes DiReFT stream its tile instead
  *                            of holding it in registers)
  *   PREFT_TEST_ROWBLOCKS(b)  MFMA kernels: 16-row blocks per wavefront: 0 = automatic, 1 or 2
- *   PREFT_TEST_COLSPLIT(c)   LoRA, MFMA column-split kernel: workgroups that share a tile, each
- *                            writing its share of the output columns: 0 = automatic (4 for
- *                            batches of up to 1024 rows, else 1), or 1..15.  Together with
- *                            variant 4 it names the column groups of the row-split kernel
+ *   PREFT_TEST_COLSPLIT(c)   LoRA, matrix cores: workgroups that share a tile of one output, each writing its share
+ *                            of the output columns (the small-batch kernel): 0 = automatic (that kernel for
+ *                            batches of up to 1024 rows), 1 = the kernels of larger batches, 2..15 (fp32: 1..15).
+ *                            Together with variant 4 it names the column groups of the row-split kernel
  *                            instead: 0 = automatic, 1 or 2
  *   PREFT_TEST_RESIDENT(n)   0 = automatic.  LoRA: 1 = two launches (preft_workspace_bytes_z)
  *                            wherever that form exists, whatever the batch size.  In-place
@@ -221,8 +221,8 @@ int preft_lora_apply(void *y, int64_t ldy, const void *x, int64_t ldx,
  * disjoint column ranges of one buffer (a fused qkv or gate-up output: same row stride, every
  * range inside one row); any other overlap, and any overlap with x, is PREFT_EINVAL.
  * The result is that of n_proj preft_lora_apply calls.  For bf16 and rank 1..16,
- * and for rank 17..64 when every width is a multiple of 128 and the batch has more
- * than 1024 rows, they run as one launch that reads x once; otherwise the call issues one launch per
+ * and for rank 17..64 when every width is a multiple of 128 or the batch has at most
+ * 1024 rows (and the rank is a multiple of 4), they run as one launch that reads x once; otherwise the call issues one launch per
  * projection.
  */
 int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, const int32_t *d_out,

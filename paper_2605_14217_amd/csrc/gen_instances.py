@@ -26,6 +26,8 @@ FAMILIES = {            # kernel template -> (header, rough relative compile cos
     "preft::mfma_wide_layers_kernel": ("mfma_wide_kernel.hpp", 3),
     "preft::f32_tile_kernel": ("f32_kernel.hpp", 2),
     "preft::f32_tile_layers_kernel": ("f32_kernel.hpp", 2),
+    "preft::small_tile_kernel": ("small_kernel.hpp", 3),
+    "preft::small_tile_layers_kernel": ("small_kernel.hpp", 3),
     "preft::mfma_expand_kernel": ("expand_kernel.hpp", 1),
     "preft::mfma_tile_kernel": ("mfma_kernel.hpp", 2),
     "preft::mfma_tile_layers_kernel": ("mfma_kernel.hpp", 2),

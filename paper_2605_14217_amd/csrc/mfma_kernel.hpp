@@ -69,15 +69,13 @@ constexpr int MFMA_TRS = 17;      // LDS row stride of the turn buffer in 16-byt
 // shapes need two workgroups per compute unit so that one streams in while the other streams out.
 constexpr int mfma_min_waves(int NB, int MB, int WAVES, int HUNITS)
 {
-    return (HUNITS > 0 && WAVES == 8 && NB * MB == 1 && HUNITS <= 4) ? 4 : 1;
+    return (HUNITS > 0 && WAVES == 8 && NB * MB == 1 && HUNITS <= 4) ? 4 : (WAVES == 4 && HUNITS == 0 && NB * MB >= 4 && NB <= 4) ? 2 : 1;
 }
 
 // SLICES > 1 (LoRA only): packed projections.  The outputs y_0 .. y_{SLICES-1} are all computed
 // from the same x (q, k, v of an attention block; gate and up of an MLP), each with its own
 // factors of NB rank blocks: one shrink sweep over x feeds SLICES * NB accumulator blocks, then
 // one expand sweep per output.  x is read once instead of SLICES times.
-//
-// COLSPLIT (LoRA only): the small-batch shape, see below.
 //
 // PARTIAL (in place, HUNITS > 0): the wavefront keeps its first HUNITS units and streams the rest in
 // both sweeps -- for tiles too large to hold (32 rows of 8192 elements are the whole register file).
@@ -94,7 +92,7 @@ constexpr int mfma_min_waves(int NB, int MB, int WAVES, int HUNITS)
 //
 // ZOUT: the shrink sweep alone.  z goes to the workspace in the form the expand's MFMAs take it, 1 KB per
 // 16-row block and rank block, and mfma_expand_kernel does the expand in a second launch.
-template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bool COLSPLIT = false, bool PARTIAL = false,
+template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bool PARTIAL = false,
           int ODD = 0, bool ZOUT = false>
 __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 {
@@ -102,12 +100,10 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     static_assert(!ODD || (NB == 1 && !PARTIAL), "the any-rank shape covers rank <= 16");
     static_assert(ODD == 0 || ODD == 2 || ODD == 4, "pieces per lane of a unit's factor block");
     constexpr bool STREAMS = HUNITS == 0 || PARTIAL;         // some units pass through both sweeps
-    static_assert(!COLSPLIT || !DIREFT, "a tile of an in-place call belongs to one workgroup");
-    // x is read a second time by this workgroup (in place without a resident tile) or by the
-    // workgroups that share the tile (small-batch shape): then its loads stay cacheable
-    // (in place, the units the wavefront does not keep: HUNITS names how many of its units stay in
+    // x is read a second time by this workgroup (in place without a resident tile): then its loads stay cacheable
+    // (the units the wavefront does not keep: HUNITS names how many of its units stay in
     // registers; the others are streamed in both sweeps)
-    constexpr bool X_READ_AGAIN = DIREFT || COLSPLIT;
+    constexpr bool X_READ_AGAIN = DIREFT;
     constexpr int R = 16 * MB;
     constexpr int NBT = NB * SLICES;                          // rank blocks of the shrink sweep
     constexpr bool PREFETCH_A = (NBT * MB <= 3);              // register budget
@@ -120,28 +116,10 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     __shared__ u32x4_t turn[WAVES][MB * 16 * MFMA_TRS];       // wavefront-private turn buffers: activations
     __shared__ u32x4_t turn_a[WAVES][16 * MFMA_TRS];          // ... and one rank block of the factor
 
-    // Small batches (LoRA): col_split workgroups share a tile.  Each runs the whole shrink sweep
-    // (the tile's x and the factor come from L2 after the first) and expands its own share of
-    // the output columns, so that a step of a few dozen rows is spread over the chip instead
-    // of walking every column in one workgroup.  Never in place: another workgroup's writes
-    // must not meet this one's reads.
     if (!schedule_matches(p)) return;
-    const int csplit = COLSPLIT ? p.col_split : 1;
-    int n_chunk_units, cslice = 0;
+    int n_chunk_units;
     const int n_units = tile_units<R>(p, &n_chunk_units);
-    int unit;
-    if constexpr (COLSPLIT) {
-        // the workgroups that share a tile sit side by side on one XCD (workgroup ids are dealt round-robin
-        // to the 8 XCDs), so that all but the first of them find the tile's x in that XCD's L2
-        const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-        const int per_xcd = (n_units + 7) >> 3;
-        const int t = j / csplit;
-        cslice = j - t * csplit;
-        unit = t < per_xcd ? xcd * per_xcd + t : -1;
-        if (unit >= n_units) unit = -1;
-    } else {
-        unit = xcd_unit(n_units);
-    }
+    const int unit = xcd_unit(n_units);
     if (unit < 0) return;
     if constexpr (ZOUT) {
         if (unit >= p.z_blocks) return;                       // only tables whose segments overlap list that many tiles
@@ -352,12 +330,9 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     u32x4_t y_early[MB][4];
     u32x2_t w_early[4][2][NB];
     if constexpr (EARLY_UNIT) {
-        const int c_units = p.d_out >> 7;
-        const int ubase = c_units * cslice / csplit;
-        const int n_cu = c_units * (cslice + 1) / csplit - ubase;
-        if (n_cu > wave) {
+        if ((p.d_out >> 7) > wave) {
             const int64_t ldy_b = p.ldy * 2;
-            const int64_t off = (int64_t)(ubase + wave) * 256;
+            const int64_t off = (int64_t)wave * 256;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 y_early[0][i] = ld16_stream(as_global(p.y) + row_u[0][i] * ldy_b + c16 * 16 + off);
@@ -370,7 +345,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
                 for (int s = 0; s < 4; ++s)
 #pragma unroll
                     for (int e = 0; e < 2; ++e)
-                        w_early[s][e][0] = ld8(w0p + (int64_t)4 * e * r * 2 + ((ubase + wave) * 4 + s) * w_step);
+                        w_early[s][e][0] = ld8(w0p + (int64_t)4 * e * r * 2 + (wave * 4 + s) * w_step);
             }
         }
     }
@@ -488,13 +463,9 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     gcptr_t Bt = as_global(slice_Bt<SL>(p)[adapter]);
     const int d_out = slice_d_out<SL>(p);
     const int64_t ldy_b = slice_ldy<SL>(p) * 2;
-    // this workgroup's share of the output: whole units [ubase, ubase + n_cu), and the tail
-    // steps of an odd width if it has the last share
     const int c_units = d_out >> 7;
-    const int ubase = c_units * cslice / csplit;
-    const int n_cu = c_units * (cslice + 1) / csplit - ubase;
-    const int c_per = (n_cu + WAVES - 1) / WAVES;
-    auto c_unit = [&](int u) { return ubase + (CONTIG ? wave * c_per + u : wave + u * WAVES); };
+    const int c_per = (c_units + WAVES - 1) / WAVES;
+    auto c_unit = [&](int u) { return CONTIG ? wave * c_per + u : wave + u * WAVES; };
     gptr_t yu[MB][4];             // unit order
     gptr_t ys[MB];                // step order
 #pragma unroll
@@ -600,8 +571,8 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
             for (int i = 0; i < 4; ++i) st16_stream(yu[mb][i] + off, tr[(mb * 16 + 4 * i + q) * MFMA_TRS + c16]);
     };
 
-    const int my_cu = CONTIG ? max(0, min(c_per, n_cu - wave * c_per)) : (n_cu > wave ? (n_cu - wave + WAVES - 1) / WAVES : 0);
-    const int c_steps = cslice == csplit - 1 ? (d_out + 31) >> 5 : 0;
+    const int my_cu = CONTIG ? max(0, min(c_per, c_units - wave * c_per)) : (c_units > wave ? (c_units - wave + WAVES - 1) / WAVES : 0);
+    const int c_steps = (d_out + 31) >> 5;
     const int c_tail_step = c_units * 4 + wave;
 
     // streamed units first (in place these are second reads: the sooner after the first the better),
@@ -700,11 +671,11 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     if constexpr (SLICES > 2) expand_slice(std::integral_constant<int, 2>{});
 }
 
-template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bool COLSPLIT = false, bool PARTIAL = false,
+template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bool PARTIAL = false,
           int ODD = 0, bool ZOUT = false>
 __global__ __launch_bounds__(WAVES * 64, mfma_min_waves(NB, MB, WAVES, HUNITS)) void mfma_tile_kernel(ApplyArgs p)
 {
-    mfma_tile_body<NB, MB, WAVES, HUNITS, DIREFT, SLICES, COLSPLIT, PARTIAL, ODD, ZOUT>(p);
+    mfma_tile_body<NB, MB, WAVES, HUNITS, DIREFT, SLICES, PARTIAL, ODD, ZOUT>(p);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer
@@ -712,7 +683,7 @@ template <int NB, int MB, int WAVES, int HUNITS, bool PARTIAL = false, int ODD =
 __global__ __launch_bounds__(WAVES * 64, mfma_min_waves(NB, MB, WAVES, HUNITS)) void mfma_tile_layers_kernel(ApplyArgs p)
 {
     select_layer(p);
-    mfma_tile_body<NB, MB, WAVES, HUNITS, true, 1, false, PARTIAL, ODD>(p);
+    mfma_tile_body<NB, MB, WAVES, HUNITS, true, 1, PARTIAL, ODD>(p);
 }
 
 }  // namespace preft

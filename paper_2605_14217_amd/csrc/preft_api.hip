@@ -9,6 +9,7 @@
 #include "mfma_wide_kernel.hpp"
 #include "row_kernel.hpp"
 #include "schedule.hpp"
+#include "small_kernel.hpp"
 #include "valu_kernel.hpp"
 // most kernel instantiations are compiled in instances/group_*.hip (see gen_instances.py), in parallel
 #ifndef PREFT_NO_EXTERN_KERNELS
@@ -16,6 +17,7 @@
 #endif
 
 #include <mutex>
+
 
 static_assert(preft::PREFT_MAX_RANK_DEV == PREFT_MAX_RANK, "device and public rank limits differ");
 
@@ -143,22 +145,96 @@ inline unsigned tile_grid(const ApplyArgs &a, int64_t S, int rows)
     if (!a.gathered_only) units += chunk_capacity(a.T, S) * (CHUNK_ROWS / rows);
     return (unsigned)(((units + 7) / 8) * 8 * (a.col_split > 1 ? a.col_split : 1));
 }
-// Workgroups per tile for the LoRA column-split kernel: a batch of a few hundred rows has too
-// few tiles to occupy the chip, and one workgroup per tile would walk every output column alone.
-inline int choose_col_split(int32_t T, const Knobs &k)
+// Small batches take a kernel of their own (small_kernel.hpp).
+// How many 16-row tiles a small batch is likely to have: rows / 16, and a partial tile for every second segment or adapter.
+inline int64_t likely_tiles(const ApplyArgs &a, int64_t S) { return a.T / 16 + (S < a.N ? S : a.N) / 2 + 1; }
+
+constexpr int32_t SMALL_T = 1024;
+constexpr int64_t DEEP_WGS = 200;                             // at most one workgroup per compute unit, with room for a poor estimate
+
+inline bool takes_small(const ApplyArgs &a, int64_t S, bool direft, const Knobs &k)
 {
-    if (k.colsplit && k.variant != 4) return k.colsplit;      // with variant 4 the knob names the row-split kernel's column groups
-    return T <= 1024 ? 4 : 1;
+    if (a.rank < 4 || ((a.rank % 4) && a.rank > 16) || a.d_in > (1 << 22)) return false;
+    if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
+    if (!direft && k.colsplit) return k.colsplit > 1;
+    if (a.T > SMALL_T) return false;
+    if (!direft) return true;
+    // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 32
+    // rows: 10.0 and 10.6 us, 1000 rows 11.4 and 13.1; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
+    // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81; 8 layers of 1000 rows, rank 32: 54 and 69)
+    if (likely_tiles(a, S) * a.n_layers > DEEP_WGS) return false;
+    return a.rank > 16 || ((a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048);
 }
 
-// the small-batch shape of the column-split kernel (col_split > 1): one shape per rank class
-template <int NB, int SLICES, int PIECES = 0>
-void launch_mfma_colsplit(const ApplyArgs &a, int64_t S, hipStream_t stream)
+// What a workgroup of the small-batch kernel is (out of place): the units of 128 columns it expands, and whether it has
+// the compute unit to itself.  One unit for every wavefront as long as that makes at most about one workgroup per
+// compute unit; beyond, the repeated shrink sweeps cost more than the shorter expand gains.  Measured (us, 64 or 65
+// tiles, rank 16): 5 adapters, 4096 -> 4096: 8 units, shallow 13.7, 16 units, deep 11.6; 64 adapters (512 decode
+// rows): 11.8 and 17.5 -- there every workgroup brings factors of its own from memory, and two on a compute unit hide
+// each other's trips; 4096 -> 2 x 14336: up to 640 shallow workgroups 33.6 / 36.5, up to 300 36.0 / 29.5.  Above rank 32
+// there are no registers for two on a compute unit: deep, with 4 wavefronts where many adapters meet more
+// than a workgroup per compute unit (rank 64, 4096 -> 4096, 512 decode rows: 8 wavefronts 30.9, 4 wavefronts 23.6; 1000 rows of
+// 5 adapters 29.0 / 30.8).
+struct SmallShape { int units; bool deep; int waves; };
+
+inline SmallShape small_shape(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
 {
-    constexpr int WAVES = NB >= 4 ? 4 : 8;                 // register budget
-    hipLaunchKernelGGL((mfma_tile_kernel<NB, 1, WAVES, 0, false, SLICES, true, false, PIECES>), dim3(tile_grid(a, S, 16)),
-                       dim3(WAVES * 64), 0, stream, a);
+    int most = 0, d[3] = {a.d_out, n_slices > 1 ? a.more[0].d_out : 0, n_slices > 2 ? a.more[1].d_out : 0};
+    for (int i = 0; i < n_slices; ++i) { d[i] = (d[i] + 127) / 128; if (d[i] > most) most = d[i]; }
+    if (k.colsplit) return {(most + k.colsplit - 1) / k.colsplit, true, SMALL_WAVES};
+    const int64_t tiles = likely_tiles(a, S);
+    auto workgroups = [&](int units) {
+        int64_t shares = 0;
+        for (int i = 0; i < n_slices; ++i) shares += (d[i] + units - 1) / units;
+        return tiles * shares;
+    };
+    // mostly short segments, and enough adapters for most tiles to have one of their own
+    const bool many_adapters = a.T < 16 * S && 32 * (S < a.N ? S : (int64_t)a.N) > a.T;
+    if (a.rank > 32) {
+        const int waves = many_adapters && workgroups(SMALL_WAVES) > DEEP_WGS ? 4 : SMALL_WAVES;
+        for (int units = SMALL_WAVES; units <= 16 * SMALL_WAVES; units *= 2)
+            if (workgroups(units) <= 288) return {units, true, waves};
+        return {16 * SMALL_WAVES, true, waves};
+    }
+    for (int units = SMALL_WAVES; units <= (many_adapters ? 1 : 4) * SMALL_WAVES; units *= 2)
+        if (workgroups(units) <= DEEP_WGS) return {units, true, SMALL_WAVES};
+    for (int units = SMALL_WAVES; units <= 8 * SMALL_WAVES; units *= 2)
+        if (workgroups(units) <= (many_adapters ? 300 : 640)) return {units, false, SMALL_WAVES};
+    return {8 * SMALL_WAVES, false, SMALL_WAVES};
 }
+
+template <int NB, bool DIREFT, bool ODD>
+void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
+{
+    const unsigned tiles = tile_grid(a, S, 16);               // col_split is 1 here
+    if constexpr (DIREFT) {
+        void (*kernel)(ApplyArgs, int) = small_tile_kernel<NB, true, ODD, true>;
+        if (a.h_layers) kernel = small_tile_layers_kernel<NB, ODD>;
+        hipLaunchKernelGGL(kernel, dim3(tiles, a.n_layers), dim3(SMALL_WAVES * 64), 0, stream, a, 1);
+    } else {
+        const SmallShape shape = small_shape(a, S, n_slices, k);
+        const int cols = 128 * shape.units;
+        int64_t shares = (a.d_out + cols - 1) / cols;
+        for (int i = 1; i < n_slices; ++i) shares += (a.more[i - 1].d_out + cols - 1) / cols;
+        a.col_split = shape.units;
+        void (*kernel)(ApplyArgs, int) = small_tile_kernel<NB, false, ODD, true>;
+        if constexpr (NB <= 2) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false>; }
+        if constexpr (NB > 2) { if (shape.waves == 4) kernel = small_tile_kernel<NB, false, ODD, true, 4>; }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * shares)), dim3(shape.waves * 64), 0, stream, a, n_slices);
+    }
+}
+
+// ranks 4..128 in multiples of 4, and every rank from 5 to 15
+template <bool DIREFT>
+void launch_small(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
+{
+    if (a.rank % 4)        launch_small_shape<1, DIREFT, true>(a, S, n_slices, k, stream);
+    else if (a.rank <= 16) launch_small_shape<1, DIREFT, false>(a, S, n_slices, k, stream);
+    else if (a.rank <= 32) launch_small_shape<2, DIREFT, false>(a, S, n_slices, k, stream);
+    else if (a.rank <= 64) launch_small_shape<4, DIREFT, false>(a, S, n_slices, k, stream);
+    else                   launch_small_shape<8, DIREFT, false>(a, S, n_slices, k, stream);
+}
+
 // the row-split kernel takes whole chunks only
 inline unsigned chunk_grid(const ApplyArgs &a, int64_t S, int rows)
 {
@@ -170,7 +246,7 @@ inline unsigned chunk_grid(const ApplyArgs &a, int64_t S, int rows)
 template <int NB, int MB, int WAVES, int HUNITS>
 void launch_mfma_partial(const ApplyArgs &a, int64_t S, hipStream_t stream)
 {
-    void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, MB, WAVES, HUNITS, true, 1, false, true>;
+    void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, MB, WAVES, HUNITS, true, 1, true>;
     if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, MB, WAVES, HUNITS, true>;
     hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, 16 * MB), a.n_layers), dim3(WAVES * 64), 0, stream, a);
 }
@@ -327,11 +403,11 @@ bool launch_mfma_split16(const ApplyArgs &a, int64_t S, const Knobs &k, hipStrea
     constexpr int WAVES = SLICES == 3 ? 4 : 8;
     if (!wants_split(a, S, SLICES, k)) return false;
     if (a.rank % 4) {
-        hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, false, 2, true>), dim3(tile_grid(a, S, 16)),
+        hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, 2, true>), dim3(tile_grid(a, S, 16)),
                            dim3(WAVES * 64), 0, stream, a);
         return launch_expand<1, true>(a, S, SLICES, stream);
     }
-    hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, false, 0, true>), dim3(tile_grid(a, S, 16)),
+    hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, 0, true>), dim3(tile_grid(a, S, 16)),
                        dim3(WAVES * 64), 0, stream, a);
     return launch_expand<1, false>(a, S, SLICES, stream);
 }
@@ -398,10 +474,6 @@ void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t s
         if constexpr (NB == 1) {
             if (k.variant == 0 && launch_mfma_split16<1>(a, S, k, stream)) return;
         }
-        if (a.col_split > 1) {
-            launch_mfma_colsplit<NB, 1>(a, S, stream);
-            return;
-        }
     }
     if (k.variant != 3 && launch_mfma_wide<NB, DIREFT>(a, S, wide_mb, wide_waves, wide_cw, k, stream)) {
         // the row-split kernel shares one adapter's factors among the 128 rows of a chunk;
@@ -420,18 +492,14 @@ template <int SLICES, int PIECES = 0>
 void launch_mfma_packed(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
     if (k.variant == 0 && launch_mfma_split16<SLICES>(a, S, k, stream)) return;
-    if (a.col_split > 1) {
-        launch_mfma_colsplit<1, SLICES, PIECES>(a, S, stream);
-        return;
-    }
     // three outputs: 4 wavefronts per tile leave room for two workgroups per compute unit (measured
     // better on small and large batches); two outputs: as for a single projection
     const int waves = k.waves ? (k.waves == 8 ? 8 : 4) : (SLICES == 2 ? 8 : 4);
     if (waves == 8)
-        hipLaunchKernelGGL((mfma_tile_kernel<1, 1, 8, 0, false, SLICES, false, false, PIECES>), dim3(tile_grid(a, S, 16)),
+        hipLaunchKernelGGL((mfma_tile_kernel<1, 1, 8, 0, false, SLICES, false, PIECES>), dim3(tile_grid(a, S, 16)),
                            dim3(512), 0, stream, a);
     else
-        hipLaunchKernelGGL((mfma_tile_kernel<1, 1, 4, 0, false, SLICES, false, false, PIECES>), dim3(tile_grid(a, S, 16)),
+        hipLaunchKernelGGL((mfma_tile_kernel<1, 1, 4, 0, false, SLICES, false, PIECES>), dim3(tile_grid(a, S, 16)),
                            dim3(256), 0, stream, a);
 }
 
@@ -493,16 +561,15 @@ void launch_mfma_odd_pieces(const ApplyArgs &a, int64_t S, hipStream_t stream)
         const int units = (a.d_in >> 7) + ((a.d_in & 127) ? 1 : 0);
         const bool L = a.h_layers != nullptr;
         if (units <= 32) {
-            kernel = L ? mfma_tile_layers_kernel<1, 1, 4, 8, false, PIECES> : mfma_tile_kernel<1, 1, 4, 8, true, 1, false, false, PIECES>;
+            kernel = L ? mfma_tile_layers_kernel<1, 1, 4, 8, false, PIECES> : mfma_tile_kernel<1, 1, 4, 8, true, 1, false, PIECES>;
             waves = 4;
         } else if (units <= 64) {
-            kernel = L ? mfma_tile_layers_kernel<1, 1, 8, 8, false, PIECES> : mfma_tile_kernel<1, 1, 8, 8, true, 1, false, false, PIECES>;
+            kernel = L ? mfma_tile_layers_kernel<1, 1, 8, 8, false, PIECES> : mfma_tile_kernel<1, 1, 8, 8, true, 1, false, PIECES>;
         } else {
-            kernel = L ? mfma_tile_layers_kernel<1, 1, 8, 0, false, PIECES> : mfma_tile_kernel<1, 1, 8, 0, true, 1, false, false, PIECES>;
+            kernel = L ? mfma_tile_layers_kernel<1, 1, 8, 0, false, PIECES> : mfma_tile_kernel<1, 1, 8, 0, true, 1, false, PIECES>;
         }
     } else {
-        kernel = a.col_split > 1 ? mfma_tile_kernel<1, 1, 8, 0, false, 1, true, false, PIECES>
-                                 : mfma_tile_kernel<1, 1, 8, 0, false, 1, false, false, PIECES>;
+        kernel = mfma_tile_kernel<1, 1, 8, 0, false, 1, false, PIECES>;
     }
     hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, 16), a.n_layers), dim3(waves * 64), 0, stream, a);
 }
@@ -683,9 +750,8 @@ int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipSt
         launch_f32<DIREFT>(a, S, k, stream);
         break;
     case Path::Mfma: {                     // the tile kernels take chunks and gathered tiles alike
-        ApplyArgs b = a;
-        if (!DIREFT) b.col_split = choose_col_split(a.T, k);
-        launch_mfma_rank<DIREFT>(b, S, k, stream);
+        if (takes_small(a, S, DIREFT, k)) launch_small<DIREFT>(a, S, 1, k, stream);
+        else                           launch_mfma_rank<DIREFT>(a, S, k, stream);
         break;
     }
     case Path::Valu:
@@ -864,9 +930,13 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
                             (k.waves == 0 || k.waves == 4);
     bool fused_wide = n_proj > 1 && dtype == PREFT_BF16 && rank > 16 && rank <= 64 &&
                       (k.variant == 0 || k.variant == 4 || k.variant == 5) && k.waves == 0 && k.rowblocks == 0 && (d_in % 128) == 0 &&
-                      choose_col_split(T, k) == 1;
+                      (k.colsplit ? k.colsplit == 1 || k.variant == 4 : T > SMALL_T);
     for (int32_t i = 0; i < n_proj && fused_wide; ++i) fused_wide = (d_out[i] % 128) == 0;
-    const bool fused = fused_mfma || fused_valu || fused_wide;
+    ApplyArgs a;
+    bind_schedule(a, workspace, T, S, N, mode);
+    a.x = x; a.ldx = ldx; a.d_in = d_in; a.rank = rank;
+    const bool fused_small = n_proj > 1 && dtype == PREFT_BF16 && takes_small(a, S, false, k);
+    const bool fused = fused_small || fused_mfma || fused_valu || fused_wide;
     if (!fused) {                                  // same result, one launch per projection
         for (int32_t i = 0; i < n_proj; ++i) {
             rc = preft_lora_apply(y[i], ldy[i], x, ldx, T, d_in, d_out[i], seg_start, seg_adapter, seg_prefill_len, S,
@@ -875,20 +945,19 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
         }
         return PREFT_OK;
     }
-    ApplyArgs a;
-    bind_schedule(a, workspace, T, S, N, mode);
-    a.y = y[0]; a.x = x; a.ldy = ldy[0]; a.ldx = ldx; a.d_in = d_in; a.d_out = d_out[0];
-    a.A_pool = A_pools[0]; a.Bt_pool = B_pools[0]; a.bias_pool = nullptr; a.rank = rank; a.scale = scale;
+    a.y = y[0]; a.ldy = ldy[0]; a.d_out = d_out[0];
+    a.A_pool = A_pools[0]; a.Bt_pool = B_pools[0]; a.bias_pool = nullptr; a.scale = scale;
     bind_z(a, workspace, bytes, T, S, rank, n_proj);
     for (int32_t i = 1; i < n_proj; ++i) {
         a.more[i - 1].y = y[i]; a.more[i - 1].ldy = ldy[i]; a.more[i - 1].d_out = d_out[i];
         a.more[i - 1].A_pool = A_pools[i]; a.more[i - 1].Bt_pool = B_pools[i];
     }
-    if (fused_wide) {
+    if (fused_small) {
+        launch_small<false>(a, S, n_proj, k, st);
+    } else if (fused_wide) {
         if (rank <= 32) launch_mfma_wide_packed<2>(a, n_proj, S, k, st);
         else            launch_mfma_wide_packed<4>(a, n_proj, S, k, st);
     } else if (fused_mfma) {
-        a.col_split = choose_col_split(T, k);
         const int pieces = (rank % 4) == 0 ? 0 : rank < 8 ? 2 : 4;      // the any-rank shape's block pieces per lane
         if (n_proj == 2) {
             if (pieces == 0)      launch_mfma_packed<2>(a, S, k, st);

@@ -1,0 +1,310 @@
+// Small batches (bf16, matrix cores): a step of a few dozen to about a thousand rows has a handful of 16-row tiles, and
+// what counts is the chain of dependent trips to memory from launch to last store, not bytes.
+//
+// A workgroup of 8 wavefronts takes one 16-row tile and, out of place, one share of the columns of one output: it
+// runs the whole shrink sweep of that output (the tile's x and the factor come from L2 after the first workgroup) and
+// expands its share.  Packed outputs are separate workgroups: sharing x between them would put their expand sweeps
+// behind one another.  In place a tile belongs to one workgroup (another's writes must not meet its reads).
+// The trips: launch arguments; schedule header; tile; adapter pointers; up to BATCH units of x and of the factor
+// per wavefront, all requested at once; and, requested before the cross-wavefront sum of z, the first DEPTH units of
+// y and its factors.  Operand layouts and the order of every sum as in mfma_tile_kernel.
+// Against the shape before (four workgroups per tile, each shrinking every output, two units in flight, the expand
+// requested after the sum; one launch per output above rank 16): q+k+v 4096 -> 4096 + 2 x 1024 as a replayed graph, rank 16: 32
+// decode rows 14.5 -> 9.0 us, a 1000-row batch 27.6 -> 14.7; rank 64: 49 -> 21, 75 -> 45; 4096 -> 4096 rank 16: 8.1 -> 7.5, 15.9 -> 11.6.
+#pragma once
+#include "common.hpp"
+#include "mfma_kernel.hpp"
+
+namespace preft {
+
+constexpr int SMALL_WAVES = 8;
+
+// DEEP: few workgroups, each alone on its compute unit: up to 256 registers for requests in flight.  Otherwise 128, two
+// workgroups per compute unit, which hide one another's trips.
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
+__device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices)
+{
+    // units of the shrink and of the expand sweep in flight (registers)
+    constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : NB == 1 ? 2 : 1;
+    constexpr int DEPTH = DEEP ? (NB == 1 ? (ODD ? 2 : 4) : NB == 2 ? 2 : 1) : 1;
+    static_assert(!ODD || NB == 1, "the any-rank form covers rank <= 16");
+    constexpr bool W_LATE = NB > 4;                           // factors of the expand step by step (registers)
+    static_assert(DEEP || NB <= 2, "128 registers do not hold a unit of more rank blocks");
+    constexpr int PIECES = 4;                                 // any-rank form: 16-byte pieces of a unit's factor block per lane
+    __shared__ u32x4_t turn[WAVES][2][16 * MFMA_TRS];         // activations, and the factor
+    __shared__ float red[WAVES * NB * 4 * 64];
+
+    if (!schedule_matches(p)) return;
+    // the workgroups of a tile: shares of the first output, then those of the others; side by side on one XCD
+    const int per_share = p.col_split;                        // units of a share
+    auto shares_of = [&](int d) { return ((d + 127) / 128 + per_share - 1) / per_share; };
+    const int sh0 = DIREFT ? 1 : shares_of(p.d_out);
+    const int sh1 = !DIREFT && n_slices > 1 ? shares_of(p.more[0].d_out) : 0;
+    const int sh2 = !DIREFT && n_slices > 2 ? shares_of(p.more[1].d_out) : 0;
+    const int shares = sh0 + sh1 + sh2;
+    int n_chunk_units;
+    const int n_units = tile_units<16>(p, &n_chunk_units);
+    const int per_xcd = (n_units + 7) >> 3;
+    const int t = (blockIdx.x >> 3) / shares;
+    int share = (blockIdx.x >> 3) - t * shares;
+    const int unit = (blockIdx.x & 7) * per_xcd + t;
+    if (t >= per_xcd || unit >= n_units) return;
+
+    // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
+    const bool gathered = unit >= n_chunk_units;
+    const int row0 = gathered ? 0 : unit % (CHUNK_ROWS / 16) * 16;
+    const i32x4_t entry = *reinterpret_cast<const PREFT_CONST i32x4_t *>(
+        gathered ? as_const(p.gtiles) + (unit - n_chunk_units) : as_const(p.chunks) + unit / (CHUNK_ROWS / 16));
+    const int n_rows = min(16, entry[2] - row0);
+    if (n_rows <= 0) return;                                  // uniform over the workgroup
+
+    int sl = 0;
+    void *y = p.y;
+    int64_t ldy = p.ldy;
+    int d_out = p.d_out;
+    const void *const *A_pool = p.A_pool, *const *Bt_pool = p.Bt_pool;
+    if (share >= sh0) {
+        sl = share >= sh0 + sh1 ? 2 : 1;
+        share -= sl == 2 ? sh0 + sh1 : sh0;
+        y = p.more[sl - 1].y; ldy = p.more[sl - 1].ldy; d_out = p.more[sl - 1].d_out;
+        A_pool = p.more[sl - 1].A_pool; Bt_pool = p.more[sl - 1].Bt_pool;
+    }
+    gcptr_t A = as_global(as_const(A_pool)[entry[0]]);
+    gcptr_t Bt = as_global(as_const(Bt_pool)[entry[0]]);
+
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int rl = lane & 15, g = lane >> 4;                  // MFMA order
+    const int q = lane >> 4, c16 = lane & 15;                 // unit load order
+    const int r = p.rank;
+    u32x4_t *tr = turn[wave][0], *tra = turn[wave][1];
+
+    // row slots past the tile alias its last row: same loads, same values; their stores are left out
+    int32_t row[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) row[i] = entry[1] + row0 + min(4 * i + q, n_rows - 1);
+    if (gathered) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) row[i] = p.shorts[row[i]].y;
+    }
+    gcptr_t xu[4];
+    gptr_t yu[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        xu[i] = as_global(p.x) + row[i] * p.ldx * 2;
+        yu[i] = as_global(y) + row[i] * ldy * 2;
+    }
+
+    // ---------------------------------------------------------------- shrink
+    f32x4_t acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    {
+        const int x_last = p.d_in * 2 - 16;                   // a row's last 16-byte piece; d_in % 8 == 0
+        const int k_units = (p.d_in + 127) >> 7;
+        auto load_a = [&](u32x4_t (&a)[4], int b, int off) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)                       // ranks past r alias the last one: their z is zeroed
+                a[i] = ld16(A + (uint32_t)(min(16 * b + 4 * i + q, r - 1) * (x_last + 16) + off));
+        };
+        // two halves of a batch take turns: one is on its way while the other is used
+        constexpr int HALVES = BATCH > 1 ? 2 : 1, H = BATCH / HALVES;
+        u32x4_t xr[HALVES][H][4], ar[HALVES][H][NB][4];
+        auto request = [&](u32x4_t (&x)[H][4], u32x4_t (&a)[H][NB][4], int u0) {
+#pragma unroll
+            for (int k = 0; k < H; ++k)
+                if (u0 + k * WAVES < k_units) {
+                    const int off = min((u0 + k * WAVES) * 256 + c16 * 16, x_last);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[k][i] = ld16(xu[i] + off);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) load_a(a[k][b], b, off);
+                }
+        };
+        auto use = [&](u32x4_t (&x)[H][4], u32x4_t (&a)[H][NB][4], int u0) {
+#pragma unroll
+            for (int k = 0; k < H; ++k)
+                if (u0 + k * WAVES < k_units) {
+                    if ((u0 + k * WAVES) * 256 + c16 * 16 > x_last) {    // past the width: zero times zero
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            x[k][i] = u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+                            for (int b = 0; b < NB; ++b) a[k][b][i] = u32x4_t{0u, 0u, 0u, 0u};
+                        }
+                    }
+                    u32x4_t xo[4], ao[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = x[k][i];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) xo[s] = tr[rl * MFMA_TRS + 4 * s + g];
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) tra[(4 * i + q) * MFMA_TRS + c16] = a[k][b][i];
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) ao[s] = tra[rl * MFMA_TRS + 4 * s + g];
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+                            acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ao[s]), as_bf16x8(xo[s]), acc[b], 0, 0, 0);
+                    }
+                }
+        };
+        if constexpr (HALVES == 2) {
+            request(xr[0], ar[0], wave);
+            request(xr[1], ar[1], wave + H * WAVES);
+            int u = wave;
+            for (; u + 2 * H * WAVES < k_units; u += 2 * H * WAVES) {
+                use(xr[0], ar[0], u);
+                request(xr[0], ar[0], u + 2 * H * WAVES);
+                use(xr[1], ar[1], u + H * WAVES);
+                request(xr[1], ar[1], u + 3 * H * WAVES);
+            }
+            use(xr[0], ar[0], u);
+            use(xr[1], ar[1], u + H * WAVES);
+        } else {
+            for (int u = wave; u < k_units; u += H * WAVES) {
+                request(xr[0], ar[0], u);
+                use(xr[0], ar[0], u);
+            }
+        }
+    }
+
+    // ---------------------------------------------------------------- first units of the expand
+    const int c_units = (d_out + 127) >> 7;
+    const int ubase = DIREFT ? 0 : share * per_share, uend = DIREFT ? c_units : min(ubase + per_share, c_units);
+    const int y_last = d_out * 2 - 16;
+    u32x4_t Y[DEPTH][4];
+    u32x2_t W[DEPTH][W_LATE ? 1 : 4][2][NB];
+    u32x4_t Wb[ODD ? DEPTH : 1][PIECES];
+    auto load_w = [&](u32x2_t (&w)[2][NB], int u, int s) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            // MFMA e of step s: columns 32 s + 8 (m / 4) + 4 e + m % 4 (past the width: the last one; not stored)
+            const int col = min(u * 128 + 32 * s + 8 * (rl >> 2) + 4 * e + (rl & 3), d_out - 1);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int rank0 = 16 * b + 4 * g;
+                w[e][b] = ld8(Bt + ((int64_t)col * r + (rank0 < r ? rank0 : 0)) * 2);
+            }
+        }
+    };
+    auto load_yw = [&](int k, int u) {
+        const int off = min(u * 256 + c16 * 16, y_last);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Y[k][i] = ld16(yu[i] + off);
+        if constexpr (ODD) {                                  // the unit's [128 columns][r] block, contiguous
+            const int last = (d_out - u * 128) * r / 8 - 1;
+#pragma unroll
+            for (int j = 0; j < PIECES; ++j) Wb[k][j] = ld16(Bt + (int64_t)u * 256 * r + min(min(lane + 64 * j, 16 * r - 1), last) * 16);
+        } else if constexpr (!W_LATE) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) load_w(W[k][s], u, s);
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < DEPTH; ++k)
+        if (ubase + wave + k * WAVES < uend) load_yw(k, ubase + wave + k * WAVES);
+
+    // ---------------------------------------------------------------- sum over the wavefronts, z -> expand operand
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[((wave * NB + b) * 4 + v) * 64 + lane] = acc[b][v];
+    __syncthreads();                                          // also: every read of the tile precedes every write (in place: a unit belongs to one wavefront)
+    bf16x8_t zop[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int rank0 = 16 * b + 4 * g;
+        gcptr_t bias = DIREFT ? bias_of(p, entry[0]) : nullptr;
+        float zv[4], rem[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) s += red[((w * NB + b) * 4 + v) * 64 + lane];
+            float add = 0.f;
+            if (DIREFT && bias && rank0 + v < r) add = Elem<bf16_tag>::load1(bias, rank0 + v);
+            zv[v] = rank0 + v < r ? (s + add) * p.scale : 0.f;
+            rem[v] = zv[v] - __uint_as_float((pack_bf16(zv[v], 0.f) & 0xffffu) << 16);
+        }
+        zop[b] = as_bf16x8(u32x4_t{pack_bf16(zv[0], zv[1]), pack_bf16(zv[2], zv[3]), pack_bf16(rem[0], rem[1]), pack_bf16(rem[2], rem[3])});
+    }
+
+    // ---------------------------------------------------------------- expand
+    // any-rank form: this lane's factors of step 0, column 8 (rl / 4) + rl % 4 in the parked block, and which of
+    // its four ranks exist (see mfma_tile_kernel)
+    const int odd_at = (8 * (rl >> 2) + (rl & 3)) * r + 4 * g, odd_n = r - 4 * g;
+    const uint32_t *odd_words = reinterpret_cast<const uint32_t *>(tra) + ((odd_n > 0 ? odd_at : 0) >> 1);
+    const uint32_t odd_shift = (odd_at & 1) * 16;
+    const uint32_t odd_m01 = odd_n >= 2 ? 0xffffffffu : odd_n == 1 ? 0xffffu : 0u;
+    const uint32_t odd_m23 = odd_n >= 4 ? 0xffffffffu : odd_n == 3 ? 0xffffu : 0u;
+    auto finish = [&](int k, int u) {
+        u32x4_t yo[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[k][i];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) yo[s] = tr[rl * MFMA_TRS + 4 * s + g];
+        if constexpr (ODD) {
+#pragma unroll
+            for (int j = 0; j < PIECES; ++j)
+                if (lane + 64 * j < 16 * r) tra[lane + 64 * j] = Wb[k][j];
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if constexpr (W_LATE) load_w(W[0][0], u, s);
+            float out[8];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                f32x4_t d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    u32x2_t w;
+                    if constexpr (ODD) {
+                        const uint32_t *w3 = odd_words + (16 * s + 2 * e) * r;
+                        const uint32_t d0 = w3[0], d1 = w3[1], d2 = w3[2];
+                        w = u32x2_t{__builtin_amdgcn_alignbit(d1, d0, odd_shift) & odd_m01, __builtin_amdgcn_alignbit(d2, d1, odd_shift) & odd_m23};
+                    } else {
+                        w = W[k][W_LATE ? 0 : s][e][b];
+                    }
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), zop[b], d, 0, 0, 0);
+                }
+                const uint32_t y01 = yo[s][2 * e], y23 = yo[s][2 * e + 1];
+                out[4 * e + 0] = bf16_lo(y01) + d[0];
+                out[4 * e + 1] = bf16_hi(y01) + d[1];
+                out[4 * e + 2] = bf16_lo(y23) + d[2];
+                out[4 * e + 3] = bf16_hi(y23) + d[3];
+            }
+            tr[rl * MFMA_TRS + 4 * s + g] = Elem<bf16_tag>::pack(out);
+        }
+        const int off = u * 256 + c16 * 16;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const u32x4_t o = tr[(4 * i + q) * MFMA_TRS + c16];
+            if (off <= y_last && 4 * i + q < n_rows) st16_stream(yu[i] + off, o);
+        }
+    };
+    for (int u = ubase + wave; u < uend; u += WAVES * DEPTH) {
+#pragma unroll
+        for (int k = 0; k < DEPTH; ++k)
+            if (u + k * WAVES < uend) {
+                finish(k, u + k * WAVES);
+                if (u + (k + DEPTH) * WAVES < uend) load_yw(k, u + (k + DEPTH) * WAVES);
+            }
+    }
+}
+
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES = SMALL_WAVES>
+__global__ __launch_bounds__(WAVES * 64, DEEP ? 2 : 4) void small_tile_kernel(ApplyArgs p, int n_slices)
+{
+    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES>(p, n_slices);
+}
+
+// the same for one of several residual streams (in-place calls): blockIdx.y is the layer
+template <int NB, bool ODD>
+__global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(ApplyArgs p, int n_slices)
+{
+    select_layer(p);
+    small_tile_body<NB, true, ODD, true, SMALL_WAVES>(p, n_slices);
+}
+
+}  // namespace preft
