@@ -163,7 +163,8 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, bool direft, const Knobs 
     // rows: 10.0 and 10.6 us, 1000 rows 11.4 and 13.1; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
     // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81; 8 layers of 1000 rows, rank 32: 54 and 69)
     if (likely_tiles(a, S) * a.n_layers > DEEP_WGS) return false;
-    return a.rank > 16 || ((a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048);
+    if (a.rank > 16) return a.rank <= 64;                     // above, its registers spill: rank 128, d = 6320, 77 rows 123 and 130 us
+    return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
 }
 
 // What a workgroup of the small-batch kernel is (out of place): the units of 128 columns it expands, and whether it has
@@ -224,7 +225,7 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
     }
 }
 
-// ranks 4..128 in multiples of 4, and every rank from 5 to 15
+// ranks 4..128 (in place 4..64) in multiples of 4, and every rank from 5 to 15
 template <bool DIREFT>
 void launch_small(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
 {
@@ -232,7 +233,7 @@ void launch_small(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, h
     else if (a.rank <= 16) launch_small_shape<1, DIREFT, false>(a, S, n_slices, k, stream);
     else if (a.rank <= 32) launch_small_shape<2, DIREFT, false>(a, S, n_slices, k, stream);
     else if (a.rank <= 64) launch_small_shape<4, DIREFT, false>(a, S, n_slices, k, stream);
-    else                   launch_small_shape<8, DIREFT, false>(a, S, n_slices, k, stream);
+    else if constexpr (!DIREFT) launch_small_shape<8, false, false>(a, S, n_slices, k, stream);
 }
 
 // the row-split kernel takes whole chunks only
