@@ -371,6 +371,12 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     if (!a.zws || (k.variant != 0 && k.variant != 4) || k.waves || k.rowblocks || k.colsplit) return false;
     if (k.resident == 1) return true;
     if (a.T <= 1024) return false;
+    // 352 814 rows of the 70B layer's shapes, one launch -> two, us: rank 64 q+k+v 4878 -> 5537, o 3648 -> 3936, gate+up
+    // 18 408 -> 19 585 (the single launch has tiles enough, and its shrink hides behind other workgroups' expand); rank 1
+    // q+k+v 3359 -> 3558, but o 2999 -> 2711, gate+up 16 868 -> 14 177, down 5604 -> 4841; rank 16 and 32 faster or even throughout
+    // Rank 64, 60 000 rows: 8192 -> 2 x 28672 3166 -> 3242, 8192 -> 8192 596 -> 602, q+k+v 851 -> 894; 37 000 rows: 518 -> 454 (8192 -> 8192).
+    if (a.rank > 32 && a.T > 49152) return false;
+    if (a.rank < 4 && n_slices == 3 && a.T > 131072) return false;
     if (a.rank > 16) return true;
     if (a.all_tokens && a.T < 8 * S) return false;
     int64_t width = a.d_out;
