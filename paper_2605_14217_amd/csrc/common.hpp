@@ -65,6 +65,15 @@ __host__ __device__ inline int64_t gtile_capacity(int64_t T, int64_t S, int64_t 
     return c < rows ? c : rows;
 }
 
+// z area of a LoRA call whose sweeps run as two launches: for every 16-row block, output and rank block of 16 that
+// the rank really has, 64 pieces of 16 bytes, one per lane.  What the shrink kernels write, what the expand kernel reads and
+// what the host reserves all come from these two: the kernels carry padded rank blocks (4 at rank 33..48), the area does not.
+__host__ __device__ constexpr int z_rank_blocks(int rank) { return (rank + 15) / 16; }
+__host__ __device__ constexpr int64_t z_piece(int64_t block, int n_slices, int slice, int rank_blocks, int b)
+{
+    return ((block * n_slices + slice) * rank_blocks + b) * 64;
+}
+
 // ---------------------------------------------------------------------------------------
 // bf16 <-> fp32
 // ---------------------------------------------------------------------------------------

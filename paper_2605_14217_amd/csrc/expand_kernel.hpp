@@ -2,7 +2,7 @@
 //
 // A ZOUT launch of mfma_tile_kernel or mfma_wide_kernel has left z in the workspace in the form the MFMAs
 // below take it (scaled, split into bf16 head and remainder): 1 KB per 16-row block, output and rank block of
-// 16; lane l of a wavefront holds the 16-byte piece l (ranks 4 (l / 16) .. + 3 of row l % 16).
+// 16 (z_piece); lane l of a wavefront holds the 16-byte piece l (ranks 4 (l / 16) .. + 3 of row l % 16).
 //
 // Bound: HBM (y once in, once out).  What decides how much of it a kernel gets is the order in which the chip
 // walks the rows.  Measured with kernels that only move the bytes (read and write y, 89 600 rows of 28 672 bf16):
@@ -122,12 +122,17 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
 #pragma unroll
         for (int s = 0; s < AHEAD; ++s) load_w(s);
         bf16x8_t zop[MB][NB];
-        gcptr_t zb = as_global(p.zws) + ((block0 * n_slices + sl) * NB * 64 + lane) * 16;
+        const int rank_blocks = NB < 4 ? NB : z_rank_blocks(r);              // 33..48: the fourth block is padding, z = 0
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const int m = mb * 16 < n_rows ? mb : 0;          // row blocks past the tile: any z will do
+            gcptr_t zb = as_global(p.zws) + (z_piece(block0 + m, n_slices, sl, rank_blocks, 0) + lane) * 16;
 #pragma unroll
-            for (int b = 0; b < NB; ++b) zop[mb][b] = as_bf16x8(ld16(zb + (m * n_slices * NB + b) * 1024));
+            for (int b = 0; b < NB; ++b) {
+                u32x4_t zv = {0u, 0u, 0u, 0u};
+                if (NB < 4 || b < 3 || rank_blocks > b) zv = ld16(zb + b * 1024);
+                zop[mb][b] = as_bf16x8(zv);
+            }
         }
         // where the pieces land in LDS: two 8-byte halves, neither straddles a column (multiples of 4)
         int w_dst[NB][2];

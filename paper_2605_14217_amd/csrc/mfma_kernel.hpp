@@ -433,10 +433,11 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     }
 
     if constexpr (ZOUT) {                                     // every wavefront holds the same z: they share the writing
-        u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + (int64_t)unit * (NBT * 64) + lane;
+        static_assert(NB == 1, "one rank block per output");
+        u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + lane;
 #pragma unroll
         for (int b = 0; b < NBT; ++b)
-            if (b % WAVES == wave) zw[b * 64] = as_u32x4(zop[b][0]);
+            if (b % WAVES == wave) zw[z_piece(unit, SLICES, b, 1, 0)] = as_u32x4(zop[b][0]);
         return;
     }
 

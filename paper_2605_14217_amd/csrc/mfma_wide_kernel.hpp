@@ -53,7 +53,7 @@ constexpr int wide_lds_bytes(int NB, int MB, int RW, int CW)
 //
 // ZOUT (LoRA only): the shrink sweep alone.  z, already in the form the expand's MFMAs take it (scaled,
 // split into bf16 head and remainder, in lane order), goes to the z area of the workspace, 1 KB per
-// 16-row block and rank block, and mfma_expand_kernel does the expand in a second launch.
+// 16-row block and rank block that exists (z_piece), and mfma_expand_kernel does the expand in a second launch.
 //
 // EO (ZOUT only): even and odd units are summed apart and added at the end, as the two column groups of the
 // single launch do, so that both forms give the same bits.  The read-only sweep itself is faster without column
@@ -350,9 +350,13 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
     if constexpr (ZOUT) {
         if (cg == 0) {                                        // with column groups every one of them holds the same z
             const int64_t blk16 = (int64_t)(unit_id / TPC) * (CHUNK_ROWS / 16) + tile_row0 / 16 + rb;
-            u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + blk16 * (NBT * 64) + lane;
+            const int rank_blocks = NB < 4 ? NB : z_rank_blocks(r);          // 33..48: the fourth block is padding and has no room
+            u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + lane;
+            if (blk16 < p.z_blocks) {                         // the list is cut to its capacity, so this always holds
 #pragma unroll
-            for (int b = 0; b < NBT; ++b) zw[b * 64] = as_u32x4(zop[b][0]);
+                for (int b = 0; b < NBT; ++b)
+                    if (b % NB < rank_blocks) zw[z_piece(blk16, SLICES, b / NB, rank_blocks, b % NB)] = as_u32x4(zop[b][0]);
+            }
         }
         return;
     }

@@ -65,12 +65,11 @@ size_t workspace_bytes(int64_t T, int64_t S)
            (size_t)short_capacity(T, S) * (sizeof(int4) + sizeof(int2));
 }
 
-// z area (LoRA calls whose sweeps run as two launches): after the schedule, 1 KB per 16-row block of
-// a chunk and rank block of 16
+// z area (LoRA calls whose sweeps run as two launches): after the schedule, the pieces of every 16-row block of a chunk
 size_t z_offset(int64_t T, int64_t S) { return (workspace_bytes(T, S) + 255) & ~(size_t)255; }
 size_t z_bytes(int64_t T, int64_t S, int rank, int n_proj)
 {
-    return (size_t)chunk_capacity(T, S) * (CHUNK_ROWS / 16) * (size_t)(((rank + 15) / 16) * n_proj) * 1024;
+    return (size_t)z_piece(chunk_capacity(T, S) * (CHUNK_ROWS / 16), n_proj, 0, z_rank_blocks(rank), 0) * 16;
 }
 
 ScheduleView view_of(void *workspace, int64_t T, int64_t S)
