@@ -74,6 +74,14 @@ __host__ __device__ constexpr int64_t z_piece(int64_t block, int n_slices, int s
     return ((block * n_slices + slice) * rank_blocks + b) * 64;
 }
 
+// Last 16-byte piece of the [columns][rank] bf16 factor block that starts `columns` columns before a matrix' end and of which
+// a wavefront reads at most `most` columns.  (All the columns that are left, times the rank, would not fit 32 bits:
+// 2^25 columns at rank 64.)
+__host__ __device__ constexpr int last_factor_piece(int columns, int most, int rank)
+{
+    return (columns < most ? columns : most) * rank / 8 - 1;
+}
+
 // ---------------------------------------------------------------------------------------
 // bf16 <-> fp32
 // ---------------------------------------------------------------------------------------

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
         // factors of the 32 columns of step s: 4 r contiguous 16-byte pieces, of which this lane takes lane + 64 j
         // (lanes past them the last one)
         gcptr_t Wp = as_global(as_const(Bt_pool)[entry.x]) + (int64_t)c0 * r * 2;
-        const int w_last = (d_out - c0) * r / 8 - 1;          // last piece that exists, from column c0 on
+        const int w_last = last_factor_piece(d_out - c0, 128, r);            // last piece that exists, from column c0 on
         constexpr int AHEAD = NB >= 4 ? 2 : 4;                // register budget
         u32x4_t W[4][NB];
         auto load_w = [&](int s) {

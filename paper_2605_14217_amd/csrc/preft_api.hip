@@ -151,9 +151,11 @@ inline int64_t likely_tiles(const ApplyArgs &a, int64_t S) { return a.T / 16 + (
 constexpr int32_t SMALL_T = 1024;
 constexpr int64_t DEEP_WGS = 200;                             // at most one workgroup per compute unit, with room for a poor estimate
 
-inline bool takes_small(const ApplyArgs &a, int64_t S, bool direft, const Knobs &k)
+// `widest`: columns of the widest output
+inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool direft, const Knobs &k)
 {
-    if (a.rank < 4 || ((a.rank % 4) && a.rank > 16) || a.d_in > (1 << 22)) return false;
+    if (a.rank < 4 || ((a.rank % 4) && a.rank > 16)) return false;
+    if (a.d_in > (1 << 22) || widest > (1 << 22)) return false;          // offsets within a row or a factor, and the launch, fit 32 bits
     if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
     if (!direft && k.colsplit) return k.colsplit > 1;
     if (a.T > SMALL_T) return false;
@@ -321,28 +323,21 @@ inline bool wide_widths_ok(const ApplyArgs &a, int cw)
     return (a.d_in % m) == 0 && (a.d_out % m) == 0;
 }
 
-// the expand launch of a call whose z is in the workspace: a workgroup per 16 MB rows x 512 columns
-template <int NB, int MB, bool ODD>
-bool launch_expand_shape(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
+// The expand launch of a call whose z is in the workspace: a workgroup per 32 rows x 512 columns.
+constexpr int EXPAND_MB = 2;
+
+inline int64_t expand_panels(const ApplyArgs &a, int n_slices)
 {
-    constexpr int COLS = EXPAND_WAVES * 128;
+    constexpr int64_t COLS = EXPAND_WAVES * 128;
     int64_t panels = (a.d_out + COLS - 1) / COLS;
     for (int i = 1; i < n_slices; ++i) panels += (a.more[i - 1].d_out + COLS - 1) / COLS;
-    // more tiles than the batch's rows fill are likely to be empty: the kernel strides over what exceeds the grid
-    const int64_t bound = tile_grid(a, S, 16 * MB), likely = (int64_t)a.T / (16 * MB) * 5 / 4 + 64;
-    if (bound * panels >= ((int64_t)1 << 31)) return false;
-    hipLaunchKernelGGL((mfma_expand_kernel<NB, MB, ODD>), dim3((unsigned)((bound < likely ? bound : likely) * panels)),
-                       dim3(EXPAND_WAVES * 64), 0, stream, a, n_slices);
-    return true;
+    return panels;
 }
 
-bool rows_off_lines(const ApplyArgs &a, int n_slices);
-
-template <int NB, bool ODD>
-bool launch_expand(ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
+// the kernel numbers its tiles in 32 bits
+inline bool expand_ids_fit(const ApplyArgs &a, int64_t S, int n_slices)
 {
-    a.xcd_runs = rows_off_lines(a, n_slices);
-    return launch_expand_shape<NB, 2, ODD>(a, S, n_slices, stream);
+    return tile_grid(a, S, 16 * EXPAND_MB) * expand_panels(a, n_slices) < ((int64_t)1 << 31);
 }
 
 // Rows that do not start on 128-byte lines: neighbouring panels share lines, so they go to one XCD.
@@ -351,6 +346,18 @@ bool rows_off_lines(const ApplyArgs &a, int n_slices)
     bool off = ((reinterpret_cast<uintptr_t>(a.y) | (uintptr_t)(a.ldy * 2)) & 127) != 0;
     for (int i = 1; i < n_slices; ++i) off = off || ((reinterpret_cast<uintptr_t>(a.more[i - 1].y) | (uintptr_t)(a.more[i - 1].ldy * 2)) & 127) != 0;
     return off;
+}
+
+template <int NB, bool ODD>
+void launch_expand(ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
+{
+    a.xcd_runs = rows_off_lines(a, n_slices);
+    // More tiles than the batch's rows fill are likely to be empty: the kernel strides over what exceeds the grid (and over
+    // what would exceed the 2^32 work items of a launch)
+    const int64_t bound = tile_grid(a, S, 16 * EXPAND_MB), likely = (int64_t)a.T / (16 * EXPAND_MB) * 5 / 4 + 64;
+    const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices), most = (int64_t)1 << 23;
+    hipLaunchKernelGGL((mfma_expand_kernel<NB, EXPAND_MB, ODD>), dim3((unsigned)(grid < most ? grid : most)), dim3(EXPAND_WAVES * 64), 0,
+                       stream, a, n_slices);
 }
 
 // LoRA with a z area in the workspace: the shrink sweep leaves z there and the expand runs as a launch of its
@@ -368,6 +375,7 @@ bool rows_off_lines(const ApplyArgs &a, int n_slices)
 bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
 {
     if (!a.zws || (k.variant != 0 && k.variant != 4) || k.waves || k.rowblocks || k.colsplit) return false;
+    if (!expand_ids_fit(a, S, n_slices)) return false;
     if (k.resident == 1) return true;
     if (a.T <= 1024) return false;
     // 352 814 rows of the 70B layer's shapes, one launch -> two, us: rank 64 q+k+v 4878 -> 5537, o 3648 -> 3936, gate+up
@@ -392,14 +400,16 @@ bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream
     a.chunks_only = 1;
     if (a.rank % 4) {
         hipLaunchKernelGGL((mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, true>), dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
-        return launch_expand<NB, true>(a, S, SLICES, stream);
+        launch_expand<NB, true>(a, S, SLICES, stream);
+        return true;
     }
     void (*shrink)(ApplyArgs) = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true>;
     if constexpr (NB <= 2) {                                // the single launch sums in two column groups then
         if ((a.d_in % 256) == 0) shrink = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, false, true>;
     }
     hipLaunchKernelGGL(shrink, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
-    return launch_expand<NB, false>(a, S, SLICES, stream);
+    launch_expand<NB, false>(a, S, SLICES, stream);
+    return true;
 }
 
 // rank 1..16: the column-split kernel's shrink sweep, then the expand launch; chunks and gathered tiles alike
@@ -411,11 +421,13 @@ bool launch_mfma_split16(const ApplyArgs &a, int64_t S, const Knobs &k, hipStrea
     if (a.rank % 4) {
         hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, 2, true>), dim3(tile_grid(a, S, 16)),
                            dim3(WAVES * 64), 0, stream, a);
-        return launch_expand<1, true>(a, S, SLICES, stream);
+        launch_expand<1, true>(a, S, SLICES, stream);
+        return true;
     }
     hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, 0, true>), dim3(tile_grid(a, S, 16)),
                        dim3(WAVES * 64), 0, stream, a);
-    return launch_expand<1, false>(a, S, SLICES, stream);
+    launch_expand<1, false>(a, S, SLICES, stream);
+    return true;
 }
 
 template <int NB, bool DIREFT>
@@ -756,7 +768,7 @@ int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipSt
         launch_f32<DIREFT>(a, S, k, stream);
         break;
     case Path::Mfma: {                     // the tile kernels take chunks and gathered tiles alike
-        if (takes_small(a, S, DIREFT, k)) launch_small<DIREFT>(a, S, 1, k, stream);
+        if (takes_small(a, S, a.d_out, DIREFT, k)) launch_small<DIREFT>(a, S, 1, k, stream);
         else                           launch_mfma_rank<DIREFT>(a, S, k, stream);
         break;
     }
@@ -941,7 +953,9 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
     ApplyArgs a;
     bind_schedule(a, workspace, T, S, N, mode);
     a.x = x; a.ldx = ldx; a.d_in = d_in; a.rank = rank;
-    const bool fused_small = n_proj > 1 && dtype == PREFT_BF16 && takes_small(a, S, false, k);
+    int32_t widest = 0;
+    for (int32_t i = 0; i < n_proj; ++i) if (d_out[i] > widest) widest = d_out[i];
+    const bool fused_small = n_proj > 1 && dtype == PREFT_BF16 && takes_small(a, S, widest, false, k);
     const bool fused = fused_small || fused_mfma || fused_valu || fused_wide;
     if (!fused) {                                  // same result, one launch per projection
         for (int32_t i = 0; i < n_proj; ++i) {

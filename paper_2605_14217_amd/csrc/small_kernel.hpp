@@ -193,7 +193,7 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices
 #pragma unroll
         for (int i = 0; i < 4; ++i) Y[k][i] = ld16(yu[i] + off);
         if constexpr (ODD) {                                  // the unit's [128 columns][r] block, contiguous
-            const int last = (d_out - u * 128) * r / 8 - 1;
+            const int last = last_factor_piece(d_out - u * 128, 128, r);
 #pragma unroll
             for (int j = 0; j < PIECES; ++j) Wb[k][j] = ld16(Bt + (int64_t)u * 256 * r + min(min(lane + 64 * j, 16 * r - 1), last) * 16);
         } else if constexpr (!W_LATE) {

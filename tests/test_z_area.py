@@ -1,8 +1,6 @@
 """The z area of a workspace (preft_workspace_bytes_z) holds every piece that a two-launch LoRA call writes: on the
 host, for every rank, from the address function the kernels use; on the GPU, with guard bytes right behind it."""
-import os
 import shutil
-import subprocess
 
 import numpy as np
 import pytest
@@ -11,18 +9,13 @@ import torch
 import paper_2605_14217_amd as preft
 from paper_2605_14217_amd import workloads as wl
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
-def test_the_area_covers_every_piece_the_kernels_write(tmp_path):
-    exe = tmp_path / "z_area"
-    build = subprocess.run(["hipcc", "--cuda-host-only", "-std=c++17", os.path.join(ROOT, "tests", "z_area_driver.hip"), "-o", str(exe)],
-                           capture_output=True, text=True)
-    assert build.returncode == 0, build.stderr
+def test_the_area_covers_every_piece_the_kernels_write(tmp_path_factory):
+    from test_host_rules import ask
     # batches whose chunk list fills its capacity best: few long segments, whole chunks; and segments just above a chunk
     batches = [[2048], [128], [129], [1152], [4096], [1000] * 8, [700] * 50, [5] * 400, [129] * 30, [128] * 16 + [1] * 40]
-    asked, args = [], []
+    asked, lines = [], []
     for lens in batches:
         # whole chunks, the last one up to the 64-row tile that holds its last row; and the gathered tiles (at most one per short segment)
         last = [n for n in lens if n > 4][-1]
@@ -31,8 +24,8 @@ def test_the_area_covers_every_piece_the_kernels_write(tmp_path):
         for rank in range(1, 65):
             for n_proj in (1, 2, 3):
                 asked.append((lens, rank, n_proj))
-                args += [str(blocks + (gathered if rank <= 16 else 0)), str(rank), str(n_proj)]
-    ends = [int(v) for v in subprocess.run([str(exe)] + args, capture_output=True, text=True, check=True).stdout.split()]
+                lines.append(f"z {blocks + (gathered if rank <= 16 else 0)} {rank} {n_proj}")
+    ends = [int(v) for v in ask(tmp_path_factory, lines)]
     assert len(ends) == len(asked)
     for (lens, rank, n_proj), end in zip(asked, ends):
         T, S = sum(lens), len(lens)
