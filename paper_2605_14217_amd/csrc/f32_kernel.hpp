@@ -155,7 +155,9 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int rank0 = 16 * b + 4 * g;
-            if constexpr (ODD) {                              // ranks past r alias the last one: their z is zero
+            // ranks past r: the load aliases one that exists, and the value is masked where it is used (zero times an
+            // infinite factor would not be zero)
+            if constexpr (ODD) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) wr[b][e] = ld4(wc + min(rank0 + e, r - 1) * 4);
             } else {
@@ -209,12 +211,20 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
         for (int s = 0; s < 4; ++s) {
             u32x4_t (&w)[NB] = wr[AHEAD ? s : 0];
             if constexpr (!AHEAD) load_w(w, u, s);
+            auto masked = [&](int b, int e) { return 16 * b + 4 * g + (ODD ? e : 0) < r ? w[b][e] : 0u; };
+            if (NB < 8 && r != 16 * NB) {                     // (8 blocks: where they are used; a second copy of w would spill)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[b][e] = masked(b, e);
+            }
             f32x4_t part[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 part[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int b = 0; b < NB; ++b) part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f(w[b][e]), z[b][e], part[e], 0, 0, 0);
+                for (int b = 0; b < NB; ++b)
+                    part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f(NB < 8 ? w[b][e] : masked(b, e)), z[b][e], part[e], 0, 0, 0);
             }
             const f32x4_t d = (part[0] + part[1]) + (part[2] + part[3]);
             u32x4_t o;
