@@ -33,11 +33,70 @@ constexpr int EXPAND_WAVES = 4;                               // 128-column unit
 // lie as in memory (a lane then shifts its four factors into place and may look one word past them).
 constexpr int expand_fac_bytes(int NB) { return 32 * (32 * NB + 8) + 16; }
 
+// The tiles of an expand launch: column panels (those of the first output, then those of the others) of row blocks, ids in
+// memory order.
+struct ExpandTiles {
+    int pan0, pan1, panels, chunk_tiles;
+    uint32_t n_ids, per_xcd;
+};
+
+template <int R>
+__device__ __forceinline__ ExpandTiles expand_tiles(const ApplyArgs &p, int n_slices)
+{
+    ExpandTiles t;
+    auto panels_of = [](int d) { return (d + EXPAND_WAVES * 128 - 1) / (EXPAND_WAVES * 128); };
+    t.pan0 = panels_of(p.d_out);
+    t.pan1 = n_slices > 1 ? panels_of(p.more[0].d_out) : 0;
+    t.panels = t.pan0 + t.pan1 + (n_slices > 2 ? panels_of(p.more[1].d_out) : 0);
+    const PREFT_CONST int32_t *header = as_const(p.header);
+    t.chunk_tiles = header[HDR_CHUNKS] * (CHUNK_ROWS / R);
+    t.n_ids = (uint32_t)(t.chunk_tiles + (p.chunks_only ? 0 : header[HDR_GTILES])) * (uint32_t)t.panels;     // below 2^31 (host-checked)
+    t.per_xcd = (t.n_ids + 7) >> 3;
+    return t;
+}
+
+// One of them: `n_rows` rows, from row0 of the chunk or gathered tile `entry`; its first block of z; output, and panel of it.
+struct ExpandTile {
+    int4 entry;
+    int row0, n_rows, sl, panel, d_out;
+    int64_t block0, ldy_b;
+    bool gathered;
+    void *y;
+    const void *const *Bt_pool;
+};
+
+template <int R>
+__device__ __forceinline__ bool expand_tile(const ApplyArgs &p, const ExpandTiles &ts, uint32_t slot, ExpandTile &t)
+{
+    constexpr int TPC = CHUNK_ROWS / R, MB = R / 16;
+    const uint32_t id = p.xcd_runs ? (slot & 7) * ts.per_xcd + (slot >> 3) : slot;
+    if (id >= ts.n_ids) return false;
+    const int tile_id = (int)(id / (uint32_t)ts.panels);
+    t.panel = (int)id - tile_id * ts.panels;
+    t.gathered = tile_id >= ts.chunk_tiles;
+    t.row0 = t.gathered ? 0 : tile_id % TPC * R;              // within the chunk
+    t.entry = __builtin_bit_cast(int4, *reinterpret_cast<const PREFT_CONST i32x4_t *>(
+        t.gathered ? as_const(p.gtiles) + (tile_id - ts.chunk_tiles) : as_const(p.chunks) + tile_id / TPC));
+    t.n_rows = min(R, t.entry.z - t.row0);
+    t.block0 = t.gathered ? (int64_t)ts.chunk_tiles * MB + (tile_id - ts.chunk_tiles) : (int64_t)tile_id * MB;
+    if (t.n_rows <= 0 || t.block0 >= p.z_blocks) return false;    // (tables whose segments overlap can list more tiles than z has room for)
+    t.sl = 0;
+    t.y = p.y;
+    t.ldy_b = p.ldy * 2;
+    t.d_out = p.d_out;
+    t.Bt_pool = p.Bt_pool;
+    if (t.panel >= ts.pan0) {
+        t.sl = t.panel >= ts.pan0 + ts.pan1 ? 2 : 1;
+        t.panel -= t.sl == 2 ? ts.pan0 + ts.pan1 : ts.pan0;
+        t.y = p.more[t.sl - 1].y; t.ldy_b = p.more[t.sl - 1].ldy * 2; t.d_out = p.more[t.sl - 1].d_out; t.Bt_pool = p.more[t.sl - 1].Bt_pool;
+    }
+    return true;
+}
+
 template <int NB, int MB, bool ODD>
 __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(ApplyArgs p, int n_slices)
 {
     constexpr int R = 16 * MB;
-    constexpr int TPC = CHUNK_ROWS / R;
     static_assert(CHUNK_ROWS % R == 0, "tile height must divide the chunk height");
     __shared__ u32x4_t turn[EXPAND_WAVES][16 * MFMA_TRS];
     __shared__ __attribute__((aligned(16))) char fac[EXPAND_WAVES][expand_fac_bytes(NB)];
@@ -50,41 +109,16 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
     u32x4_t *tr = turn[wave];
     char *fw = fac[wave];
 
-    // column panels: those of the first output, then those of the others
-    auto panels_of = [](int d) { return (d + EXPAND_WAVES * 128 - 1) / (EXPAND_WAVES * 128); };
-    const int pan0 = panels_of(p.d_out);
-    const int pan1 = n_slices > 1 ? panels_of(p.more[0].d_out) : 0;
-    const int pan2 = n_slices > 2 ? panels_of(p.more[1].d_out) : 0;
-    const int panels = pan0 + pan1 + pan2;
-    const PREFT_CONST int32_t *header = as_const(p.header);
-    const int chunk_tiles = header[HDR_CHUNKS] * TPC;
-    const int n_tiles = chunk_tiles + (p.chunks_only ? 0 : header[HDR_GTILES]);
-    const uint32_t n_ids = (uint32_t)n_tiles * (uint32_t)panels;     // below 2^31 (host-checked)
-
-    const uint32_t per_xcd = (n_ids + 7) >> 3;
-    for (uint32_t slot = blockIdx.x; slot < per_xcd * 8; slot += gridDim.x) {
-        const uint32_t id = p.xcd_runs ? (slot & 7) * per_xcd + (slot >> 3) : slot;
-        if (id >= n_ids) continue;
-        const int tile_id = (int)(id / (uint32_t)panels);
-        int panel = (int)id - tile_id * panels;
-        const bool gathered = tile_id >= chunk_tiles;
-        const int row0 = gathered ? 0 : tile_id % TPC * R;    // within the chunk
-        const int4 entry = __builtin_bit_cast(int4, *reinterpret_cast<const PREFT_CONST i32x4_t *>(
-            gathered ? as_const(p.gtiles) + (tile_id - chunk_tiles) : as_const(p.chunks) + tile_id / TPC));
-        const int n_rows = min(R, entry.z - row0);
-        const int64_t block0 = gathered ? (int64_t)chunk_tiles * MB + (tile_id - chunk_tiles) : (int64_t)tile_id * MB;
-        if (n_rows <= 0 || block0 >= p.z_blocks) continue;    // (tables whose segments overlap can list more tiles than z has room for)
-        int sl = 0;
-        void *y = p.y;
-        int64_t ldy_b = p.ldy * 2;
-        int d_out = p.d_out;
-        const void *const *Bt_pool = p.Bt_pool;
-        if (panel >= pan0) {
-            sl = panel >= pan0 + pan1 ? 2 : 1;
-            panel -= sl == 2 ? pan0 + pan1 : pan0;
-            y = p.more[sl - 1].y; ldy_b = p.more[sl - 1].ldy * 2; d_out = p.more[sl - 1].d_out; Bt_pool = p.more[sl - 1].Bt_pool;
-        }
-        const int c0 = (panel * EXPAND_WAVES + __builtin_amdgcn_readfirstlane(wave)) * 128;   // this wavefront's first column
+    const ExpandTiles tiles = expand_tiles<R>(p, n_slices);
+    for (uint32_t slot = blockIdx.x; slot < tiles.per_xcd * 8; slot += gridDim.x) {
+        ExpandTile t;
+        if (!expand_tile<R>(p, tiles, slot, t)) continue;
+        const int4 entry = t.entry;
+        const int row0 = t.row0, n_rows = t.n_rows, sl = t.sl, d_out = t.d_out;
+        const bool gathered = t.gathered;
+        const int64_t ldy_b = t.ldy_b, block0 = t.block0;
+        const void *const *Bt_pool = t.Bt_pool;
+        const int c0 = (t.panel * EXPAND_WAVES + __builtin_amdgcn_readfirstlane(wave)) * 128;   // this wavefront's first column
         if (c0 >= d_out) continue;
 
         // Every request of the tile at once, none of them conditional on the lane: row slots past the tile alias
@@ -103,7 +137,7 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
                 for (int i = 0; i < 4; ++i) row[mb][i] = p.shorts[row[mb][i]].y;
         }
         u32x4_t Y[MB][4];
-        gptr_t yc = as_global(y) + (int64_t)c0 * 2;           // uniform
+        gptr_t yc = as_global(t.y) + (int64_t)c0 * 2;           // uniform
         const int y_col = (col_ok ? c16 * 8 : d_out - 8 - c0) * 2;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
@@ -214,6 +248,78 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
                 if (col_ok && mb * 16 + 4 * i + q < n_rows) st16_stream(yc + (row[mb][i] * ldy_b + c16 * 16), o);
             }
         }
+    }
+}
+
+// The same for rank 1-3, after a ZOUT launch of valu_tile_kernel: too thin for the matrix cores, and z stays in fp32.  A lane
+// keeps the order its loads come in -- 8 columns of the rows 4 i + q -- so that y needs no turn through LDS; its factors are the
+// RANK 16-byte pieces of those 8 columns, the sums those of valu_tile_kernel: the bits of the single launch.
+template <int RANK, int MB>
+__global__ __launch_bounds__(EXPAND_WAVES * 64) void thin_expand_kernel(ApplyArgs p, int n_slices)
+{
+    constexpr int R = 16 * MB;
+    if (!schedule_matches(p)) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int q = lane >> 4, c16 = lane & 15;                 // unit load order
+    const ExpandTiles tiles = expand_tiles<R>(p, n_slices);
+    for (uint32_t slot = blockIdx.x; slot < tiles.per_xcd * 8; slot += gridDim.x) {
+        ExpandTile t;
+        if (!expand_tile<R>(p, tiles, slot, t)) continue;
+        const int c0 = (t.panel * EXPAND_WAVES + __builtin_amdgcn_readfirstlane(wave)) * 128;   // this wavefront's first column
+        if (c0 >= t.d_out) continue;
+        // row slots past the tile alias its last row, columns past the width the last ones; only the stores are masked
+        int32_t row[MB][4];
+        const bool col_ok = c0 + c16 * 8 < t.d_out;
+        const int col = col_ok ? c16 * 8 : t.d_out - 8 - c0;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) row[mb][i] = t.entry.y + t.row0 + min(mb * 16 + 4 * i + q, t.n_rows - 1);
+        if (t.gathered) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) row[mb][i] = p.shorts[row[mb][i]].y;
+        }
+        gptr_t yc = as_global(t.y) + ((int64_t)c0 + col) * 2;
+        u32x4_t Y[MB][4], raw[RANK], zv[MB][4];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Y[mb][i] = ld16_stream(yc + row[mb][i] * t.ldy_b);
+        gcptr_t wp = as_global(as_const(t.Bt_pool)[t.entry.x]) + ((int64_t)c0 + col) * RANK * 2;
+#pragma unroll
+        for (int j = 0; j < RANK; ++j) raw[j] = ld16(wp + j * 16);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int s = min(mb * 16 + 4 * i + q, t.n_rows - 1);
+                zv[mb][i] = ld16(as_global(p.zws) + (z_piece(t.block0 + s / 16, n_slices, t.sl, 1, 0) + s % 16) * 16);
+            }
+        float w[8 * RANK];
+#pragma unroll
+        for (int j = 0; j < RANK; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                w[j * 8 + 2 * k] = bf16_lo(raw[j][k]);
+                w[j * 8 + 2 * k + 1] = bf16_hi(raw[j][k]);
+            }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float out[8];
+                Elem<bf16_tag>::unpack(Y[mb][i], out);
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    float d = 0.f;
+#pragma unroll
+                    for (int k = 0; k < RANK; ++k) d = fmaf(w[c * RANK + k], __uint_as_float(zv[mb][i][k]), d);
+                    out[c] += d;
+                }
+                if (col_ok && mb * 16 + 4 * i + q < t.n_rows) st16_stream(yc + row[mb][i] * t.ldy_b, Elem<bf16_tag>::pack(out));
+            }
     }
 }
 

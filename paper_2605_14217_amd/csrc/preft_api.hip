@@ -348,16 +348,20 @@ bool rows_off_lines(const ApplyArgs &a, int n_slices)
     return off;
 }
 
-template <int NB, bool ODD>
-void launch_expand(ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
+void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
 {
     a.xcd_runs = rows_off_lines(a, n_slices);
     // More tiles than the batch's rows fill are likely to be empty: the kernel strides over what exceeds the grid (and over
     // what would exceed the 2^32 work items of a launch)
     const int64_t bound = tile_grid(a, S, 16 * EXPAND_MB), likely = (int64_t)a.T / (16 * EXPAND_MB) * 5 / 4 + 64;
     const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices), most = (int64_t)1 << 23;
-    hipLaunchKernelGGL((mfma_expand_kernel<NB, EXPAND_MB, ODD>), dim3((unsigned)(grid < most ? grid : most)), dim3(EXPAND_WAVES * 64), 0,
-                       stream, a, n_slices);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(EXPAND_WAVES * 64), 0, stream, a, n_slices);
+}
+
+template <int NB, bool ODD>
+void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
+{
+    launch_expand_kernel(mfma_expand_kernel<NB, EXPAND_MB, ODD>, a, S, n_slices, stream);
 }
 
 // LoRA with a z area in the workspace: the shrink sweep leaves z there and the expand runs as a launch of its
@@ -365,7 +369,11 @@ void launch_expand(ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
 //   rank 16, 4096 -> 2 x 14336: 1100 rows 67 -> 36 us, 8000 rows 247 -> 181, 37 000 rows 909 -> 789; 4096 -> 4096:
 //     15.3 -> 15.5, 48.6 -> 46.2, 167 -> 159; 500 rows (against four workgroups per tile): 10.9 -> 13.2;
 //     1024 -> 2728 (rows off 128-byte lines): 2000 rows 11.3 -> 13.6, 37 000 rows 114 -> 120; 2000 -> 3208:
-//     15.0 -> 14.4, 154 -> 148.  Ranks 1-15 alike (rank 1, 2 x 14336: 37 000 rows 967 -> 763).
+//     15.0 -> 14.4, 154 -> 148.  Ranks 4-15 alike.
+//   rank 1-3 (vector-ALU kernels), 4096 -> 4096: 1500 rows 13-15 -> 14-16, 11 300 rows 52 -> 52, 42 000 rows 190 -> 170;
+//     4096 -> 2 x 14336: 1500 rows 62-82 -> 39-44, 42 000 rows 1030 -> 864; q+k+v of 8192, 350 000 rows 3556-3676 -> 3218-3407;
+//     1024 -> 1024 + 2 x 512, 140 000 rows 258-265 -> 255-293; rows off 128-byte lines, 1024 -> 2728 10-11 -> 12-13,
+//     2000 -> 3208, 11 200 rows 42-44 -> 50.
 //   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 518 -> 454; rank 32 86 -> 48,
 //     105 -> 97, 355 -> 372.
 //   decode rows alone, 7 per adapter (gathered tiles), rank 16, 8192 -> 8192: 1200 rows 30 -> 35, 3584 rows 89 -> 89;
@@ -378,16 +386,15 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     if (!expand_ids_fit(a, S, n_slices)) return false;
     if (k.resident == 1) return true;
     if (a.T <= 1024) return false;
-    // 352 814 rows of the 70B layer's shapes, one launch -> two, us: rank 64 q+k+v 4878 -> 5537, o 3648 -> 3936, gate+up
-    // 18 408 -> 19 585 (the single launch has tiles enough, and its shrink hides behind other workgroups' expand); rank 1
-    // q+k+v 3359 -> 3558, but o 2999 -> 2711, gate+up 16 868 -> 14 177, down 5604 -> 4841; rank 16 and 32 faster or even throughout
-    // Rank 64, 60 000 rows: 8192 -> 2 x 28672 3166 -> 3242, 8192 -> 8192 596 -> 602, q+k+v 851 -> 894; 37 000 rows: 518 -> 454 (8192 -> 8192).
+    // Rank 64, 352 814 rows of the 70B layer's shapes, one launch -> two, us: q+k+v 4878 -> 5537, o 3648 -> 3936, gate+up
+    // 18 408 -> 19 585 (the single launch has tiles enough, and its shrink hides behind other workgroups' expand); 60 000 rows:
+    // 8192 -> 2 x 28672 3166 -> 3242, 8192 -> 8192 596 -> 602, q+k+v 851 -> 894; 37 000 rows: 518 -> 454 (8192 -> 8192).
     if (a.rank > 32 && a.T > 49152) return false;
-    if (a.rank < 4 && n_slices == 3 && a.T > 131072) return false;
     if (a.rank > 16) return true;
     if (a.all_tokens && a.T < 8 * S) return false;
     int64_t width = a.d_out;
     for (int i = 1; i < n_slices; ++i) width += a.more[i - 1].d_out;
+    if (a.rank < 4) return a.T * width >= 12000000 && width >= 3072 && !rows_off_lines(a, n_slices);
     return a.T * width >= 6000000 && (width >= 3072 || !rows_off_lines(a, n_slices));
 }
 
@@ -412,7 +419,7 @@ bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream
     return true;
 }
 
-// rank 1..16: the column-split kernel's shrink sweep, then the expand launch; chunks and gathered tiles alike
+// rank 4..16: the column-split kernel's shrink sweep, then the expand launch; chunks and gathered tiles alike
 template <int SLICES>
 bool launch_mfma_split16(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
@@ -427,6 +434,24 @@ bool launch_mfma_split16(const ApplyArgs &a, int64_t S, const Knobs &k, hipStrea
     hipLaunchKernelGGL((mfma_tile_kernel<1, 1, WAVES, 0, false, SLICES, false, 0, true>), dim3(tile_grid(a, S, 16)),
                        dim3(WAVES * 64), 0, stream, a);
     launch_expand<1, false>(a, S, SLICES, stream);
+    return true;
+}
+
+// rank 1..3: the vector-ALU kernel's shrink sweep and the expand launch that goes with it
+template <int RANK, int SLICES>
+void launch_valu_split_rank(const ApplyArgs &a, int64_t S, hipStream_t stream)
+{
+    hipLaunchKernelGGL((valu_tile_kernel<RANK, 4, 4, false, SLICES, 0, true>), dim3(tile_grid(a, S, 16)), dim3(256), 0, stream, a);
+    launch_expand_kernel(thin_expand_kernel<RANK, EXPAND_MB>, a, S, SLICES, stream);
+}
+
+template <int SLICES>
+bool launch_valu_split(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
+{
+    if (k.variant != 0 || !wants_split(a, S, SLICES, k)) return false;
+    if (a.rank == 1)      launch_valu_split_rank<1, SLICES>(a, S, stream);
+    else if (a.rank == 2) launch_valu_split_rank<2, SLICES>(a, S, stream);
+    else                  launch_valu_split_rank<3, SLICES>(a, S, stream);
     return true;
 }
 
@@ -774,7 +799,7 @@ int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipSt
     }
     case Path::Valu:
         if constexpr (!DIREFT) {
-            if (k.variant == 0 && launch_mfma_split16<1>(a, S, k, stream)) break;
+            if (a.rank <= 3 && launch_valu_split<1>(a, S, k, stream)) break;
         }
         launch_valu_rank<DIREFT>(a, S, k, stream);
         break;
@@ -989,7 +1014,7 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
             else                  launch_mfma_packed<3, 4>(a, S, k, st);
         }
     } else {
-        if (k.variant == 0 && (n_proj == 2 ? launch_mfma_split16<2>(a, S, k, st) : launch_mfma_split16<3>(a, S, k, st))) return check_launch();
+        if (n_proj == 2 ? launch_valu_split<2>(a, S, k, st) : launch_valu_split<3>(a, S, k, st)) return check_launch();
         if (n_proj == 2) launch_valu_packed<2>(a, S, st);
         else             launch_valu_packed<3>(a, S, st);
     }

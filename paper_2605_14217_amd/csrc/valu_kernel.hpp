@@ -20,6 +20,10 @@
 //
 // SLICES > 1 (LoRA only): packed projections, as in mfma_tile_kernel: the outputs share x, so
 // one shrink sweep feeds SLICES * RANK partial sums per row and one expand sweep per output follows.
+//
+// ZOUT (LoRA only): the shrink sweep alone.  z stays what it is, RANK floats per row: row t of a 16-row tile writes them into
+// piece t of the tile's part of the workspace's z area, and thin_expand_kernel does the expand in a second launch, with the
+// sums of the expand below in their order.
 #pragma once
 #include "common.hpp"
 #include "mfma_kernel.hpp"   // xcd_unit
@@ -34,7 +38,7 @@ __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float acc)
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), acc, false);
 }
 
-template <int RANK, int RB, int WAVES, bool DIREFT, int SLICES = 1, int HV = 0>
+template <int RANK, int RB, int WAVES, bool DIREFT, int SLICES = 1, int HV = 0, bool ZOUT = false>
 __device__ __forceinline__ void valu_tile_body(const ApplyArgs &p)
 {
     constexpr int R = RB * WAVES;
@@ -42,11 +46,15 @@ __device__ __forceinline__ void valu_tile_body(const ApplyArgs &p)
     constexpr int RT = RANK * SLICES;                         // partial sums per row in the shrink sweep
     static_assert(SLICES == 1 || !DIREFT, "packed projections are a LoRA feature");
     static_assert(CHUNK_ROWS % R == 0, "tile height must divide the chunk height");
+    static_assert(!ZOUT || (R == 16 && RANK <= 4 && !DIREFT), "z: one piece per row of a 16-row block");
 
     if (!schedule_matches(p)) return;
     int n_chunk_units;
     const int unit = xcd_unit(tile_units<R>(p, &n_chunk_units));
     if (unit < 0) return;
+    if constexpr (ZOUT) {
+        if (unit >= p.z_blocks) return;                       // only tables whose segments overlap list that many tiles
+    }
     TileRows tile;
     if (!tile_rows<R>(p, unit, n_chunk_units, tile)) return;
     const int adapter = tile.adapter;
@@ -144,6 +152,20 @@ __device__ __forceinline__ void valu_tile_body(const ApplyArgs &p)
         for (int i = 0; i < RB; ++i) z[i][k] = (wave_sum(z[i][k]) + bias) * p.scale;
     }
 
+    if constexpr (ZOUT) {                                     // every lane holds every sum: lane sl * RB + i writes row i of output sl
+        u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + wave_row0;
+#pragma unroll
+        for (int sl = 0; sl < SLICES; ++sl)
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+                u32x4_t v = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int k = 0; k < RANK; ++k) v[k] = __float_as_uint(z[i][sl * RANK + k]);
+                if (lane == sl * RB + i) zw[z_piece(unit, SLICES, sl, 1, 0) + i] = v;
+            }
+        return;
+    }
+
     // ---------------------------------------------------------------- expand (once per output)
     auto expand_slice = [&](auto sl_tag) {
         constexpr int SL = decltype(sl_tag)::value;
@@ -222,10 +244,10 @@ __device__ __forceinline__ void valu_tile_body(const ApplyArgs &p)
     if constexpr (SLICES > 2) expand_slice(std::integral_constant<int, 2>{});
 }
 
-template <int RANK, int RB, int WAVES, bool DIREFT, int SLICES = 1, int HV = 0>
+template <int RANK, int RB, int WAVES, bool DIREFT, int SLICES = 1, int HV = 0, bool ZOUT = false>
 __global__ __launch_bounds__(WAVES * 64) void valu_tile_kernel(ApplyArgs p)
 {
-    valu_tile_body<RANK, RB, WAVES, DIREFT, SLICES, HV>(p);
+    valu_tile_body<RANK, RB, WAVES, DIREFT, SLICES, HV, ZOUT>(p);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer

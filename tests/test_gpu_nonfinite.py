@@ -65,3 +65,13 @@ POISON = ["factor", "nan factor", "row", "first factor"]
 def test_fp32(rank, poison):
     _run("f32", rank, 132, 140, 100, poison)
     _run("f32", rank, 132, 132, 100, poison, direft=True)
+
+
+@pytest.mark.parametrize("poison", POISON)
+@pytest.mark.parametrize("rank", [1, 2, 3])
+def test_bf16_rank_1_to_3_in_two_launches(rank, poison):
+    prev = preft.set_test_flags(preft.test_flags(resident=1))
+    try:
+        _run("bf16", rank, 136, 520, 100, poison, z_rank=rank)
+    finally:
+        preft.set_test_flags(prev)

@@ -1,7 +1,7 @@
 """LoRA as two launches (shrink into the workspace's z area, then the expand in 2-D tiles): every rank class, at the
 edges of its tiles -- 32 rows x 512 columns, 128-column units, 32-column steps -- against the oracle, and bit for
-bit against the single launch where both sum in the same order (rank >= 4; ranks 1-3 otherwise take the vector-ALU
-kernel).  Bars of parity_util: row-wise 1e-2 for bf16 storage."""
+bit against the single launch: how many bytes of workspace a call is handed decides which launches it takes, never what
+it returns.  Bars of parity_util: row-wise 1e-2 for bf16 storage."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # prompts of 1, 15..17, 31..33, 127..129 rows between decode rows, and one empty segment
 LENS = [1, 15, 16, 17, 31, 32, 33, 5, 0, 127, 128, 129, 4, 560] + [1] * 40
 
-CASES = [(1, 512, (512,)), (3, 1000, (520, 8)), (4, 128, (128, 1032, 512)), (5, 264, (640,)), (7, 1000, (2728, 2728)),
+CASES = [(1, 512, (512,)), (1, 136, (1032, 8, 520)), (2, 1096, (2056, 384)), (3, 1000, (520, 8)), (3, 4104, (136, 520, 1024)), (4, 128, (128, 1032, 512)), (5, 264, (640,)), (7, 1000, (2728, 2728)),
          (8, 136, (1544,)), (12, 520, (504, 512)), (16, 4104, (512,)), (16, 512, (1536, 256, 256)), (13, 384, (1288, 24, 512)),
          (17, 128, (128,)), (20, 256, (512, 256)), (31, 384, (512, 128, 256)), (36, 128, (1152,)), (48, 256, (512,)),
          (63, 256, (640, 512)), (64, 128, (128, 1664))]
@@ -61,8 +61,6 @@ def test_two_launches_match_the_oracle_and_the_single_launch(rank, d_in, d_outs,
             want = ora.lora(y0.cpu(), x.cpu(), tab.seg_start, tab.seg_adapter, tab.seg_prefill_len,
                             [a.cpu() for a in pl.A], [b.cpu() for b in pl.B], rank, 2.0, pos)
             compare(y, y0, want, owner, "bf16")
-        # the any-rank shape of the single launch sums 8 partial z also for three outputs
-        if rank >= 4 and not (rank < 16 and rank % 4 and len(d_outs) == 3):
-            one = call(mode, preft.test_flags(variant=5, colsplit=1))
-            for y, y1 in zip(two, one):
-                assert torch.equal(bits(y), bits(y1))
+        one = call(mode, preft.test_flags(variant=5, colsplit=1) if rank >= 4 else preft.test_flags(variant=2))
+        for y, y1 in zip(two, one):
+            assert torch.equal(bits(y), bits(y1))
