@@ -146,7 +146,7 @@ size_t preft_workspace_bytes(int32_t T, int32_t S);
  * handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the expand
  * in 2-D tiles -- where that is faster: wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
  * 1100), and every shape above rank 16 (up to 5x on 1100 rows).  With fewer bytes, or outside those limits,
- * the same call runs as before, with the same result within the rounding of fp32 sums.
+ * the same call runs in one launch.  The result is the same bit for bit.
  * The z area lies behind the schedule and is rewritten by every such call: calls that
  * share a workspace must be ordered on one stream, as they must be for the schedule already.
  * Returns 0 for a negative T or S, a rank outside 1..PREFT_MAX_RANK or n_proj outside

@@ -398,6 +398,14 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     return a.T * width >= 6000000 && (width >= 3072 || !rows_off_lines(a, n_slices));
 }
 
+// Whether the row-split kernel's single launch runs with two column groups at rank 17-32: every width a multiple of 256.
+bool column_groups_fit(const ApplyArgs &a, int n_slices)
+{
+    bool fit = wide_widths_ok(a, 2);
+    for (int i = 1; i < n_slices; ++i) fit = fit && (a.more[i - 1].d_out % 256) == 0;
+    return fit;
+}
+
 // rank 17..64: the row-split kernel's shrink sweep of the chunks, then their expand launch
 template <int NB, int SLICES>
 bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream_t stream)
@@ -411,8 +419,8 @@ bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream
         return true;
     }
     void (*shrink)(ApplyArgs) = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true>;
-    if constexpr (NB <= 2) {                                // the single launch sums in two column groups then
-        if ((a.d_in % 256) == 0) shrink = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, false, true>;
+    if constexpr (NB <= 2) {                                // where the single launch sums in two column groups, so does this one
+        if (column_groups_fit(a, SLICES)) shrink = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, false, true>;
     }
     hipLaunchKernelGGL(shrink, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
     launch_expand<NB, false>(a, S, SLICES, stream);
@@ -572,8 +580,7 @@ void launch_mfma_wide_packed(const ApplyArgs &a, int n_proj, int64_t S, const Kn
         return;
     }
     // two column groups at rank 32 where every width allows it (see launch_mfma_nb)
-    bool cw2 = NB <= 2 && (a.d_in % 256) == 0 && (a.d_out % 256) == 0;
-    for (int i = 1; i < n_proj; ++i) cw2 = cw2 && (a.more[i - 1].d_out % 256) == 0;
+    const bool cw2 = NB <= 2 && column_groups_fit(a, n_proj);
     void (*kernel)(ApplyArgs) = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 1, false, 2> : mfma_wide_kernel<NB, 1, 4, 1, false, 3>;
     if constexpr (NB <= 2) {
         if (cw2) kernel = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 2, false, 2> : mfma_wide_kernel<NB, 1, 4, 2, false, 3>;
