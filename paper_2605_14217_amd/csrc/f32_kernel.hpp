@@ -44,8 +44,8 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
     // workgroups that share a tile sit side by side on one XCD (ids are dealt round-robin to the 8 XCDs)
     const int per_xcd = (n_units + 7) >> 3;
     const int t = (blockIdx.x >> 3) / csplit, cslice = (blockIdx.x >> 3) - t * csplit;
-    const int unit = (blockIdx.x & 7) * per_xcd + t;
-    if (t >= per_xcd || unit >= n_units) return;
+    const int unit = t < per_xcd ? few_tiles_unit(p, n_chunk_units, per_xcd, t) : n_units;
+    if (unit >= n_units) return;
     TileRows tile;
     if (!tile_rows<16>(p, unit, n_chunk_units, tile)) return; // uniform over the workgroup
 

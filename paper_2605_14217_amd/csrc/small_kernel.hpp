@@ -47,8 +47,8 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices
     const int per_xcd = (n_units + 7) >> 3;
     const int t = (blockIdx.x >> 3) / shares;
     int share = (blockIdx.x >> 3) - t * shares;
-    const int unit = (blockIdx.x & 7) * per_xcd + t;
-    if (t >= per_xcd || unit >= n_units) return;
+    const int unit = t < per_xcd ? few_tiles_unit(p, n_chunk_units, per_xcd, t) : n_units;
+    if (unit >= n_units) return;
 
     // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
     const bool gathered = unit >= n_chunk_units;
@@ -72,7 +72,7 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices
     gcptr_t A = as_global(as_const(A_pool)[entry[0]]);
     gcptr_t Bt = as_global(as_const(Bt_pool)[entry[0]]);
 
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int rl = lane & 15, g = lane >> 4;                  // MFMA order
     const int q = lane >> 4, c16 = lane & 15;                 // unit load order
     const int r = p.rank;
