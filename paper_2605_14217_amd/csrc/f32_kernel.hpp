@@ -23,6 +23,8 @@
 #include "common.hpp"
 #include "mfma_kernel.hpp"
 
+#include <type_traits>
+
 namespace preft {
 
 constexpr int F32_WAVES = 8;
@@ -159,7 +161,7 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
             // infinite factor would not be zero)
             if constexpr (ODD) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) wr[b][e] = ld4(wc + min(rank0 + e, r - 1) * 4);
+                for (int e = 0; e < 4; ++e) wr[b][e] = ld4(wc + (b < NB / 2 ? rank0 + e : min(rank0 + e, r - 1)) * 4);     // the first half always exists
             } else {
                 wr[b] = ld16(wc + (rank0 < r ? rank0 : 0) * 4);
             }
@@ -204,6 +206,9 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
     __syncthreads();                                          // the area is the turn buffers again
 
     // ---------------------------------------------------------------- expand
+    uint32_t last_mask[4];                                    // up to rank 32: which of the lane's factors of the last block exist
+#pragma unroll
+    for (int e = 0; e < 4; ++e) last_mask[e] = 16 * (NB - 1) + 4 * g + (ODD ? e : 0) < r ? 0xffffffffu : 0u;
     auto finish = [&](u32x4_t (&yr)[4], u32x4_t (&wr)[NW][NB], int u) {
         u32x4_t yo[4];
         turned(yr, yo, tr);
@@ -214,18 +219,29 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
             auto masked = [&](int b, int e) { return 16 * b + 4 * g + (ODD ? e : 0) < r ? w[b][e] : 0u; };
             if (NB < 8 && r != 16 * NB) {                     // (8 blocks: where they are used; a second copy of w would spill)
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (NB <= 2) {                  // only the last block can be partial
+                        w[NB - 1][e] &= last_mask[e];
+                    } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) w[b][e] = masked(b, e);
+                        for (int b = 0; b < NB; ++b) w[b][e] = masked(b, e);
+                    }
+                }
             }
             f32x4_t part[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                part[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < 4; ++e) part[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            auto products = [&](auto blocks_tag, auto masked_tag) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f(NB < 8 ? w[b][e] : masked(b, e)), z[b][e], part[e], 0, 0, 0);
-            }
+                for (int b = 0; b < decltype(blocks_tag)::value; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f(decltype(masked_tag)::value ? masked(b, e) : w[b][e]), z[b][e], part[e], 0, 0, 0);
+            };
+            if constexpr (NB < 8) products(std::integral_constant<int, NB>{}, std::false_type{});
+            else if (r == 128)    products(std::integral_constant<int, 8>{}, std::false_type{});
+            else if (r == 96)     products(std::integral_constant<int, 6>{}, std::false_type{});
+            else                  products(std::integral_constant<int, NB>{}, std::true_type{});
             const f32x4_t d = (part[0] + part[1]) + (part[2] + part[3]);
             u32x4_t o;
 #pragma unroll

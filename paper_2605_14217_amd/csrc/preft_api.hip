@@ -16,6 +16,7 @@
 #include "instances/extern_kernels.inc"
 #endif
 
+#include <cmath>
 #include <mutex>
 
 
@@ -746,6 +747,58 @@ void launch_rows(const ApplyArgs &a, int64_t S, bool chunks_too, hipStream_t str
     hipLaunchKernelGGL(short_kernel, dim3((unsigned)g, a.n_layers), dim3(ROW_THREADS), 0, stream, a);
 }
 
+// How many of N adapters n segments are expected to name.
+inline int64_t likely_adapters(int64_t n, int64_t N)
+{
+    if (n <= 0 || N <= 0) return 0;
+    return (int64_t)((double)N * -expm1(-(double)n / (double)N) + 0.5);
+}
+
+// How many 16-row tiles a batch is likely to have.  Rows in excess of one per segment belong to prompts: a prompt ends in a
+// partial tile; the other segments, where every position counts, are gathered by adapter, which ends in a partial tile each.
+inline int64_t f32_likely_tiles(const ApplyArgs &a, int64_t S)
+{
+    const int64_t extra = a.T > S ? a.T - S : 0, prompts = S < extra / 16 + 1 ? S : extra / 16 + 1;
+    int64_t singles = a.all_tokens ? (a.T < S ? a.T : S) - (extra ? prompts : 0) : 0;
+    if (singles < 0) singles = 0;
+    const int64_t owners = likely_adapters(singles, a.N), gathered = singles / 16 + owners / 2;
+    return extra / 16 + (extra ? prompts / 2 + 1 : 0) + (gathered > owners ? gathered : owners);
+}
+
+// Whether the per-row kernel is the faster one for an fp32 call.  A workgroup of the tile kernel walks its tile's columns 512 at a
+// time, a trip to memory each, and in place does so alone: few tiles of wide rows wait for that chain (about 2 us per 1000 columns
+// of each sweep).  The per-row kernel has a workgroup for every four rows, about 1 us per 1000 columns at rank 1, 1.8 at rank 4, and is
+// left behind from rank 8 on, at ranks that are no power of two wherever its groups are full (prompts), by batches that fill the
+// chip, and by mixed ones, where it takes its chunks and its gathered rows one after the other.  Measured on three sets of buffers in turn, per-row / tile kernel, us:
+//   in place: rank 1, d = 4872, 65 decode rows 13 / 27, 300 prompt rows 15 / 28, 1080 23 / 31, d = 8192, 4000 78 / 64; 1000 decode rows
+//     of 512 22 / 11, 4 rows of 1024 7 / 9; three prompts of 340 rows and three decode rows, d = 4096, rank 1 33 / 27; rank 4, d = 8192, 100 prompt rows 21 / 38, 500 decode rows 29 / 41; rank 3,
+//     d = 4872, 65 decode rows 0.72 of the tile kernel's time, 300 prompt rows 1.23; rank 5, 16 decode rows 0.64, 65 rows of as many
+//     adapters 0.94; rank 8 1.1 and more.
+//   out of place: rank 1, 8192 -> 1024, 300 prompt rows 0.61, 2048 -> 8192 1.41, 65 decode rows 0.72, 2500 prompt rows 1.03; rank 4,
+//     8192 -> 8192, 500 decode rows 0.86, 1000 1.09, 4872 -> 8192, 65 decode rows 1.1; rank 8, 14336 -> 1024, 16 rows 0.64,
+//     8192 -> 8192 1.9.
+bool f32_rows_win(const ApplyArgs &a, int64_t S, bool direft)
+{
+    const int r = a.rank;
+    const int64_t T = (int64_t)a.T * a.n_layers, tiles = f32_likely_tiles(a, S) * a.n_layers, in = a.d_in, out = a.d_out;
+    const bool prompts = a.T >= 2 * S, mixed = prompts && a.all_tokens && S > 1 + a.T / 256;
+    if (r > 8 || T > 2048 || mixed) return false;
+    if (direft) {
+        if (r <= 2) return in >= 1024;
+        if (r == 4) return in >= 1536 && tiles <= 256 && tiles * 16 <= in;
+        if (r == 3) return !prompts && in >= 1024 && T <= (in >= 4096 ? 512 : 128);
+        return r < 8 && !prompts && in >= 1536 && tiles <= (r == 5 ? 60 : 32);
+    }
+    if (r <= 2 || r == 4) {
+        if ((prompts || in < 1024) && tiles <= 48) return r == 4 ? out < in : out <= in;
+        if (r == 4) return in >= 4096 && (prompts || T <= 768) && (T > 128 || in >= out);
+        return in >= 2048 || out > 2048;
+    }
+    if (prompts) return tiles <= 32 && in >= (r == 3 ? 6 : r == 8 ? 7 : 12) * out;
+    if (r == 3) return 2 * in >= 3 * out && in >= 4096 && tiles <= 200 && T <= 512;
+    return in >= (r == 8 ? 6 : 4) * out && (tiles <= 60 || (r < 8 && in >= 8 * out && tiles <= 200));
+}
+
 // fp32: 8 wavefronts per 16-row tile; out of place, col_split workgroups per tile
 template <int NB, bool DIREFT>
 void launch_f32_nb(const ApplyArgs &a, int64_t S, hipStream_t stream)
@@ -760,12 +813,29 @@ void launch_f32_nb(const ApplyArgs &a, int64_t S, hipStream_t stream)
     hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, 16), a.n_layers), dim3(F32_WAVES * 64), 0, stream, a);
 }
 
-// Workgroups per tile out of place (rank 16, 4096 -> 4096, 1 / 2 / 4 / 8 of them): 300 rows 26 / 21 / 17 / 16 us, 2304
-// rows 34 / 40 / 47 / 75 (144 tiles keep the chip busy, and every further workgroup repeats the shrink).
+// Workgroups per tile out of place, where few tiles leave the chip idle.  Each repeats the shrink; a workgroup takes about 8 us
+// and 1 us for every 512 columns of x, 1.25 us for every 512 columns of its share of y; one fits a compute unit.  (rank 16, 4096 -> 4096, 1 / 2 / 4 / 8 workgroups: 300 rows
+// 26 / 21 / 17 / 16 us, 2304 rows 34 / 40 / 47 / 75; rank 4, 2048 -> 8192, 500 decode rows of 64 adapters, 1 / 2 / 8: 31 / 21 / 29;
+// 8192 -> 8192, 200 decode rows of 400 adapters, 1 / 8: 42 / 104.)
+inline int f32_col_split(const ApplyArgs &a, int64_t S)
+{
+    const double tiles = (double)f32_likely_tiles(a, S), in = a.d_in / 512.0, out = a.d_out / 512.0;
+    int best = 1;
+    double best_us = 0;
+    for (int split = 1; split <= 8 && split * 64 <= a.d_out + 63; split *= 2) {
+        const double rounds = tiles * split > 240 ? tiles * split / 240 : 1, us = rounds * (8 + in + 1.25 * out / split);
+        // a first factor of megabytes is read from memory again by every further workgroup (rank 96, 8192 -> 14336, 1700 rows, 1 / 2 of them:
+        // 391 / 473 us); and a gain within the estimate's error is none (rank 96, 680 -> 512: 25 / 30)
+        if (split > 1 && tiles * split > 128 && (int64_t)a.d_in * a.rank > (1 << 19)) break;
+        if (split == 1 || us < (tiles * split > 128 ? 0.9 : 1.0) * best_us) { best = split; best_us = us; }
+    }
+    return best;
+}
+
 template <bool DIREFT>
 void launch_f32(ApplyArgs a, int64_t S, const Knobs &k, hipStream_t stream)
 {
-    if (!DIREFT) a.col_split = k.colsplit ? k.colsplit : a.T <= 512 ? 8 : a.T <= 1024 ? 4 : 1;
+    if (!DIREFT) a.col_split = k.colsplit ? k.colsplit : f32_col_split(a, S);
     if (a.rank <= 16)      launch_f32_nb<1, DIREFT>(a, S, stream);
     else if (a.rank <= 32) launch_f32_nb<2, DIREFT>(a, S, stream);
     else if (a.rank <= 64) launch_f32_nb<4, DIREFT>(a, S, stream);
@@ -774,12 +844,17 @@ void launch_f32(ApplyArgs a, int64_t S, const Knobs &k, hipStream_t stream)
 
 enum class Path { Rows, Valu, Mfma, F32 };
 
-Path choose_path(int dtype, int32_t T, int rank, bool widths_128, bool narrow, const Knobs &k)
+Path choose_path(const ApplyArgs &a, int64_t S, bool direft, int dtype, const Knobs &k)
 {
+    const int rank = a.rank;
     if (k.variant == 1) return Path::Rows;
-    // fp32: a handful of rows at rank 1-4 has no use for the matrix cores (rank 1, 5 rows of 4872, in place: per-row
-    // kernel 15 us, tile kernel 24; rank 8, 32 rows of 4096: 26 and 21; rank 16, 2304 rows: 82 and 29)
-    if (dtype != PREFT_BF16) return narrow && (rank > 4 || T > 64) ? Path::F32 : Path::Rows;
+    if (dtype != PREFT_BF16) {
+        const bool narrow = a.d_in <= (1 << 22) && a.d_out <= (1 << 22);     // byte offsets within a factor fit 32 bits
+        if (!narrow) return Path::Rows;
+        if (k.variant == 0 && k.colsplit == 0 && f32_rows_win(a, S, direft)) return Path::Rows;
+        return Path::F32;
+    }
+    const bool widths_128 = wide_widths_ok(a, 1);
     // matrix-core kernels: multiples of 4, every rank from 5 to 16 (the any-rank shape of the column-split
     // kernel) and, widths being multiples of 128, every rank above (the any-rank form of the row-split
     // kernel); ranks 1..3 are a vector-ALU matter
@@ -794,8 +869,7 @@ Path choose_path(int dtype, int32_t T, int rank, bool widths_128, bool narrow, c
 template <bool DIREFT>
 int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipStream_t stream)
 {
-    const bool narrow = a.d_in <= (1 << 22) && a.d_out <= (1 << 22);     // byte offsets within a factor fit 32 bits
-    switch (choose_path(dtype, a.T, a.rank, wide_widths_ok(a, 1), narrow, k)) {
+    switch (choose_path(a, S, DIREFT, dtype, k)) {
     case Path::F32:
         launch_f32<DIREFT>(a, S, k, stream);
         break;
