@@ -163,8 +163,11 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
             gcptr_t zb = as_global(p.zws) + (z_piece(block0 + m, n_slices, sl, rank_blocks, 0) + lane) * 16;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                u32x4_t zv = {0u, 0u, 0u, 0u};
-                if (NB < 4 || b < 3 || rank_blocks > b) zv = ld16(zb + b * 1024);
+                u32x4_t zv = ld16(zb + (NB < 4 || b < 3 ? b : rank_blocks - 1) * 1024);
+                if (NB == 4 && b == 3) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) zv[k] = rank_blocks > 3 ? zv[k] : 0u;
+                }
                 zop[mb][b] = as_bf16x8(zv);
             }
         }

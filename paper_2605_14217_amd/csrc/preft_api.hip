@@ -149,6 +149,20 @@ inline unsigned tile_grid(const ApplyArgs &a, int64_t S, int rows)
 // How many 16-row tiles a small batch is likely to have: rows / 16, and a partial tile for every second segment or adapter.
 inline int64_t likely_tiles(const ApplyArgs &a, int64_t S) { return a.T / 16 + (S < a.N ? S : a.N) / 2 + 1; }
 
+// Rows of segments of more than one row, if no segment is empty: prompts.  A step of decode rows alone has none, and where only
+// prompt positions count it has next to nothing to do: its launches are sized for that (a kernel strides over what exceeds its grid).
+inline int64_t prompt_rows(const ApplyArgs &a, int64_t S) { return a.T > S ? a.T - S : 0; }
+
+// Units of a 16-row launch that a small batch is likely to list: 8 for every chunk, prompts of 16 rows and more; every gathered tile
+// that all-position rows can make, and a few of prompts' short ends.
+inline unsigned likely_units(const ApplyArgs &a, int64_t S)
+{
+    const int64_t rows = prompt_rows(a, S), chunks = rows ? rows / CHUNK_ROWS + (rows / 16 < S ? rows / 16 : S) + 2 : 0;
+    const int64_t gathered = gtile_capacity(a.T, S, a.N), units = chunks * (CHUNK_ROWS / 16) + (a.all_tokens || gathered < 8 ? gathered : 8);
+    const unsigned bound = tile_grid(a, S, 16), likely = (unsigned)((units + 7) / 8 * 8);
+    return likely < bound ? likely : bound;
+}
+
 constexpr int32_t SMALL_T = 1024;
 constexpr int64_t DEEP_WGS = 200;                             // at most one workgroup per compute unit, with room for a poor estimate
 
@@ -209,7 +223,7 @@ inline SmallShape small_shape(const ApplyArgs &a, int64_t S, int n_slices, const
 template <int NB, bool DIREFT, bool ODD>
 void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
 {
-    const unsigned tiles = tile_grid(a, S, 16);               // col_split is 1 here
+    const unsigned tiles = likely_units(a, S);                // a multiple of 8 (col_split is 1 here)
     if constexpr (DIREFT) {
         void (*kernel)(ApplyArgs, int) = small_tile_kernel<NB, true, ODD, true>;
         if (a.h_layers) kernel = small_tile_layers_kernel<NB, ODD>;
@@ -352,9 +366,11 @@ bool rows_off_lines(const ApplyArgs &a, int n_slices)
 void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
 {
     a.xcd_runs = rows_off_lines(a, n_slices);
-    // More tiles than the batch's rows fill are likely to be empty: the kernel strides over what exceeds the grid (and over
-    // what would exceed the 2^32 work items of a launch)
-    const int64_t bound = tile_grid(a, S, 16 * EXPAND_MB), likely = (int64_t)a.T / (16 * EXPAND_MB) * 5 / 4 + 64;
+    // More tiles than the likely rows fill are likely to be empty, and an empty workgroup is not free (3584 decode rows, prompt
+    // positions, 8192 -> 2 x 28672: 22 848 of them 23 us): the kernel strides over what exceeds the grid (and over what would
+    // exceed the 2^32 work items of a launch)
+    const int64_t rows = a.all_tokens && !a.chunks_only ? a.T : prompt_rows(a, S);
+    const int64_t bound = tile_grid(a, S, 16 * EXPAND_MB), likely = rows / (16 * EXPAND_MB) * 5 / 4 + (rows / 8 < 64 ? rows / 8 + 1 : 64);
     const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices), most = (int64_t)1 << 23;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(EXPAND_WAVES * 64), 0, stream, a, n_slices);
 }
@@ -387,6 +403,8 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     if (!expand_ids_fit(a, S, n_slices)) return false;
     if (k.resident == 1) return true;
     if (a.T <= 1024) return false;
+    // hardly a prompt row, and none of the others counts, or the second launch does not take them: nothing to expand
+    if ((!a.all_tokens || a.rank > 16) && prompt_rows(a, S) < 64) return false;
     // Rank 64, 352 814 rows of the 70B layer's shapes, one launch -> two, us: q+k+v 4878 -> 5537, o 3648 -> 3936, gate+up
     // 18 408 -> 19 585 (the single launch has tiles enough, and its shrink hides behind other workgroups' expand); 60 000 rows:
     // 8192 -> 2 x 28672 3166 -> 3242, 8192 -> 8192 596 -> 602, q+k+v 851 -> 894; 37 000 rows: 518 -> 454 (8192 -> 8192).

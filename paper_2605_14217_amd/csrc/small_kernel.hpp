@@ -21,8 +21,10 @@ constexpr int SMALL_WAVES = 8;
 
 // DEEP: few workgroups, each alone on its compute unit: up to 256 registers for requests in flight.  Otherwise 128, two
 // workgroups per compute unit, which hide one another's trips.
+// One tile and share; `unit` and `share` are uniform over the workgroup.
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
-__device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices)
+__device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int n_chunk_units, int share, int sh0, int sh1,
+                                               u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
 {
     // units of the shrink and of the expand sweep in flight (registers)
     constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : NB == 1 ? 2 : 1;
@@ -31,26 +33,8 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices
     constexpr bool W_LATE = NB > 4;                           // factors of the expand step by step (registers)
     static_assert(DEEP || NB <= 2, "128 registers do not hold a unit of more rank blocks");
     constexpr int PIECES = 4;                                 // any-rank form: 16-byte pieces of a unit's factor block per lane
-    __shared__ u32x4_t turn[WAVES][2][16 * MFMA_TRS];         // activations, and the factor
-    __shared__ float red[WAVES * NB * 4 * 64];
-
-    if (!schedule_matches(p)) return;
-    // the workgroups of a tile: shares of the first output, then those of the others; side by side on one XCD
-    const int per_share = p.col_split;                        // units of a share
-    auto shares_of = [&](int d) { return ((d + 127) / 128 + per_share - 1) / per_share; };
-    const int sh0 = DIREFT ? 1 : shares_of(p.d_out);
-    const int sh1 = !DIREFT && n_slices > 1 ? shares_of(p.more[0].d_out) : 0;
-    const int sh2 = !DIREFT && n_slices > 2 ? shares_of(p.more[1].d_out) : 0;
-    const int shares = sh0 + sh1 + sh2;
-    int n_chunk_units;
-    const int n_units = tile_units<16>(p, &n_chunk_units);
-    const int per_xcd = (n_units + 7) >> 3;
-    const int t = (blockIdx.x >> 3) / shares;
-    int share = (blockIdx.x >> 3) - t * shares;
-    const int unit = t < per_xcd ? few_tiles_unit(p, n_chunk_units, per_xcd, t) : n_units;
-    if (unit >= n_units) return;
-
     // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
+    const int per_share = p.col_split;                        // units of a share
     const bool gathered = unit >= n_chunk_units;
     const int row0 = gathered ? 0 : unit % (CHUNK_ROWS / 16) * 16;
     const i32x4_t entry = *reinterpret_cast<const PREFT_CONST i32x4_t *>(
@@ -72,7 +56,9 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices
     gcptr_t A = as_global(as_const(A_pool)[entry[0]]);
     gcptr_t Bt = as_global(as_const(Bt_pool)[entry[0]]);
 
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));                            // recomputed for every tile: what hangs on the lane would fill the registers
     const int rl = lane & 15, g = lane >> 4;                  // MFMA order
     const int q = lane >> 4, c16 = lane & 15;                 // unit load order
     const int r = p.rank;
@@ -290,6 +276,33 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices
                 finish(k, u + k * WAVES);
                 if (u + (k + DEPTH) * WAVES < uend) load_yw(k, u + (k + DEPTH) * WAVES);
             }
+    }
+}
+
+// The workgroups of a tile -- shares of the first output, then those of the others -- sit side by side on one XCD.  A launch has
+// as many as the batch is likely to need; what exceeds it is strided over.
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
+__device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices)
+{
+    __shared__ u32x4_t turn[WAVES][2][16 * MFMA_TRS];         // activations, and the factor
+    __shared__ float red[WAVES * NB * 4 * 64];
+
+    if (!schedule_matches(p)) return;
+    const int per_share = p.col_split;                        // units of a share
+    auto shares_of = [&](int d) { return ((d + 127) / 128 + per_share - 1) / per_share; };
+    const int sh0 = DIREFT ? 1 : shares_of(p.d_out);
+    const int sh1 = !DIREFT && n_slices > 1 ? shares_of(p.more[0].d_out) : 0;
+    const int sh2 = !DIREFT && n_slices > 2 ? shares_of(p.more[1].d_out) : 0;
+    const int shares = sh0 + sh1 + sh2;
+    int n_chunk_units;
+    const int n_units = tile_units<16>(p, &n_chunk_units);
+    const int per_xcd = (n_units + 7) >> 3, step = (gridDim.x >> 3) / shares;     // the grid is a multiple of 8 shares
+    int t = (blockIdx.x >> 3) / shares;
+    const int share = (blockIdx.x >> 3) - t * shares;
+    for (; t < per_xcd; t += step) {
+        const int unit = few_tiles_unit(p, n_chunk_units, per_xcd, t);
+        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES>(p, unit, n_chunk_units, share, sh0, sh1, turn, red);
+        __syncthreads();                                      // the next tile's sums go where this one's are still being read
     }
 }
 

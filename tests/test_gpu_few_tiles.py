@@ -8,7 +8,9 @@ from paper_2605_14217_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 LENGTHS = {"short": [10, 14, 11, 13] + [1] * 14, "one": [5], "nine": [17] * 9, "full": [128, 128, 256, 120], "edge": [96, 95, 97] + [2] * 5,
-           "many": [6] * 70 + [1] * 30, "thousand": [100] * 10}
+           "many": [6] * 70 + [1] * 30, "thousand": [100] * 10,
+           # empty segments hide the prompt rows from the host's estimate: the launches are too small and stride over their tiles
+           "empty": [0] * 500 + [200, 90, 33] + [0] * 400 + [3, 129, 1, 1]}
 
 
 @pytest.mark.parametrize("dtype,rank", [("bf16", 5), ("bf16", 16), ("bf16", 64), ("f32", 7), ("f32", 16)])
@@ -25,3 +27,26 @@ def test_every_row_once(lens, dtype, rank):
     for all_tokens in (False, True):
         run_lora_case(tab, pool, x, y0, dtype, 2.0, all_tokens, pad_cols=8)
         run_direft_case(tab, edit, x, dtype, 0.5, all_tokens, pad_cols=8)
+
+
+@pytest.mark.parametrize("rank", [3, 7, 16, 32, 40, 64])
+@pytest.mark.parametrize("lens", [[1] * 1100, [0] * 2000 + [700, 500, 2, 1], [1] * 1100 + [90]], ids=["decode", "hidden", "one-prompt"])
+def test_batches_with_next_to_no_prompt(lens, rank):
+    """Above 1024 rows: a step of decode rows alone, prompts hidden from the host's estimate by empty segments, and one prompt beside
+    decode rows; with a workspace that has room for two launches, chosen by the library and forced."""
+    import paper_2605_14217_amd as preft
+    from parity_util import run_lora_case
+    N = 6
+    rng = np.random.Generator(np.random.PCG64(len(lens)))
+    lens = np.array(lens)
+    tab = wl.from_lengths(lens, rng.integers(-1, N, size=len(lens)), np.where(lens > 1, lens, 0))
+    x = wl.activations(tab.T, 256, "bf16", device="cuda", seed=1)
+    y0 = wl.activations(tab.T, 1152, "bf16", device="cuda", seed=2)
+    pool = wl.lora_pool(N, rank, 256, 1152, "bf16", device="cuda", seed=3)
+    for flags in (0, preft.test_flags(resident=1)):
+        prev = preft.set_test_flags(flags)
+        try:
+            for all_tokens in (False, True):
+                run_lora_case(tab, pool, x, y0, "bf16", 2.0, all_tokens, pad_cols=8, z_room=True)
+        finally:
+            preft.set_test_flags(prev)
