@@ -177,8 +177,8 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool dire
     if (!direft) return true;
     // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 32
     // rows: 10.0 and 10.6 us, 1000 rows 11.4 and 13.1; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
-    // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81; 8 layers of 1000 rows, rank 32: 54 and 69)
-    if (likely_tiles(a, S) * a.n_layers > DEEP_WGS) return false;
+    // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81)
+    if (likely_tiles(a, S) > DEEP_WGS) return false;          // whatever n_layers: a layer's result is that of its one-layer call, bit for bit
     if (a.rank > 16) return a.rank <= 64;                     // above, its registers spill: rank 128, d = 6320, 77 rows 123 and 130 us
     return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
 }
@@ -798,7 +798,7 @@ inline int64_t f32_likely_tiles(const ApplyArgs &a, int64_t S)
 bool f32_rows_win(const ApplyArgs &a, int64_t S, bool direft)
 {
     const int r = a.rank;
-    const int64_t T = (int64_t)a.T * a.n_layers, tiles = f32_likely_tiles(a, S) * a.n_layers, in = a.d_in, out = a.d_out;
+    const int64_t T = a.T, tiles = f32_likely_tiles(a, S), in = a.d_in, out = a.d_out;       // whatever n_layers: see takes_small
     const bool prompts = a.T >= 2 * S, mixed = prompts && a.all_tokens && S > 1 + a.T / 256;
     if (r > 8 || T > 2048 || mixed) return false;
     if (direft) {

@@ -50,3 +50,18 @@ def test_batches_with_next_to_no_prompt(lens, rank):
                 run_lora_case(tab, pool, x, y0, "bf16", 2.0, all_tokens, pad_cols=8, z_room=True)
         finally:
             preft.set_test_flags(prev)
+
+
+@pytest.mark.parametrize("dtype,rank,d,rows", [("bf16", 32, 1024, 1000), ("bf16", 16, 1000, 900), ("bf16", 7, 264, 700), ("f32", 4, 2048, 600),
+                                               ("f32", 1, 1536, 700), ("f32", 3, 4096, 150)])
+def test_many_layers_give_the_bits_of_one(dtype, rank, d, rows):
+    """A layer of a many-layer call is its one-layer call, bit for bit: which kernel runs does not hang on the number of layers."""
+    from parity_util import run_direft_layers_case
+    N, L = 3, 4
+    tab = wl.from_lengths(np.array([rows // 2, rows - rows // 2 - 40] + [1] * 40), np.arange(42) % N, np.array([rows // 2, rows - rows // 2 - 40] + [1] * 40))
+    if rows == 150:
+        tab = wl.from_lengths(np.ones(rows, int), np.arange(rows) % N, np.ones(rows, int))
+    pools = [wl.direft_pool(N, rank, d, dtype, device="cuda", seed=l) for l in range(L)]
+    hs = [wl.activations(tab.T, d, dtype, device="cuda", seed=9 + l) for l in range(L)]
+    for all_tokens in (False, True):
+        run_direft_layers_case(tab, pools, hs, dtype, 0.5, all_tokens, [True] * L, pad_cols=8)
