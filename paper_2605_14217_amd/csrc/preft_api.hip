@@ -390,7 +390,7 @@ void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stre
 //   rank 1-3 (vector-ALU kernels), 4096 -> 4096: 1500 rows 13-15 -> 14-16, 11 300 rows 52 -> 52, 42 000 rows 190 -> 170;
 //     4096 -> 2 x 14336: 1500 rows 62-82 -> 39-44, 42 000 rows 1030 -> 864; q+k+v of 8192, 350 000 rows 3556-3676 -> 3218-3407;
 //     1024 -> 1024 + 2 x 512, 140 000 rows 258-265 -> 255-293; rows off 128-byte lines, 1024 -> 2728 10-11 -> 12-13,
-//     2000 -> 3208, 11 200 rows 42-44 -> 50.
+//     2000 -> 3208, 11 200 rows 42-44 -> 50, but several outputs off lines, 4096 -> 9640 + 296, 1500 rows 26 -> 18.
 //   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 518 -> 454; rank 32 86 -> 48,
 //     105 -> 97, 355 -> 372.
 //   decode rows alone, 7 per adapter (gathered tiles), rank 16, 8192 -> 8192: 1200 rows 30 -> 35, 3584 rows 89 -> 89;
@@ -413,7 +413,7 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     if (a.all_tokens && a.T < 8 * S) return false;
     int64_t width = a.d_out;
     for (int i = 1; i < n_slices; ++i) width += a.more[i - 1].d_out;
-    if (a.rank < 4) return a.T * width >= 12000000 && width >= 3072 && !rows_off_lines(a, n_slices);
+    if (a.rank < 4) return a.T * width >= (n_slices > 1 ? 6000000 : 12000000) && width >= 3072 && (n_slices > 1 || !rows_off_lines(a, n_slices));
     return a.T * width >= 6000000 && (width >= 3072 || !rows_off_lines(a, n_slices));
 }
 
