@@ -1,0 +1,134 @@
+// What the host knows about a batch before its schedule exists, and the rules that choose from it: launch sizes, the small-batch
+// kernel and its shape.  Host code without state; preft_api.hip launches by it, tests ask it.
+#pragma once
+#include "common.hpp"
+#include "small_kernel.hpp"
+
+#include <cmath>
+
+namespace preft {
+
+// Kernel selection for tests and benchmarks, carried by the mode argument of the call itself
+// (PREFT_TEST_* of the public header): the library keeps no state between calls.
+struct Knobs {
+    int variant, waves, rowblocks, colsplit, resident;
+};
+
+// Upper bound of the units of a tile-kernel launch of height `rows`, from host-visible sizes,
+// rounded to the 8 XCDs.
+inline unsigned tile_grid(const ApplyArgs &a, int64_t S, int rows)
+{
+    const int64_t per_gtile = rows >= GTILE_ROWS ? 1 : GTILE_ROWS / rows;
+    int64_t units = gtile_capacity(a.T, S, a.N) * per_gtile;
+    if (!a.gathered_only) units += chunk_capacity(a.T, S) * (CHUNK_ROWS / rows);
+    return (unsigned)(((units + 7) / 8) * 8 * (a.col_split > 1 ? a.col_split : 1));
+}
+
+// How many of N adapters n segments are expected to name.
+inline int64_t likely_adapters(int64_t n, int64_t N)
+{
+    if (n <= 0 || N <= 0) return 0;
+    return (int64_t)((double)N * -expm1(-(double)n / (double)N) + 0.5);
+}
+
+// How many 16-row tiles a batch is likely to have.  Rows in excess of one per segment belong to prompts: a prompt ends in a
+// partial tile; the other segments, where every position counts, are gathered by adapter, which ends in a partial tile each.
+inline int64_t likely_tiles(const ApplyArgs &a, int64_t S)
+{
+    const int64_t extra = a.T > S ? a.T - S : 0, prompts = S < extra / 16 + 1 ? S : extra / 16 + 1;
+    int64_t singles = a.all_tokens ? (a.T < S ? a.T : S) - (extra ? prompts : 0) : 0;
+    if (singles < 0) singles = 0;
+    const int64_t owners = likely_adapters(singles, a.N), gathered = singles / 16 + owners / 2;
+    return extra / 16 + (extra ? prompts / 2 + 1 : 0) + (gathered > owners ? gathered : owners);
+}
+
+// Small batches take a kernel of their own (small_kernel.hpp).
+// Rows of segments of more than one row, if no segment is empty: prompts.  A step of decode rows alone has none, and where only
+// prompt positions count it has next to nothing to do: its launches are sized for that (a kernel strides over what exceeds its grid).
+inline int64_t prompt_rows(const ApplyArgs &a, int64_t S) { return a.T > S ? a.T - S : 0; }
+
+// Units of a 16-row launch that a small batch is likely to list: 8 for every chunk, prompts of 16 rows and more; every gathered tile
+// that all-position rows can make, and a few of prompts' short ends.
+inline unsigned likely_units(const ApplyArgs &a, int64_t S)
+{
+    const int64_t rows = prompt_rows(a, S), chunks = rows ? rows / CHUNK_ROWS + (rows / 16 < S ? rows / 16 : S) + 2 : 0;
+    const int64_t gathered = gtile_capacity(a.T, S, a.N), units = chunks * (CHUNK_ROWS / 16) + (a.all_tokens || gathered < 8 ? gathered : 8);
+    const unsigned bound = tile_grid(a, S, 16), likely = (unsigned)((units + 7) / 8 * 8);
+    return likely < bound ? likely : bound;
+}
+
+constexpr int32_t SMALL_T = 1024;
+constexpr int64_t DEEP_WGS = 200;                             // at most one workgroup per compute unit, with room for a poor estimate
+
+// `widest`: columns of the widest output
+inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool direft, const Knobs &k)
+{
+    if (a.rank < 4 || ((a.rank % 4) && a.rank > 16)) return false;
+    if (a.d_in > (1 << 22) || widest > (1 << 22)) return false;          // offsets within a row or a factor, and the launch, fit 32 bits
+    if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
+    if (!direft && k.colsplit) return k.colsplit > 1;
+    if (a.T > SMALL_T) return false;
+    if (!direft) return true;
+    // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 32
+    // rows: 10.0 and 10.6 us, 1000 rows 11.4 and 13.1; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
+    // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81)
+    if (likely_tiles(a, S) > 200) return false;               // whatever n_layers: a layer's result is that of its one-layer call, bit for bit
+    if (a.rank > 16) return a.rank <= 64;                     // above, its registers spill: rank 128, d = 6320, 77 rows 123 and 130 us
+    return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
+}
+
+// What a workgroup of the small-batch kernel is (out of place): the units of 128 columns it expands, and whether it has
+// the compute unit to itself (deep).
+//
+// As many shares as make at most about one workgroup per compute unit: the repeated shrink costs nothing while compute units are idle, and a
+// share's factors come lane by lane through the texture path, which is what a wide share waits for from rank 17 on.  Down to
+// 8 units at rank 4-16 (4 of a narrow output), 2 at rank 17-32, 1 above.  Measured (us, 8 units a share / the rule's): rank 64, 376 -> 1024, 2 rows 11.3 / 6.2;
+// 1024 -> 1024, 377 decode rows of 2 adapters 12.8 / 7.7; rank 96, 1024 -> 1024, 67 rows 15.8 / 9.5; rank 32, 1024 -> 1504, 10 rows
+// 6.5 / 5.2; rank 16, 512 -> 1024, 200 rows 4.8 / 4.3.  More workgroups than that wait for one another: rank 96, 512 -> 1024, 45
+// tiles, 4 / 8 shares 10.3 / 17.2; rank 5, 4096 -> 11168 + 512, 18 tiles, 9 / 12 shares 10.6 / 14.5; 4096 -> 2 x 14336, one tile, 28 / 56
+// shares 7.6 / 12.4.
+// Where even that is too many (rank 4-16): two on a compute unit, of 128 registers each, hide each other's trips, which also
+// suits batches where every tile has an adapter of its own (4096 -> 4096, 512 decode rows of 64 adapters: 8 units, shallow 11.8, 16
+// units, deep 17.5; 1000 rows of 5 adapters 13.7 and 11.6; 4096 -> 2 x 14336: up to 640 shallow workgroups 33.6 / 36.5, up to 300
+// 36.0 / 29.5).  From rank 17 on the LDS does not hold two on a compute unit: deep, and above rank 32 with 4 wavefronts where many
+// adapters meet more than a workgroup per compute unit (rank 64, 4096 -> 4096, 512 decode rows: 8 wavefronts 30.9, 4 wavefronts 23.6; 1000
+// rows of 5 adapters 29.0 / 30.8).
+struct SmallShape { int units; bool deep; int waves; };
+
+inline SmallShape small_shape(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
+{
+    int most = 0, d[3] = {a.d_out, n_slices > 1 ? a.more[0].d_out : 0, n_slices > 2 ? a.more[1].d_out : 0};
+    for (int i = 0; i < n_slices; ++i) { d[i] = (d[i] + 127) / 128; if (d[i] > most) most = d[i]; }
+    if (k.colsplit) return {(most + k.colsplit - 1) / k.colsplit, true, SMALL_WAVES};
+    const int64_t tiles = likely_tiles(a, S) + 1;
+    auto workgroups = [&](int units) {
+        int64_t shares = 0;
+        for (int i = 0; i < n_slices; ++i) shares += (d[i] + units - 1) / units;
+        return tiles * shares;
+    };
+    // mostly short segments, and enough adapters for most tiles to have one of their own
+    const bool many_adapters = a.T < 16 * S && 32 * (S < a.N ? S : (int64_t)a.N) > a.T;
+    const int waves = a.rank > 32 && many_adapters && workgroups(SMALL_WAVES) > DEEP_WGS ? 4 : SMALL_WAVES;
+    const int least = a.rank > 32 ? 1 : a.rank > 16 ? 2 : most <= 2 * SMALL_WAVES ? 4 : SMALL_WAVES;
+    const int widest = (many_adapters && a.rank <= 16 ? 1 : 4) * SMALL_WAVES;
+    // a tile's workgroups share one XCD: 32 compute units for the tiles that meet there
+    const int64_t tiles_of_xcd = tiles <= 9 ? 1 : (tiles + 10) / 8, most_shares = DEEP_WGS / tiles < 32 / tiles_of_xcd ? DEEP_WGS / tiles : 32 / tiles_of_xcd;
+    int64_t shares = (most + least - 1) / least;
+    if (shares > most_shares) shares = most_shares;
+    for (; shares > 0 && waves == SMALL_WAVES; --shares) {
+        int units = (int)((most + shares - 1) / shares);
+        if (units > SMALL_WAVES) units = units > 2 * SMALL_WAVES ? 4 * SMALL_WAVES : 2 * SMALL_WAVES;   // whole rounds of the wavefronts
+        if (units > widest) break;
+        if (workgroups(units) <= most_shares * tiles) return {units, true, waves};
+    }
+    if (a.rank > 16) {
+        for (int units = SMALL_WAVES; units <= 16 * SMALL_WAVES; units *= 2)
+            if (workgroups(units) <= 288) return {units, true, waves};
+        return {16 * SMALL_WAVES, true, waves};
+    }
+    for (int units = SMALL_WAVES; units <= 8 * SMALL_WAVES; units *= 2)
+        if (workgroups(units) <= (many_adapters ? 300 : 640)) return {units, false, SMALL_WAVES};
+    return {8 * SMALL_WAVES, false, SMALL_WAVES};
+}
+
+}  // namespace preft

@@ -3,6 +3,7 @@
 #include "../../include/preft.h"
 
 #include "common.hpp"
+#include "dispatch.hpp"
 #include "expand_kernel.hpp"
 #include "f32_kernel.hpp"
 #include "mfma_kernel.hpp"
@@ -16,9 +17,7 @@
 #include "instances/extern_kernels.inc"
 #endif
 
-#include <cmath>
 #include <mutex>
-
 
 static_assert(preft::PREFT_MAX_RANK_DEV == PREFT_MAX_RANK, "device and public rank limits differ");
 
@@ -32,11 +31,6 @@ namespace {
 
 using namespace preft;
 
-// Kernel selection for tests and benchmarks, carried by the mode argument of the call itself
-// (PREFT_TEST_* of the public header): the library keeps no state between calls.
-struct Knobs {
-    int variant, waves, rowblocks, colsplit, resident;
-};
 constexpr int MODE_TEST_MASK = 0x7fff0000;
 constexpr int MODE_MASK = PREFT_ALL_TOKENS | PREFT_SCHEDULE_READY | MODE_TEST_MASK;
 
@@ -136,90 +130,6 @@ int launch_schedule(void *workspace, const int32_t *seg_start, const int32_t *se
 // ------------------------------------------------------------------------------------
 // tile-kernel dispatch
 // ------------------------------------------------------------------------------------
-// Upper bound of the units of a tile-kernel launch of height `rows`, from host-visible sizes,
-// rounded to the 8 XCDs.
-inline unsigned tile_grid(const ApplyArgs &a, int64_t S, int rows)
-{
-    const int64_t per_gtile = rows >= GTILE_ROWS ? 1 : GTILE_ROWS / rows;
-    int64_t units = gtile_capacity(a.T, S, a.N) * per_gtile;
-    if (!a.gathered_only) units += chunk_capacity(a.T, S) * (CHUNK_ROWS / rows);
-    return (unsigned)(((units + 7) / 8) * 8 * (a.col_split > 1 ? a.col_split : 1));
-}
-// Small batches take a kernel of their own (small_kernel.hpp).
-// How many 16-row tiles a small batch is likely to have: rows / 16, and a partial tile for every second segment or adapter.
-inline int64_t likely_tiles(const ApplyArgs &a, int64_t S) { return a.T / 16 + (S < a.N ? S : a.N) / 2 + 1; }
-
-// Rows of segments of more than one row, if no segment is empty: prompts.  A step of decode rows alone has none, and where only
-// prompt positions count it has next to nothing to do: its launches are sized for that (a kernel strides over what exceeds its grid).
-inline int64_t prompt_rows(const ApplyArgs &a, int64_t S) { return a.T > S ? a.T - S : 0; }
-
-// Units of a 16-row launch that a small batch is likely to list: 8 for every chunk, prompts of 16 rows and more; every gathered tile
-// that all-position rows can make, and a few of prompts' short ends.
-inline unsigned likely_units(const ApplyArgs &a, int64_t S)
-{
-    const int64_t rows = prompt_rows(a, S), chunks = rows ? rows / CHUNK_ROWS + (rows / 16 < S ? rows / 16 : S) + 2 : 0;
-    const int64_t gathered = gtile_capacity(a.T, S, a.N), units = chunks * (CHUNK_ROWS / 16) + (a.all_tokens || gathered < 8 ? gathered : 8);
-    const unsigned bound = tile_grid(a, S, 16), likely = (unsigned)((units + 7) / 8 * 8);
-    return likely < bound ? likely : bound;
-}
-
-constexpr int32_t SMALL_T = 1024;
-constexpr int64_t DEEP_WGS = 200;                             // at most one workgroup per compute unit, with room for a poor estimate
-
-// `widest`: columns of the widest output
-inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool direft, const Knobs &k)
-{
-    if (a.rank < 4 || ((a.rank % 4) && a.rank > 16)) return false;
-    if (a.d_in > (1 << 22) || widest > (1 << 22)) return false;          // offsets within a row or a factor, and the launch, fit 32 bits
-    if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
-    if (!direft && k.colsplit) return k.colsplit > 1;
-    if (a.T > SMALL_T) return false;
-    if (!direft) return true;
-    // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 32
-    // rows: 10.0 and 10.6 us, 1000 rows 11.4 and 13.1; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
-    // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81)
-    if (likely_tiles(a, S) > DEEP_WGS) return false;          // whatever n_layers: a layer's result is that of its one-layer call, bit for bit
-    if (a.rank > 16) return a.rank <= 64;                     // above, its registers spill: rank 128, d = 6320, 77 rows 123 and 130 us
-    return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
-}
-
-// What a workgroup of the small-batch kernel is (out of place): the units of 128 columns it expands, and whether it has
-// the compute unit to itself.  One unit for every wavefront as long as that makes at most about one workgroup per
-// compute unit; beyond, the repeated shrink sweeps cost more than the shorter expand gains.  Measured (us, 64 or 65
-// tiles, rank 16): 5 adapters, 4096 -> 4096: 8 units, shallow 13.7, 16 units, deep 11.6; 64 adapters (512 decode
-// rows): 11.8 and 17.5 -- there every workgroup brings factors of its own from memory, and two on a compute unit hide
-// each other's trips; 4096 -> 2 x 14336: up to 640 shallow workgroups 33.6 / 36.5, up to 300 36.0 / 29.5.  Above rank 32
-// there are no registers for two on a compute unit: deep, with 4 wavefronts where many adapters meet more
-// than a workgroup per compute unit (rank 64, 4096 -> 4096, 512 decode rows: 8 wavefronts 30.9, 4 wavefronts 23.6; 1000 rows of
-// 5 adapters 29.0 / 30.8).
-struct SmallShape { int units; bool deep; int waves; };
-
-inline SmallShape small_shape(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
-{
-    int most = 0, d[3] = {a.d_out, n_slices > 1 ? a.more[0].d_out : 0, n_slices > 2 ? a.more[1].d_out : 0};
-    for (int i = 0; i < n_slices; ++i) { d[i] = (d[i] + 127) / 128; if (d[i] > most) most = d[i]; }
-    if (k.colsplit) return {(most + k.colsplit - 1) / k.colsplit, true, SMALL_WAVES};
-    const int64_t tiles = likely_tiles(a, S);
-    auto workgroups = [&](int units) {
-        int64_t shares = 0;
-        for (int i = 0; i < n_slices; ++i) shares += (d[i] + units - 1) / units;
-        return tiles * shares;
-    };
-    // mostly short segments, and enough adapters for most tiles to have one of their own
-    const bool many_adapters = a.T < 16 * S && 32 * (S < a.N ? S : (int64_t)a.N) > a.T;
-    if (a.rank > 32) {
-        const int waves = many_adapters && workgroups(SMALL_WAVES) > DEEP_WGS ? 4 : SMALL_WAVES;
-        for (int units = SMALL_WAVES; units <= 16 * SMALL_WAVES; units *= 2)
-            if (workgroups(units) <= 288) return {units, true, waves};
-        return {16 * SMALL_WAVES, true, waves};
-    }
-    for (int units = SMALL_WAVES; units <= (many_adapters ? 1 : 4) * SMALL_WAVES; units *= 2)
-        if (workgroups(units) <= DEEP_WGS) return {units, true, SMALL_WAVES};
-    for (int units = SMALL_WAVES; units <= 8 * SMALL_WAVES; units *= 2)
-        if (workgroups(units) <= (many_adapters ? 300 : 640)) return {units, false, SMALL_WAVES};
-    return {8 * SMALL_WAVES, false, SMALL_WAVES};
-}
-
 template <int NB, bool DIREFT, bool ODD>
 void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
 {
@@ -235,7 +145,7 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
         for (int i = 1; i < n_slices; ++i) shares += (a.more[i - 1].d_out + cols - 1) / cols;
         a.col_split = shape.units;
         void (*kernel)(ApplyArgs, int) = small_tile_kernel<NB, false, ODD, true>;
-        if constexpr (NB <= 2) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false>; }
+        if constexpr (NB == 1) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false>; }
         if constexpr (NB > 2) { if (shape.waves == 4) kernel = small_tile_kernel<NB, false, ODD, true, 4>; }
         hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * shares)), dim3(shape.waves * 64), 0, stream, a, n_slices);
     }
@@ -765,24 +675,6 @@ void launch_rows(const ApplyArgs &a, int64_t S, bool chunks_too, hipStream_t str
     hipLaunchKernelGGL(short_kernel, dim3((unsigned)g, a.n_layers), dim3(ROW_THREADS), 0, stream, a);
 }
 
-// How many of N adapters n segments are expected to name.
-inline int64_t likely_adapters(int64_t n, int64_t N)
-{
-    if (n <= 0 || N <= 0) return 0;
-    return (int64_t)((double)N * -expm1(-(double)n / (double)N) + 0.5);
-}
-
-// How many 16-row tiles a batch is likely to have.  Rows in excess of one per segment belong to prompts: a prompt ends in a
-// partial tile; the other segments, where every position counts, are gathered by adapter, which ends in a partial tile each.
-inline int64_t f32_likely_tiles(const ApplyArgs &a, int64_t S)
-{
-    const int64_t extra = a.T > S ? a.T - S : 0, prompts = S < extra / 16 + 1 ? S : extra / 16 + 1;
-    int64_t singles = a.all_tokens ? (a.T < S ? a.T : S) - (extra ? prompts : 0) : 0;
-    if (singles < 0) singles = 0;
-    const int64_t owners = likely_adapters(singles, a.N), gathered = singles / 16 + owners / 2;
-    return extra / 16 + (extra ? prompts / 2 + 1 : 0) + (gathered > owners ? gathered : owners);
-}
-
 // Whether the per-row kernel is the faster one for an fp32 call.  A workgroup of the tile kernel walks its tile's columns 512 at a
 // time, a trip to memory each, and in place does so alone: few tiles of wide rows wait for that chain (about 2 us per 1000 columns
 // of each sweep).  The per-row kernel has a workgroup for every four rows, about 1 us per 1000 columns at rank 1, 1.8 at rank 4, and is
@@ -798,7 +690,7 @@ inline int64_t f32_likely_tiles(const ApplyArgs &a, int64_t S)
 bool f32_rows_win(const ApplyArgs &a, int64_t S, bool direft)
 {
     const int r = a.rank;
-    const int64_t T = a.T, tiles = f32_likely_tiles(a, S), in = a.d_in, out = a.d_out;       // whatever n_layers: see takes_small
+    const int64_t T = a.T, tiles = likely_tiles(a, S), in = a.d_in, out = a.d_out;       // whatever n_layers: see takes_small
     const bool prompts = a.T >= 2 * S, mixed = prompts && a.all_tokens && S > 1 + a.T / 256;
     if (r > 8 || T > 2048 || mixed) return false;
     if (direft) {
@@ -837,7 +729,7 @@ void launch_f32_nb(const ApplyArgs &a, int64_t S, hipStream_t stream)
 // 8192 -> 8192, 200 decode rows of 400 adapters, 1 / 8: 42 / 104.)
 inline int f32_col_split(const ApplyArgs &a, int64_t S)
 {
-    const double tiles = (double)f32_likely_tiles(a, S), in = a.d_in / 512.0, out = a.d_out / 512.0;
+    const double tiles = (double)likely_tiles(a, S), in = a.d_in / 512.0, out = a.d_out / 512.0;
     int best = 1;
     double best_us = 0;
     for (int split = 1; split <= 8 && split * 64 <= a.d_out + 63; split *= 2) {

@@ -19,19 +19,19 @@ namespace preft {
 
 constexpr int SMALL_WAVES = 8;
 
-// DEEP: few workgroups, each alone on its compute unit: up to 256 registers for requests in flight.  Otherwise 128, two
-// workgroups per compute unit, which hide one another's trips.
+// DEEP: few workgroups, each alone on its compute unit: up to 256 registers for requests in flight.  Otherwise (rank <= 16: the LDS
+// of more rank blocks does not fit twice) 128, two workgroups per compute unit, which hide one another's trips.
 // One tile and share; `unit` and `share` are uniform over the workgroup.
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
 __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int n_chunk_units, int share, int sh0, int sh1,
                                                u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
 {
     // units of the shrink and of the expand sweep in flight (registers)
-    constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : NB == 1 ? 2 : 1;
+    constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : 2;
     constexpr int DEPTH = DEEP ? (NB == 1 ? (ODD ? 2 : 4) : NB == 2 ? 2 : 1) : 1;
     static_assert(!ODD || NB == 1, "the any-rank form covers rank <= 16");
     constexpr bool W_LATE = NB > 4;                           // factors of the expand step by step (registers)
-    static_assert(DEEP || NB <= 2, "128 registers do not hold a unit of more rank blocks");
+    static_assert(DEEP || NB == 1, "two workgroups of more rank blocks do not fit a compute unit");
     constexpr int PIECES = 4;                                 // any-rank form: 16-byte pieces of a unit's factor block per lane
     // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
     const int per_share = p.col_split;                        // units of a share

@@ -3,7 +3,9 @@
 //   z BLOCKS RANK OUTPUTS      end, in bytes behind the start of the z area, of the last piece that a two-launch LoRA call
 //                              writes for that many 16-row blocks
 //   piece COLUMNS MOST RANK    last_factor_piece
-#include "../paper_2605_14217_amd/csrc/common.hpp"
+//   small T S N ALL RANK D_IN D0 D1 D2   whether a LoRA call with these outputs (0: none) takes the small-batch kernel, and as what:
+//                              units of a share, deep, wavefronts, units of the launch
+#include "../paper_2605_14217_amd/csrc/dispatch.hpp"
 
 #include <cstdio>
 #include <cstring>
@@ -12,7 +14,21 @@ int main()
 {
     char what[16];
     while (std::scanf("%15s", what) == 1) {
-        long long a[3];
+        long long a[9];
+        if (!std::strcmp(what, "small")) {
+            for (long long &v : a)
+                if (std::scanf("%lld", &v) != 1) return 1;
+            preft::ApplyArgs p = {};
+            p.T = (int)a[0]; p.N = (int)a[2]; p.all_tokens = (int)a[3]; p.rank = (int)a[4]; p.d_in = (int)a[5];
+            p.d_out = (int)a[6]; p.more[0].d_out = (int)a[7]; p.more[1].d_out = (int)a[8]; p.n_layers = 1; p.col_split = 1;
+            const int n = a[8] ? 3 : a[7] ? 2 : 1;
+            int widest = 0;
+            for (int i = 6; i < 9; ++i) widest = a[i] > widest ? (int)a[i] : widest;
+            const preft::Knobs k = {};
+            const preft::SmallShape s = preft::small_shape(p, a[1], n, k);
+            std::printf("%d %d %d %d %u\n", preft::takes_small(p, a[1], widest, false, k), s.units, s.deep, s.waves, preft::likely_units(p, a[1]));
+            continue;
+        }
         if (std::scanf("%lld %lld %lld", &a[0], &a[1], &a[2]) != 3) return 1;
         if (!std::strcmp(what, "z")) {
             const int rank = (int)a[1], n = (int)a[2], nb = preft::z_rank_blocks(rank);

@@ -1,0 +1,56 @@
+"""The small-batch kernel's shapes, each reached by the sizes of a call and not by a test flag: deep workgroups of one unit up to
+many, the shallow ones of rank 4-16, the 4-wavefront ones above rank 32; single and packed outputs, ragged widths, decode rows of many
+adapters and prompts, both position sets.  The dispatch is asked on the host that a call takes the shape it is here for; the
+result is compared with the oracle (parity_util's bars)."""
+import shutil
+
+import numpy as np
+import pytest
+
+import paper_2605_14217_amd as preft
+from paper_2605_14217_amd import workloads as wl
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(shutil.which("hipcc") is None, reason="asks the dispatch through hipcc")]
+
+# (what the call is here for: deep, wavefronts, least units of a share), rank, d_in, outputs, decode rows, adapters, prompts
+CASES = [
+    ((0, 8, 8), 16, 264, (14336, 14336), 32, 32, ()), ((0, 8, 8), 7, 200, (13336, 14344), 40, 40, ()), ((0, 8, 8), 4, 512, (4104,), 512, 512, ()),
+    ((0, 8, 8), 15, 128, (8192, 1032, 1024), 512, 400, ()), ((0, 8, 16), 12, 1000, (14336, 14336), 16, 5, (200,) * 4),
+    ((1, 8, 8), 16, 512, (4096,), 500, 21, ()), ((1, 8, 4), 8, 512, (1024,), 3, 2, ()), ((1, 8, 2), 24, 512, (1024,), 16, 16, (200,)),
+    ((1, 8, 2), 32, 264, (14336, 14344), 32, 32, ()), ((1, 8, 32), 20, 136, (14336, 14336, 4096), 512, 64, ()),
+    ((1, 8, 1), 64, 376, (1024,), 2, 1, ()), ((1, 8, 1), 36, 136, (1096, 520), 10, 3, (17,)), ((1, 8, 1), 128, 256, (1024,), 20, 8, (60, 5)),
+    ((1, 4, 8), 40, 256, (4096,), 512, 512, ()), ((1, 4, 8), 64, 264, (14336, 1032), 64, 64, ()), ((1, 4, 8), 96, 128, (6152,), 96, 96, ()),
+    ((1, 4, 8), 128, 136, (4096, 4096, 136), 40, 40, ()),
+]
+
+
+@pytest.mark.parametrize("shape,rank,d_in,d_outs,decode,N,prompts", CASES, ids=[f"r{c[1]}-{c[2]}-{'x'.join(map(str, c[3]))}-{c[4]}of{c[5]}" for c in CASES])
+def test_shape_against_the_oracle(tmp_path_factory, shape, rank, d_in, d_outs, decode, N, prompts):
+    from oracle import preft_oracle as ora
+    from parity_util import check_guards, compare, dev_tables, lora_pools_to_device, padded
+    from test_host_rules import ask
+    rng = np.random.Generator(np.random.PCG64(rank + d_in))
+    lens = np.array(list(prompts) + [1] * decode)
+    order = rng.permutation(len(lens))
+    ids = np.concatenate([rng.integers(0, N, size=len(prompts)), rng.permutation(np.arange(decode) % N)]).astype(int)
+    tab = wl.from_lengths(lens[order], ids[order], np.where(lens > 1, lens, 0)[order])
+    T = tab.T
+    widths = list(d_outs) + [0] * (3 - len(d_outs))
+    answer = ask(tmp_path_factory, [f"small {T} {tab.S} {N} 1 {rank} {d_in} " + " ".join(map(str, widths))])[0].split()
+    takes, units, deep, waves = (int(v) for v in answer[:4])
+    assert takes == 1 and (deep, waves) == shape[:2] and units >= shape[2], answer
+    ss, sa, sp = dev_tables(tab)
+    x = wl.activations(T, d_in, "bf16", device="cuda", seed=1)
+    y0s = [wl.activations(T, n, "bf16", device="cuda", seed=2 + i) for i, n in enumerate(d_outs)]
+    pools = [wl.lora_pool(N, rank, d_in, n, "bf16", device="cuda", seed=9 + i) for i, n in enumerate(d_outs)]
+    tables = [lora_pools_to_device(pl) for pl in pools]
+    ws = preft.new_workspace(T, tab.S)
+    for mode, pos in ((preft.PREFT_ALL_TOKENS, ora.ALL_POSITIONS), (preft.PREFT_PREFILL_ONLY, ora.PROMPT_ONLY)):
+        bufs = [padded(y, 8, 7.0) for y in y0s]
+        preft.preft_lora_apply_packed([b[1] for b in bufs], x, ss, sa, sp, [t[0] for t in tables], [t[1] for t in tables], rank, 2.0, mode, ws)
+        owner = ora.positions(T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, pos)
+        for (buf, y), y0, pl in zip(bufs, y0s, pools):
+            check_guards(buf, T, y0.shape[1], 7.0)
+            want = ora.lora(y0.cpu(), x.cpu(), tab.seg_start, tab.seg_adapter, tab.seg_prefill_len,
+                            [a.cpu() for a in pl.A], [b.cpu() for b in pl.B], rank, 2.0, pos)
+            compare(y, y0, want, owner, "bf16")
