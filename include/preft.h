@@ -142,10 +142,11 @@ size_t preft_workspace_bytes(int32_t T, int32_t S);
 /*
  * Bytes of a workspace that, beyond the schedule, has room for the intermediate z = A_i x of Eq. 2 of
  * every active row: LoRA calls of up to `rank` with up to n_proj outputs per call.  A bf16 LoRA call of
- * rank 1..64 (above rank 16: d_in and every d_out a multiple of 128) on a batch of more than 1024 rows (above rank 32: at most 49 152) that is
- * handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the expand
- * in 2-D tiles -- where that is faster: wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
- * 1100), and every shape above rank 16 (up to 5x on 1100 rows).  With fewer bytes, or outside those limits,
+ * rank 1..64 (above rank 16: d_in and every d_out a multiple of 128) on a batch of more than 1024 rows (above rank 32:
+ * at most 49 152) that is handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the
+ * expand in 2-D tiles -- where that is faster: wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
+ * 1100), and every shape above rank 16 (up to 5x on 1100 rows); not on a step of decode rows that has nothing to apply.
+ * With fewer bytes, or outside those limits,
  * the same call runs in one launch.  The result is the same bit for bit.
  * The z area lies behind the schedule and is rewritten by every such call: calls that
  * share a workspace must be ordered on one stream, as they must be for the schedule already.
@@ -197,7 +198,8 @@ int preft_schedule(void *workspace, size_t workspace_bytes,
  * a few points below their neighbours), with one exception: a rank above 16 that is not a multiple
  * of 4 needs d_in and d_out to be multiples of 128 for that, and takes the slow per-row kernels
  * otherwise (an adapter of such a rank and such widths is served faster when its factors are
- * zero-padded to the next multiple of 4).  fp32 runs on the matrix cores too (fp32 products and sums).
+ * zero-padded to the next multiple of 4).  fp32 runs on the matrix cores too (fp32 products and sums), up to rank 8 on
+ * the per-row kernels where those are faster.
  * Unless mode carries PREFT_SCHEDULE_READY the call first runs the scheduler into
  * `workspace` (>= preft_workspace_bytes(T, S) bytes).
  * T == 0 or S == 0 returns PREFT_OK without launching.
@@ -220,10 +222,10 @@ int preft_lora_apply(void *y, int64_t ldy, const void *x, int64_t ldx,
  * and B_pools are HOST arrays of n_proj entries.  The outputs may be separate buffers or
  * disjoint column ranges of one buffer (a fused qkv or gate-up output: same row stride, every
  * range inside one row); any other overlap, and any overlap with x, is PREFT_EINVAL.
- * The result is that of n_proj preft_lora_apply calls.  For bf16 and rank 1..16,
- * and for rank 17..64 when every width is a multiple of 128 or the batch has at most
- * 1024 rows (and the rank is a multiple of 4), they run as one launch that reads x once; otherwise the call issues one launch per
- * projection.
+ * The result is that of n_proj preft_lora_apply calls.  For bf16 they run as one launch at rank 1..16, above it at ranks that
+ * are multiples of 4 on batches of at most 1024 rows, and on larger batches at rank 17..64 when every width is a
+ * multiple of 128; otherwise the call issues one launch per projection.  (Batches of at most 1024 rows read x once per workgroup, the
+ * others once per launch.)
  */
 int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, const int32_t *d_out,
                             const void *x, int64_t ldx, int32_t T, int32_t d_in,

@@ -165,8 +165,10 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported activation dtype {dtype}")
 
 
-def _matrix(t: torch.Tensor, name: str):
+def _matrix(t: torch.Tensor, name: str, i: int = -1):
     if t.dim() != 2 or not t.is_cuda or t.stride(1) != 1:
+        if i >= 0:
+            name = f"{name}[{i}]"
         raise ValueError(f"{name}: need a 2-D device tensor with unit column stride")
     T, d = t.shape
     return t.data_ptr(), t.stride(0), T, d
@@ -302,7 +304,7 @@ def preft_lora_apply_packed(ys: Sequence[torch.Tensor], x: torch.Tensor, seg_sta
     yp, ldy, d_out, Ap, Bp = [], [], [], [], []
     for i in range(n):
         y, A, B = ys[i], A_pools[i], B_pools[i]
-        ptr, ld, T2, d = _matrix(y, "ys")
+        ptr, ld, T2, d = _matrix(y, "ys", i)
         if T2 != T or y.dtype is not dtype:
             raise ValueError("x and every y must agree in rows and dtype")
         if A.numel() != N or B.numel() != N or A.dtype is not _INT64:
@@ -384,7 +386,7 @@ def preft_direft_apply_layers(hs: Sequence[torch.Tensor], h_layers: torch.Tensor
     hp, ldh, T, d = _matrix(hs[0], "hs[0]")
     like = (ldh, T, d)
     for i, h in enumerate(hs):
-        if _matrix(h, "hs")[1:] != like or h.dtype is not hs[0].dtype:
+        if _matrix(h, "hs", i)[1:] != like or h.dtype is not hs[0].dtype:
             raise ValueError("the residual streams must agree in shape, row stride and dtype")
     for t, name in ((h_layers, "h_layers"), (W1_pools, "W1_pools"), (W2t_pools, "W2t_pools"), (b_pools, "b_pools")):
         if t is None and name == "b_pools":

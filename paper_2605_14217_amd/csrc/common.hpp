@@ -344,7 +344,7 @@ __device__ __forceinline__ int tile_units(const ApplyArgs &p, int *n_chunk_units
 // to the 8 XCDs; an XCD has per_xcd slots).  As a rule an XCD takes a run of neighbouring units, which share an adapter's factors
 // through its L2.  A handful of short prompts breaks that up: a chunk counts 8 tiles of 16 rows, and where most of
 // them are empty the full ones gather on one or two XCDs (4 prompts of 10-14 rows and 14 decode rows: 6 tiles of 12 workgroups each on
-// 32 compute units, 20.0 us; spread 14).  Then the tiles of chunk c go to the XCDs 3 c, 3 c + 1, ... in turn (3: chunks
+// 32 compute units, 20.0 us; spread 12).  Then the tiles of chunk c go to the XCDs 3 c, 3 c + 1, ... in turn (3: chunks
 // of one to three tiles do not meet).  (Of
 // thousands of rows every XCD has enough, and sharing the factors counts: fp32, rank 96, 5000 rows 391 us in runs, 482 spread.)
 __device__ __forceinline__ int few_tiles_unit(const ApplyArgs &p, int n_chunk_units, int per_xcd, int t)

@@ -14,12 +14,10 @@
 //
 // The factors of its columns are contiguous in the [d_out, r] layout: they are fetched in whole lines and turned
 // through LDS, 32 columns at a time.  (Fetched in MFMA order, lanes of neighbouring columns, every lane is an
-// access of its own in the texture path: that path was busy 59 % of the time at rank 64, 1455 accesses per
-// wavefront, and the launch 5290 us instead of 4270.)  Two row blocks per wavefront halve the factor traffic; four
+// access of its own in the texture path: at rank 64, 89 740 rows of 2 x 28 672, 5290 us instead of 4270.)  Two row blocks per wavefront halve the factor traffic; four
 // leave too few wavefronts in flight.
-// gate+up of the 8B layer, rank 16, 36 864 rows (4.2 GB of y): 700 us = 6.0 TB/s; the column sweeps of the
-// single launch 850.  70B layer, rank 64, 89 740 rows (20.6 GB): 4270 us = 4.8 TB/s (184 registers: two wavefronts
-// per SIMD); the barrier-and-stride panel kernel before this one 5180.
+// gate+up of the 8B layer, rank 16, 36 864 rows (4.2 GB of y): 718 us = 5.9 TB/s, in a call that took 931 in one launch and takes 790.
+// 8192 -> 8192, rank 64, 35 000 rows (1.15 GB of y): 258 us = 4.4 TB/s (200 registers: two wavefronts per SIMD), rank 48 253.
 #pragma once
 #include "common.hpp"
 #include "mfma_kernel.hpp"

@@ -15,9 +15,12 @@
 // Widths are multiples of 4: pieces past the width alias the last one, are zeroed in the shrink and not stored.
 //
 // Bound: HBM in principle; in practice latency (fp32 batches are small).  Hence col_split workgroups share a tile of
-// an out-of-place call, each running the whole shrink and expanding its share of the columns.
+// an out-of-place call, each running the whole shrink and expanding its share of the columns; where few tiles of wide rows wait for
+// the chain of units all the same, the per-row kernel is taken (f32_rows_win).
 // Per-row kernel (no matrix cores, factors streamed for every 4 rows) and this one: 4096 -> 4096, rank 16, 2304 rows 80 and
-// 34 us (floor 19), 20 480 rows 508 and 205 (169); rank 64, 2304 rows 397 and 76; in place, d = 4096, rank 63 2660 and 89.
+// 32 us (floor 19), 20 480 rows 508 and 205 (169); rank 64, 2304 rows 397 and 70; in place, d = 4096, rank 63 2730 and 88.  Above rank
+// 64 the in-place form and the ranks that are no multiple of 4 spill (55-460 registers) and are still the faster ones: in place, d =
+// 4096, 2304 rows, rank 127 5780 and 373, rank 100, 1024 -> 1024 960 and 35, 24 rows of d = 4832, rank 96 550 and 168.
 // Relative error against 64 bits 1.5e-7 and 1.1e-7 (rank 16), 1.6e-7 and 1.2e-7 (rank 64).
 #pragma once
 #include "common.hpp"
@@ -36,7 +39,6 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
 {
     constexpr int WAVES = F32_WAVES;
     constexpr bool AHEAD = NB <= 2;                           // register budget: factors requested a unit ahead, or block by block
-    constexpr bool AGAIN = true;                              // x is read by the workgroups that share the tile, or again in place
     __shared__ __attribute__((aligned(16))) char lds[f32_red_bytes(NB) > f32_turn_bytes() ? f32_red_bytes(NB) : f32_turn_bytes()];
 
     if (!schedule_matches(p)) return;
@@ -97,7 +99,7 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
         auto load = [&](u32x4_t (&xr)[4], u32x4_t (&ar)[NA][4], int u) {
             const int off = min(u * 256 + c16 * 16, last);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) xr[i] = ld16_first<AGAIN>(xu[i] + off);
+            for (int i = 0; i < 4; ++i) xr[i] = ld16(xu[i] + off);      // read again by the workgroups that share the tile, or in place
             if constexpr (AHEAD) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) load_a(ar[b], b, u);
@@ -176,11 +178,10 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
             for (int s = 0; s < 4; ++s) load_w(wr[s], u, s);
         }
     };
-    constexpr bool EARLY = AHEAD;
 
     // ---------------------------------------------------------------- sum over the wavefronts
     float z[NB][4];
-    if (EARLY && ubase + wave < uend) load_yw(y0, w0, ubase + wave);
+    if (AHEAD && ubase + wave < uend) load_yw(y0, w0, ubase + wave);
     __syncthreads();                                          // the turn buffers become the sum's area
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -256,7 +257,7 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
         }
     };
     int u = ubase + wave;
-    if (!EARLY && u < uend) load_yw(y0, w0, u);
+    if (!AHEAD && u < uend) load_yw(y0, w0, u);
     while (u < uend) {
         if (u + WAVES < uend) load_yw(y1, w1, u + WAVES);
         finish(y0, w0, u);

@@ -1,7 +1,7 @@
 // Per-row ("batched gather matrix-vector") kernel: one workgroup applies one adapter to a group
 // of at most GROUP_ROWS rows that share it.
 //
-// This is the generic fallback for what the tile kernels do not cover (fp32 of rank 1-4 on a handful of rows;
+// This is the generic fallback for what the tile kernels do not cover (fp32 of rank 1-8 where few tiles meet wide rows;
 // bf16 ranks that are neither <= 8 nor multiples of 4): a chunk is cut into groups of consecutive
 // rows, and the short rows (decode tokens of the all-position baseline, segments with at most
 // SHORT_ROWS active rows), which the scheduler has sorted by adapter and cut into gathered tiles,

@@ -896,9 +896,9 @@ TWO_LAUNCH_CASES = [
 
 @pytest.mark.parametrize("rank,d_in,d_outs", TWO_LAUNCH_CASES, ids=[f"r{c[0]}-{c[1]}-{'x'.join(map(str, c[2]))}" for c in TWO_LAUNCH_CASES])
 def test_two_launch_lora_equals_the_single_launch_and_the_oracle(rank, d_in, d_outs):
-    """A workspace with room for z (preft_workspace_bytes_z) lets a LoRA call at rank 20..64 run its
+    """A workspace with room for z (preft_workspace_bytes_z) lets a LoRA call at rank 1..64 run its
     shrink and its expand as two launches, the expand in 2-D tiles (single and packed calls; by itself on
-    batches of 8192 to 131072 rows -- the full-size tests have such cases -- and here, on a smaller batch,
+    batches of more than 1024 rows where that is faster -- the full-size tests have such cases -- and here
     by test flag).  The result must equal the small workspace's bit for bit (same arithmetic, same
     order), both must match the oracle, in both modes; the guard columns of the buffer and every
     inactive row stay untouched."""
