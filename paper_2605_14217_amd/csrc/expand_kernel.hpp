@@ -17,7 +17,7 @@
 // access of its own in the texture path: at rank 64, 89 740 rows of 2 x 28 672, 5290 us instead of 4270.)  Two row blocks per wavefront halve the factor traffic; four
 // leave too few wavefronts in flight.
 // gate+up of the 8B layer, rank 16, 36 864 rows (4.2 GB of y): 718 us = 5.9 TB/s, in a call that took 931 in one launch and takes 790.
-// 8192 -> 8192, rank 64, 35 000 rows (1.15 GB of y): 258 us = 4.4 TB/s (200 registers: two wavefronts per SIMD), rank 48 253.
+// Rank 33-64: panel_expand_kernel below, this one where its panels do not fit the widths or the rank is no multiple of 4.
 #pragma once
 #include "common.hpp"
 #include "mfma_kernel.hpp"
@@ -38,11 +38,11 @@ struct ExpandTiles {
     uint32_t n_ids, per_xcd;
 };
 
-template <int R>
+template <int R, int COLS = EXPAND_WAVES * 128>
 __device__ __forceinline__ ExpandTiles expand_tiles(const ApplyArgs &p, int n_slices)
 {
     ExpandTiles t;
-    auto panels_of = [](int d) { return (d + EXPAND_WAVES * 128 - 1) / (EXPAND_WAVES * 128); };
+    auto panels_of = [](int d) { return (d + COLS - 1) / COLS; };
     t.pan0 = panels_of(p.d_out);
     t.pan1 = n_slices > 1 ? panels_of(p.more[0].d_out) : 0;
     t.panels = t.pan0 + t.pan1 + (n_slices > 2 ? panels_of(p.more[1].d_out) : 0);
@@ -249,6 +249,117 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
                 if (col_ok && mb * 16 + 4 * i + q < n_rows) st16_stream(yc + (row[mb][i] * ldy_b + c16 * 16), o);
             }
         }
+    }
+}
+
+// The same in tiles of 16 RW rows x 128 PU columns whose factors the RW wavefronts share through LDS (rank 33-64 in multiples of 4, widths
+// multiples of 128 PU; chunks only).  At rank 64 a wavefront of mfma_expand_kernel holds the factors of its own columns on their way, 200 registers
+// and two wavefronts per SIMD, and every 32 rows fetch the factors again: too little y in flight (8B layer's o, 38 400 rows: 147 us =
+// 4.3 TB/s).  Shared by 64 rows they take half the traffic and 16 pieces a lane: 154 registers, 52 KB of LDS, three workgroups per compute
+// unit, which also hide the barrier.  Whole calls, rank 64, mfma_expand_kernel / this one, us: 4096 -> 4096, 1400 rows 46 / 46, 38 000 rows 227 / 208;
+// 4096 -> 2 x 14336, 1400 rows 81 / 78, 38 000 rows 1031 / 923; 8192 -> 8192, 45 000 rows 484 / 444; 1024 -> 1024 69 / 67; rank 52
+// alike.  Tiles in memory order; dealt to the XCDs as runs 977 for the 923, 65 for the 67.
+constexpr int PANEL_RW = 4, PANEL_PU = 2;
+
+template <int NB, int RW, int PU>
+__global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, int n_slices)
+{
+    constexpr int R = 16 * RW, NT = RW * 64;
+    constexpr int W_ITERS = NB * 16 * 16 * PU / NT;           // 16 r PU pieces, r <= 16 NB
+    static_assert(CHUNK_ROWS % R == 0, "tile height must divide the chunk height");
+    __shared__ u32x4_t turn[RW][16 * MFMA_TRS];
+    __shared__ __attribute__((aligned(16))) char fac[PU * 128 * (32 * NB + 8)];      // column c at byte c (2 r + 8)
+
+    if (!schedule_matches(p)) return;
+    const int rb = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int rl = lane & 15, g = lane >> 4;                  // MFMA order
+    const int q = lane >> 4, c16 = lane & 15;                 // unit load order
+    const int r = p.rank, cs = 2 * r + 8;
+    u32x4_t *tr = turn[rb];
+
+    const ExpandTiles tiles = expand_tiles<R, PU * 128>(p, n_slices);
+    for (uint32_t slot = blockIdx.x; slot < tiles.per_xcd * 8; slot += gridDim.x) {
+        ExpandTile t;
+        if (!expand_tile<R>(p, tiles, slot, t)) continue;     // uniform over the workgroup
+        const int c0 = t.panel * PU * 128;
+
+        // every request of the tile first: its factors, this row block's z, its units of y (rows past the tile alias its last one)
+        gcptr_t Wp = as_global(as_const(t.Bt_pool)[t.entry.x]) + (int64_t)c0 * r * 2;
+        const int w_last = 16 * r * PU - 1;                   // the panel's last piece: lanes past it take it again
+        u32x4_t W[W_ITERS];
+#pragma unroll
+        for (int j = 0; j < W_ITERS; ++j) W[j] = ld16(Wp + (uint32_t)(min((int)threadIdx.x + j * NT, w_last) * 16));
+        const int rank_blocks = z_rank_blocks(r);             // 33..48: the fourth block is padding, z = 0
+        const int zrb = rb * 16 < t.n_rows ? rb : 0;          // row blocks past the tile: any z will do
+        gcptr_t zb = as_global(p.zws) + (z_piece(t.block0 + zrb, n_slices, t.sl, rank_blocks, 0) + lane) * 16;
+        bf16x8_t zop[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            u32x4_t zv = ld16(zb + (b < NB - 1 ? b : rank_blocks - 1) * 1024);
+            if (b == NB - 1) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) zv[k] = rank_blocks == NB ? zv[k] : 0u;
+            }
+            zop[b] = as_bf16x8(zv);
+        }
+        gptr_t yu[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            yu[i] = as_global(t.y) + ((int64_t)t.entry.y + t.row0 + min(rb * 16 + 4 * i + q, t.n_rows - 1)) * t.ldy_b + (int64_t)c0 * 2 + c16 * 16;
+        u32x4_t Y[PU][4];
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Y[u][i] = ld16_stream(yu[i] + u * 256);
+
+        // factors to LDS: two 8-byte halves per piece, neither straddles a column (r % 4 == 0)
+#pragma unroll
+        for (int j = 0; j < W_ITERS; ++j) {
+            const int piece = min((int)threadIdx.x + j * NT, w_last);
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                const int byte = piece * 16 + hh * 8;
+                *reinterpret_cast<u32x2_t *>(fac + byte + byte / (2 * r) * 8) = u32x2_t{W[j][2 * hh], W[j][2 * hh + 1]};
+            }
+        }
+        __syncthreads();
+
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+            u32x4_t yop[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[u][i];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) yop[s] = tr[rl * MFMA_TRS + 4 * s + g];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                f32x4_t d[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {                 // columns 2m + e of the step, as in mfma_expand_kernel
+                    d[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const int rank0 = 16 * b + 4 * g;
+                        const u32x2_t w = *reinterpret_cast<const u32x2_t *>(fac + (u * 128 + s * 32 + 2 * rl + e) * cs + (rank0 < r ? rank0 : 0) * 2);
+                        d[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), zop[b], d[e], 0, 0, 0);
+                    }
+                }
+                const u32x4_t yv = yop[s];
+                float out[8];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    out[2 * v]     = bf16_lo(yv[v]) + d[0][v];
+                    out[2 * v + 1] = bf16_hi(yv[v]) + d[1][v];
+                }
+                tr[rl * MFMA_TRS + 4 * s + g] = Elem<bf16_tag>::pack(out);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const u32x4_t o = tr[(4 * i + q) * MFMA_TRS + c16];
+                if (rb * 16 + 4 * i + q < t.n_rows) st16_stream(yu[i] + u * 256, o);
+            }
+        }
+        __syncthreads();                                      // the next tile's factors overwrite this one's
     }
 }
 

@@ -29,6 +29,7 @@ FAMILIES = {            # kernel template -> (header, rough relative compile cos
     "preft::small_tile_kernel": ("small_kernel.hpp", 3),
     "preft::small_tile_layers_kernel": ("small_kernel.hpp", 3),
     "preft::mfma_expand_kernel": ("expand_kernel.hpp", 1),
+    "preft::panel_expand_kernel": ("expand_kernel.hpp", 1),
     "preft::thin_expand_kernel": ("expand_kernel.hpp", 1),
     "preft::mfma_tile_kernel": ("mfma_kernel.hpp", 2),
     "preft::mfma_tile_layers_kernel": ("mfma_kernel.hpp", 2),

@@ -251,18 +251,17 @@ inline bool wide_widths_ok(const ApplyArgs &a, int cw)
 // The expand launch of a call whose z is in the workspace: a workgroup per 32 rows x 512 columns.
 constexpr int EXPAND_MB = 2;
 
-inline int64_t expand_panels(const ApplyArgs &a, int n_slices)
+inline int64_t expand_panels(const ApplyArgs &a, int n_slices, int64_t cols)
 {
-    constexpr int64_t COLS = EXPAND_WAVES * 128;
-    int64_t panels = (a.d_out + COLS - 1) / COLS;
-    for (int i = 1; i < n_slices; ++i) panels += (a.more[i - 1].d_out + COLS - 1) / COLS;
+    int64_t panels = (a.d_out + cols - 1) / cols;
+    for (int i = 1; i < n_slices; ++i) panels += (a.more[i - 1].d_out + cols - 1) / cols;
     return panels;
 }
 
 // the kernel numbers its tiles in 32 bits
 inline bool expand_ids_fit(const ApplyArgs &a, int64_t S, int n_slices)
 {
-    return tile_grid(a, S, 16 * EXPAND_MB) * expand_panels(a, n_slices) < ((int64_t)1 << 31);
+    return tile_grid(a, S, 16 * EXPAND_MB) * expand_panels(a, n_slices, EXPAND_WAVES * 128) < ((int64_t)1 << 31);
 }
 
 // Rows that do not start on 128-byte lines: neighbouring panels share lines, so they go to one XCD.
@@ -273,15 +272,17 @@ bool rows_off_lines(const ApplyArgs &a, int n_slices)
     return off;
 }
 
-void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
+// a workgroup of four wavefronts for every tile of `height` rows x `cols` columns
+void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S, int n_slices, hipStream_t stream,
+                          int height = 16 * EXPAND_MB, int cols = EXPAND_WAVES * 128)
 {
     a.xcd_runs = rows_off_lines(a, n_slices);
     // More tiles than the likely rows fill are likely to be empty, and an empty workgroup is not free (3584 decode rows, prompt
     // positions, 8192 -> 2 x 28672: 22 848 of them 23 us): the kernel strides over what exceeds the grid (and over what would
     // exceed the 2^32 work items of a launch)
     const int64_t rows = a.all_tokens && !a.chunks_only ? a.T : prompt_rows(a, S);
-    const int64_t bound = tile_grid(a, S, 16 * EXPAND_MB), likely = rows / (16 * EXPAND_MB) * 5 / 4 + (rows / 8 < 64 ? rows / 8 + 1 : 64);
-    const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices), most = (int64_t)1 << 23;
+    const int64_t bound = tile_grid(a, S, height), likely = rows / height * 5 / 4 + (rows / 8 < 64 ? rows / 8 + 1 : 64);
+    const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices, cols), most = (int64_t)1 << 23;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(EXPAND_WAVES * 64), 0, stream, a, n_slices);
 }
 
@@ -301,7 +302,7 @@ void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stre
 //     4096 -> 2 x 14336: 1500 rows 62-82 -> 39-44, 42 000 rows 1030 -> 864; q+k+v of 8192, 350 000 rows 3556-3676 -> 3218-3407;
 //     1024 -> 1024 + 2 x 512, 140 000 rows 258-265 -> 255-293; rows off 128-byte lines, 1024 -> 2728 10-11 -> 12-13,
 //     2000 -> 3208, 11 200 rows 42-44 -> 50, but several outputs off lines, 4096 -> 9640 + 296, 1500 rows 26 -> 18.
-//   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 518 -> 454; rank 32 86 -> 48,
+//   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 518 -> 454 (panel_expand_kernel: 3 to 9 % less); rank 32 86 -> 48,
 //     105 -> 97, 355 -> 372.
 //   decode rows alone, 7 per adapter (gathered tiles), rank 16, 8192 -> 8192: 1200 rows 30 -> 35, 3584 rows 89 -> 89;
 //     one per adapter 87 -> 109.
@@ -335,6 +336,15 @@ bool column_groups_fit(const ApplyArgs &a, int n_slices)
     return fit;
 }
 
+// Whether the expand launch of rank 33-64 (multiples of 4) takes panel_expand_kernel: every output a whole number of its panels.  It has
+// three wavefronts per SIMD where mfma_expand_kernel has registers for two; no size has been seen where it is the slower one (its figures).
+bool panels_fit(const ApplyArgs &a, int n_slices)
+{
+    bool fit = (a.d_out % (PANEL_PU * 128)) == 0;
+    for (int i = 1; i < n_slices; ++i) fit = fit && (a.more[i - 1].d_out % (PANEL_PU * 128)) == 0;
+    return fit;
+}
+
 // rank 17..64: the row-split kernel's shrink sweep of the chunks, then their expand launch
 template <int NB, int SLICES>
 bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream_t stream)
@@ -352,6 +362,12 @@ bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream
         if (column_groups_fit(a, SLICES)) shrink = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, false, true>;
     }
     hipLaunchKernelGGL(shrink, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
+    if constexpr (NB == 4) {
+        if (panels_fit(a, SLICES)) {
+            launch_expand_kernel(panel_expand_kernel<NB, PANEL_RW, PANEL_PU>, a, S, SLICES, stream, 16 * PANEL_RW, 128 * PANEL_PU);
+            return true;
+        }
+    }
     launch_expand<NB, false>(a, S, SLICES, stream);
     return true;
 }

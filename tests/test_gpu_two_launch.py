@@ -17,7 +17,9 @@ LENS = [1, 15, 16, 17, 31, 32, 33, 5, 0, 127, 128, 129, 4, 560] + [1] * 40
 CASES = [(1, 512, (512,)), (1, 136, (1032, 8, 520)), (2, 1096, (2056, 384)), (3, 1000, (520, 8)), (3, 4104, (136, 520, 1024)), (4, 128, (128, 1032, 512)), (5, 264, (640,)), (7, 1000, (2728, 2728)),
          (8, 136, (1544,)), (12, 520, (504, 512)), (16, 4104, (512,)), (16, 512, (1536, 256, 256)), (13, 384, (1288, 24, 512)),
          (17, 128, (128,)), (20, 256, (512, 256)), (24, 256, (384,)), (32, 512, (256, 128)), (28, 1024, (512, 640, 256)), (31, 384, (512, 128, 256)), (36, 128, (1152,)), (48, 256, (512,)),
-         (63, 256, (640, 512)), (64, 128, (128, 1664))]
+         (63, 256, (640, 512)), (64, 128, (128, 1664)),
+         # panels of 64 rows x 256 columns that share their factors (rank 33-64 in multiples of 4, every width a multiple of 256)
+         (36, 384, (256,)), (40, 128, (512, 256)), (48, 256, (768, 256, 1024)), (52, 128, (256, 1280)), (60, 640, (512,)), (64, 128, (256, 512, 256)), (64, 1024, (1536,))]
 
 
 @pytest.mark.parametrize("pad", [0, 8])
