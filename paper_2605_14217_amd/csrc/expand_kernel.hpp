@@ -255,10 +255,11 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
 // The same in tiles of 16 RW rows x 128 PU columns whose factors the RW wavefronts share through LDS (rank 33-64 in multiples of 4, widths
 // multiples of 128 PU; chunks only).  At rank 64 a wavefront of mfma_expand_kernel holds the factors of its own columns on their way, 200 registers
 // and two wavefronts per SIMD, and every 32 rows fetch the factors again: too little y in flight (8B layer's o, 38 400 rows: 147 us =
-// 4.3 TB/s).  Shared by 64 rows they take half the traffic and 16 pieces a lane: 154 registers, 52 KB of LDS, three workgroups per compute
+// 4.3 TB/s).  Shared by 64 rows they take half the traffic and 8 pieces a lane: 163 registers, 52 KB of LDS, three workgroups per compute
 // unit, which also hide the barrier.  Whole calls, rank 64, mfma_expand_kernel / this one, us: 4096 -> 4096, 1400 rows 46 / 46, 38 000 rows 227 / 208;
 // 4096 -> 2 x 14336, 1400 rows 81 / 78, 38 000 rows 1031 / 923; 8192 -> 8192, 45 000 rows 484 / 444; 1024 -> 1024 69 / 67; rank 52
 // alike.  Tiles in memory order; dealt to the XCDs as runs 977 for the 923, 65 for the 67.
+// Short prompts, 4096 -> 2 x 14336: 120 of 10-16 rows 161 / 153, 200 of 20-60 360 / 317, 60 of 33-34 148 / 131, 40 of 20 93 / 99.
 constexpr int PANEL_RW = 4, PANEL_PU = 2;
 
 template <int NB, int RW, int PU>
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, i
     __shared__ __attribute__((aligned(16))) char fac[PU * 128 * (32 * NB + 8)];      // column c at byte c (2 r + 8)
 
     if (!schedule_matches(p)) return;
-    const int rb = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int rb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int rl = lane & 15, g = lane >> 4;                  // MFMA order
     const int q = lane >> 4, c16 = lane & 15;                 // unit load order
     const int r = p.rank, cs = 2 * r + 8;
@@ -306,11 +307,14 @@ __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, i
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             yu[i] = as_global(t.y) + ((int64_t)t.entry.y + t.row0 + min(rb * 16 + 4 * i + q, t.n_rows - 1)) * t.ldy_b + (int64_t)c0 * 2 + c16 * 16;
+        const bool mine = rb * 16 < t.n_rows;                 // a short prompt's tile: its other wavefronts only bring factors
         u32x4_t Y[PU][4];
+        if (mine) {
 #pragma unroll
-        for (int u = 0; u < PU; ++u)
+            for (int u = 0; u < PU; ++u)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) Y[u][i] = ld16_stream(yu[i] + u * 256);
+                for (int i = 0; i < 4; ++i) Y[u][i] = ld16_stream(yu[i] + u * 256);
+        }
 
         // factors to LDS: two 8-byte halves per piece, neither straddles a column (r % 4 == 0)
 #pragma unroll
@@ -326,6 +330,7 @@ __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, i
 
 #pragma unroll
         for (int u = 0; u < PU; ++u) {
+            if (!mine) break;
             u32x4_t yop[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[u][i];

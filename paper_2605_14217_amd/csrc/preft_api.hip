@@ -337,7 +337,7 @@ bool column_groups_fit(const ApplyArgs &a, int n_slices)
 }
 
 // Whether the expand launch of rank 33-64 (multiples of 4) takes panel_expand_kernel: every output a whole number of its panels.  It has
-// three wavefronts per SIMD where mfma_expand_kernel has registers for two; no size has been seen where it is the slower one (its figures).
+// three wavefronts per SIMD where mfma_expand_kernel has registers for two; hardly a batch has been seen where it is the slower one (its figures).
 bool panels_fit(const ApplyArgs &a, int n_slices)
 {
     bool fit = (a.d_out % (PANEL_PU * 128)) == 0;
