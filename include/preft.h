@@ -142,8 +142,8 @@ size_t preft_workspace_bytes(int32_t T, int32_t S);
 /*
  * Bytes of a workspace that, beyond the schedule, has room for the intermediate z = A_i x of Eq. 2 of
  * every active row: LoRA calls of up to `rank` with up to n_proj outputs per call.  A bf16 LoRA call of
- * rank 1..64 (above rank 16: d_in and every d_out a multiple of 128) on a batch of more than 1024 rows (above rank 32:
- * at most 49 152) that is handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the
+ * rank 1..64 (above rank 16: d_in and every d_out a multiple of 128) on a batch of more than 1024 rows
+ * that is handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the
  * expand in 2-D tiles -- where that is faster: wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
  * 1100), and every shape above rank 16 (up to 5x on 1100 rows); not on a step of decode rows that has nothing to apply.
  * With fewer bytes, or outside those limits,

@@ -12,12 +12,15 @@
 // workgroup takes one tile of 16 MB rows x 512 columns and ends, tiles of a row block side by side, and every
 // request of the tile is issued before anything is computed.  A wavefront takes 128 columns and needs no barrier.
 //
-// The factors of its columns are contiguous in the [d_out, r] layout: they are fetched in whole lines and turned
-// through LDS, 32 columns at a time.  (Fetched in MFMA order, lanes of neighbouring columns, every lane is an
-// access of its own in the texture path: at rank 64, 89 740 rows of 2 x 28 672, 5290 us instead of 4270.)  Two row blocks per wavefront halve the factor traffic; four
-// leave too few wavefronts in flight.
-// gate+up of the 8B layer, rank 16, 36 864 rows (4.2 GB of y): 718 us = 5.9 TB/s, in a call that took 931 in one launch and takes 790.
-// Rank 33-64: panel_expand_kernel below, this one where its panels do not fit the widths or the rank is no multiple of 4.
+// z is the first operand of the MFMAs and the factors are the second: lane (n, g) of MFMA k then ends up with column 8 n + k of the rows
+// 4 g .. 4 g + 3, the eight MFMAs of a 128-column unit with the 8 consecutive columns of those rows -- what the lane loads of y
+// in 256-byte row pieces.  So y passes through registers only.  (Factors first, as in the kernels with both sweeps, leaves a lane
+// the columns of one row, 64 bytes beside its neighbour's, and y goes through LDS on its way in and out: 2/3 of the LDS traffic,
+// and its buffers.)  The factors are contiguous in the [d_out, r] layout: fetched in whole lines, turned through LDS.  (Fetched in
+// MFMA order every lane is an access of its own in the texture path: at rank 64, 89 740 rows of 2 x 28 672, 5290 us instead of 4270.)
+// Two row blocks per wavefront halve the factor traffic; four leave too few wavefronts in flight.
+// gate+up of the 8B layer, rank 16, 36 864 rows (4.2 GB of y), whole call: one launch 931 us, y turned through LDS 801, now 783 = 5.8 TB/s.
+// Rank 33-64: panel_expand_kernel below.
 #pragma once
 #include "common.hpp"
 #include "mfma_kernel.hpp"
@@ -26,10 +29,41 @@ namespace preft {
 
 constexpr int EXPAND_WAVES = 4;                               // 128-column units (one per wavefront) of a workgroup
 
-// LDS of a wavefront: one 16-row turn buffer, and the factors of 32 columns.  A column's factors are padded by
-// 8 bytes so that the 16 columns of an MFMA operand read spread over all banks; ranks that are not multiples of 4
-// lie as in memory (a lane then shifts its four factors into place and may look one word past them).
-constexpr int expand_fac_bytes(int NB) { return 32 * (32 * NB + 8) + 16; }
+// Factors in LDS, 128 columns at a time.  MFMA k takes the columns 8 n + k, n = 0 .. 15 (a lane then ends up with the 8 consecutive
+// columns that it loaded, see below), so those lie side by side: column c in group c % 8, at place c / 8 of it.  A column takes
+// 2 or 6 words modulo 8, so that the 16 columns of an operand read fall on different banks, and a group of them 2 words modulo
+// 32, which spreads the writes.  Ranks that are not multiples of 4 lie as in memory (a lane then shifts its
+// four factors into place and may look one word past them).
+template <int NB>
+struct FactorLds {
+    static constexpr int GROUP = 16 * (32 * NB + 8) + 8, BYTES = 8 * GROUP + 16;
+    int r4, column;                                           // quarters of 4 factors, and bytes, of a column
+    float inv;
+    __device__ __forceinline__ explicit FactorLds(int r) : r4(r >> 2), column(2 * r + (r % 8 ? 0 : 8)), inv(4.0f / (float)r) {}
+    // where quarter i of a contiguous [128][r] block goes.  (i + 0.5) / r4 is below 128 and at least 0.5 / 16 away from a
+    // whole number: the rounding of the product, below 1e-4, never reaches one.
+    __device__ __forceinline__ int quarter(int i) const
+    {
+        const int c = (int)(((float)i + 0.5f) * inv);
+        return (c & 7) * GROUP + (c >> 3) * column + (i - c * r4) * 8;
+    }
+    // what lane (n16, g) brings to MFMA k of rank block b: the factors 16 b + 4 g .. + 3 of column 8 n16 + k (of ranks that do not
+    // exist others, or zeros: their z is zero)
+    template <bool ODD>
+    __device__ __forceinline__ u32x2_t operand(const char *fac, int k, int b, int n16, int g, int r) const
+    {
+        const int rank0 = 16 * b + 4 * g, n = r - rank0;      // n: how many of the lane's four ranks exist
+        if constexpr (ODD) {
+            const uint32_t m01 = n >= 2 ? 0xffffffffu : n == 1 ? 0xffffu : 0u, m23 = n >= 4 ? 0xffffffffu : n == 3 ? 0xffffu : 0u;
+            const int at = (8 * n16 + k) * r + (n > 0 ? rank0 : 0);
+            const uint32_t *w3 = reinterpret_cast<const uint32_t *>(fac) + (at >> 1);
+            const uint32_t sh = (at & 1) * 16, d0 = w3[0], d1 = w3[1], d2 = w3[2];
+            return u32x2_t{__builtin_amdgcn_alignbit(d1, d0, sh) & m01, __builtin_amdgcn_alignbit(d2, d1, sh) & m23};
+        } else {
+            return *reinterpret_cast<const u32x2_t *>(fac + k * GROUP + n16 * column + (n > 0 ? rank0 : 0) * 2);
+        }
+    }
+};
 
 // The tiles of an expand launch: column panels (those of the first output, then those of the others) of row blocks, ids in
 // memory order.
@@ -92,25 +126,25 @@ __device__ __forceinline__ bool expand_tile(const ApplyArgs &p, const ExpandTile
 }
 
 template <int NB, int MB, bool ODD>
-__global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(ApplyArgs p, int n_slices)
+__global__ __launch_bounds__(EXPAND_WAVES * 64, 4) void mfma_expand_kernel(ApplyArgs p, int n_slices)
 {
     constexpr int R = 16 * MB;
-    static_assert(CHUNK_ROWS % R == 0, "tile height must divide the chunk height");
-    __shared__ u32x4_t turn[EXPAND_WAVES][16 * MFMA_TRS];
-    __shared__ __attribute__((aligned(16))) char fac[EXPAND_WAVES][expand_fac_bytes(NB)];
+    static_assert(CHUNK_ROWS % R == 0 && NB <= 2, "tile height must divide the chunk height; rank blocks as in z_rank_blocks");
+    __shared__ __attribute__((aligned(16))) char fac[EXPAND_WAVES][FactorLds<NB>::BYTES];
 
     if (!schedule_matches(p)) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int rl = lane & 15, g = lane >> 4;                  // MFMA order
-    const int q = lane >> 4, c16 = lane & 15;                 // unit load order
+    const int wave = threadIdx.x >> 6;
     const int r = p.rank;
-    u32x4_t *tr = turn[wave];
     char *fw = fac[wave];
 
     const ExpandTiles tiles = expand_tiles<R>(p, n_slices);
     for (uint32_t slot = blockIdx.x; slot < tiles.per_xcd * 8; slot += gridDim.x) {
         ExpandTile t;
         if (!expand_tile<R>(p, tiles, slot, t)) continue;
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));                        // recomputed for every tile: what hangs on the lane would fill the registers
+        const int n16 = lane & 15, g = lane >> 4;             // columns 8 n16 .. + 7 of the unit, rows 4 g .. + 3 of a block
+        const FactorLds<NB> fl(r);
         const int4 entry = t.entry;
         const int row0 = t.row0, n_rows = t.n_rows, sl = t.sl, d_out = t.d_out;
         const bool gathered = t.gathered;
@@ -120,104 +154,70 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
         if (c0 >= d_out) continue;
 
         // Every request of the tile at once, none of them conditional on the lane: row slots past the tile alias
-        // its last row, columns past the width the last ones, factor pieces past a column group's end its last
+        // its last row, columns past the width the last ones, factor pieces past the width its last
         // piece.  Only the stores are masked.
-        int32_t row[MB][4];
-        const bool col_ok = c0 + c16 * 8 < d_out;             // d_out % 8 == 0: a lane's 8 columns exist or not
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) row[mb][i] = entry.y + row0 + min(mb * 16 + 4 * i + q, n_rows - 1);
-        if (gathered) {
+        const bool col_ok = c0 + n16 * 8 < d_out;             // d_out % 8 == 0: a lane's 8 columns exist or not
+        const int rows_left = col_ok ? n_rows - 4 * g : 0;    // the rows mb * 16 + v below that are the lane's to store
+        gptr_t yp[MB][4];
+        {
+            int32_t row[MB][4];
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) row[mb][i] = p.shorts[row[mb][i]].y;
+                for (int v = 0; v < 4; ++v) row[mb][v] = entry.y + row0 + min(mb * 16 + 4 * g + v, n_rows - 1);
+            if (gathered) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) row[mb][v] = p.shorts[row[mb][v]].y;
+            }
+            gptr_t yc = as_global(t.y) + (int64_t)c0 * 2;       // uniform
+            const int y_col = (col_ok ? n16 * 8 : d_out - 8 - c0) * 2;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) yp[mb][v] = yc + (row[mb][v] * ldy_b + y_col);
         }
-        u32x4_t Y[MB][4];
-        gptr_t yc = as_global(t.y) + (int64_t)c0 * 2;           // uniform
-        const int y_col = (col_ok ? c16 * 8 : d_out - 8 - c0) * 2;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Y[mb][i] = ld16_stream(yc + (row[mb][i] * ldy_b + y_col));
-        // factors of the 32 columns of step s: 4 r contiguous 16-byte pieces, of which this lane takes lane + 64 j
+        // factors of the unit's 128 columns: 16 r contiguous 16-byte pieces, of which this lane takes lane + 64 j
         // (lanes past them the last one)
         gcptr_t Wp = as_global(as_const(Bt_pool)[entry.x]) + (int64_t)c0 * r * 2;
         const int w_last = last_factor_piece(d_out - c0, 128, r);            // last piece that exists, from column c0 on
-        constexpr int AHEAD = NB >= 4 ? 2 : 4;                // register budget
-        u32x4_t W[4][NB];
-        auto load_w = [&](int s) {
+        u32x4_t W[4 * NB];
 #pragma unroll
-            for (int j = 0; j < NB; ++j) W[s][j] = ld16(Wp + (uint32_t)(min(s * 4 * r + min(lane + 64 * j, 4 * r - 1), w_last) * 16));
-        };
-#pragma unroll
-        for (int s = 0; s < AHEAD; ++s) load_w(s);
+        for (int j = 0; j < 4 * NB; ++j) W[j] = ld16(Wp + (uint32_t)(min(min(lane + 64 * j, 16 * r - 1), w_last) * 16));
         bf16x8_t zop[MB][NB];
-        const int rank_blocks = NB < 4 ? NB : z_rank_blocks(r);              // 33..48: the fourth block is padding, z = 0
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const int m = mb * 16 < n_rows ? mb : 0;          // row blocks past the tile: any z will do
-            gcptr_t zb = as_global(p.zws) + (z_piece(block0 + m, n_slices, sl, rank_blocks, 0) + lane) * 16;
+            gcptr_t zb = as_global(p.zws) + (z_piece(block0 + m, n_slices, sl, NB, 0) + lane) * 16;
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                u32x4_t zv = ld16(zb + (NB < 4 || b < 3 ? b : rank_blocks - 1) * 1024);
-                if (NB == 4 && b == 3) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) zv[k] = rank_blocks > 3 ? zv[k] : 0u;
-                }
-                zop[mb][b] = as_bf16x8(zv);
-            }
+            for (int b = 0; b < NB; ++b) zop[mb][b] = as_bf16x8(ld16(zb + b * 1024));
         }
-        // where the pieces land in LDS: two 8-byte halves, neither straddles a column (multiples of 4)
-        int w_dst[NB][2];
+        u32x4_t Y[MB][4];
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int byte = min(lane + 64 * j, 4 * r - 1) * 16 + hh * 8;
-                w_dst[j][hh] = ODD ? byte : byte + byte / (2 * r) * 8;
-            }
+            for (int v = 0; v < 4; ++v) Y[mb][v] = ld16_stream(yp[mb][v]);
 
-        // to MFMA order: lane (row rl, g) holds columns 8g .. 8g+7 of step s
-        u32x4_t yop[MB][4];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[mb][i];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) yop[mb][s] = tr[rl * MFMA_TRS + 4 * s + g];
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                if constexpr (ODD) {
-                    *reinterpret_cast<u32x4_t *>(fw + w_dst[j][0]) = W[s][j];
-                } else {
-                    *reinterpret_cast<u32x2_t *>(fw + w_dst[j][0]) = u32x2_t{W[s][j][0], W[s][j][1]};
-                    *reinterpret_cast<u32x2_t *>(fw + w_dst[j][1]) = u32x2_t{W[s][j][2], W[s][j][3]};
-                }
+        for (int j = 0; j < 4 * NB; ++j) {
+            const int piece = min(lane + 64 * j, 16 * r - 1);
+            if constexpr (ODD) {
+                *reinterpret_cast<u32x4_t *>(fw + piece * 16) = W[j];
+            } else {                                          // two 8-byte halves, neither straddles a column
+                *reinterpret_cast<u32x2_t *>(fw + fl.quarter(2 * piece)) = u32x2_t{W[j][0], W[j][1]};
+                *reinterpret_cast<u32x2_t *>(fw + fl.quarter(2 * piece + 1)) = u32x2_t{W[j][2], W[j][3]};
             }
-            if (s + AHEAD < 4) load_w(s + AHEAD);
-            // MFMA e takes columns 2m + e of the step: lane (row, g) owns outputs 8g + 2v + e
+        }
+        // z as the first operand, the factors as the second: lane (n16, g) of MFMA k ends up with column 8 n16 + k of the rows
+        // 4 g .. 4 g + 3 -- the elements it has loaded, so y needs no turn through LDS on its way in or out
+#pragma unroll
+        for (int k2 = 0; k2 < 4; ++k2) {
             u32x2_t w[2][NB];
 #pragma unroll
             for (int e = 0; e < 2; ++e)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const int rank0 = 16 * b + 4 * g, n = r - rank0;      // n: how many of the lane's four ranks exist
-                    if constexpr (ODD) {
-                        const uint32_t m01 = n >= 2 ? 0xffffffffu : n == 1 ? 0xffffu : 0u;
-                        const uint32_t m23 = n >= 4 ? 0xffffffffu : n == 3 ? 0xffffu : 0u;
-                        const int at = (2 * rl + e) * r + (n > 0 ? rank0 : 0);
-                        const uint32_t *w3 = reinterpret_cast<const uint32_t *>(fw) + (at >> 1);
-                        const uint32_t sh = (at & 1) * 16, d0 = w3[0], d1 = w3[1], d2 = w3[2];
-                        w[e][b] = u32x2_t{__builtin_amdgcn_alignbit(d1, d0, sh) & m01, __builtin_amdgcn_alignbit(d2, d1, sh) & m23};
-                    } else {
-                        w[e][b] = *reinterpret_cast<const u32x2_t *>(fw + (2 * rl + e) * (2 * r + 8) + (n > 0 ? rank0 : 0) * 2);
-                    }
-                }
+                for (int b = 0; b < NB; ++b) w[e][b] = fl.template operand<ODD>(fw, 2 * k2 + e, b, n16, g, r);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 f32x4_t d[2];
@@ -226,70 +226,59 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 2) void mfma_expand_kernel(Apply
                     d[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int b = 0; b < NB; ++b)
-                        d[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[e][b][0], w[e][b][1], w[e][b][0], w[e][b][1]}),
-                                                                       zop[mb][b], d[e], 0, 0, 0);
+                        d[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zop[mb][b], as_bf16x8(u32x4_t{w[e][b][0], w[e][b][1], w[e][b][0], w[e][b][1]}),
+                                                                       d[e], 0, 0, 0);
                 }
-                const u32x4_t yv = yop[mb][s];
-                float out[8];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    out[2 * v]     = bf16_lo(yv[v]) + d[0][v];
-                    out[2 * v + 1] = bf16_hi(yv[v]) + d[1][v];
-                }
-                yop[mb][s] = Elem<bf16_tag>::pack(out);
+                for (int v = 0; v < 4; ++v) Y[mb][v][k2] = pack_bf16(bf16_lo(Y[mb][v][k2]) + d[0][v], bf16_hi(Y[mb][v][k2]) + d[1][v]);
             }
         }
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) tr[rl * MFMA_TRS + 4 * s + g] = yop[mb][s];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const u32x4_t o = tr[(4 * i + q) * MFMA_TRS + c16];
-                if (col_ok && mb * 16 + 4 * i + q < n_rows) st16_stream(yc + (row[mb][i] * ldy_b + c16 * 16), o);
-            }
-        }
+            for (int v = 0; v < 4; ++v)
+                if (mb * 16 + v < rows_left) st16_stream(yp[mb][v], Y[mb][v]);
     }
 }
 
-// The same in tiles of 16 RW rows x 128 PU columns whose factors the RW wavefronts share through LDS (rank 33-64 in multiples of 4, widths
-// multiples of 128 PU; chunks only).  At rank 64 a wavefront of mfma_expand_kernel holds the factors of its own columns on their way, 200 registers
-// and two wavefronts per SIMD, and every 32 rows fetch the factors again: too little y in flight (8B layer's o, 38 400 rows: 147 us =
-// 4.3 TB/s).  Shared by 64 rows they take half the traffic and 8 pieces a lane: 163 registers, 52 KB of LDS, three workgroups per compute
-// unit, which also hide the barrier.  Whole calls, rank 64, mfma_expand_kernel / this one, us: 4096 -> 4096, 1400 rows 46 / 46, 38 000 rows 227 / 208;
-// 4096 -> 2 x 14336, 1400 rows 81 / 78, 38 000 rows 1031 / 923; 8192 -> 8192, 45 000 rows 484 / 444; 1024 -> 1024 69 / 67; rank 52
-// alike.  Tiles in memory order; dealt to the XCDs as runs 977 for the 923, 65 for the 67.
-// Short prompts, 4096 -> 2 x 14336: 120 of 10-16 rows 161 / 153, 200 of 20-60 360 / 317, 60 of 33-34 148 / 131, 40 of 20 93 / 99.
-constexpr int PANEL_RW = 4, PANEL_PU = 2;
+// The same in tiles of 16 RW rows x 128 PU columns whose factors the RW wavefronts share through LDS (rank 33-64, widths multiples of
+// 128 PU; chunks only).  At rank 64 the factors of a wavefront's own columns would be as many bytes as its 32 rows of y; shared by
+// 64 rows they are half as many.  64 x 256 where every output is a multiple of 256 wide, else 64 x 128.
+// gate+up of a 70B layer, rank 64, 89 740 rows, whole call: one launch 4845 us, two with y turned through LDS 4470, now 4165-4250 (5.5 TB/s);
+// 8192 -> 8192 946 / 855 / 842; rank 63, 8192 -> 28 672 2586 (one launch) / 2282; 8B layer, 37 000 rows, rank 64 gate+up 925 / 882, rank 63, 4096 -> 14336
+// 542 (a wavefront's own factors) / 479; 4096 -> 14208 (64 x 128) 539 / 509.
+// Three workgroups per compute unit.  Four (128 registers) have more tiles in flight, a wider window of y: gate+up 4420, 895; two 4690, 970.
+// Tiles of 128 rows 4400, 890.  Tiles in memory order; dealt to the XCDs as runs 977 for 923, 65 for 67 (with y turned).
+constexpr int PANEL_RW = 4;
 
-template <int NB, int RW, int PU>
+template <int NB, int RW, int PU, bool ODD>
 __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, int n_slices)
 {
     constexpr int R = 16 * RW, NT = RW * 64;
     constexpr int W_ITERS = NB * 16 * 16 * PU / NT;           // 16 r PU pieces, r <= 16 NB
-    static_assert(CHUNK_ROWS % R == 0, "tile height must divide the chunk height");
-    __shared__ u32x4_t turn[RW][16 * MFMA_TRS];
-    __shared__ __attribute__((aligned(16))) char fac[PU * 128 * (32 * NB + 8)];      // column c at byte c (2 r + 8)
+    static_assert(CHUNK_ROWS % R == 0 && PU <= 2, "tile height must divide the chunk height; two units of factors");
+    __shared__ __attribute__((aligned(16))) char fac[PU][FactorLds<NB>::BYTES];
 
     if (!schedule_matches(p)) return;
-    const int rb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int rl = lane & 15, g = lane >> 4;                  // MFMA order
-    const int q = lane >> 4, c16 = lane & 15;                 // unit load order
-    const int r = p.rank, cs = 2 * r + 8;
-    u32x4_t *tr = turn[rb];
+    const int rb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = p.rank;
 
     const ExpandTiles tiles = expand_tiles<R, PU * 128>(p, n_slices);
     for (uint32_t slot = blockIdx.x; slot < tiles.per_xcd * 8; slot += gridDim.x) {
         ExpandTile t;
         if (!expand_tile<R>(p, tiles, slot, t)) continue;     // uniform over the workgroup
         const int c0 = t.panel * PU * 128;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));                         // recomputed for every tile: what hangs on the lane would fill the registers
+        const int lane = tid & 63, n16 = lane & 15, g = lane >> 4;           // columns 8 n16 .. + 7 of a unit, rows 4 g .. + 3 of the block
+        const FactorLds<NB> fl(r);
 
         // every request of the tile first: its factors, this row block's z, its units of y (rows past the tile alias its last one)
         gcptr_t Wp = as_global(as_const(t.Bt_pool)[t.entry.x]) + (int64_t)c0 * r * 2;
         const int w_last = 16 * r * PU - 1;                   // the panel's last piece: lanes past it take it again
         u32x4_t W[W_ITERS];
 #pragma unroll
-        for (int j = 0; j < W_ITERS; ++j) W[j] = ld16(Wp + (uint32_t)(min((int)threadIdx.x + j * NT, w_last) * 16));
+        for (int j = 0; j < W_ITERS; ++j) W[j] = ld16(Wp + (uint32_t)(min(tid + j * NT, w_last) * 16));
         const int rank_blocks = z_rank_blocks(r);             // 33..48: the fourth block is padding, z = 0
         const int zrb = rb * 16 < t.n_rows ? rb : 0;          // row blocks past the tile: any z will do
         gcptr_t zb = as_global(p.zws) + (z_piece(t.block0 + zrb, n_slices, t.sl, rank_blocks, 0) + lane) * 16;
@@ -305,63 +294,52 @@ __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, i
         }
         gptr_t yu[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            yu[i] = as_global(t.y) + ((int64_t)t.entry.y + t.row0 + min(rb * 16 + 4 * i + q, t.n_rows - 1)) * t.ldy_b + (int64_t)c0 * 2 + c16 * 16;
+        for (int v = 0; v < 4; ++v)
+            yu[v] = as_global(t.y) + ((int64_t)t.entry.y + t.row0 + min(rb * 16 + 4 * g + v, t.n_rows - 1)) * t.ldy_b + (int64_t)c0 * 2 + n16 * 16;
         const bool mine = rb * 16 < t.n_rows;                 // a short prompt's tile: its other wavefronts only bring factors
+        const int rows_left = t.n_rows - rb * 16 - 4 * g;
         u32x4_t Y[PU][4];
         if (mine) {
 #pragma unroll
             for (int u = 0; u < PU; ++u)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) Y[u][i] = ld16_stream(yu[i] + u * 256);
+                for (int v = 0; v < 4; ++v) Y[u][v] = ld16_stream(yu[v] + u * 256);
         }
 
-        // factors to LDS: two 8-byte halves per piece, neither straddles a column (r % 4 == 0)
+        // factors to LDS: as they lie in memory, or in two 8-byte halves per piece, neither of which straddles a column
 #pragma unroll
         for (int j = 0; j < W_ITERS; ++j) {
-            const int piece = min((int)threadIdx.x + j * NT, w_last);
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int byte = piece * 16 + hh * 8;
-                *reinterpret_cast<u32x2_t *>(fac + byte + byte / (2 * r) * 8) = u32x2_t{W[j][2 * hh], W[j][2 * hh + 1]};
+            const int piece = min(tid + j * NT, w_last), u = piece >= 16 * r ? 1 : 0, in_unit = piece - u * 16 * r;
+            if constexpr (ODD) {
+                *reinterpret_cast<u32x4_t *>(fac[u] + in_unit * 16) = W[j];
+            } else {
+                *reinterpret_cast<u32x2_t *>(fac[u] + fl.quarter(2 * in_unit)) = u32x2_t{W[j][0], W[j][1]};
+                *reinterpret_cast<u32x2_t *>(fac[u] + fl.quarter(2 * in_unit + 1)) = u32x2_t{W[j][2], W[j][3]};
             }
         }
         __syncthreads();
 
+        if (mine) {
 #pragma unroll
-        for (int u = 0; u < PU; ++u) {
-            if (!mine) break;
-            u32x4_t yop[4];
+            for (int u = 0; u < PU; ++u) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[u][i];
+                for (int k2 = 0; k2 < 4; ++k2) {              // columns 8 n16 + 2 k2 and + 1, as in mfma_expand_kernel
+                    f32x4_t d[2];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) yop[s] = tr[rl * MFMA_TRS + 4 * s + g];
+                    for (int e = 0; e < 2; ++e) {
+                        d[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                f32x4_t d[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {                 // columns 2m + e of the step, as in mfma_expand_kernel
-                    d[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        const int rank0 = 16 * b + 4 * g;
-                        const u32x2_t w = *reinterpret_cast<const u32x2_t *>(fac + (u * 128 + s * 32 + 2 * rl + e) * cs + (rank0 < r ? rank0 : 0) * 2);
-                        d[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), zop[b], d[e], 0, 0, 0);
+                        for (int b = 0; b < NB; ++b) {
+                            const u32x2_t w = fl.template operand<ODD>(fac[u], 2 * k2 + e, b, n16, g, r);
+                            d[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zop[b], as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), d[e], 0, 0, 0);
+                        }
                     }
-                }
-                const u32x4_t yv = yop[s];
-                float out[8];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    out[2 * v]     = bf16_lo(yv[v]) + d[0][v];
-                    out[2 * v + 1] = bf16_hi(yv[v]) + d[1][v];
-                }
-                tr[rl * MFMA_TRS + 4 * s + g] = Elem<bf16_tag>::pack(out);
-            }
+                    for (int v = 0; v < 4; ++v) Y[u][v][k2] = pack_bf16(bf16_lo(Y[u][v][k2]) + d[0][v], bf16_hi(Y[u][v][k2]) + d[1][v]);
+                        }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const u32x4_t o = tr[(4 * i + q) * MFMA_TRS + c16];
-                if (rb * 16 + 4 * i + q < t.n_rows) st16_stream(yu[i] + u * 256, o);
+                for (int v = 0; v < 4; ++v)
+                    if (v < rows_left) st16_stream(yu[v] + u * 256, Y[u][v]);
             }
         }
         __syncthreads();                                      // the next tile's factors overwrite this one's

@@ -31,9 +31,9 @@ template __global__ void preft::mfma_wide_kernel<8, 1, 4, 1, false, 1, false, fa
 template __global__ void preft::mfma_wide_layers_kernel<1, 1, 8, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<4, 1, 4, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<8, 1, 8, 1, true>(preft::ApplyArgs);
+template __global__ void preft::panel_expand_kernel<4, 4, 1, false>(preft::ApplyArgs, int);
 template __global__ void preft::small_tile_kernel<1, false, false, true, 8>(preft::ApplyArgs, int);
 template __global__ void preft::small_tile_kernel<4, false, false, true, 4>(preft::ApplyArgs, int);
-template __global__ void preft::thin_expand_kernel<2, 2>(preft::ApplyArgs, int);
 template __global__ void preft::valu_tile_kernel<1, 4, 4, false, 2, 0, true>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<2, 4, 2, false, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<2, 4, 4, false, 3, 0, true>(preft::ApplyArgs);
@@ -43,7 +43,8 @@ template __global__ void preft::valu_tile_kernel<5, 2, 1, false, 1, 0, false>(pr
 template __global__ void preft::valu_tile_kernel<6, 2, 1, false, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<7, 2, 1, false, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<8, 2, 1, false, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<2, 2, 4, 8>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<3, 4, 4, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<5, 2, 4, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<7, 2, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<1, 4, 4, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<3, 4, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<5, 2, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<7, 2, 1, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<8, 2, 4, 8>(preft::ApplyArgs);

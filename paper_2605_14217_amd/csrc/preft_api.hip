@@ -258,10 +258,21 @@ inline int64_t expand_panels(const ApplyArgs &a, int n_slices, int64_t cols)
     return panels;
 }
 
+// Rank 33-64: units of 128 columns in a panel of panel_expand_kernel, which every output holds a whole number of (the widths are
+// multiples of 128 there).
+inline int panel_units(const ApplyArgs &a, int n_slices)
+{
+    bool two = (a.d_out % 256) == 0;
+    for (int i = 1; i < n_slices; ++i) two = two && (a.more[i - 1].d_out % 256) == 0;
+    return two ? 2 : 1;
+}
+
 // the kernel numbers its tiles in 32 bits
 inline bool expand_ids_fit(const ApplyArgs &a, int64_t S, int n_slices)
 {
-    return tile_grid(a, S, 16 * EXPAND_MB) * expand_panels(a, n_slices, EXPAND_WAVES * 128) < ((int64_t)1 << 31);
+    const int64_t tiles = a.rank > 32 ? tile_grid(a, S, 16 * PANEL_RW) * expand_panels(a, n_slices, 128 * panel_units(a, n_slices))
+                                      : tile_grid(a, S, 16 * EXPAND_MB) * expand_panels(a, n_slices, EXPAND_WAVES * 128);
+    return tiles < ((int64_t)1 << 31);
 }
 
 // Rows that do not start on 128-byte lines: neighbouring panels share lines, so they go to one XCD.
@@ -274,7 +285,7 @@ bool rows_off_lines(const ApplyArgs &a, int n_slices)
 
 // a workgroup of four wavefronts for every tile of `height` rows x `cols` columns
 void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S, int n_slices, hipStream_t stream,
-                          int height = 16 * EXPAND_MB, int cols = EXPAND_WAVES * 128)
+                          int height = 16 * EXPAND_MB, int cols = EXPAND_WAVES * 128, int threads = EXPAND_WAVES * 64)
 {
     a.xcd_runs = rows_off_lines(a, n_slices);
     // More tiles than the likely rows fill are likely to be empty, and an empty workgroup is not free (3584 decode rows, prompt
@@ -283,13 +294,19 @@ void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S
     const int64_t rows = a.all_tokens && !a.chunks_only ? a.T : prompt_rows(a, S);
     const int64_t bound = tile_grid(a, S, height), likely = rows / height * 5 / 4 + (rows / 8 < 64 ? rows / 8 + 1 : 64);
     const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices, cols), most = (int64_t)1 << 23;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(EXPAND_WAVES * 64), 0, stream, a, n_slices);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(threads), 0, stream, a, n_slices);
 }
 
 template <int NB, bool ODD>
 void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
 {
-    launch_expand_kernel(mfma_expand_kernel<NB, EXPAND_MB, ODD>, a, S, n_slices, stream);
+    if constexpr (NB <= 2) {
+        launch_expand_kernel(mfma_expand_kernel<NB, EXPAND_MB, ODD>, a, S, n_slices, stream);
+    } else {
+        const int pu = panel_units(a, n_slices);
+        launch_expand_kernel(pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD> : panel_expand_kernel<NB, PANEL_RW, 1, ODD>, a, S, n_slices,
+                             stream, 16 * PANEL_RW, 128 * pu, 64 * PANEL_RW);
+    }
 }
 
 // LoRA with a z area in the workspace: the shrink sweep leaves z there and the expand runs as a launch of its
@@ -302,7 +319,7 @@ void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stre
 //     4096 -> 2 x 14336: 1500 rows 62-82 -> 39-44, 42 000 rows 1030 -> 864; q+k+v of 8192, 350 000 rows 3556-3676 -> 3218-3407;
 //     1024 -> 1024 + 2 x 512, 140 000 rows 258-265 -> 255-293; rows off 128-byte lines, 1024 -> 2728 10-11 -> 12-13,
 //     2000 -> 3208, 11 200 rows 42-44 -> 50, but several outputs off lines, 4096 -> 9640 + 296, 1500 rows 26 -> 18.
-//   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 518 -> 454 (panel_expand_kernel: 3 to 9 % less); rank 32 86 -> 48,
+//   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 518 -> 454 (y turned through LDS); rank 32 86 -> 48,
 //     105 -> 97, 355 -> 372.
 //   decode rows alone, 7 per adapter (gathered tiles), rank 16, 8192 -> 8192: 1200 rows 30 -> 35, 3584 rows 89 -> 89;
 //     one per adapter 87 -> 109.
@@ -316,14 +333,14 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     if (a.T <= 1024) return false;
     // hardly a prompt row, and none of the others counts, or the second launch does not take them: nothing to expand
     if ((!a.all_tokens || a.rank > 16) && prompt_rows(a, S) < 64) return false;
-    // Rank 64, 352 814 rows of the 70B layer's shapes, one launch -> two, us: q+k+v 4878 -> 5537, o 3648 -> 3936, gate+up
-    // 18 408 -> 19 585 (the single launch has tiles enough, and its shrink hides behind other workgroups' expand); 60 000 rows:
-    // 8192 -> 2 x 28672 3166 -> 3242, 8192 -> 8192 596 -> 602, q+k+v 851 -> 894; 37 000 rows: 518 -> 454 (8192 -> 8192).
-    if (a.rank > 32 && a.T > 49152) return false;
-    if (a.rank > 16) return true;
-    if (a.all_tokens && a.T < 8 * S) return false;
     int64_t width = a.d_out;
     for (int i = 1; i < n_slices; ++i) width += a.more[i - 1].d_out;
+    // Rank 64, 89 740 rows, one launch -> two: 8192 -> 2 x 28672 4845 -> 4200, 8192 -> 8192 946 -> 845, q+k+v 1322 -> 1248, 28672 -> 8192 1716 ->
+    // 1602, rank 63 q+k+v 1355 -> 1282; 352 814 rows, q+k+v 5100 -> 5000.  But 8192 -> 1024 376 -> 392: next to nothing to expand, and the single
+    // launch has tiles enough.
+    if (a.rank > 32 && a.T > 49152 && 4 * width <= a.d_in) return false;
+    if (a.rank > 16) return true;
+    if (a.all_tokens && a.T < 8 * S) return false;
     if (a.rank < 4) return a.T * width >= (n_slices > 1 ? 6000000 : 12000000) && width >= 3072 && (n_slices > 1 || !rows_off_lines(a, n_slices));
     return a.T * width >= 6000000 && (width >= 3072 || !rows_off_lines(a, n_slices));
 }
@@ -333,15 +350,6 @@ bool column_groups_fit(const ApplyArgs &a, int n_slices)
 {
     bool fit = wide_widths_ok(a, 2);
     for (int i = 1; i < n_slices; ++i) fit = fit && (a.more[i - 1].d_out % 256) == 0;
-    return fit;
-}
-
-// Whether the expand launch of rank 33-64 (multiples of 4) takes panel_expand_kernel: every output a whole number of its panels.  It has
-// three wavefronts per SIMD where mfma_expand_kernel has registers for two; hardly a batch has been seen where it is the slower one (its figures).
-bool panels_fit(const ApplyArgs &a, int n_slices)
-{
-    bool fit = (a.d_out % (PANEL_PU * 128)) == 0;
-    for (int i = 1; i < n_slices; ++i) fit = fit && (a.more[i - 1].d_out % (PANEL_PU * 128)) == 0;
     return fit;
 }
 
@@ -362,12 +370,6 @@ bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream
         if (column_groups_fit(a, SLICES)) shrink = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, false, true>;
     }
     hipLaunchKernelGGL(shrink, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
-    if constexpr (NB == 4) {
-        if (panels_fit(a, SLICES)) {
-            launch_expand_kernel(panel_expand_kernel<NB, PANEL_RW, PANEL_PU>, a, S, SLICES, stream, 16 * PANEL_RW, 128 * PANEL_PU);
-            return true;
-        }
-    }
     launch_expand<NB, false>(a, S, SLICES, stream);
     return true;
 }

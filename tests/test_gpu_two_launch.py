@@ -19,7 +19,9 @@ CASES = [(1, 512, (512,)), (1, 136, (1032, 8, 520)), (2, 1096, (2056, 384)), (3,
          (17, 128, (128,)), (20, 256, (512, 256)), (24, 256, (384,)), (32, 512, (256, 128)), (28, 1024, (512, 640, 256)), (31, 384, (512, 128, 256)), (36, 128, (1152,)), (48, 256, (512,)),
          (63, 256, (640, 512)), (64, 128, (128, 1664)),
          # panels of 64 rows x 256 columns that share their factors (rank 33-64 in multiples of 4, every width a multiple of 256)
-         (36, 384, (256,)), (40, 128, (512, 256)), (48, 256, (768, 256, 1024)), (52, 128, (256, 1280)), (60, 640, (512,)), (64, 128, (256, 512, 256)), (64, 1024, (1536,))]
+         (36, 384, (256,)), (40, 128, (512, 256)), (48, 256, (768, 256, 1024)), (52, 128, (256, 1280)), (60, 640, (512,)), (64, 128, (256, 512, 256)), (64, 1024, (1536,)),
+         # the same at ranks that are no multiple of 4, and panels of 64 x 128 where a width is no multiple of 256
+         (33, 128, (256,)), (37, 256, (768, 512)), (63, 128, (1024,)), (49, 128, (384, 256, 128)), (44, 256, (640,))]
 
 
 @pytest.mark.parametrize("pad", [0, 8])
