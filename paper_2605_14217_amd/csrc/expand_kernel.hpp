@@ -31,15 +31,17 @@ constexpr int EXPAND_WAVES = 4;                               // 128-column unit
 
 // Factors in LDS, 128 columns at a time.  MFMA k takes the columns 8 n + k, n = 0 .. 15 (a lane then ends up with the 8 consecutive
 // columns that it loaded, see below), so those lie side by side: column c in group c % 8, at place c / 8 of it.  A column takes
-// 2 or 6 words modulo 8, so that the 16 columns of an operand read fall on different banks, and a group of them 2 words modulo
-// 32, which spreads the writes.  Ranks that are not multiples of 4 lie as in memory (a lane then shifts its
+// 16 bytes modulo 32: then the 16 columns of an 8-byte operand read, and the four pieces in each, meet no bank twice (measured, one read
+// of a wavefront: 16, 48, 80, 144 bytes 1.87, as linear addresses; 24, 40, 72, 136 2.96; 128 8.99).  A group is 8 bytes longer, which spreads
+// the writes.  Ranks that are not multiples of 4 lie as in memory (a lane then shifts its
 // four factors into place and may look one word past them).
+__host__ __device__ constexpr int factor_column_bytes(int r) { return ((2 * r + 15) & ~31) + 16; }
 template <int NB>
 struct FactorLds {
-    static constexpr int GROUP = 16 * (32 * NB + 8) + 8, BYTES = 8 * GROUP + 16;
+    static constexpr int GROUP = 16 * factor_column_bytes(16 * NB) + 8, BYTES = 8 * GROUP + 16;
     int r4, column;                                           // quarters of 4 factors, and bytes, of a column
     float inv;
-    __device__ __forceinline__ explicit FactorLds(int r) : r4(r >> 2), column(2 * r + (r % 8 ? 0 : 8)), inv(4.0f / (float)r) {}
+    __device__ __forceinline__ explicit FactorLds(int r) : r4(r >> 2), column(factor_column_bytes(r)), inv(4.0f / (float)r) {}
     // where quarter i of a contiguous [128][r] block goes.  (i + 0.5) / r4 is below 128 and at least 0.5 / 16 away from a
     // whole number: the rounding of the product, below 1e-4, never reaches one.
     __device__ __forceinline__ int quarter(int i) const

@@ -63,7 +63,8 @@ __device__ __forceinline__ int xcd_unit(int n_units)
     return v < n_units ? v : -1;
 }
 
-constexpr int MFMA_TRS = 17;      // LDS row stride of the turn buffer in 16-byte vectors (256 B + 16 B pad)
+constexpr int MFMA_TRS = 18;      // LDS row stride of the turn buffer in 16-byte vectors.  256 B + 32 B: the reads in MFMA order meet no bank twice
+                                  // (measured, one read of a wavefront: + 0 B 16.0, + 16 B 4.75, + 32 B 2.96 = linear addresses)
 
 // Wavefronts per SIMD the register allocation must leave room for: the register-resident DiReFT
 // shapes need two workgroups per compute unit so that one streams in while the other streams out.
