@@ -97,7 +97,7 @@ enum {
  *                            batches of up to 1024 rows), 1 = the kernels of larger batches, 2..15 (fp32: 1..15).
  *                            Together with variant 4 it names the column groups of the row-split kernel
  *                            instead: 0 = automatic, 1 or 2
- *   PREFT_TEST_RESIDENT(n)   0 = automatic.  LoRA: 1 = two launches (preft_workspace_bytes_z)
+ *   PREFT_TEST_RESIDENT(n)   0 = automatic.  LoRA, and in place at rank 33..64: 1 = two launches (preft_workspace_bytes_z)
  *                            wherever that form exists, whatever the batch size.  In-place
  *                            MFMA kernel at rank 20..32 (automatic: 32-row tiles streamed in
  *                            both sweeps): 3 = every wavefront keeps 8 of its
@@ -141,11 +141,13 @@ size_t preft_workspace_bytes(int32_t T, int32_t S);
 
 /*
  * Bytes of a workspace that, beyond the schedule, has room for the intermediate z = A_i x of Eq. 2 of
- * every active row: LoRA calls of up to `rank` with up to n_proj outputs per call.  A bf16 LoRA call of
+ * every active row: LoRA calls of up to `rank` with up to n_proj outputs per call, or in-place calls (preft_direft_apply,
+ * preft_loreft_apply) of up to `rank`.  A bf16 LoRA call of
  * rank 1..64 (above rank 16: d_in and every d_out a multiple of 128) on a batch of more than 1024 rows
  * that is handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the
  * expand in 2-D tiles -- where that is faster: wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
  * 1100), and every shape above rank 16 (up to 5x on 1100 rows); not on a step of decode rows that has nothing to apply.
+ * So does a bf16 in-place call of rank 33..64, d a multiple of 128, where that is faster (d >= 4096: 5 to 50 % less time).
  * With fewer bytes, or outside those limits,
  * the same call runs in one launch.  The result is the same bit for bit.
  * The z area lies behind the schedule and is rewritten by every such call: calls that

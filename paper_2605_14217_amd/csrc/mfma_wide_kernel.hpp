@@ -39,19 +39,22 @@
 
 namespace preft {
 
-constexpr int wide_fac_bytes(int NB, int CW)                   // one buffer of CW factor units
+// Row stride of an A unit in LDS, in 16-byte vectors.  With the shrink sweep alone a rank's 16 chunks lie in a row of their own
+// length, chunk c of rank k at place c ^ (k % 16): no bank is met twice there either, and three workgroups of 64 ranks fit a compute unit.
+constexpr int wide_a_row(bool zout) { return zout ? 16 : MFMA_TRS; }
+constexpr int wide_fac_bytes(int NB, int CW, bool zout)        // one buffer of CW factor units
 {
-    const int fa = NB * 16 * MFMA_TRS * 16;                   // A unit: NB*16 ranks x 272 B
-    const int fb = 128 * (32 * NB + 8);                       // B unit: 128 columns x (2r + 8) B
+    const int fa = NB * 16 * wide_a_row(zout) * 16;           // A unit: NB*16 ranks x 288 (256) B
+    const int fb = zout ? 0 : 128 * (32 * NB + 8);            // B unit: 128 columns x (2r + 8) B
     return CW * (fa > fb ? fa : fb);
 }
-constexpr int wide_lds_bytes(int NB, int MB, int RW, int CW)
+constexpr int wide_lds_bytes(int NB, int MB, int RW, int CW, bool zout)
 {
-    return RW * CW * MB * 16 * MFMA_TRS * 16 + 2 * wide_fac_bytes(NB, CW);
+    return RW * CW * MB * 16 * MFMA_TRS * 16 + 2 * wide_fac_bytes(NB, CW, zout);
 }
 
 //
-// ZOUT (LoRA only): the shrink sweep alone.  z, already in the form the expand's MFMAs take it (scaled,
+// ZOUT: the shrink sweep alone.  z, already in the form the expand's MFMAs take it (scaled,
 // split into bf16 head and remainder, in lane order), goes to the z area of the workspace, 1 KB per
 // 16-row block and rank block that exists (z_piece), and mfma_expand_kernel does the expand in a second launch.
 //
@@ -69,23 +72,24 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
 {
     static_assert(!ODD || (MB == 1 && CW == 1), "the any-rank form: the basic shape");
     static_assert(SLICES == 1 || !DIREFT, "packed projections are a LoRA feature");
-    static_assert(!ZOUT || (!DIREFT && MB == 1), "the two-launch form: LoRA, 16-row blocks per wavefront");
     static_assert(!EO || (ZOUT && CW == 1), "one wavefront in place of two column groups");
     constexpr int WAVES = RW * CW;
+    constexpr bool AHEAD2 = ZOUT && SLICES == 1;              // factor units requested two steps ahead
     constexpr int NBT = NB * SLICES;                          // accumulator blocks of the shrink sweep
     constexpr int R = 16 * MB * RW;
     constexpr int TPC = CHUNK_ROWS / R;
     constexpr int NT = WAVES * 64;
-    constexpr int A_UNIT = NB * 16 * MFMA_TRS;                // 16-byte vectors of an A unit in LDS
+    constexpr int A_ROW = wide_a_row(ZOUT), A_UNIT = NB * 16 * A_ROW;    // 16-byte vectors of a rank, and of an A unit, in LDS
+    auto a_place = [](int rank, int chunk) { return rank * A_ROW + (ZOUT ? chunk ^ (rank & 15) : chunk); };
     constexpr int A_PIECES = NB * 16 * 16 * CW;               // 16-byte pieces of a step's A units (padded ranks included)
     constexpr int A_ITERS = (A_PIECES + NT - 1) / NT;
     constexpr int B_UNIT = 128 * (32 * NB + 8);               // bytes reserved for a B unit in LDS
     constexpr int B_ITERS = (NB * 16 * 16 * CW + NT - 1) / NT;   // upper bound: 16 r CW pieces, r <= 16 NB
-    constexpr int FAC = wide_fac_bytes(NB, CW);
+    constexpr int FAC = wide_fac_bytes(NB, CW, ZOUT);
     static_assert(CHUNK_ROWS % R == 0, "tile height must divide the chunk height");
     static_assert(CW == 1 || WAVES * NB * MB * 4 * 64 * 4 <= 2 * FAC, "the partial sums of one output must fit the factor area");
 
-    __shared__ __attribute__((aligned(16))) char lds_raw[wide_lds_bytes(NB, MB, RW, CW)];
+    __shared__ __attribute__((aligned(16))) char lds_raw[wide_lds_bytes(NB, MB, RW, CW, ZOUT)];
     u32x4_t *turn_all = reinterpret_cast<u32x4_t *>(lds_raw);
     char *fac = lds_raw + WAVES * MB * 16 * MFMA_TRS * 16;    // factor area (A units, later B units): two buffers of FAC bytes
 
@@ -124,6 +128,14 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
             row_u[mb][i] = (int64_t)ch.y + tile_row0 + min(t, n_rows - 1);
             xu[mb][i] = as_global(p.x) + row_u[mb][i] * ldx_b + (cg * 16 + c16) * 16;
         }
+    // the same as 32-bit offsets from the tile's first row (the shrink sweep alone: the host has checked the widths)
+    gcptr_t x_tile = as_global(p.x) + ((int64_t)ch.y + tile_row0) * ldx_b;
+    uint32_t x_off[MB][4];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            x_off[mb][i] = (uint32_t)min(rb * 16 * MB + mb * 16 + 4 * i + q, n_rows - 1) * (uint32_t)ldx_b + (cg * 16 + c16) * 16;
 
     auto unit_to_mfma = [&](const u32x4_t (&raw)[MB][4], u32x4_t (&op)[MB][4]) {
 #pragma unroll
@@ -152,7 +164,10 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) raw[mb][i] = ld16_first<DIREFT>(xu[mb][i] + (int64_t)u * (256 * CW));
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (ZOUT) raw[mb][i] = ld16_stream(x_tile + (int64_t)u * (256 * CW) + x_off[mb][i]);
+                else raw[mb][i] = ld16_first<DIREFT>(xu[mb][i] + (int64_t)u * (256 * CW));
+            }
     };
     // this thread's pieces of the step's A units: piece = (rank, 16-byte chunk of the 256 CW bytes of the step)
     auto load_a = [&](u32x4_t (&areg)[A_ITERS], gcptr_t Asl, int u) {
@@ -160,8 +175,10 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
         for (int i = 0; i < A_ITERS; ++i) {
             const int piece = tid + i * NT;
             const int rank = min(piece / (16 * CW), r - 1);   // padding ranks alias rank r-1 (their z is zeroed)
-            if (A_PIECES % NT == 0 || piece < A_PIECES)
-                areg[i] = ld16(Asl + ((int64_t)rank * p.d_in) * 2 + (int64_t)u * (256 * CW) + (piece % (16 * CW)) * 16);
+            if (A_PIECES % NT == 0 || piece < A_PIECES) {
+                if constexpr (ZOUT) areg[i] = ld16(Asl + (int64_t)u * (256 * CW) + (uint32_t)(rank * p.d_in * 2 + (piece % (16 * CW)) * 16));
+                else areg[i] = ld16(Asl + ((int64_t)rank * p.d_in) * 2 + (int64_t)u * (256 * CW) + (piece % (16 * CW)) * 16);
+            }
         }
     };
     auto publish_a = [&](const u32x4_t (&areg)[A_ITERS], int buf) {
@@ -171,17 +188,18 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
             const int piece = tid + i * NT;
             const int chunk = piece % (16 * CW);
             if (A_PIECES % NT == 0 || piece < A_PIECES)
-                fa[(chunk >> 4) * A_UNIT + (piece / (16 * CW)) * MFMA_TRS + (chunk & 15)] = areg[i];
+                fa[(chunk >> 4) * A_UNIT + a_place(piece / (16 * CW), chunk & 15)] = areg[i];
         }
     };
     auto mfma_a = [&](const u32x4_t (&op)[MB][4], int buf, auto sl_tag, auto eo_tag) {
         constexpr int SL = decltype(sl_tag)::value, E = decltype(eo_tag)::value;
         const u32x4_t *fa = reinterpret_cast<const u32x4_t *>(fac + buf * FAC) + cg * A_UNIT;
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int s = 0; s < 4; ++s) {
+            if constexpr (ZOUT && NB == 4) { if (s == 2 || RW == 8) __builtin_amdgcn_sched_barrier(0); }
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const u32x4_t ao = fa[(16 * b + rl) * MFMA_TRS + 4 * s + g];
+                const u32x4_t ao = fa[16 * b * A_ROW + a_place(rl, 4 * s + g)];
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) {
                     const u32x4_t xo = op[mb][s];
@@ -189,6 +207,7 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
                                                                                         acc_eo[E][SL * NB + b][mb], 0, 0, 0);
                 }
             }
+        }
     };
     {
         // Pipeline.  A wavefront keeps two units of x on their way (three register buffers in
@@ -203,11 +222,54 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
         // come in threes with compile-time buffer numbers; GUARD = false (steady state) has no
         // conditional load, so that the compiler's wait counts stay exact; the last trips of a sweep
         // check which requests still exist.
-        u32x4_t X[3][MB][4], op[MB][4], areg[SLICES][A_ITERS];
+        u32x4_t X[AHEAD2 ? 2 : 3][MB][4], op[MB][4], areg[AHEAD2 ? 2 : SLICES][A_ITERS];
         int par = 0;                                          // LDS buffer of the current step
+        constexpr std::integral_constant<bool, false> steady{};
+        constexpr std::integral_constant<bool, true> guarded{};
+        constexpr std::integral_constant<int, 0> b0{};
+        constexpr std::integral_constant<int, 1> b1{};
+        constexpr std::integral_constant<int, 2> b2{};
+        load_a(areg[0], A[0], 0);
+        if constexpr (SLICES > 1) load_a(areg[1], A[1], 0);
+        load_x(X[0], 0);
+        if constexpr (AHEAD2) { if (k_steps > 1) load_a(areg[1], A[0], 1); }
+        if (k_steps > 1) load_x(X[1], 1);
+        publish_a(areg[0], 0);
+        __syncthreads();
+        int u = 0;
+        if constexpr (AHEAD2) {
+            // One output and nothing else to come: everything runs two steps ahead through two sets of registers, a unit of x into
+            // those that the turn has just emptied.  Then publishing the next factor units waits for no activations but those
+            // of the step that is done.
+            auto trip = [&](auto ti_tag, int u, auto guard_tag) {        // trip ti of a round: u = ti modulo 2
+                constexpr int TI = decltype(ti_tag)::value;
+                constexpr bool GUARD = decltype(guard_tag)::value;
+                const bool has1 = !GUARD || u + 1 < k_steps, has2 = !GUARD || u + 2 < k_steps;
+                unit_to_mfma(X[TI], op);
+                if (has2) load_a(areg[TI], A[0], u + 2);
+                if (has2) load_x(X[TI], u + 2);
+                mfma_a(op, TI, b0, std::integral_constant<int, EO ? TI : 0>{});
+                if (has1) publish_a(areg[TI ^ 1], TI ^ 1);
+                __syncthreads();
+            };
+            for (; u + 4 <= k_steps; u += 2) {
+                trip(b0, u, steady);
+                trip(b1, u + 1, steady);
+            }
+            for (; u < k_steps; u += 2) {
+                trip(b0, u, guarded);
+                if (u + 1 < k_steps) trip(b1, u + 1, guarded);
+            }
+            if constexpr (EO) {
+#pragma unroll
+                for (int b = 0; b < NBT; ++b)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) acc[b][mb] += acc_eo[1][b][mb];
+            }
+        } else {
         auto trip = [&](auto ti_tag, int u, auto guard_tag) {   // trip ti of a round: u = ti modulo 3 (and 2, when EO)
-            constexpr int XI = decltype(ti_tag)::value % 3;
-            constexpr std::integral_constant<int, EO ? decltype(ti_tag)::value % 2 : 0> eo_tag{};
+            constexpr int TI = decltype(ti_tag)::value, XI = TI % 3;
+            constexpr std::integral_constant<int, EO ? TI % 2 : 0> eo_tag{};
             constexpr bool GUARD = decltype(guard_tag)::value;
             const bool has1 = !GUARD || u + 1 < k_steps, has2 = !GUARD || u + 2 < k_steps;
             auto step = [&](auto sl_tag) {
@@ -231,18 +293,6 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
             if constexpr (SLICES > 1) step(std::integral_constant<int, 1>{});
             if constexpr (SLICES > 2) step(std::integral_constant<int, 2>{});
         };
-        constexpr std::integral_constant<bool, false> steady{};
-        constexpr std::integral_constant<bool, true> guarded{};
-        constexpr std::integral_constant<int, 0> b0{};
-        constexpr std::integral_constant<int, 1> b1{};
-        constexpr std::integral_constant<int, 2> b2{};
-        load_a(areg[0], A[0], 0);
-        if constexpr (SLICES > 1) load_a(areg[1], A[1], 0);
-        load_x(X[0], 0);
-        if (k_steps > 1) load_x(X[1], 1);
-        publish_a(areg[0], 0);
-        __syncthreads();
-        int u = 0;
         if constexpr (EO) {
             constexpr std::integral_constant<int, 3> b3{};
             constexpr std::integral_constant<int, 4> b4{};
@@ -278,6 +328,7 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
                 if (u + 1 < k_steps) trip(b1, u + 1, guarded);
                 if (u + 2 < k_steps) trip(b2, u + 2, guarded);
             }
+        }
         }
     }
 
@@ -349,13 +400,15 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
 
     if constexpr (ZOUT) {
         if (cg == 0) {                                        // with column groups every one of them holds the same z
-            const int64_t blk16 = (int64_t)(unit_id / TPC) * (CHUNK_ROWS / 16) + tile_row0 / 16 + rb;
+            const int64_t blk16 = (int64_t)(unit_id / TPC) * (CHUNK_ROWS / 16) + tile_row0 / 16 + rb * MB;
             const int rank_blocks = NB < 4 ? NB : z_rank_blocks(r);          // 33..48: the fourth block is padding and has no room
             u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + lane;
-            if (blk16 < p.z_blocks) {                         // the list is cut to its capacity, so this always holds
+            if (blk16 + MB <= p.z_blocks) {                   // the list is cut to its capacity, so this always holds
 #pragma unroll
                 for (int b = 0; b < NBT; ++b)
-                    if (b % NB < rank_blocks) zw[z_piece(blk16, SLICES, b / NB, rank_blocks, b % NB)] = as_u32x4(zop[b][0]);
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+                        if (b % NB < rank_blocks) zw[z_piece(blk16 + mb, SLICES, b / NB, rank_blocks, b % NB)] = as_u32x4(zop[b][mb]);
             }
         }
         return;
@@ -533,13 +586,13 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
 // Wavefronts per SIMD the register allocation must leave room for.  Packed launches carry SLICES * NB
 // accumulator blocks: with four wavefronts per workgroup they are held to two workgroups per compute
 // unit, which the unpacked shapes reach by themselves.
-constexpr int wide_min_waves(int RW, int CW, int SLICES)
+constexpr int wide_min_waves(int RW, int CW, int SLICES, bool zout)
 {
-    return (RW * CW == 4 && SLICES > 1) ? 2 : 1;
+    return (RW * CW == 8 && SLICES == 1 && zout) ? 4 : (RW * CW == 4 && (SLICES > 1 || zout)) ? 2 : 1;
 }
 
 template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false, bool EO = false>
-__global__ __launch_bounds__(RW * CW * 64, wide_min_waves(RW, CW, SLICES)) void mfma_wide_kernel(ApplyArgs p)
+__global__ __launch_bounds__(RW * CW * 64, wide_min_waves(RW, CW, SLICES, ZOUT)) void mfma_wide_kernel(ApplyArgs p)
 {
     mfma_wide_body<NB, MB, RW, CW, DIREFT, SLICES, ZOUT, ODD, EO>(p);
 }

@@ -283,6 +283,9 @@ bool rows_off_lines(const ApplyArgs &a, int n_slices)
     return off;
 }
 
+// the shrink launch of rank 17-64 keeps byte offsets within a 64-row tile of x and within a factor in 32 bits
+inline bool offsets_fit(const ApplyArgs &a) { return a.rank <= 16 || (a.ldx <= (1 << 22) && a.d_in <= (1 << 22)); }
+
 // a workgroup of four wavefronts for every tile of `height` rows x `cols` columns
 void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S, int n_slices, hipStream_t stream,
                           int height = 16 * EXPAND_MB, int cols = EXPAND_WAVES * 128, int threads = EXPAND_WAVES * 64)
@@ -319,7 +322,7 @@ void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stre
 //     4096 -> 2 x 14336: 1500 rows 62-82 -> 39-44, 42 000 rows 1030 -> 864; q+k+v of 8192, 350 000 rows 3556-3676 -> 3218-3407;
 //     1024 -> 1024 + 2 x 512, 140 000 rows 258-265 -> 255-293; rows off 128-byte lines, 1024 -> 2728 10-11 -> 12-13,
 //     2000 -> 3208, 11 200 rows 42-44 -> 50, but several outputs off lines, 4096 -> 9640 + 296, 1500 rows 26 -> 18.
-//   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 518 -> 454 (y turned through LDS); rank 32 86 -> 48,
+//   rank 64, 8192 -> 8192: 1100 rows 167 -> 81 us, 8000 rows 182 -> 136, 37 000 rows 522 -> 387; rank 32 86 -> 48,
 //     105 -> 97, 355 -> 372.
 //   decode rows alone, 7 per adapter (gathered tiles), rank 16, 8192 -> 8192: 1200 rows 30 -> 35, 3584 rows 89 -> 89;
 //     one per adapter 87 -> 109.
@@ -328,7 +331,7 @@ void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stre
 bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
 {
     if (!a.zws || (k.variant != 0 && k.variant != 4) || k.waves || k.rowblocks || k.colsplit) return false;
-    if (!expand_ids_fit(a, S, n_slices)) return false;
+    if (!expand_ids_fit(a, S, n_slices) || !offsets_fit(a)) return false;
     if (k.resident == 1) return true;
     if (a.T <= 1024) return false;
     // hardly a prompt row, and none of the others counts, or the second launch does not take them: nothing to expand
@@ -345,6 +348,19 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     return a.T * width >= 6000000 && (width >= 3072 || !rows_off_lines(a, n_slices));
 }
 
+// The in-place call of rank 33-64 as two launches.  The single launch reads h twice as well, in 64-row tiles that sweep all columns; narrow
+// rows find part of the second read in the caches, as long as the batch fills the chip.  Rank 64, one launch -> two, us: 89 740 rows,
+// d = 512 / 1024 / 2048 / 3072 / 4096 / 8192 / 14336: 56 -> 79, 110 -> 131, 234 -> 241, 338 -> 337, 447 -> 433, 878 -> 828, 1620 -> 1446; 23 000 rows, d = 2048
+// 61 -> 69, 3072 90 -> 95, 4096 132 -> 115; 7000 rows, 512 14.8 -> 15.8, 1024 25 -> 23, 2048 45 -> 38, 4096 (10 prompts) 89 -> 56; 2500 rows, 1024 22 -> 18,
+// 8192 155 -> 81.
+bool wants_split_in_place(const ApplyArgs &a, int64_t S, const Knobs &k)
+{
+    if (!a.zws || a.h_layers || (k.variant != 0 && k.variant != 4) || k.waves || k.rowblocks || k.colsplit) return false;
+    if (!expand_ids_fit(a, S, 1) || !offsets_fit(a)) return false;
+    if (k.resident == 1) return true;
+    return a.T > 1024 && prompt_rows(a, S) >= 64 && (a.d_in >= 4096 || (a.d_in >= 1024 && a.T <= 8192));
+}
+
 // Whether the row-split kernel's single launch runs with two column groups at rank 17-32: every width a multiple of 256.
 bool column_groups_fit(const ApplyArgs &a, int n_slices)
 {
@@ -353,24 +369,39 @@ bool column_groups_fit(const ApplyArgs &a, int n_slices)
     return fit;
 }
 
+// The shrink launch of rank 17-64: tiles of 64 rows, or, at rank 33-64 of several outputs or of the largest calls, of 128, whose eight
+// wavefronts share a step's factors: half the factor traffic, half as many workgroups (and with three outputs the four-wavefront form spills).
+// 64 / 128 rows, whole calls, us: three outputs, 8192 -> 8192 + 2 x 1024, 89 740 rows 1270 / 1124, 4096 -> 4096 + 2 x 1024, 2500 rows 89 / 78, 9500
+// rows 119 / 108; two, 8192 -> 2 x 28672, 89 740 rows 4120 / 4067, 4096 -> 2 x 14336, 23 000 rows 525 / 519, 9500 rows 223 / 233; one,
+// 89 740 rows, 28672 -> 8192 1603 / 1503, 8192 -> 8192 836 / 835, in place 828 / 837, 37 000 rows, 4096 -> 4096 182 / 200.  Rank 32: 14336 -> 4096,
+// 37 000 rows 307 / 332.
+template <int NB, int SLICES, bool DIREFT>
+void launch_wide_shrink(const ApplyArgs &a, int64_t S, hipStream_t stream)
+{
+    constexpr int RW = NB == 4 && SLICES == 3 ? 8 : 4;
+    void (*kernel)(ApplyArgs) = (a.rank % 4) ? mfma_wide_kernel<NB, 1, RW, 1, DIREFT, SLICES, true, true> : mfma_wide_kernel<NB, 1, RW, 1, DIREFT, SLICES, true>;
+    int waves = RW;
+    if constexpr (NB <= 2) {                                // where the single launch sums in two column groups, so does this one
+        if (a.rank % 4 == 0 && column_groups_fit(a, SLICES)) kernel = mfma_wide_kernel<NB, 1, 4, 1, DIREFT, SLICES, true, false, true>;
+    } else if constexpr (!DIREFT && SLICES < 3) {
+        if (SLICES == 2 ? a.T > 16384 : a.T > 49152 && a.d_in > 8192) {
+            kernel = (a.rank % 4) ? mfma_wide_kernel<NB, 1, 8, 1, DIREFT, SLICES, true, true> : mfma_wide_kernel<NB, 1, 8, 1, DIREFT, SLICES, true>;
+            waves = 8;
+        }
+    }
+    hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 16 * waves)), dim3(64 * waves), 0, stream, a);
+}
+
 // rank 17..64: the row-split kernel's shrink sweep of the chunks, then their expand launch
-template <int NB, int SLICES>
+template <int NB, int SLICES, bool DIREFT = false>
 bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream_t stream)
 {
-    if (!wants_split(a0, S, SLICES, k) || (a0.d_in % 128) != 0) return false;
+    if (!(DIREFT ? wants_split_in_place(a0, S, k) : wants_split(a0, S, SLICES, k)) || (a0.d_in % 128) != 0) return false;
     ApplyArgs a = a0;
     a.chunks_only = 1;
-    if (a.rank % 4) {
-        hipLaunchKernelGGL((mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, true>), dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
-        launch_expand<NB, true>(a, S, SLICES, stream);
-        return true;
-    }
-    void (*shrink)(ApplyArgs) = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true>;
-    if constexpr (NB <= 2) {                                // where the single launch sums in two column groups, so does this one
-        if (column_groups_fit(a, SLICES)) shrink = mfma_wide_kernel<NB, 1, 4, 1, false, SLICES, true, false, true>;
-    }
-    hipLaunchKernelGGL(shrink, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
-    launch_expand<NB, false>(a, S, SLICES, stream);
+    launch_wide_shrink<NB, SLICES, DIREFT>(a, S, stream);
+    if (a.rank % 4) launch_expand<NB, true>(a, S, SLICES, stream);
+    else            launch_expand<NB, false>(a, S, SLICES, stream);
     return true;
 }
 
@@ -415,8 +446,8 @@ bool launch_mfma_wide(const ApplyArgs &a, int64_t S, int mb, int waves, int cw, 
 {
     if (NB < 2 && k.variant != 4) return false;               // rank <= 16: only on request
     if (!wide_widths_ok(a, 1)) return false;
-    if constexpr (!DIREFT && NB >= 2 && NB <= 4) {
-        if (launch_mfma_split<NB, 1>(a, S, k, stream)) return true;
+    if constexpr (NB == 4 || (NB == 2 && !DIREFT)) {
+        if (launch_mfma_split<NB, 1, DIREFT>(a, S, k, stream)) return true;
     }
     if (!wide_widths_ok(a, cw)) cw = 1;
     if (mb != 1 && NB <= 4) {                                  // 4 wavefronts x 32 rows
@@ -591,9 +622,8 @@ void launch_mfma_odd_wide(const ApplyArgs &a, int64_t S, const Knobs &k, hipStre
 {
     const int nb = (a.rank + 15) / 16;
     bool split = false;
-    if constexpr (!DIREFT) {
-        if (nb <= 4) split = nb <= 2 ? launch_mfma_split<2, 1>(a, S, k, stream) : launch_mfma_split<4, 1>(a, S, k, stream);
-    }
+    if (nb > 2 && nb <= 4) split = launch_mfma_split<4, 1, DIREFT>(a, S, k, stream);
+    if constexpr (!DIREFT) { if (nb <= 2) split = launch_mfma_split<2, 1>(a, S, k, stream); }
     if (split)        {}
     else if (nb <= 2)      launch_wide_shape<2, 1, 4, 1, DIREFT, true>(a, S, stream);
     else if (nb <= 4) launch_wide_shape<4, 1, 4, 1, DIREFT, true>(a, S, stream);
@@ -864,7 +894,7 @@ int check_matrix(const void *p, int64_t ld, int32_t width, int dtype)
 // the residual stream(s) and the pools
 int direft_launch(ApplyArgs a, int64_t ldh, int32_t T, int32_t d, const int32_t *seg_start,
                   const int32_t *seg_adapter, const int32_t *seg_prefill_len, int32_t S, int32_t N, int32_t rank,
-                  float scale, int dtype, int mode, void *workspace, void *stream)
+                  float scale, int dtype, int mode, void *workspace, size_t bytes, void *stream)
 {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (!(mode & PREFT_SCHEDULE_READY)) {
@@ -872,6 +902,7 @@ int direft_launch(ApplyArgs a, int64_t ldh, int32_t T, int32_t d, const int32_t 
         if (rc != PREFT_OK) return rc;
     }
     bind_schedule(a, workspace, T, S, N, mode);
+    bind_z(a, workspace, bytes, T, S, rank, 1);
     a.ldy = ldh; a.ldx = ldh; a.d_in = d; a.d_out = d;
     a.rank = rank; a.scale = scale;
     return launch_apply<true>(a, S, dtype, knobs_of(mode), st);
@@ -1082,7 +1113,7 @@ int preft_direft_apply(void *h, int64_t ldh, int32_t T, int32_t d, const int32_t
     ApplyArgs a;
     a.y = h; a.x = h; a.A_pool = W1_pool; a.Bt_pool = W2t_pool; a.bias_pool = b_pool;
     return direft_launch(a, ldh, T, d, seg_start, seg_adapter, seg_prefill_len, S, N, rank, scale, dtype, mode,
-                         workspace, stream);
+                         workspace, bytes, stream);
 }
 
 int preft_direft_apply_static(void *h, int64_t ldh, int32_t T, int32_t d, const int32_t *seg_start,
@@ -1129,7 +1160,7 @@ int preft_direft_apply_layers(void *const *h_layers, int64_t ldh, int32_t n_laye
     a.h_layers = h_layers; a.A_layers = W1_pools; a.Bt_layers = W2t_pools; a.bias_layers = b_pools;
     a.n_layers = n_layers;
     return direft_launch(a, ldh, T, d, seg_start, seg_adapter, seg_prefill_len, S, N, rank, scale, dtype, mode,
-                         workspace, stream);
+                         workspace, bytes, stream);
 }
 
 int preft_schedule_counts(const void *workspace, int32_t *counts, void *stream)

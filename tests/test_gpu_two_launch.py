@@ -68,3 +68,37 @@ def test_two_launches_match_the_oracle_and_the_single_launch(rank, d_in, d_outs,
         one = call(mode, preft.test_flags(variant=5, colsplit=1) if rank >= 4 else preft.test_flags(variant=2))
         for y, y1 in zip(two, one):
             assert torch.equal(bits(y), bits(y1))
+
+
+@pytest.mark.parametrize("rank,d", [(36, 256), (48, 384), (64, 128), (64, 1024), (33, 128), (63, 256), (50, 640)])
+def test_in_place_as_two_launches(rank, d):
+    """DiReFT at rank 33-64: against the oracle, and bit for bit what a workspace without room for z gets (one launch)."""
+    from oracle import preft_oracle as ora
+    from parity_util import bits, check_guards, compare, dev_tables, direft_pools_to_device, padded
+    N = 5
+    rng = np.random.Generator(np.random.PCG64(rank + d))
+    lens = np.array(LENS)
+    tab = wl.from_lengths(lens, rng.integers(-1, N + 1, size=len(lens)), np.where(np.arange(len(lens)) < 14, np.maximum(lens - (lens > 100), 0), 0))
+    T = tab.T
+    ss, sa, sp = dev_tables(tab)
+    h0 = wl.activations(T, d, "bf16", device="cuda", seed=3)
+    pool = wl.direft_pool(N, rank, d, "bf16", device="cuda", seed=4)
+    W1, W2t, b, keep = direft_pools_to_device(pool, bias=True)
+    for mode, pos in ((preft.PREFT_PREFILL_ONLY, ora.PROMPT_ONLY), (preft.PREFT_ALL_TOKENS, ora.ALL_POSITIONS)):
+        got = []
+        for z_rank, flags in ((rank, preft.test_flags(resident=1)), (0, preft.test_flags(variant=4))):
+            ws = preft.new_workspace(T, tab.S, z_rank=z_rank)
+            ws.fill_(0xa5)
+            buf, h = padded(h0, 8, 7.0)
+            prev = preft.set_test_flags(flags)
+            try:
+                preft.preft_direft_apply(h, ss, sa, sp, W1, W2t, b, rank, 0.5, mode, ws)
+            finally:
+                preft.set_test_flags(prev)
+            torch.cuda.synchronize()
+            check_guards(buf, T, d, 7.0)
+            got.append(h)
+        want = ora.direft(h0.cpu(), tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, [a.cpu() for a in pool.A],
+                          [m.cpu() for m in pool.B], [v.cpu() for v in pool.b], rank, 0.5, pos)
+        compare(got[0], h0, want, ora.positions(T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, pos), "bf16")
+        assert torch.equal(bits(got[0]), bits(got[1]))
