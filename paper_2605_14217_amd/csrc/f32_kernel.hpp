@@ -39,6 +39,8 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
 {
     constexpr int WAVES = F32_WAVES;
     constexpr bool AHEAD = NB <= 2;                           // register budget: factors requested a unit ahead, or block by block
+    constexpr bool BY_LDS = ODD && NB <= 2;                   // expand: z the first operand, whole units of factors through LDS
+    static_assert(!BY_LDS || 64 * 16 * NB * 4 <= 2 * 16 * MFMA_TRS * 16, "a unit's factors fit the turn buffers");
     __shared__ __attribute__((aligned(16))) char lds[f32_red_bytes(NB) > f32_turn_bytes() ? f32_red_bytes(NB) : f32_turn_bytes()];
 
     if (!schedule_matches(p)) return;
@@ -72,7 +74,7 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         xu[i] = as_global(p.x) + row_u[i] * p.ldx * 4;
-        yu[i] = as_global(p.y) + row_u[i] * p.ldy * 4;
+        yu[i] = as_global(p.y) + (BY_LDS ? tile.row(4 * q + i) : row_u[i]) * p.ldy * 4;
     }
     auto turned = [&](const u32x4_t (&raw)[4], u32x4_t (&op)[4], u32x4_t *buf) {
 #pragma unroll
@@ -173,7 +175,12 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
         const int off = min(u * 256 + c16 * 16, y_last);
 #pragma unroll
         for (int i = 0; i < 4; ++i) yr[i] = ld16_stream(yu[i] + off);
-        if constexpr (AHEAD) {
+        if constexpr (BY_LDS) {                               // the unit's [64 columns][r] block, 16 r contiguous pieces
+            gcptr_t block = Bt + (int64_t)u * 256 * r;
+            const int last = min(16 * r, (p.d_out - u * 64) * r / 4) - 1;   // d_out % 4 == 0
+#pragma unroll
+            for (int j = 0; j < 4 * NB; ++j) wr[j / NB][j % NB] = ld16(block + min(lane + 64 * j, last) * 16);
+        } else if constexpr (AHEAD) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) load_w(wr[s], u, s);
         }
@@ -210,7 +217,40 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
     uint32_t last_mask[4];                                    // up to rank 32: which of the lane's factors of the last block exist
 #pragma unroll
     for (int e = 0; e < 4; ++e) last_mask[e] = 16 * (NB - 1) + 4 * g + (ODD ? e : 0) < r ? 0xffffffffu : 0u;
-    auto finish = [&](u32x4_t (&yr)[4], u32x4_t (&wr)[NW][NB], int u) {
+    // Ranks that are no multiple of 4, up to 32: MFMA t of rank block b and column place k takes ranks 16b + 4g + t of the columns 4n + k; lane
+    // (n, g) then owns the columns 4n .. 4n + 3 of the rows 4g .. 4g + 3, which it has loaded: y passes through registers only.
+    // The factors of a unit are fetched in whole lines and lie in LDS as in memory.  (Fetched element by element as the operand
+    // wants them, every lane is an access of its own: 4096 -> 4096, 2304 rows, rank 7 / 31 35.2 / 49.0 us, now 30.5 / 44.0; in place, rank 11,
+    // 11 500 rows 120 and 104.  Multiples of 4 fetch 16 bytes a lane and gain nothing: rank 8 30.1 and 30.6, rank 16 31.9 and 31.2, rank 20 156 and 160.)
+    char *fac = reinterpret_cast<char *>(tr);
+    auto finish_by_lds = [&](u32x4_t (&y)[4], u32x4_t (&w)[NW][NB], int u) {
+#pragma unroll
+        for (int j = 0; j < 4 * NB; ++j)
+            if (lane + 64 * j < 16 * r) *reinterpret_cast<u32x4_t *>(fac + (lane + 64 * j) * 16) = w[j / NB][j % NB];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            f32x4_t part[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int rank = 16 * b + 4 * g + e;      // past r: one that exists, masked (zero times an infinite factor would not be zero)
+                    uint32_t v = *reinterpret_cast<const uint32_t *>(fac + ((4 * c16 + k) * r + min(rank, r - 1)) * 4);
+                    if (b == NB - 1) v &= last_mask[e];
+                    part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[b][e], f(v), part[e], 0, 0, 0);
+                }
+            const f32x4_t d = (part[0] + part[1]) + (part[2] + part[3]);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) y[v][k] = __float_as_uint(f(y[v][k]) + d[v]);
+        }
+        const int off = u * 256 + c16 * 16;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (off <= y_last && 4 * q + v < tile.n_rows) st16_stream(yu[v] + off, y[v]);
+    };
+    auto finish_lane_order = [&](u32x4_t (&yr)[4], u32x4_t (&wr)[NW][NB], int u) {
         u32x4_t yo[4];
         turned(yr, yo, tr);
 #pragma unroll
@@ -255,6 +295,10 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
             const u32x4_t o = tr[(4 * i + q) * MFMA_TRS + c16];
             if (off <= y_last && 4 * i + q < tile.n_rows) st16_stream(yu[i] + off, o);
         }
+    };
+    auto finish = [&](u32x4_t (&yr)[4], u32x4_t (&wr)[NW][NB], int u) {
+        if constexpr (BY_LDS) finish_by_lds(yr, wr, u);
+        else                  finish_lane_order(yr, wr, u);
     };
     int u = ubase + wave;
     if (!AHEAD && u < uend) load_yw(y0, w0, u);
