@@ -34,7 +34,7 @@ template __global__ void preft::mfma_wide_layers_kernel<1, 1, 4, 1, false>(preft
 template __global__ void preft::mfma_wide_layers_kernel<2, 1, 8, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<8, 1, 4, 1, false>(preft::ApplyArgs);
 template __global__ void preft::panel_expand_kernel<4, 4, 1, false>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_kernel<2, false, false, true, 8>(preft::ApplyArgs, int);
+template __global__ void preft::small_tile_kernel<2, false, false, true, 8>(preft::ApplyArgs, preft::SmallLaunch);
 template __global__ void preft::valu_tile_kernel<1, 4, 4, false, 2, 0, true>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<2, 4, 2, false, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<2, 4, 4, false, 3, 0, true>(preft::ApplyArgs);

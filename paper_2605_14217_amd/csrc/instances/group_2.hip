@@ -33,8 +33,8 @@ template __global__ void preft::mfma_wide_layers_kernel<1, 1, 4, 2, false>(preft
 template __global__ void preft::mfma_wide_layers_kernel<2, 2, 4, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<8, 1, 8, 1, false>(preft::ApplyArgs);
 template __global__ void preft::panel_expand_kernel<4, 4, 1, true>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_kernel<1, false, false, false, 8>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_kernel<2, true, false, true, 8>(preft::ApplyArgs, int);
+template __global__ void preft::small_tile_kernel<1, false, false, false, 8>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<2, true, false, true, 8>(preft::ApplyArgs, preft::SmallLaunch);
 template __global__ void preft::valu_tile_kernel<1, 4, 4, false, 3, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<2, 4, 2, true, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<2, 4, 4, true, 1, 0, false>(preft::ApplyArgs);

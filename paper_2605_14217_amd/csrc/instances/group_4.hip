@@ -31,9 +31,9 @@ template __global__ void preft::mfma_wide_kernel<8, 1, 4, 1, true, 1, false, fal
 template __global__ void preft::mfma_wide_layers_kernel<1, 2, 4, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<4, 1, 4, 1, true>(preft::ApplyArgs);
 template __global__ void preft::panel_expand_kernel<4, 4, 2, true>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_kernel<1, false, true, false, 8>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_kernel<4, false, false, true, 8>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_layers_kernel<1, false>(preft::ApplyArgs, int);
+template __global__ void preft::small_tile_kernel<1, false, true, false, 8>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<4, false, false, true, 8>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_layers_kernel<1, false>(preft::ApplyArgs, preft::SmallLaunch);
 template __global__ void preft::valu_tile_kernel<1, 2, 4, true, 1, 8, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<1, 4, 2, true, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<1, 4, 4, true, 1, 0, false>(preft::ApplyArgs);

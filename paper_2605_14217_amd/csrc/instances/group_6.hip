@@ -29,9 +29,9 @@ template __global__ void preft::mfma_wide_kernel<4, 1, 8, 1, false, 3, true, tru
 template __global__ void preft::mfma_wide_kernel<8, 1, 8, 1, false, 1, false, true, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<2, 1, 4, 1, true>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<4, 1, 8, 1, false>(preft::ApplyArgs);
-template __global__ void preft::small_tile_kernel<1, true, false, true, 8>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_kernel<8, false, false, true, 4>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_layers_kernel<2, false>(preft::ApplyArgs, int);
+template __global__ void preft::small_tile_kernel<1, true, false, true, 8>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<8, false, false, true, 4>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_layers_kernel<2, false>(preft::ApplyArgs, preft::SmallLaunch);
 template __global__ void preft::thin_expand_kernel<2, 2>(preft::ApplyArgs, int);
 template __global__ void preft::valu_tile_kernel<1, 4, 1, true, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<1, 4, 4, false, 1, 0, true>(preft::ApplyArgs);

@@ -135,19 +135,21 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
 {
     const unsigned tiles = likely_units(a, S);                // a multiple of 8 (col_split is 1 here)
     if constexpr (DIREFT) {
-        void (*kernel)(ApplyArgs, int) = small_tile_kernel<NB, true, ODD, true>;
+        void (*kernel)(ApplyArgs, SmallLaunch) = small_tile_kernel<NB, true, ODD, true>;
         if (a.h_layers) kernel = small_tile_layers_kernel<NB, ODD>;
-        hipLaunchKernelGGL(kernel, dim3(tiles, a.n_layers), dim3(SMALL_WAVES * 64), 0, stream, a, 1);
+        hipLaunchKernelGGL(kernel, dim3(tiles, a.n_layers), dim3(SMALL_WAVES * 64), 0, stream, a, SmallLaunch{1, 0});
     } else {
         const SmallShape shape = small_shape(a, S, n_slices, k);
         const int cols = 128 * shape.units;
-        int64_t shares = (a.d_out + cols - 1) / cols;
-        for (int i = 1; i < n_slices; ++i) shares += (a.more[i - 1].d_out + cols - 1) / cols;
+        auto shares_of = [&](int d) { return (d + cols - 1) / cols; };
+        const SmallLaunch l = {shares_of(a.d_out), n_slices > 1 ? shares_of(a.more[0].d_out) : 0};
+        const int shares = l.shares0 + l.shares1 + (n_slices > 2 ? shares_of(a.more[1].d_out) : 0);     // small_shape: 1536 at most
         a.col_split = shape.units;
-        void (*kernel)(ApplyArgs, int) = small_tile_kernel<NB, false, ODD, true>;
+        void (*kernel)(ApplyArgs, SmallLaunch) = small_tile_kernel<NB, false, ODD, true>;
         if constexpr (NB == 1) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false>; }
         if constexpr (NB > 2) { if (shape.waves == 4) kernel = small_tile_kernel<NB, false, ODD, true, 4>; }
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * shares)), dim3(shape.waves * 64), 0, stream, a, n_slices);
+        const unsigned slots = tiles / 8 < 65535 ? tiles / 8 : 65535;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)shares * 8, slots), dim3(shape.waves * 64), 0, stream, a, l);
     }
 }
 

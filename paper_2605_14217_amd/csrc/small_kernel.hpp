@@ -22,39 +22,36 @@ constexpr int SMALL_WAVES = 8;
 // DEEP: few workgroups, each alone on its compute unit: up to 256 registers for requests in flight.  Otherwise (rank <= 16: the LDS
 // of more rank blocks does not fit twice) 128, two workgroups per compute unit, which hide one another's trips.
 // One tile and share; `unit` and `share` are uniform over the workgroup.
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
-__device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int n_chunk_units, int share, int sh0, int sh1,
-                                               u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
+//
+// NG: groups of four rows that the tile fills at most, 1 or 4.  Of a gathered tile of one to four decode rows the other three quarters of
+// every load of x and y would bring the same rows again, and the texture path is what a workgroup waits for: 256 KB of x and A
+// for a 4096-wide shrink.  (32 decode rows of 32 adapters, rank 16, replayed: q+k+v 8.0 -> 6.5 us, 4096 -> 4096 7.1 -> 5.7, 4096 -> 2 x 14336
+// 13.7 -> 10.9, 14336 -> 4096 14.5 -> 11.0, with the launch arguments asked for together.)  Rows that are not loaded leave what was in the turn buffer: their z and y are their own and are not stored.
+struct SmallOutput {                                          // the output of a workgroup, and which share of its columns
+    void *y;
+    int64_t ldy;
+    int d_out, share;
+    const void *const *A_pool, *const *Bt_pool;
+};
+
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, int NG>
+__device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallOutput &o, const i32x4_t entry, bool gathered, int row0, int n_rows,
+                                                u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
 {
     // units of the shrink and of the expand sweep in flight (registers)
     constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : 2;
-    constexpr int DEPTH = DEEP ? (NB == 1 ? (ODD ? 2 : 4) : NB == 2 ? 2 : 1) : 1;
+    constexpr bool EARLY = NG == 1 && DEEP && NB <= 2;         // registers for the first units of the expand beside the shrink's
+    constexpr int DEPTH = DEEP ? (NB == 1 ? (ODD || EARLY ? 2 : 4) : NB == 2 ? (EARLY ? 1 : 2) : 1) : 1;
     static_assert(!ODD || NB == 1, "the any-rank form covers rank <= 16");
     constexpr bool W_LATE = NB > 4;                           // factors of the expand step by step (registers)
     static_assert(DEEP || NB == 1, "two workgroups of more rank blocks do not fit a compute unit");
     constexpr int PIECES = 4;                                 // any-rank form: 16-byte pieces of a unit's factor block per lane
-    // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
     const int per_share = p.col_split;                        // units of a share
-    const bool gathered = unit >= n_chunk_units;
-    const int row0 = gathered ? 0 : unit % (CHUNK_ROWS / 16) * 16;
-    const i32x4_t entry = *reinterpret_cast<const PREFT_CONST i32x4_t *>(
-        gathered ? as_const(p.gtiles) + (unit - n_chunk_units) : as_const(p.chunks) + unit / (CHUNK_ROWS / 16));
-    const int n_rows = min(16, entry[2] - row0);
-    if (n_rows <= 0) return;                                  // uniform over the workgroup
-
-    int sl = 0;
-    void *y = p.y;
-    int64_t ldy = p.ldy;
-    int d_out = p.d_out;
-    const void *const *A_pool = p.A_pool, *const *Bt_pool = p.Bt_pool;
-    if (share >= sh0) {
-        sl = share >= sh0 + sh1 ? 2 : 1;
-        share -= sl == 2 ? sh0 + sh1 : sh0;
-        y = p.more[sl - 1].y; ldy = p.more[sl - 1].ldy; d_out = p.more[sl - 1].d_out;
-        A_pool = p.more[sl - 1].A_pool; Bt_pool = p.more[sl - 1].Bt_pool;
-    }
-    gcptr_t A = as_global(as_const(A_pool)[entry[0]]);
-    gcptr_t Bt = as_global(as_const(Bt_pool)[entry[0]]);
+    void *const y = o.y;
+    const int64_t ldy = o.ldy;
+    const int d_out = o.d_out, share = o.share;
+    gcptr_t A = as_global(as_const(o.A_pool)[entry[0]]);
+    gcptr_t Bt = as_global(as_const(o.Bt_pool)[entry[0]]);
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int lane = threadIdx.x & 63;
@@ -65,101 +62,26 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int
     u32x4_t *tr = turn[wave][0], *tra = turn[wave][1];
 
     // row slots past the tile alias its last row: same loads, same values; their stores are left out
-    int32_t row[4];
+    int32_t row[NG];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) row[i] = entry[1] + row0 + min(4 * i + q, n_rows - 1);
+    for (int i = 0; i < NG; ++i) row[i] = entry[1] + row0 + min(4 * i + q, n_rows - 1);
     if (gathered) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) row[i] = p.shorts[row[i]].y;
+        for (int i = 0; i < NG; ++i) row[i] = p.shorts[row[i]].y;
     }
-    gcptr_t xu[4];
-    gptr_t yu[4];
+    gcptr_t xu[NG];
+    gptr_t yu[NG];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NG; ++i) {
         xu[i] = as_global(p.x) + row[i] * p.ldx * 2;
         yu[i] = as_global(y) + row[i] * ldy * 2;
     }
 
-    // ---------------------------------------------------------------- shrink
-    f32x4_t acc[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    {
-        const int x_last = p.d_in * 2 - 16;                   // a row's last 16-byte piece; d_in % 8 == 0
-        const int k_units = (p.d_in + 127) >> 7;
-        auto load_a = [&](u32x4_t (&a)[4], int b, int off) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)                       // ranks past r alias the last one: their z is zeroed
-                a[i] = ld16(A + (uint32_t)(min(16 * b + 4 * i + q, r - 1) * (x_last + 16) + off));
-        };
-        // two halves of a batch take turns: one is on its way while the other is used
-        constexpr int HALVES = BATCH > 1 ? 2 : 1, H = BATCH / HALVES;
-        u32x4_t xr[HALVES][H][4], ar[HALVES][H][NB][4];
-        auto request = [&](u32x4_t (&x)[H][4], u32x4_t (&a)[H][NB][4], int u0) {
-#pragma unroll
-            for (int k = 0; k < H; ++k)
-                if (u0 + k * WAVES < k_units) {
-                    const int off = min((u0 + k * WAVES) * 256 + c16 * 16, x_last);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) x[k][i] = ld16(xu[i] + off);
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) load_a(a[k][b], b, off);
-                }
-        };
-        auto use = [&](u32x4_t (&x)[H][4], u32x4_t (&a)[H][NB][4], int u0) {
-#pragma unroll
-            for (int k = 0; k < H; ++k)
-                if (u0 + k * WAVES < k_units) {
-                    if ((u0 + k * WAVES) * 256 + c16 * 16 > x_last) {    // past the width: zero times zero
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            x[k][i] = u32x4_t{0u, 0u, 0u, 0u};
-#pragma unroll
-                            for (int b = 0; b < NB; ++b) a[k][b][i] = u32x4_t{0u, 0u, 0u, 0u};
-                        }
-                    }
-                    u32x4_t xo[4], ao[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = x[k][i];
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) xo[s] = tr[rl * MFMA_TRS + 4 * s + g];
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) tra[(4 * i + q) * MFMA_TRS + c16] = a[k][b][i];
-#pragma unroll
-                        for (int s = 0; s < 4; ++s) ao[s] = tra[rl * MFMA_TRS + 4 * s + g];
-#pragma unroll
-                        for (int s = 0; s < 4; ++s)
-                            acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ao[s]), as_bf16x8(xo[s]), acc[b], 0, 0, 0);
-                    }
-                }
-        };
-        if constexpr (HALVES == 2) {
-            request(xr[0], ar[0], wave);
-            request(xr[1], ar[1], wave + H * WAVES);
-            int u = wave;
-            for (; u + 2 * H * WAVES < k_units; u += 2 * H * WAVES) {
-                use(xr[0], ar[0], u);
-                request(xr[0], ar[0], u + 2 * H * WAVES);
-                use(xr[1], ar[1], u + H * WAVES);
-                request(xr[1], ar[1], u + 3 * H * WAVES);
-            }
-            use(xr[0], ar[0], u);
-            use(xr[1], ar[1], u + H * WAVES);
-        } else {
-            for (int u = wave; u < k_units; u += H * WAVES) {
-                request(xr[0], ar[0], u);
-                use(xr[0], ar[0], u);
-            }
-        }
-    }
-
-    // ---------------------------------------------------------------- first units of the expand
+    // ---------------------------------------------------------------- requests of the expand
     const int c_units = (d_out + 127) >> 7;
     const int ubase = DIREFT ? 0 : share * per_share, uend = DIREFT ? c_units : min(ubase + per_share, c_units);
     const int y_last = d_out * 2 - 16;
-    u32x4_t Y[DEPTH][4];
+    u32x4_t Y[DEPTH][NG];
     u32x2_t W[DEPTH][W_LATE ? 1 : 4][2][NB];
     u32x4_t Wb[ODD ? DEPTH : 1][PIECES];
     auto load_w = [&](u32x2_t (&w)[2][NB], int u, int s) {
@@ -177,7 +99,7 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int
     auto load_yw = [&](int k, int u) {
         const int off = min(u * 256 + c16 * 16, y_last);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) Y[k][i] = ld16(yu[i] + off);
+        for (int i = 0; i < NG; ++i) Y[k][i] = ld16(yu[i] + off);
         if constexpr (ODD) {                                  // the unit's [128 columns][r] block, contiguous
             const int last = last_factor_piece(d_out - u * 128, 128, r);
 #pragma unroll
@@ -187,9 +109,89 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int
             for (int s = 0; s < 4; ++s) load_w(W[k][s], u, s);
         }
     };
+    auto request_expand = [&] {
 #pragma unroll
-    for (int k = 0; k < DEPTH; ++k)
-        if (ubase + wave + k * WAVES < uend) load_yw(k, ubase + wave + k * WAVES);
+            for (int k = 0; k < DEPTH; ++k)
+            if (ubase + wave + k * WAVES < uend) load_yw(k, ubase + wave + k * WAVES);
+    };
+
+    // ---------------------------------------------------------------- shrink
+    f32x4_t acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    {
+        const int x_last = p.d_in * 2 - 16;                   // a row's last 16-byte piece; d_in % 8 == 0
+        const int k_units = (p.d_in + 127) >> 7;
+        auto load_a = [&](u32x4_t (&a)[4], int b, int off) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)                       // ranks past r alias the last one: their z is zeroed
+                a[i] = ld16(A + (uint32_t)(min(16 * b + 4 * i + q, r - 1) * (x_last + 16) + off));
+        };
+        // two halves of a batch take turns: one is on its way while the other is used
+        constexpr int HALVES = BATCH > 1 ? 2 : 1, H = BATCH / HALVES;
+        u32x4_t xr[HALVES][H][NG], ar[HALVES][H][NB][4];
+        auto request = [&](u32x4_t (&x)[H][NG], u32x4_t (&a)[H][NB][4], int u0) {
+#pragma unroll
+            for (int k = 0; k < H; ++k)
+                if (u0 + k * WAVES < k_units) {
+                    const int off = min((u0 + k * WAVES) * 256 + c16 * 16, x_last);
+#pragma unroll
+                    for (int i = 0; i < NG; ++i) x[k][i] = ld16(xu[i] + off);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) load_a(a[k][b], b, off);
+                }
+        };
+        auto use = [&](u32x4_t (&x)[H][NG], u32x4_t (&a)[H][NB][4], int u0) {
+#pragma unroll
+            for (int k = 0; k < H; ++k)
+                if (u0 + k * WAVES < k_units) {
+                    if ((u0 + k * WAVES) * 256 + c16 * 16 > x_last) {    // past the width: zero times zero
+#pragma unroll
+                        for (int i = 0; i < NG; ++i) x[k][i] = u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+#pragma unroll
+                            for (int b = 0; b < NB; ++b) a[k][b][i] = u32x4_t{0u, 0u, 0u, 0u};
+                    }
+                    u32x4_t xo[4], ao[4];
+#pragma unroll
+                    for (int i = 0; i < NG; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = x[k][i];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) xo[s] = tr[rl * MFMA_TRS + 4 * s + g];
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) tra[(4 * i + q) * MFMA_TRS + c16] = a[k][b][i];
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) ao[s] = tra[rl * MFMA_TRS + 4 * s + g];
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+                            acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ao[s]), as_bf16x8(xo[s]), acc[b], 0, 0, 0);
+                    }
+                }
+        };
+        if constexpr (HALVES == 2) {
+            request(xr[0], ar[0], wave);
+            request(xr[1], ar[1], wave + H * WAVES);
+            if constexpr (EARLY) request_expand();
+            int u = wave;
+            for (; u + 2 * H * WAVES < k_units; u += 2 * H * WAVES) {
+                use(xr[0], ar[0], u);
+                request(xr[0], ar[0], u + 2 * H * WAVES);
+                use(xr[1], ar[1], u + H * WAVES);
+                request(xr[1], ar[1], u + 3 * H * WAVES);
+            }
+            use(xr[0], ar[0], u);
+            use(xr[1], ar[1], u + H * WAVES);
+        } else {
+            for (int u = wave; u < k_units; u += H * WAVES) {
+                request(xr[0], ar[0], u);
+                use(xr[0], ar[0], u);
+            }
+        }
+    }
+
+    if constexpr (!EARLY) request_expand();                   // before z is summed
 
     // ---------------------------------------------------------------- sum over the wavefronts, z -> expand operand
 #pragma unroll
@@ -227,7 +229,7 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int
     auto finish = [&](int k, int u) {
         u32x4_t yo[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[k][i];
+        for (int i = 0; i < NG; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[k][i];
 #pragma unroll
         for (int s = 0; s < 4; ++s) yo[s] = tr[rl * MFMA_TRS + 4 * s + g];
         if constexpr (ODD) {
@@ -264,9 +266,9 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int
         }
         const int off = u * 256 + c16 * 16;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const u32x4_t o = tr[(4 * i + q) * MFMA_TRS + c16];
-            if (off <= y_last && 4 * i + q < n_rows) st16_stream(yu[i] + off, o);
+        for (int i = 0; i < NG; ++i) {
+            const u32x4_t v = tr[(4 * i + q) * MFMA_TRS + c16];
+            if (off <= y_last && 4 * i + q < n_rows) st16_stream(yu[i] + off, v);
         }
     };
     for (int u = ubase + wave; u < uend; u += WAVES * DEPTH) {
@@ -279,45 +281,67 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, int unit, int
     }
 }
 
-// The workgroups of a tile -- shares of the first output, then those of the others -- sit side by side on one XCD.  A launch has
-// as many as the batch is likely to need; what exceeds it is strided over.
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
-__device__ __forceinline__ void small_tile_body(const ApplyArgs &p, int n_slices)
+__device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOutput &o, int unit, int n_chunk_units,
+                                               u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
+{
+    // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
+    const bool gathered = unit >= n_chunk_units;
+    const int row0 = gathered ? 0 : unit % (CHUNK_ROWS / 16) * 16;
+    const i32x4_t entry = *reinterpret_cast<const PREFT_CONST i32x4_t *>(
+        gathered ? as_const(p.gtiles) + (unit - n_chunk_units) : as_const(p.chunks) + unit / (CHUNK_ROWS / 16));
+    const int n_rows = min(16, entry[2] - row0);
+    if (n_rows <= 0) return;                                  // uniform over the workgroup
+    if (n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4>(p, o, entry, gathered, row0, n_rows, turn, red);
+    else            small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1>(p, o, entry, gathered, row0, n_rows, turn, red);
+}
+
+// A launch out of place: blockIdx.x = 8 share + XCD, blockIdx.y = the slot of a tile on that XCD (in place: blockIdx.x = 8 slot + XCD).  The shares of a
+// tile -- those of the first output, then those of the others -- sit on one XCD, and the slots that have a tile come first.  A
+// launch has as many slots as the batch is likely to need; what exceeds it is strided over.
+struct SmallLaunch { int shares0, shares1; };
+
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
+__device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallLaunch &l)
 {
     __shared__ u32x4_t turn[WAVES][2][16 * MFMA_TRS];         // activations, and the factor
     __shared__ float red[WAVES * NB * 4 * 64];
 
+    // What the launch arguments say is asked for together with the header: each line of them that is touched later is a trip of its own.
+    SmallOutput o = {p.y, p.ldy, p.d_out, 0, p.A_pool, p.Bt_pool};
+    if constexpr (!DIREFT) {
+        o.share = blockIdx.x >> 3;
+        if (o.share >= l.shares0) {
+            const int sl = o.share >= l.shares0 + l.shares1 ? 2 : 1;
+            o.share -= sl == 2 ? l.shares0 + l.shares1 : l.shares0;
+            o.y = p.more[sl - 1].y; o.ldy = p.more[sl - 1].ldy; o.d_out = p.more[sl - 1].d_out;
+            o.A_pool = p.more[sl - 1].A_pool; o.Bt_pool = p.more[sl - 1].Bt_pool;
+        }
+    }
+    asm volatile("" ::"s"(o.y), "s"(o.d_out), "s"(o.A_pool), "s"(o.Bt_pool), "s"(p.x), "s"(p.gtiles), "s"(p.chunks), "s"(p.shorts), "s"(p.rank));
     if (!schedule_matches(p)) return;
-    const int per_share = p.col_split;                        // units of a share
-    auto shares_of = [&](int d) { return ((d + 127) / 128 + per_share - 1) / per_share; };
-    const int sh0 = DIREFT ? 1 : shares_of(p.d_out);
-    const int sh1 = !DIREFT && n_slices > 1 ? shares_of(p.more[0].d_out) : 0;
-    const int sh2 = !DIREFT && n_slices > 2 ? shares_of(p.more[1].d_out) : 0;
-    const int shares = sh0 + sh1 + sh2;
     int n_chunk_units;
     const int n_units = tile_units<16>(p, &n_chunk_units);
-    const int per_xcd = (n_units + 7) >> 3, step = (gridDim.x >> 3) / shares;     // the grid is a multiple of 8 shares
-    int t = (blockIdx.x >> 3) / shares;
-    const int share = (blockIdx.x >> 3) - t * shares;
-    for (; t < per_xcd; t += step) {
+    const int per_xcd = (n_units + 7) >> 3;
+    for (int t = DIREFT ? blockIdx.x >> 3 : blockIdx.y; t < per_xcd; t += DIREFT ? gridDim.x >> 3 : gridDim.y) {
         const int unit = few_tiles_unit(p, n_chunk_units, per_xcd, t);
-        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES>(p, unit, n_chunk_units, share, sh0, sh1, turn, red);
+        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES>(p, o, unit, n_chunk_units, turn, red);
         __syncthreads();                                      // the next tile's sums go where this one's are still being read
     }
 }
 
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES = SMALL_WAVES>
-__global__ __launch_bounds__(WAVES * 64, DEEP ? 2 : 4) void small_tile_kernel(ApplyArgs p, int n_slices)
+__global__ __launch_bounds__(WAVES * 64, DEEP ? 2 : 4) void small_tile_kernel(ApplyArgs p, SmallLaunch l)
 {
-    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES>(p, n_slices);
+    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES>(p, l);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer
 template <int NB, bool ODD>
-__global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(ApplyArgs p, int n_slices)
+__global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(ApplyArgs p, SmallLaunch l)
 {
     select_layer(p);
-    small_tile_body<NB, true, ODD, true, SMALL_WAVES>(p, n_slices);
+    small_tile_body<NB, true, ODD, true, SMALL_WAVES>(p, l);
 }
 
 }  // namespace preft

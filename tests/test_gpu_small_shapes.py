@@ -54,3 +54,43 @@ def test_shape_against_the_oracle(tmp_path_factory, shape, rank, d_in, d_outs, d
             want = ora.lora(y0.cpu(), x.cpu(), tab.seg_start, tab.seg_adapter, tab.seg_prefill_len,
                             [a.cpu() for a in pl.A], [b.cpu() for b in pl.B], rank, 2.0, pos)
             compare(y, y0, want, owner, "bf16")
+
+
+@pytest.mark.parametrize("rank,d,d_out", [(16, 512, 4096), (4, 136, 264), (7, 1000, 520), (32, 256, 1032), (64, 384, 512), (96, 128, 256)])
+def test_tiles_of_one_to_sixteen_rows(rank, d, d_out):
+    """Tiles of at most four rows load a quarter of what others do: gathered tiles of 1, 4, 5 and 16 rows and prompts that end 1, 4 and 5 rows
+    into a tile, out of place and in place, against the oracle; and the row's bits are those it has beside others in a tile."""
+    from oracle import preft_oracle as ora
+    from parity_util import bits, compare, dev_tables, direft_pools_to_device, lora_pools_to_device
+    counts, prompts = [1, 4, 5, 16], [17, 20, 21, 36]
+    N = len(counts) + len(prompts)
+    lens = np.array([1] * sum(counts) + prompts)
+    ids = np.concatenate([np.repeat(np.arange(len(counts)), counts), len(counts) + np.arange(len(prompts))]).astype(int)
+    order = np.random.Generator(np.random.PCG64(rank)).permutation(len(lens))
+    x = None
+    rows = {}                                                 # the same rows under one adapter each, and all under adapter 0 (fuller tiles)
+    for kind, who in (("own", ids[order]), ("one", np.zeros(len(lens), dtype=int))):
+        tab = wl.from_lengths(lens[order], who, np.where(lens > 1, lens, 0)[order])
+        if x is None:
+            x, y0, h0 = (wl.activations(tab.T, n, "bf16", device="cuda", seed=i) for i, n in enumerate((d, d_out, d)))
+        ss, sa, sp = dev_tables(tab)
+        pool, dpool = wl.lora_pool(N, rank, d, d_out, "bf16", device="cuda", seed=5), wl.direft_pool(N, rank, d, "bf16", device="cuda", seed=6)
+        if kind == "own":                                     # every adapter has the same weights, so that rows can be compared
+            for m in (pool.A, pool.B, dpool.A, dpool.B, dpool.b):
+                for i in range(1, N):
+                    m[i].copy_(m[0])
+            same = pool, dpool
+        pool, dpool = same
+        A, B, keep = lora_pools_to_device(pool)
+        W1, W2t, b, keep2 = direft_pools_to_device(dpool)
+        ws = preft.new_workspace(tab.T, tab.S)
+        y, h = y0.clone(), h0.clone()
+        preft.preft_lora_apply(y, x, ss, sa, sp, A, B, rank, 2.0, preft.PREFT_ALL_TOKENS, ws)
+        preft.preft_direft_apply(h, ss, sa, sp, W1, W2t, b, rank, 0.5, preft.PREFT_ALL_TOKENS, ws)
+        owner = ora.positions(tab.T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, ora.ALL_POSITIONS)
+        tables = (tab.seg_start, tab.seg_adapter, tab.seg_prefill_len)
+        compare(y, y0, ora.lora(y0.cpu(), x.cpu(), *tables, [a.cpu() for a in pool.A], [m.cpu() for m in pool.B], rank, 2.0, ora.ALL_POSITIONS), owner, "bf16")
+        compare(h, h0, ora.direft(h0.cpu(), *tables, [a.cpu() for a in dpool.A], [m.cpu() for m in dpool.B], [v.cpu() for v in dpool.b], rank, 0.5,
+                                  ora.ALL_POSITIONS), owner, "bf16")
+        rows[kind] = y, h
+    assert bits(rows["own"][0]).equal(bits(rows["one"][0])) and bits(rows["own"][1]).equal(bits(rows["one"][1]))
