@@ -122,7 +122,7 @@ int launch_schedule(void *workspace, const int32_t *seg_start, const int32_t *se
                     hipStream_t stream)
 {
     ScheduleView v = view_of(workspace, T, S);
-    hipLaunchKernelGGL(schedule_kernel, dim3(1), dim3(SCHED_THREADS), 0, stream, seg_start, seg_adapter,
+    hipLaunchKernelGGL(schedule_kernel, dim3(1), dim3(sched_threads(S, N)), 0, stream, seg_start, seg_adapter,
                        seg_prefill_len, S, T, N, (mode & PREFT_ALL_TOKENS) ? 1 : 0, v);
     return check_launch();
 }
