@@ -69,11 +69,15 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool dire
     if (!direft && k.colsplit) return k.colsplit > 1;
     if (a.T > SMALL_T) return false;
     if (!direft) return true;
-    // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 32
-    // rows: 10.0 and 10.6 us, 1000 rows 11.4 and 13.1; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
+    // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 1000
+    // rows 11.4 and 13.1 us; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
     // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81)
     if (likely_tiles(a, S) > 200) return false;               // whatever n_layers: a layer's result is that of its one-layer call, bit for bit
     if (a.rank > 16) return a.rank <= 64;                     // above, its registers spill: rank 128, d = 6320, 77 rows 123 and 130 us
+    // A few decode rows of an adapter each: tiles of which this kernel loads a quarter.  Rank 16, 32 rows of 32 adapters, resident / this, us: d = 4096 9.2 /
+    // 8.2, 8192 14.8 / 13.2, 8 layers of 4096 17.5 / 13.6; rank 7, 8192 17.5 / 15.3; d = 14336 (streamed) 27.6 / 22.4; but 256 rows of 200 adapters
+    // 12.5 / 13.6, of 32 10.4 / 11.0, and 8 layers of 46 tiles, more than a tile for every compute unit, 22.0 / 25.0.
+    if (a.all_tokens && prompt_rows(a, S) == 0 && likely_tiles(a, S) <= 32 && a.T <= 3 * likely_tiles(a, S)) return true;
     return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
 }
 
