@@ -1,5 +1,8 @@
 """ctypes binding of libpreft.so: argument marshalling only, same names as the C ABI.
 
+The schedule and apply calls of a serving loop go through _marshal.so (csrc/marshal.cpp) where their arguments are
+ordinary tensors that pass every check; what it does not take, and a package in which it is not built, go through ctypes.
+
 PyTorch supplies device memory and the current HIP stream; every step of the path runs in
 the library's kernels.  There is no fallback: if the library is missing, calls raise.
 """
@@ -75,6 +78,7 @@ ABI_SYMBOLS = ("preft_workspace_bytes", "preft_workspace_bytes_z", "preft_schedu
                "preft_slots_stats", "preft_schedule_counts", "preft_strerror", "preft_version")
 
 _lib = None
+_native = None                                                # _marshal, bound to _lib's entry points
 
 
 class PreftError(RuntimeError):
@@ -86,7 +90,7 @@ class PreftError(RuntimeError):
 def load_library(path: Optional[str] = None):
     """Load libpreft.so (built in-tree by paper_2605_14217_amd.build; the environment variable
     PREFT_LIBRARY names another build of it) and declare its prototypes."""
-    global _lib
+    global _lib, _native
     if _lib is not None and path is None:
         return _lib
     path = path or os.environ.get("PREFT_LIBRARY") or LIB_PATH
@@ -144,7 +148,23 @@ def load_library(path: Optional[str] = None):
     lib.preft_version.restype = c.c_int
     lib.preft_version.argtypes = []
     _lib = lib
+    _native = _load_marshal(lib)
     return lib
+
+
+def _load_marshal(lib):
+    if not os.path.exists(os.path.join(_HERE, "_marshal.so")):
+        return None
+    try:
+        from . import _marshal
+    except ImportError as e:                                  # built against another torch
+        import warnings
+        warnings.warn(f"preft: _marshal.so does not load ({e}); rebuild with python -m paper_2605_14217_amd.build.  Calls are marshalled in Python.")
+        return None
+    _marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        lib.preft_schedule, lib.preft_lora_apply, lib.preft_lora_apply_packed, lib.preft_direft_apply, lib.preft_loreft_apply,
+        lib.preft_direft_apply_layers)))
+    return _marshal
 
 
 # ----------------------------------------------------------------------------------------
@@ -253,6 +273,10 @@ def new_workspace(T: int, S: int, device="cuda", z_rank: int = 0, z_proj: int = 
 
 def preft_schedule(workspace: torch.Tensor, seg_start, seg_adapter, seg_prefill_len, T: int, N: int,
                    mode: int, stream=None) -> None:
+    if _native is not None:
+        rc = _native.schedule(workspace, seg_start, seg_adapter, seg_prefill_len, T, N, mode, _stream(stream))
+        if rc is not None:
+            return _check(rc, "preft_schedule")
     S = int(seg_adapter.numel())
     rc = load_library().preft_schedule(
         workspace.data_ptr(), workspace.numel() * workspace.element_size(),
@@ -273,6 +297,11 @@ def preft_lora_apply(y: torch.Tensor, x: torch.Tensor, seg_start, seg_adapter, s
                      workspace: torch.Tensor, stream=None) -> None:
     """y[t] += scale * B_i (A_i x[t]) on active rows, in place.  A_pool/B_pool: pointer tables
     (see pointer_table) of [rank, d_in] and [d_out, rank] matrices."""
+    if _native is not None:
+        rc = _native.lora(y, x, seg_start, seg_adapter, seg_prefill_len, A_pool, B_pool, rank, scale, mode, workspace, _stream(stream),
+                          _extra_mode_bits)
+        if rc is not None:
+            return _check(rc, "preft_lora_apply")
     yp, ldy, T, d_out = _matrix(y, "y")
     xp, ldx, T2, d_in = _matrix(x, "x")
     if T != T2 or x.dtype is not y.dtype:
@@ -295,6 +324,11 @@ def preft_lora_apply_packed(ys: Sequence[torch.Tensor], x: torch.Tensor, seg_sta
                             workspace: torch.Tensor, stream=None) -> None:
     """ys[p][t] += scale * B_{p,i} (A_{p,i} x[t]) for every projection p of the same x (q,k,v or
     gate,up); ys may be separate tensors or column slices of one tensor."""
+    if _native is not None:
+        rc = _native.lora_packed(ys, x, seg_start, seg_adapter, seg_prefill_len, A_pools, B_pools, rank, scale, mode, workspace,
+                                 _stream(stream), _extra_mode_bits)
+        if rc is not None:
+            return _check(rc, "preft_lora_apply_packed")
     n = len(ys)
     if len(A_pools) != n or len(B_pools) != n:
         raise ValueError("one A pool and one B pool per output")
@@ -382,6 +416,11 @@ def preft_direft_apply_layers(hs: Sequence[torch.Tensor], h_layers: torch.Tensor
     stride and dtype); h_layers = pointer_table(hs) made once by the caller; W1_pools / W2t_pools /
     b_pools: int64 device tensors of len(hs) entries, each the data_ptr() of that layer's pointer
     table of N slots (b_pools None: no bias; an entry 0: no bias in that layer)."""
+    if _native is not None:
+        rc = _native.reft_layers(hs, h_layers, seg_start, seg_adapter, seg_prefill_len, W1_pools, W2t_pools, b_pools, N, rank, scale, mode,
+                                 workspace, _stream(stream), _extra_mode_bits)
+        if rc is not None:
+            return _check(rc, "preft_direft_apply_layers")
     L = len(hs)
     hp, ldh, T, d = _matrix(hs[0], "hs[0]")
     like = (ldh, T, d)
@@ -406,6 +445,11 @@ def preft_direft_apply_layers(hs: Sequence[torch.Tensor], h_layers: torch.Tensor
 
 def _reft_apply(entry: str, h, seg_start, seg_adapter, seg_prefill_len, W1_pool, W2t_pool, b_pool, rank, scale,
                 mode, workspace, stream) -> None:
+    if _native is not None:
+        rc = _native.reft(entry == "preft_loreft_apply", h, seg_start, seg_adapter, seg_prefill_len, W1_pool, W2t_pool, b_pool, rank, scale,
+                          mode, workspace, _stream(stream), _extra_mode_bits)
+        if rc is not None:
+            return _check(rc, entry)
     hp, ldh, T, d = _matrix(h, "h")
     S = int(seg_adapter.numel())
     N = int(W1_pool.numel())

@@ -1,4 +1,4 @@
-"""Builds libpreft.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Builds libpreft.so (hand-written HIP for gfx950) and _marshal.so (the binding's marshalling) in-tree."""
 from __future__ import annotations
 
 import os
@@ -7,6 +7,7 @@ import subprocess
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libpreft.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -24,10 +25,23 @@ def sources():
     return [os.path.join(CSRC, "preft_api.hip"), os.path.join(CSRC, "slots.hip")] + groups
 
 
+def marshal_command(out: str):
+    """g++ line of the extension module (host code only, against this torch's headers)."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd += [f for d in include_paths() + [sysconfig.get_paths()["include"]] for f in ("-isystem", d)]
+    return cmd + [os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build_library(verbose: bool = False) -> str:
     """Compile every HIP source (one hipcc per translation unit, in parallel) and link them into
     paper_2605_14217_amd/libpreft.so; returns its path."""
     import concurrent.futures
+    import shutil
     import tempfile
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"]
@@ -44,13 +58,19 @@ def build_library(verbose: bool = False) -> str:
 
     with tempfile.TemporaryDirectory(prefix="preft_build_") as tmpdir:
         objects = [os.path.join(tmpdir, f"{i}_{os.path.basename(src)}.o") for i, src in enumerate(sources())]
+        commands = [marshal_command(os.path.join(tmpdir, "_marshal.so"))]
+        commands += [[hipcc] + compile_flags + ["-c", src, "-o", obj] for src, obj in zip(sources(), objects)]
         with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as pool:
-            list(pool.map(lambda so: run([hipcc] + compile_flags + ["-c", so[0], "-o", so[1]]), zip(sources(), objects)))
+            list(pool.map(run, commands))
         tmp = LIB_PATH + f".{os.getpid()}.tmp"
         run([hipcc] + HIPCC_FLAGS + objects + ["-o", tmp])
+        marshal = MARSHAL_PATH + f".{os.getpid()}.tmp"
+        shutil.copyfile(os.path.join(tmpdir, "_marshal.so"), marshal)
+        os.chmod(marshal, 0o755)
     if verbose and messages:
         print("\n".join(messages))
     os.replace(tmp, LIB_PATH)
+    os.replace(marshal, MARSHAL_PATH)
     return LIB_PATH
 
 

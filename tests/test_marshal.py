@@ -1,0 +1,82 @@
+"""csrc/marshal.cpp: it answers None to whatever is not an ordinary call (the binding's own path then says what is wrong), and what it
+takes ends as the same C call: same bits, same error codes, as with marshalling in Python."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_14217_amd as preft
+from paper_2605_14217_amd import binding
+from paper_2605_14217_amd import workloads as wl
+
+
+@pytest.fixture
+def native():
+    preft.load_library()
+    assert binding._native is not None, "_marshal.so is not built"
+    return binding._native
+
+
+def test_what_is_no_ordinary_call_goes_through_the_binding(native):
+    t = torch.zeros(4, 8)
+    i32, i64 = torch.zeros(3, dtype=torch.int32), torch.zeros(2, dtype=torch.int64)
+    ws = torch.zeros(64, dtype=torch.uint8)
+    rest = (4, 1.0, 0, ws, 0, 0)
+    assert native.lora(t, t, i32, i32, i32, i64, i64, *rest) is None                 # host tensors
+    assert native.lora(t, None, i32, i32, i32, i64, i64, *rest) is None
+    assert native.lora(t) is None and native.schedule() is None and native.reft(False) is None
+    assert native.lora_packed([], t, i32, i32, i32, [], [], *rest) is None
+    assert native.reft_layers([], i64, i32, i32, i32, i64, i64, None, 2, *rest) is None
+    with pytest.raises(ValueError, match="y: need a 2-D device tensor"):
+        preft.preft_lora_apply(t, t, i32, i32, i32, i64, i64, 4, 1.0, 0, ws, stream=0)
+    with pytest.raises(ValueError, match="seg_start"):
+        preft.preft_schedule(ws, i32, i32, i32, 4, 2, 0, stream=0)
+    with pytest.raises(TypeError):
+        native.bind(1, 2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_same_calls_as_the_python_path(native, dtype, monkeypatch):
+    from parity_util import bits, dev_tables, direft_pools_to_device, lora_pools_to_device
+    N, r, d = 3, 8, 256
+    lens = np.array([40, 1, 1, 17, 1])
+    tab = wl.from_lengths(lens, np.array([0, 1, 2, 2, -1]), np.where(lens > 1, lens, 0))
+    ss, sa, sp = dev_tables(tab)
+    x, h0, y0 = (wl.activations(tab.T, n, dtype, device="cuda", seed=n) for n in (d, d + 8, 2 * d))
+    A, B, keep = lora_pools_to_device(wl.lora_pool(N, r, d, d, dtype, device="cuda", seed=1))
+    dp = wl.direft_pool(N, r, d + 8, dtype, device="cuda", seed=2)
+    W1, W2t, b, keep2 = direft_pools_to_device(dp)
+
+    def step(stream):
+        ws = preft.new_workspace(tab.T, tab.S, z_rank=r, z_proj=2)
+        y, h, l = y0.clone(), h0.clone(), h0.clone()
+        ls = [h0.clone(), h0.clone()]
+        tables = [torch.tensor([t.data_ptr()] * 2, dtype=torch.int64, device="cuda") for t in (W1, W2t, b)]
+        mode, ready = preft.PREFT_ALL_TOKENS, preft.PREFT_ALL_TOKENS | preft.PREFT_SCHEDULE_READY
+        preft.preft_schedule(ws, ss, sa, sp, tab.T, N, mode, stream)
+        preft.preft_lora_apply(y[:, :d], x, ss, sa, sp, A, B, r, 2.0, ready, ws, stream)
+        preft.preft_lora_apply_packed((y[:, :d], y[:, d:]), x, ss, sa, sp, [A, A], (B, B), r, 0.5, ready, ws, stream)
+        preft.preft_direft_apply(h, ss, sa, sp, W1, W2t, b, r, 0.5, ready, ws, stream)
+        preft.preft_loreft_apply(l, ss, sa, sp, W1, W2t, None, r, 1, ready, ws, stream)              # an int as scale
+        preft.preft_direft_apply_layers(ls, preft.pointer_table(ls), ss, sa, sp, *tables, N, r, 0.5, ready, ws, stream)
+        codes = []
+        for bad in (dict(rank=0), dict(rank=500), dict(mode=0x8000)):
+            with pytest.raises(preft.PreftError) as e:
+                preft.preft_lora_apply(y[:, :d], x, ss, sa, sp, A, B, bad.get("rank", r), 2.0, bad.get("mode", ready), ws, stream)
+            codes.append((e.value.code, str(e.value)))
+        with pytest.raises(ValueError, match="equal length"):
+            preft.preft_lora_apply(y[:, :d], x, ss, sa, sp, A, B[:1], r, 2.0, ready, ws, stream)
+        with pytest.raises(ValueError, match="unit column stride"):
+            preft.preft_direft_apply(h.t(), ss, sa, sp, W1, W2t, b, r, 0.5, ready, ws, stream)
+        torch.cuda.synchronize()
+        return [y, h, l] + ls, codes
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    got = [step(None), step(side)]
+    monkeypatch.setattr(binding, "_native", None)
+    want, codes = step(None)
+    for tensors, c in got:
+        assert c == codes and all(torch.equal(bits(a), bits(w)) for a, w in zip(tensors, want))
+    assert not torch.equal(bits(want[0]), bits(y0))
