@@ -250,7 +250,8 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
         for (int v = 0; v < 4; ++v)
             if (off <= y_last && 4 * q + v < tile.n_rows) st16_stream(yu[v] + off, y[v]);
     };
-    auto finish_lane_order = [&](u32x4_t (&yr)[4], u32x4_t (&wr)[NW][NB], int u) {
+    auto finish = [&](u32x4_t (&yr)[4], u32x4_t (&wr)[NW][NB], int u) {
+        if constexpr (BY_LDS) { finish_by_lds(yr, wr, u); return; }
         u32x4_t yo[4];
         turned(yr, yo, tr);
 #pragma unroll
@@ -295,10 +296,6 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
             const u32x4_t o = tr[(4 * i + q) * MFMA_TRS + c16];
             if (off <= y_last && 4 * i + q < tile.n_rows) st16_stream(yu[i] + off, o);
         }
-    };
-    auto finish = [&](u32x4_t (&yr)[4], u32x4_t (&wr)[NW][NB], int u) {
-        if constexpr (BY_LDS) finish_by_lds(yr, wr, u);
-        else                  finish_lane_order(yr, wr, u);
     };
     int u = ubase + wave;
     if (!AHEAD && u < uend) load_yw(y0, w0, u);
