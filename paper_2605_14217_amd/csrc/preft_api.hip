@@ -135,8 +135,9 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
 {
     const unsigned tiles = likely_units(a, S);                // a multiple of 8 (col_split is 1 here)
     if constexpr (DIREFT) {
-        void (*kernel)(ApplyArgs, SmallLaunch) = small_tile_kernel<NB, true, ODD, true>;
-        if (a.h_layers) kernel = small_tile_layers_kernel<NB, ODD>;
+        const bool few = a.all_tokens && prompt_rows(a, S) == 0;
+        void (*kernel)(ApplyArgs, SmallLaunch) = few ? small_tile_kernel<NB, true, ODD, true> : small_tile_kernel<NB, true, ODD, true, SMALL_WAVES, false>;
+        if (a.h_layers) kernel = few ? small_tile_layers_kernel<NB, ODD, true> : small_tile_layers_kernel<NB, ODD, false>;
         hipLaunchKernelGGL(kernel, dim3(tiles, a.n_layers), dim3(SMALL_WAVES * 64), 0, stream, a, SmallLaunch{1, 0});
     } else {
         const SmallShape shape = small_shape(a, S, n_slices, k);
@@ -290,23 +291,30 @@ inline bool offsets_fit(const ApplyArgs &a) { return a.rank <= 16 || (a.ldx <= (
 
 // a workgroup of four wavefronts for every tile of `height` rows x `cols` columns
 void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S, int n_slices, hipStream_t stream,
-                          int height = 16 * EXPAND_MB, int cols = EXPAND_WAVES * 128, int threads = EXPAND_WAVES * 64)
+                          int height = 16 * EXPAND_MB, int cols = EXPAND_WAVES * 128, int threads = EXPAND_WAVES * 64, int off_lines_lds = 0)
 {
     a.xcd_runs = rows_off_lines(a, n_slices);
+    const int idle_lds = a.xcd_runs ? off_lines_lds : 0;       // keeps workgroups off a compute unit
     // More tiles than the likely rows fill are likely to be empty, and an empty workgroup is not free (3584 decode rows, prompt
     // positions, 8192 -> 2 x 28672: 22 848 of them 23 us): the kernel strides over what exceeds the grid (and over what would
     // exceed the 2^32 work items of a launch)
     const int64_t rows = a.all_tokens && !a.chunks_only ? a.T : prompt_rows(a, S);
     const int64_t bound = tile_grid(a, S, height), likely = rows / height * 5 / 4 + (rows / 8 < 64 ? rows / 8 + 1 : 64);
     const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices, cols), most = (int64_t)1 << 23;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(threads), 0, stream, a, n_slices);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(threads), idle_lds, stream, a, n_slices);
 }
 
 template <int NB, bool ODD>
 void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
 {
     if constexpr (NB <= 2) {
-        launch_expand_kernel(mfma_expand_kernel<NB, EXPAND_MB, ODD>, a, S, n_slices, stream);
+        // Rows off 128-byte lines share lines between panels, and those of a fourth workgroup on the compute unit are one window too many (as
+        // at rank 17-32, where the factors leave room for three).  Four / three / two, us: rank 16, 4096 -> 9640, 69 000 rows 714 / 679 / 758, rank 8,
+        // 4096 -> 5336, 16 600 rows 112 / 107 / 121; on lines 4096 -> 4096, 37 000 rows 152.4 / 153.2 / 200, 4096 -> 2 x 14336, 4600 rows 107.0 / 107.7 / 144.
+        constexpr int THREE = 16384;                          // 25 KB and this
+        static_assert(NB > 1 || (3 * (EXPAND_WAVES * FactorLds<1>::BYTES + THREE) <= 160 * 1024 && 4 * (EXPAND_WAVES * FactorLds<1>::BYTES + THREE) > 160 * 1024), "three workgroups");
+        launch_expand_kernel(mfma_expand_kernel<NB, EXPAND_MB, ODD>, a, S, n_slices, stream, 16 * EXPAND_MB, EXPAND_WAVES * 128, EXPAND_WAVES * 64,
+                             NB == 1 ? THREE : 0);
     } else {
         const int pu = panel_units(a, n_slices);
         launch_expand_kernel(pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD> : panel_expand_kernel<NB, PANEL_RW, 1, ODD>, a, S, n_slices,

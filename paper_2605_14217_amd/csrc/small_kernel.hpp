@@ -281,7 +281,8 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     }
 }
 
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
+// FEW: with the form for tiles of up to four rows (in place only for steps of decode rows: its second copy of the code costs the others 0.1 us of 4.5).
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW>
 __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOutput &o, int unit, int n_chunk_units,
                                                u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
 {
@@ -292,8 +293,8 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOu
         gathered ? as_const(p.gtiles) + (unit - n_chunk_units) : as_const(p.chunks) + unit / (CHUNK_ROWS / 16));
     const int n_rows = min(16, entry[2] - row0);
     if (n_rows <= 0) return;                                  // uniform over the workgroup
-    if (n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4>(p, o, entry, gathered, row0, n_rows, turn, red);
-    else            small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1>(p, o, entry, gathered, row0, n_rows, turn, red);
+    if (!FEW || n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4>(p, o, entry, gathered, row0, n_rows, turn, red);
+    else if constexpr (FEW) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1>(p, o, entry, gathered, row0, n_rows, turn, red);
 }
 
 // A launch out of place: blockIdx.x = 8 share + XCD, blockIdx.y = the slot of a tile on that XCD (in place: blockIdx.x = 8 slot + XCD).  The shares of a
@@ -301,7 +302,7 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOu
 // launch has as many slots as the batch is likely to need; what exceeds it is strided over.
 struct SmallLaunch { int shares0, shares1; };
 
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES>
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW>
 __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallLaunch &l)
 {
     __shared__ u32x4_t turn[WAVES][2][16 * MFMA_TRS];         // activations, and the factor
@@ -318,30 +319,30 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallL
             o.A_pool = p.more[sl - 1].A_pool; o.Bt_pool = p.more[sl - 1].Bt_pool;
         }
     }
-    asm volatile("" ::"s"(o.y), "s"(o.d_out), "s"(o.A_pool), "s"(o.Bt_pool), "s"(p.x), "s"(p.gtiles), "s"(p.chunks), "s"(p.shorts), "s"(p.rank));
+    if constexpr (!DIREFT) asm volatile("" ::"s"(o.y), "s"(o.d_out), "s"(o.A_pool), "s"(o.Bt_pool), "s"(p.x), "s"(p.gtiles), "s"(p.chunks), "s"(p.shorts), "s"(p.rank));
     if (!schedule_matches(p)) return;
     int n_chunk_units;
     const int n_units = tile_units<16>(p, &n_chunk_units);
     const int per_xcd = (n_units + 7) >> 3;
     for (int t = DIREFT ? blockIdx.x >> 3 : blockIdx.y; t < per_xcd; t += DIREFT ? gridDim.x >> 3 : gridDim.y) {
         const int unit = few_tiles_unit(p, n_chunk_units, per_xcd, t);
-        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES>(p, o, unit, n_chunk_units, turn, red);
+        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES, FEW>(p, o, unit, n_chunk_units, turn, red);
         __syncthreads();                                      // the next tile's sums go where this one's are still being read
     }
 }
 
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES = SMALL_WAVES>
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES = SMALL_WAVES, bool FEW = true>
 __global__ __launch_bounds__(WAVES * 64, DEEP ? 2 : 4) void small_tile_kernel(ApplyArgs p, SmallLaunch l)
 {
-    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES>(p, l);
+    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES, FEW>(p, l);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer
-template <int NB, bool ODD>
+template <int NB, bool ODD, bool FEW>
 __global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(ApplyArgs p, SmallLaunch l)
 {
     select_layer(p);
-    small_tile_body<NB, true, ODD, true, SMALL_WAVES>(p, l);
+    small_tile_body<NB, true, ODD, true, SMALL_WAVES, FEW>(p, l);
 }
 
 }  // namespace preft
