@@ -195,13 +195,10 @@ int preft_schedule(void *workspace, size_t workspace_bytes,
  * 14336-wide bf16 buffer with rows every 16384 elements: 64 -> 71 % of peak bandwidth): a caller
  * that owns the layout of its activations should pad wide rows to the next power of two.
  * rank in 1..PREFT_MAX_RANK.  scale is the paper's alpha (or alpha/r), already evaluated.
- * Every rank is computed as given (rank 1 is not padded to 8 in memory).  Every bf16 rank runs on
- * the library's fast kernels (vector-ALU and matrix-core kernels; ranks that are not multiples of 4
- * a few points below their neighbours), with one exception: a rank above 16 that is not a multiple
- * of 4 needs d_in and d_out to be multiples of 128 for that, and takes the slow per-row kernels
- * otherwise (an adapter of such a rank and such widths is served faster when its factors are
- * zero-padded to the next multiple of 4).  fp32 runs on the matrix cores too (fp32 products and sums), up to rank 8 on
- * the per-row kernels where those are faster.
+ * Every rank is computed as given (rank 1 is not padded to 8 in memory), on the library's fast kernels (vector-ALU and
+ * matrix-core kernels; ranks that are not multiples of 4 a few points below their neighbours).  Above rank 16 such a rank is
+ * served best on widths that are multiples of 128; on others, batches of more than 1024 rows run in one launch per output.  fp32 runs on the
+ * matrix cores too (fp32 products and sums), up to rank 8 on the per-row kernels where those are faster.
  * Unless mode carries PREFT_SCHEDULE_READY the call first runs the scheduler into
  * `workspace` (>= preft_workspace_bytes(T, S) bytes).
  * T == 0 or S == 0 returns PREFT_OK without launching.
@@ -224,8 +221,8 @@ int preft_lora_apply(void *y, int64_t ldy, const void *x, int64_t ldx,
  * and B_pools are HOST arrays of n_proj entries.  The outputs may be separate buffers or
  * disjoint column ranges of one buffer (a fused qkv or gate-up output: same row stride, every
  * range inside one row); any other overlap, and any overlap with x, is PREFT_EINVAL.
- * The result is that of n_proj preft_lora_apply calls.  For bf16 they run as one launch at rank 1..16, above it at ranks that
- * are multiples of 4 on batches of at most 1024 rows, and on larger batches at rank 17..64 when every width is a
+ * The result is that of n_proj preft_lora_apply calls.  For bf16 they run as one launch at rank 1..16, above it on batches
+ * of at most 1024 rows, and on larger batches at rank 17..64 when every width is a
  * multiple of 128; otherwise the call issues one launch per projection.  (Batches of at most 1024 rows read x once per workgroup, the
  * others once per launch.)
  */

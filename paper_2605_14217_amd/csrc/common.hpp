@@ -82,6 +82,11 @@ __host__ __device__ constexpr int last_factor_piece(int columns, int most, int r
     return (columns < most ? columns : most) * rank / 8 - 1;
 }
 
+// Ranks above 16 that are no multiple of 4: a lane's factors `rank0 .. rank0 + 3` of a column, of which `rank` may hold fewer, come as four
+// consecutive ones that all exist, from quad_start on, and are shifted down by the ones before (quad_from; ranks past the last: zero).
+__host__ __device__ constexpr int quad_start(int rank0, int rank) { return rank0 < rank - 4 ? rank0 : rank - 4; }
+static_assert(quad_start(0, 17) == 0 && quad_start(16, 17) == 13 && quad_start(12, 17) == 12 && quad_start(60, 63) == 59 && quad_start(60, 33) == 29, "four that exist");
+
 // ---------------------------------------------------------------------------------------
 // bf16 <-> fp32
 // ---------------------------------------------------------------------------------------
@@ -130,6 +135,8 @@ __device__ __forceinline__ u32x4_t ld16(gcptr_t p) { return *reinterpret_cast<co
 __device__ __forceinline__ u32x4_t ld16(gptr_t p) { return *reinterpret_cast<const PREFT_GLOBAL u32x4_t *>(p); }
 __device__ __forceinline__ u32x2_t ld8(gcptr_t p) { return *reinterpret_cast<const PREFT_GLOBAL u32x2_t *>(p); }
 __device__ __forceinline__ uint32_t ld4(gcptr_t p) { return *reinterpret_cast<const PREFT_GLOBAL uint32_t *>(p); }
+typedef u32x2_t u32x2_any_t __attribute__((aligned(2)));
+__device__ __forceinline__ u32x2_t ld8_any(gcptr_t p) { return *reinterpret_cast<const PREFT_GLOBAL u32x2_any_t *>(p); }   // from any element
 __device__ __forceinline__ void st16(gptr_t p, u32x4_t v) { *reinterpret_cast<PREFT_GLOBAL u32x4_t *>(p) = v; }
 // Activations are touched once per call: their loads and stores carry the non-temporal hint, so
 // that they stream through the caches without displacing the adapter factors, which every tile
@@ -145,6 +152,12 @@ __device__ __forceinline__ u32x4_t ld16_stream(gcptr_t p)
     else return ld16(p);
 }
 __device__ __forceinline__ u32x4_t ld16_stream(gptr_t p) { return ld16_stream((gcptr_t)p); }
+__device__ __forceinline__ u32x2_t quad_from(u32x2_t four, int rank0, int rank)
+{
+    const int before = rank0 - quad_start(rank0, rank);
+    const uint64_t v = before < 4 ? __builtin_bit_cast(uint64_t, four) >> (16 * (before & 3)) : 0;
+    return __builtin_bit_cast(u32x2_t, v);
+}
 // first of two reads of the same bytes (an in-place call that does not keep its tile): cacheable
 template <bool AGAIN_LATER>
 __device__ __forceinline__ u32x4_t ld16_first(gcptr_t p)

@@ -63,7 +63,7 @@ constexpr int64_t DEEP_WGS = 200;                             // at most one wor
 // `widest`: columns of the widest output
 inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool direft, const Knobs &k)
 {
-    if (a.rank < 4 || ((a.rank % 4) && a.rank > 16)) return false;
+    if (a.rank < 4) return false;
     if (a.d_in > (1 << 22) || widest > (1 << 22)) return false;          // offsets within a row or a factor, and the launch, fit 32 bits
     if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
     if (!direft && k.colsplit) return k.colsplit > 1;

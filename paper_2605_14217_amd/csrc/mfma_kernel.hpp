@@ -90,6 +90,8 @@ constexpr int mfma_min_waves(int NB, int MB, int WAVES, int HUNITS)
 // two bytes at a time, zero for the ranks past r.  ODD is the number of 16-byte pieces of that block a
 // lane carries: 2 up to rank 8, 4 up to rank 16.  In place with the tile in registers, the blocks of the
 // first two units are requested before the reduction of z and the next ones while a unit is finished.
+// ODD = 1 (rank > 16): the same ranks above 16 (17, 18, 19, 21, ...), whatever the widths: a lane's four factors of a column are one
+// 8-byte load from wherever they start (quad_from), which the texture path takes a few cycles longer for.
 //
 // ZOUT: the shrink sweep alone.  z goes to the workspace in the form the expand's MFMAs take it, 1 KB per
 // 16-row block and rank block, and mfma_expand_kernel does the expand in a second launch.
@@ -98,8 +100,9 @@ template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bo
 __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 {
     static_assert(!PARTIAL || HUNITS > 0, "a partially resident tile keeps some units");
-    static_assert(!ODD || (NB == 1 && !PARTIAL), "the any-rank shape covers rank <= 16");
-    static_assert(ODD == 0 || ODD == 2 || ODD == 4, "pieces per lane of a unit's factor block");
+    static_assert(!ODD || ((ODD == 1) == (NB > 1) && !PARTIAL), "ranks that are no multiple of 4: blocks up to rank 16, loads of four above");
+    static_assert(ODD == 0 || ODD == 1 || ODD == 2 || ODD == 4, "pieces per lane of a unit's factor block, or 1");
+    constexpr bool PARKED = ODD > 1;
     constexpr bool STREAMS = HUNITS == 0 || PARTIAL;         // some units pass through both sweeps
     // x is read a second time by this workgroup (in place without a resident tile): then its loads stay cacheable
     // (the units the wavefront does not keep: HUNITS names how many of its units stay in
@@ -354,9 +357,9 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     // what a wavefront holds of a unit's factors between request and use: its MFMA operands
     // (8-byte pieces straight from memory), or, for ranks that are not multiples of 4, its share
     // of the unit's contiguous [128 columns][r] block (16 r pieces of 16 bytes, ODD per lane)
-    using wbuf_t = std::conditional_t<(ODD > 0), u32x4_t[ODD > 0 ? ODD : 1], u32x2_t[4][2][NB]>;
+    using wbuf_t = std::conditional_t<PARKED, u32x4_t[PARKED ? ODD : 1], u32x2_t[4][2][NB]>;
     auto load_w_block = [&](wbuf_t &wb, gcptr_t Bt, int unit_index) {     // any-rank shape only
-        if constexpr (ODD > 0) {
+        if constexpr (PARKED) {
             gcptr_t base = Bt + (int64_t)unit_index * 256 * r;
 #pragma unroll
             for (int i = 0; i < ODD; ++i)
@@ -364,9 +367,9 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
         }
     };
     // in place, tile in registers: the blocks of two units are in flight
-    constexpr int W_AHEAD = (ODD > 0 && HUNITS > 0) ? 2 : 1;
+    constexpr int W_AHEAD = (PARKED && HUNITS > 0) ? 2 : 1;
     wbuf_t w_ahead[W_AHEAD];
-    if constexpr (ODD > 0 && HUNITS > 0) {
+    if constexpr (PARKED && HUNITS > 0) {
 #pragma unroll
         for (int u = 0; u < W_AHEAD; ++u)
             if (u < my_ku) load_w_block(w_ahead[u], as_global(p.Bt_pool[adapter]), k_unit(u));
@@ -485,7 +488,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
         for (int b = 0; b < NB; ++b) {
             const int col = 8 * (rl >> 2) + 4 * e + (rl & 3);
             const int rank0 = 16 * b + 4 * g;
-            bp[e][b] = Bt + ((int64_t)col * r + (rank0 < r ? rank0 : 0)) * 2;
+            bp[e][b] = Bt + ((int64_t)col * r + (ODD == 1 ? quad_start(rank0, r) : rank0 < r ? rank0 : 0)) * 2;
         }
     const int64_t w_step = (int64_t)32 * r * 2;               // bytes per 32 output columns
 
@@ -510,7 +513,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
         return Elem<bf16_tag>::pack(out);
     };
     auto load_w_unit = [&](wbuf_t &wb, int u) {
-        if constexpr (ODD > 0) {
+        if constexpr (PARKED) {
             load_w_block(wb, Bt, c_unit(u));
         } else {
             const int cs0 = c_unit(u) * 4;
@@ -519,13 +522,13 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) wb[s][e][b] = ld8(bp[e][b] + (cs0 + s) * w_step);
+                    for (int b = 0; b < NB; ++b) wb[s][e][b] = ODD == 1 ? ld8_any(bp[e][b] + (cs0 + s) * w_step) : ld8(bp[e][b] + (cs0 + s) * w_step);
         }
     };
     // the MFMA operands of step s of a unit from what load_w_unit fetched (any-rank shape: from the
     // block parked in LDS)
     auto w_operands = [&](const wbuf_t &wb, int s, u32x2_t (&wv)[2][NB]) {
-        if constexpr (ODD > 0) {
+        if constexpr (PARKED) {
             // this lane's four factors of a column are two or three consecutive 32-bit words of the
             // block (three when they start on an odd element): shift them into place, mask the ranks past r
 #pragma unroll
@@ -539,7 +542,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 #pragma unroll
             for (int e = 0; e < 2; ++e)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) wv[e][b] = wb[s][e][b];
+                for (int b = 0; b < NB; ++b) wv[e][b] = ODD == 1 ? quad_from(wb[s][e][b], 16 * b + 4 * g, r) : wb[s][e][b];
         }
     };
     auto load_y_unit = [&](u32x4_t (&raw)[MB][4], int u) {
@@ -551,7 +554,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     };
     // a whole unit: y (MFMA order) -> out, turned back to load order through LDS and stored
     auto finish_unit = [&](const u32x4_t (&yop)[MB][4], const wbuf_t &wb, int u) {
-        if constexpr (ODD > 0) {
+        if constexpr (PARKED) {
 #pragma unroll
             for (int i = 0; i < ODD; ++i)
                 if (lane + 64 * i < 16 * r) tra[lane + 64 * i] = wb[i];
@@ -618,7 +621,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 #pragma unroll
         for (int u = 0; u < HUNITS; ++u)
             if (u < my_cu) {
-                if constexpr (ODD > 0) {
+                if constexpr (PARKED) {
                     finish_unit(hreg[u], w_ahead[u % W_AHEAD], u);
                     if (u + W_AHEAD < HUNITS && u + W_AHEAD < my_cu) load_w_unit(w_ahead[u % W_AHEAD], u + W_AHEAD);
                 } else {
@@ -643,12 +646,14 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 gcptr_t wp = bp[e][b] + c_tail_step * w_step - back;
-                if constexpr (ODD > 0) {                      // two bytes at a time, zero past rank r
+                if constexpr (PARKED) {                       // two bytes at a time, zero past rank r
                     uint32_t f[4];
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         f[v] = 4 * g + v < r ? (uint32_t) reinterpret_cast<const PREFT_GLOBAL uint16_t *>(wp)[v] : 0u;
                     wv[e][b] = u32x2_t{f[0] | (f[1] << 16), f[2] | (f[3] << 16)};
+                } else if constexpr (ODD == 1) {
+                    wv[e][b] = quad_from(ld8_any(wp), 16 * b + 4 * g, r);
                 } else {
                     wv[e][b] = ld8(wp);
                 }

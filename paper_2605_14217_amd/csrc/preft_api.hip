@@ -154,15 +154,19 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
     }
 }
 
-// ranks 4..128 (in place 4..64) in multiples of 4, and every rank from 5 to 15
+// ranks 4..128, in place 4..64
 template <bool DIREFT>
 void launch_small(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
 {
-    if (a.rank % 4)        launch_small_shape<1, DIREFT, true>(a, S, n_slices, k, stream);
-    else if (a.rank <= 16) launch_small_shape<1, DIREFT, false>(a, S, n_slices, k, stream);
-    else if (a.rank <= 32) launch_small_shape<2, DIREFT, false>(a, S, n_slices, k, stream);
-    else if (a.rank <= 64) launch_small_shape<4, DIREFT, false>(a, S, n_slices, k, stream);
-    else if constexpr (!DIREFT) launch_small_shape<8, false, false>(a, S, n_slices, k, stream);
+    auto launch = [&](auto odd_tag) {
+        constexpr bool ODD = decltype(odd_tag)::value;
+        if (a.rank <= 16)      launch_small_shape<1, DIREFT, ODD>(a, S, n_slices, k, stream);
+        else if (a.rank <= 32) launch_small_shape<2, DIREFT, ODD>(a, S, n_slices, k, stream);
+        else if (a.rank <= 64) launch_small_shape<4, DIREFT, ODD>(a, S, n_slices, k, stream);
+        else if constexpr (!DIREFT) launch_small_shape<8, false, ODD>(a, S, n_slices, k, stream);
+    };
+    if (a.rank % 4) launch(std::integral_constant<bool, true>{});
+    else            launch(std::integral_constant<bool, false>{});
 }
 
 // the row-split kernel takes whole chunks only
@@ -542,8 +546,22 @@ void launch_mfma_packed(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream
                            dim3(256), 0, stream, a);
 }
 
-template <typename E, bool DIREFT>
-void launch_rows(const ApplyArgs &a, int64_t S, bool chunks_too, hipStream_t stream);
+// ranks above 16 that are no multiple of 4: the column-split kernel, 4 wavefronts on 16 rows (`mb` 2: 32, rank 17-32)
+template <int NB, bool DIREFT>
+void launch_mfma_odd_stream(const ApplyArgs &a, int64_t S, int mb, hipStream_t stream)
+{
+    void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, 1, 4, 0, DIREFT, 1, false, 1>;
+    if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 1, 4, 0, false, 1>; }
+    int rows = 16;
+    if constexpr (NB == 2) {
+        if (mb == 2) {
+            rows = 32;
+            kernel = mfma_tile_kernel<NB, 2, 4, 0, DIREFT, 1, false, 1>;
+            if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 2, 4, 0, false, 1>; }
+        }
+    }
+    hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, rows), a.n_layers), dim3(256), 0, stream, a);
+}
 
 // packed projections at rank 32..64 (widths multiples of 128): the row-split kernel with one sweep
 // over x for all outputs.  It takes the chunks; the gathered tiles (all-token mode: decode rows)
@@ -553,7 +571,7 @@ void launch_mfma_wide_packed(const ApplyArgs &a, int n_proj, int64_t S, const Kn
 {
     const bool split = n_proj == 2 ? launch_mfma_split<NB, 2>(a, S, k, stream) : launch_mfma_split<NB, 3>(a, S, k, stream);
     if (a.rank % 4) {
-        // the any-rank form: the basic shape for the chunks, the per-row kernel for the gathered tiles
+        // the any-rank form: the basic shape for the chunks, the column-split kernel for the gathered tiles
         void (*odd)(ApplyArgs) = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 1, false, 2, false, true>
                                              : mfma_wide_kernel<NB, 1, 4, 1, false, 3, false, true>;
         if (!split) hipLaunchKernelGGL(odd, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
@@ -563,7 +581,8 @@ void launch_mfma_wide_packed(const ApplyArgs &a, int n_proj, int64_t S, const Kn
                 g.y = a.more[i - 1].y; g.ldy = a.more[i - 1].ldy; g.d_out = a.more[i - 1].d_out;
                 g.A_pool = a.more[i - 1].A_pool; g.Bt_pool = a.more[i - 1].Bt_pool;
             }
-            launch_rows<bf16_tag, false>(g, S, false, stream);
+            g.gathered_only = 1;
+            launch_mfma_odd_stream<NB, false>(g, S, 1, stream);
         }
         return;
     }
@@ -624,28 +643,34 @@ void launch_mfma_odd(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t 
     else             launch_mfma_odd_pieces<DIREFT, 4>(a, S, stream);
 }
 
-// bf16 ranks above 16 that are not multiples of 4, widths multiples of 128: the row-split kernel's any-rank
-// form takes the chunks (its basic shape: 4 wavefronts x 16 rows, above rank 64 8 x 16), the per-row kernel
-// the gathered tiles (all-token mode: decode rows)
-template <bool DIREFT>
+// bf16 ranks above 16 that are not multiples of 4.  Widths multiples of 128: the row-split kernel's any-rank form takes the chunks (its
+// basic shape: 4 wavefronts x 16 rows, above rank 64 8 x 16), the column-split kernel the gathered tiles (all-token mode: decode
+// rows); other widths: the column-split kernel takes all.  (They took the per-row kernels: 30 to 300 times as long.)
+template <int NB, bool DIREFT>
 void launch_mfma_odd_wide(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
-    const int nb = (a.rank + 15) / 16;
+    if (!wide_widths_ok(a, 1) || k.variant == 3) {
+        launch_mfma_odd_stream<NB, DIREFT>(a, S, 2, stream);
+        return;
+    }
     bool split = false;
-    if (nb > 2 && nb <= 4) split = launch_mfma_split<4, 1, DIREFT>(a, S, k, stream);
-    if constexpr (!DIREFT) { if (nb <= 2) split = launch_mfma_split<2, 1>(a, S, k, stream); }
-    if (split)        {}
-    else if (nb <= 2)      launch_wide_shape<2, 1, 4, 1, DIREFT, true>(a, S, stream);
-    else if (nb <= 4) launch_wide_shape<4, 1, 4, 1, DIREFT, true>(a, S, stream);
-    else              launch_wide_shape<8, 1, 8, 1, DIREFT, true>(a, S, stream);
-    launch_rows<bf16_tag, DIREFT>(a, S, false, stream);
+    if constexpr (NB == 4 || (NB == 2 && !DIREFT)) split = launch_mfma_split<NB, 1, DIREFT>(a, S, k, stream);
+    if (!split) launch_wide_shape<NB, 1, NB <= 4 ? 4 : 8, 1, DIREFT, true>(a, S, stream);
+    ApplyArgs g = a;
+    g.gathered_only = 1;
+    launch_mfma_odd_stream<NB, DIREFT>(g, S, 1, stream);
 }
 
 template <bool DIREFT>
 void launch_mfma_rank(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
     const int nb = (a.rank + 15) / 16;
-    if ((a.rank % 4) && a.rank > 16) { launch_mfma_odd_wide<DIREFT>(a, S, k, stream); return; }   // widths: choose_path
+    if ((a.rank % 4) && a.rank > 16) {
+        if (nb <= 2)      launch_mfma_odd_wide<2, DIREFT>(a, S, k, stream);
+        else if (nb <= 4) launch_mfma_odd_wide<4, DIREFT>(a, S, k, stream);
+        else              launch_mfma_odd_wide<8, DIREFT>(a, S, k, stream);
+        return;
+    }
     if (a.rank % 4) { launch_mfma_odd<DIREFT>(a, S, k, stream); return; }      // rank <= 16 (choose_path)
     if (nb <= 1)      launch_mfma_nb<1, DIREFT>(a, S, k, stream);
     else if (nb <= 2) launch_mfma_nb<2, DIREFT>(a, S, k, stream);
@@ -822,11 +847,10 @@ Path choose_path(const ApplyArgs &a, int64_t S, bool direft, int dtype, const Kn
         if (k.variant == 0 && k.colsplit == 0 && f32_rows_win(a, S, direft)) return Path::Rows;
         return Path::F32;
     }
-    const bool widths_128 = wide_widths_ok(a, 1);
-    // matrix-core kernels: multiples of 4, every rank from 5 to 16 (the any-rank shape of the column-split
-    // kernel) and, widths being multiples of 128, every rank above (the any-rank form of the row-split
-    // kernel); ranks 1..3 are a vector-ALU matter
-    const bool valu_ok = rank <= 8, mfma_ok = (rank % 4) == 0 || (rank > 4 && rank < 16) || (rank > 16 && widths_128);
+    // matrix-core kernels from rank 4 on; ranks 1..3 are a vector-ALU matter.  (Ranks above 16 that are no multiple of 4 on widths
+    // that are no multiples of 128: byte offsets within a factor in 32 bits)
+    const bool narrow = a.d_in <= (1 << 22) && a.d_out <= (1 << 22);
+    const bool valu_ok = rank <= 8, mfma_ok = rank >= 4 && ((rank % 4) == 0 || rank < 16 || wide_widths_ok(a, 1) || narrow);
     if (k.variant == 2 && valu_ok) return Path::Valu;
     if ((k.variant == 3 || k.variant == 4) && mfma_ok) return Path::Mfma;
     if (rank <= 3) return Path::Valu;

@@ -38,11 +38,11 @@ template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, int NG>
 __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallOutput &o, const i32x4_t entry, bool gathered, int row0, int n_rows,
                                                 u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
 {
+    constexpr bool PARKED = ODD && NB == 1, ANY = ODD && NB > 1;        // ranks that are no multiple of 4: up to 16, and above
     // units of the shrink and of the expand sweep in flight (registers)
     constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : 2;
     constexpr bool EARLY = NG == 1 && DEEP && NB <= 2;         // registers for the first units of the expand beside the shrink's
-    constexpr int DEPTH = DEEP ? (NB == 1 ? (ODD || EARLY ? 2 : 4) : NB == 2 ? (EARLY ? 1 : 2) : 1) : 1;
-    static_assert(!ODD || NB == 1, "the any-rank form covers rank <= 16");
+    constexpr int DEPTH = DEEP ? (NB == 1 ? (PARKED || EARLY ? 2 : 4) : NB == 2 ? (EARLY ? 1 : 2) : 1) : 1;
     constexpr bool W_LATE = NB > 4;                           // factors of the expand step by step (registers)
     static_assert(DEEP || NB == 1, "two workgroups of more rank blocks do not fit a compute unit");
     constexpr int PIECES = 4;                                 // any-rank form: 16-byte pieces of a unit's factor block per lane
@@ -83,7 +83,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     const int y_last = d_out * 2 - 16;
     u32x4_t Y[DEPTH][NG];
     u32x2_t W[DEPTH][W_LATE ? 1 : 4][2][NB];
-    u32x4_t Wb[ODD ? DEPTH : 1][PIECES];
+    u32x4_t Wb[PARKED ? DEPTH : 1][PIECES];
     auto load_w = [&](u32x2_t (&w)[2][NB], int u, int s) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
@@ -92,7 +92,8 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const int rank0 = 16 * b + 4 * g;
-                w[e][b] = ld8(Bt + ((int64_t)col * r + (rank0 < r ? rank0 : 0)) * 2);
+                if constexpr (ANY) w[e][b] = ld8_any(Bt + ((int64_t)col * r + quad_start(rank0, r)) * 2);
+                else w[e][b] = ld8(Bt + ((int64_t)col * r + (rank0 < r ? rank0 : 0)) * 2);
             }
         }
     };
@@ -100,7 +101,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         const int off = min(u * 256 + c16 * 16, y_last);
 #pragma unroll
         for (int i = 0; i < NG; ++i) Y[k][i] = ld16(yu[i] + off);
-        if constexpr (ODD) {                                  // the unit's [128 columns][r] block, contiguous
+        if constexpr (PARKED) {                               // the unit's [128 columns][r] block, contiguous
             const int last = last_factor_piece(d_out - u * 128, 128, r);
 #pragma unroll
             for (int j = 0; j < PIECES; ++j) Wb[k][j] = ld16(Bt + (int64_t)u * 256 * r + min(min(lane + 64 * j, 16 * r - 1), last) * 16);
@@ -232,7 +233,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         for (int i = 0; i < NG; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[k][i];
 #pragma unroll
         for (int s = 0; s < 4; ++s) yo[s] = tr[rl * MFMA_TRS + 4 * s + g];
-        if constexpr (ODD) {
+        if constexpr (PARKED) {
 #pragma unroll
             for (int j = 0; j < PIECES; ++j)
                 if (lane + 64 * j < 16 * r) tra[lane + 64 * j] = Wb[k][j];
@@ -247,12 +248,13 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     u32x2_t w;
-                    if constexpr (ODD) {
+                    if constexpr (PARKED) {
                         const uint32_t *w3 = odd_words + (16 * s + 2 * e) * r;
                         const uint32_t d0 = w3[0], d1 = w3[1], d2 = w3[2];
                         w = u32x2_t{__builtin_amdgcn_alignbit(d1, d0, odd_shift) & odd_m01, __builtin_amdgcn_alignbit(d2, d1, odd_shift) & odd_m23};
                     } else {
                         w = W[k][W_LATE ? 0 : s][e][b];
+                        if constexpr (ANY) w = quad_from(w, 16 * b + 4 * g, r);
                     }
                     d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), zop[b], d, 0, 0, 0);
                 }
