@@ -32,6 +32,7 @@ FAMILIES = {            # kernel template -> (header, rough relative compile cos
     "preft::panel_expand_kernel": ("expand_kernel.hpp", 1),
     "preft::thin_expand_kernel": ("expand_kernel.hpp", 1),
     "preft::mfma_tile_kernel": ("mfma_kernel.hpp", 2),
+    "preft::mfma_tile_outputs_kernel": ("mfma_kernel.hpp", 2),
     "preft::mfma_tile_layers_kernel": ("mfma_kernel.hpp", 2),
     "preft::valu_tile_kernel": ("valu_kernel.hpp", 1),
     "preft::valu_tile_layers_kernel": ("valu_kernel.hpp", 1),

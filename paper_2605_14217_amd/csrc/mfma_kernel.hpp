@@ -685,6 +685,16 @@ __global__ __launch_bounds__(WAVES * 64, mfma_min_waves(NB, MB, WAVES, HUNITS)) 
     mfma_tile_body<NB, MB, WAVES, HUNITS, DIREFT, SLICES, PARTIAL, ODD, ZOUT>(p);
 }
 
+// the same for one of a packed call's outputs: blockIdx.y (the gathered tiles of ranks above 16, which other launches leave over)
+template <int NB, int WAVES, int ODD>
+__global__ __launch_bounds__(WAVES * 64, mfma_min_waves(NB, 1, WAVES, 0)) void mfma_tile_outputs_kernel(ApplyArgs p)
+{
+    // (by name: an index into the arguments would put them all into scratch memory)
+    if (blockIdx.y == 1) { p.y = p.more[0].y; p.ldy = p.more[0].ldy; p.d_out = p.more[0].d_out; p.A_pool = p.more[0].A_pool; p.Bt_pool = p.more[0].Bt_pool; }
+    if (blockIdx.y == 2) { p.y = p.more[1].y; p.ldy = p.more[1].ldy; p.d_out = p.more[1].d_out; p.A_pool = p.more[1].A_pool; p.Bt_pool = p.more[1].Bt_pool; }
+    mfma_tile_body<NB, 1, WAVES, 0, false, 1, false, ODD>(p);
+}
+
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer
 template <int NB, int MB, int WAVES, int HUNITS, bool PARTIAL = false, int ODD = 0>
 __global__ __launch_bounds__(WAVES * 64, mfma_min_waves(NB, MB, WAVES, HUNITS)) void mfma_tile_layers_kernel(ApplyArgs p)

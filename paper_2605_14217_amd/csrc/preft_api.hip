@@ -563,45 +563,29 @@ void launch_mfma_odd_stream(const ApplyArgs &a, int64_t S, int mb, hipStream_t s
     hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, rows), a.n_layers), dim3(256), 0, stream, a);
 }
 
-// packed projections at rank 32..64 (widths multiples of 128): the row-split kernel with one sweep
+// packed projections at rank 17..64 (widths multiples of 128): the row-split kernel with one sweep
 // over x for all outputs.  It takes the chunks; the gathered tiles (all-token mode: decode rows)
-// go to one launch of the column-split kernel per output.
+// go to one launch of the column-split kernel, an output in each plane of its grid.  (One launch per output cost 4.7 us each with
+// nothing to do: rank 64, 4096 -> 4096 + 2 x 1024, 2500 rows 78 -> 74.5, with 900 decode rows in all-token mode 177 -> 141.)
 template <int NB>
 void launch_mfma_wide_packed(const ApplyArgs &a, int n_proj, int64_t S, const Knobs &k, hipStream_t stream)
 {
     const bool split = n_proj == 2 ? launch_mfma_split<NB, 2>(a, S, k, stream) : launch_mfma_split<NB, 3>(a, S, k, stream);
-    if (a.rank % 4) {
-        // the any-rank form: the basic shape for the chunks, the column-split kernel for the gathered tiles
-        void (*odd)(ApplyArgs) = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 1, false, 2, false, true>
-                                             : mfma_wide_kernel<NB, 1, 4, 1, false, 3, false, true>;
-        if (!split) hipLaunchKernelGGL(odd, dim3(chunk_grid(a, S, 64)), dim3(256), 0, stream, a);
-        for (int i = 0; i < n_proj; ++i) {
-            ApplyArgs g = a;
-            if (i > 0) {
-                g.y = a.more[i - 1].y; g.ldy = a.more[i - 1].ldy; g.d_out = a.more[i - 1].d_out;
-                g.A_pool = a.more[i - 1].A_pool; g.Bt_pool = a.more[i - 1].Bt_pool;
-            }
-            g.gathered_only = 1;
-            launch_mfma_odd_stream<NB, false>(g, S, 1, stream);
+    const bool odd = (a.rank % 4) != 0;
+    // two column groups at rank 32 where every width allows it (see launch_mfma_nb); the any-rank form has the basic shape only
+    const bool cw2 = NB <= 2 && !odd && column_groups_fit(a, n_proj);
+    if (!split) {
+        void (*kernel)(ApplyArgs) = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 1, false, 2> : mfma_wide_kernel<NB, 1, 4, 1, false, 3>;
+        if constexpr (NB <= 2) {
+            if (cw2) kernel = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 2, false, 2> : mfma_wide_kernel<NB, 1, 4, 2, false, 3>;
         }
-        return;
+        if (odd) kernel = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 1, false, 2, false, true> : mfma_wide_kernel<NB, 1, 4, 1, false, 3, false, true>;
+        hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 64)), dim3(cw2 ? 512 : 256), 0, stream, a);
     }
-    // two column groups at rank 32 where every width allows it (see launch_mfma_nb)
-    const bool cw2 = NB <= 2 && column_groups_fit(a, n_proj);
-    void (*kernel)(ApplyArgs) = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 1, false, 2> : mfma_wide_kernel<NB, 1, 4, 1, false, 3>;
-    if constexpr (NB <= 2) {
-        if (cw2) kernel = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 2, false, 2> : mfma_wide_kernel<NB, 1, 4, 2, false, 3>;
-    }
-    if (!split) hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 64)), dim3(cw2 ? 512 : 256), 0, stream, a);
-    for (int i = 0; i < n_proj; ++i) {
-        ApplyArgs g = a;
-        if (i > 0) {
-            g.y = a.more[i - 1].y; g.ldy = a.more[i - 1].ldy; g.d_out = a.more[i - 1].d_out;
-            g.A_pool = a.more[i - 1].A_pool; g.Bt_pool = a.more[i - 1].Bt_pool;
-        }
-        g.gathered_only = 1;
-        launch_mfma_stream<NB, false>(g, S, 1, 4, stream);
-    }
+    ApplyArgs g = a;
+    g.gathered_only = 1;
+    void (*gathered)(ApplyArgs) = odd ? mfma_tile_outputs_kernel<NB, 4, 1> : mfma_tile_outputs_kernel<NB, 4, 0>;
+    hipLaunchKernelGGL(gathered, dim3(tile_grid(g, S, 16), n_proj), dim3(256), 0, stream, g);
 }
 
 // bf16 ranks up to 16 that are not multiples of 4 (5, 6, 7, 9, ...): the column-split kernel's any-rank
