@@ -627,13 +627,24 @@ void launch_mfma_odd(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t 
     else             launch_mfma_odd_pieces<DIREFT, 4>(a, S, stream);
 }
 
+// Whether an in-place call of rank 17-31, no multiple of 4, takes 32-row tiles of the column-split kernel instead of 64-row tiles of the
+// row-split one, as the multiples of 4 always do: twice as many tiles, and their second read of h follows the first sooner.  But the large batches
+// of narrow rows find that read in the caches either way, and some ranks' unaligned factors cost the texture path more (21 and 31 of those measured).
+// Row-split / column-split, us: 2300 rows, d = 1024 / 4096 / 8192, rank 18 18.6 / 9.7, 64 / 27, 123 / 47, rank 31 18.8 / 11.6, 65 / 33, 126 / 60;
+// 14 000 rows, d = 512, rank 31 16.0 / 12.6, 8192, rank 29 154 / 117; 35 000 rows, rank 31, d = 512 25 / 30, 2048 89 / 86, 3072 130 / 135, 4096 187 / 178,
+// 8192 391 / 367; 90 000 rows, rank 19, d = 1024 87 / 102, 8192 855 / 693, rank 21 2048 190 / 208, 8192 848 / 793, rank 31 4096 400 / 406, 8192 867 / 823.
+bool odd_streams_in_place(const ApplyArgs &a)
+{
+    return a.T <= 16384 || a.d_in >= 8192 || (a.d_in >= 4096 && a.T <= 49152);
+}
+
 // bf16 ranks above 16 that are not multiples of 4.  Widths multiples of 128: the row-split kernel's any-rank form takes the chunks (its
 // basic shape: 4 wavefronts x 16 rows, above rank 64 8 x 16), the column-split kernel the gathered tiles (all-token mode: decode
 // rows); other widths: the column-split kernel takes all.  (They took the per-row kernels: 30 to 300 times as long.)
 template <int NB, bool DIREFT>
 void launch_mfma_odd_wide(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
-    if (!wide_widths_ok(a, 1) || k.variant == 3) {
+    if (!wide_widths_ok(a, 1) || k.variant == 3 || (DIREFT && NB == 2 && k.variant == 0 && odd_streams_in_place(a))) {
         launch_mfma_odd_stream<NB, DIREFT>(a, S, 2, stream);
         return;
     }

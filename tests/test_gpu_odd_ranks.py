@@ -75,3 +75,40 @@ def test_every_rank_meets_its_own_factor(rank, d, d_out, rows):
     preft.preft_lora_apply(y, x, ss, sa, sp, preft.pointer_table([A]), preft.pointer_table([B]), rank, 1.0, preft.PREFT_PREFILL_ONLY,
                            preft.new_workspace(rows, 1))
     assert torch.equal(y, B.t()[torch.arange(rows, device="cuda") % rank])
+
+
+@pytest.mark.parametrize("rank,d", [(17, 128), (18, 4096), (30, 2048), (31, 1024)])
+def test_in_place_on_widths_that_are_multiples_of_128(rank, d):
+    """Rank 17-31 in place: the column-split kernel up to 16 384 rows and on wide rows, the row-split kernel beyond, which the test flags
+    choose as well; both against the oracle on the same rows, and the default call one of the two to the bit."""
+    from oracle import preft_oracle as ora
+    from paper_2605_14217_amd import binding as B
+    from parity_util import bits, compare, dev_tables, direft_pools_to_device
+    N = 4
+    for T_prompts in ([700, 600], [700, 600] + [5100] * 3):
+        lens = np.array([1, 15, 16, 17, 33, 5, 4, 129] + T_prompts + [1] * 20)
+        tab = wl.from_lengths(lens, np.random.Generator(np.random.PCG64(rank)).integers(-1, N + 1, size=len(lens)), np.where(lens > 1, lens, 0))
+        ss, sa, sp = dev_tables(tab)
+        tables = (tab.seg_start, tab.seg_adapter, tab.seg_prefill_len)
+        x = wl.activations(tab.T, d, "bf16", device="cuda", seed=1)
+        pool = wl.direft_pool(N, rank, d, "bf16", device="cuda", seed=20)
+        W1, W2t, b, keep = direft_pools_to_device(pool)
+        ws = preft.new_workspace(tab.T, tab.S, z_rank=rank)
+        got = {}
+        for variant in (0, 3, 4):
+            h = x.clone()
+            prev = B.set_test_flags(B.test_flags(variant=variant))
+            try:
+                preft.preft_direft_apply(h, ss, sa, sp, W1, W2t, b, rank, 0.5, preft.PREFT_ALL_TOKENS, ws)
+            finally:
+                B.set_test_flags(prev)
+            got[variant] = h
+        streams = tab.T <= 16384 or d >= 4096                   # and these are fewer than 49 152
+        assert torch.equal(bits(got[0]), bits(got[3 if streams else 4]))
+        if tab.T <= 16384:
+            owner = ora.positions(tab.T, *tables, N, ora.ALL_POSITIONS)
+            want = ora.direft(x.cpu(), *tables, [a.cpu() for a in pool.A], [m.cpu() for m in pool.B], [v.cpu() for v in pool.b], rank, 0.5, ora.ALL_POSITIONS)
+            for h in got.values():
+                compare(h, x, want, owner, "bf16")
+        else:
+            assert (got[3].float() - got[4].float()).abs().max() <= 2 ** -6 * got[4].float().abs().max()      # two bf16 roundings of the largest value
