@@ -1,5 +1,5 @@
-// MFMA tile kernel for larger ranks (bf16, rank % 4 == 0, 32 <= rank <= 128 in practice),
-// widths that are multiples of 128 * CW.
+// MFMA tile kernel for larger ranks (bf16, 17 to 128; no multiple of 4 with the ODD form), widths that are multiples of
+// 128 * CW.
 //
 // From rank 32 up the adapter factors outweigh a 16-row tile's activations (rank r costs
 // r/16 factor bytes per activation byte), so here several 16-row blocks share the factors: a
@@ -8,7 +8,7 @@
 // unit cg.  In each step the workgroup loads the CW units of A (r ranks x 256 bytes each) or of
 // B (128 columns x r factors each, contiguous in the [d_out, r] layout) once, with fully
 // coalesced 16-byte loads, into a double-buffered LDS area, and every wavefront reads its MFMA
-// operands from there (padded strides, no bank conflicts).  Factor traffic from L2 drops to
+// operands from there (padded strides or permuted places, no bank conflicts).  Factor traffic from L2 drops to
 // r / (16 MB RW) of the activation traffic.
 //
 // Why column groups.  Measured on this chip with a kernel that only moves the bytes (read x,

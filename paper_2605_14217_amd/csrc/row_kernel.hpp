@@ -2,7 +2,7 @@
 // of at most GROUP_ROWS rows that share it.
 //
 // This is the generic fallback for what the tile kernels do not cover (fp32 of rank 1-8 where few tiles meet wide rows;
-// bf16 ranks that are neither <= 8 nor multiples of 4): a chunk is cut into groups of consecutive
+// bf16 ranks above 16 that are no multiple of 4 on rows of more than 4 million elements): a chunk is cut into groups of consecutive
 // rows, and the short rows (decode tokens of the all-position baseline, segments with at most
 // SHORT_ROWS active rows), which the scheduler has sorted by adapter and cut into gathered tiles,
 // into groups of rows of one adapter -- an adapter's factors are streamed once per group rather
