@@ -57,6 +57,28 @@ inline unsigned likely_units(const ApplyArgs &a, int64_t S)
     return likely < bound ? likely : bound;
 }
 
+// The column-split kernel keeps byte offsets within a first factor in 31 bits: up to the first 128 columns of the last rank's row (rank 127: 8.5
+// million columns, 64: 17, 16: 71 million).  Beyond, the row-split kernel takes chunks of whole 128-column units, and the
+// per-row kernels the rest; both count in 64 bits.
+inline bool column_split_fits(const ApplyArgs &a) { return (int64_t)(a.rank - 1) * a.d_in + 128 <= ((int64_t)1 << 30); }
+
+// widths the row-split shape with `cw` column groups takes
+inline bool wide_widths_ok(const ApplyArgs &a, int cw)
+{
+    const int m = 128 * cw;
+    return (a.d_in % m) == 0 && (a.d_out % m) == 0;
+}
+
+// Whether the matrix-core kernels take a bf16 call: from rank 4 on (ranks 1..3 are a vector-ALU matter).
+inline bool mfma_takes(const ApplyArgs &a, const Knobs &k)
+{
+    if (a.rank < 4) return false;
+    if (a.rank > 16 && wide_widths_ok(a, 1) && k.variant != 3) return true;      // the row-split kernel, its gathered tiles apart
+    // the column-split kernel; ranks above 16 that are no multiple of 4 up to the widths of the small-batch kernel
+    const bool narrow = a.d_in <= (1 << 22) && a.d_out <= (1 << 22);
+    return column_split_fits(a) && ((a.rank % 4) == 0 || a.rank < 16 || wide_widths_ok(a, 1) || narrow);
+}
+
 constexpr int32_t SMALL_T = 1024;
 constexpr int64_t DEEP_WGS = 200;                             // at most one workgroup per compute unit, with room for a poor estimate
 
@@ -133,6 +155,24 @@ inline SmallShape small_shape(const ApplyArgs &a, int64_t S, int n_slices, const
     for (int units = SMALL_WAVES; units <= 8 * SMALL_WAVES; units *= 2)
         if (workgroups(units) <= (many_adapters ? 300 : 640)) return {units, false, SMALL_WAVES};
     return {8 * SMALL_WAVES, false, SMALL_WAVES};
+}
+
+// Whether an in-place call of rank 17-31, no multiple of 4, takes 32-row tiles of the column-split kernel instead of 64-row tiles of the
+// row-split one, as the multiples of 4 always do: twice as many tiles, and their second read of h follows the first sooner.  But the large batches
+// of narrow rows find that read in the caches either way, and some ranks' unaligned factors cost the texture path more (21 and 31 of those measured).
+// Row-split / column-split, us: 2300 rows, d = 1024 / 4096 / 8192, rank 18 18.6 / 9.7, 64 / 27, 123 / 47, rank 31 18.8 / 11.6, 65 / 33, 126 / 60;
+// 14 000 rows, d = 512, rank 31 16.0 / 12.6, 8192, rank 29 154 / 117; 35 000 rows, rank 31, d = 512 25 / 30, 2048 89 / 86, 3072 130 / 135, 4096 187 / 178,
+// 8192 391 / 367; 90 000 rows, rank 19, d = 1024 87 / 102, 8192 855 / 693, rank 21 2048 190 / 208, 8192 848 / 793, rank 31 4096 400 / 406, 8192 867 / 823.
+inline bool odd_streams_in_place(const ApplyArgs &a)
+{
+    if (!column_split_fits(a)) return false;
+    return a.T <= 16384 || a.d_in >= 8192 || (a.d_in >= 4096 && a.T <= 49152);
+}
+
+// Ranks above 16 that are no multiple of 4: whether the column-split kernel takes the whole call, chunks and gathered tiles.
+inline bool odd_streams(const ApplyArgs &a, bool direft, const Knobs &k)
+{
+    return !wide_widths_ok(a, 1) || k.variant == 3 || (direft && a.rank <= 32 && k.variant == 0 && odd_streams_in_place(a));
 }
 
 }  // namespace preft

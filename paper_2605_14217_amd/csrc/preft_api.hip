@@ -248,13 +248,6 @@ void launch_wide_shape(const ApplyArgs &a, int64_t S, hipStream_t stream)
     hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 16 * MB * RW), a.n_layers), dim3(RW * CW * 64), 0, stream, a);
 }
 
-// widths the shape with `cw` column groups takes
-inline bool wide_widths_ok(const ApplyArgs &a, int cw)
-{
-    const int m = 128 * cw;
-    return (a.d_in % m) == 0 && (a.d_out % m) == 0;
-}
-
 // The expand launch of a call whose z is in the workspace: a workgroup per 32 rows x 512 columns.
 constexpr int EXPAND_MB = 2;
 
@@ -477,6 +470,39 @@ bool launch_mfma_wide(const ApplyArgs &a, int64_t S, int mb, int waves, int cw, 
     return true;
 }
 
+// ranks above 16 that are no multiple of 4: the column-split kernel, 4 wavefronts on 16 rows (`mb` 2: 32, rank 17-32)
+template <int NB, bool DIREFT>
+void launch_mfma_odd_stream(const ApplyArgs &a, int64_t S, int mb, hipStream_t stream)
+{
+    void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, 1, 4, 0, DIREFT, 1, false, 1>;
+    if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 1, 4, 0, false, 1>; }
+    int rows = 16;
+    if constexpr (NB == 2) {
+        if (mb == 2) {
+            rows = 32;
+            kernel = mfma_tile_kernel<NB, 2, 4, 0, DIREFT, 1, false, 1>;
+            if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 2, 4, 0, false, 1>; }
+        }
+    }
+    hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, rows), a.n_layers), dim3(256), 0, stream, a);
+}
+
+template <typename E, bool DIREFT>
+void launch_rows(const ApplyArgs &a, int64_t S, bool chunks_too, hipStream_t stream);
+
+// The gathered tiles (16 rows of an adapter) of a call whose chunks the row-split kernel takes, which shares an adapter's factors among
+// the 128 rows of a chunk: 16-row tiles of the column-split kernel, the per-row kernel where that one's offsets do not fit
+template <int NB, bool DIREFT>
+void launch_gathered(ApplyArgs a, int64_t S, hipStream_t stream)
+{
+    a.gathered_only = 1;
+    if (!column_split_fits(a)) { launch_rows<bf16_tag, DIREFT>(a, S, false, stream); return; }
+    if constexpr (NB > 1) {
+        if (a.rank % 4) { launch_mfma_odd_stream<NB, DIREFT>(a, S, 1, stream); return; }
+    }
+    launch_mfma_stream<NB, DIREFT>(a, S, 1, NB >= 2 ? 4 : 8, stream);
+}
+
 template <int NB, bool DIREFT>
 void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
@@ -501,7 +527,7 @@ void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t s
         // 16-row tile, and the tile's second read mostly still finds it in the memory-side cache)
         // measured ahead of the resident and row-split shapes at d = 4096 and d = 8192
         if constexpr (NB == 2) {
-            if (k.waves == 0 && (k.variant == 0 || k.variant == 5) && k.rowblocks == 0) {
+            if (k.waves == 0 && (k.variant == 0 || k.variant == 5) && k.rowblocks == 0 && column_split_fits(a)) {
                 // resident == 3 (tests): each wavefront keeps 8 of its units in registers and streams the
                 // rest twice.  Measured on the skewed batch (d = 8192): traffic through the fabric falls
                 // by a sixth (half of the tile is read once), the time by 4 % (5985 against 6216 us): the
@@ -519,11 +545,7 @@ void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t s
         }
     }
     if (k.variant != 3 && launch_mfma_wide<NB, DIREFT>(a, S, wide_mb, wide_waves, wide_cw, k, stream)) {
-        // the row-split kernel shares one adapter's factors among the 128 rows of a chunk;
-        // gathered tiles (16 rows of an adapter) go to the column-split kernel
-        ApplyArgs g = a;
-        g.gathered_only = 1;
-        launch_mfma_stream<NB, DIREFT>(g, S, 1, NB >= 2 ? 4 : 8, stream);
+        launch_gathered<NB, DIREFT>(a, S, stream);
         return;
     }
     launch_mfma_stream<NB, DIREFT>(a, S, mb, waves, stream);
@@ -544,23 +566,6 @@ void launch_mfma_packed(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream
     else
         hipLaunchKernelGGL((mfma_tile_kernel<1, 1, 4, 0, false, SLICES, false, PIECES>), dim3(tile_grid(a, S, 16)),
                            dim3(256), 0, stream, a);
-}
-
-// ranks above 16 that are no multiple of 4: the column-split kernel, 4 wavefronts on 16 rows (`mb` 2: 32, rank 17-32)
-template <int NB, bool DIREFT>
-void launch_mfma_odd_stream(const ApplyArgs &a, int64_t S, int mb, hipStream_t stream)
-{
-    void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, 1, 4, 0, DIREFT, 1, false, 1>;
-    if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 1, 4, 0, false, 1>; }
-    int rows = 16;
-    if constexpr (NB == 2) {
-        if (mb == 2) {
-            rows = 32;
-            kernel = mfma_tile_kernel<NB, 2, 4, 0, DIREFT, 1, false, 1>;
-            if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 2, 4, 0, false, 1>; }
-        }
-    }
-    hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, rows), a.n_layers), dim3(256), 0, stream, a);
 }
 
 // packed projections at rank 17..64 (widths multiples of 128): the row-split kernel with one sweep
@@ -584,6 +589,16 @@ void launch_mfma_wide_packed(const ApplyArgs &a, int n_proj, int64_t S, const Kn
     }
     ApplyArgs g = a;
     g.gathered_only = 1;
+    if (!column_split_fits(a)) {
+        for (int i = 0; i < n_proj; ++i) {
+            if (i > 0) {
+                g.y = a.more[i - 1].y; g.ldy = a.more[i - 1].ldy; g.d_out = a.more[i - 1].d_out;
+                g.A_pool = a.more[i - 1].A_pool; g.Bt_pool = a.more[i - 1].Bt_pool;
+            }
+            launch_rows<bf16_tag, false>(g, S, false, stream);
+        }
+        return;
+    }
     void (*gathered)(ApplyArgs) = odd ? mfma_tile_outputs_kernel<NB, 4, 1> : mfma_tile_outputs_kernel<NB, 4, 0>;
     hipLaunchKernelGGL(gathered, dim3(tile_grid(g, S, 16), n_proj), dim3(256), 0, stream, g);
 }
@@ -627,33 +642,20 @@ void launch_mfma_odd(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t 
     else             launch_mfma_odd_pieces<DIREFT, 4>(a, S, stream);
 }
 
-// Whether an in-place call of rank 17-31, no multiple of 4, takes 32-row tiles of the column-split kernel instead of 64-row tiles of the
-// row-split one, as the multiples of 4 always do: twice as many tiles, and their second read of h follows the first sooner.  But the large batches
-// of narrow rows find that read in the caches either way, and some ranks' unaligned factors cost the texture path more (21 and 31 of those measured).
-// Row-split / column-split, us: 2300 rows, d = 1024 / 4096 / 8192, rank 18 18.6 / 9.7, 64 / 27, 123 / 47, rank 31 18.8 / 11.6, 65 / 33, 126 / 60;
-// 14 000 rows, d = 512, rank 31 16.0 / 12.6, 8192, rank 29 154 / 117; 35 000 rows, rank 31, d = 512 25 / 30, 2048 89 / 86, 3072 130 / 135, 4096 187 / 178,
-// 8192 391 / 367; 90 000 rows, rank 19, d = 1024 87 / 102, 8192 855 / 693, rank 21 2048 190 / 208, 8192 848 / 793, rank 31 4096 400 / 406, 8192 867 / 823.
-bool odd_streams_in_place(const ApplyArgs &a)
-{
-    return a.T <= 16384 || a.d_in >= 8192 || (a.d_in >= 4096 && a.T <= 49152);
-}
-
 // bf16 ranks above 16 that are not multiples of 4.  Widths multiples of 128: the row-split kernel's any-rank form takes the chunks (its
 // basic shape: 4 wavefronts x 16 rows, above rank 64 8 x 16), the column-split kernel the gathered tiles (all-token mode: decode
 // rows); other widths: the column-split kernel takes all.  (They took the per-row kernels: 30 to 300 times as long.)
 template <int NB, bool DIREFT>
 void launch_mfma_odd_wide(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
-    if (!wide_widths_ok(a, 1) || k.variant == 3 || (DIREFT && NB == 2 && k.variant == 0 && odd_streams_in_place(a))) {
+    if (odd_streams(a, DIREFT, k)) {
         launch_mfma_odd_stream<NB, DIREFT>(a, S, 2, stream);
         return;
     }
     bool split = false;
     if constexpr (NB == 4 || (NB == 2 && !DIREFT)) split = launch_mfma_split<NB, 1, DIREFT>(a, S, k, stream);
     if (!split) launch_wide_shape<NB, 1, NB <= 4 ? 4 : 8, 1, DIREFT, true>(a, S, stream);
-    ApplyArgs g = a;
-    g.gathered_only = 1;
-    launch_mfma_odd_stream<NB, DIREFT>(g, S, 1, stream);
+    launch_gathered<NB, DIREFT>(a, S, stream);
 }
 
 template <bool DIREFT>
@@ -842,10 +844,7 @@ Path choose_path(const ApplyArgs &a, int64_t S, bool direft, int dtype, const Kn
         if (k.variant == 0 && k.colsplit == 0 && f32_rows_win(a, S, direft)) return Path::Rows;
         return Path::F32;
     }
-    // matrix-core kernels from rank 4 on; ranks 1..3 are a vector-ALU matter.  (Ranks above 16 that are no multiple of 4 on widths
-    // that are no multiples of 128: byte offsets within a factor in 32 bits)
-    const bool narrow = a.d_in <= (1 << 22) && a.d_out <= (1 << 22);
-    const bool valu_ok = rank <= 8, mfma_ok = rank >= 4 && ((rank % 4) == 0 || rank < 16 || wide_widths_ok(a, 1) || narrow);
+    const bool valu_ok = rank <= 8, mfma_ok = mfma_takes(a, k);
     if (k.variant == 2 && valu_ok) return Path::Valu;
     if ((k.variant == 3 || k.variant == 4) && mfma_ok) return Path::Mfma;
     if (rank <= 3) return Path::Valu;
@@ -1036,8 +1035,6 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
     }
     const int ready = mode | PREFT_SCHEDULE_READY;
     const Knobs k = knobs_of(mode);
-    const bool fused_mfma = n_proj > 1 && dtype == PREFT_BF16 && rank >= 4 && rank <= 16 &&
-                            (k.variant == 0 || k.variant == 3 || k.variant == 5);
     const bool fused_valu = n_proj > 1 && dtype == PREFT_BF16 && rank <= 3 && (k.variant == 0 || k.variant == 2) &&
                             (k.waves == 0 || k.waves == 4);
     bool fused_wide = n_proj > 1 && dtype == PREFT_BF16 && rank > 16 && rank <= 64 &&
@@ -1047,6 +1044,8 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
     ApplyArgs a;
     bind_schedule(a, workspace, T, S, N, mode);
     a.x = x; a.ldx = ldx; a.d_in = d_in; a.rank = rank;
+    const bool fused_mfma = n_proj > 1 && dtype == PREFT_BF16 && rank >= 4 && rank <= 16 &&
+                            (k.variant == 0 || k.variant == 3 || k.variant == 5) && column_split_fits(a);
     int32_t widest = 0;
     for (int32_t i = 0; i < n_proj; ++i) if (d_out[i] > widest) widest = d_out[i];
     const bool fused_small = n_proj > 1 && dtype == PREFT_BF16 && takes_small(a, S, widest, false, k);

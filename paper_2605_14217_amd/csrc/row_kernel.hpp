@@ -1,8 +1,9 @@
 // Per-row ("batched gather matrix-vector") kernel: one workgroup applies one adapter to a group
 // of at most GROUP_ROWS rows that share it.
 //
-// This is the generic fallback for what the tile kernels do not cover (fp32 of rank 1-8 where few tiles meet wide rows;
-// bf16 ranks above 16 that are no multiple of 4 on rows of more than 4 million elements): a chunk is cut into groups of consecutive
+// This is the generic fallback for what the tile kernels do not cover (fp32 of rank 1-8 where few tiles meet wide rows, or on rows of
+// more than 4 million elements; bf16 where a first factor is beyond the column-split kernel's offsets, column_split_fits, and at ranks
+// above 16 that are no multiple of 4 on rows of more than 4 million elements and no whole 128-column units): a chunk is cut into groups of consecutive
 // rows, and the short rows (decode tokens of the all-position baseline, segments with at most
 // SHORT_ROWS active rows), which the scheduler has sorted by adapter and cut into gathered tiles,
 // into groups of rows of one adapter -- an adapter's factors are streamed once per group rather

@@ -112,3 +112,33 @@ def test_in_place_on_widths_that_are_multiples_of_128(rank, d):
                 compare(h, x, want, owner, "bf16")
         else:
             assert (got[3].float() - got[4].float()).abs().max() <= 2 ** -6 * got[4].float().abs().max()      # two bf16 roundings of the largest value
+
+
+@pytest.mark.parametrize("rank,d,outs,lens,in_place", [(127, 8523264, (128,), [5, 1], False), (64, 17301504, (128,), [5, 1], False), (31, 35791488, (), [5], True),
+                                                       (63, 17432576, (128, 256), [600, 500, 1], False), (16, 71586816, (8, 16), [5, 1], False)])
+def test_factors_beyond_the_column_split_kernels_offsets(rank, d, outs, lens, in_place):
+    """First factors of more than 2^31 bytes, whose last rank lies beyond a signed 32-bit offset: only that rank's row holds anything, ones and minus ones, and
+    x single ones, so that z is a small integer and y that integer times its factor, to the bit."""
+    from parity_util import dev_tables
+    lens = np.array(lens)
+    T = int(lens.sum())
+    tab = wl.from_lengths(lens, np.zeros(len(lens), int), np.where(lens > 1, lens, 0))
+    ss, sa, sp = dev_tables(tab)
+    g = torch.Generator(device="cuda").manual_seed(rank)
+    A = torch.zeros(rank, d, dtype=torch.bfloat16, device="cuda")
+    A[rank - 1] = 2 * torch.randint(0, 2, (d,), generator=g, device="cuda") - 1
+    at = torch.randint(0, d, (T, 64), generator=g, device="cuda")          # places of x that hold a one
+    x = torch.zeros(T, d, dtype=torch.bfloat16, device="cuda").scatter_(1, at, 1.0)
+    z = torch.stack([A[rank - 1][torch.unique(at[t])].float().sum() for t in range(T)]).view(T, 1)
+    Ap = preft.pointer_table([A])
+    ws = preft.new_workspace(T, len(lens), z_rank=min(rank, 64), z_proj=max(1, len(outs)))
+    Bs = [torch.randint(-3, 4, (n, rank), generator=g, device="cuda").to(torch.bfloat16) for n in (outs or (d,))]
+    if in_place:
+        want = (x.float() + z * Bs[0][:, rank - 1].float()).to(torch.bfloat16)
+        preft.preft_direft_apply(x, ss, sa, sp, Ap, preft.pointer_table(Bs), None, rank, 1.0, preft.PREFT_ALL_TOKENS, ws)
+        assert torch.equal(x, want)
+        return
+    ys = [torch.zeros(T, n, dtype=torch.bfloat16, device="cuda") for n in outs]
+    preft.preft_lora_apply_packed(ys, x, ss, sa, sp, [Ap] * len(outs), [preft.pointer_table([b]) for b in Bs], rank, 1.0, preft.PREFT_ALL_TOKENS, ws)
+    for y, b in zip(ys, Bs):
+        assert torch.equal(y, (z * b[:, rank - 1].float()).to(torch.bfloat16))
