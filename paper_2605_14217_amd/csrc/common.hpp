@@ -158,6 +158,36 @@ __device__ __forceinline__ u32x2_t quad_from(u32x2_t four, int rank0, int rank)
     const uint64_t v = before < 4 ? __builtin_bit_cast(uint64_t, four) >> (16 * (before & 3)) : 0;
     return __builtin_bit_cast(u32x2_t, v);
 }
+// Those ranks' z goes to the matrix cores whole: its 24 bits as three bf16 numbers of 8, cut and not rounded, whose sum it is (elsewhere two of 8, 1.5e-5 of
+// z).  Infinite and NaN: the head alone.
+struct WholeZ { uint32_t head[2], mid[2], low[2]; };         // ranks 0 and 1, 2 and 3 of the lane's four
+__device__ __forceinline__ WholeZ whole_z(const float (&z)[4])
+{
+    WholeZ w;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        uint32_t part[3][2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const float v = z[2 * i + e];
+            part[0][e] = __float_as_uint(v) & 0xffff0000u;
+            const float rest = (part[0][e] & 0x7f800000u) != 0x7f800000u ? v - __uint_as_float(part[0][e]) : 0.f;
+            part[1][e] = __float_as_uint(rest) & 0xffff0000u;
+            part[2][e] = __float_as_uint(rest - __uint_as_float(part[1][e]));
+        }
+        auto pair = [&](int k) { return (part[k][0] >> 16) | (part[k][1] & 0xffff0000u); };
+        w.head[i] = pair(0); w.mid[i] = pair(1); w.low[i] = pair(2);
+    }
+    return w;
+}
+// two bf16 factors, infinite and NaN ones as zeros: what meets the parts of z below its head, whose product with the factor they would turn into NaN
+__device__ __forceinline__ uint32_t finite_only(uint32_t two)
+{
+    const uint32_t special = ((two & 0x7f807f80u) + 0x00800080u) & 0x80008000u;      // the top bit of each whose exponent is all ones
+    return two & ~(special | (special - (special >> 15)));
+}
+__device__ __forceinline__ u32x2_t finite_only(u32x2_t four) { return u32x2_t{finite_only(four[0]), finite_only(four[1])}; }
+
 // first of two reads of the same bytes (an in-place call that does not keep its tile): cacheable
 template <bool AGAIN_LATER>
 __device__ __forceinline__ u32x4_t ld16_first(gcptr_t p)

@@ -51,6 +51,26 @@ namespace preft {
 __device__ __forceinline__ bf16x8_t as_bf16x8(u32x4_t v) { return __builtin_bit_cast(bf16x8_t, v); }
 __device__ __forceinline__ u32x4_t as_u32x4(bf16x8_t v) { return __builtin_bit_cast(u32x4_t, v); }
 
+// Ranks above 16 that are no multiple of 4: the products of a column group's factors with z, whole (whole_z).  The factors meet head and middle
+// part in one MFMA per rank block, the lowest parts of two blocks in one more.  FINITE: infinite and NaN factors meet the head
+// alone (inf times a lower part of the other sign, or zero, is NaN where inf times z is inf).  That costs seven instructions for every two
+// factors, so a unit is computed without it first and again only where a result is NaN.
+template <int NB, bool FINITE, typename W, typename Z, typename L>
+__device__ __forceinline__ f32x4_t whole_z_products(W factors, Z z, L low)
+{
+    f32x4_t d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NB / 2; ++i) {
+        const u32x2_t w[2] = {factors(2 * i), factors(2 * i + 1)};
+        const u32x2_t f[2] = {FINITE ? finite_only(w[0]) : w[0], FINITE ? finite_only(w[1]) : w[1]};
+        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{f[0][0], f[0][1], f[1][0], f[1][1]}), as_bf16x8(low(i)), d, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[e][0], w[e][1], f[e][0], f[e][1]}), z(2 * i + e), d, 0, 0, 0);
+    }
+    return d;
+}
+
 // XCD-aware unit index: workgroup ids are dealt round-robin to the 8 XCDs, so the units
 // are cut into 8 contiguous runs and XCD x walks run x in order.  Consecutive units (same
 // segment, same adapter) then share one XCD's L2.
@@ -91,7 +111,9 @@ constexpr int mfma_min_waves(int NB, int MB, int WAVES, int HUNITS)
 // lane carries: 2 up to rank 8, 4 up to rank 16.  In place with the tile in registers, the blocks of the
 // first two units are requested before the reduction of z and the next ones while a unit is finished.
 // ODD = 1 (rank > 16): the same ranks above 16 (17, 18, 19, 21, ...), whatever the widths: a lane's four factors of a column are one
-// 8-byte load from wherever they start (quad_from), which the texture path takes a few cycles longer for.
+// 8-byte load from wherever they start (quad_from), which the texture path takes a few cycles longer for.  They keep all 24 bits of z
+// (whole_z), as the per-row kernels do that these calls took before: an MFMA per two rank blocks more, 0 to 4 % (rank 63, 1000 -> 2728, 11 700 rows 132 -> 137 us, 4096 ->
+// 4096, 900 rows 37.4 -> 37.9; rank 31 in place, d = 4096, 11 700 rows 62.4 -> 62.7; rank 18, 8192, 2200 rows 45.2 -> 47.5).
 //
 // ZOUT: the shrink sweep alone.  z goes to the workspace in the form the expand's MFMAs take it, 1 KB per
 // 16-row block and rank block, and mfma_expand_kernel does the expand in a second launch.
@@ -402,7 +424,10 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     // ---------------------------------------------------------------- z -> expand operand
     // lane (row rl, g) holds z[row][16b + 4g + v]; add the bias, apply the prefactor, zero the
     // padding ranks, and split into bf16 head + bf16 remainder.
+    constexpr bool WHOLE = ODD == 1;                          // z in three parts (whole_z)
+    static_assert(!WHOLE || SLICES == 1, "one output");
     bf16x8_t zop[NBT][MB];
+    u32x4_t zlow[WHOLE ? NB / 2 : 1][MB];                     // the lowest parts, two rank blocks in one operand
 #pragma unroll
     for (int b = 0; b < NBT; ++b) {
         const int rank0 = 16 * (b % NB) + 4 * g;              // rank within the block's own slice
@@ -426,6 +451,13 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
                 const uint32_t hb = pack_bf16(zv, 0.f) & 0xffffu;
                 head_f[v] = zv;
                 rem_f[v] = zv - __uint_as_float(hb << 16);
+            }
+            if constexpr (WHOLE) {
+                const WholeZ w = whole_z(head_f);
+                zop[b][mb] = as_bf16x8(u32x4_t{w.head[0], w.head[1], w.mid[0], w.mid[1]});
+                zlow[b / 2][mb][2 * (b % 2)] = w.low[0];
+                zlow[b / 2][mb][2 * (b % 2) + 1] = w.low[1];
+                continue;
             }
             u32x4_t packed;
             packed[0] = pack_bf16(head_f[0], head_f[1]);
@@ -493,16 +525,22 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     const int64_t w_step = (int64_t)32 * r * 2;               // bytes per 32 output columns
 
     // out = y + delta for one 32-column step and one row block; y and the result in MFMA order
-    auto expand_step = [&](const u32x4_t yv, const u32x2_t (&wv)[2][NB], int mb) -> u32x4_t {
+    // (finite_tag: whole_z_products; `nan` tells whether a result is NaN, ranks above 16 that are no multiple of 4 only)
+    auto expand_step = [&](const u32x4_t yv, const u32x2_t (&wv)[2][NB], int mb, auto finite_tag, bool &nan) -> u32x4_t {
         float out[8];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if constexpr (WHOLE) {
+                d = whole_z_products<NB, decltype(finite_tag)::value>([&](int b) { return wv[e][b]; }, [&](int b) { return zop[b][mb]; }, [&](int i) { return zlow[i][mb]; });
+                nan = nan || __builtin_isunordered(d[0], d[1]) || __builtin_isunordered(d[2], d[3]);
+            } else {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const u32x2_t w = wv[e][b];
-                const bf16x8_t wop = as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]});
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wop, zop[SL * NB + b][mb], d, 0, 0, 0);
+                for (int b = 0; b < NB; ++b) {
+                    const u32x2_t w = wv[e][b];
+                    const bf16x8_t wop = as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]});
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wop, zop[SL * NB + b][mb], d, 0, 0, 0);
+                }
             }
             const uint32_t y01 = yv[2 * e], y23 = yv[2 * e + 1];
             out[4 * e + 0] = bf16_lo(y01) + d[0];
@@ -559,16 +597,22 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
             for (int i = 0; i < ODD; ++i)
                 if (lane + 64 * i < 16 * r) tra[lane + 64 * i] = wb[i];
         }
+        auto columns = [&](auto finite_tag) {
+            bool nan = false;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            u32x2_t wv[2][NB];
-            w_operands(wb, s, wv);
+            for (int s = 0; s < 4; ++s) {
+                u32x2_t wv[2][NB];
+                w_operands(wb, s, wv);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const u32x4_t yv = yop[mb][s];
-                tr[(mb * 16 + rl) * MFMA_TRS + 4 * s + g] = expand_step(yv, wv, mb);
+                for (int mb = 0; mb < MB; ++mb) {
+                    const u32x4_t yv = yop[mb][s];
+                    tr[(mb * 16 + rl) * MFMA_TRS + 4 * s + g] = expand_step(yv, wv, mb, finite_tag, nan);
+                }
             }
-        }
+            return nan;
+        };
+        const bool nan = columns(std::false_type{});
+        if constexpr (WHOLE) { if (__any(nan)) columns(std::true_type{}); }
         const int64_t off = (int64_t)c_unit(u) * 256;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
@@ -668,7 +712,10 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
         }
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-            const u32x4_t o = mfma_to_step(expand_step(yv[mb], wv, mb));
+            bool nan = false;
+            u32x4_t out = expand_step(yv[mb], wv, mb, std::false_type{}, nan);
+            if constexpr (WHOLE) { if (__any(nan)) out = expand_step(yv[mb], wv, mb, std::true_type{}, nan); }
+            const u32x4_t o = mfma_to_step(out);
             if (col_ok) st16_stream(ys[mb] + off, o);
         }
     }

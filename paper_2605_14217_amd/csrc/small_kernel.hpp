@@ -201,6 +201,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         for (int v = 0; v < 4; ++v) red[((wave * NB + b) * 4 + v) * 64 + lane] = acc[b][v];
     __syncthreads();                                          // also: every read of the tile precedes every write (in place: a unit belongs to one wavefront)
     bf16x8_t zop[NB];
+    u32x4_t zlow[ANY ? NB / 2 : 1];                           // what two parts of bf16 leave of z (whole_z), two rank blocks in one operand
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int rank0 = 16 * b + 4 * g;
@@ -216,7 +217,14 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             zv[v] = rank0 + v < r ? (s + add) * p.scale : 0.f;
             rem[v] = zv[v] - __uint_as_float((pack_bf16(zv[v], 0.f) & 0xffffu) << 16);
         }
-        zop[b] = as_bf16x8(u32x4_t{pack_bf16(zv[0], zv[1]), pack_bf16(zv[2], zv[3]), pack_bf16(rem[0], rem[1]), pack_bf16(rem[2], rem[3])});
+        if constexpr (ANY) {
+            const WholeZ w = whole_z(zv);
+            zop[b] = as_bf16x8(u32x4_t{w.head[0], w.head[1], w.mid[0], w.mid[1]});
+            zlow[b / 2][2 * (b % 2)] = w.low[0];
+            zlow[b / 2][2 * (b % 2) + 1] = w.low[1];
+        } else {
+            zop[b] = as_bf16x8(u32x4_t{pack_bf16(zv[0], zv[1]), pack_bf16(zv[2], zv[3]), pack_bf16(rem[0], rem[1]), pack_bf16(rem[2], rem[3])});
+        }
     }
 
     // ---------------------------------------------------------------- expand
@@ -238,6 +246,10 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             for (int j = 0; j < PIECES; ++j)
                 if (lane + 64 * j < 16 * r) tra[lane + 64 * j] = Wb[k][j];
         }
+        // FINITE (ANY only): infinite and NaN factors meet the head of z alone.  Tells whether a result is NaN
+        auto columns = [&](auto finite_tag) {
+        constexpr bool FINITE = decltype(finite_tag)::value;
+        bool nan = false;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             if constexpr (W_LATE) load_w(W[0][0], u, s);
@@ -245,6 +257,11 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 f32x4_t d = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (ANY) {
+                    d = whole_z_products<NB, FINITE>([&](int b) { return quad_from(W[k][W_LATE ? 0 : s][e][b], 16 * b + 4 * g, r); },
+                                                     [&](int b) { return zop[b]; }, [&](int i) { return zlow[i]; });
+                    nan = nan || __builtin_isunordered(d[0], d[1]) || __builtin_isunordered(d[2], d[3]);
+                } else {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     u32x2_t w;
@@ -254,9 +271,9 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
                         w = u32x2_t{__builtin_amdgcn_alignbit(d1, d0, odd_shift) & odd_m01, __builtin_amdgcn_alignbit(d2, d1, odd_shift) & odd_m23};
                     } else {
                         w = W[k][W_LATE ? 0 : s][e][b];
-                        if constexpr (ANY) w = quad_from(w, 16 * b + 4 * g, r);
                     }
                     d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), zop[b], d, 0, 0, 0);
+                }
                 }
                 const uint32_t y01 = yo[s][2 * e], y23 = yo[s][2 * e + 1];
                 out[4 * e + 0] = bf16_lo(y01) + d[0];
@@ -265,6 +282,12 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
                 out[4 * e + 3] = bf16_hi(y23) + d[3];
             }
             tr[rl * MFMA_TRS + 4 * s + g] = Elem<bf16_tag>::pack(out);
+        }
+        return nan;
+        };
+        const bool nan = columns(std::false_type{});
+        if constexpr (ANY) {                                  // (rows that do not exist may hold anything)
+            if (__any(nan && rl < n_rows)) columns(std::true_type{});
         }
         const int off = u * 256 + c16 * 16;
 #pragma unroll
