@@ -161,7 +161,7 @@ def _load_marshal(lib):
         import warnings
         warnings.warn(f"preft: _marshal.so does not load ({e}); rebuild with python -m paper_2605_14217_amd.build.  Calls are marshalled in Python.")
         return None
-    _marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+    _marshal.bind(PoolRef, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
         lib.preft_schedule, lib.preft_lora_apply, lib.preft_lora_apply_packed, lib.preft_direft_apply, lib.preft_loreft_apply,
         lib.preft_direft_apply_layers)))
     return _marshal

@@ -1,8 +1,8 @@
 // Marshalling of the calls of a serving loop: the arguments of a schedule or apply call, as torch tensors, to the C ABI.
 //
 // A ctypes call of 21 arguments, with every property of ten tensors asked for from Python, takes 4 to 7 us beside the 3 us of
-// the launch itself; a launch of 6 us waits for it.  Here the same takes below 1 us.  Only the ordinary case is handled: anything
-// else -- a tensor subclass, a table that is no tensor, a check that fails, an exception of torch -- answers None, and the
+// the launch itself; a launch of 6 us waits for it.  Here the same takes below 1 us, also with the slot manager's pools (binding.PoolRef) and with
+// numbers of any type.  Anything else -- a tensor subclass, another table, a check that fails, an exception of torch -- answers None, and the
 // caller goes through binding.py's own path, which makes the same checks and raises what they raise.
 #include <Python.h>
 
@@ -53,8 +53,27 @@ bool as_segments(PyObject *const *o, Segments &s)
     return as_table(o[0], (int64_t)s.S + 1, s.start) && as_table(o[1], s.S, s.adapter) && as_table(o[2], s.S, s.prefill);
 }
 
+PyObject *g_pool_ref, *g_address, *g_length;                  // binding.PoolRef, and the names of what it holds
+
+bool as_pool_ref(PyObject *o, int64_t &n, const void *const *&p)
+{
+    if ((PyObject *)Py_TYPE(o) != g_pool_ref) return false;
+    PyObject *address = PyObject_GetAttr(o, g_address), *length = address ? PyObject_GetAttr(o, g_length) : nullptr;
+    bool ok = length && PyLong_CheckExact(address) && PyLong_CheckExact(length);
+    if (ok) {
+        void *at = PyLong_AsVoidPtr(address);
+        const long long count = PyLong_AsLongLong(length);
+        ok = !PyErr_Occurred() && count >= 0 && count <= INT32_MAX && (n < 0 || count == n);
+        if (ok) { p = static_cast<const void *const *>(at); n = count; }
+    }
+    Py_XDECREF(address);
+    Py_XDECREF(length);
+    return ok;
+}
+
 bool as_pool(PyObject *o, int64_t &n, const void *const *&p)      // n < 0: any length
 {
+    if (as_pool_ref(o, n, p)) return true;
     const at::Tensor *t = tensor(o);
     if (!t || t->scalar_type() != at::kLong || (n >= 0 && t->numel() != n) || t->numel() > INT32_MAX) return false;
     n = t->numel();
@@ -64,9 +83,16 @@ bool as_pool(PyObject *o, int64_t &n, const void *const *&p)      // n < 0: any 
 
 bool as_int(PyObject *o, int32_t &v)
 {
-    if (!PyLong_CheckExact(o)) return false;
     int overflow = 0;
-    const long long x = PyLong_AsLongLongAndOverflow(o, &overflow);
+    long long x;
+    if (PyLong_CheckExact(o)) {
+        x = PyLong_AsLongLongAndOverflow(o, &overflow);
+    } else {                                                  // whole numbers of other types: NumPy's, truth values
+        PyObject *i = PyIndex_Check(o) ? PyNumber_Index(o) : nullptr;
+        if (!i) return false;
+        x = PyLong_AsLongLongAndOverflow(i, &overflow);
+        Py_DECREF(i);
+    }
     if (overflow || x < INT32_MIN || x > INT32_MAX) return false;
     v = (int32_t)x;
     return true;
@@ -95,8 +121,9 @@ bool as_stream(PyObject *o, void *&p)
 bool as_rest(PyObject *const *o, Rest &r)
 {
     if (!as_int(o[0], r.rank) || !as_int(o[2], r.mode) || !as_int(o[5], r.extra)) return false;
-    if (!PyFloat_CheckExact(o[1])) return false;
-    r.scale = (float)PyFloat_AS_DOUBLE(o[1]);
+    const double scale = PyFloat_AsDouble(o[1]);              // whole numbers and NumPy's too
+    if (scale == -1.0 && PyErr_Occurred()) return false;
+    r.scale = (float)scale;
     r.mode |= r.extra;
     return as_workspace(o[3], r.workspace, r.bytes) && as_stream(o[4], r.stream);
 }
@@ -236,11 +263,12 @@ PyObject *reft_layers(PyObject *, PyObject *const *o, Py_ssize_t n)
     });
 }
 
-// addresses of the loaded library's entry points, in the order below
+// binding.PoolRef, and the addresses of the loaded library's entry points in the order below
 PyObject *bind(PyObject *, PyObject *const *o, Py_ssize_t n)
 {
     void *p[6];
-    if (n != 6) { PyErr_SetString(PyExc_TypeError, "six addresses"); return nullptr; }
+    if (n != 7) { PyErr_SetString(PyExc_TypeError, "a class and six addresses"); return nullptr; }
+    PyObject *const pool_ref = *o++;
     for (int i = 0; i < 6; ++i) {
         p[i] = PyLong_AsVoidPtr(o[i]);
         if (PyErr_Occurred()) return nullptr;
@@ -251,6 +279,12 @@ PyObject *bind(PyObject *, PyObject *const *o, Py_ssize_t n)
     g_direft = reinterpret_cast<decltype(g_direft)>(p[3]);
     g_loreft = reinterpret_cast<decltype(g_loreft)>(p[4]);
     g_layers = reinterpret_cast<decltype(g_layers)>(p[5]);
+    if (!g_address) g_address = PyUnicode_InternFromString("_address");
+    if (!g_length) g_length = PyUnicode_InternFromString("_n");
+    if (!g_address || !g_length) return nullptr;
+    Py_INCREF(pool_ref);
+    Py_XDECREF(g_pool_ref);
+    g_pool_ref = pool_ref;
     Py_RETURN_NONE;
 }
 

@@ -80,3 +80,47 @@ def test_same_calls_as_the_python_path(native, dtype, monkeypatch):
     for tensors, c in got:
         assert c == codes and all(torch.equal(bits(a), bits(w)) for a, w in zip(tensors, want))
     assert not torch.equal(bits(want[0]), bits(y0))
+
+
+@pytest.mark.gpu
+def test_slot_pools_and_numbers_of_other_types_are_marshalled_too(native):
+    """The slot manager's pools, NumPy integers and whole-number scales: one native call each (an answer that is not None), with the bits of
+    the ordinary call; a pool of another length is declined."""
+    from parity_util import bits, dev_tables
+    N, r, d = 3, 8, 256
+    tab = wl.from_lengths(np.array([40, 1, 17]), np.array([0, 1, 2]), np.array([40, 1, 17]))
+    seg = dev_tables(tab)
+    x, y0 = (wl.activations(tab.T, n, "bf16", device="cuda", seed=n) for n in (d, d + 8))
+    pool = wl.lora_pool(N, r, d, d + 8, "bf16", device="cuda", seed=1)
+    host = [[t.cpu().contiguous() for t in part] for part in (pool.A, pool.B)]
+    stream = torch.cuda.current_stream().cuda_stream
+    ws = preft.new_workspace(tab.T, tab.S)
+    mgr = preft.preft_slots_create(N, N, [r * d * 2, (d + 8) * r * 2])
+    try:
+        for a in range(N):
+            for part in range(2):
+                preft.preft_slots_store(mgr, a, part, host[part][a])
+        slots = preft.preft_slots_acquire(mgr, list(range(N)))
+        refs = [preft.preft_slots_pool(mgr, part) for part in range(2)]
+        order = sorted(range(N), key=lambda a: slots[a])       # slot -> adapter
+        tables = [preft.pointer_table([m[a].contiguous() for a in order]) for m in (pool.A, pool.B)]
+        got = []
+        for A, B, rank, scale, mode in ((*tables, r, 2.0, preft.PREFT_ALL_TOKENS), (*refs, r, 2.0, preft.PREFT_ALL_TOKENS), (refs[0], tables[1], np.int64(r), 2, np.int32(1)),
+                                        (*tables, np.int32(r), np.float32(2.0), True)):
+            y, z = y0.clone(), y0.clone()
+            assert native.lora(y, x, *seg, A, B, rank, scale, mode, ws, stream, 0) == 0
+            assert native.lora_packed([z], x, *seg, [A], [B], rank, scale, mode, ws, stream, 0) == 0
+            got += [y, z]
+        h, l = x.clone(), x.clone()
+        square = binding.PoolRef(refs[0].data_ptr(), N)          # [r, d] matrices as both factors: any bytes will do
+        assert native.reft(False, h, *seg, square, square, None, r, 1, preft.PREFT_ALL_TOKENS, ws, stream, 0) == 0
+        assert native.reft(False, l, *seg, tables[0], square, None, r, 1.0, preft.PREFT_ALL_TOKENS, ws, stream, 0) == 0
+        assert native.schedule(ws, *seg, np.int64(tab.T), N, 1, stream) == 0
+        assert native.lora(y0, x, *seg, refs[0], binding.PoolRef(refs[1].data_ptr(), N - 1), r, 2.0, 1, ws, stream, 0) is None
+        assert native.lora(y0, x, *seg, *refs, 2.5, 2.0, 1, ws, stream, 0) is None and native.lora(y0, x, *seg, *refs, r, "2", 1, ws, stream, 0) is None
+        assert native.lora(y0, x, *seg, *refs, 1 << 40, 2.0, 1, ws, stream, 0) is None
+        torch.cuda.synchronize()
+        assert all(torch.equal(bits(v), bits(got[0])) for v in got) and torch.equal(bits(h), bits(l)) and not torch.equal(bits(got[0]), bits(y0))
+    finally:
+        torch.cuda.synchronize()
+        preft.preft_slots_destroy(mgr)
