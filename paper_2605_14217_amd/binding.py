@@ -208,6 +208,14 @@ def _stream(stream):
     return getattr(stream, "cuda_stream", stream)
 
 
+def _native_stream(stream):
+    """The handle for a native call, or None, which that declines, where there is no device to ask: the caller's own checks come first then."""
+    try:
+        return _stream(stream)
+    except (RuntimeError, AssertionError):
+        return None
+
+
 def _host_stream(stream):
     """Stream of a call that takes no device tensor: torch's device state may not exist yet."""
     if stream is None:
@@ -274,7 +282,7 @@ def new_workspace(T: int, S: int, device="cuda", z_rank: int = 0, z_proj: int = 
 def preft_schedule(workspace: torch.Tensor, seg_start, seg_adapter, seg_prefill_len, T: int, N: int,
                    mode: int, stream=None) -> None:
     if _native is not None:
-        rc = _native.schedule(workspace, seg_start, seg_adapter, seg_prefill_len, T, N, mode, _stream(stream))
+        rc = _native.schedule(workspace, seg_start, seg_adapter, seg_prefill_len, T, N, mode, _native_stream(stream))
         if rc is not None:
             return _check(rc, "preft_schedule")
     S = int(seg_adapter.numel())
@@ -298,7 +306,7 @@ def preft_lora_apply(y: torch.Tensor, x: torch.Tensor, seg_start, seg_adapter, s
     """y[t] += scale * B_i (A_i x[t]) on active rows, in place.  A_pool/B_pool: pointer tables
     (see pointer_table) of [rank, d_in] and [d_out, rank] matrices."""
     if _native is not None:
-        rc = _native.lora(y, x, seg_start, seg_adapter, seg_prefill_len, A_pool, B_pool, rank, scale, mode, workspace, _stream(stream),
+        rc = _native.lora(y, x, seg_start, seg_adapter, seg_prefill_len, A_pool, B_pool, rank, scale, mode, workspace, _native_stream(stream),
                           _extra_mode_bits)
         if rc is not None:
             return _check(rc, "preft_lora_apply")
@@ -326,7 +334,7 @@ def preft_lora_apply_packed(ys: Sequence[torch.Tensor], x: torch.Tensor, seg_sta
     gate,up); ys may be separate tensors or column slices of one tensor."""
     if _native is not None:
         rc = _native.lora_packed(ys, x, seg_start, seg_adapter, seg_prefill_len, A_pools, B_pools, rank, scale, mode, workspace,
-                                 _stream(stream), _extra_mode_bits)
+                                 _native_stream(stream), _extra_mode_bits)
         if rc is not None:
             return _check(rc, "preft_lora_apply_packed")
     n = len(ys)
@@ -418,7 +426,7 @@ def preft_direft_apply_layers(hs: Sequence[torch.Tensor], h_layers: torch.Tensor
     table of N slots (b_pools None: no bias; an entry 0: no bias in that layer)."""
     if _native is not None:
         rc = _native.reft_layers(hs, h_layers, seg_start, seg_adapter, seg_prefill_len, W1_pools, W2t_pools, b_pools, N, rank, scale, mode,
-                                 workspace, _stream(stream), _extra_mode_bits)
+                                 workspace, _native_stream(stream), _extra_mode_bits)
         if rc is not None:
             return _check(rc, "preft_direft_apply_layers")
     L = len(hs)
@@ -447,7 +455,7 @@ def _reft_apply(entry: str, h, seg_start, seg_adapter, seg_prefill_len, W1_pool,
                 mode, workspace, stream) -> None:
     if _native is not None:
         rc = _native.reft(entry == "preft_loreft_apply", h, seg_start, seg_adapter, seg_prefill_len, W1_pool, W2t_pool, b_pool, rank, scale,
-                          mode, workspace, _stream(stream), _extra_mode_bits)
+                          mode, workspace, _native_stream(stream), _extra_mode_bits)
         if rc is not None:
             return _check(rc, entry)
     hp, ldh, T, d = _matrix(h, "h")

@@ -30,6 +30,17 @@ def test_what_is_no_ordinary_call_goes_through_the_binding(native):
         preft.preft_lora_apply(t, t, i32, i32, i32, i64, i64, 4, 1.0, 0, ws, stream=0)
     with pytest.raises(ValueError, match="seg_start"):
         preft.preft_schedule(ws, i32, i32, i32, 4, 2, 0, stream=0)
+    if not torch.cuda.is_available():                         # nor does asking for the current stream come before the checks
+        with pytest.raises(ValueError, match="y: need a 2-D device tensor"):
+            preft.preft_lora_apply(t, t, i32, i32, i32, i64, i64, 4, 1.0, 0, ws)
+        with pytest.raises(ValueError, match=r"ys\[0\]|x: need a 2-D device tensor"):
+            preft.preft_lora_apply_packed([t], t, i32, i32, i32, [i64], [i64], 4, 1.0, 0, ws)
+        with pytest.raises(ValueError, match="h: need a 2-D device tensor"):
+            preft.preft_direft_apply(t, i32, i32, i32, i64, i64, None, 4, 1.0, 0, ws)
+        with pytest.raises(ValueError, match=r"hs\[0\]: need a 2-D device tensor"):
+            preft.preft_direft_apply_layers([t], i64, i32, i32, i32, i64, i64, None, 2, 4, 1.0, 0, ws)
+        with pytest.raises(ValueError, match="seg_start"):
+            preft.preft_schedule(ws, i32, i32, i32, 4, 2, 0)
     with pytest.raises(TypeError):
         native.bind(1, 2)
 
