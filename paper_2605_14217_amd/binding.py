@@ -155,11 +155,16 @@ def load_library(path: Optional[str] = None):
 def _load_marshal(lib):
     if not os.path.exists(os.path.join(_HERE, "_marshal.so")):
         return None
+    from .build import built_for
     try:
         from . import _marshal
-    except ImportError as e:                                  # built against another torch
+        theirs = _marshal.built_for() if hasattr(_marshal, "built_for") else "an unknown torch"
+        why = None if theirs == built_for() else f"was built for {theirs}, this is {built_for()}"
+    except ImportError as e:                                  # another torch or Python, to which it does not even link
+        why = f"does not load ({e})"
+    if why:
         import warnings
-        warnings.warn(f"preft: _marshal.so does not load ({e}); rebuild with python -m paper_2605_14217_amd.build.  Calls are marshalled in Python.")
+        warnings.warn(f"preft: _marshal.so {why}; rebuild with python -m paper_2605_14217_amd.build.  Calls are marshalled in Python.")
         return None
     _marshal.bind(PoolRef, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
         lib.preft_schedule, lib.preft_lora_apply, lib.preft_lora_apply_packed, lib.preft_direft_apply, lib.preft_loreft_apply,

@@ -25,6 +25,14 @@ def sources():
     return [os.path.join(CSRC, "preft_api.hip"), os.path.join(CSRC, "slots.hip")] + groups
 
 
+def built_for() -> str:
+    """The torch and Python whose object layouts marshal.cpp compiles in: _marshal.so is used with these only."""
+    import sys
+
+    import torch
+    return f"torch {torch.__version__} {torch.version.git_version} python {sys.hexversion:x}"
+
+
 def marshal_command(out: str):
     """g++ line of the extension module (host code only, against this torch's headers)."""
     import sysconfig
@@ -32,7 +40,8 @@ def marshal_command(out: str):
     import torch
     from torch.utils.cpp_extension import include_paths
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DPREFT_BUILT_FOR="{built_for()}"']
     cmd += [f for d in include_paths() + [sysconfig.get_paths()["include"]] for f in ("-isystem", d)]
     return cmd + [os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
 

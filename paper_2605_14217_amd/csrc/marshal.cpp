@@ -288,7 +288,11 @@ PyObject *bind(PyObject *, PyObject *const *o, Py_ssize_t n)
     Py_RETURN_NONE;
 }
 
+// What it was compiled against (build.py): sizes, strides and addresses are read at that torch's and Python's offsets
+PyObject *built_for(PyObject *, PyObject *) { return PyUnicode_FromString(PREFT_BUILT_FOR); }
+
 PyMethodDef methods[] = {
+    {"built_for", built_for, METH_NOARGS, nullptr},
     {"bind", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(bind)), METH_FASTCALL, nullptr},
     {"schedule", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(schedule)), METH_FASTCALL, nullptr},
     {"lora", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(lora)), METH_FASTCALL, nullptr},

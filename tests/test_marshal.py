@@ -45,6 +45,15 @@ def test_what_is_no_ordinary_call_goes_through_the_binding(native):
         native.bind(1, 2)
 
 
+def test_a_module_built_for_another_torch_is_not_used(native, monkeypatch):
+    """It reads tensors at the offsets of the torch and Python that it was compiled against: any other pair goes without it."""
+    from paper_2605_14217_amd import build
+    assert native.built_for() == build.built_for() and torch.__version__ in native.built_for()
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + "x")
+    with pytest.warns(UserWarning, match="was built for"):
+        assert binding._load_marshal(binding._lib) is None
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_same_calls_as_the_python_path(native, dtype, monkeypatch):
