@@ -46,11 +46,33 @@ def marshal_command(out: str):
     return cmd + [os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
 
 
+def build_marshal(tmpdir: str) -> bool:
+    """Compile _marshal.so and put it in place.  The library does without it (calls go through ctypes): where g++, torch's headers or the
+    compilation fail, that is said, an older module is removed and the answer is False."""
+    import shutil
+    import warnings
+    try:
+        built = os.path.join(tmpdir, "_marshal.so")
+        proc = subprocess.run(marshal_command(built), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        why = proc.stdout[-4000:] if proc.returncode != 0 else None
+    except (OSError, ImportError, AttributeError) as e:
+        why = str(e)
+    if why is not None:
+        warnings.warn(f"_marshal.so is not built, calls will be marshalled in Python: {why}")
+        if os.path.exists(MARSHAL_PATH):
+            os.remove(MARSHAL_PATH)
+        return False
+    tmp = MARSHAL_PATH + f".{os.getpid()}.tmp"
+    shutil.copyfile(built, tmp)
+    os.chmod(tmp, 0o755)
+    os.replace(tmp, MARSHAL_PATH)
+    return True
+
+
 def build_library(verbose: bool = False) -> str:
     """Compile every HIP source (one hipcc per translation unit, in parallel) and link them into
-    paper_2605_14217_amd/libpreft.so; returns its path."""
+    paper_2605_14217_amd/libpreft.so; returns its path.  Beside it _marshal.so, where that can be built."""
     import concurrent.futures
-    import shutil
     import tempfile
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"]
@@ -67,19 +89,16 @@ def build_library(verbose: bool = False) -> str:
 
     with tempfile.TemporaryDirectory(prefix="preft_build_") as tmpdir:
         objects = [os.path.join(tmpdir, f"{i}_{os.path.basename(src)}.o") for i, src in enumerate(sources())]
-        commands = [marshal_command(os.path.join(tmpdir, "_marshal.so"))]
-        commands += [[hipcc] + compile_flags + ["-c", src, "-o", obj] for src, obj in zip(sources(), objects)]
+        commands = [[hipcc] + compile_flags + ["-c", src, "-o", obj] for src, obj in zip(sources(), objects)]
         with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as pool:
+            marshal = pool.submit(build_marshal, tmpdir)
             list(pool.map(run, commands))
+            marshal.result()
         tmp = LIB_PATH + f".{os.getpid()}.tmp"
         run([hipcc] + HIPCC_FLAGS + objects + ["-o", tmp])
-        marshal = MARSHAL_PATH + f".{os.getpid()}.tmp"
-        shutil.copyfile(os.path.join(tmpdir, "_marshal.so"), marshal)
-        os.chmod(marshal, 0o755)
     if verbose and messages:
         print("\n".join(messages))
     os.replace(tmp, LIB_PATH)
-    os.replace(marshal, MARSHAL_PATH)
     return LIB_PATH
 
 

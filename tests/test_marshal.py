@@ -1,5 +1,8 @@
 """csrc/marshal.cpp: it answers None to whatever is not an ordinary call (the binding's own path then says what is wrong), and what it
 takes ends as the same C call: same bits, same error codes, as with marshalling in Python."""
+import ctypes
+import shutil
+
 import numpy as np
 import pytest
 import torch
@@ -52,6 +55,26 @@ def test_a_module_built_for_another_torch_is_not_used(native, monkeypatch):
     monkeypatch.setattr(torch, "__version__", torch.__version__ + "x")
     with pytest.warns(UserWarning, match="was built for"):
         assert binding._load_marshal(binding._lib) is None
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+@pytest.mark.parametrize("command", [["/nonexistent/g++"], ["g++", "/nonexistent.cpp"], None], ids=["no compiler", "does not compile", "no torch headers"])
+def test_the_library_is_built_without_the_module(command, tmp_path, monkeypatch):
+    """What keeps _marshal.so from being built keeps neither libpreft.so from it nor an older module in place."""
+    from paper_2605_14217_amd import build
+    src = tmp_path / "one.hip"
+    src.write_text('#include <hip/hip_runtime.h>\nextern "C" int one() { return 1; }\n')
+
+    def no_headers(out):
+        raise ImportError("torch.utils.cpp_extension")
+    monkeypatch.setattr(build, "sources", lambda: [str(src)])
+    monkeypatch.setattr(build, "LIB_PATH", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(build, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+    monkeypatch.setattr(build, "marshal_command", no_headers if command is None else lambda out: command)
+    (tmp_path / "_marshal.so").write_text("older")
+    with pytest.warns(UserWarning, match="not built"):
+        assert build.build_library() == str(tmp_path / "lib.so")
+    assert ctypes.CDLL(str(tmp_path / "lib.so")).one() == 1 and not (tmp_path / "_marshal.so").exists()
 
 
 @pytest.mark.gpu
