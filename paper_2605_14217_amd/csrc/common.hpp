@@ -180,7 +180,8 @@ __device__ __forceinline__ WholeZ whole_z(const float (&z)[4])
     }
     return w;
 }
-// two bf16 factors, infinite and NaN ones as zeros: what meets the parts of z below its head, whose product with the factor they would turn into NaN
+// two bf16 factors, infinite and NaN ones as zeros: what meets the parts of z below its head, whose product with such a factor makes NaN of what the head's
+// makes an infinity
 __device__ __forceinline__ uint32_t finite_only(uint32_t two)
 {
     const uint32_t special = ((two & 0x7f807f80u) + 0x00800080u) & 0x80008000u;      // the top bit of each whose exponent is all ones

@@ -52,9 +52,9 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(u32x4_t v) { return __builtin_bit_
 __device__ __forceinline__ u32x4_t as_u32x4(bf16x8_t v) { return __builtin_bit_cast(u32x4_t, v); }
 
 // Ranks above 16 that are no multiple of 4: the products of a column group's factors with z, whole (whole_z).  The factors meet head and middle
-// part in one MFMA per rank block, the lowest parts of two blocks in one more.  FINITE: infinite and NaN factors meet the head
-// alone (inf times a lower part of the other sign, or zero, is NaN where inf times z is inf).  That costs seven instructions for every two
-// factors, so a unit is computed without it first and again only where a result is NaN.
+// part in one MFMA per rank block, the lowest parts of two blocks in one more.  FINITE: infinite and NaN factors meet the head alone.  That costs seven
+// instructions for every two factors, so a unit is computed without, and from memory again, four times in a loop, only where a result is NaN.  (The
+// two forms side by side, unrolled, cost the small-batch kernel 0.5 us of 6; one loop around one form spills what is hoisted out of it.)
 template <int NB, bool FINITE, typename W, typename Z, typename L>
 __device__ __forceinline__ f32x4_t whole_z_products(W factors, Z z, L low)
 {
@@ -112,8 +112,8 @@ constexpr int mfma_min_waves(int NB, int MB, int WAVES, int HUNITS)
 // first two units are requested before the reduction of z and the next ones while a unit is finished.
 // ODD = 1 (rank > 16): the same ranks above 16 (17, 18, 19, 21, ...), whatever the widths: a lane's four factors of a column are one
 // 8-byte load from wherever they start (quad_from), which the texture path takes a few cycles longer for.  They keep all 24 bits of z
-// (whole_z), as the per-row kernels do that these calls took before: an MFMA per two rank blocks more, 0 to 4 % (rank 63, 1000 -> 2728, 11 700 rows 132 -> 137 us, 4096 ->
-// 4096, 900 rows 37.4 -> 37.9; rank 31 in place, d = 4096, 11 700 rows 62.4 -> 62.7; rank 18, 8192, 2200 rows 45.2 -> 47.5).
+// (whole_z), as the per-row kernels do that these calls took before: an MFMA per two rank blocks more, 0 to 5 % (rank 63, 1000 -> 2728, 11 700 rows 132 -> 138 us; rank 127,
+// 4096 -> 4096, 660 rows 44.5 -> 44.7; rank 31, 488 -> 4096 + 512, 233 rows 5.9 -> 6.1; in place, rank 18, 8192, 2200 rows 45.2 -> 46.8).
 //
 // ZOUT: the shrink sweep alone.  z goes to the workspace in the form the expand's MFMAs take it, 1 KB per
 // 16-row block and rank block, and mfma_expand_kernel does the expand in a second launch.
@@ -525,8 +525,8 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
     const int64_t w_step = (int64_t)32 * r * 2;               // bytes per 32 output columns
 
     // out = y + delta for one 32-column step and one row block; y and the result in MFMA order
-    // (finite_tag: whole_z_products; `nan` tells whether a result is NaN, ranks above 16 that are no multiple of 4 only)
-    auto expand_step = [&](const u32x4_t yv, const u32x2_t (&wv)[2][NB], int mb, auto finite_tag, bool &nan) -> u32x4_t {
+    // (WHOLE only: `nan`, whether a result is NaN; finite_tag as in whole_z_products)
+    auto expand_step = [&](const u32x4_t yv, const u32x2_t (&wv)[2][NB], int mb, bool &nan, auto finite_tag) -> u32x4_t {
         float out[8];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
@@ -597,22 +597,37 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
             for (int i = 0; i < ODD; ++i)
                 if (lane + 64 * i < 16 * r) tra[lane + 64 * i] = wb[i];
         }
-        auto columns = [&](auto finite_tag) {
-            bool nan = false;
+        bool nan = false;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                u32x2_t wv[2][NB];
-                w_operands(wb, s, wv);
+        for (int s = 0; s < 4; ++s) {
+            u32x2_t wv[2][NB];
+            w_operands(wb, s, wv);
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    const u32x4_t yv = yop[mb][s];
-                    tr[(mb * 16 + rl) * MFMA_TRS + 4 * s + g] = expand_step(yv, wv, mb, finite_tag, nan);
+            for (int mb = 0; mb < MB; ++mb) {
+                const u32x4_t yv = yop[mb][s];
+                tr[(mb * 16 + rl) * MFMA_TRS + 4 * s + g] = expand_step(yv, wv, mb, nan, std::false_type{});
+            }
+        }
+        if constexpr (WHOLE) {
+            if (__any(nan)) {
+                u32x4_t raw[MB][4], op[MB][4];
+                load_y_unit(raw, u);
+                unit_to_mfma(raw, op);                        // leaves the unit in the turn buffer
+#pragma unroll 1
+                for (int s = 0; s < 4; ++s) {
+                    u32x2_t wv[2][NB];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) wv[e][b] = quad_from(ld8_any(bp[e][b] + (c_unit(u) * 4 + s) * w_step), 16 * b + 4 * g, r);
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) {
+                        u32x4_t &place = tr[(mb * 16 + rl) * MFMA_TRS + 4 * s + g];
+                        place = expand_step(place, wv, mb, nan, std::true_type{});
+                    }
                 }
             }
-            return nan;
-        };
-        const bool nan = columns(std::false_type{});
-        if constexpr (WHOLE) { if (__any(nan)) columns(std::true_type{}); }
+        }
         const int64_t off = (int64_t)c_unit(u) * 256;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
@@ -713,8 +728,8 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             bool nan = false;
-            u32x4_t out = expand_step(yv[mb], wv, mb, std::false_type{}, nan);
-            if constexpr (WHOLE) { if (__any(nan)) out = expand_step(yv[mb], wv, mb, std::true_type{}, nan); }
+            u32x4_t out = expand_step(yv[mb], wv, mb, nan, std::false_type{});
+            if constexpr (WHOLE) { if (__any(nan)) out = expand_step(yv[mb], wv, mb, nan, std::true_type{}); }
             const u32x4_t o = mfma_to_step(out);
             if (col_ok) st16_stream(ys[mb] + off, o);
         }

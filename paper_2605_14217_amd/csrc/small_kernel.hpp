@@ -235,6 +235,38 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     const uint32_t odd_shift = (odd_at & 1) * 16;
     const uint32_t odd_m01 = odd_n >= 2 ? 0xffffffffu : odd_n == 1 ? 0xffffu : 0u;
     const uint32_t odd_m23 = odd_n >= 4 ? 0xffffffffu : odd_n == 3 ? 0xffffu : 0u;
+    // y plus the products of step s, in MFMA order (ANY only: `nan`, whether a result is NaN; finite_tag as in whole_z_products)
+    auto products = [&](const u32x4_t y, const u32x2_t (&wv)[2][NB], int s, bool &nan, auto finite_tag) -> u32x4_t {
+        float out[8];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            f32x4_t d = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (ANY) {
+                d = whole_z_products<NB, decltype(finite_tag)::value>([&](int b) { return quad_from(wv[e][b], 16 * b + 4 * g, r); },
+                                                                      [&](int b) { return zop[b]; }, [&](int i) { return zlow[i]; });
+                nan = nan || __builtin_isunordered(d[0], d[1]) || __builtin_isunordered(d[2], d[3]);
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    u32x2_t w;
+                    if constexpr (PARKED) {
+                        const uint32_t *w3 = odd_words + (16 * s + 2 * e) * r;
+                        const uint32_t d0 = w3[0], d1 = w3[1], d2 = w3[2];
+                        w = u32x2_t{__builtin_amdgcn_alignbit(d1, d0, odd_shift) & odd_m01, __builtin_amdgcn_alignbit(d2, d1, odd_shift) & odd_m23};
+                    } else {
+                        w = wv[e][b];
+                    }
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), zop[b], d, 0, 0, 0);
+                }
+            }
+            const uint32_t y01 = y[2 * e], y23 = y[2 * e + 1];
+            out[4 * e + 0] = bf16_lo(y01) + d[0];
+            out[4 * e + 1] = bf16_hi(y01) + d[1];
+            out[4 * e + 2] = bf16_lo(y23) + d[2];
+            out[4 * e + 3] = bf16_hi(y23) + d[3];
+        }
+        return Elem<bf16_tag>::pack(out);
+    };
     auto finish = [&](int k, int u) {
         u32x4_t yo[4];
 #pragma unroll
@@ -246,50 +278,26 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             for (int j = 0; j < PIECES; ++j)
                 if (lane + 64 * j < 16 * r) tra[lane + 64 * j] = Wb[k][j];
         }
-        // FINITE (ANY only): infinite and NaN factors meet the head of z alone.  Tells whether a result is NaN
-        auto columns = [&](auto finite_tag) {
-        constexpr bool FINITE = decltype(finite_tag)::value;
         bool nan = false;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             if constexpr (W_LATE) load_w(W[0][0], u, s);
-            float out[8];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                f32x4_t d = {0.f, 0.f, 0.f, 0.f};
-                if constexpr (ANY) {
-                    d = whole_z_products<NB, FINITE>([&](int b) { return quad_from(W[k][W_LATE ? 0 : s][e][b], 16 * b + 4 * g, r); },
-                                                     [&](int b) { return zop[b]; }, [&](int i) { return zlow[i]; });
-                    nan = nan || __builtin_isunordered(d[0], d[1]) || __builtin_isunordered(d[2], d[3]);
-                } else {
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    u32x2_t w;
-                    if constexpr (PARKED) {
-                        const uint32_t *w3 = odd_words + (16 * s + 2 * e) * r;
-                        const uint32_t d0 = w3[0], d1 = w3[1], d2 = w3[2];
-                        w = u32x2_t{__builtin_amdgcn_alignbit(d1, d0, odd_shift) & odd_m01, __builtin_amdgcn_alignbit(d2, d1, odd_shift) & odd_m23};
-                    } else {
-                        w = W[k][W_LATE ? 0 : s][e][b];
-                    }
-                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), zop[b], d, 0, 0, 0);
-                }
-                }
-                const uint32_t y01 = yo[s][2 * e], y23 = yo[s][2 * e + 1];
-                out[4 * e + 0] = bf16_lo(y01) + d[0];
-                out[4 * e + 1] = bf16_hi(y01) + d[1];
-                out[4 * e + 2] = bf16_lo(y23) + d[2];
-                out[4 * e + 3] = bf16_hi(y23) + d[3];
-            }
-            tr[rl * MFMA_TRS + 4 * s + g] = Elem<bf16_tag>::pack(out);
-        }
-        return nan;
-        };
-        const bool nan = columns(std::false_type{});
-        if constexpr (ANY) {                                  // (rows that do not exist may hold anything)
-            if (__any(nan && rl < n_rows)) columns(std::true_type{});
+            tr[rl * MFMA_TRS + 4 * s + g] = products(yo[s], W[k][W_LATE ? 0 : s], s, nan, std::false_type{});
         }
         const int off = u * 256 + c16 * 16;
+        if constexpr (ANY) {
+            if (__any(nan && rl < n_rows)) {                  // (rows that do not exist may hold anything)
+#pragma unroll
+                for (int i = 0; i < NG; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = ld16(yu[i] + min(off, y_last));
+#pragma unroll 1
+                for (int s = 0; s < 4; ++s) {
+                    u32x2_t w[2][NB];
+                    load_w(w, u, s);
+                    u32x4_t &place = tr[rl * MFMA_TRS + 4 * s + g];
+                    place = products(place, w, s, nan, std::true_type{});
+                }
+            }
+        }
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
             const u32x4_t v = tr[(4 * i + q) * MFMA_TRS + c16];
