@@ -341,7 +341,8 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallL
     __shared__ u32x4_t turn[WAVES][2][16 * MFMA_TRS];         // activations, and the factor
     __shared__ float red[WAVES * NB * 4 * 64];
 
-    // What the launch arguments say is asked for together with the header: each line of them that is touched later is a trip of its own.
+    // What the launch arguments say is asked for together with the header: each line of them that is touched later is a trip of its own (in
+    // place, rank 16, d = 512, 220 rows 4.4 us without, 4.3 with).
     SmallOutput o = {p.y, p.ldy, p.d_out, 0, p.A_pool, p.Bt_pool};
     if constexpr (!DIREFT) {
         o.share = blockIdx.x >> 3;
@@ -353,6 +354,7 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallL
         }
     }
     if constexpr (!DIREFT) asm volatile("" ::"s"(o.y), "s"(o.d_out), "s"(o.A_pool), "s"(o.Bt_pool), "s"(p.x), "s"(p.gtiles), "s"(p.chunks), "s"(p.shorts), "s"(p.rank));
+    else asm volatile("" ::"s"(p.rank), "s"(p.d_out), "s"(p.col_split));
     if (!schedule_matches(p)) return;
     int n_chunk_units;
     const int n_units = tile_units<16>(p, &n_chunk_units);
@@ -374,6 +376,9 @@ __global__ __launch_bounds__(WAVES * 64, DEEP ? 2 : 4) void small_tile_kernel(Ap
 template <int NB, bool ODD, bool FEW>
 __global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(ApplyArgs p, SmallLaunch l)
 {
+    // beside the layer's pointers, not after them (8 layers, d = 512, 220 rows 7.7 us, now 7.3; 4 layers, d = 1024, 600 rows 7.4 / 7.1)
+    // (above rank 32 there are no registers for that: 8 layers, rank 64, d = 1024, 400 rows 21.9 / 24.2)
+    if constexpr (NB <= 2) asm volatile("" ::"s"(p.rank), "s"(p.d_out), "s"(p.col_split), "s"(p.header), "s"(p.T));
     select_layer(p);
     small_tile_body<NB, true, ODD, true, SMALL_WAVES, FEW>(p, l);
 }
