@@ -127,7 +127,15 @@ __device__ __forceinline__ bool expand_tile(const ApplyArgs &p, const ExpandTile
     return true;
 }
 
-template <int NB, int MB, bool ODD>
+// Of an output whose rows do not start on 128-byte lines, the lines at the ends of a row's 256-byte pieces are asked for by two wavefronts or panels: with
+// the non-temporal hint they are fetched twice.  So y comes without it there, with it elsewhere (YHINT: no such output; only such; some: a test per tile,
+// fenced in, or the compiler makes one of the two loads, without the hint).  Hint / none, whole calls, us: rank 16, 4096 -> 9640, 1400 rows 25.1 / 21.1, 5000 62 /
+// 47, 45 000 457 / 403; rank 8, 1024 -> 5336, 2400 rows 20.6 / 17.4; rank 7, 1000 -> 2 x 2728, 2150 rows 24.9 / 22.1; on lines, 4096 -> 4096, 37 000
+// rows 152 / 170.  Some: 1024 -> 8192 + 616 (off) + 14336, 5000 rows, hint / none / by output 94 / 104 / 86, 43 000 rows 756 / 808 / 733.
+__host__ __device__ __forceinline__ bool shares_lines(const void *y, int64_t ldy_b) { return ((reinterpret_cast<uintptr_t>(y) | (uintptr_t)ldy_b) & 127) != 0; }
+enum class YHint { All, None, ByOutput };
+
+template <int NB, int MB, bool ODD, YHint YHINT>
 __global__ __launch_bounds__(EXPAND_WAVES * 64, 4) void mfma_expand_kernel(ApplyArgs p, int n_slices)
 {
     constexpr int R = 16 * MB;
@@ -196,10 +204,21 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 4) void mfma_expand_kernel(Apply
             for (int b = 0; b < NB; ++b) zop[mb][b] = as_bf16x8(ld16(zb + b * 1024));
         }
         u32x4_t Y[MB][4];
+        auto load_y = [&](auto load) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) Y[mb][v] = ld16_stream(yp[mb][v]);
+                for (int v = 0; v < 4; ++v) Y[mb][v] = load(yp[mb][v]);
+        };
+        if constexpr (YHINT == YHint::None) {
+            load_y([](gptr_t a) { return ld16(a); });
+        } else if (YHINT == YHint::ByOutput && shares_lines(t.y, ldy_b)) {
+            asm volatile("" ::: "memory");
+            load_y([](gptr_t a) { return ld16(a); });
+            asm volatile("" ::: "memory");
+        } else {
+            load_y([](gptr_t a) { return ld16_stream(a); });
+        }
 
 #pragma unroll
         for (int j = 0; j < 4 * NB; ++j) {

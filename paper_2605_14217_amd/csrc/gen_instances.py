@@ -1,6 +1,6 @@
 """Writes csrc/instances/: the kernel instantiations of libpreft.so spread over several translation units.
 
-preft_api.hip uses some 330 instantiations of the tile kernels; in one translation unit that is minutes
+preft_api.hip uses some 340 instantiations of the tile kernels; in one translation unit that is minutes
 of compile time.  This script asks the compiler which instantiations preft_api.hip needs (its
 kernel-resource-usage remarks, with the extern declarations switched off), deals them out to a few
 instances/group_<k>.hip files as explicit instantiations, and lists them all in

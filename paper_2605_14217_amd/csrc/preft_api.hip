@@ -275,43 +275,49 @@ inline bool expand_ids_fit(const ApplyArgs &a, int64_t S, int n_slices)
     return tiles < ((int64_t)1 << 31);
 }
 
-// Rows that do not start on 128-byte lines: neighbouring panels share lines, so they go to one XCD.
-bool rows_off_lines(const ApplyArgs &a, int n_slices)
+// Columns of outputs whose rows do not start on 128-byte lines: neighbouring panels of those share lines.
+int64_t columns_off_lines(const ApplyArgs &a, int n_slices)
 {
-    bool off = ((reinterpret_cast<uintptr_t>(a.y) | (uintptr_t)(a.ldy * 2)) & 127) != 0;
-    for (int i = 1; i < n_slices; ++i) off = off || ((reinterpret_cast<uintptr_t>(a.more[i - 1].y) | (uintptr_t)(a.more[i - 1].ldy * 2)) & 127) != 0;
+    int64_t off = shares_lines(a.y, a.ldy * 2) ? a.d_out : 0;
+    for (int i = 1; i < n_slices; ++i) off += shares_lines(a.more[i - 1].y, a.more[i - 1].ldy * 2) ? a.more[i - 1].d_out : 0;
     return off;
 }
+bool rows_off_lines(const ApplyArgs &a, int n_slices) { return columns_off_lines(a, n_slices) > 0; }
 
 // the shrink launch of rank 17-64 keeps byte offsets within a 64-row tile of x and within a factor in 32 bits
 inline bool offsets_fit(const ApplyArgs &a) { return a.rank <= 16 || (a.ldx <= (1 << 22) && a.d_in <= (1 << 22)); }
 
 // a workgroup of four wavefronts for every tile of `height` rows x `cols` columns
 void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S, int n_slices, hipStream_t stream,
-                          int height = 16 * EXPAND_MB, int cols = EXPAND_WAVES * 128, int threads = EXPAND_WAVES * 64, int off_lines_lds = 0)
+                          int height = 16 * EXPAND_MB, int cols = EXPAND_WAVES * 128, int threads = EXPAND_WAVES * 64)
 {
-    a.xcd_runs = rows_off_lines(a, n_slices);
-    const int idle_lds = a.xcd_runs ? off_lines_lds : 0;       // keeps workgroups off a compute unit
+    // Panels that share lines go to one XCD, from an eighth of the columns on (rank 8, 5000 rows, 1024 -> 5336, runs / memory order 26.3 / 29.4 us, 8192 on lines and
+    // 2056 off 42.8 / 45.2, 8192 + 14336 on and 616 off 104 / 98, 2500 rows 58.5 / 52.0)
+    int64_t all = a.d_out;
+    for (int i = 1; i < n_slices; ++i) all += a.more[i - 1].d_out;
+    a.xcd_runs = 8 * columns_off_lines(a, n_slices) >= all;
     // More tiles than the likely rows fill are likely to be empty, and an empty workgroup is not free (3584 decode rows, prompt
     // positions, 8192 -> 2 x 28672: 22 848 of them 23 us): the kernel strides over what exceeds the grid (and over what would
     // exceed the 2^32 work items of a launch)
     const int64_t rows = a.all_tokens && !a.chunks_only ? a.T : prompt_rows(a, S);
     const int64_t bound = tile_grid(a, S, height), likely = rows / height * 5 / 4 + (rows / 8 < 64 ? rows / 8 + 1 : 64);
     const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices, cols), most = (int64_t)1 << 23;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(threads), idle_lds, stream, a, n_slices);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(threads), 0, stream, a, n_slices);
 }
 
 template <int NB, bool ODD>
 void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
 {
     if constexpr (NB <= 2) {
-        // Rows off 128-byte lines share lines between panels, and those of a fourth workgroup on the compute unit are one window too many (as
-        // at rank 17-32, where the factors leave room for three).  Four / three / two, us: rank 16, 4096 -> 9640, 69 000 rows 714 / 679 / 758, rank 8,
-        // 4096 -> 5336, 16 600 rows 112 / 107 / 121; on lines 4096 -> 4096, 37 000 rows 152.4 / 153.2 / 200, 4096 -> 2 x 14336, 4600 rows 107.0 / 107.7 / 144.
-        constexpr int THREE = 16384;                          // 25 KB and this
-        static_assert(NB > 1 || (3 * (EXPAND_WAVES * FactorLds<1>::BYTES + THREE) <= 160 * 1024 && 4 * (EXPAND_WAVES * FactorLds<1>::BYTES + THREE) > 160 * 1024), "three workgroups");
-        launch_expand_kernel(mfma_expand_kernel<NB, EXPAND_MB, ODD>, a, S, n_slices, stream, 16 * EXPAND_MB, EXPAND_WAVES * 128, EXPAND_WAVES * 64,
-                             NB == 1 ? THREE : 0);
+        void (*kernel)(ApplyArgs, int) = mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::All>;
+        if constexpr (NB == 1) {                              // (above rank 16 rows are off lines by their pitch only)
+            int64_t on = a.d_out;
+            for (int i = 1; i < n_slices; ++i) on += a.more[i - 1].d_out;
+            const int64_t off = columns_off_lines(a, n_slices);
+            on -= off;
+            if (off > 0) kernel = on > 0 ? mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::ByOutput> : mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::None>;
+        }
+        launch_expand_kernel(kernel, a, S, n_slices, stream);
     } else {
         const int pu = panel_units(a, n_slices);
         launch_expand_kernel(pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD> : panel_expand_kernel<NB, PANEL_RW, 1, ODD>, a, S, n_slices,
