@@ -158,21 +158,27 @@ inline SmallShape small_shape(const ApplyArgs &a, int64_t S, int n_slices, const
 }
 
 // Whether an in-place call of rank 17-31, no multiple of 4, takes 32-row tiles of the column-split kernel instead of 64-row tiles of the
-// row-split one, as the multiples of 4 always do: twice as many tiles, and their second read of h follows the first sooner.  But the large batches
-// of narrow rows find that read in the caches either way, and some ranks' unaligned factors cost the texture path more (21 and 31 of those measured).
-// Row-split / column-split, us: 2300 rows, d = 1024 / 4096 / 8192, rank 18 18.6 / 9.7, 64 / 27, 123 / 47, rank 31 18.8 / 11.6, 65 / 33, 126 / 60;
-// 14 000 rows, d = 512, rank 31 16.0 / 12.6, 8192, rank 29 154 / 117; 35 000 rows, rank 31, d = 512 25 / 30, 2048 89 / 86, 3072 130 / 135, 4096 187 / 178,
-// 8192 391 / 367; 90 000 rows, rank 19, d = 1024 87 / 102, 8192 855 / 693, rank 21 2048 190 / 208, 8192 848 / 793, rank 31 4096 400 / 406, 8192 867 / 823.
-inline bool odd_streams_in_place(const ApplyArgs &a)
+// row-split one, as the multiples of 4 always do: twice as many tiles, and their second read of h follows the first sooner.  But large batches
+// of narrow rows find that read in the caches either way; prompts of a few dozen rows fill 32-row tiles no better and read an adapter's factors for
+// twice as many of them; and ranks 21 and 31 have the texture path busy with their unaligned factors as soon as the tiles fill the chip (each rank
+// was measured: 17-30 differ by a few percent, those two by 20 more).  A layer takes the kernel of its one-layer call, so the line is drawn where several layers
+// lose little.  Row-split / column-split, us: 1500 rows, d = 1024 / 4096 / 8192, rank 18 18.1 / 9.7, 62 / 26, 116 / 45, rank 31 18.3 / 11.2, 64 / 32, 121 / 56;
+// 12 000 rows, d = 8192, rank 29 147 / 113, 31 147 / 128; 29 000 rows, 8192, rank 18 267 / 250, 23 276 / 265, 29 263 / 265, 31 268 / 289; 12 000 rows of prompts of
+// 40, d = 4096, rank 18 109 / 98, 23 110 / 111, 31 115 / 139, d = 1024, 19 32 / 35, 31 33 / 41; several layers of d = 4096: 2 x 5300 rows of short prompts, rank 18
+// 90 / 82, 23 91 / 92, 31 94 / 114, 4 x 5000, 18 99 / 94, 23 101 / 101, 31 100 / 117, 4 x 2000, 23 69 / 52, 31 69 / 62.  35 000 rows, d = 512, rank 31 25 / 30, 2048 89 / 86.
+inline bool odd_streams_in_place(const ApplyArgs &a, int64_t S)
 {
     if (!column_split_fits(a)) return false;
+    const bool short_prompts = a.T < 64 * S;
+    if (a.rank == 21 || a.rank == 31) return a.T <= 2048 && !short_prompts;
+    if (short_prompts && a.T > 8192 && a.d_in < 2048) return false;
     return a.T <= 16384 || a.d_in >= 8192 || (a.d_in >= 4096 && a.T <= 49152);
 }
 
 // Ranks above 16 that are no multiple of 4: whether the column-split kernel takes the whole call, chunks and gathered tiles.
-inline bool odd_streams(const ApplyArgs &a, bool direft, const Knobs &k)
+inline bool odd_streams(const ApplyArgs &a, int64_t S, bool direft, const Knobs &k)
 {
-    return !wide_widths_ok(a, 1) || k.variant == 3 || (direft && a.rank <= 32 && k.variant == 0 && odd_streams_in_place(a));
+    return !wide_widths_ok(a, 1) || k.variant == 3 || (direft && a.rank <= 32 && k.variant == 0 && odd_streams_in_place(a, S));
 }
 
 }  // namespace preft

@@ -654,7 +654,7 @@ void launch_mfma_odd(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t 
 template <int NB, bool DIREFT>
 void launch_mfma_odd_wide(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t stream)
 {
-    if (odd_streams(a, DIREFT, k)) {
+    if (odd_streams(a, S, DIREFT, k)) {
         launch_mfma_odd_stream<NB, DIREFT>(a, S, 2, stream);
         return;
     }

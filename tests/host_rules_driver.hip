@@ -5,7 +5,7 @@
 //   piece COLUMNS MOST RANK    last_factor_piece
 //   small T S N ALL RANK D_IN D0 D1 D2   whether a LoRA call with these outputs (0: none) takes the small-batch kernel, and as what:
 //                              units of a share, deep, wavefronts, units of the launch
-//   route T RANK D_IN D_OUT DIREFT   what takes a bf16 call above 1024 rows: whether the matrix-core kernels do; whether the column-split kernel
+//   route T S RANK D_IN D_OUT DIREFT   what takes a bf16 call above 1024 rows: whether the matrix-core kernels do; whether the column-split kernel
 //                              then takes the chunks of a rank above 16 that is no multiple of 4; and whether it fits
 #include "../paper_2605_14217_amd/csrc/dispatch.hpp"
 
@@ -32,12 +32,12 @@ int main()
             continue;
         }
         if (!std::strcmp(what, "route")) {
-            for (int i = 0; i < 5; ++i)
+            for (int i = 0; i < 6; ++i)
                 if (std::scanf("%lld", &a[i]) != 1) return 1;
             preft::ApplyArgs p = {};
-            p.T = (int)a[0]; p.rank = (int)a[1]; p.d_in = (int)a[2]; p.d_out = (int)a[3];
+            p.T = (int)a[0]; p.rank = (int)a[2]; p.d_in = (int)a[3]; p.d_out = (int)a[4];
             const preft::Knobs k = {};
-            std::printf("%d %d %d\n", preft::mfma_takes(p, k), preft::odd_streams(p, a[4] != 0, k), preft::column_split_fits(p));
+            std::printf("%d %d %d\n", preft::mfma_takes(p, k), preft::odd_streams(p, a[1], a[5] != 0, k), preft::column_split_fits(p));
             continue;
         }
         if (std::scanf("%lld %lld %lld", &a[0], &a[1], &a[2]) != 3) return 1;

@@ -1,6 +1,8 @@
 """Ranks above 16 that are no multiple of 4, on widths that are multiples of 128 and on others: the small-batch kernel (up to 1024 rows), the
 column-split kernel (chunks and gathered tiles of 32 and 16 rows), packed and in place, one layer and several.  Against the oracle
 (parity_util's bars), and the last rank's factors to a value: an integer check that no neighbouring column's factor gets in."""
+import shutil
+
 import numpy as np
 import pytest
 import torch
@@ -77,16 +79,19 @@ def test_every_rank_meets_its_own_factor(rank, d, d_out, rows):
     assert torch.equal(y, B.t()[torch.arange(rows, device="cuda") % rank])
 
 
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="asks the dispatch through hipcc")
 @pytest.mark.parametrize("rank,d", [(17, 128), (18, 4096), (30, 2048), (31, 1024)])
-def test_in_place_on_widths_that_are_multiples_of_128(rank, d):
-    """Rank 17-31 in place: the column-split kernel up to 16 384 rows and on wide rows, the row-split kernel beyond, which the test flags
-    choose as well; both against the oracle on the same rows, and the default call one of the two to the bit."""
+def test_in_place_on_widths_that_are_multiples_of_128(rank, d, tmp_path_factory):
+    """Rank 17-31 in place: the column-split and the row-split kernel, which the test flags choose; both against the oracle on the same rows, and
+    the default call the one that the dispatch names, to the bit: short prompts, long ones, and a batch above 16 384 rows."""
     from oracle import preft_oracle as ora
     from paper_2605_14217_amd import binding as B
     from parity_util import bits, compare, dev_tables, direft_pools_to_device
+    from test_host_rules import ask
     N = 4
-    for T_prompts in ([700, 600], [700, 600] + [5100] * 3):
-        lens = np.array([1, 15, 16, 17, 33, 5, 4, 129] + T_prompts + [1] * 20)
+    seen = set()
+    for lens in ([1, 15, 16, 17, 33, 5, 4, 129, 700, 600] + [1] * 20, [17, 129, 700, 600], [1, 15, 16, 17, 33, 5, 4, 129, 700, 600] + [5100] * 3 + [1] * 20):
+        lens = np.array(lens)
         tab = wl.from_lengths(lens, np.random.Generator(np.random.PCG64(rank)).integers(-1, N + 1, size=len(lens)), np.where(lens > 1, lens, 0))
         ss, sa, sp = dev_tables(tab)
         tables = (tab.seg_start, tab.seg_adapter, tab.seg_prefill_len)
@@ -103,7 +108,8 @@ def test_in_place_on_widths_that_are_multiples_of_128(rank, d):
             finally:
                 B.set_test_flags(prev)
             got[variant] = h
-        streams = tab.T <= 16384 or d >= 4096                   # and these are fewer than 49 152
+        streams = int(ask(tmp_path_factory, [f"route {tab.T} {tab.S} {rank} {d} {d} 1"])[0].split()[1])
+        seen.add(streams)
         assert torch.equal(bits(got[0]), bits(got[3 if streams else 4]))
         if tab.T <= 16384:
             owner = ora.positions(tab.T, *tables, N, ora.ALL_POSITIONS)
@@ -112,6 +118,7 @@ def test_in_place_on_widths_that_are_multiples_of_128(rank, d):
                 compare(h, x, want, owner, "bf16")
         else:
             assert (got[3].float() - got[4].float()).abs().max() <= 2 ** -6 * got[4].float().abs().max()      # two bf16 roundings of the largest value
+    assert seen == ({1} if d >= 4096 else {0, 1})
 
 
 @pytest.mark.parametrize("rank,d,outs,lens,in_place", [(127, 8523264, (128,), [5, 1], False), (64, 17301504, (128,), [5, 1], False), (31, 35791488, (), [5], True),

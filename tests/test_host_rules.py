@@ -42,7 +42,7 @@ def test_the_column_split_kernel_takes_only_what_its_offsets_reach(tmp_path_fact
     cases = [(T, rank, d, d_out, direft) for rank in (4, 5, 15, 16, 17, 20, 31, 32, 33, 63, 64, 65, 127, 128) for d in widths
              for T in (8, 2000, 400000) for d_out, direft in ((128, 0), (d, 1))]
     reached = set()
-    for (T, rank, d, d_out, direft), got in zip(cases, ask(tmp_path_factory, [f"route {T} {r} {d} {o} {i}" for T, r, d, o, i in cases])):
+    for (T, rank, d, d_out, direft), got in zip(cases, ask(tmp_path_factory, [f"route {T} {1 + T // 600} {r} {d} {o} {i}" for T, r, d, o, i in cases])):
         takes, streams, fits = (int(v) for v in got.split())
         assert fits == (((rank - 1) * d + 120) * 2 < (1 << 31) - 15)         # 16 bytes from there on
         whole_units = d % 128 == 0 and d_out % 128 == 0
