@@ -34,12 +34,13 @@ constexpr int F32_WAVES = 8;
 constexpr int f32_red_bytes(int NB) { return F32_WAVES * NB * 4 * 64 * 4; }
 constexpr int f32_turn_bytes() { return F32_WAVES * 2 * 16 * MFMA_TRS * 16; }
 
-template <int NB, bool DIREFT, bool ODD>
+// BY_LDS (ranks up to 32 that are no multiple of 4): the expand takes z as its first operand and whole units of factors through LDS, see below.
+template <int NB, bool DIREFT, bool ODD, bool BY_LDS>
 __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
 {
     constexpr int WAVES = F32_WAVES;
     constexpr bool AHEAD = NB <= 2;                           // register budget: factors requested a unit ahead, or block by block
-    constexpr bool BY_LDS = ODD && NB <= 2;                   // expand: z the first operand, whole units of factors through LDS
+    static_assert(!BY_LDS || (ODD && NB <= 2), "ranks up to 32 that are no multiple of 4");
     static_assert(!BY_LDS || 64 * 16 * NB * 4 <= 2 * 16 * MFMA_TRS * 16, "a unit's factors fit the turn buffers");
     __shared__ __attribute__((aligned(16))) char lds[f32_red_bytes(NB) > f32_turn_bytes() ? f32_red_bytes(NB) : f32_turn_bytes()];
 
@@ -310,15 +311,15 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
     }
 }
 
-template <int NB, bool DIREFT, bool ODD>
-__global__ __launch_bounds__(F32_WAVES * 64) void f32_tile_kernel(ApplyArgs p) { f32_tile_body<NB, DIREFT, ODD>(p); }
+template <int NB, bool DIREFT, bool ODD, bool BY_LDS>
+__global__ __launch_bounds__(F32_WAVES * 64) void f32_tile_kernel(ApplyArgs p) { f32_tile_body<NB, DIREFT, ODD, BY_LDS>(p); }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer
 template <int NB, bool ODD>
 __global__ __launch_bounds__(F32_WAVES * 64) void f32_tile_layers_kernel(ApplyArgs p)
 {
     select_layer(p);
-    f32_tile_body<NB, true, ODD>(p);
+    f32_tile_body<NB, true, ODD, ODD && NB <= 2>(p);
 }
 
 }  // namespace preft

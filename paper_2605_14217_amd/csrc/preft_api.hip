@@ -799,12 +799,21 @@ bool f32_rows_win(const ApplyArgs &a, int64_t S, bool direft)
 template <int NB, bool DIREFT>
 void launch_f32_nb(const ApplyArgs &a, int64_t S, hipStream_t stream)
 {
+    constexpr bool BY_LDS = NB <= 2;
     void (*kernel)(ApplyArgs);
     if constexpr (DIREFT) {
         if (a.h_layers) kernel = (a.rank % 4) ? f32_tile_layers_kernel<NB, true> : f32_tile_layers_kernel<NB, false>;
-        else            kernel = (a.rank % 4) ? f32_tile_kernel<NB, true, true> : f32_tile_kernel<NB, true, false>;
+        else            kernel = (a.rank % 4) ? f32_tile_kernel<NB, true, true, BY_LDS> : f32_tile_kernel<NB, true, false, false>;
     } else {
-        kernel = (a.rank % 4) ? f32_tile_kernel<NB, false, true> : f32_tile_kernel<NB, false, false>;
+        kernel = (a.rank % 4) ? f32_tile_kernel<NB, false, true, BY_LDS> : f32_tile_kernel<NB, false, false, false>;
+        // A workgroup of one or two units of 64 columns has one or two wavefronts at work on them, and LDS is only a further step on their way; at
+        // rank 17-31, twice the factors, so is one unit for each of the eight.  Factors by LDS / lane by lane, 14 rows, us: rank 7, 512 -> 512 5.4 / 5.2, 1024 5.5 /
+        // 5.2, 4096 (8 units a workgroup) 6.0 / 6.8; rank 31, 512 7.2 / 6.5, 1024 7.3 / 6.6, 2104 -> 4096 14.3 / 14.0, 512 -> 4096 8.5 / 8.9; 1200 rows, rank 31, 2104 ->
+        // 512 15.0 / 14.7, 4096 (32 units) 25.4 / 26.6, rank 7 9.6 / 10.3, 17.7 / 20.2.
+        if constexpr (BY_LDS) {
+            const int units = (a.d_out + 63) / 64 / (a.col_split > 1 ? a.col_split : 1);
+            if (a.rank % 4 && units < (NB == 1 ? F32_WAVES / 2 : 2 * F32_WAVES)) kernel = f32_tile_kernel<NB, false, true, false>;
+        }
     }
     hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, 16), a.n_layers), dim3(F32_WAVES * 64), 0, stream, a);
 }

@@ -19,7 +19,8 @@ def _table(N):
 
 @pytest.mark.parametrize("colsplit", [0, 3])
 @pytest.mark.parametrize("rank,d_in,d_out", [(1, 68, 4), (4, 512, 512), (5, 1004, 700), (16, 4, 516), (17, 324, 64), (33, 512, 132),
-                                             (64, 196, 1000), (65, 128, 260), (127, 576, 68), (128, 64, 2052)])
+                                             (64, 196, 1000), (65, 128, 260), (127, 576, 68), (128, 64, 2052),
+                                             (7, 264, 1028), (15, 72, 260), (31, 132, 4100)])
 def test_lora(rank, d_in, d_out, colsplit):
     from parity_util import run_lora_case
     N = 4
@@ -45,3 +46,23 @@ def test_direft_and_layers(rank, d):
     for all_tokens in (False, True):
         run_direft_case(tab, pools[0], hs[0], "f32", 0.5, all_tokens, pad_cols=4, null_bias=(1,))
         run_direft_layers_case(tab, pools, hs, "f32", 0.5, all_tokens, [True, False], pad_cols=8)
+
+
+@pytest.mark.parametrize("rank,d_out", [(1, 516), (7, 1028), (13, 260), (18, 4100), (31, 2052)])
+def test_both_forms_of_the_expand_give_the_same_bits(rank, d_out):
+    """Ranks up to 32 that are no multiple of 4: factors through LDS where a workgroup has units enough, lane by lane where many share a tile."""
+    from parity_util import bits, dev_tables, lora_pools_to_device
+    tab = _table(4)
+    pool = wl.lora_pool(4, rank, 196, d_out, "f32", device="cuda", seed=rank)
+    A, B, keep = lora_pools_to_device(pool)
+    x, y0 = (wl.activations(tab.T, n, "f32", device="cuda", seed=n) for n in (196, d_out))
+    got = []
+    for colsplit in (1, 8):
+        y = y0.clone()
+        prev = preft.set_test_flags(preft.test_flags(colsplit=colsplit))
+        try:
+            preft.preft_lora_apply(y, x, *dev_tables(tab), A, B, rank, 2.0, preft.PREFT_ALL_TOKENS, preft.new_workspace(tab.T, tab.S))
+        finally:
+            preft.set_test_flags(prev)
+        got.append(y)
+    assert torch.equal(bits(got[0]), bits(got[1])) and not torch.equal(bits(got[0]), bits(y0))
