@@ -38,14 +38,34 @@ LORA = [
     # a workspace with room for z: on a batch of this size the call runs its sweeps as two launches
     ("llama8b_lora", "gate", 64, False, "dense", "z"), ("llama8b_lora", "o", 32, True, "dense", "z"),
     ("llama8b_lora", "down", 48, False, "dense", "z"),
-    # ... and on the larger batches as one, whatever the workspace
-    ("llama70b_lora", "down", 64, False, "dense", "z"),
+    # ... and so do the larger batches; on rows this wide the first launch takes tiles of 128 rows
+    ("llama70b_lora", "down", 64, False, "dense", "z"), ("llama70b_lora", "down", 63, False, "dense", "z"),
 ]
 
 
 def _pow2_pad(width):
     """Guard columns that bring a row to the next power of two: the row pitch bench.py uses by default."""
     return (1 << (width - 1).bit_length()) - width
+
+
+def _one_launch_agrees(y0s, x, tables, tab, pools, rank, scale, mode):
+    """The calls that a workspace with room for z runs as two launches (z appears in it) give the bits of the single launch."""
+    ss, sa, sp = tables
+    ws = preft.new_workspace(tab.T, tab.S, z_rank=rank, z_proj=len(y0s))
+    schedule = preft.new_workspace(tab.T, tab.S).numel()
+    results = []
+    for flags in (0, preft.test_flags(variant=5)):
+        ws.fill_(0xa5)
+        ys = [y0.clone() for y0 in y0s]
+        prev = preft.set_test_flags(flags)
+        try:
+            preft.preft_lora_apply_packed(ys, x, ss, sa, sp, [p[0] for p in pools], [p[1] for p in pools], rank, scale, mode, ws)
+        finally:
+            preft.set_test_flags(prev)
+        assert bool((ws[schedule:] != 0xa5).any()) == (flags == 0)
+        results.append(ys)
+    for two, one in zip(*results):
+        assert torch.equal(two.view(torch.int16), one.view(torch.int16))
 
 
 @pytest.mark.parametrize("case", LORA, ids=["-".join([c[0], c[1], f"r{c[2]}", "all" if c[3] else "prefill", *c[4:]])
@@ -65,6 +85,10 @@ def test_fullsize_lora(case):
     worst, counts = run_lora_case(tab, pool, x, y0, "bf16", cfg["lora_scale"], all_tokens, rows=rows,
                                   pad_x=0 if dense else _pow2_pad(d_in), pad_y=0 if dense else _pow2_pad(d_out),
                                   z_room=len(case) > 5)
+    if len(case) > 5:
+        from parity_util import dev_tables, lora_pools_to_device
+        _one_launch_agrees([y0], x, dev_tables(tab), tab, [lora_pools_to_device(pool)], rank, cfg["lora_scale"],
+                           preft.PREFT_ALL_TOKENS if all_tokens else preft.PREFT_PREFILL_ONLY)
     print(f"  T={tab.T} S={tab.S} rows checked={tab.T if rows is None else len(rows)} worst {worst:.2e} counts {counts}")
 
 
@@ -100,7 +124,9 @@ PACKED = [("llama8b_lora", ("q", "k", "v"), 16, False), ("llama8b_lora", ("gate"
           ("llama70b_lora", ("q", "k", "v"), 64, False, "dense"), ("llama70b_lora", ("gate", "up"), 64, False, "dense"),
           ("llama70b_lora", ("q", "k", "v"), 32, True, "dense"), ("llama70b_lora", ("gate", "up"), 64, True),
           # a workspace with room for z: two launches on a batch of this size
-          ("llama8b_lora", ("q", "k", "v"), 64, False, "dense", "z"), ("llama8b_lora", ("gate", "up"), 32, True, "dense", "z")]
+          ("llama8b_lora", ("q", "k", "v"), 64, False, "dense", "z"), ("llama8b_lora", ("gate", "up"), 32, True, "dense", "z"),
+          # ... whose first launch takes tiles of 128 rows for two outputs at rank 33-64
+          ("llama8b_lora", ("gate", "up"), 64, False, "dense", "z"), ("llama8b_lora", ("gate", "up"), 63, True, "dense", "z")]
 
 
 @pytest.mark.parametrize("case", PACKED,
@@ -144,6 +170,8 @@ def test_fullsize_packed_lora(case):
                         cfg["lora_scale"], pos, rows=rows, gathered=True)
         worst = max(worst, compare(ys[i], y0s[i], want, owner, "bf16", rows=rows))
         check_guards(bufs[i][0], tab.T, y0s[i].shape[1], 7.0)
+    if len(case) > 5:
+        _one_launch_agrees(y0s, x, (ss, sa, sp), tab, tables, rank, cfg["lora_scale"], mode)
     print(f"  T={tab.T} S={tab.S} rows checked={len(rows)} outputs={len(projs)} worst {worst:.2e}")
 
 
