@@ -135,7 +135,7 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
 {
     const unsigned tiles = likely_units(a, S);                // a multiple of 8 (col_split is 1 here)
     if constexpr (DIREFT) {
-        const bool few = a.all_tokens && prompt_rows(a, S) == 0;
+        const bool few = small_in_place_few(a, S);
         void (*kernel)(ApplyArgs, SmallLaunch) = few ? small_tile_kernel<NB, true, ODD, true> : small_tile_kernel<NB, true, ODD, true, SMALL_WAVES, false>;
         if (a.h_layers) kernel = few ? small_tile_layers_kernel<NB, ODD, true> : small_tile_layers_kernel<NB, ODD, false>;
         hipLaunchKernelGGL(kernel, dim3(tiles, a.n_layers), dim3(SMALL_WAVES * 64), 0, stream, a, SmallLaunch{1, 0});

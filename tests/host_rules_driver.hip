@@ -5,6 +5,7 @@
 //   piece COLUMNS MOST RANK    last_factor_piece
 //   small T S N ALL RANK D_IN D0 D1 D2   whether a LoRA call with these outputs (0: none) takes the small-batch kernel, and as what:
 //                              units of a share, deep, wavefronts, units of the launch
+//   in_place T S N ALL RANK D  whether an in-place call takes the small-batch kernel, and whether with quarter tiles (decode rows alone)
 //   route T S RANK D_IN D_OUT DIREFT   what takes a bf16 call above 1024 rows: whether the matrix-core kernels do; whether the column-split kernel
 //                              then takes the chunks of a rank above 16 that is no multiple of 4; and whether it fits
 #include "../paper_2605_14217_amd/csrc/dispatch.hpp"
@@ -29,6 +30,14 @@ int main()
             const preft::Knobs k = {};
             const preft::SmallShape s = preft::small_shape(p, a[1], n, k);
             std::printf("%d %d %d %d %u\n", preft::takes_small(p, a[1], widest, false, k), s.units, s.deep, s.waves, preft::likely_units(p, a[1]));
+            continue;
+        }
+        if (!std::strcmp(what, "in_place")) {
+            for (int i = 0; i < 6; ++i)
+                if (std::scanf("%lld", &a[i]) != 1) return 1;
+            preft::ApplyArgs p = {};
+            p.T = (int)a[0]; p.N = (int)a[2]; p.all_tokens = (int)a[3]; p.rank = (int)a[4]; p.d_in = p.d_out = (int)a[5]; p.n_layers = 1;
+            std::printf("%d %d\n", preft::takes_small(p, a[1], p.d_in, true, preft::Knobs{}), preft::small_in_place_few(p, a[1]));
             continue;
         }
         if (!std::strcmp(what, "route")) {

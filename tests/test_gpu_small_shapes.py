@@ -6,6 +6,7 @@ import shutil
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2605_14217_amd as preft
 from paper_2605_14217_amd import workloads as wl
@@ -58,8 +59,9 @@ def test_shape_against_the_oracle(tmp_path_factory, shape, rank, d_in, d_outs, d
 
 @pytest.mark.parametrize("rank,d,d_out", [(16, 512, 4096), (4, 136, 264), (7, 1000, 520), (32, 256, 1032), (64, 384, 512), (96, 128, 256)])
 def test_tiles_of_one_to_sixteen_rows(rank, d, d_out):
-    """Tiles of at most four rows load a quarter of what others do: gathered tiles of 1, 4, 5 and 16 rows and prompts that end 1, 4 and 5 rows
-    into a tile, out of place and in place, against the oracle; and the row's bits are those it has beside others in a tile."""
+    """Gathered tiles of 1, 4, 5 and 16 rows and prompts that end 1, 4 and 5 rows into a tile, out of place (where tiles of at most four rows load a
+    quarter of what others do) and in place beside prompts (where they do not), against the oracle; and the row's bits are those it has
+    beside others in a tile."""
     from oracle import preft_oracle as ora
     from parity_util import bits, compare, dev_tables, direft_pools_to_device, lora_pools_to_device
     counts, prompts = [1, 4, 5, 16], [17, 20, 21, 36]
@@ -94,3 +96,30 @@ def test_tiles_of_one_to_sixteen_rows(rank, d, d_out):
                                   ora.ALL_POSITIONS), owner, "bf16")
         rows[kind] = y, h
     assert bits(rows["own"][0]).equal(bits(rows["one"][0])) and bits(rows["own"][1]).equal(bits(rows["one"][1]))
+
+
+@pytest.mark.parametrize("rank,d", [(4, 4096), (4, 8192), (5, 2120), (7, 4104), (7, 8192), (16, 2760), (16, 8192), (16, 14336), (17, 1000), (24, 4096),
+                                    (24, 1000), (31, 1000), (31, 8192), (32, 4096), (33, 2056), (63, 1000), (63, 8192), (64, 4096), (64, 8192), (64, 264)])
+def test_in_place_steps_of_decode_rows(tmp_path_factory, rank, d):
+    """A step of single rows alone in place: the form that loads a quarter for tiles of at most four rows, at 1, 4, 5 and 16 rows of an adapter,
+    one layer and several, against the oracle; and each row has the bits that it has in a batch beside a prompt, where the quarter form does not run."""
+    from parity_util import bits, dev_tables, direft_pools_to_device, run_direft_layers_case
+    from test_host_rules import ask
+    counts, N, L = [1, 4, 5, 16], 40, 3
+    ids = np.random.Generator(np.random.PCG64(rank + d)).permutation(np.repeat([3, 11, 17, 39], counts))
+    tab = wl.from_lengths(np.ones(len(ids), int), ids, np.zeros(len(ids), int))
+    beside = wl.from_lengths(np.append(np.ones(len(ids), int), 30), np.append(ids, 7), np.append(np.zeros(len(ids), int), 30))
+    few, other = (tuple(map(int, a.split())) for a in ask(tmp_path_factory, [f"in_place {t.T} {t.S} {N} 1 {rank} {d}" for t in (tab, beside)]))
+    assert few == (1, 1) and other[1] == 0
+    pools = [wl.direft_pool(N, rank, d, "bf16", device="cuda", seed=l) for l in range(L)]
+    hs = [wl.activations(tab.T, d, "bf16", device="cuda", seed=9 + l) for l in range(L)]
+    run_direft_layers_case(tab, pools, hs, "bf16", 0.5, True, [True, False, True], pad_cols=8)
+    if other[0]:                                              # beside the prompt the same kernel, in its other form
+        W1, W2t, b, keep = direft_pools_to_device(pools[0])
+        rows = []
+        for t in (tab, beside):
+            h = torch.zeros(t.T, d, dtype=torch.bfloat16, device="cuda")
+            h[:tab.T] = hs[0]
+            preft.preft_direft_apply(h, *dev_tables(t), W1, W2t, b, rank, 0.5, preft.PREFT_ALL_TOKENS, preft.new_workspace(t.T, t.S))
+            rows.append(h[:tab.T])
+        assert bits(rows[0]).equal(bits(rows[1]))
