@@ -73,6 +73,7 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
     static_assert(!ODD || (MB == 1 && CW == 1), "the any-rank form: the basic shape");
     static_assert(SLICES == 1 || !DIREFT, "packed projections are a LoRA feature");
     static_assert(!EO || (ZOUT && CW == 1), "one wavefront in place of two column groups");
+    static_assert(!ZOUT || MB == 1, "z is written in one row block of 16 rows per wavefront");
     constexpr int WAVES = RW * CW;
     constexpr bool AHEAD2 = ZOUT && SLICES == 1;              // factor units requested two steps ahead
     constexpr int NBT = NB * SLICES;                          // accumulator blocks of the shrink sweep
@@ -400,15 +401,13 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
 
     if constexpr (ZOUT) {
         if (cg == 0) {                                        // with column groups every one of them holds the same z
-            const int64_t blk16 = (int64_t)(unit_id / TPC) * (CHUNK_ROWS / 16) + tile_row0 / 16 + rb * MB;
+            const int64_t blk16 = (int64_t)(unit_id / TPC) * (CHUNK_ROWS / 16) + tile_row0 / 16 + rb;
             const int rank_blocks = NB < 4 ? NB : z_rank_blocks(r);          // 33..48: the fourth block is padding and has no room
             u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + lane;
-            if (blk16 + MB <= p.z_blocks) {                   // the list is cut to its capacity, so this always holds
+            if (blk16 < p.z_blocks) {                         // the list is cut to its capacity, so this always holds
 #pragma unroll
                 for (int b = 0; b < NBT; ++b)
-#pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-                        if (b % NB < rank_blocks) zw[z_piece(blk16 + mb, SLICES, b / NB, rank_blocks, b % NB)] = as_u32x4(zop[b][mb]);
+                    if (b % NB < rank_blocks) zw[z_piece(blk16, SLICES, b / NB, rank_blocks, b % NB)] = as_u32x4(zop[b][0]);
             }
         }
         return;
