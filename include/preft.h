@@ -49,9 +49,13 @@
  * return; they never synchronise.  All launch shapes depend on host-visible sizes only,
  * so a call may be captured into a HIP graph.
  *
- * Arithmetic: products and sums are accumulated in fp32 (PREFT_BF16 and PREFT_F32); the
- * rank-r intermediate stays in fp32; each output element is rounded once, to nearest
- * even, to the activation dtype.
+ * Arithmetic: products and sums are accumulated in fp32 (PREFT_BF16 and PREFT_F32) and each
+ * output element is rounded once, to nearest even, to the activation dtype.  The rank-r
+ * intermediate z stays in fp32 for PREFT_F32 and for PREFT_BF16 at rank 1..3.  At rank 4 and up in
+ * bf16 it goes to the matrix cores as a bf16 head and a bf16 remainder, about 16 bits of it, so
+ * an infinite z gives NaN there; at ranks above 16 that are no multiple of 4 it keeps its 24
+ * bits, and infinities, wherever the call does not take the row-split kernel (widths that are
+ * no multiple of 128, up to 1024 rows, gathered rows; parts of the in-place calls at rank 17..31).
  *
  * Errors: every entry point returns PREFT_OK (0) or a negative code and leaves the output
  * untouched when it returns an error detected before launch.
@@ -81,13 +85,14 @@ enum {
  *   PREFT_TEST_VARIANT(v)    0 = automatic
  *                            1 = per-row kernel everywhere
  *                            2 = vector-ALU tile kernel where it applies (bf16, rank <= 8)
- *                            3 = MFMA tile kernel, column-split shape (bf16, rank a multiple
- *                                of 4 or between 5 and 15)
+ *                            3 = MFMA tile kernel, column-split shape (bf16, rank 4 and up, first
+ *                                factors of less than about 2^30 elements; ranks above 16 that
+ *                                are no multiple of 4 on rows of up to 2^22 columns)
  *                            4 = MFMA tile kernel, row-split shape with the factors shared
  *                                through LDS where it applies (rank a multiple of 4 or above
  *                                16, widths multiples of 128), and no register-resident DiReFT
- *                            5 = automatic, but both sweeps of a LoRA call in one launch even
- *                                if the workspace has room for z (preft_workspace_bytes_z)
+ *                            5 = automatic, but both sweeps of a call in one launch, LoRA or in
+ *                                place, even if the workspace has room for z (preft_workspace_bytes_z)
  *   PREFT_TEST_WAVES(w)      wavefronts per tile workgroup: 0 = automatic, else 1, 2, 4 or 8
  *                            (any non-zero value also makes DiReFT stream its tile instead
  *                            of holding it in registers)
@@ -260,6 +265,8 @@ int preft_direft_apply(void *h, int64_t ldh, int32_t T, int32_t d,
  * same arguments and same results, bit for bit, as preft_direft_apply -- except that the schedule is
  * kept in a static area of device memory inside the library (PREFT_STATIC_SCRATCH_BYTES bytes,
  * which every GPU the library runs on holds until the process ends) instead of a caller workspace.
+ * The rest of the area takes the place of a workspace's room for z: a call that runs as two launches
+ * (bf16, rank 33..64, see preft_workspace_bytes_z) keeps z there if it fits, and otherwise runs as one.
  * The call allocates and frees nothing, on the host or the device.
  *
  * Limit: preft_workspace_bytes(T, S) <= PREFT_STATIC_SCRATCH_BYTES (every batch of up to 32 768
@@ -269,7 +276,7 @@ int preft_direft_apply(void *h, int64_t ldh, int32_t T, int32_t d,
  * rewrites everything it reads from it (nothing there has to start at zero), and with
  * PREFT_SCHEDULE_READY it reuses the schedule the previous static call on this GPU left, under the
  * same T, S, N and position-set check as any apply call.  Two calls that overlap in time on one GPU
- * (different streams, different threads) race on the area: order them.  The first call on a device
+ * (different streams, different threads) race on the area, with PREFT_SCHEDULE_READY too: order them.  The first call on a device
  * looks up the area's address (no allocation); under graph capture make one call before capturing.
  */
 #define PREFT_STATIC_SCRATCH_BYTES (1u << 20)

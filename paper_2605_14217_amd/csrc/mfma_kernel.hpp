@@ -1,4 +1,4 @@
-// MFMA tile kernel (bf16 storage, fp32 accumulation), rank a multiple of 4 up to 128.
+// MFMA tile kernel (bf16 storage, fp32 accumulation), every rank from 4 to 128.
 //
 // One workgroup of WAVES wavefronts owns a tile of R = 16 * MB consecutive active rows of
 // one segment.  The wavefronts split the *columns* in units of 128 (256 bytes per row):

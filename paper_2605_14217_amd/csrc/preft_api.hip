@@ -538,7 +538,8 @@ void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t s
                 // rest twice.  Measured on the skewed batch (d = 8192): traffic through the fabric falls
                 // by a sixth (half of the tile is read once), the time by 4 % (5985 against 6216 us): the
                 // 256 + 248 registers leave one workgroup of four wavefronts per compute unit, and what
-                // binds is the latency of the factor sweeps, not the bytes.  Not the default.
+                // binds is the latency of the factor sweeps, not the bytes.  Not the default: measured at that
+                // one batch and width only, which draws no line over widths and rows.
                 if (k.resident == 3) launch_mfma_partial<2, 2, 4, 8>(a, S, stream);
                 else                 launch_mfma<2, 2, 4, 0, true>(a, S, stream);
                 return;
