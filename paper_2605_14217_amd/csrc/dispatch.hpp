@@ -163,18 +163,25 @@ inline SmallShape small_shape(const ApplyArgs &a, int64_t S, int n_slices, const
 // Whether an in-place call of rank 17-31, no multiple of 4, takes 32-row tiles of the column-split kernel instead of 64-row tiles of the
 // row-split one, as the multiples of 4 always do: twice as many tiles, and their second read of h follows the first sooner.  But large batches
 // of narrow rows find that read in the caches either way; prompts of a few dozen rows fill 32-row tiles no better and read an adapter's factors for
-// twice as many of them; and ranks 21 and 31 have the texture path busy with their unaligned factors as soon as the tiles fill the chip (each rank
-// was measured: 17-30 differ by a few percent, those two by 20 more).  A layer takes the kernel of its one-layer call, so the line is drawn where several layers
-// lose little.  Row-split / column-split, us: 1500 rows, d = 1024 / 4096 / 8192, rank 18 18.1 / 9.7, 62 / 26, 116 / 45, rank 31 18.3 / 11.2, 64 / 32, 121 / 56;
-// 12 000 rows, d = 8192, rank 29 147 / 113, 31 147 / 128; 29 000 rows, 8192, rank 18 267 / 250, 23 276 / 265, 29 263 / 265, 31 268 / 289; 12 000 rows of prompts of
-// 40, d = 4096, rank 18 109 / 98, 23 110 / 111, 31 115 / 139, d = 1024, 19 32 / 35, 31 33 / 41; several layers of d = 4096: 2 x 5300 rows of short prompts, rank 18
-// 90 / 82, 23 91 / 92, 31 94 / 114, 4 x 5000, 18 99 / 94, 23 101 / 101, 31 100 / 117, 4 x 2000, 23 69 / 52, 31 69 / 62.  35 000 rows, d = 512, rank 31 25 / 30, 2048 89 / 86.
+// twice as many of them; and ranks 21 and 31 have the texture path busy with their unaligned factors as soon as the tiles fill the chip twice (each rank
+// was measured: 17-30 differ by a few percent, those two by 20 more).  Row-split / column-split, us: 1500 rows, d = 1024 / 4096 / 8192, rank 18 18.1 /
+// 9.7, 62 / 26, 116 / 45, rank 31 18.3 / 11.2, 64 / 32, 121 / 56; 29 000 rows, 8192, rank 18 267 / 250, 23 276 / 265, 29 263 / 265; 12 000 rows of prompts of
+// 40, d = 4096, rank 18 109 / 98, 23 110 / 111, 31 115 / 139, d = 1024, 19 32 / 35, 31 33 / 41; 52 000 rows of prompts of 35, d = 8192, rank 17 787 / 1016, 18 792 / 904,
+// 29 818 / 1066; 39 000 of prompts of 130, 485 / 391, 491 / 364, 502 / 416; 35 000 rows, d = 512, rank 31 25 / 30, 2048 89 / 86.
+// Rank 31 (21 the same to 3 %), prompts of 600 rows, d = 1024 / 4096 / 14336: 6000 rows 20.9 / 13.0, 68 / 36, 225 / 115; 13 200 rows 24.3 / 20.7, 73 / 66, 299 / 264;
+// 16 800 rows 29.0 / 31.6, 94 / 101, 379 / 409; 21 000 rows, 4096 / 8192 104 / 116, 230 / 236; 30 000 rows 181 / 150, 354 / 325, 160 000 rows 576 / 623, 1352 / 1279.
+// Prompts of 40 rows, d = 1024 / 4096 / 14336: 5000 rows 22.5 / 18.3, 69 / 58, 225 / 195; 8000 rows 26.2 / 29.6, 87 / 87, 295 / 297, and 8000 of prompts of 190 beside 156
+// decode rows 23.0 / 19.4, 69 / 59, 252 / 227, which the host cannot tell apart; 10 500 rows of prompts of 40, 27 / 33, 90 / 113, 310 / 393; of 65, 45 000 rows, 4096 263 / 330.
+// A layer takes the kernel of its one-layer call, whatever that costs where layers add up to another number of tiles (rank 31, d = 4096, 4 x 3600 rows 91 / 67, 2 x 12 000
+// 110 / 126, 4 x 4000 of prompts of 40 120 / 147).
 inline bool odd_streams_in_place(const ApplyArgs &a, int64_t S)
 {
     if (!column_split_fits(a)) return false;
-    const bool short_prompts = a.T < 64 * S;
-    if (a.rank == 21 || a.rank == 31) return a.T <= 2048 && !short_prompts;
-    if (short_prompts && a.T > 8192 && a.d_in < 2048) return false;
+    if (a.rank == 21 || a.rank == 31) {
+        if (a.T <= 14336) return a.T <= 8192 || a.T >= 48 * S;
+        if (a.T < 28672 || a.T < 128 * S) return false;
+    }
+    if (a.T < 64 * S && (a.T > 16384 || (a.T > 8192 && a.d_in < 2048))) return false;
     return a.T <= 16384 || a.d_in >= 8192 || (a.d_in >= 4096 && a.T <= 49152);
 }
 

@@ -83,14 +83,14 @@ def test_every_rank_meets_its_own_factor(rank, d, d_out, rows):
 @pytest.mark.parametrize("rank,d", [(17, 128), (18, 4096), (30, 2048), (31, 1024)])
 def test_in_place_on_widths_that_are_multiples_of_128(rank, d, tmp_path_factory):
     """Rank 17-31 in place: the column-split and the row-split kernel, which the test flags choose; both against the oracle on the same rows, and
-    the default call the one that the dispatch names, to the bit: short prompts, long ones, and a batch above 16 384 rows."""
+    the default call the one that the dispatch names, to the bit: short prompts, long ones, a batch above 16 384 rows, and one of short prompts alone."""
     from oracle import preft_oracle as ora
     from paper_2605_14217_amd import binding as B
     from parity_util import bits, compare, dev_tables, direft_pools_to_device
     from test_host_rules import ask
     N = 4
     seen = set()
-    for lens in ([1, 15, 16, 17, 33, 5, 4, 129, 700, 600] + [1] * 20, [17, 129, 700, 600], [1, 15, 16, 17, 33, 5, 4, 129, 700, 600] + [5100] * 3 + [1] * 20):
+    for lens in ([1, 15, 16, 17, 33, 5, 4, 129, 700, 600] + [1] * 20, [17, 129, 700, 600], [1, 15, 16, 17, 33, 5, 4, 129, 700, 600] + [5100] * 3 + [1] * 20, [40] * 220):
         lens = np.array(lens)
         tab = wl.from_lengths(lens, np.random.Generator(np.random.PCG64(rank)).integers(-1, N + 1, size=len(lens)), np.where(lens > 1, lens, 0))
         ss, sa, sp = dev_tables(tab)
