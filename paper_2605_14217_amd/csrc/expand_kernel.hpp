@@ -266,10 +266,10 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 4) void mfma_expand_kernel(Apply
 // 128 PU; chunks only).  At rank 64 the factors of a wavefront's own columns would be as many bytes as its 32 rows of y; shared by
 // 64 rows they are half as many.  64 x 256 where every output is a multiple of 256 wide, else 64 x 128.
 // gate+up of a 70B layer, rank 64, 89 740 rows, whole call: one launch 4845 us, two with y turned through LDS 4470, without 4165-4250, and 4060-4120
-// since the shrink launch takes tiles of 128 rows (5.7 TB/s); 8192 -> 8192 946 / 855 / 842; rank 63, 8192 -> 28 672 2586 (one launch) / 2282; 8B layer, 37 000 rows, rank 64 gate+up 925 / 882, rank 63, 4096 -> 14336
-// 542 (a wavefront's own factors) / 479; 4096 -> 14208 (64 x 128) 539 / 509.
-// Three workgroups per compute unit, at the 4165-4250 and 842 of the figures above.  Four (128 registers) spill: gate+up 5324; kept from spilling by a barrier to the
-// compiler's scheduler they have a wider window of y in flight, 4420 and 895; two 4690, 970.
+// since the shrink launch takes tiles of 128 rows (5.7 TB/s); 8192 -> 8192 946 / 855 / 842; rank 63, 8192 -> 28 672 2586 (one launch) / 2282; 8B layer,
+// 37 000 rows, rank 64 gate+up 925 / 882, rank 63, 4096 -> 14336 542 (a wavefront's own factors) / 479; 4096 -> 14208 (64 x 128) 539 / 509.
+// Three workgroups per compute unit, at the 4165-4250 and 842 of the figures above.  Four (128 registers) spill: gate+up 5324; kept from spilling by a
+// barrier to the compiler's scheduler they have a wider window of y in flight, 4420 and 895; two 4690, 970.
 // Tiles of 128 rows 4400, 890.  Tiles in memory order; dealt to the XCDs as runs 977 for 923, 65 for 67 (with y turned).
 constexpr int PANEL_RW = 4;
 
