@@ -99,6 +99,9 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool dire
     // A few decode rows of an adapter each: tiles of which this kernel loads a quarter.  Rank 16, 32 rows of 32 adapters, resident / this, us: d = 4096 9.2 /
     // 8.2, 8192 14.8 / 13.2, 8 layers of 4096 17.5 / 13.6; rank 7, 8192 17.5 / 15.3; d = 14336 (streamed) 27.6 / 22.4; but 256 rows of 200 adapters
     // 12.5 / 13.6, of 32 10.4 / 11.0, and 8 layers of 46 tiles, more than a tile for every compute unit, 22.0 / 25.0.
+    // That is for adapters drawn alike.  Where a few of them have most of the rows their tiles are full, and this kernel reads h twice: 16-64 rows of 8-64 adapters,
+    // the i-th as likely as 1 / i^1.1, d = 4096, rank 8 and 16 9.1-10.3 / 10.5-10.7, 7 11.4-11.8 / 11.2-11.5, 8192, rank 16 15.1-16.9 / 17.2-18.7, 14336 25.8-28.3 /
+    // 25.4-29.6.  The host cannot tell the two apart.
     if (a.all_tokens && prompt_rows(a, S) == 0 && likely_tiles(a, S) <= 32 && a.T <= 3 * likely_tiles(a, S)) return true;
     return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
 }
