@@ -13,11 +13,25 @@
 // decode rows 14.5 -> 9.0 us, a 1000-row batch 27.6 -> 14.7; rank 64: 49 -> 21, 75 -> 45; 4096 -> 4096 rank 16: 8.1 -> 7.5, 15.9 -> 11.6.
 #pragma once
 #include "common.hpp"
+#include "expand_kernel.hpp"                                 // FactorLds
 #include "mfma_kernel.hpp"
 
 namespace preft {
 
 constexpr int SMALL_WAVES = 8;
+
+// Whether a unit's factors of the expand go through LDS in whole lines and y does not, as in mfma_expand_kernel (DIRECT below).  Where they are few (up
+// to rank 16) the address arithmetic and the trip through LDS cost a lone tile more than y's two: 32 decode rows, 4096 -> 4096, rank 16 5.8 us, 6.1 with it; rank 32, tiles of up to four
+// rows, 7.4 / 7.6.  Without / with it, us: rank 32, 900 prompt rows 14.4 / 13.5, in place, 32 decode rows, d = 4096 13.4 / 11.4; rank 7 (which had its factors in LDS
+// already), 600 prompt rows 8.4 / 8.0, 200 decode rows 7.6 / 7.3.  (Factors straight from memory in that column order, 16 lines an instruction: in place 7.9 / 12.2, rank 48 17.7 / 36.)
+template <int NB, bool DIREFT, bool ODD> constexpr bool small_direct(int NG) { return ODD ? NB == 1 : NB == 2 && (DIREFT || NG == 4); }
+// A wavefront's own LDS, in 16-byte vectors: a unit of activations and one of the factor in turn, later a unit's factors of the expand.
+template <int NB, bool DIREFT, bool ODD>
+constexpr int small_area()
+{
+    constexpr int turns = 2 * 16 * MFMA_TRS, factors = small_direct<NB, DIREFT, ODD>(4) ? (FactorLds<NB>::BYTES + 15) / 16 : 0;
+    return turns > factors ? turns : factors;
+}
 
 // DEEP: few workgroups, each alone on its compute unit: up to 256 registers for requests in flight.  Otherwise (rank <= 16: the LDS
 // of more rank blocks does not fit twice) 128, two workgroups per compute unit, which hide one another's trips.
@@ -36,16 +50,20 @@ struct SmallOutput {                                          // the output of a
 
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, int NG>
 __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallOutput &o, const i32x4_t entry, bool gathered, int row0, int n_rows,
-                                                u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
+                                                u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD>()], float (&red)[WAVES * NB * 4 * 64])
 {
-    constexpr bool PARKED = ODD && NB == 1, ANY = ODD && NB > 1;        // ranks that are no multiple of 4: up to 16, and above
+    constexpr bool ANY = ODD && NB > 1;                       // ranks above 16 that are no multiple of 4
+    constexpr bool DIRECT = small_direct<NB, DIREFT, ODD>(NG);
     // units of the shrink and of the expand sweep in flight (registers)
     constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : 2;
-    constexpr bool EARLY = NG == 1 && DEEP && NB <= 2;         // registers for the first units of the expand beside the shrink's
-    constexpr int DEPTH = DEEP ? (NB == 1 ? (PARKED || EARLY ? 2 : 4) : NB == 2 ? (EARLY ? 1 : 2) : 1) : 1;
+    // units of the expand that are asked for before the shrink's last ones are used (registers).  With that, waits for one unit at a time (sweep below) and
+    // the bias ahead of the sums, 32 decode rows of 32 adapters, rank 16, replayed: 14336 -> 4096 10.9 -> 10.4 us, 4096 -> 2 x 14336 10.9 -> 10.6, in place, d = 4096,
+    // 8.1 -> 7.9, 8 layers of it 12.8 -> 12.2, a layer's six launches 47.9 -> 45.7; 481 prompt rows, rank 8, q+k+v 9.2 -> 8.8.
+    constexpr int EARLY = NG == 1 && DEEP && NB <= 2 ? (DIREFT && NB == 1 ? 2 : 1) : 0;
+    constexpr int DEPTH = DEEP ? (NB == 1 ? (DIRECT || NG == 1 ? 2 : 4) : NB == 2 ? 2 : 1) : 1;
     constexpr bool W_LATE = NB > 4;                           // factors of the expand step by step (registers)
     static_assert(DEEP || NB == 1, "two workgroups of more rank blocks do not fit a compute unit");
-    constexpr int PIECES = 4;                                 // any-rank form: 16-byte pieces of a unit's factor block per lane
+    constexpr int PIECES = 4 * NB;                            // DIRECT: 16-byte pieces of a unit's factor block per lane
     const int per_share = p.col_split;                        // units of a share
     void *const y = o.y;
     const int64_t ldy = o.ldy;
@@ -59,12 +77,14 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     const int rl = lane & 15, g = lane >> 4;                  // MFMA order
     const int q = lane >> 4, c16 = lane & 15;                 // unit load order
     const int r = p.rank;
-    u32x4_t *tr = turn[wave][0], *tra = turn[wave][1];
+    u32x4_t *tr = area[wave], *tra = area[wave] + 16 * MFMA_TRS;
 
-    // row slots past the tile alias its last row: same loads, same values; their stores are left out
+    // Row slot of the lane in load i (DIRECT: those that an accumulator of z times factors has for it).  Slots past the tile alias its last
+    // row: same loads, same values; their stores are left out
+    auto slot = [&](int i) { return DIRECT && NG > 1 ? 4 * q + i : 4 * i + q; };
     int32_t row[NG];
 #pragma unroll
-    for (int i = 0; i < NG; ++i) row[i] = entry[1] + row0 + min(4 * i + q, n_rows - 1);
+    for (int i = 0; i < NG; ++i) row[i] = entry[1] + row0 + min(slot(i), n_rows - 1);
     if (gathered) {
 #pragma unroll
         for (int i = 0; i < NG; ++i) row[i] = p.shorts[row[i]].y;
@@ -82,8 +102,8 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     const int ubase = DIREFT ? 0 : share * per_share, uend = DIREFT ? c_units : min(ubase + per_share, c_units);
     const int y_last = d_out * 2 - 16;
     u32x4_t Y[DEPTH][NG];
-    u32x2_t W[DEPTH][W_LATE ? 1 : 4][2][NB];
-    u32x4_t Wb[PARKED ? DEPTH : 1][PIECES];
+    u32x2_t W[DIRECT ? 1 : DEPTH][W_LATE || DIRECT ? 1 : 4][2][NB];
+    u32x4_t Wb[DIRECT ? DEPTH : 1][PIECES];
     auto load_w = [&](u32x2_t (&w)[2][NB], int u, int s) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
@@ -101,7 +121,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         const int off = min(u * 256 + c16 * 16, y_last);
 #pragma unroll
         for (int i = 0; i < NG; ++i) Y[k][i] = ld16(yu[i] + off);
-        if constexpr (PARKED) {                               // the unit's [128 columns][r] block, contiguous
+        if constexpr (DIRECT) {                               // the unit's [128 columns][r] block, contiguous
             const int last = last_factor_piece(d_out - u * 128, 128, r);
 #pragma unroll
             for (int j = 0; j < PIECES; ++j) Wb[k][j] = ld16(Bt + (int64_t)u * 256 * r + min(min(lane + 64 * j, 16 * r - 1), last) * 16);
@@ -110,9 +130,15 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             for (int s = 0; s < 4; ++s) load_w(W[k][s], u, s);
         }
     };
+    // A request that hangs on a branch has every later wait wait for all that is on its way: the first ones ask for units that need not exist (the
+    // last one again).
+    auto request_early = [&] {
+#pragma unroll
+        for (int k = 0; k < EARLY; ++k) load_yw(k, min(ubase + wave + k * WAVES, c_units - 1));
+    };
     auto request_expand = [&] {
 #pragma unroll
-            for (int k = 0; k < DEPTH; ++k)
+        for (int k = EARLY; k < DEPTH; ++k)
             if (ubase + wave + k * WAVES < uend) load_yw(k, ubase + wave + k * WAVES);
     };
 
@@ -128,13 +154,12 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             for (int i = 0; i < 4; ++i)                       // ranks past r alias the last one: their z is zeroed
                 a[i] = ld16(A + (uint32_t)(min(16 * b + 4 * i + q, r - 1) * (x_last + 16) + off));
         };
-        // two halves of a batch take turns: one is on its way while the other is used
         constexpr int HALVES = BATCH > 1 ? 2 : 1, H = BATCH / HALVES;
-        u32x4_t xr[HALVES][H][NG], ar[HALVES][H][NB][4];
-        auto request = [&](u32x4_t (&x)[H][NG], u32x4_t (&a)[H][NB][4], int u0) {
+        auto request = [&](auto &x, auto &a, int u0, auto always) {
+            constexpr int UNITS = sizeof(x) / sizeof(x[0]);
 #pragma unroll
-            for (int k = 0; k < H; ++k)
-                if (u0 + k * WAVES < k_units) {
+            for (int k = 0; k < UNITS; ++k)
+                if (decltype(always)::value || u0 + k * WAVES < k_units) {
                     const int off = min((u0 + k * WAVES) * 256 + c16 * 16, x_last);
 #pragma unroll
                     for (int i = 0; i < NG; ++i) x[k][i] = ld16(xu[i] + off);
@@ -142,9 +167,10 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
                     for (int b = 0; b < NB; ++b) load_a(a[k][b], b, off);
                 }
         };
-        auto use = [&](u32x4_t (&x)[H][NG], u32x4_t (&a)[H][NB][4], int u0) {
+        auto use = [&](auto &x, auto &a, int u0) {
+            constexpr int UNITS = sizeof(x) / sizeof(x[0]);
 #pragma unroll
-            for (int k = 0; k < H; ++k)
+            for (int k = 0; k < UNITS; ++k)
                 if (u0 + k * WAVES < k_units) {
                     if ((u0 + k * WAVES) * 256 + c16 * 16 > x_last) {    // past the width: zero times zero
 #pragma unroll
@@ -156,7 +182,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
                     }
                     u32x4_t xo[4], ao[4];
 #pragma unroll
-                    for (int i = 0; i < NG; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = x[k][i];
+                    for (int i = 0; i < NG; ++i) tr[slot(i) * MFMA_TRS + c16] = x[k][i];
 #pragma unroll
                     for (int s = 0; s < 4; ++s) xo[s] = tr[rl * MFMA_TRS + 4 * s + g];
 #pragma unroll
@@ -171,28 +197,81 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
                     }
                 }
         };
-        if constexpr (HALVES == 2) {
-            request(xr[0], ar[0], wave);
-            request(xr[1], ar[1], wave + H * WAVES);
-            if constexpr (EARLY) request_expand();
+        // Tiles of few rows: `B` units on their way, each in registers of its own.  No request hangs on a branch (past the last unit: that one again, not
+        // used), so a wait is for its own unit and the others go on arriving.
+        auto sweep = [&](auto b_tag) {
+            constexpr int B = decltype(b_tag)::value;
+            u32x4_t xr[B][1][NG], ar[B][1][NB][4];
+            auto ask = [&](int k, int u) { request(xr[k], ar[k], min(u, k_units - 1), std::true_type{}); };
+#pragma unroll
+            for (int k = 0; k < B; ++k) ask(k, wave + k * WAVES);
+            int u = wave;
+            for (; u + B * WAVES < k_units; u += B * WAVES) {
+#pragma unroll
+                for (int k = 0; k < B; ++k) {
+                    use(xr[k], ar[k], u + k * WAVES);
+                    ask(k, u + (B + k) * WAVES);
+                }
+            }
+            request_early();
+#pragma unroll
+            for (int k = 0; k < B; ++k) use(xr[k], ar[k], u + k * WAVES);
+        };
+        if constexpr (NG == 1 && BATCH > 1) {
+            if (k_units <= WAVES) sweep(std::integral_constant<int, 1>{});
+            else if (BATCH > 2 && k_units <= 2 * WAVES) sweep(std::integral_constant<int, 2>{});
+            else sweep(std::integral_constant<int, BATCH>{});
+        } else if constexpr (HALVES == 2) {
+            // two halves of a batch take turns: one is on its way while the other is used
+            u32x4_t xr[2][H][NG], ar[2][H][NB][4];
+            request(xr[0], ar[0], wave, std::false_type{});
+            request(xr[1], ar[1], wave + H * WAVES, std::false_type{});
             int u = wave;
             for (; u + 2 * H * WAVES < k_units; u += 2 * H * WAVES) {
                 use(xr[0], ar[0], u);
-                request(xr[0], ar[0], u + 2 * H * WAVES);
+                request(xr[0], ar[0], u + 2 * H * WAVES, std::false_type{});
                 use(xr[1], ar[1], u + H * WAVES);
-                request(xr[1], ar[1], u + 3 * H * WAVES);
+                request(xr[1], ar[1], u + 3 * H * WAVES, std::false_type{});
             }
             use(xr[0], ar[0], u);
             use(xr[1], ar[1], u + H * WAVES);
         } else {
+            u32x4_t xr[1][H][NG], ar[1][H][NB][4];
             for (int u = wave; u < k_units; u += H * WAVES) {
-                request(xr[0], ar[0], u);
+                request(xr[0], ar[0], u, std::false_type{});
                 use(xr[0], ar[0], u);
             }
         }
     }
 
-    if constexpr (!EARLY) request_expand();                   // before z is summed
+    request_expand();                                         // before z is summed
+
+    const FactorLds<DIRECT ? NB : 1> fl(r);
+    char *const fw = reinterpret_cast<char *>(area[wave]);
+    auto park = [&](int k) {                                  // a unit's factors to LDS
+        if constexpr (DIRECT) {
+#pragma unroll
+            for (int j = 0; j < PIECES; ++j) {
+                const int piece = min(lane + 64 * j, 16 * r - 1);
+                if constexpr (ODD) {
+                    *reinterpret_cast<u32x4_t *>(fw + piece * 16) = Wb[k][j];
+                } else {                                      // two 8-byte halves, neither straddles a column
+                    *reinterpret_cast<u32x2_t *>(fw + fl.quarter(2 * piece)) = u32x2_t{Wb[k][j][0], Wb[k][j][1]};
+                    *reinterpret_cast<u32x2_t *>(fw + fl.quarter(2 * piece + 1)) = u32x2_t{Wb[k][j][2], Wb[k][j][3]};
+                }
+            }
+        }
+    };
+    // (at rank 17-32 before the sums, whose wait it fills; with half the factors it is quicker not to wait for them here)
+    constexpr bool PARK_FIRST = NB == 2;
+    if constexpr (PARK_FIRST) park(0);
+
+    // the bias of rank `lane` (in place: r <= 64): its two trips beside the wait for the sums, not after it
+    float bias = 0.f;
+    if constexpr (DIREFT) {
+        gcptr_t bias_p = bias_of(p, entry[0]);
+        if (bias_p) bias = Elem<bf16_tag>::load1(bias_p, min(lane, r - 1));
+    }
 
     // ---------------------------------------------------------------- sum over the wavefronts, z -> expand operand
 #pragma unroll
@@ -200,20 +279,21 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
         for (int v = 0; v < 4; ++v) red[((wave * NB + b) * 4 + v) * 64 + lane] = acc[b][v];
     __syncthreads();                                          // also: every read of the tile precedes every write (in place: a unit belongs to one wavefront)
+    // DIRECT, up to four rows: those stand in rows 0, 4, 8, 12 of the operand, so that a lane's accumulators begin with its own row
+    const int zlane = DIRECT && NG == 1 ? (rl >> 2) + 16 * g : lane;
     bf16x8_t zop[NB];
     u32x4_t zlow[ANY ? NB / 2 : 1];                           // what two parts of bf16 leave of z (whole_z), two rank blocks in one operand
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int rank0 = 16 * b + 4 * g;
-        gcptr_t bias = DIREFT ? bias_of(p, entry[0]) : nullptr;
         float zv[4], rem[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             float s = 0.f;
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w) s += red[((w * NB + b) * 4 + v) * 64 + lane];
+            for (int w = 0; w < WAVES; ++w) s += red[((w * NB + b) * 4 + v) * 64 + zlane];
             float add = 0.f;
-            if (DIREFT && bias && rank0 + v < r) add = Elem<bf16_tag>::load1(bias, rank0 + v);
+            if constexpr (DIREFT) add = __shfl(bias, rank0 + v, 64);
             zv[v] = rank0 + v < r ? (s + add) * p.scale : 0.f;
             rem[v] = zv[v] - __uint_as_float((pack_bf16(zv[v], 0.f) & 0xffffu) << 16);
         }
@@ -228,13 +308,6 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     }
 
     // ---------------------------------------------------------------- expand
-    // any-rank form: this lane's factors of step 0, column 8 (rl / 4) + rl % 4 in the parked block, and which of
-    // its four ranks exist (see mfma_tile_kernel)
-    const int odd_at = (8 * (rl >> 2) + (rl & 3)) * r + 4 * g, odd_n = r - 4 * g;
-    const uint32_t *odd_words = reinterpret_cast<const uint32_t *>(tra) + ((odd_n > 0 ? odd_at : 0) >> 1);
-    const uint32_t odd_shift = (odd_at & 1) * 16;
-    const uint32_t odd_m01 = odd_n >= 2 ? 0xffffffffu : odd_n == 1 ? 0xffffu : 0u;
-    const uint32_t odd_m23 = odd_n >= 4 ? 0xffffffffu : odd_n == 3 ? 0xffffu : 0u;
     // y plus the products of step s, in MFMA order (ANY only: `nan`, whether a result is NaN; finite_tag as in whole_z_products)
     auto products = [&](const u32x4_t y, const u32x2_t (&wv)[2][NB], int s, bool &nan, auto finite_tag) -> u32x4_t {
         float out[8];
@@ -248,14 +321,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             } else {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    u32x2_t w;
-                    if constexpr (PARKED) {
-                        const uint32_t *w3 = odd_words + (16 * s + 2 * e) * r;
-                        const uint32_t d0 = w3[0], d1 = w3[1], d2 = w3[2];
-                        w = u32x2_t{__builtin_amdgcn_alignbit(d1, d0, odd_shift) & odd_m01, __builtin_amdgcn_alignbit(d2, d1, odd_shift) & odd_m23};
-                    } else {
-                        w = wv[e][b];
-                    }
+                    const u32x2_t w = wv[e][b];
                     d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), zop[b], d, 0, 0, 0);
                 }
             }
@@ -267,17 +333,36 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         }
         return Elem<bf16_tag>::pack(out);
     };
+    // z as the first operand, the factors as the second: lane (n16, g) of MFMA k ends up with column 8 n16 + k of the rows
+    // that it has loaded
+    auto finish_direct = [&](int k, int u) {
+        if (!PARK_FIRST || u != ubase + wave) park(k);
+#pragma unroll
+        for (int k2 = 0; k2 < 4; ++k2) {
+            f32x4_t d[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                d[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const u32x2_t w = fl.template operand<ODD>(fw, 2 * k2 + e, b, c16, g, r);
+                    d[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zop[b], as_bf16x8(u32x4_t{w[0], w[1], w[0], w[1]}), d[e], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NG; ++i) Y[k][i][k2] = pack_bf16(bf16_lo(Y[k][i][k2]) + d[0][i], bf16_hi(Y[k][i][k2]) + d[1][i]);
+        }
+        const int off = u * 256 + c16 * 16;
+#pragma unroll
+        for (int i = 0; i < NG; ++i)
+            if (off <= y_last && slot(i) < n_rows) st16_stream(yu[i] + off, Y[k][i]);
+    };
     auto finish = [&](int k, int u) {
         u32x4_t yo[4];
 #pragma unroll
-        for (int i = 0; i < NG; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = Y[k][i];
+        for (int i = 0; i < NG; ++i) tr[slot(i) * MFMA_TRS + c16] = Y[k][i];
 #pragma unroll
         for (int s = 0; s < 4; ++s) yo[s] = tr[rl * MFMA_TRS + 4 * s + g];
-        if constexpr (PARKED) {
-#pragma unroll
-            for (int j = 0; j < PIECES; ++j)
-                if (lane + 64 * j < 16 * r) tra[lane + 64 * j] = Wb[k][j];
-        }
         bool nan = false;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -288,7 +373,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         if constexpr (ANY) {
             if (__any(nan && rl < n_rows)) {                  // (rows that do not exist may hold anything)
 #pragma unroll
-                for (int i = 0; i < NG; ++i) tr[(4 * i + q) * MFMA_TRS + c16] = ld16(yu[i] + min(off, y_last));
+                for (int i = 0; i < NG; ++i) tr[slot(i) * MFMA_TRS + c16] = ld16(yu[i] + min(off, y_last));
 #pragma unroll 1
                 for (int s = 0; s < 4; ++s) {
                     u32x2_t w[2][NB];
@@ -300,15 +385,16 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         }
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
-            const u32x4_t v = tr[(4 * i + q) * MFMA_TRS + c16];
-            if (off <= y_last && 4 * i + q < n_rows) st16_stream(yu[i] + off, v);
+            const u32x4_t v = tr[slot(i) * MFMA_TRS + c16];
+            if (off <= y_last && slot(i) < n_rows) st16_stream(yu[i] + off, v);
         }
     };
     for (int u = ubase + wave; u < uend; u += WAVES * DEPTH) {
 #pragma unroll
         for (int k = 0; k < DEPTH; ++k)
             if (u + k * WAVES < uend) {
-                finish(k, u + k * WAVES);
+                if constexpr (DIRECT) finish_direct(k, u + k * WAVES);
+                else finish(k, u + k * WAVES);
                 if (u + (k + DEPTH) * WAVES < uend) load_yw(k, u + (k + DEPTH) * WAVES);
             }
     }
@@ -317,7 +403,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 // FEW: with the form for tiles of up to four rows (in place only for steps of decode rows: its second copy of the code costs the others 0.1 us of 4.5).
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW>
 __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOutput &o, int unit, int n_chunk_units,
-                                               u32x4_t (&turn)[WAVES][2][16 * MFMA_TRS], float (&red)[WAVES * NB * 4 * 64])
+                                               u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD>()], float (&red)[WAVES * NB * 4 * 64])
 {
     // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
     const bool gathered = unit >= n_chunk_units;
@@ -326,8 +412,8 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOu
         gathered ? as_const(p.gtiles) + (unit - n_chunk_units) : as_const(p.chunks) + unit / (CHUNK_ROWS / 16));
     const int n_rows = min(16, entry[2] - row0);
     if (n_rows <= 0) return;                                  // uniform over the workgroup
-    if (!FEW || n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4>(p, o, entry, gathered, row0, n_rows, turn, red);
-    else if constexpr (FEW) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1>(p, o, entry, gathered, row0, n_rows, turn, red);
+    if (!FEW || n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4>(p, o, entry, gathered, row0, n_rows, area, red);
+    else if constexpr (FEW) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1>(p, o, entry, gathered, row0, n_rows, area, red);
 }
 
 // A launch out of place: blockIdx.x = 8 share + XCD, blockIdx.y = the slot of a tile on that XCD (in place: blockIdx.x = 8 slot + XCD).  The shares of a
@@ -338,7 +424,7 @@ struct SmallLaunch { int shares0, shares1; };
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW>
 __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallLaunch &l)
 {
-    __shared__ u32x4_t turn[WAVES][2][16 * MFMA_TRS];         // activations, and the factor
+    __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, ODD>()];
     __shared__ float red[WAVES * NB * 4 * 64];
 
     // What the launch arguments say is asked for together with the header: each line of them that is touched later is a trip of its own (in
@@ -361,7 +447,7 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallL
     const int per_xcd = (n_units + 7) >> 3;
     for (int t = DIREFT ? blockIdx.x >> 3 : blockIdx.y; t < per_xcd; t += DIREFT ? gridDim.x >> 3 : gridDim.y) {
         const int unit = few_tiles_unit(p, n_chunk_units, per_xcd, t);
-        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES, FEW>(p, o, unit, n_chunk_units, turn, red);
+        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES, FEW>(p, o, unit, n_chunk_units, area, red);
         __syncthreads();                                      // the next tile's sums go where this one's are still being read
     }
 }

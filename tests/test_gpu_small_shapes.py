@@ -123,3 +123,18 @@ def test_in_place_steps_of_decode_rows(tmp_path_factory, rank, d):
             preft.preft_direft_apply(h, *dev_tables(t), W1, W2t, b, rank, 0.5, preft.PREFT_ALL_TOKENS, preft.new_workspace(t.T, t.S))
             rows.append(h[:tab.T])
         assert bits(rows[0]).equal(bits(rows[1]))
+
+
+@pytest.mark.parametrize("rank", [4, 7, 16, 20, 32])
+@pytest.mark.parametrize("d_in", [8, 1024, 1032, 2048, 2056, 4096, 4104, 6152, 9216])
+def test_shrink_of_few_rows(rank, d_in):
+    """Tiles of at most four rows: one, two and four units of d_in on their way in each wavefront, with and without a round that repeats, a last
+    unit that is cut off and wavefronts without one; in place and out of place, against the oracle."""
+    from parity_util import run_direft_case, run_lora_case
+    N, counts = 5, [1, 3, 4, 6]
+    ids = np.random.Generator(np.random.PCG64(rank + d_in)).permutation(np.repeat(np.arange(4), counts))
+    tab = wl.from_lengths(np.ones(len(ids), int), ids, np.zeros(len(ids), int))
+    x = wl.activations(tab.T, d_in, "bf16", device="cuda", seed=1)
+    y0 = wl.activations(tab.T, 392, "bf16", device="cuda", seed=2)
+    run_lora_case(tab, wl.lora_pool(N, rank, d_in, 392, "bf16", device="cuda", seed=3), x, y0, "bf16", 2.0, True, pad_cols=8)
+    run_direft_case(tab, wl.direft_pool(N, rank, d_in, "bf16", device="cuda", seed=4), x, "bf16", 0.5, True, pad_cols=8)
