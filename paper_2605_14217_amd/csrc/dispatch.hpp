@@ -85,7 +85,7 @@ constexpr int64_t DEEP_WGS = 200;                             // at most one wor
 // `widest`: columns of the widest output
 inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool direft, const Knobs &k)
 {
-    if (a.rank < 4) return false;
+    if (a.rank < 4 && (k.variant || k.colsplit)) return false;            // those name the vector-ALU kernel there
     if (a.d_in > (1 << 22) || widest > (1 << 22)) return false;          // offsets within a row or a factor, and the launch, fit 32 bits
     if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
     if (!direft && k.colsplit) return k.colsplit > 1;
@@ -103,6 +103,9 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool dire
     // the i-th as likely as 1 / i^1.1, d = 4096, rank 8 and 16 9.1-10.3 / 10.5-10.7, 7 11.4-11.8 / 11.2-11.5, 8192, rank 16 15.1-16.9 / 17.2-18.7, 14336 25.8-28.3 /
     // 25.4-29.6.  The host cannot tell the two apart.
     if (a.all_tokens && prompt_rows(a, S) == 0 && likely_tiles(a, S) <= 32 && a.T <= 3 * likely_tiles(a, S)) return true;
+    // Ranks 1-3, rows resident in a wavefront's registers / this, us: rank 1, d = 1024, 250 and 920 prompt rows 3.6 / 3.7, 4.2 / 3.9, 4096 7.6 / 7.1, 512 decode rows 8.2 /
+    // 7.2, rank 3 9.7 / 8.4, 11.2 / 9.3, 11.1 / 8.6; but rank 1, d = 512, 250 rows 3.2 / 3.4.
+    if (a.rank == 1 && a.d_in <= 512) return false;
     return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
 }
 

@@ -130,14 +130,14 @@ int launch_schedule(void *workspace, const int32_t *seg_start, const int32_t *se
 // ------------------------------------------------------------------------------------
 // tile-kernel dispatch
 // ------------------------------------------------------------------------------------
-template <int NB, bool DIREFT, bool ODD>
+template <int NB, bool DIREFT, bool ODD, int RK = 0>
 void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
 {
     const unsigned tiles = likely_units(a, S);                // a multiple of 8 (col_split is 1 here)
     if constexpr (DIREFT) {
         const bool few = small_in_place_few(a, S);
-        void (*kernel)(ApplyArgs, SmallLaunch) = few ? small_tile_kernel<NB, true, ODD, true> : small_tile_kernel<NB, true, ODD, true, SMALL_WAVES, false>;
-        if (a.h_layers) kernel = few ? small_tile_layers_kernel<NB, ODD, true> : small_tile_layers_kernel<NB, ODD, false>;
+        void (*kernel)(ApplyArgs, SmallLaunch) = few ? small_tile_kernel<NB, true, ODD, true, SMALL_WAVES, true, RK> : small_tile_kernel<NB, true, ODD, true, SMALL_WAVES, false, RK>;
+        if (a.h_layers) kernel = few ? small_tile_layers_kernel<NB, ODD, true, RK> : small_tile_layers_kernel<NB, ODD, false, RK>;
         hipLaunchKernelGGL(kernel, dim3(tiles, a.n_layers), dim3(SMALL_WAVES * 64), 0, stream, a, SmallLaunch{1, 0});
     } else {
         const SmallShape shape = small_shape(a, S, n_slices, k);
@@ -146,27 +146,32 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
         const SmallLaunch l = {shares_of(a.d_out), n_slices > 1 ? shares_of(a.more[0].d_out) : 0};
         const int shares = l.shares0 + l.shares1 + (n_slices > 2 ? shares_of(a.more[1].d_out) : 0);     // small_shape: 1536 at most
         a.col_split = shape.units;
-        void (*kernel)(ApplyArgs, SmallLaunch) = small_tile_kernel<NB, false, ODD, true>;
-        if constexpr (NB == 1) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false>; }
+        void (*kernel)(ApplyArgs, SmallLaunch) = small_tile_kernel<NB, false, ODD, true, SMALL_WAVES, true, RK>;
+        if constexpr (NB == 1) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false, SMALL_WAVES, true, RK>; }
         if constexpr (NB > 2) { if (shape.waves == 4) kernel = small_tile_kernel<NB, false, ODD, true, 4>; }
         const unsigned slots = tiles / 8 < 65535 ? tiles / 8 : 65535;
         hipLaunchKernelGGL(kernel, dim3((unsigned)shares * 8, slots), dim3(shape.waves * 64), 0, stream, a, l);
     }
 }
 
-// ranks 4..128, in place 4..64
+// ranks 1..128, in place 1..64
 template <bool DIREFT>
 void launch_small(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
 {
     auto launch = [&](auto odd_tag) {
         constexpr bool ODD = decltype(odd_tag)::value;
-        if (a.rank <= 16)      launch_small_shape<1, DIREFT, ODD>(a, S, n_slices, k, stream);
+        if (a.rank <= 8)       launch_small_shape<1, DIREFT, ODD, 8>(a, S, n_slices, k, stream);
+        else if (a.rank <= 16) launch_small_shape<1, DIREFT, ODD>(a, S, n_slices, k, stream);
         else if (a.rank <= 32) launch_small_shape<2, DIREFT, ODD>(a, S, n_slices, k, stream);
         else if (a.rank <= 64) launch_small_shape<4, DIREFT, ODD>(a, S, n_slices, k, stream);
         else if constexpr (!DIREFT) launch_small_shape<8, false, ODD>(a, S, n_slices, k, stream);
     };
-    if (a.rank % 4) launch(std::integral_constant<bool, true>{});
-    else            launch(std::integral_constant<bool, false>{});
+    if (a.rank == 1)       launch_small_shape<1, DIREFT, false, 1>(a, S, n_slices, k, stream);
+    else if (a.rank == 2)  launch_small_shape<1, DIREFT, false, 2>(a, S, n_slices, k, stream);
+    else if (a.rank == 3)  launch_small_shape<1, DIREFT, false, 3>(a, S, n_slices, k, stream);
+    else if (a.rank == 4)  launch_small_shape<1, DIREFT, false, 4>(a, S, n_slices, k, stream);
+    else if (a.rank % 4)   launch(std::integral_constant<bool, true>{});
+    else                   launch(std::integral_constant<bool, false>{});
 }
 
 // the row-split kernel takes whole chunks only
@@ -881,6 +886,7 @@ int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipSt
         break;
     }
     case Path::Valu:
+        if (takes_small(a, S, a.d_out, DIREFT, k)) { launch_small<DIREFT>(a, S, 1, k, stream); break; }
         if constexpr (!DIREFT) {
             if (a.rank <= 3 && launch_valu_split<1>(a, S, k, stream)) break;
         }

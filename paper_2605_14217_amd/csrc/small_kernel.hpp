@@ -48,12 +48,19 @@ struct SmallOutput {                                          // the output of a
     const void *const *A_pool, *const *Bt_pool;
 };
 
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, int NG>
+// RK: 0, or what is known of a rank up to 8: 1, 2, 3 are that rank, 4 is rank 4, 8 the ranks 5 to 8.  An instruction brings four ranks of a unit of A:
+// ranks up to 4 and up to 8 leave out three and two of the four.  Ranks 1-3 are too thin for the matrix cores' expand, and z stays
+// in fp32: the sums of valu_tile_kernel, a lane's 8 columns of its rows, whose factors are RK 16-byte pieces.
+// Before / now, replayed, us: 32 decode rows of 32 adapters, a layer's six launches, rank 1 64.5 / 28.1, 3 118 / 33.5 (valu_tile_kernel: 16 rows of a tile on four wavefronts),
+// 8 44.1 / 40.8; rank 4, 4096 -> 4096 5.7 / 4.8; 1000 prompt rows, rank 3, 4096 -> 2 x 14336 75 / 27; in place, d = 4096, rank 1 5.8 / 4.8, 3 7.3 / 5.4, 8 7.9 / 7.4.
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, int NG, int RK>
 __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallOutput &o, const i32x4_t entry, bool gathered, int row0, int n_rows,
                                                 u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD>()], float (&red)[WAVES * NB * 4 * 64])
 {
     constexpr bool ANY = ODD && NB > 1;                       // ranks above 16 that are no multiple of 4
-    constexpr bool DIRECT = small_direct<NB, DIREFT, ODD>(NG);
+    constexpr bool DIRECT = small_direct<NB, DIREFT, ODD>(NG), THIN = RK >= 1 && RK <= 3;
+    constexpr int AG = RK == 0 ? 4 : RK <= 4 ? 1 : 2;         // groups of four ranks in a unit of A
+    static_assert(RK == 0 || NB == 1, "one rank block");
     // units of the shrink and of the expand sweep in flight (registers)
     constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : 2;
     // units of the expand that are asked for before the shrink's last ones are used (registers).  With that, waits for one unit at a time (sweep below) and
@@ -102,8 +109,8 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     const int ubase = DIREFT ? 0 : share * per_share, uend = DIREFT ? c_units : min(ubase + per_share, c_units);
     const int y_last = d_out * 2 - 16;
     u32x4_t Y[DEPTH][NG];
-    u32x2_t W[DIRECT ? 1 : DEPTH][W_LATE || DIRECT ? 1 : 4][2][NB];
-    u32x4_t Wb[DIRECT ? DEPTH : 1][PIECES];
+    u32x2_t W[DIRECT || THIN ? 1 : DEPTH][W_LATE || DIRECT || THIN ? 1 : 4][2][NB];
+    u32x4_t Wb[DIRECT || THIN ? DEPTH : 1][THIN ? RK : PIECES];
     auto load_w = [&](u32x2_t (&w)[2][NB], int u, int s) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
@@ -121,7 +128,11 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         const int off = min(u * 256 + c16 * 16, y_last);
 #pragma unroll
         for (int i = 0; i < NG; ++i) Y[k][i] = ld16(yu[i] + off);
-        if constexpr (DIRECT) {                               // the unit's [128 columns][r] block, contiguous
+        if constexpr (THIN) {                                 // the lane's 8 columns (past the width: the last 8)
+            gcptr_t wp = Bt + (int64_t)(off >> 4) * (16 * RK);
+#pragma unroll
+            for (int j = 0; j < RK; ++j) Wb[k][j] = ld16(wp + j * 16);
+        } else if constexpr (DIRECT) {                        // the unit's [128 columns][r] block, contiguous
             const int last = last_factor_piece(d_out - u * 128, 128, r);
 #pragma unroll
             for (int j = 0; j < PIECES; ++j) Wb[k][j] = ld16(Bt + (int64_t)u * 256 * r + min(min(lane + 64 * j, 16 * r - 1), last) * 16);
@@ -149,9 +160,9 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     {
         const int x_last = p.d_in * 2 - 16;                   // a row's last 16-byte piece; d_in % 8 == 0
         const int k_units = (p.d_in + 127) >> 7;
-        auto load_a = [&](u32x4_t (&a)[4], int b, int off) {
+        auto load_a = [&](u32x4_t (&a)[AG], int b, int off) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)                       // ranks past r alias the last one: their z is zeroed
+            for (int i = 0; i < AG; ++i)                      // ranks past r alias the last one: their z is zeroed
                 a[i] = ld16(A + (uint32_t)(min(16 * b + 4 * i + q, r - 1) * (x_last + 16) + off));
         };
         constexpr int HALVES = BATCH > 1 ? 2 : 1, H = BATCH / HALVES;
@@ -176,7 +187,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
                         for (int i = 0; i < NG; ++i) x[k][i] = u32x4_t{0u, 0u, 0u, 0u};
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
+                        for (int i = 0; i < AG; ++i)
 #pragma unroll
                             for (int b = 0; b < NB; ++b) a[k][b][i] = u32x4_t{0u, 0u, 0u, 0u};
                     }
@@ -188,9 +199,9 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) tra[(4 * i + q) * MFMA_TRS + c16] = a[k][b][i];
+                        for (int i = 0; i < AG; ++i) tra[(4 * i + q) * MFMA_TRS + c16] = a[k][b][i];
 #pragma unroll
-                        for (int s = 0; s < 4; ++s) ao[s] = tra[rl * MFMA_TRS + 4 * s + g];
+                        for (int s = 0; s < 4; ++s) ao[s] = tra[(rl & (4 * AG - 1)) * MFMA_TRS + 4 * s + g];
 #pragma unroll
                         for (int s = 0; s < 4; ++s)
                             acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ao[s]), as_bf16x8(xo[s]), acc[b], 0, 0, 0);
@@ -201,7 +212,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         // used), so a wait is for its own unit and the others go on arriving.
         auto sweep = [&](auto b_tag) {
             constexpr int B = decltype(b_tag)::value;
-            u32x4_t xr[B][1][NG], ar[B][1][NB][4];
+            u32x4_t xr[B][1][NG], ar[B][1][NB][AG];
             auto ask = [&](int k, int u) { request(xr[k], ar[k], min(u, k_units - 1), std::true_type{}); };
 #pragma unroll
             for (int k = 0; k < B; ++k) ask(k, wave + k * WAVES);
@@ -223,7 +234,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             else sweep(std::integral_constant<int, BATCH>{});
         } else if constexpr (HALVES == 2) {
             // two halves of a batch take turns: one is on its way while the other is used
-            u32x4_t xr[2][H][NG], ar[2][H][NB][4];
+            u32x4_t xr[2][H][NG], ar[2][H][NB][AG];
             request(xr[0], ar[0], wave, std::false_type{});
             request(xr[1], ar[1], wave + H * WAVES, std::false_type{});
             int u = wave;
@@ -236,7 +247,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             use(xr[0], ar[0], u);
             use(xr[1], ar[1], u + H * WAVES);
         } else {
-            u32x4_t xr[1][H][NG], ar[1][H][NB][4];
+            u32x4_t xr[1][H][NG], ar[1][H][NB][AG];
             for (int u = wave; u < k_units; u += H * WAVES) {
                 request(xr[0], ar[0], u, std::false_type{});
                 use(xr[0], ar[0], u);
@@ -249,7 +260,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     const FactorLds<DIRECT ? NB : 1> fl(r);
     char *const fw = reinterpret_cast<char *>(area[wave]);
     auto park = [&](int k) {                                  // a unit's factors to LDS
-        if constexpr (DIRECT) {
+        if constexpr (DIRECT && !THIN) {
 #pragma unroll
             for (int j = 0; j < PIECES; ++j) {
                 const int piece = min(lane + 64 * j, 16 * r - 1);
@@ -281,6 +292,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     __syncthreads();                                          // also: every read of the tile precedes every write (in place: a unit belongs to one wavefront)
     // DIRECT, up to four rows: those stand in rows 0, 4, 8, 12 of the operand, so that a lane's accumulators begin with its own row
     const int zlane = DIRECT && NG == 1 ? (rl >> 2) + 16 * g : lane;
+    float zt[NG][THIN ? RK : 1];
     bf16x8_t zop[NB];
     u32x4_t zlow[ANY ? NB / 2 : 1];                           // what two parts of bf16 leave of z (whole_z), two rank blocks in one operand
 #pragma unroll
@@ -288,7 +300,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         const int rank0 = 16 * b + 4 * g;
         float zv[4], rem[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < (THIN ? RK : 4); ++v) {
             float s = 0.f;
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) s += red[((w * NB + b) * 4 + v) * 64 + zlane];
@@ -297,7 +309,12 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             zv[v] = rank0 + v < r ? (s + add) * p.scale : 0.f;
             rem[v] = zv[v] - __uint_as_float((pack_bf16(zv[v], 0.f) & 0xffffu) << 16);
         }
-        if constexpr (ANY) {
+        if constexpr (THIN) {                                 // lanes 0 to 15 hold the rows' z, the lane's rows are slot(i)
+#pragma unroll
+            for (int i = 0; i < NG; ++i)
+#pragma unroll
+                for (int v = 0; v < RK; ++v) zt[i][v] = __shfl(zv[v], slot(i), 64);
+        } else if constexpr (ANY) {
             const WholeZ w = whole_z(zv);
             zop[b] = as_bf16x8(u32x4_t{w.head[0], w.head[1], w.mid[0], w.mid[1]});
             zlow[b / 2][2 * (b % 2)] = w.low[0];
@@ -357,6 +374,30 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         for (int i = 0; i < NG; ++i)
             if (off <= y_last && slot(i) < n_rows) st16_stream(yu[i] + off, Y[k][i]);
     };
+    auto finish_thin = [&](int k, int u) {
+        float w[8 * RK + 1];
+#pragma unroll
+        for (int j = 0; j < RK; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                w[j * 8 + 2 * e] = bf16_lo(Wb[k][j][e]);
+                w[j * 8 + 2 * e + 1] = bf16_hi(Wb[k][j][e]);
+            }
+        const int off = u * 256 + c16 * 16;
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            float out[8];
+            Elem<bf16_tag>::unpack(Y[k][i], out);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                float d = 0.f;
+#pragma unroll
+                for (int v = 0; v < RK; ++v) d = fmaf(w[c * RK + v], zt[i][v], d);
+                out[c] += d;
+            }
+            if (off <= y_last && slot(i) < n_rows) st16_stream(yu[i] + off, Elem<bf16_tag>::pack(out));
+        }
+    };
     auto finish = [&](int k, int u) {
         u32x4_t yo[4];
 #pragma unroll
@@ -393,7 +434,8 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
         for (int k = 0; k < DEPTH; ++k)
             if (u + k * WAVES < uend) {
-                if constexpr (DIRECT) finish_direct(k, u + k * WAVES);
+                if constexpr (THIN) finish_thin(k, u + k * WAVES);
+                else if constexpr (DIRECT) finish_direct(k, u + k * WAVES);
                 else finish(k, u + k * WAVES);
                 if (u + (k + DEPTH) * WAVES < uend) load_yw(k, u + (k + DEPTH) * WAVES);
             }
@@ -401,7 +443,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 }
 
 // FEW: with the form for tiles of up to four rows (in place only for steps of decode rows: its second copy of the code costs the others 0.1 us of 4.5).
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW>
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW, int RK>
 __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOutput &o, int unit, int n_chunk_units,
                                                u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD>()], float (&red)[WAVES * NB * 4 * 64])
 {
@@ -412,8 +454,8 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOu
         gathered ? as_const(p.gtiles) + (unit - n_chunk_units) : as_const(p.chunks) + unit / (CHUNK_ROWS / 16));
     const int n_rows = min(16, entry[2] - row0);
     if (n_rows <= 0) return;                                  // uniform over the workgroup
-    if (!FEW || n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4>(p, o, entry, gathered, row0, n_rows, area, red);
-    else if constexpr (FEW) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1>(p, o, entry, gathered, row0, n_rows, area, red);
+    if (!FEW || n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4, RK>(p, o, entry, gathered, row0, n_rows, area, red);
+    else if constexpr (FEW) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1, RK>(p, o, entry, gathered, row0, n_rows, area, red);
 }
 
 // A launch out of place: blockIdx.x = 8 share + XCD, blockIdx.y = the slot of a tile on that XCD (in place: blockIdx.x = 8 slot + XCD).  The shares of a
@@ -421,7 +463,7 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOu
 // launch has as many slots as the batch is likely to need; what exceeds it is strided over.
 struct SmallLaunch { int shares0, shares1; };
 
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW>
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW, int RK>
 __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallLaunch &l)
 {
     __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, ODD>()];
@@ -447,26 +489,26 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallL
     const int per_xcd = (n_units + 7) >> 3;
     for (int t = DIREFT ? blockIdx.x >> 3 : blockIdx.y; t < per_xcd; t += DIREFT ? gridDim.x >> 3 : gridDim.y) {
         const int unit = few_tiles_unit(p, n_chunk_units, per_xcd, t);
-        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES, FEW>(p, o, unit, n_chunk_units, area, red);
+        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES, FEW, RK>(p, o, unit, n_chunk_units, area, red);
         __syncthreads();                                      // the next tile's sums go where this one's are still being read
     }
 }
 
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES = SMALL_WAVES, bool FEW = true>
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES = SMALL_WAVES, bool FEW = true, int RK = 0>
 __global__ __launch_bounds__(WAVES * 64, DEEP ? 2 : 4) void small_tile_kernel(ApplyArgs p, SmallLaunch l)
 {
-    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES, FEW>(p, l);
+    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES, FEW, RK>(p, l);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer
-template <int NB, bool ODD, bool FEW>
+template <int NB, bool ODD, bool FEW, int RK = 0>
 __global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(ApplyArgs p, SmallLaunch l)
 {
     // beside the layer's pointers, not after them (8 layers, d = 512, 220 rows 7.7 us, now 7.3; 4 layers, d = 1024, 600 rows 7.4 / 7.1)
     // (above rank 32 there are no registers for that: 8 layers, rank 64, d = 1024, 400 rows 21.9 / 24.2)
     if constexpr (NB <= 2) asm volatile("" ::"s"(p.rank), "s"(p.d_out), "s"(p.col_split), "s"(p.header), "s"(p.T));
     select_layer(p);
-    small_tile_body<NB, true, ODD, true, SMALL_WAVES, FEW>(p, l);
+    small_tile_body<NB, true, ODD, true, SMALL_WAVES, FEW, RK>(p, l);
 }
 
 }  // namespace preft

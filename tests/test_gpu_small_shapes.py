@@ -138,3 +138,43 @@ def test_shrink_of_few_rows(rank, d_in):
     y0 = wl.activations(tab.T, 392, "bf16", device="cuda", seed=2)
     run_lora_case(tab, wl.lora_pool(N, rank, d_in, 392, "bf16", device="cuda", seed=3), x, y0, "bf16", 2.0, True, pad_cols=8)
     run_direft_case(tab, wl.direft_pool(N, rank, d_in, "bf16", device="cuda", seed=4), x, "bf16", 0.5, True, pad_cols=8)
+
+
+@pytest.mark.parametrize("rank", [1, 2, 3, 4, 5, 8])
+@pytest.mark.parametrize("d_in,d_outs", [(264, (1032,)), (4104, (512,)), (1000, (520, 8, 2056)), (6152, (4096,))])
+def test_small_ranks(rank, d_in, d_outs):
+    """Ranks up to 8, of whose first factor a wavefront loads one or two groups of four ranks, and ranks 1-3, whose expand runs on the vector ALU: tiles of one
+    to sixteen rows, prompts and decode rows, out of place and in place (one layer and several), infinite factors of one adapter, against the oracle."""
+    from oracle import preft_oracle as ora
+    from parity_util import check_guards, compare, dev_tables, lora_pools_to_device, padded, run_direft_case, run_direft_layers_case
+    N, counts, prompts = 9, [1, 4, 5, 16], [17, 20, 36, 130]
+    lens = np.array([1] * sum(counts) + prompts)
+    ids = np.concatenate([np.repeat(np.arange(4), counts), 4 + np.arange(4)]).astype(int)
+    order = np.random.Generator(np.random.PCG64(rank + d_in)).permutation(len(lens))
+    tab = wl.from_lengths(lens[order], ids[order], np.where(lens > 1, lens, 0)[order])
+    T = tab.T
+    ss, sa, sp = dev_tables(tab)
+    x = wl.activations(T, d_in, "bf16", device="cuda", seed=1)
+    y0s = [wl.activations(T, n, "bf16", device="cuda", seed=2 + i) for i, n in enumerate(d_outs)]
+    pools = [wl.lora_pool(N, rank, d_in, n, "bf16", device="cuda", seed=9 + i) for i, n in enumerate(d_outs)]
+    tables = [lora_pools_to_device(pl) for pl in pools]
+    for mode, pos in ((preft.PREFT_ALL_TOKENS, ora.ALL_POSITIONS), (preft.PREFT_PREFILL_ONLY, ora.PROMPT_ONLY)):
+        bufs = [padded(y, 8, 7.0) for y in y0s]
+        preft.preft_lora_apply_packed([b[1] for b in bufs], x, ss, sa, sp, [t[0] for t in tables], [t[1] for t in tables], rank, 2.0, mode, preft.new_workspace(T, tab.S))
+        owner = ora.positions(T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, pos)
+        for (buf, y), y0, pl in zip(bufs, y0s, pools):
+            check_guards(buf, T, y0.shape[1], 7.0)
+            want = ora.lora(y0.cpu(), x.cpu(), tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, [a.cpu() for a in pl.A], [b.cpu() for b in pl.B], rank, 2.0, pos)
+            compare(y, y0, want, owner, "bf16")
+        run_direft_case(tab, wl.direft_pool(N, rank, d_in, "bf16", device="cuda", seed=4), x, "bf16", 0.5, pos == ora.ALL_POSITIONS, pad_cols=8)
+    run_direft_layers_case(tab, [wl.direft_pool(N, rank, d_in, "bf16", device="cuda", seed=l) for l in range(2)],
+                           [wl.activations(T, d_in, "bf16", device="cuda", seed=9 + l) for l in range(2)], "bf16", 0.5, True, [True, False], pad_cols=8)
+    # an infinite factor makes infinities where its product with z does not vanish, never NaN, and only in its own adapter's rows
+    pools[0].B[4][:] = float("inf")
+    A, B, keep = lora_pools_to_device(pools[0])
+    y = y0s[0].clone()
+    preft.preft_lora_apply(y, x, ss, sa, sp, A, B, rank, 2.0, preft.PREFT_ALL_TOKENS, preft.new_workspace(T, tab.S))
+    mine = torch.from_numpy(ora.positions(T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, ora.ALL_POSITIONS) == 4).cuda()
+    assert bool(torch.isfinite(y[~mine]).all()) and not bool(torch.isfinite(y[mine]).any())
+    if rank == 1:
+        assert bool(torch.isinf(y[mine]).all())
