@@ -99,7 +99,7 @@ enum {
  *   PREFT_TEST_ROWBLOCKS(b)  MFMA kernels: 16-row blocks per wavefront: 0 = automatic, 1 or 2
  *   PREFT_TEST_COLSPLIT(c)   LoRA, matrix cores: workgroups that share a tile of one output, each writing its share
  *                            of the output columns (the small-batch kernel): 0 = automatic (that kernel for
- *                            batches of up to 1024 rows), 1 = the kernels of larger batches, 2..15 (fp32: 1..15).
+ *                            batches of up to 1024 rows and, at rank 1..16, a few thousand), 1 = the kernels of larger batches, 2..15 (fp32: 1..15).
  *                            Together with variant 4 it names the column groups of the row-split kernel
  *                            instead: 0 = automatic, 1 or 2
  *   PREFT_TEST_RESIDENT(n)   0 = automatic.  LoRA, and in place at rank 33..64: 1 = two launches (preft_workspace_bytes_z)

@@ -82,15 +82,33 @@ inline bool mfma_takes(const ApplyArgs &a, const Knobs &k)
 constexpr int32_t SMALL_T = 1024;
 constexpr int64_t DEEP_WGS = 200;                             // at most one workgroup per compute unit, with room for a poor estimate
 
-// `widest`: columns of the widest output
-inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, bool direft, const Knobs &k)
+// Up to rank 16 the small-batch kernel stays ahead of the two launches (and of the single ones) beyond SMALL_T rows as long as the call is no long stream: the
+// elements of x, of y twice and of the factors of the likely adapters.  What then costs it is that the shares of a tile repeat its shrink.  Two launches (or one) / this kernel, us:
+// rank 16, 2000 rows of prompts of 400 beside 32 adapters, 512 -> 2072 (9 million elements) 8.3 / 7.1, 4096 -> 4096 (27) 17.0 / 13.9, 14336 -> 4096 (51) 30.9 / 22.9, 8192 -> 8192 (58)
+// 27.1 / 28.2, 4096 -> 2 x 14336 (127) 51.7 / 69.8; 5000 rows, 4096 -> 512 16.4 / 13.2, 4096 -> 4096 (64) 31.9 / 24.2, 1024 -> 4096 + 2 x 1024 (68) 33.6 / 27.5, 14336 -> 4096 (118)
+// 57.2 / 65.4, 8192 -> 8192 (127) 53.2 / 67.0; 2200 rows of prompts of 55, 4096 -> 4096 24.5 / 15.1; 2000 decode rows of 64 adapters, 8192 -> 8192 (65) 32.6 / 24.2, of 500, 4096 -> 512 (46)
+// 22.2 / 17.5, 4096 -> 4096 (89) 32.0 / 32.3, 1024 -> 4096 + 2 x 1024 (82) 35.0 / 40.9.  Ranks 8 and 11 alike.  Rank 3, 5000 rows, 4096 -> 4096 31.1 / 21.3, 8192 -> 8192 51.7 / 56.0; 4000
+// decode rows of 64 adapters, 4096 -> 2 x 14336 (265) 136 / 119; rank 1, 2000 of 500, 4096 -> 512 7.7 / 9.0.
+constexpr int32_t SMALL_STREAM_T = 6144;
+inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
+{
+    if (a.rank > 16 || a.T > SMALL_STREAM_T) return false;
+    const int64_t d = a.d_in, singles = a.all_tokens && a.T < 2 * S;
+    if (a.rank <= 2 && singles && 8 * width <= d) return false;
+    const int64_t elements = a.T * (d + 2 * width) + likely_adapters(S, a.N) * a.rank * (d + width);
+    const int64_t most = a.rank < 4 && singles ? 180000000 : d >= 8192 && width >= 8192 && a.T >= 64 * S ? 48000000 : 76000000;
+    return elements <= most;
+}
+
+// `widest`: columns of the widest output, `width`: of all outputs
+inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t width, bool direft, const Knobs &k)
 {
     if (a.rank < 4 && (k.variant || k.colsplit)) return false;            // those name the vector-ALU kernel there
     if (a.d_in > (1 << 22) || widest > (1 << 22)) return false;          // offsets within a row or a factor, and the launch, fit 32 bits
     if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
     if (!direft && k.colsplit) return k.colsplit > 1;
+    if (!direft) return a.T <= SMALL_T || (k.variant == 0 && no_long_stream(a, S, width));
     if (a.T > SMALL_T) return false;
-    if (!direft) return true;
     // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 1000
     // rows 11.4 and 13.1 us; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
     // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81)

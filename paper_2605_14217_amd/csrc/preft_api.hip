@@ -881,12 +881,12 @@ int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipSt
         launch_f32<DIREFT>(a, S, k, stream);
         break;
     case Path::Mfma: {                     // the tile kernels take chunks and gathered tiles alike
-        if (takes_small(a, S, a.d_out, DIREFT, k)) launch_small<DIREFT>(a, S, 1, k, stream);
+        if (takes_small(a, S, a.d_out, a.d_out, DIREFT, k)) launch_small<DIREFT>(a, S, 1, k, stream);
         else                           launch_mfma_rank<DIREFT>(a, S, k, stream);
         break;
     }
     case Path::Valu:
-        if (takes_small(a, S, a.d_out, DIREFT, k)) { launch_small<DIREFT>(a, S, 1, k, stream); break; }
+        if (takes_small(a, S, a.d_out, a.d_out, DIREFT, k)) { launch_small<DIREFT>(a, S, 1, k, stream); break; }
         if constexpr (!DIREFT) {
             if (a.rank <= 3 && launch_valu_split<1>(a, S, k, stream)) break;
         }
@@ -1069,8 +1069,9 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
     const bool fused_mfma = n_proj > 1 && dtype == PREFT_BF16 && rank >= 4 && rank <= 16 &&
                             (k.variant == 0 || k.variant == 3 || k.variant == 5) && column_split_fits(a);
     int32_t widest = 0;
-    for (int32_t i = 0; i < n_proj; ++i) if (d_out[i] > widest) widest = d_out[i];
-    const bool fused_small = n_proj > 1 && dtype == PREFT_BF16 && takes_small(a, S, widest, false, k);
+    int64_t width = 0;
+    for (int32_t i = 0; i < n_proj; ++i) { width += d_out[i]; if (d_out[i] > widest) widest = d_out[i]; }
+    const bool fused_small = n_proj > 1 && dtype == PREFT_BF16 && takes_small(a, S, widest, width, false, k);
     const bool fused = fused_small || fused_mfma || fused_valu || fused_wide;
     if (!fused) {                                  // same result, one launch per projection
         for (int32_t i = 0; i < n_proj; ++i) {
