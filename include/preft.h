@@ -92,7 +92,8 @@ enum {
  *                                through LDS where it applies (rank a multiple of 4 or above
  *                                16, widths multiples of 128), and no register-resident DiReFT
  *                            5 = automatic, but both sweeps of a call in one launch, LoRA or in
- *                                place, even if the workspace has room for z (preft_workspace_bytes_z)
+ *                                place, even if the workspace has room for z (preft_workspace_bytes_z); above 1024 rows
+ *                                those of the kernels of larger batches
  *   PREFT_TEST_WAVES(w)      wavefronts per tile workgroup: 0 = automatic, else 1, 2, 4 or 8
  *                            (any non-zero value also makes DiReFT stream its tile instead
  *                            of holding it in registers)
@@ -102,8 +103,10 @@ enum {
  *                            batches of up to 1024 rows and, at rank 1..16, a few thousand), 1 = the kernels of larger batches, 2..15 (fp32: 1..15).
  *                            Together with variant 4 it names the column groups of the row-split kernel
  *                            instead: 0 = automatic, 1 or 2
- *   PREFT_TEST_RESIDENT(n)   0 = automatic.  LoRA, and in place at rank 33..64: 1 = two launches (preft_workspace_bytes_z)
- *                            wherever that form exists, whatever the batch size.  In-place
+ *   PREFT_TEST_RESIDENT(n)   0 = automatic.  LoRA, and in place at rank 33..128: 1 = two launches (preft_workspace_bytes_z)
+ *                            of the kernels of larger batches wherever that form exists, whatever the batch size.  Rank
+ *                            20..128 in multiples of 4: 2 = the small-batch kernel at any batch size, as two launches
+ *                            where the workspace has room for z.  In-place
  *                            MFMA kernel at rank 20..32 (automatic: 32-row tiles streamed in
  *                            both sweeps): 3 = every wavefront keeps 8 of its
  *                            128-column units in registers between the sweeps (half of a
@@ -147,12 +150,13 @@ size_t preft_workspace_bytes(int32_t T, int32_t S);
 /*
  * Bytes of a workspace that, beyond the schedule, has room for the intermediate z = A_i x of Eq. 2 of
  * every active row: LoRA calls of up to `rank` with up to n_proj outputs per call, or in-place calls (preft_direft_apply,
- * preft_loreft_apply) of up to `rank`.  A bf16 LoRA call of
- * rank 1..64 (above rank 16: d_in and every d_out a multiple of 128) on a batch of more than 1024 rows
+ * preft_loreft_apply) of up to `rank`.  A bf16 LoRA call
  * that is handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the
- * expand in 2-D tiles -- where that is faster: wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
- * 1100), and every shape above rank 16 (up to 5x on 1100 rows); not on a step of decode rows that has nothing to apply.
- * So does a bf16 in-place call of rank 33..64, d a multiple of 128, where that is faster (d >= 4096: 5 to 50 % less time).
+ * expand in 2-D tiles -- where that is faster: on more than 1024 rows wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
+ * 1100), and nearly every shape above rank 16; above rank 32 smaller batches too (rank 64, 4096 -> 4096, 900 rows: half
+ * the time); not on a step of decode rows that has nothing to apply.
+ * So does a bf16 in-place call above rank 32 where that is faster (d = 4096, 900 rows: rank 64 in two fifths of the time, rank 128 in a seventh),
+ * and on rows of 8192 and more from rank 17 on.
  * With fewer bytes, or outside those limits,
  * the same call runs in one launch.  The result is the same bit for bit.
  * The z area lies behind the schedule and is rewritten by every such call: calls that

@@ -33,13 +33,18 @@ inline int64_t likely_adapters(int64_t n, int64_t N)
 
 // How many 16-row tiles a batch is likely to have.  Rows in excess of one per segment belong to prompts: a prompt ends in a
 // partial tile; the other segments, where every position counts, are gathered by adapter, which ends in a partial tile each.
-inline int64_t likely_tiles(const ApplyArgs &a, int64_t S)
+inline int64_t likely_gathered(const ApplyArgs &a, int64_t S)
 {
     const int64_t extra = a.T > S ? a.T - S : 0, prompts = S < extra / 16 + 1 ? S : extra / 16 + 1;
     int64_t singles = a.all_tokens ? (a.T < S ? a.T : S) - (extra ? prompts : 0) : 0;
     if (singles < 0) singles = 0;
     const int64_t owners = likely_adapters(singles, a.N), gathered = singles / 16 + owners / 2;
-    return extra / 16 + (extra ? prompts / 2 + 1 : 0) + (gathered > owners ? gathered : owners);
+    return gathered > owners ? gathered : owners;
+}
+inline int64_t likely_tiles(const ApplyArgs &a, int64_t S)
+{
+    const int64_t extra = a.T > S ? a.T - S : 0, prompts = S < extra / 16 + 1 ? S : extra / 16 + 1;
+    return extra / 16 + (extra ? prompts / 2 + 1 : 0) + likely_gathered(a, S);
 }
 
 // Small batches take a kernel of their own (small_kernel.hpp).
@@ -51,7 +56,7 @@ inline int64_t prompt_rows(const ApplyArgs &a, int64_t S) { return a.T > S ? a.T
 // that all-position rows can make, and a few of prompts' short ends.
 inline unsigned likely_units(const ApplyArgs &a, int64_t S)
 {
-    const int64_t rows = prompt_rows(a, S), chunks = rows ? rows / CHUNK_ROWS + (rows / 16 < S ? rows / 16 : S) + 2 : 0;
+    const int64_t rows = a.gathered_only ? 0 : prompt_rows(a, S), chunks = rows ? rows / CHUNK_ROWS + (rows / 16 < S ? rows / 16 : S) + 2 : 0;
     const int64_t gathered = gtile_capacity(a.T, S, a.N), units = chunks * (CHUNK_ROWS / 16) + (a.all_tokens || gathered < 8 ? gathered : 8);
     const unsigned bound = tile_grid(a, S, 16), likely = (unsigned)((units + 7) / 8 * 8);
     return likely < bound ? likely : bound;
@@ -80,6 +85,7 @@ inline bool mfma_takes(const ApplyArgs &a, const Knobs &k)
 }
 
 constexpr int32_t SMALL_T = 1024;
+constexpr int32_t SMALL_WIDTH = 1 << 22;                      // offsets within a row or a factor, and the launch, fit 32 bits
 constexpr int64_t DEEP_WGS = 200;                             // at most one workgroup per compute unit, with room for a poor estimate
 
 // Up to rank 16 the small-batch kernel stays ahead of the two launches (and of the single ones) beyond SMALL_T rows as long as the call is no long stream: the
@@ -92,7 +98,15 @@ constexpr int64_t DEEP_WGS = 200;                             // at most one wor
 constexpr int32_t SMALL_STREAM_T = 6144;
 inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
 {
-    if (a.rank > 16 || a.T > SMALL_STREAM_T) return false;
+    if (a.rank > 16) {
+        if (a.rank % 4) return false;
+        const bool ragged = a.d_in % 128 || width % 128;      // (not each width: packed calls with one ragged output have the others wide)
+        if (a.rank <= 48 && a.d_in < 2048 && a.all_tokens && a.T < 2 * S) return false;
+        if (a.rank > 32 && ragged) return true;
+        if (a.T <= 4096) return true;
+        return a.T <= SMALL_STREAM_T && a.d_in >= 2048 && (a.rank <= 32 || width <= 16384) && a.rank <= 64;
+    }
+    if (a.T > SMALL_STREAM_T) return false;
     const int64_t d = a.d_in, singles = a.all_tokens && a.T < 2 * S;
     if (a.rank <= 2 && singles && 8 * width <= d) return false;
     const int64_t elements = a.T * (d + 2 * width) + likely_adapters(S, a.N) * a.rank * (d + width);
@@ -104,7 +118,8 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
 inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t width, bool direft, const Knobs &k)
 {
     if (a.rank < 4 && (k.variant || k.colsplit)) return false;            // those name the vector-ALU kernel there
-    if (a.d_in > (1 << 22) || widest > (1 << 22)) return false;          // offsets within a row or a factor, and the launch, fit 32 bits
+    if (a.d_in > SMALL_WIDTH || widest > SMALL_WIDTH) return false;
+    if (k.resident == 2 && a.rank > 16 && a.rank % 4 == 0) return true;
     if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
     if (!direft && k.colsplit) return k.colsplit > 1;
     if (!direft) return a.T <= SMALL_T || (k.variant == 0 && no_long_stream(a, S, width));
@@ -113,7 +128,8 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     // rows 11.4 and 13.1 us; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
     // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81)
     if (likely_tiles(a, S) > 200) return false;               // whatever n_layers: a layer's result is that of its one-layer call, bit for bit
-    if (a.rank > 16) return a.rank <= 64;                     // above, its registers spill: rank 128, d = 6320, 77 rows 123 and 130 us
+    if (a.rank > 64) return a.rank % 4 == 0;
+    if (a.rank > 16) return true;
     // A few decode rows of an adapter each: tiles of which this kernel loads a quarter.  Rank 16, 32 rows of 32 adapters, resident / this, us: d = 4096 9.2 /
     // 8.2, 8192 14.8 / 13.2, 8 layers of 4096 17.5 / 13.6; rank 7, 8192 17.5 / 15.3; d = 14336 (streamed) 27.6 / 22.4; but 256 rows of 200 adapters
     // 12.5 / 13.6, of 32 10.4 / 11.0, and 8 layers of 46 tiles, more than a tile for every compute unit, 22.0 / 25.0.
@@ -129,6 +145,27 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
 
 // In place its form for tiles of up to four rows runs for steps of decode rows alone (others pay 0.1 of 4.5 us for a second copy of the code).
 inline bool small_in_place_few(const ApplyArgs &a, int64_t S) { return a.all_tokens && prompt_rows(a, S) == 0; }
+
+// Whether a call of the small-batch kernel's order at rank 17 and up (multiples of 4) runs its sweeps as two launches: then a tile's shrink is not repeated
+// by every share of its columns, and the expand shares its factors among 32 or 64 rows.  `width`: of all outputs.
+inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool direft, const Knobs &k)
+{
+    if (a.rank <= 16 || a.rank % 4 || k.variant == 5 || k.colsplit) return false;
+    if (k.resident == 2) return true;
+    const bool singles = a.T < 2 * S;
+    if (!a.all_tokens && prompt_rows(a, S) < 64) return false;            // hardly a row to do
+    if (a.T > SMALL_T) return true;
+    const int64_t tiles = likely_tiles(a, S), panels = tiles * width;
+    if (direft) return a.rank > 64 || (a.rank > 48 ? a.d_in >= 1024 : a.rank > 32 ? a.d_in >= 2048 : a.d_in >= 8192 && tiles <= 48);
+    if (a.rank > 112) return true;
+    if (a.rank > 64) return a.d_in >= 4096 || (!singles && panels >= 100000);
+    if (a.rank > 48) return singles ? (a.d_in >= 4096 && width >= 4096) || panels >= 250000 : panels >= 80000;
+    return a.rank > 32 && !singles && panels >= 150000;
+}
+
+// Out of place its form for tiles of up to four rows is in the kernel where most of the tiles are gathered rows: a second copy of the code costs the others 0.3 to 0.6 us (rank
+// 32, 512 -> 2072, 880 prompt rows 6.1 / 5.5).
+inline bool small_few(const ApplyArgs &a, int64_t S) { return 2 * likely_gathered(a, S) > likely_tiles(a, S); }
 
 // What a workgroup of the small-batch kernel is (out of place): the units of 128 columns it expands, and whether it has
 // the compute unit to itself (deep).

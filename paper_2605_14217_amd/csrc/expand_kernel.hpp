@@ -273,7 +273,8 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 4) void mfma_expand_kernel(Apply
 // Tiles of 128 rows 4400, 890.  Tiles in memory order; dealt to the XCDs as runs 977 for 923, 65 for 67 (with y turned).
 constexpr int PANEL_RW = 4;
 
-template <int NB, int RW, int PU, bool ODD>
+// ANY: any widths (multiples of 8), and gathered tiles too, of which the first wavefront has the rows.
+template <int NB, int RW, int PU, bool ODD, bool ANY = false>
 __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, int n_slices)
 {
     constexpr int R = 16 * RW, NT = RW * 64;
@@ -297,27 +298,33 @@ __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, i
 
         // every request of the tile first: its factors, this row block's z, its units of y (rows past the tile alias its last one)
         gcptr_t Wp = as_global(as_const(t.Bt_pool)[t.entry.x]) + (int64_t)c0 * r * 2;
-        const int w_last = 16 * r * PU - 1;                   // the panel's last piece: lanes past it take it again
+        // the panel's last piece: lanes past it take it again
+        const int w_last = ANY ? last_factor_piece(t.d_out - c0, 128 * PU, r) : 16 * r * PU - 1;
         u32x4_t W[W_ITERS];
 #pragma unroll
         for (int j = 0; j < W_ITERS; ++j) W[j] = ld16(Wp + (uint32_t)(min(tid + j * NT, w_last) * 16));
-        const int rank_blocks = z_rank_blocks(r);             // 33..48: the fourth block is padding, z = 0
+        const int rank_blocks = z_rank_blocks(r);             // more than NB / 2; what is missing of NB is padding, z = 0
         const int zrb = rb * 16 < t.n_rows ? rb : 0;          // row blocks past the tile: any z will do
         gcptr_t zb = as_global(p.zws) + (z_piece(t.block0 + zrb, n_slices, t.sl, rank_blocks, 0) + lane) * 16;
         bf16x8_t zop[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            u32x4_t zv = ld16(zb + (b < NB - 1 ? b : rank_blocks - 1) * 1024);
-            if (b == NB - 1) {
+            u32x4_t zv = ld16(zb + (b <= NB / 2 ? b : min(b, rank_blocks - 1)) * 1024);
+            if (b > NB / 2) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) zv[k] = rank_blocks == NB ? zv[k] : 0u;
+                for (int k = 0; k < 4; ++k) zv[k] = b < rank_blocks ? zv[k] : 0u;
             }
             zop[b] = as_bf16x8(zv);
         }
         gptr_t yu[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            yu[v] = as_global(t.y) + ((int64_t)t.entry.y + t.row0 + min(rb * 16 + 4 * g + v, t.n_rows - 1)) * t.ldy_b + (int64_t)c0 * 2 + n16 * 16;
+        for (int v = 0; v < 4; ++v) {
+            int64_t row = (int64_t)t.entry.y + t.row0 + min(rb * 16 + 4 * g + v, t.n_rows - 1);
+            if constexpr (ANY) { if (t.gathered) row = p.shorts[row].y; }
+            yu[v] = as_global(t.y) + row * t.ldy_b + (int64_t)c0 * 2 + (ANY ? 0 : n16 * 16);
+        }
+        // where the lane's 8 columns of unit u begin (ANY: past the width the last 8, which are not stored again)
+        auto y_off = [&](int u) { return ANY ? min(u * 256 + n16 * 16, (t.d_out - c0) * 2 - 16) : u * 256; };
         const bool mine = rb * 16 < t.n_rows;                 // a short prompt's tile: its other wavefronts only bring factors
         const int rows_left = t.n_rows - rb * 16 - 4 * g;
         u32x4_t Y[PU][4];
@@ -325,7 +332,7 @@ __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, i
 #pragma unroll
             for (int u = 0; u < PU; ++u)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) Y[u][v] = ld16_stream(yu[v] + u * 256);
+                for (int v = 0; v < 4; ++v) Y[u][v] = ld16_stream(yu[v] + y_off(u));
         }
 
         // factors to LDS: as they lie in memory, or in two 8-byte halves per piece, neither of which straddles a column
@@ -361,7 +368,7 @@ __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, i
                         }
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (v < rows_left) st16_stream(yu[v] + u * 256, Y[u][v]);
+                    if (v < rows_left && (!ANY || c0 + u * 128 + n16 * 8 < t.d_out)) st16_stream(yu[v] + y_off(u), Y[u][v]);
             }
         }
         __syncthreads();                                      // the next tile's factors overwrite this one's

@@ -28,6 +28,7 @@ FAMILIES = {            # kernel template -> (header, rough relative compile cos
     "preft::f32_tile_layers_kernel": ("f32_kernel.hpp", 2),
     "preft::small_tile_kernel": ("small_kernel.hpp", 3),
     "preft::small_tile_layers_kernel": ("small_kernel.hpp", 3),
+    "preft::small_shrink_kernel": ("small_kernel.hpp", 3),
     "preft::mfma_expand_kernel": ("expand_kernel.hpp", 1),
     "preft::panel_expand_kernel": ("expand_kernel.hpp", 1),
     "preft::thin_expand_kernel": ("expand_kernel.hpp", 1),

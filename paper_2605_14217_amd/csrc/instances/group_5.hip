@@ -31,21 +31,29 @@ template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, false, 1, false, fa
 template __global__ void preft::mfma_wide_kernel<4, 1, 4, 1, false, 2, true, true, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_kernel<4, 1, 4, 2, false, 1, false, false, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_kernel<4, 1, 8, 1, false, 3, true, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_kernel<8, 1, 8, 1, false, 1, false, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_layers_kernel<1, 1, 8, 1, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_layers_kernel<4, 1, 4, 1, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_wide_layers_kernel<8, 1, 8, 1, true>(preft::ApplyArgs);
-template __global__ void preft::panel_expand_kernel<4, 4, 2, true>(preft::ApplyArgs, int);
-template __global__ void preft::small_tile_kernel<1, false, false, false, 8, true, 3>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_kernel<1, false, false, true, 8, true, 4>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_kernel<1, true, false, true, 8, false, 1>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_kernel<1, true, false, true, 8, true, 2>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_kernel<1, true, true, true, 8, true, 8>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_kernel<4, false, false, true, 4, true, 0>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_kernel<4, true, true, true, 8, true, 0>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_layers_kernel<1, false, true, 0>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_layers_kernel<1, true, false, 8>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::small_tile_layers_kernel<4, false, false, 0>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::mfma_wide_kernel<8, 1, 4, 1, true, 1, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_kernel<8, 1, 8, 1, true, 1, true, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_layers_kernel<1, 1, 4, 2, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_layers_kernel<2, 2, 4, 1, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_wide_layers_kernel<8, 1, 8, 1, false>(preft::ApplyArgs);
+template __global__ void preft::panel_expand_kernel<4, 4, 2, false, true>(preft::ApplyArgs, int);
+template __global__ void preft::small_shrink_kernel<2, true, 0>(preft::ApplyArgs, int);
+template __global__ void preft::small_tile_kernel<1, false, false, false, 8, true, 0, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<1, false, false, true, 8, false, 1, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<1, false, false, true, 8, true, 2, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<1, false, true, false, 8, true, 8, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<1, true, false, true, 8, false, 2, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<1, true, false, true, 8, true, 3, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<2, false, false, true, 8, false, 0, false>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<2, false, false, true, 8, true, 24, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<2, true, true, true, 8, false, 0, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<4, false, true, true, 4, true, 0, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<8, false, false, true, 4, false, 0, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_kernel<8, false, true, true, 8, true, 0, true>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_layers_kernel<1, false, false, 8>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_layers_kernel<1, true, false, 0>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_layers_kernel<2, false, true, 24>(preft::ApplyArgs, preft::SmallLaunch);
+template __global__ void preft::small_tile_layers_kernel<8, false, false, 0>(preft::ApplyArgs, preft::SmallLaunch);
 template __global__ void preft::valu_tile_kernel<1, 4, 1, true, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<1, 4, 4, false, 2, 0, true>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<2, 4, 2, false, 1, 0, false>(preft::ApplyArgs);
@@ -56,7 +64,8 @@ template __global__ void preft::valu_tile_kernel<5, 2, 1, false, 1, 0, false>(pr
 template __global__ void preft::valu_tile_kernel<6, 2, 1, false, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<7, 2, 1, false, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<8, 2, 1, false, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<2, 4, 2, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<4, 4, 1, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<6, 2, 1, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<7, 2, 4, 8>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<1, 4, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<3, 4, 1, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<5, 2, 1, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<6, 2, 4, 8>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<8, 2, 4, 0>(preft::ApplyArgs);

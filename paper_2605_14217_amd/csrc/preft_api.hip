@@ -146,9 +146,15 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
         const SmallLaunch l = {shares_of(a.d_out), n_slices > 1 ? shares_of(a.more[0].d_out) : 0};
         const int shares = l.shares0 + l.shares1 + (n_slices > 2 ? shares_of(a.more[1].d_out) : 0);     // small_shape: 1536 at most
         a.col_split = shape.units;
-        void (*kernel)(ApplyArgs, SmallLaunch) = small_tile_kernel<NB, false, ODD, true, SMALL_WAVES, true, RK>;
-        if constexpr (NB == 1) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false, SMALL_WAVES, true, RK>; }
-        if constexpr (NB > 2) { if (shape.waves == 4) kernel = small_tile_kernel<NB, false, ODD, true, 4>; }
+        auto pick = [&](auto few_tag) {
+            constexpr bool FEW = decltype(few_tag)::value;
+            void (*kernel)(ApplyArgs, SmallLaunch) = small_tile_kernel<NB, false, ODD, true, SMALL_WAVES, FEW, RK>;
+            if constexpr (NB == 2 && !ODD) { if (shape.units < SMALL_WAVES) kernel = small_tile_kernel<NB, false, ODD, true, SMALL_WAVES, FEW, RK, false>; }
+            if constexpr (NB == 1) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false, SMALL_WAVES, FEW, RK>; }
+            if constexpr (NB > 2) { if (shape.waves == 4) kernel = small_tile_kernel<NB, false, ODD, true, 4, FEW>; }
+            return kernel;
+        };
+        void (*kernel)(ApplyArgs, SmallLaunch) = small_few(a, S) ? pick(std::true_type{}) : pick(std::false_type{});
         const unsigned slots = tiles / 8 < 65535 ? tiles / 8 : 65535;
         hipLaunchKernelGGL(kernel, dim3((unsigned)shares * 8, slots), dim3(shape.waves * 64), 0, stream, a, l);
     }
@@ -162,9 +168,10 @@ void launch_small(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, h
         constexpr bool ODD = decltype(odd_tag)::value;
         if (a.rank <= 8)       launch_small_shape<1, DIREFT, ODD, 8>(a, S, n_slices, k, stream);
         else if (a.rank <= 16) launch_small_shape<1, DIREFT, ODD>(a, S, n_slices, k, stream);
+        else if (!ODD && a.rank <= 24) launch_small_shape<2, DIREFT, false, 24>(a, S, n_slices, k, stream);
         else if (a.rank <= 32) launch_small_shape<2, DIREFT, ODD>(a, S, n_slices, k, stream);
         else if (a.rank <= 64) launch_small_shape<4, DIREFT, ODD>(a, S, n_slices, k, stream);
-        else if constexpr (!DIREFT) launch_small_shape<8, false, ODD>(a, S, n_slices, k, stream);
+        else                   launch_small_shape<8, DIREFT, ODD>(a, S, n_slices, k, stream);
     };
     if (a.rank == 1)       launch_small_shape<1, DIREFT, false, 1>(a, S, n_slices, k, stream);
     else if (a.rank == 2)  launch_small_shape<1, DIREFT, false, 2>(a, S, n_slices, k, stream);
@@ -305,7 +312,7 @@ void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S
     // positions, 8192 -> 2 x 28672: 22 848 of them 23 us): the kernel strides over what exceeds the grid (and over what would
     // exceed the 2^32 work items of a launch)
     const int64_t rows = a.all_tokens && !a.chunks_only ? a.T : prompt_rows(a, S);
-    const int64_t bound = tile_grid(a, S, height), likely = rows / height * 5 / 4 + (rows / 8 < 64 ? rows / 8 + 1 : 64);
+    const int64_t bound = tile_grid(a, S, height), likely = rows / height * 5 / 4 + (rows / 8 < 64 ? rows / 8 + 1 : 64) + (a.chunks_only ? 0 : likely_gathered(a, S));
     const int64_t grid = (bound < likely ? bound : likely) * expand_panels(a, n_slices, cols), most = (int64_t)1 << 23;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(grid < most ? grid : most)), dim3(threads), 0, stream, a, n_slices);
 }
@@ -324,7 +331,7 @@ void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stre
         }
         launch_expand_kernel(kernel, a, S, n_slices, stream);
     } else {
-        const int pu = panel_units(a, n_slices);
+        const int pu = NB == 8 ? 1 : panel_units(a, n_slices);        // rank 65-128: one unit of factors is 35 KB of LDS
         launch_expand_kernel(pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD> : panel_expand_kernel<NB, PANEL_RW, 1, ODD>, a, S, n_slices,
                              stream, 16 * PANEL_RW, 128 * pu, 64 * PANEL_RW);
     }
@@ -376,7 +383,9 @@ bool wants_split_in_place(const ApplyArgs &a, int64_t S, const Knobs &k)
     if (!a.zws || a.h_layers || (k.variant != 0 && k.variant != 4) || k.waves || k.rowblocks || k.colsplit) return false;
     if (!expand_ids_fit(a, S, 1) || !offsets_fit(a)) return false;
     if (k.resident == 1) return true;
-    return a.T > 1024 && prompt_rows(a, S) >= 64 && (a.d_in >= 4096 || (a.d_in >= 1024 && a.T <= 8192));
+    if (a.T <= 1024 || prompt_rows(a, S) < 64) return false;
+    if (a.rank > 64) return a.d_in >= 1024 || a.T <= 8192;
+    return a.d_in >= 4096 || (a.d_in >= 1024 && a.T <= 8192);
 }
 
 // Whether the row-split kernel's single launch runs with two column groups at rank 17-32: every width a multiple of 256.
@@ -397,15 +406,19 @@ template <int NB, int SLICES, bool DIREFT>
 void launch_wide_shrink(const ApplyArgs &a, int64_t S, hipStream_t stream)
 {
     constexpr int RW = NB == 4 && SLICES == 3 ? 8 : 4;
-    void (*kernel)(ApplyArgs) = (a.rank % 4) ? mfma_wide_kernel<NB, 1, RW, 1, DIREFT, SLICES, true, true> : mfma_wide_kernel<NB, 1, RW, 1, DIREFT, SLICES, true>;
+    void (*kernel)(ApplyArgs) = mfma_wide_kernel<NB, 1, RW, 1, DIREFT, SLICES, true>;
+    if constexpr (NB <= 4) { if (a.rank % 4) kernel = mfma_wide_kernel<NB, 1, RW, 1, DIREFT, SLICES, true, true>; }
     int waves = RW;
     if constexpr (NB <= 2) {                                // where the single launch sums in two column groups, so does this one
         if (a.rank % 4 == 0 && column_groups_fit(a, SLICES)) kernel = mfma_wide_kernel<NB, 1, 4, 1, DIREFT, SLICES, true, false, true>;
-    } else if constexpr (!DIREFT && SLICES < 3) {
+    } else if constexpr (NB == 4 && !DIREFT && SLICES < 3) {
         if (SLICES == 2 ? a.T > 16384 : a.T > 49152 && a.d_in > 8192) {
             kernel = (a.rank % 4) ? mfma_wide_kernel<NB, 1, 8, 1, DIREFT, SLICES, true, true> : mfma_wide_kernel<NB, 1, 8, 1, DIREFT, SLICES, true>;
             waves = 8;
         }
+    }
+    if constexpr (NB == 8) {                                // one workgroup on a compute unit in either form
+        if (prompt_rows(a, S) / 64 + S / 4 > 256) { kernel = mfma_wide_kernel<NB, 1, 8, 1, DIREFT, SLICES, true>; waves = 8; }
     }
     hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 16 * waves)), dim3(64 * waves), 0, stream, a);
 }
@@ -418,9 +431,41 @@ bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream
     ApplyArgs a = a0;
     a.chunks_only = 1;
     launch_wide_shrink<NB, SLICES, DIREFT>(a, S, stream);
-    if (a.rank % 4) launch_expand<NB, true>(a, S, SLICES, stream);
-    else            launch_expand<NB, false>(a, S, SLICES, stream);
+    if constexpr (NB <= 4) {
+        if (a.rank % 4) { launch_expand<NB, true>(a, S, SLICES, stream); return true; }
+    }
+    launch_expand<NB, false>(a, S, SLICES, stream);
     return true;
+}
+
+// Rank 17 and up in multiples of 4, few tiles: the small-batch kernel's shrink sweep, then the expand launch; chunks and gathered tiles alike, any widths
+template <bool DIREFT>
+void launch_small_split(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
+{
+    const unsigned tiles = likely_units(a, S), slots = tiles / 8 < 65535 ? tiles / 8 : 65535;
+    // two rank blocks a workgroup while that makes no more workgroups than compute units, else up to four, which share the tile's x
+    const int blocks = z_rank_blocks(a.rank), most = likely_tiles(a, S) * n_slices * ((blocks + 1) / 2) <= 256 ? 2 : 4, rank_parts = (blocks + most - 1) / most, nb = (blocks + rank_parts - 1) / rank_parts;
+    void (*shrink)(ApplyArgs, int) = nb == 4 ? small_shrink_kernel<4, DIREFT> : nb == 3 ? small_shrink_kernel<3, DIREFT> : a.rank <= 24 ? small_shrink_kernel<2, DIREFT, 24> : small_shrink_kernel<2, DIREFT>;
+    hipLaunchKernelGGL(shrink, dim3((unsigned)(n_slices * rank_parts) * 8, slots), dim3(SMALL_WAVES * 64), 0, stream, a, n_slices);
+    if (a.rank <= 32)
+        launch_expand<2, false>(a, S, n_slices, stream);
+    else if (a.rank <= 64)
+        launch_expand_kernel(panel_expand_kernel<4, PANEL_RW, 2, false, true>, a, S, n_slices, stream, 16 * PANEL_RW, 256, 64 * PANEL_RW);
+    else
+        launch_expand_kernel(panel_expand_kernel<8, PANEL_RW, 1, false, true>, a, S, n_slices, stream, 16 * PANEL_RW, 128, 64 * PANEL_RW);
+}
+
+// A call that the small-batch kernel takes: in one launch, or in two where that is faster and the workspace has room for z; the same sums in the same
+// order either way
+template <bool DIREFT>
+void launch_small_order(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
+{
+    int64_t width = a.d_out;
+    for (int i = 1; i < n_slices; ++i) width += a.more[i - 1].d_out;
+    const int cols = a.rank <= 32 ? EXPAND_WAVES * 128 : a.rank <= 64 ? 256 : 128, height = a.rank <= 32 ? 16 * EXPAND_MB : 16 * PANEL_RW;
+    const bool ids_fit = tile_grid(a, S, height) * expand_panels(a, n_slices, cols) < ((int64_t)1 << 31);
+    if (a.zws && !a.h_layers && ids_fit && small_in_two(a, S, width, DIREFT, k)) launch_small_split<DIREFT>(a, S, n_slices, stream);
+    else launch_small<DIREFT>(a, S, n_slices, k, stream);
 }
 
 // rank 4..16: the column-split kernel's shrink sweep, then the expand launch; chunks and gathered tiles alike
@@ -464,7 +509,7 @@ bool launch_mfma_wide(const ApplyArgs &a, int64_t S, int mb, int waves, int cw, 
 {
     if (NB < 2 && k.variant != 4) return false;               // rank <= 16: only on request
     if (!wide_widths_ok(a, 1)) return false;
-    if constexpr (NB == 4 || (NB == 2 && !DIREFT)) {
+    if constexpr (NB >= 4 || (NB == 2 && !DIREFT)) {
         if (launch_mfma_split<NB, 1, DIREFT>(a, S, k, stream)) return true;
     }
     if (!wide_widths_ok(a, cw)) cw = 1;
@@ -502,12 +547,37 @@ template <typename E, bool DIREFT>
 void launch_rows(const ApplyArgs &a, int64_t S, bool chunks_too, hipStream_t stream);
 
 // The gathered tiles (16 rows of an adapter) of a call whose chunks the row-split kernel takes, which shares an adapter's factors among
-// the 128 rows of a chunk: 16-row tiles of the column-split kernel, the per-row kernel where that one's offsets do not fit
+// the 128 rows of a chunk.  A few of them go to the small-batch kernel, whose workgroups share a tile's columns (4096 -> 4096, rank 64, 7500 prompt rows
+// beside 50 decode rows 98 -> 94 us; prompt positions only, an empty launch); many to 16-row tiles of the column-split kernel, an output in each plane of the grid, which
+// run the shrink once (1024 -> 4096 + 2 x 1024, rank 48, 3000 decode rows of 200 adapters 59 us, 74 there); what neither reaches with 32-bit offsets to
+// the per-row kernel.
 template <int NB, bool DIREFT>
-void launch_gathered(ApplyArgs a, int64_t S, hipStream_t stream)
+void launch_gathered(ApplyArgs a, int64_t S, int n_slices, hipStream_t stream)
 {
     a.gathered_only = 1;
-    if (!column_split_fits(a)) { launch_rows<bf16_tag, DIREFT>(a, S, false, stream); return; }
+    int widest = a.d_out;
+    for (int i = 1; i < n_slices; ++i) widest = a.more[i - 1].d_out > widest ? a.more[i - 1].d_out : widest;
+    if (likely_gathered(a, S) <= 128 && a.d_in <= SMALL_WIDTH && widest <= SMALL_WIDTH) {
+        launch_small<DIREFT>(a, S, n_slices, Knobs{}, stream);
+        return;
+    }
+    auto output = [&](int i) {
+        if (i > 0) {
+            a.y = a.more[i - 1].y; a.ldy = a.more[i - 1].ldy; a.d_out = a.more[i - 1].d_out;
+            a.A_pool = a.more[i - 1].A_pool; a.Bt_pool = a.more[i - 1].Bt_pool;
+        }
+    };
+    if (!column_split_fits(a)) {
+        for (int i = 0; i < n_slices; ++i) { output(i); launch_rows<bf16_tag, DIREFT>(a, S, false, stream); }
+        return;
+    }
+    if constexpr (!DIREFT && (NB == 2 || NB == 4)) {
+        if (n_slices > 1) {
+            void (*kernel)(ApplyArgs) = a.rank % 4 ? mfma_tile_outputs_kernel<NB, 4, 1> : mfma_tile_outputs_kernel<NB, 4, 0>;
+            hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, 16), n_slices), dim3(256), 0, stream, a);
+            return;
+        }
+    }
     if constexpr (NB > 1) {
         if (a.rank % 4) { launch_mfma_odd_stream<NB, DIREFT>(a, S, 1, stream); return; }
     }
@@ -557,7 +627,7 @@ void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t s
         }
     }
     if (k.variant != 3 && launch_mfma_wide<NB, DIREFT>(a, S, wide_mb, wide_waves, wide_cw, k, stream)) {
-        launch_gathered<NB, DIREFT>(a, S, stream);
+        launch_gathered<NB, DIREFT>(a, S, 1, stream);
         return;
     }
     launch_mfma_stream<NB, DIREFT>(a, S, mb, waves, stream);
@@ -599,20 +669,7 @@ void launch_mfma_wide_packed(const ApplyArgs &a, int n_proj, int64_t S, const Kn
         if (odd) kernel = n_proj == 2 ? mfma_wide_kernel<NB, 1, 4, 1, false, 2, false, true> : mfma_wide_kernel<NB, 1, 4, 1, false, 3, false, true>;
         hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 64)), dim3(cw2 ? 512 : 256), 0, stream, a);
     }
-    ApplyArgs g = a;
-    g.gathered_only = 1;
-    if (!column_split_fits(a)) {
-        for (int i = 0; i < n_proj; ++i) {
-            if (i > 0) {
-                g.y = a.more[i - 1].y; g.ldy = a.more[i - 1].ldy; g.d_out = a.more[i - 1].d_out;
-                g.A_pool = a.more[i - 1].A_pool; g.Bt_pool = a.more[i - 1].Bt_pool;
-            }
-            launch_rows<bf16_tag, false>(g, S, false, stream);
-        }
-        return;
-    }
-    void (*gathered)(ApplyArgs) = odd ? mfma_tile_outputs_kernel<NB, 4, 1> : mfma_tile_outputs_kernel<NB, 4, 0>;
-    hipLaunchKernelGGL(gathered, dim3(tile_grid(g, S, 16), n_proj), dim3(256), 0, stream, g);
+    launch_gathered<NB, false>(a, S, n_proj, stream);
 }
 
 // bf16 ranks up to 16 that are not multiples of 4 (5, 6, 7, 9, ...): the column-split kernel's any-rank
@@ -667,7 +724,7 @@ void launch_mfma_odd_wide(const ApplyArgs &a, int64_t S, const Knobs &k, hipStre
     bool split = false;
     if constexpr (NB == 4 || (NB == 2 && !DIREFT)) split = launch_mfma_split<NB, 1, DIREFT>(a, S, k, stream);
     if (!split) launch_wide_shape<NB, 1, NB <= 4 ? 4 : 8, 1, DIREFT, true>(a, S, stream);
-    launch_gathered<NB, DIREFT>(a, S, stream);
+    launch_gathered<NB, DIREFT>(a, S, 1, stream);
 }
 
 template <bool DIREFT>
@@ -881,7 +938,7 @@ int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipSt
         launch_f32<DIREFT>(a, S, k, stream);
         break;
     case Path::Mfma: {                     // the tile kernels take chunks and gathered tiles alike
-        if (takes_small(a, S, a.d_out, a.d_out, DIREFT, k)) launch_small<DIREFT>(a, S, 1, k, stream);
+        if (takes_small(a, S, a.d_out, a.d_out, DIREFT, k)) launch_small_order<DIREFT>(a, S, 1, k, stream);
         else                           launch_mfma_rank<DIREFT>(a, S, k, stream);
         break;
     }
@@ -1089,7 +1146,7 @@ int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, 
         a.more[i - 1].A_pool = A_pools[i]; a.more[i - 1].Bt_pool = B_pools[i];
     }
     if (fused_small) {
-        launch_small<false>(a, S, n_proj, k, st);
+        launch_small_order<false>(a, S, n_proj, k, st);
     } else if (fused_wide) {
         if (rank <= 32) launch_mfma_wide_packed<2>(a, n_proj, S, k, st);
         else            launch_mfma_wide_packed<4>(a, n_proj, S, k, st);

@@ -24,12 +24,13 @@ constexpr int SMALL_WAVES = 8;
 // to rank 16) the address arithmetic and the trip through LDS cost a lone tile more than y's two: 32 decode rows, 4096 -> 4096, rank 16 5.8 us, 6.1 with it; rank 32, tiles of up to four
 // rows, 7.4 / 7.6.  Without / with it, us: rank 32, 900 prompt rows 14.4 / 13.5, in place, 32 decode rows, d = 4096 13.4 / 11.4; rank 7 (which had its factors in LDS
 // already), 600 prompt rows 8.4 / 8.0, 200 decode rows 7.6 / 7.3.  (Factors straight from memory in that column order, 16 lines an instruction: in place 7.9 / 12.2, rank 48 17.7 / 36.)
-template <int NB, bool DIREFT, bool ODD> constexpr bool small_direct(int NG) { return ODD ? NB == 1 : NB == 2 && (DIREFT || NG == 4); }
+// LINES: rank 17-32 out of place, shares of 8 units and more, where every wavefront has a unit (rank 32, 4096 -> 512, 300 rows, shares of 2 units, without / with 7.9 / 8.6).
+template <int NB, bool DIREFT, bool ODD, bool LINES> constexpr bool small_direct(int NG) { return ODD ? NB == 1 : NB == 2 && (DIREFT || (LINES && NG == 4)); }
 // A wavefront's own LDS, in 16-byte vectors: a unit of activations and one of the factor in turn, later a unit's factors of the expand.
-template <int NB, bool DIREFT, bool ODD>
+template <int NB, bool DIREFT, bool ODD, bool LINES>
 constexpr int small_area()
 {
-    constexpr int turns = 2 * 16 * MFMA_TRS, factors = small_direct<NB, DIREFT, ODD>(4) ? (FactorLds<NB>::BYTES + 15) / 16 : 0;
+    constexpr int turns = 2 * 16 * MFMA_TRS, factors = small_direct<NB, DIREFT, ODD, LINES>(4) ? (FactorLds<NB>::BYTES + 15) / 16 : 0;
     return turns > factors ? turns : factors;
 }
 
@@ -46,44 +47,50 @@ struct SmallOutput {                                          // the output of a
     int64_t ldy;
     int d_out, share;
     const void *const *A_pool, *const *Bt_pool;
+    int slice, slices, rank0;                                 // the shrink alone: which output of how many, and its first rank
 };
 
-// RK: 0, or what is known of a rank up to 8: 1, 2, 3 are that rank, 4 is rank 4, 8 the ranks 5 to 8.  An instruction brings four ranks of a unit of A:
-// ranks up to 4 and up to 8 leave out three and two of the four.  Ranks 1-3 are too thin for the matrix cores' expand, and z stays
+// RK: 0, or the largest rank of the form: 1, 2, 3 and 4 are that rank, 8 the ranks 5 to 8, 24 the ranks 20 and 24.  An instruction brings four ranks of a unit of A:
+// those that no such rank has are left out.  Ranks 1-3 are too thin for the matrix cores' expand, and z stays
 // in fp32: the sums of valu_tile_kernel, a lane's 8 columns of its rows, whose factors are RK 16-byte pieces.
 // Before / now, replayed, us: 32 decode rows of 32 adapters, a layer's six launches, rank 1 64.5 / 28.1, 3 118 / 33.5 (valu_tile_kernel: 16 rows of a tile on four wavefronts),
 // 8 44.1 / 40.8; rank 4, 4096 -> 4096 5.7 / 4.8; 1000 prompt rows, rank 3, 4096 -> 2 x 14336 75 / 27; in place, d = 4096, rank 1 5.8 / 4.8, 3 7.3 / 5.4, 8 7.9 / 7.4.
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, int NG, int RK>
-__device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallOutput &o, const i32x4_t entry, bool gathered, int row0, int n_rows,
-                                                u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD>()], float (&red)[WAVES * NB * 4 * 64])
+//
+// ZOUT: the shrink alone, of the NB rank blocks from o.rank0 on.  z goes to the workspace in the form the expand's MFMAs take it (z_piece), and an expand
+// launch follows.
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, int NG, int RK, bool ZOUT, bool LINES>
+__device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallOutput &o, const i32x4_t entry, bool gathered, int row0, int n_rows, int unit,
+                                                u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD, LINES>()], float (&red)[WAVES * NB * 4 * 64])
 {
     constexpr bool ANY = ODD && NB > 1;                       // ranks above 16 that are no multiple of 4
-    constexpr bool DIRECT = small_direct<NB, DIREFT, ODD>(NG), THIN = RK >= 1 && RK <= 3;
-    constexpr int AG = RK == 0 ? 4 : RK <= 4 ? 1 : 2;         // groups of four ranks in a unit of A
-    static_assert(RK == 0 || NB == 1, "one rank block");
+    constexpr bool DIRECT = !ZOUT && small_direct<NB, DIREFT, ODD, LINES>(NG), THIN = RK >= 1 && RK <= 3;
+    constexpr int RANKS = RK ? RK : 16 * NB;
+    auto groups = [](int b) constexpr { return RANKS - 16 * b >= 16 ? 4 : (RANKS - 16 * b + 3) / 4; };     // of four ranks in block b of a unit of A: 1, 2 or 4
     // units of the shrink and of the expand sweep in flight (registers)
-    constexpr int BATCH = DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : 2;
+    constexpr int BATCH = ZOUT ? 2 : DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : 2;
     // units of the expand that are asked for before the shrink's last ones are used (registers).  With that, waits for one unit at a time (sweep below) and
     // the bias ahead of the sums, 32 decode rows of 32 adapters, rank 16, replayed: 14336 -> 4096 10.9 -> 10.4 us, 4096 -> 2 x 14336 10.9 -> 10.6, in place, d = 4096,
     // 8.1 -> 7.9, 8 layers of it 12.8 -> 12.2, a layer's six launches 47.9 -> 45.7; 481 prompt rows, rank 8, q+k+v 9.2 -> 8.8.
-    constexpr int EARLY = NG == 1 && DEEP && NB <= 2 ? (DIREFT && NB == 1 ? 2 : 1) : 0;
-    constexpr int DEPTH = DEEP ? (NB == 1 ? (DIRECT || NG == 1 ? 2 : 4) : NB == 2 ? 2 : 1) : 1;
+    constexpr int EARLY = !ZOUT && NG == 1 && DEEP && NB <= 2 ? (DIREFT && NB == 1 ? 2 : 1) : 0;
+    constexpr int DEPTH = DEEP ? (NB == 1 ? (DIRECT || NG == 1 ? 2 : 4) : NB == 2 ? (NG == 1 ? 1 : 2) : 1) : 1;
     constexpr bool W_LATE = NB > 4;                           // factors of the expand step by step (registers)
     static_assert(DEEP || NB == 1, "two workgroups of more rank blocks do not fit a compute unit");
-    constexpr int PIECES = 4 * NB;                            // DIRECT: 16-byte pieces of a unit's factor block per lane
+    constexpr int PIECES = (RANKS + 3) / 4;                   // DIRECT: 16-byte pieces of a unit's factor block per lane
     const int per_share = p.col_split;                        // units of a share
     void *const y = o.y;
     const int64_t ldy = o.ldy;
     const int d_out = o.d_out, share = o.share;
+    static_assert(!ZOUT || (!ODD && NB > 1 && NB <= WAVES), "multiples of 4 above 16; a wavefront writes a rank block");
+    const int r = ZOUT ? min(p.rank - o.rank0, 16 * NB) : p.rank;        // ranks of this workgroup
     gcptr_t A = as_global(as_const(o.A_pool)[entry[0]]);
-    gcptr_t Bt = as_global(as_const(o.Bt_pool)[entry[0]]);
+    if constexpr (ZOUT) A += (int64_t)o.rank0 * p.d_in * 2;
+    gcptr_t Bt = ZOUT ? nullptr : as_global(as_const(o.Bt_pool)[entry[0]]);
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int lane = threadIdx.x & 63;
     asm volatile("" : "+v"(lane));                            // recomputed for every tile: what hangs on the lane would fill the registers
     const int rl = lane & 15, g = lane >> 4;                  // MFMA order
     const int q = lane >> 4, c16 = lane & 15;                 // unit load order
-    const int r = p.rank;
     u32x4_t *tr = area[wave], *tra = area[wave] + 16 * MFMA_TRS;
 
     // Row slot of the lane in load i (DIRECT: those that an accumulator of z times factors has for it).  Slots past the tile alias its last
@@ -147,6 +154,14 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
         for (int k = 0; k < EARLY; ++k) load_yw(k, min(ubase + wave + k * WAVES, c_units - 1));
     };
+    // (only where every wavefront has a unit: rank 20, 512 -> 2072, 32 decode rows 4.2 us, 4.9 where all eight asked for those of two)
+    constexpr bool ALWAYS_EARLY = NB == 1;
+    const bool early = EARLY > 0 && uend - ubase >= WAVES;
+    auto request_some = [&] {
+#pragma unroll
+        for (int k = 0; k < EARLY; ++k)
+            if (ubase + wave + k * WAVES < uend) load_yw(k, ubase + wave + k * WAVES);
+    };
     auto request_expand = [&] {
 #pragma unroll
         for (int k = EARLY; k < DEPTH; ++k)
@@ -160,9 +175,9 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     {
         const int x_last = p.d_in * 2 - 16;                   // a row's last 16-byte piece; d_in % 8 == 0
         const int k_units = (p.d_in + 127) >> 7;
-        auto load_a = [&](u32x4_t (&a)[AG], int b, int off) {
+        auto load_a = [&](u32x4_t (&a)[4], int b, int off) {
 #pragma unroll
-            for (int i = 0; i < AG; ++i)                      // ranks past r alias the last one: their z is zeroed
+            for (int i = 0; i < groups(b); ++i)                      // ranks past r alias the last one: their z is zeroed
                 a[i] = ld16(A + (uint32_t)(min(16 * b + 4 * i + q, r - 1) * (x_last + 16) + off));
         };
         constexpr int HALVES = BATCH > 1 ? 2 : 1, H = BATCH / HALVES;
@@ -187,7 +202,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
                         for (int i = 0; i < NG; ++i) x[k][i] = u32x4_t{0u, 0u, 0u, 0u};
 #pragma unroll
-                        for (int i = 0; i < AG; ++i)
+                        for (int i = 0; i < 4; ++i)
 #pragma unroll
                             for (int b = 0; b < NB; ++b) a[k][b][i] = u32x4_t{0u, 0u, 0u, 0u};
                     }
@@ -199,9 +214,9 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
 #pragma unroll
-                        for (int i = 0; i < AG; ++i) tra[(4 * i + q) * MFMA_TRS + c16] = a[k][b][i];
+                        for (int i = 0; i < groups(b); ++i) tra[(4 * i + q) * MFMA_TRS + c16] = a[k][b][i];
 #pragma unroll
-                        for (int s = 0; s < 4; ++s) ao[s] = tra[(rl & (4 * AG - 1)) * MFMA_TRS + 4 * s + g];
+                        for (int s = 0; s < 4; ++s) ao[s] = tra[(rl & (4 * groups(b) - 1)) * MFMA_TRS + 4 * s + g];
 #pragma unroll
                         for (int s = 0; s < 4; ++s)
                             acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ao[s]), as_bf16x8(xo[s]), acc[b], 0, 0, 0);
@@ -212,29 +227,41 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         // used), so a wait is for its own unit and the others go on arriving.
         auto sweep = [&](auto b_tag) {
             constexpr int B = decltype(b_tag)::value;
-            u32x4_t xr[B][1][NG], ar[B][1][NB][AG];
+            if (wave >= k_units) {
+                if (ALWAYS_EARLY || early) request_early(); else request_some();
+                return;
+            }
+            u32x4_t xr[B][1][NG], ar[B][1][NB][4];
             auto ask = [&](int k, int u) { request(xr[k], ar[k], min(u, k_units - 1), std::true_type{}); };
 #pragma unroll
             for (int k = 0; k < B; ++k) ask(k, wave + k * WAVES);
             int u = wave;
-            for (; u + B * WAVES < k_units; u += B * WAVES) {
+            if constexpr (B == BATCH) {                       // (fewer only where they are all)
+                for (; u + B * WAVES < k_units; u += B * WAVES) {
 #pragma unroll
-                for (int k = 0; k < B; ++k) {
-                    use(xr[k], ar[k], u + k * WAVES);
-                    ask(k, u + (B + k) * WAVES);
+                    for (int k = 0; k < B; ++k) {
+                        use(xr[k], ar[k], u + k * WAVES);
+                        ask(k, u + (B + k) * WAVES);
+                    }
                 }
             }
-            request_early();
+            if (ALWAYS_EARLY || early) {
+                request_early();
 #pragma unroll
-            for (int k = 0; k < B; ++k) use(xr[k], ar[k], u + k * WAVES);
+                for (int k = 0; k < B; ++k) use(xr[k], ar[k], u + k * WAVES);
+            } else {
+                request_some();
+#pragma unroll
+                for (int k = 0; k < B; ++k) use(xr[k], ar[k], u + k * WAVES);
+            }
         };
-        if constexpr (NG == 1 && BATCH > 1) {
+        if constexpr ((NG == 1 || ZOUT) && BATCH > 1) {
             if (k_units <= WAVES) sweep(std::integral_constant<int, 1>{});
             else if (BATCH > 2 && k_units <= 2 * WAVES) sweep(std::integral_constant<int, 2>{});
             else sweep(std::integral_constant<int, BATCH>{});
         } else if constexpr (HALVES == 2) {
             // two halves of a batch take turns: one is on its way while the other is used
-            u32x4_t xr[2][H][NG], ar[2][H][NB][AG];
+            u32x4_t xr[2][H][NG], ar[2][H][NB][4];
             request(xr[0], ar[0], wave, std::false_type{});
             request(xr[1], ar[1], wave + H * WAVES, std::false_type{});
             int u = wave;
@@ -247,7 +274,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             use(xr[0], ar[0], u);
             use(xr[1], ar[1], u + H * WAVES);
         } else {
-            u32x4_t xr[1][H][NG], ar[1][H][NB][AG];
+            u32x4_t xr[1][H][NG], ar[1][H][NB][4];
             for (int u = wave; u < k_units; u += H * WAVES) {
                 request(xr[0], ar[0], u, std::false_type{});
                 use(xr[0], ar[0], u);
@@ -255,7 +282,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         }
     }
 
-    request_expand();                                         // before z is summed
+    if constexpr (!ZOUT) request_expand();                    // before z is summed
 
     const FactorLds<DIRECT ? NB : 1> fl(r);
     char *const fw = reinterpret_cast<char *>(area[wave]);
@@ -277,11 +304,14 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     constexpr bool PARK_FIRST = NB == 2;
     if constexpr (PARK_FIRST) park(0);
 
-    // the bias of rank `lane` (in place: r <= 64): its two trips beside the wait for the sums, not after it
-    float bias = 0.f;
+    // the bias of ranks `lane` and, above rank 64, 64 + `lane`: its two trips beside the wait for the sums, not after it
+    float bias[NB > 4 ? 2 : 1] = {};
     if constexpr (DIREFT) {
         gcptr_t bias_p = bias_of(p, entry[0]);
-        if (bias_p) bias = Elem<bf16_tag>::load1(bias_p, min(lane, r - 1));
+        if (bias_p) {
+#pragma unroll
+            for (int j = 0; j < (NB > 4 ? 2 : 1); ++j) bias[j] = Elem<bf16_tag>::load1(bias_p, (ZOUT ? o.rank0 : 0) + min(64 * j + lane, r - 1));
+        }
     }
 
     // ---------------------------------------------------------------- sum over the wavefronts, z -> expand operand
@@ -297,6 +327,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
     u32x4_t zlow[ANY ? NB / 2 : 1];                           // what two parts of bf16 leave of z (whole_z), two rank blocks in one operand
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
+        if constexpr (ZOUT) { if (b != wave) continue; }      // (uniform)
         const int rank0 = 16 * b + 4 * g;
         float zv[4], rem[4];
 #pragma unroll
@@ -305,7 +336,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) s += red[((w * NB + b) * 4 + v) * 64 + zlane];
             float add = 0.f;
-            if constexpr (DIREFT) add = __shfl(bias, rank0 + v, 64);
+            if constexpr (DIREFT) add = __shfl(bias[b / 4], rank0 % 64 + v, 64);
             zv[v] = rank0 + v < r ? (s + add) * p.scale : 0.f;
             rem[v] = zv[v] - __uint_as_float((pack_bf16(zv[v], 0.f) & 0xffffu) << 16);
         }
@@ -323,6 +354,14 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             zop[b] = as_bf16x8(u32x4_t{pack_bf16(zv[0], zv[1]), pack_bf16(zv[2], zv[3]), pack_bf16(rem[0], rem[1]), pack_bf16(rem[2], rem[3])});
         }
     }
+
+    if constexpr (ZOUT) {
+        u32x4_t *zw = reinterpret_cast<u32x4_t *>(p.zws) + lane;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            if (b == wave && 16 * b < r) zw[z_piece(unit, o.slices, o.slice, z_rank_blocks(p.rank), o.rank0 / 16 + b)] = as_u32x4(zop[b]);
+        return;
+    } else {
 
     // ---------------------------------------------------------------- expand
     // y plus the products of step s, in MFMA order (ANY only: `nan`, whether a result is NaN; finite_tag as in whole_z_products)
@@ -440,12 +479,13 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
                 if (u + (k + DEPTH) * WAVES < uend) load_yw(k, u + (k + DEPTH) * WAVES);
             }
     }
+    }
 }
 
 // FEW: with the form for tiles of up to four rows (in place only for steps of decode rows: its second copy of the code costs the others 0.1 us of 4.5).
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW, int RK>
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW, int RK, bool ZOUT, bool LINES>
 __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOutput &o, int unit, int n_chunk_units,
-                                               u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD>()], float (&red)[WAVES * NB * 4 * 64])
+                                               u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD, LINES>()], float (&red)[WAVES * NB * 4 * 64])
 {
     // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
     const bool gathered = unit >= n_chunk_units;
@@ -454,8 +494,8 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOu
         gathered ? as_const(p.gtiles) + (unit - n_chunk_units) : as_const(p.chunks) + unit / (CHUNK_ROWS / 16));
     const int n_rows = min(16, entry[2] - row0);
     if (n_rows <= 0) return;                                  // uniform over the workgroup
-    if (!FEW || n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4, RK>(p, o, entry, gathered, row0, n_rows, area, red);
-    else if constexpr (FEW) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1, RK>(p, o, entry, gathered, row0, n_rows, area, red);
+    if (!FEW || n_rows > 4) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 4, RK, ZOUT, LINES>(p, o, entry, gathered, row0, n_rows, unit, area, red);
+    else if constexpr (FEW) small_tile_rows<NB, DIREFT, ODD, DEEP, WAVES, 1, RK, ZOUT, LINES>(p, o, entry, gathered, row0, n_rows, unit, area, red);
 }
 
 // A launch out of place: blockIdx.x = 8 share + XCD, blockIdx.y = the slot of a tile on that XCD (in place: blockIdx.x = 8 slot + XCD).  The shares of a
@@ -463,15 +503,15 @@ __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOu
 // launch has as many slots as the batch is likely to need; what exceeds it is strided over.
 struct SmallLaunch { int shares0, shares1; };
 
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW, int RK>
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW, int RK, bool LINES>
 __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallLaunch &l)
 {
-    __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, ODD>()];
+    __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, ODD, LINES>()];
     __shared__ float red[WAVES * NB * 4 * 64];
 
     // What the launch arguments say is asked for together with the header: each line of them that is touched later is a trip of its own (in
     // place, rank 16, d = 512, 220 rows 4.4 us without, 4.3 with).
-    SmallOutput o = {p.y, p.ldy, p.d_out, 0, p.A_pool, p.Bt_pool};
+    SmallOutput o = {p.y, p.ldy, p.d_out, 0, p.A_pool, p.Bt_pool, 0, 1, 0};
     if constexpr (!DIREFT) {
         o.share = blockIdx.x >> 3;
         if (o.share >= l.shares0) {
@@ -489,15 +529,15 @@ __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallL
     const int per_xcd = (n_units + 7) >> 3;
     for (int t = DIREFT ? blockIdx.x >> 3 : blockIdx.y; t < per_xcd; t += DIREFT ? gridDim.x >> 3 : gridDim.y) {
         const int unit = few_tiles_unit(p, n_chunk_units, per_xcd, t);
-        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES, FEW, RK>(p, o, unit, n_chunk_units, area, red);
+        if (unit < n_units) small_tile_one<NB, DIREFT, ODD, DEEP, WAVES, FEW, RK, false, LINES>(p, o, unit, n_chunk_units, area, red);
         __syncthreads();                                      // the next tile's sums go where this one's are still being read
     }
 }
 
-template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES = SMALL_WAVES, bool FEW = true, int RK = 0>
+template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES = SMALL_WAVES, bool FEW = true, int RK = 0, bool LINES = true>
 __global__ __launch_bounds__(WAVES * 64, DEEP ? 2 : 4) void small_tile_kernel(ApplyArgs p, SmallLaunch l)
 {
-    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES, FEW, RK>(p, l);
+    small_tile_body<NB, DIREFT, ODD, DEEP, WAVES, FEW, RK, LINES>(p, l);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer
@@ -508,7 +548,36 @@ __global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(
     // (above rank 32 there are no registers for that: 8 layers, rank 64, d = 1024, 400 rows 21.9 / 24.2)
     if constexpr (NB <= 2) asm volatile("" ::"s"(p.rank), "s"(p.d_out), "s"(p.col_split), "s"(p.header), "s"(p.T));
     select_layer(p);
-    small_tile_body<NB, true, ODD, true, SMALL_WAVES, FEW, RK>(p, l);
+    small_tile_body<NB, true, ODD, true, SMALL_WAVES, FEW, RK, true>(p, l);
+}
+
+// The shrink of a two-launch call of few tiles, rank 17 and up in multiples of 4: blockIdx.x = 8 part + XCD, a part being NB rank blocks of one of the
+// outputs; blockIdx.y = the slot of a tile on that XCD.  Bound: a compute unit's texture path (64 bytes a cycle), through which a workgroup brings its tile's x and 32 to
+// 64 ranks of A; two units on their way per wavefront.  Against the row-split kernel's 64-row tiles, whose wavefronts sweep all columns of their rows
+// one unit after the other, whole calls, us: 1400 prompt rows, 4096 -> 4096, rank 32 30.2 / 17.0, 64 36.7 / 17.8; 8192 -> 8192, rank 64 64 / 26; 3600 rows, 4096 -> 4096, rank 32 57.8 /
+// 32.4.  Against the small-batch kernel's single launch, 900 rows: rank 64, 4096 -> 4096 26.9 / 14.7, in place 42 / 16.5; rank 128 48 / 17.5, in place 137 (128-row tiles) / 19.6.
+template <int NB, bool DIREFT, int RK = 0>
+__global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_shrink_kernel(ApplyArgs p, int slices)
+{
+    constexpr int WAVES = SMALL_WAVES;
+    __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, false, false>()];
+    __shared__ float red[WAVES * NB * 4 * 64];
+    const int parts = (p.rank + 16 * NB - 1) / (16 * NB), part = blockIdx.x >> 3, sl = part / parts;
+    SmallOutput o = {nullptr, 0, 0, 0, p.A_pool, nullptr, sl, slices, (part - sl * parts) * 16 * NB};
+    if constexpr (!DIREFT) {
+        if (sl == 1) o.A_pool = p.more[0].A_pool;
+        if (sl == 2) o.A_pool = p.more[1].A_pool;
+    }
+    asm volatile("" ::"s"(o.A_pool), "s"(p.x), "s"(p.gtiles), "s"(p.chunks), "s"(p.shorts), "s"(p.rank), "s"(p.zws));
+    if (!schedule_matches(p)) return;
+    int n_chunk_units;
+    const int n_units = min((int64_t)tile_units<16>(p, &n_chunk_units), p.z_blocks);      // (only tables whose segments overlap list more tiles)
+    const int per_xcd = (n_units + 7) >> 3;
+    for (int t = blockIdx.y; t < per_xcd; t += gridDim.y) {
+        const int unit = few_tiles_unit(p, n_chunk_units, per_xcd, t);
+        if (unit < n_units) small_tile_one<NB, DIREFT, false, true, WAVES, true, RK, true, false>(p, o, unit, n_chunk_units, area, red);
+        __syncthreads();                                      // the next tile's sums go where this one's are still being read
+    }
 }
 
 }  // namespace preft

@@ -102,3 +102,110 @@ def test_in_place_as_two_launches(rank, d):
                           [m.cpu() for m in pool.B], [v.cpu() for v in pool.b], rank, 0.5, pos)
         compare(got[0], h0, want, ora.positions(T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, pos), "bf16")
         assert torch.equal(bits(got[0]), bits(got[1]))
+
+
+def _table(rank, d, N, empty=0):
+    rng = np.random.Generator(np.random.PCG64(rank + d))
+    lens = np.array(LENS + [0] * empty)
+    return wl.from_lengths(lens, rng.integers(-1, N + 1, size=len(lens)), np.where(np.arange(len(lens)) < 14, np.maximum(lens - (lens > 100), 0), 0))
+
+
+def _lora(tab, N, rank, d_in, d_outs, sides):
+    """Every side (flags, room for z) against the oracle, guards untouched, and all of them bit for bit alike; both position sets."""
+    from oracle import preft_oracle as ora
+    from parity_util import bits, check_guards, compare, dev_tables, lora_pools_to_device, padded
+    T = tab.T
+    ss, sa, sp = dev_tables(tab)
+    x = wl.activations(T, d_in, "bf16", device="cuda", seed=1)
+    y0s = [wl.activations(T, n, "bf16", device="cuda", seed=2 + i) for i, n in enumerate(d_outs)]
+    pools = [wl.lora_pool(N, rank, d_in, n, "bf16", device="cuda", seed=9 + i) for i, n in enumerate(d_outs)]
+    tables = [lora_pools_to_device(pl) for pl in pools]
+    for mode, pos in ((preft.PREFT_PREFILL_ONLY, ora.PROMPT_ONLY), (preft.PREFT_ALL_TOKENS, ora.ALL_POSITIONS)):
+        owner = ora.positions(T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, pos)
+        got = []
+        for flags, room in sides:
+            ws = preft.new_workspace(T, tab.S, z_rank=rank if room else 0, z_proj=len(d_outs))
+            ws.fill_(0xa5)
+            bufs = [padded(y, 8, 7.0) for y in y0s]
+            prev = preft.set_test_flags(flags)
+            try:
+                preft.preft_lora_apply_packed([b[1] for b in bufs], x, ss, sa, sp, [t[0] for t in tables], [t[1] for t in tables], rank, 2.0, mode, ws)
+            finally:
+                preft.set_test_flags(prev)
+            torch.cuda.synchronize()
+            for (buf, _), n in zip(bufs, d_outs):
+                check_guards(buf, T, n, 7.0)
+            got.append([b[1] for b in bufs])
+        for i, pl in enumerate(pools):
+            want = ora.lora(y0s[i].cpu(), x.cpu(), tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, [a.cpu() for a in pl.A], [b.cpu() for b in pl.B], rank, 2.0, pos)
+            compare(got[0][i], y0s[i], want, owner, "bf16")
+            for other in got[1:]:
+                assert torch.equal(bits(got[0][i]), bits(other[i]))
+
+
+def _direft(tab, N, rank, d, sides, layers):
+    """The same in place; `layers`: the flags of a call of two layers, each of which has the bits of its one-layer call."""
+    from oracle import preft_oracle as ora
+    from parity_util import bits, check_guards, compare, dev_tables, direft_pools_to_device, padded
+    T = tab.T
+    ss, sa, sp = dev_tables(tab)
+    h0 = wl.activations(T, d, "bf16", device="cuda", seed=3)
+    pool = wl.direft_pool(N, rank, d, "bf16", device="cuda", seed=4)
+    W1, W2t, b, keep = direft_pools_to_device(pool, bias=True)
+    table = lambda t: torch.tensor([t.data_ptr()] * 2, dtype=torch.int64, device="cuda")
+    for mode, pos in ((preft.PREFT_PREFILL_ONLY, ora.PROMPT_ONLY), (preft.PREFT_ALL_TOKENS, ora.ALL_POSITIONS)):
+        got = []
+        for flags, room in sides + [(layers, True)]:
+            ws = preft.new_workspace(T, tab.S, z_rank=rank if room else 0)
+            ws.fill_(0xa5)
+            bufs = [padded(h0, 8, 7.0) for _ in range(2)]
+            prev = preft.set_test_flags(flags)
+            try:
+                if len(got) < len(sides):
+                    preft.preft_direft_apply(bufs[0][1], ss, sa, sp, W1, W2t, b, rank, 0.5, mode, ws)
+                else:
+                    hs = [v[1] for v in bufs]
+                    preft.preft_direft_apply_layers(hs, torch.tensor([v.data_ptr() for v in hs], dtype=torch.int64, device="cuda"), ss, sa, sp, table(W1), table(W2t), table(b), N, rank, 0.5, mode, ws)
+            finally:
+                preft.set_test_flags(prev)
+            torch.cuda.synchronize()
+            for buf, _ in bufs:
+                check_guards(buf, T, d, 7.0)
+            got.append(bufs[0][1])
+            if len(got) > len(sides):
+                assert torch.equal(bits(bufs[0][1]), bits(bufs[1][1]))
+        want = ora.direft(h0.cpu(), tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, [a.cpu() for a in pool.A], [m.cpu() for m in pool.B], [v.cpu() for v in pool.b],
+                          rank, 0.5, pos)
+        compare(got[0], h0, want, ora.positions(T, tab.seg_start, tab.seg_adapter, tab.seg_prefill_len, N, pos), "bf16")
+        for other in got[1:]:
+            assert torch.equal(bits(got[0]), bits(other))
+
+
+# the small-batch kernel's shrink as a launch of its own: one to four rank blocks a workgroup, ranks that end in a block, one to three outputs, widths that are no
+# multiple of 128 or of a panel, d_in of one to three rounds of the wavefronts' units
+SHRINK = [(20, 264, (1032, 8, 520)), (24, 4104, (512,)), (28, 128, (128, 1032)), (32, 1000, (520,)), (36, 136, (1096, 520)), (48, 4104, (264,)), (52, 512, (1536, 256, 264)),
+          (64, 2056, (520,)), (68, 264, (136,)), (96, 1032, (1032, 520)), (100, 128, (264,)), (112, 512, (640,)), (128, 4104, (136, 1544))]
+
+
+@pytest.mark.parametrize("rank,d_in,d_outs", SHRINK, ids=[f"r{c[0]}-{c[1]}-{'x'.join(map(str, c[2]))}" for c in SHRINK])
+@pytest.mark.parametrize("many", [False, True])
+def test_small_batch_shrink_then_expand(rank, d_in, d_outs, many):
+    """Against the oracle, and bit for bit the small-batch kernel's single launch; many: so many segments that a workgroup takes three or four rank blocks."""
+    tab = _table(rank, d_in, 5, 3000 if many else 0)
+    _lora(tab, 5, rank, d_in, d_outs, [(preft.test_flags(resident=2), True), (preft.test_flags(resident=2), False), (preft.test_flags(colsplit=3), True)])
+
+
+@pytest.mark.parametrize("rank,d", [(20, 8200), (32, 264), (36, 1032), (48, 4104), (64, 512), (68, 136), (96, 2056), (128, 264)])
+def test_small_batch_shrink_then_expand_in_place(rank, d):
+    flags = preft.test_flags(resident=2)
+    _direft(_table(rank, d, 5), 5, rank, d, [(flags, True), (flags, False)], flags)
+
+
+@pytest.mark.parametrize("rank,d_in,d_outs", [(68, 128, (128,)), (96, 256, (384, 128)), (100, 384, (256,)), (128, 1024, (640,)), (128, 256, (1152, 128, 128))])
+@pytest.mark.parametrize("tall", [False, True])
+def test_two_launches_above_rank_64(rank, d_in, d_outs, tall):
+    """64-row tiles and (tall: by the number of segments) 128-row tiles of the row-split kernel's shrink, then the panels: out of place and in place."""
+    tab = _table(rank, d_in, 5, 1100 if tall else 0)
+    one = preft.test_flags(variant=5, colsplit=1)
+    _lora(tab, 5, rank, d_in, d_outs, [(preft.test_flags(resident=1), True), (one, True)])
+    _direft(tab, 5, rank, d_in, [(preft.test_flags(resident=1), True), (preft.test_flags(resident=1), False)], preft.test_flags(resident=1))
