@@ -98,6 +98,11 @@ constexpr int64_t DEEP_WGS = 200;                             // at most one wor
 constexpr int32_t SMALL_STREAM_T = 6144;
 inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
 {
+    // Above rank 16 the two launches of the small-batch kernel's order (small_in_two) against those of 64-row tiles, us: 1400 / 3600 / 6000 / 12 000 prompt rows,
+    // 4096 -> 4096, rank 32 30 / 17, 58 / 32, 47 / 39, 66 / 68, rank 64 37 / 18, 87 / 42 (both beside 35 decode rows), 53 / 46, 72 / 84; 8192 -> 8192, rank 20 51 / 24, 93 / 47, 80 / 60, 118 / 123; 512 ->
+    // 2072 (against 16-row tiles), rank 20 6000 rows 18.9 / 22.2, rank 64 at 1400 to 24 000 rows 21 / 10, 38 / 21, 40 / 25, 128 / 78; rank 128, 512 -> 2072, 24 000 rows 248 / 94, 4096 -> 4096 at 3600
+    // rows (128-row tiles, one launch) 156 / 50, two launches of 64-row tiles 57, at 6000 68 / 66.  Decode rows, 3000 of 200 adapters: 8192 -> 8192, rank 32 97 / 81, 1024 -> 4096 + 2 x 1024
+    // 39.5 / 47.5.  (Without room for z the small-batch kernel's single launch: rank 33-64 between half and 1.45 of the time of 64-row tiles.)
     if (a.rank > 16) {
         if (a.rank % 4) return false;
         const bool ragged = a.d_in % 128 || width % 128;      // (not each width: packed calls with one ragged output have the others wide)
@@ -148,6 +153,11 @@ inline bool small_in_place_few(const ApplyArgs &a, int64_t S) { return a.all_tok
 
 // Whether a call of the small-batch kernel's order at rank 17 and up (multiples of 4) runs its sweeps as two launches: then a tile's shrink is not repeated
 // by every share of its columns, and the expand shares its factors among 32 or 64 rows.  `width`: of all outputs.
+// But it is a second chain of launch arguments, schedule and memory.  One launch / two, us, 32 decode rows of 32 adapters, 300 and 880 prompt rows: 4096 -> 4096, rank 48 12.5 / 14.0, 12.6 / 12.0, 18.4 /
+// 13.9, rank 64 15.7 / 15.2, 15.7 / 12.1, 26.9 / 14.7, rank 96 21.3 / 17.8, 22.9 / 13.3, 34 / 17; 512 -> 2072, rank 48 5.6 / 8.6, 6.0 / 8.9, 7.4 / 8.8, rank 64 6.7 / 8.6, 7.1 / 8.9, 10.2 / 8.9, rank 128 10.8 /
+// 10.9, 10.4 / 9.7, 18.1 / 11.0; rank 32, 8192 -> 8192 12.0 / 17.0, 15.3 / 15.8, 21.0 / 20.9.  In place, d = 8192, rank 20 20.1 / 15.1, 23.5 / 18.2, 25.7 / 25.8, rank 32 19.6 / 18.4, 22.2 / 20.2, 24.9 / 28.1;
+// d = 4096, rank 32 11.7 / 11.6, 13.9 / 14.4, rank 48 20.5 / 14.6, 22.3 / 14.2, 23.1 / 16.5; d = 512, rank 48 6.2 / 8.7, 6.7 / 8.7, rank 64 8.6 / 8.9, 9.1 / 8.7, rank 128 (16-row tiles of the
+// column-split kernel, 128-row tiles) 16.6 / 10.0, 23 / 9.8.
 inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool direft, const Knobs &k)
 {
     if (a.rank <= 16 || a.rank % 4 || k.variant == 5 || k.colsplit) return false;

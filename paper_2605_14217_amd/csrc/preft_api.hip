@@ -417,7 +417,10 @@ void launch_wide_shrink(const ApplyArgs &a, int64_t S, hipStream_t stream)
             waves = 8;
         }
     }
-    if constexpr (NB == 8) {                                // one workgroup on a compute unit in either form
+    // Rank 65-128: one workgroup on a compute unit in either form, so 64 rows as long as those are no more than one for each.  One launch (128-row tiles, the expand in the same
+    // workgroup) / 64 / 128, whole calls, us: rank 128, 4096 -> 4096, 3600 prompt rows 156 / 57 / 66, 12 000 167 / 89 / 96, 24 000 185 / 167 / 150; rank 96, 8192 -> 8192, 31 500 rows
+    // 621 / 418 / 395; in place, d = 4096, 12 000 rows 154 / 91 / 97.
+    if constexpr (NB == 8) {
         if (prompt_rows(a, S) / 64 + S / 4 > 256) { kernel = mfma_wide_kernel<NB, 1, 8, 1, DIREFT, SLICES, true>; waves = 8; }
     }
     hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 16 * waves)), dim3(64 * waves), 0, stream, a);
