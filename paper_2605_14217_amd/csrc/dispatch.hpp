@@ -114,6 +114,7 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
     if (a.T > SMALL_STREAM_T) return false;
     const int64_t d = a.d_in, singles = a.all_tokens && a.T < 2 * S;
     if (a.rank <= 2 && singles && 8 * width <= d) return false;
+    if (width > 10240 && !(a.rank < 4 && singles)) return false;          // rank 8, 912 -> 14336 + 4096 + 1512, 1240 prompt rows 28.3 / 34.0
     const int64_t elements = a.T * (d + 2 * width) + likely_adapters(S, a.N) * a.rank * (d + width);
     const int64_t most = a.rank < 4 && singles ? 180000000 : d >= 8192 && width >= 8192 && a.T >= 64 * S ? 48000000 : 76000000;
     return elements <= most;

@@ -256,8 +256,9 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
             }
         };
         if constexpr ((NG == 1 || ZOUT) && BATCH > 1) {
-            if (k_units <= WAVES) sweep(std::integral_constant<int, 1>{});
-            else if (BATCH > 2 && k_units <= 2 * WAVES) sweep(std::integral_constant<int, 2>{});
+            const int mine = k_units - wave;                  // units of this wavefront: of the first, every WAVES-th
+            if (mine <= WAVES) sweep(std::integral_constant<int, 1>{});
+            else if (BATCH > 2 && mine <= 2 * WAVES) sweep(std::integral_constant<int, 2>{});
             else sweep(std::integral_constant<int, BATCH>{});
         } else if constexpr (HALVES == 2) {
             // two halves of a batch take turns: one is on its way while the other is used
