@@ -152,6 +152,7 @@ __device__ __forceinline__ u32x4_t ld16_stream(gcptr_t p)
     else return ld16(p);
 }
 __device__ __forceinline__ u32x4_t ld16_stream(gptr_t p) { return ld16_stream((gcptr_t)p); }
+template <bool HINT, typename P> __device__ __forceinline__ u32x4_t ld16_hint(P p) { if constexpr (HINT) return ld16_stream(p); else return ld16(p); }
 __device__ __forceinline__ u32x2_t quad_from(u32x2_t four, int rank0, int rank)
 {
     const int before = rank0 - quad_start(rank0, rank);

@@ -47,6 +47,17 @@ inline int64_t likely_tiles(const ApplyArgs &a, int64_t S)
     return extra / 16 + (extra ? prompts / 2 + 1 : 0) + likely_gathered(a, S);
 }
 
+// Whether what a call reads and writes of its activations (once each, `es` bytes an element) is little enough for the memory-side cache (256 MB) to still hold it from the
+// kernel before, and for the kernel after: then it is read without the non-temporal hint, which has it fetched from memory.  Hint / none, us, two sets of buffers in turn: fp32,
+// rank 16, 4096 -> 4096, 2304 rows (75 MB) 31.8 / 27.1, 5000 rows (165 MB) 59 / 68; rank 31, 3760 -> 600, 6000 rows (52 MB) 36.5 / 27.2; rank 20, 1000 -> 2000, 5900 rows (35 MB) 21.7 / 19.2; in place,
+// rank 64, d = 4096, 5000 rows (41 MB) 50.6 / 46.9; 4096 -> 4096, rank 64, 8400 rows (138 MB) 60.3 / 62.7, rank 16, 12 600 rows (206 MB) 62 / 72.  Below the size of the L2s together (32 MB) the
+// lines of y that were read plainly are written back at the end of the kernel: rank 48, 4096 -> 4096, 880 rows (14 MB) 13.7 / 14.9, fp32, rank 4, 1024 -> 1024, 2400 rows (20 MB) 9.9 / 11.0.
+inline bool activations_stay(const ApplyArgs &a, int64_t width, bool direft, int es)
+{
+    const int64_t bytes = a.T * (direft ? (int64_t)a.d_in : a.d_in + width) * es * a.n_layers;
+    return bytes >= ((int64_t)28 << 20) && bytes <= ((int64_t)76 << 20);
+}
+
 // Small batches take a kernel of their own (small_kernel.hpp).
 // Rows of segments of more than one row, if no segment is empty: prompts.  A step of decode rows alone has none, and where only
 // prompt positions count it has next to nothing to do: its launches are sized for that (a kernel strides over what exceeds its grid).
@@ -114,6 +125,7 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
     if (a.T > SMALL_STREAM_T) return false;
     const int64_t d = a.d_in, singles = a.all_tokens && a.T < 2 * S;
     if (a.rank <= 2 && singles && 8 * width <= d) return false;
+    if (a.rank >= 4 && width <= 1024 && d <= 2048) return false;          // rank 16, 1104 -> 1024, 1080 prompt rows 5.4 / 5.7
     if (width > 10240 && !(a.rank < 4 && singles)) return false;          // rank 8, 912 -> 14336 + 4096 + 1512, 1240 prompt rows 28.3 / 34.0
     const int64_t elements = a.T * (d + 2 * width) + likely_adapters(S, a.N) * a.rank * (d + width);
     const int64_t most = a.rank < 4 && singles ? 180000000 : d >= 8192 && width >= 8192 && a.T >= 64 * S ? 48000000 : 76000000;

@@ -275,7 +275,7 @@ constexpr int PANEL_RW = 4;
 
 // ANY: any widths (multiples of 8), and gathered tiles too, of which the first wavefront has the rows (calls of the small-batch kernel's order).
 // Rank 65-128: 64 x 128, 35 KB of LDS (two units a workgroup: 4096 -> 4096, rank 96, 24 000 rows 144 / 150 us).
-template <int NB, int RW, int PU, bool ODD, bool ANY = false>
+template <int NB, int RW, int PU, bool ODD, bool ANY = false, bool HINT = true>
 __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, int n_slices)
 {
     constexpr int R = 16 * RW, NT = RW * 64;
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(RW * 64, 3) void panel_expand_kernel(ApplyArgs p, i
 #pragma unroll
             for (int u = 0; u < PU; ++u)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) Y[u][v] = ld16_stream(yu[v] + y_off(u));
+                for (int v = 0; v < 4; ++v) Y[u][v] = ld16_hint<HINT>(yu[v] + y_off(u));
         }
 
         // factors to LDS: as they lie in memory, or in two 8-byte halves per piece, neither of which straddles a column

@@ -35,7 +35,8 @@ constexpr int f32_red_bytes(int NB) { return F32_WAVES * NB * 4 * 64 * 4; }
 constexpr int f32_turn_bytes() { return F32_WAVES * 2 * 16 * MFMA_TRS * 16; }
 
 // BY_LDS (ranks up to 32 that are no multiple of 4): the expand takes z as its first operand and whole units of factors through LDS, see below.
-template <int NB, bool DIREFT, bool ODD, bool BY_LDS>
+// HINT: y with the non-temporal hint (activations_stay has the rule).
+template <int NB, bool DIREFT, bool ODD, bool BY_LDS, bool HINT>
 __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
 {
     constexpr int WAVES = F32_WAVES;
@@ -175,7 +176,7 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
     auto load_yw = [&](u32x4_t (&yr)[4], u32x4_t (&wr)[NW][NB], int u) {
         const int off = min(u * 256 + c16 * 16, y_last);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) yr[i] = ld16_stream(yu[i] + off);
+        for (int i = 0; i < 4; ++i) yr[i] = ld16_hint<HINT>(yu[i] + off);
         if constexpr (BY_LDS) {                               // the unit's [64 columns][r] block, 16 r contiguous pieces
             gcptr_t block = Bt + (int64_t)u * 256 * r;
             const int last = min(16 * r, (p.d_out - u * 64) * r / 4) - 1;   // d_out % 4 == 0
@@ -311,15 +312,15 @@ __device__ __forceinline__ void f32_tile_body(const ApplyArgs &p)
     }
 }
 
-template <int NB, bool DIREFT, bool ODD, bool BY_LDS>
-__global__ __launch_bounds__(F32_WAVES * 64) void f32_tile_kernel(ApplyArgs p) { f32_tile_body<NB, DIREFT, ODD, BY_LDS>(p); }
+template <int NB, bool DIREFT, bool ODD, bool BY_LDS, bool HINT = true>
+__global__ __launch_bounds__(F32_WAVES * 64) void f32_tile_kernel(ApplyArgs p) { f32_tile_body<NB, DIREFT, ODD, BY_LDS, HINT>(p); }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer
 template <int NB, bool ODD>
 __global__ __launch_bounds__(F32_WAVES * 64) void f32_tile_layers_kernel(ApplyArgs p)
 {
     select_layer(p);
-    f32_tile_body<NB, true, ODD, ODD && NB <= 2>(p);
+    f32_tile_body<NB, true, ODD, ODD && NB <= 2, true>(p);
 }
 
 }  // namespace preft

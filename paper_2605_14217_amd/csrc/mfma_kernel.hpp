@@ -117,8 +117,9 @@ constexpr int mfma_min_waves(int NB, int MB, int WAVES, int HUNITS)
 //
 // ZOUT: the shrink sweep alone.  z goes to the workspace in the form the expand's MFMAs take it, 1 KB per
 // 16-row block and rank block, and mfma_expand_kernel does the expand in a second launch.
+// HINT: activations that are read once come with the non-temporal hint.
 template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bool PARTIAL = false,
-          int ODD = 0, bool ZOUT = false>
+          int ODD = 0, bool ZOUT = false, bool HINT = true>
 __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 {
     static_assert(!PARTIAL || HUNITS > 0, "a partially resident tile keeps some units");
@@ -253,7 +254,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) raw[mb][i] = ld16_first<AGAIN>(xu[mb][i] + off);
+            for (int i = 0; i < 4; ++i) raw[mb][i] = ld16_hint<HINT && !AGAIN>(xu[mb][i] + off);
     };
     constexpr std::integral_constant<bool, false> read_once{};
     constexpr std::integral_constant<bool, X_READ_AGAIN> read_streamed{};
@@ -588,7 +589,7 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) raw[mb][i] = ld16_stream(yu[mb][i] + off);
+            for (int i = 0; i < 4; ++i) raw[mb][i] = ld16_hint<HINT>(yu[mb][i] + off);
     };
     // a whole unit: y (MFMA order) -> out, turned back to load order through LDS and stored
     auto finish_unit = [&](const u32x4_t (&yop)[MB][4], const wbuf_t &wb, int u) {
@@ -741,10 +742,10 @@ __device__ __forceinline__ void mfma_tile_body(const ApplyArgs &p)
 }
 
 template <int NB, int MB, int WAVES, int HUNITS, bool DIREFT, int SLICES = 1, bool PARTIAL = false,
-          int ODD = 0, bool ZOUT = false>
+          int ODD = 0, bool ZOUT = false, bool HINT = true>
 __global__ __launch_bounds__(WAVES * 64, mfma_min_waves(NB, MB, WAVES, HUNITS)) void mfma_tile_kernel(ApplyArgs p)
 {
-    mfma_tile_body<NB, MB, WAVES, HUNITS, DIREFT, SLICES, PARTIAL, ODD, ZOUT>(p);
+    mfma_tile_body<NB, MB, WAVES, HUNITS, DIREFT, SLICES, PARTIAL, ODD, ZOUT, HINT>(p);
 }
 
 // the same for one of a packed call's outputs: blockIdx.y (the gathered tiles of ranks above 16, which other launches leave over)

@@ -202,6 +202,9 @@ void launch_mfma(const ApplyArgs &a, int64_t S, hipStream_t stream)
 {
     constexpr int R = 16 * MB;
     void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, MB, WAVES, HUNITS, DIREFT>;
+    if constexpr (NB > 1 && !DIREFT) {
+        if (activations_stay(a, a.d_out, false, 2)) kernel = mfma_tile_kernel<NB, MB, WAVES, HUNITS, DIREFT, 1, false, 0, false, false>;
+    }
     if constexpr (DIREFT) {
         if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, MB, WAVES, HUNITS>;
     }
@@ -294,6 +297,12 @@ int64_t columns_off_lines(const ApplyArgs &a, int n_slices)
     for (int i = 1; i < n_slices; ++i) off += shares_lines(a.more[i - 1].y, a.more[i - 1].ldy * 2) ? a.more[i - 1].d_out : 0;
     return off;
 }
+int64_t out_width(const ApplyArgs &a, int n_slices)
+{
+    int64_t width = a.d_out;
+    for (int i = 1; i < n_slices; ++i) width += a.more[i - 1].d_out;
+    return width;
+}
 bool rows_off_lines(const ApplyArgs &a, int n_slices) { return columns_off_lines(a, n_slices) > 0; }
 
 // the shrink launch of rank 17-64 keeps byte offsets within a 64-row tile of x and within a factor in 32 bits
@@ -320,9 +329,11 @@ void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S
 template <int NB, bool ODD>
 void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
 {
+    const bool stay = activations_stay(a, out_width(a, n_slices), a.x == a.y, 2);
     if constexpr (NB <= 2) {
         void (*kernel)(ApplyArgs, int) = mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::All>;
-        if constexpr (NB == 1) {                              // (above rank 16 rows are off lines by their pitch only)
+        if (stay) kernel = mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::None>;
+        else if constexpr (NB == 1) {                              // (above rank 16 rows are off lines by their pitch only)
             int64_t on = a.d_out;
             for (int i = 1; i < n_slices; ++i) on += a.more[i - 1].d_out;
             const int64_t off = columns_off_lines(a, n_slices);
@@ -332,8 +343,9 @@ void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stre
         launch_expand_kernel(kernel, a, S, n_slices, stream);
     } else {
         const int pu = NB == 8 ? 1 : panel_units(a, n_slices);        // rank 65-128: one unit of factors is 35 KB of LDS
-        launch_expand_kernel(pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD> : panel_expand_kernel<NB, PANEL_RW, 1, ODD>, a, S, n_slices,
-                             stream, 16 * PANEL_RW, 128 * pu, 64 * PANEL_RW);
+        void (*kernel)(ApplyArgs, int) = pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD> : panel_expand_kernel<NB, PANEL_RW, 1, ODD>;
+        if (stay) kernel = pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD, false, false> : panel_expand_kernel<NB, PANEL_RW, 1, ODD, false, false>;
+        launch_expand_kernel(kernel, a, S, n_slices, stream, 16 * PANEL_RW, 128 * pu, 64 * PANEL_RW);
     }
 }
 
@@ -384,7 +396,8 @@ bool wants_split_in_place(const ApplyArgs &a, int64_t S, const Knobs &k)
     if (!expand_ids_fit(a, S, 1) || !offsets_fit(a)) return false;
     if (k.resident == 1) return true;
     if (a.T <= 1024 || prompt_rows(a, S) < 64) return false;
-    if (a.rank > 64) return a.d_in >= 1024 || a.T <= 8192;
+    // above rank 64, rank 96, one launch / two: 24 000 rows, d = 512 28.8 / 34, 2048 83 / 80, 4096 173 / 144; 26 600 rows, d = 1024 46 / 54; 12 000 rows, d = 512 27.0 / 25.0, 2048 79 / 51
+    if (a.rank > 64) return a.d_in >= 2048 || a.T <= 14336;
     return a.d_in >= 4096 || (a.d_in >= 1024 && a.T <= 8192);
 }
 
@@ -449,13 +462,16 @@ void launch_small_split(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t
     // two rank blocks a workgroup while that makes no more workgroups than compute units, else up to four, which share the tile's x
     const int blocks = z_rank_blocks(a.rank), most = likely_tiles(a, S) * n_slices * ((blocks + 1) / 2) <= 256 ? 2 : 4, rank_parts = (blocks + most - 1) / most, nb = (blocks + rank_parts - 1) / rank_parts;
     void (*shrink)(ApplyArgs, int) = nb == 4 ? small_shrink_kernel<4, DIREFT> : nb == 3 ? small_shrink_kernel<3, DIREFT> : a.rank <= 24 ? small_shrink_kernel<2, DIREFT, 24> : small_shrink_kernel<2, DIREFT>;
+    const bool stay = activations_stay(a, out_width(a, n_slices), DIREFT, 2);
     hipLaunchKernelGGL(shrink, dim3((unsigned)(n_slices * rank_parts) * 8, slots), dim3(SMALL_WAVES * 64), 0, stream, a, n_slices);
     if (a.rank <= 32)
         launch_expand<2, false>(a, S, n_slices, stream);
     else if (a.rank <= 64)
-        launch_expand_kernel(panel_expand_kernel<4, PANEL_RW, 2, false, true>, a, S, n_slices, stream, 16 * PANEL_RW, 256, 64 * PANEL_RW);
+        launch_expand_kernel(stay ? panel_expand_kernel<4, PANEL_RW, 2, false, true, false> : panel_expand_kernel<4, PANEL_RW, 2, false, true>, a, S, n_slices, stream, 16 * PANEL_RW, 256,
+                             64 * PANEL_RW);
     else
-        launch_expand_kernel(panel_expand_kernel<8, PANEL_RW, 1, false, true>, a, S, n_slices, stream, 16 * PANEL_RW, 128, 64 * PANEL_RW);
+        launch_expand_kernel(stay ? panel_expand_kernel<8, PANEL_RW, 1, false, true, false> : panel_expand_kernel<8, PANEL_RW, 1, false, true>, a, S, n_slices, stream, 16 * PANEL_RW, 128,
+                             64 * PANEL_RW);
 }
 
 // A call that the small-batch kernel takes: in one launch, or in two where that is faster and the workspace has room for z; the same sums in the same
@@ -533,13 +549,16 @@ bool launch_mfma_wide(const ApplyArgs &a, int64_t S, int mb, int waves, int cw, 
 template <int NB, bool DIREFT>
 void launch_mfma_odd_stream(const ApplyArgs &a, int64_t S, int mb, hipStream_t stream)
 {
+    const bool stay = !DIREFT && activations_stay(a, a.d_out, false, 2);
     void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, 1, 4, 0, DIREFT, 1, false, 1>;
+    if constexpr (!DIREFT) { if (stay) kernel = mfma_tile_kernel<NB, 1, 4, 0, DIREFT, 1, false, 1, false, false>; }
     if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 1, 4, 0, false, 1>; }
     int rows = 16;
     if constexpr (NB == 2) {
         if (mb == 2) {
             rows = 32;
             kernel = mfma_tile_kernel<NB, 2, 4, 0, DIREFT, 1, false, 1>;
+            if constexpr (!DIREFT) { if (stay) kernel = mfma_tile_kernel<NB, 2, 4, 0, DIREFT, 1, false, 1, false, false>; }
             if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 2, 4, 0, false, 1>; }
         }
     }
@@ -866,19 +885,22 @@ template <int NB, bool DIREFT>
 void launch_f32_nb(const ApplyArgs &a, int64_t S, hipStream_t stream)
 {
     constexpr bool BY_LDS = NB <= 2;
+    const bool stay = activations_stay(a, a.d_out, DIREFT, 4);
     void (*kernel)(ApplyArgs);
     if constexpr (DIREFT) {
         if (a.h_layers) kernel = (a.rank % 4) ? f32_tile_layers_kernel<NB, true> : f32_tile_layers_kernel<NB, false>;
+        else if (stay)  kernel = (a.rank % 4) ? f32_tile_kernel<NB, true, true, BY_LDS, false> : f32_tile_kernel<NB, true, false, false, false>;
         else            kernel = (a.rank % 4) ? f32_tile_kernel<NB, true, true, BY_LDS> : f32_tile_kernel<NB, true, false, false>;
     } else {
         kernel = (a.rank % 4) ? f32_tile_kernel<NB, false, true, BY_LDS> : f32_tile_kernel<NB, false, false, false>;
+        if (stay) kernel = (a.rank % 4) ? f32_tile_kernel<NB, false, true, BY_LDS, false> : f32_tile_kernel<NB, false, false, false, false>;
         // A workgroup of one or two units of 64 columns has one or two wavefronts at work on them, and LDS is only a further step on their way; at
         // rank 17-31, twice the factors, so is one unit for each of the eight.  Factors by LDS / lane by lane, 14 rows, us: rank 7, 512 -> 512 5.4 / 5.2, 1024 5.5 /
         // 5.2, 4096 (8 units a workgroup) 6.0 / 6.8; rank 31, 512 7.2 / 6.5, 1024 7.3 / 6.6, 2104 -> 4096 14.3 / 14.0, 512 -> 4096 8.5 / 8.9; 1200 rows, rank 31, 2104 ->
         // 512 15.0 / 14.7, 4096 (32 units) 25.4 / 26.6, rank 7 9.6 / 10.3, 17.7 / 20.2.
         if constexpr (BY_LDS) {
             const int units = (a.d_out + 63) / 64 / (a.col_split > 1 ? a.col_split : 1);
-            if (a.rank % 4 && units < (NB == 1 ? F32_WAVES / 2 : 2 * F32_WAVES)) kernel = f32_tile_kernel<NB, false, true, false>;
+            if (a.rank % 4 && units < (NB == 1 ? F32_WAVES / 2 : 2 * F32_WAVES)) kernel = stay ? f32_tile_kernel<NB, false, true, false, false> : f32_tile_kernel<NB, false, true, false>;
         }
     }
     hipLaunchKernelGGL(kernel, dim3(tile_grid(a, S, 16), a.n_layers), dim3(F32_WAVES * 64), 0, stream, a);
