@@ -117,7 +117,21 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
     if (a.rank > 16) {
         if (a.rank % 4) return false;
         const bool ragged = a.d_in % 128 || width % 128;      // (not each width: packed calls with one ragged output have the others wide)
-        if (a.rank <= 48 && a.d_in < 2048 && a.all_tokens && a.T < 2 * S) return false;
+        const bool singles = a.all_tokens && a.T < 2 * S;
+        if (a.rank <= 48 && a.d_in < 2048 && singles) return false;
+        // Narrow outputs, ragged: 16-row tiles of one launch / here, us: rank 32, 1024 -> 264, 2000 prompt rows 8.6 / 12.3, rank 20, 512 -> 424, 3000 7.8 / 13.6, rank 24,
+        // 4096 -> 720, 2800 18.8 / 22.3 (but 4096 -> 512, 3600 38 / 21, 4096 -> 464, 1670 16.9 / 12.0); rank 96, 320 -> 256, 2060 9.4 / 14.2, rank 48, 568 -> 560, 3250 11.4 / 13.3, rank 64,
+        // 4096 -> 304, 10 600 59 / 70 (512 -> 328, 12 200 21.4 / 19.9).
+        if (ragged && a.rank <= 32 && !singles && width <= 768 && a.T > 2000 && (width % 128 || a.d_in <= 1024)) return false;
+        if (ragged && a.rank > 32 && ((a.d_in <= 600 && width <= 576 && a.T <= 8192) || (width <= 320 && a.T > 8192))) return false;
+        // Decode rows in more tiles than compute units, most of them part-empty: rank 48, 4096 -> 4096, 1270 rows of 171 adapters 32.8 / 39.7, rank 64, 1024 -> 4096, 2360 of 451 78 / 88,
+        // rank 128, 1024 -> 512, 1060 of 286 22 / 27; full ones: rank 64, 4096 -> 9816, 4000 of 33 173 / 100, 8192 -> 4128, 4000 of 15 107 / 68, but rank 48, 4096 -> 10240, 3900 of 2 63 / 78, rank
+        // 96, 3888 -> 10544, 2700 of 86 118 / 142, rank 64, 288 -> 2176, 3600 of 64 24 / 28.
+        if (singles && a.rank > 32) {
+            const int64_t tiles = likely_tiles(a, S);
+            if (tiles > 170 && 160 * tiles > 13 * a.T) return false;
+            if (tiles > 200 && ((width > 9216 && !(ragged && a.rank <= 64)) || (a.d_in <= 512 && width <= 4096))) return false;
+        }
         if (a.rank > 32 && ragged) return true;
         if (a.T <= 4096) return true;
         return a.T <= SMALL_STREAM_T && a.d_in >= 2048 && (a.rank <= 32 || width <= 16384) && a.rank <= 64;
@@ -126,9 +140,10 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
     const int64_t d = a.d_in, singles = a.all_tokens && a.T < 2 * S;
     if (a.rank <= 2 && singles && 8 * width <= d) return false;
     if (a.rank >= 4 && width <= 1024 && d <= 2048) return false;          // rank 16, 1104 -> 1024, 1080 prompt rows 5.4 / 5.7
+    if (a.rank >= 4 && !singles && d > 8192 && width > 4608) return false;   // rank 11, 14336 -> 5176, 1470 prompt rows 26.7 / 42.5, rank 16, 14336 -> 5832, 1490 31 / 38 (rank 5, 14336 -> 4448, 1300 26 / 18)
     if (width > 10240 && !(a.rank < 4 && singles)) return false;          // rank 8, 912 -> 14336 + 4096 + 1512, 1240 prompt rows 28.3 / 34.0
     const int64_t elements = a.T * (d + 2 * width) + likely_adapters(S, a.N) * a.rank * (d + width);
-    const int64_t most = a.rank < 4 && singles ? 180000000 : d >= 8192 && width >= 8192 && a.T >= 64 * S ? 48000000 : 76000000;
+    const int64_t most = a.rank < 4 && singles ? 180000000 : d >= 8192 && width >= 8192 && a.T >= 8 * S ? 48000000 : 76000000;
     return elements <= most;
 }
 
@@ -158,6 +173,9 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     // Ranks 1-3, rows resident in a wavefront's registers / this, us: rank 1, d = 1024, 250 and 920 prompt rows 3.6 / 3.7, 4.2 / 3.9, 4096 7.6 / 7.1, 512 decode rows 8.2 /
     // 7.2, rank 3 9.7 / 8.4, 11.2 / 9.3, 11.1 / 8.6; but rank 1, d = 512, 250 rows 3.2 / 3.4.
     if (a.rank == 1 && a.d_in <= 512) return false;
+    // and wide rows of fuller tiles than a few decode rows: rank 1, d = 4096, 150 prompt rows 6.4 / 7.2, 74 decode rows of 3 adapters 6.4 / 7.3, rank 2, 230 prompt rows 7.2 / 7.9, 396 7.4 /
+    // 8.2 (482 9.5 / 8.2; 160 decode rows of 313 adapters 7.1 / 5.3)
+    if (a.rank <= 2 && a.d_in > 2048 && a.T <= 448 && a.T > 5 * likely_tiles(a, S)) return false;
     return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
 }
 
@@ -180,10 +198,11 @@ inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool dire
     if (a.T > SMALL_T) return true;
     const int64_t tiles = likely_tiles(a, S), panels = tiles * width;
     if (direft) return a.rank > 64 || (a.rank > 48 ? a.d_in >= 1024 : a.rank > 32 ? a.d_in >= 2048 : a.d_in >= 8192 && tiles <= 48);
-    if (a.rank > 112) return true;
+    if (a.rank > 112) return a.d_in > 640 || panels >= 24000;    // 512 -> 1056, 29 decode rows 8.5 / 9.7, 512 -> 608, 242 prompt rows 8.7 / 9.6; 512 -> 8192, 3 rows 10.1 / 9.4
     if (a.rank > 64) return a.d_in >= 4096 || (!singles && panels >= 100000);
     if (a.rank > 48) return singles ? (a.d_in >= 4096 && width >= 4096) || panels >= 250000 : panels >= 80000;
-    return a.rank > 32 && !singles && panels >= 150000;
+    // (hardly a shrink to repeat: 512 -> 4096, 840 prompt rows 11.3 / 12.7, 296 -> 3640, 620 7.9 / 10.4, but 304 -> 14336, 730 18.2 / 14.5)
+    return a.rank > 32 && !singles && panels >= 150000 && (a.d_in > 512 || width > 8192);
 }
 
 // Out of place its form for tiles of up to four rows is in the kernel where most of the tiles are gathered rows: a second copy of the code costs the others 0.3 to 0.6 us (rank

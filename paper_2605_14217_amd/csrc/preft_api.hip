@@ -379,6 +379,7 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     // 1602, rank 63 q+k+v 1355 -> 1282; 352 814 rows, q+k+v 5100 -> 5000.  But 8192 -> 1024 376 -> 392: next to nothing to expand, and the single
     // launch has tiles enough.
     if (a.rank > 32 && a.T > 49152 && 4 * width <= a.d_in) return false;
+    if (a.rank > 64 && a.T > 14336 && a.d_in <= 512 && width <= 512) return false;      // rank 128, 512 -> 512, one launch / two: 25 000 rows 27 / 38, 19 600 38 / 46, 4000 25 / 22
     if (a.rank > 16) return true;
     if (a.all_tokens && a.T < 8 * S) return false;
     if (a.rank < 4) return a.T * width >= (n_slices > 1 ? 6000000 : 12000000) && width >= 3072 && (n_slices > 1 || !rows_off_lines(a, n_slices));

@@ -227,10 +227,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
         // used), so a wait is for its own unit and the others go on arriving.
         auto sweep = [&](auto b_tag) {
             constexpr int B = decltype(b_tag)::value;
-            if (wave >= k_units) {
-                if (ALWAYS_EARLY || early) request_early(); else request_some();
-                return;
-            }
+            if (wave >= k_units) { request_some(); return; }
             u32x4_t xr[B][1][NG], ar[B][1][NB][4];
             auto ask = [&](int k, int u) { request(xr[k], ar[k], min(u, k_units - 1), std::true_type{}); };
 #pragma unroll
@@ -245,7 +242,10 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
                     }
                 }
             }
-            if (ALWAYS_EARLY || early) {
+            if (B == 1 && k_units <= WAVES) {                 // a unit each at most: the shrink's trip is the only one before the sums
+                use(xr[0], ar[0], u);
+                request_some();
+            } else if (ALWAYS_EARLY || early) {
                 request_early();
 #pragma unroll
                 for (int k = 0; k < B; ++k) use(xr[k], ar[k], u + k * WAVES);

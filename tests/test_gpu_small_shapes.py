@@ -98,7 +98,7 @@ def test_tiles_of_one_to_sixteen_rows(rank, d, d_out):
     assert bits(rows["own"][0]).equal(bits(rows["one"][0])) and bits(rows["own"][1]).equal(bits(rows["one"][1]))
 
 
-@pytest.mark.parametrize("rank,d", [(4, 4096), (4, 8192), (5, 2120), (7, 4104), (7, 8192), (16, 2760), (16, 8192), (16, 14336), (17, 1000), (24, 4096),
+@pytest.mark.parametrize("rank,d", [(4, 520), (12, 1024), (16, 1032), (4, 4096), (4, 8192), (5, 2120), (7, 4104), (7, 8192), (16, 2760), (16, 8192), (16, 14336), (17, 1000), (24, 4096),
                                     (24, 1000), (31, 1000), (31, 8192), (32, 4096), (33, 2056), (63, 1000), (63, 8192), (64, 4096), (64, 8192), (64, 264)])
 def test_in_place_steps_of_decode_rows(tmp_path_factory, rank, d):
     """A step of single rows alone in place: the form that loads a quarter for tiles of at most four rows, at 1, 4, 5 and 16 rows of an adapter,
