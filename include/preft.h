@@ -107,8 +107,8 @@ enum {
  *                            of the kernels of larger batches wherever that form exists, whatever the batch size.  Rank
  *                            20..128 in multiples of 4: 2 = the small-batch kernel at any batch size, as two launches
  *                            where the workspace has room for z.  In-place
- *                            MFMA kernel at rank 20..32 (automatic: 32-row tiles streamed in
- *                            both sweeps): 3 = every wavefront keeps 8 of its
+ *                            MFMA kernel at rank 20..32 (automatic: 32-row tiles, streamed in
+ *                            both sweeps up to 8192 columns and as 3 above): 3 = every wavefront keeps 8 of its
  *                            128-column units in registers between the sweeps (half of a
  *                            32-row tile of 8192 columns) and streams the rest twice
  */

@@ -58,6 +58,18 @@ inline bool activations_stay(const ApplyArgs &a, int64_t width, bool direft, int
     return bytes >= ((int64_t)28 << 20) && bytes <= ((int64_t)76 << 20);
 }
 
+// In place at rank 20-32, rows wider than 8192: whether every wavefront of the 32-row tiles keeps 8 of its units in registers between the sweeps.  It costs
+// half the wavefronts of a compute unit; a tile of such rows (576 KB at 9216) does not outlast its first sweep in an XCD's L2 in any case.  All streamed / 8 kept, us: rank 32, d = 9216 /
+// 10240 / 14336, 6000 rows 61.9 / 60.6, 73 / 70, 101 / 96; 18 000 rows 225 / 181, 264 / 209, 379 / 302; 30 000 rows 329 / 306, 393 / 351, 561 / 504; 72 000 rows 706 / 692, 814 / 779;
+// 28672, 18 000 rows 752 / 683; 4 layers of 1600 rows, 10240 125 / 72; prompts of 45 rows, 14336, 12 000 rows 410 / 391; rank 20, 18 000 rows, 14336 358 / 289, but 9216, 72 000 rows 658 /
+// 670, and 4000 decode rows of 64 adapters 124 / 141 (rank 32 148 / 145).  8192 and narrower: rank 32, 12 000 rows 109 / 106, 60 000 505 / 515, 4096 54 / 56, 2048 30 / 33, rank 20, 8192 99.5 / 104.8.
+inline bool keeps_units(const ApplyArgs &a, int64_t S)
+{
+    if (a.d_in <= 8192) return false;
+    if (a.all_tokens && a.T < 2 * S && a.T > 2048) return false;
+    return a.d_in >= 10240 || a.T <= 32768;
+}
+
 // Small batches take a kernel of their own (small_kernel.hpp).
 // Rows of segments of more than one row, if no segment is empty: prompts.  A step of decode rows alone has none, and where only
 // prompt positions count it has next to nothing to do: its launches are sized for that (a kernel strides over what exceeds its grid).

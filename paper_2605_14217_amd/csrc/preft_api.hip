@@ -632,14 +632,8 @@ void launch_mfma_nb(const ApplyArgs &a, int64_t S, const Knobs &k, hipStream_t s
         // measured ahead of the resident and row-split shapes at d = 4096 and d = 8192
         if constexpr (NB == 2) {
             if (k.waves == 0 && (k.variant == 0 || k.variant == 5) && k.rowblocks == 0 && column_split_fits(a)) {
-                // resident == 3 (tests): each wavefront keeps 8 of its units in registers and streams the
-                // rest twice.  Measured on the skewed batch (d = 8192): traffic through the fabric falls
-                // by a sixth (half of the tile is read once), the time by 4 % (5985 against 6216 us): the
-                // 256 + 248 registers leave one workgroup of four wavefronts per compute unit, and what
-                // binds is the latency of the factor sweeps, not the bytes.  Not the default: measured at that
-                // one batch and width only, which draws no line over widths and rows.
-                if (k.resident == 3) launch_mfma_partial<2, 2, 4, 8>(a, S, stream);
-                else                 launch_mfma<2, 2, 4, 0, true>(a, S, stream);
+                if (k.resident == 3 || keeps_units(a, S)) launch_mfma_partial<2, 2, 4, 8>(a, S, stream);
+                else                                      launch_mfma<2, 2, 4, 0, true>(a, S, stream);
                 return;
             }
         }

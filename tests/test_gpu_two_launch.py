@@ -209,3 +209,9 @@ def test_two_launches_above_rank_64(rank, d_in, d_outs, tall):
     one = preft.test_flags(variant=5, colsplit=1)
     _lora(tab, 5, rank, d_in, d_outs, [(preft.test_flags(resident=1), True), (one, True)])
     _direft(tab, 5, rank, d_in, [(preft.test_flags(resident=1), True), (preft.test_flags(resident=1), False)], preft.test_flags(resident=1))
+
+
+@pytest.mark.parametrize("rank,d", [(20, 9224), (32, 10240), (28, 14336)])
+def test_wide_rows_in_place_keep_units(rank, d):
+    """Rank 20-32 on rows wider than 8192: 8 units a wavefront in registers, the bits of tiles that are streamed in both sweeps."""
+    _direft(_table(rank, d, 5), 5, rank, d, [(0, True), (preft.test_flags(variant=3), True)], 0)
