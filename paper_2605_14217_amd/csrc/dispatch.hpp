@@ -58,6 +58,15 @@ inline bool activations_stay(const ApplyArgs &a, int64_t width, bool direft, int
     return bytes >= ((int64_t)28 << 20) && bytes <= ((int64_t)76 << 20);
 }
 
+// The same for the two launches of an in-place call: the expand reads h again where the shrink has read it, and neither has the hint.  Hint in the shrink, and in the expand
+// above 76 MB / none, us: rank 64, d = 4096, 12 000 / 18 000 / 24 000 / 30 000 / 36 000 rows (98 to 295 MB) 70.9 / 63.9, 99 / 89, 121 / 109, 157 / 155, 178 / 184; 8192, 1200 rows (20 MB) 62.6 / 57.3, 6000 90 /
+// 81, 12 000 (197 MB) 126 / 122, 13 800 161 / 166; 14336, 6000 154 / 143, 7800 (224 MB) 172 / 177; rank 48, 4096, 18 000 95 / 86; rank 96 121 / 110; but 1200 rows (10 MB) 44.6 / 47.3.
+inline bool h_stays(const ApplyArgs &a)
+{
+    const int64_t bytes = a.T * (int64_t)a.d_in * 2;
+    return bytes >= ((int64_t)16 << 20) && bytes <= ((int64_t)192 << 20);
+}
+
 // In place at rank 20-32, rows wider than 8192: whether every wavefront of the 32-row tiles keeps 8 of its units in registers between the sweeps.  It costs
 // half the wavefronts of a compute unit; a tile of such rows (576 KB at 9216) does not outlast its first sweep in an XCD's L2 in any case.  All streamed / 8 kept, us: rank 32, d = 9216 /
 // 10240 / 14336, 6000 rows 61.9 / 60.6, 73 / 70, 101 / 96; 18 000 rows 225 / 181, 264 / 209, 379 / 302; 30 000 rows 329 / 306, 393 / 351, 561 / 504; 72 000 rows 706 / 692, 814 / 779;

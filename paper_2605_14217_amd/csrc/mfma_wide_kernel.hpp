@@ -67,7 +67,8 @@ constexpr int wide_lds_bytes(int NB, int MB, int RW, int CW, bool zout)
 // units go to LDS as they lie in memory, a column's r factors right behind the previous column's, and a
 // lane reads its four factors of a column as the three 32-bit words that hold them, shifts them into place
 // and masks the ranks past r (as the any-rank shape of mfma_tile_kernel does for rank 5..15).
-template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false, bool EO = false>
+// HINT (ZOUT): x with the non-temporal hint (in place without it where the expand can find h in the cache: h_stays).
+template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false, bool EO = false, bool HINT = true>
 __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
 {
     static_assert(!ODD || (MB == 1 && CW == 1), "the any-rank form: the basic shape");
@@ -166,7 +167,7 @@ __device__ __forceinline__ void mfma_wide_body(const ApplyArgs &p)
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if constexpr (ZOUT) raw[mb][i] = ld16_stream(x_tile + (int64_t)u * (256 * CW) + x_off[mb][i]);
+                if constexpr (ZOUT) raw[mb][i] = ld16_hint<HINT>(x_tile + (int64_t)u * (256 * CW) + x_off[mb][i]);
                 else raw[mb][i] = ld16_first<DIREFT>(xu[mb][i] + (int64_t)u * (256 * CW));
             }
     };
@@ -590,10 +591,10 @@ constexpr int wide_min_waves(int RW, int CW, int SLICES, bool zout)
     return (RW * CW == 8 && SLICES == 1 && zout) ? 4 : (RW * CW == 4 && (SLICES > 1 || zout)) ? 2 : 1;
 }
 
-template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false, bool EO = false>
+template <int NB, int MB, int RW, int CW, bool DIREFT, int SLICES = 1, bool ZOUT = false, bool ODD = false, bool EO = false, bool HINT = true>
 __global__ __launch_bounds__(RW * CW * 64, wide_min_waves(RW, CW, SLICES, ZOUT)) void mfma_wide_kernel(ApplyArgs p)
 {
-    mfma_wide_body<NB, MB, RW, CW, DIREFT, SLICES, ZOUT, ODD, EO>(p);
+    mfma_wide_body<NB, MB, RW, CW, DIREFT, SLICES, ZOUT, ODD, EO, HINT>(p);
 }
 
 // the same for one of several residual streams (in-place calls): blockIdx.y is the layer

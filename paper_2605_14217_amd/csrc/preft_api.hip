@@ -329,7 +329,7 @@ void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S
 template <int NB, bool ODD>
 void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
 {
-    const bool stay = activations_stay(a, out_width(a, n_slices), a.x == a.y, 2);
+    const bool stay = a.x == a.y ? h_stays(a) : activations_stay(a, out_width(a, n_slices), false, 2);
     if constexpr (NB <= 2) {
         void (*kernel)(ApplyArgs, int) = mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::All>;
         if (stay) kernel = mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::None>;
@@ -420,8 +420,13 @@ template <int NB, int SLICES, bool DIREFT>
 void launch_wide_shrink(const ApplyArgs &a, int64_t S, hipStream_t stream)
 {
     constexpr int RW = NB == 4 && SLICES == 3 ? 8 : 4;
+    const bool stay = DIREFT && h_stays(a);
     void (*kernel)(ApplyArgs) = mfma_wide_kernel<NB, 1, RW, 1, DIREFT, SLICES, true>;
     if constexpr (NB <= 4) { if (a.rank % 4) kernel = mfma_wide_kernel<NB, 1, RW, 1, DIREFT, SLICES, true, true>; }
+    if constexpr (DIREFT) {
+        if (stay) kernel = mfma_wide_kernel<NB, 1, RW, 1, true, 1, true, false, false, false>;
+        if constexpr (NB <= 4) { if (stay && a.rank % 4) kernel = mfma_wide_kernel<NB, 1, RW, 1, true, 1, true, true, false, false>; }
+    }
     int waves = RW;
     if constexpr (NB <= 2) {                                // where the single launch sums in two column groups, so does this one
         if (a.rank % 4 == 0 && column_groups_fit(a, SLICES)) kernel = mfma_wide_kernel<NB, 1, 4, 1, DIREFT, SLICES, true, false, true>;
@@ -435,7 +440,11 @@ void launch_wide_shrink(const ApplyArgs &a, int64_t S, hipStream_t stream)
     // workgroup) / 64 / 128, whole calls, us: rank 128, 4096 -> 4096, 3600 prompt rows 156 / 57 / 66, 12 000 167 / 89 / 96, 24 000 185 / 167 / 150; rank 96, 8192 -> 8192, 31 500 rows
     // 621 / 418 / 395; in place, d = 4096, 12 000 rows 154 / 91 / 97.
     if constexpr (NB == 8) {
-        if (prompt_rows(a, S) / 64 + S / 4 > 256) { kernel = mfma_wide_kernel<NB, 1, 8, 1, DIREFT, SLICES, true>; waves = 8; }
+        if (prompt_rows(a, S) / 64 + S / 4 > 256) {
+            kernel = mfma_wide_kernel<NB, 1, 8, 1, DIREFT, SLICES, true>;
+            if constexpr (DIREFT) { if (stay) kernel = mfma_wide_kernel<NB, 1, 8, 1, true, 1, true, false, false, false>; }
+            waves = 8;
+        }
     }
     hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 16 * waves)), dim3(64 * waves), 0, stream, a);
 }

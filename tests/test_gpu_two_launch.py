@@ -211,6 +211,14 @@ def test_two_launches_above_rank_64(rank, d_in, d_outs, tall):
     _direft(tab, 5, rank, d_in, [(preft.test_flags(resident=1), True), (preft.test_flags(resident=1), False)], preft.test_flags(resident=1))
 
 
+@pytest.mark.parametrize("rank,d,empty", [(64, 8192, 0), (63, 7680, 0), (96, 8192, 0), (96, 8192, 1100)])
+def test_in_place_calls_that_the_cache_can_hold(rank, d, empty):
+    """17 MB of h and more, without the non-temporal hint in either launch (above rank 64 in 64- and 128-row tiles): the bits of the single launch."""
+    tab = _table(rank, d, 5, empty)
+    assert tab.T * d * 2 >= 16 << 20
+    _direft(tab, 5, rank, d, [(0, True), (preft.test_flags(variant=4), False)], 0)
+
+
 @pytest.mark.parametrize("rank,d", [(20, 9224), (32, 10240), (28, 14336)])
 def test_wide_rows_in_place_keep_units(rank, d):
     """Rank 20-32 on rows wider than 8192: 8 units a wavefront in registers, the bits of tiles that are streamed in both sweeps."""
