@@ -218,6 +218,8 @@ inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool dire
     if (!a.all_tokens && prompt_rows(a, S) < 64) return false;            // hardly a row to do
     if (a.T > SMALL_T) return true;
     const int64_t tiles = likely_tiles(a, S), panels = tiles * width;
+    // (in place, decode rows of many adapters: rank 48, d = 3184, 209 of 376 20.8 / 23.6, 2688, 535 of 197 (184 tiles) 22.3 / 31.4, 4096, 730 of 54 (72 tiles) 25.5 / 22.9)
+    if (direft && a.rank > 32 && a.rank <= 48 && a.d_in <= 4096 && singles && tiles > 128) return false;
     if (direft) return a.rank > 64 || (a.rank > 48 ? a.d_in >= 1024 : a.rank > 32 ? a.d_in >= 2048 : a.d_in >= 8192 && tiles <= 48);
     if (a.rank > 112) return a.d_in > 640 || panels >= 24000;    // 512 -> 1056, 29 decode rows 8.5 / 9.7, 512 -> 608, 242 prompt rows 8.7 / 9.6; 512 -> 8192, 3 rows 10.1 / 9.4
     if (a.rank > 64) return a.d_in >= 4096 || (!singles && panels >= 100000);
