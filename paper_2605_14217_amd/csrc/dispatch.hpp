@@ -200,6 +200,9 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     return (a.rank % 4) ? a.d_in <= 4096 : a.d_in <= 2048;
 }
 
+// a call of one output, or in place
+inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t width, bool direft, const Knobs &k) { return takes_small(a, S, width, width, direft, k); }
+
 // In place its form for tiles of up to four rows runs for steps of decode rows alone (others pay 0.1 of 4.5 us for a second copy of the code).
 inline bool small_in_place_few(const ApplyArgs &a, int64_t S) { return a.all_tokens && prompt_rows(a, S) == 0; }
 

@@ -967,12 +967,12 @@ int launch_apply(const ApplyArgs &a, int64_t S, int dtype, const Knobs &k, hipSt
         launch_f32<DIREFT>(a, S, k, stream);
         break;
     case Path::Mfma: {                     // the tile kernels take chunks and gathered tiles alike
-        if (takes_small(a, S, a.d_out, a.d_out, DIREFT, k)) launch_small_order<DIREFT>(a, S, 1, k, stream);
+        if (takes_small(a, S, a.d_out, DIREFT, k)) launch_small_order<DIREFT>(a, S, 1, k, stream);
         else                           launch_mfma_rank<DIREFT>(a, S, k, stream);
         break;
     }
     case Path::Valu:
-        if (takes_small(a, S, a.d_out, a.d_out, DIREFT, k)) { launch_small<DIREFT>(a, S, 1, k, stream); break; }
+        if (takes_small(a, S, a.d_out, DIREFT, k)) { launch_small<DIREFT>(a, S, 1, k, stream); break; }
         if constexpr (!DIREFT) {
             if (a.rank <= 3 && launch_valu_split<1>(a, S, k, stream)) break;
         }

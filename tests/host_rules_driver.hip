@@ -29,7 +29,7 @@ int main()
             for (int i = 6; i < 9; ++i) widest = a[i] > widest ? (int)a[i] : widest;
             const preft::Knobs k = {};
             const preft::SmallShape s = preft::small_shape(p, a[1], n, k);
-            std::printf("%d %d %d %d %u\n", preft::takes_small(p, a[1], widest, a[6] + a[7] + a[8], false, k), s.units, s.deep, s.waves, preft::likely_units(p, a[1]));
+            std::printf("%d %d %d %d %u\n", preft::takes_small(p, a[1], widest, false, k), s.units, s.deep, s.waves, preft::likely_units(p, a[1]));
             continue;
         }
         if (!std::strcmp(what, "in_place")) {
@@ -37,7 +37,7 @@ int main()
                 if (std::scanf("%lld", &a[i]) != 1) return 1;
             preft::ApplyArgs p = {};
             p.T = (int)a[0]; p.N = (int)a[2]; p.all_tokens = (int)a[3]; p.rank = (int)a[4]; p.d_in = p.d_out = (int)a[5]; p.n_layers = 1;
-            std::printf("%d %d\n", preft::takes_small(p, a[1], p.d_in, p.d_in, true, preft::Knobs{}), preft::small_in_place_few(p, a[1]));
+            std::printf("%d %d\n", preft::takes_small(p, a[1], p.d_in, true, preft::Knobs{}), preft::small_in_place_few(p, a[1]));
             continue;
         }
         if (!std::strcmp(what, "route")) {
