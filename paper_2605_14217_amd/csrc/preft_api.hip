@@ -466,14 +466,19 @@ bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream
 
 // Rank 17 and up in multiples of 4, few tiles: the small-batch kernel's shrink sweep, then the expand launch; chunks and gathered tiles alike, any widths
 template <bool DIREFT>
-void launch_small_split(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
+void launch_small_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, hipStream_t stream)
 {
     const unsigned tiles = likely_units(a, S), slots = tiles / 8 < 65535 ? tiles / 8 : 65535;
     // two rank blocks a workgroup while that makes no more workgroups than compute units, else up to four, which share the tile's x
     const int blocks = z_rank_blocks(a.rank), most = likely_tiles(a, S) * n_slices * ((blocks + 1) / 2) <= 256 ? 2 : 4, rank_parts = (blocks + most - 1) / most, nb = (blocks + rank_parts - 1) / rank_parts;
     void (*shrink)(ApplyArgs, int) = nb == 4 ? small_shrink_kernel<4, DIREFT> : nb == 3 ? small_shrink_kernel<3, DIREFT> : a.rank <= 24 ? small_shrink_kernel<2, DIREFT, 24> : small_shrink_kernel<2, DIREFT>;
+    int waves = SMALL_WAVES;
+    if constexpr (!DIREFT) {
+        waves = small_shape(a, S, n_slices, k).waves;         // the single launch's: its sums of z are grouped by them
+        if (waves == 4) shrink = nb == 4 ? small_shrink_kernel<4, false, 0, 4> : nb == 3 ? small_shrink_kernel<3, false, 0, 4> : small_shrink_kernel<2, false, 0, 4>;
+    }
     const bool stay = activations_stay(a, out_width(a, n_slices), DIREFT, 2);
-    hipLaunchKernelGGL(shrink, dim3((unsigned)(n_slices * rank_parts) * 8, slots), dim3(SMALL_WAVES * 64), 0, stream, a, n_slices);
+    hipLaunchKernelGGL(shrink, dim3((unsigned)(n_slices * rank_parts) * 8, slots), dim3(waves * 64), 0, stream, a, n_slices);
     if (a.rank <= 32)
         launch_expand<2, false>(a, S, n_slices, stream);
     else if (a.rank <= 64)
@@ -493,7 +498,7 @@ void launch_small_order(const ApplyArgs &a, int64_t S, int n_slices, const Knobs
     for (int i = 1; i < n_slices; ++i) width += a.more[i - 1].d_out;
     const int cols = a.rank <= 32 ? EXPAND_WAVES * 128 : a.rank <= 64 ? 256 : 128, height = a.rank <= 32 ? 16 * EXPAND_MB : 16 * PANEL_RW;
     const bool ids_fit = tile_grid(a, S, height) * expand_panels(a, n_slices, cols) < ((int64_t)1 << 31);
-    if (a.zws && !a.h_layers && ids_fit && small_in_two(a, S, width, DIREFT, k)) launch_small_split<DIREFT>(a, S, n_slices, stream);
+    if (a.zws && !a.h_layers && ids_fit && small_in_two(a, S, width, DIREFT, k)) launch_small_split<DIREFT>(a, S, n_slices, k, stream);
     else launch_small<DIREFT>(a, S, n_slices, k, stream);
 }
 

@@ -557,10 +557,10 @@ __global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(
 // 64 ranks of A; two units on their way per wavefront.  Against the row-split kernel's 64-row tiles, whose wavefronts sweep all columns of their rows
 // one unit after the other, whole calls, us: 1400 prompt rows, 4096 -> 4096, rank 32 30.2 / 17.0, 64 36.7 / 17.8; 8192 -> 8192, rank 64 64 / 26; 3600 rows, 4096 -> 4096, rank 32 57.8 /
 // 32.4.  Against the small-batch kernel's single launch, 900 rows: rank 64, 4096 -> 4096 26.9 / 14.7, in place 42 / 16.5; rank 128 48 / 17.5, in place 137 (128-row tiles) / 19.6.
-template <int NB, bool DIREFT, int RK = 0>
-__global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_shrink_kernel(ApplyArgs p, int slices)
+// WAVES: those of the single launch for the same batch (SmallShape), which sum z in that many groups: with and without room for z the bits are the same.
+template <int NB, bool DIREFT, int RK = 0, int WAVES = SMALL_WAVES>
+__global__ __launch_bounds__(WAVES * 64, 2) void small_shrink_kernel(ApplyArgs p, int slices)
 {
-    constexpr int WAVES = SMALL_WAVES;
     __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, false, false>()];
     __shared__ float red[WAVES * NB * 4 * 64];
     const int parts = (p.rank + 16 * NB - 1) / (16 * NB), part = blockIdx.x >> 3, sl = part / parts;

@@ -195,6 +195,24 @@ def test_small_batch_shrink_then_expand(rank, d_in, d_outs, many):
     _lora(tab, 5, rank, d_in, d_outs, [(preft.test_flags(resident=2), True), (preft.test_flags(resident=2), False), (preft.test_flags(colsplit=3), True)])
 
 
+@pytest.mark.parametrize("rank", [36, 64, 128])
+@pytest.mark.parametrize("decode", [True, False], ids=["decode", "prompts"])
+def test_many_adapters_sum_in_the_same_groups(tmp_path_factory, rank, decode):
+    """About as many adapters as segments: the single launch has 4 wavefronts instead of 8, and the shrink launch sums in as many groups.  With room for z, without, and
+    with room as two launches in any case: the same bits."""
+    from test_host_rules import ask
+    rng = np.random.Generator(np.random.PCG64(rank))
+    if decode:
+        tab = wl.from_lengths(np.ones(512, int), rng.integers(0, 64, 512), np.zeros(512, int))
+    else:
+        lens = rng.integers(6, 20, 64)
+        tab = wl.from_lengths(lens, rng.permutation(64), lens)
+    d_in, d_out = 1544, 4104
+    takes, _, _, waves, _ = ask(tmp_path_factory, [f"small {tab.T} {tab.S} 64 1 {rank} {d_in} {d_out} 0 0"])[0].split()
+    assert (takes, waves) == ("1", "4")
+    _lora(tab, 64, rank, d_in, (d_out,), [(0, True), (0, False), (preft.test_flags(resident=2), True)])
+
+
 @pytest.mark.parametrize("rank,d", [(20, 8200), (32, 264), (36, 1032), (48, 4104), (64, 512), (68, 136), (96, 2056), (128, 264)])
 def test_small_batch_shrink_then_expand_in_place(rank, d):
     flags = preft.test_flags(resident=2)
