@@ -130,32 +130,22 @@ constexpr int64_t DEEP_WGS = 200;                             // at most one wor
 constexpr int32_t SMALL_STREAM_T = 6144;
 inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
 {
-    // Above rank 16 the two launches of the small-batch kernel's order (small_in_two) against those of 64-row tiles, us: 1400 / 3600 / 6000 / 12 000 prompt rows,
-    // 4096 -> 4096, rank 32 30 / 17, 58 / 32, 47 / 39, 66 / 68, rank 64 37 / 18, 87 / 42 (both beside 35 decode rows), 53 / 46, 72 / 84; 8192 -> 8192, rank 20 51 / 24, 93 / 47, 80 / 60, 118 / 123; 512 ->
-    // 2072 (against 16-row tiles), rank 20 6000 rows 18.9 / 22.2, rank 64 at 1400 to 24 000 rows 21 / 10, 38 / 21, 40 / 25, 128 / 78; rank 128, 512 -> 2072, 24 000 rows 248 / 94, 4096 -> 4096 at 3600
-    // rows (128-row tiles, one launch) 156 / 50, two launches of 64-row tiles 57, at 6000 68 / 66.  Decode rows, 3000 of 200 adapters: 8192 -> 8192, rank 32 97 / 81, 1024 -> 4096 + 2 x 1024
-    // 39.5 / 47.5.  (Without room for z the small-batch kernel's single launch: rank 33-64 between half and 1.45 of the time of 64-row tiles.)
+    // Above rank 16 the small-batch kernel's order, in one launch or (small_in_two, room for z) two, against the kernels of larger batches: those have a workgroup for
+    // every 64 or 128 rows, which leaves most of the chip idle up to 4096 rows.  The sums of z differ between the two, so the choice cannot depend on the room: it is
+    // made where neither the call with room nor the one without is slower.  This order / theirs over random calls of 1025 to 6144 rows, geometric mean with room, without (slower calls of
+    // all): whole widths (multiples of 128), rank 20-32 0.63, 0.45 (0 of 114), 36-64 0.63, 0.40 (4 of 155), 68-128 0.22, 0.34 (0 of 165); others 0.63, 0.60 (1 of 101), 0.57,
+    // 0.56 (0 of 61), 0.48, 0.67 (6 of 82), none by more than a fifth.
+    // What is left to them, as the single launch with its repeated shrink or the second launch is often the slower: decode rows, whose tiles they gather too, 0.90, 0.89 (91 of 453 slower, up to
+    // 1.6); above rank 32 segments of fewer than 20 rows on narrow inputs, above rank 64 and 2048 rows of fewer than 64, 0.51, 0.83 (21 of 115, up to 1.8), ragged outputs of up to 512
+    // columns, 1.03, 0.95 (19 of 55, up to 1.5; up to rank 32 above 3072 rows, rank 24, 512 -> 88, 5258 rows 5.5 / 10.0, 8.3), and those wider than 4096 above 1536 rows, 0.42, 0.73 (21 of 122, up to 1.8), all ragged ones above 4096 rows 0.65, 0.90 (34 of 163).
     if (a.rank > 16) {
-        if (a.rank % 4) return false;
+        if (a.rank % 4 || (a.all_tokens && a.T < 2 * S)) return false;
         const bool ragged = a.d_in % 128 || width % 128;      // (not each width: packed calls with one ragged output have the others wide)
-        const bool singles = a.all_tokens && a.T < 2 * S;
-        if (a.rank <= 48 && a.d_in < 2048 && singles) return false;
-        // Narrow outputs, ragged: 16-row tiles of one launch / here, us: rank 32, 1024 -> 264, 2000 prompt rows 8.6 / 12.3, rank 20, 512 -> 424, 3000 7.8 / 13.6, rank 24,
-        // 4096 -> 720, 2800 18.8 / 22.3 (but 4096 -> 512, 3600 38 / 21, 4096 -> 464, 1670 16.9 / 12.0); rank 96, 320 -> 256, 2060 9.4 / 14.2, rank 48, 568 -> 560, 3250 11.4 / 13.3, rank 64,
-        // 4096 -> 304, 10 600 59 / 70 (512 -> 328, 12 200 21.4 / 19.9).
-        if (ragged && a.rank <= 32 && !singles && width <= 768 && a.T > 2000 && (width % 128 || a.d_in <= 1024)) return false;
-        if (ragged && a.rank > 32 && ((a.d_in <= 600 && width <= 576 && a.T <= 8192) || (width <= 320 && a.T > 8192))) return false;
-        // Decode rows in more tiles than compute units, most of them part-empty: rank 48, 4096 -> 4096, 1270 rows of 171 adapters 32.8 / 39.7, rank 64, 1024 -> 4096, 2360 of 451 78 / 88,
-        // rank 128, 1024 -> 512, 1060 of 286 22 / 27; full ones: rank 64, 4096 -> 9816, 4000 of 33 173 / 100, 8192 -> 4128, 4000 of 15 107 / 68, but rank 48, 4096 -> 10240, 3900 of 2 63 / 78, rank
-        // 96, 3888 -> 10544, 2700 of 86 118 / 142, rank 64, 288 -> 2176, 3600 of 64 24 / 28.
-        if (singles && a.rank > 32) {
-            const int64_t tiles = likely_tiles(a, S);
-            if (tiles > 170 && 160 * tiles > 13 * a.T) return false;
-            if (tiles > 200 && ((width > 9216 && !(ragged && a.rank <= 64)) || (a.d_in <= 512 && width <= 4096))) return false;
-        }
-        if (a.rank > 32 && ragged) return true;
-        if (a.T <= 4096) return true;
-        return a.T <= SMALL_STREAM_T && a.d_in >= 2048 && (a.rank <= 32 || width <= 16384) && a.rank <= 64;
+        if (ragged && width <= 512 && a.T > (a.rank <= 32 ? 3072 : SMALL_T)) return false;
+        if (a.rank <= 32) return a.T <= 4096 || (a.T <= SMALL_STREAM_T && (ragged || a.d_in >= 2048));
+        if ((a.T < 20 * S && a.d_in <= 1024) || (a.rank > 64 && a.T > 2048 && a.T < 64 * S)) return false;
+        if (ragged) return a.T <= (width <= 4096 ? 4096 : 1536);
+        return a.T <= 4096 || (a.T <= SMALL_STREAM_T && a.d_in >= 2048 && width <= 16384 && a.rank <= 64);
     }
     if (a.T > SMALL_STREAM_T) return false;
     const int64_t d = a.d_in, singles = a.all_tokens && a.T < 2 * S;
