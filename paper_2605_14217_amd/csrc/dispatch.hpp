@@ -209,14 +209,19 @@ inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool dire
     if (k.resident == 2) return true;
     const bool singles = a.T < 2 * S;
     if (!a.all_tokens && prompt_rows(a, S) < 64) return false;            // hardly a row to do
-    if (a.T > SMALL_T) return true;
+    // Above SMALL_T rows a second launch costs 2 to 4 us, and what it saves are the shrinks that the shares of the outputs repeat.  Two launches / one over random prompts of 1025 to 6144 rows,
+    // geometric mean by columns of all outputs, up to 512, 1024, 2048, 4096, more: rank 20-32 1.44, 1.23, 1.17, 1.05, 0.90; 36-48 1.18, 1.10, 0.99, 0.90, 0.71; 52-64 1.22, 1.09, 0.93, 0.74,
+    // 0.60; 68-128 1.06, 0.87, 0.77, 0.65, 0.50; next to no shrink to repeat: rank 44, 256 -> 1032, 2748 rows 11.4 / 9.2.
+    if (a.T > SMALL_T) return a.rank <= 32 ? width > 4096 : a.rank <= 64 ? width > 1024 && a.d_in * width > 640000 : width > 512;
     const int64_t tiles = likely_tiles(a, S), panels = tiles * width;
     // (in place, decode rows of many adapters: rank 48, d = 3184, 209 of 376 20.8 / 23.6, 2688, 535 of 197 (184 tiles) 22.3 / 31.4, 4096, 730 of 54 (72 tiles) 25.5 / 22.9)
     if (direft && a.rank > 32 && a.rank <= 48 && a.d_in <= 4096 && singles && tiles > 128) return false;
-    if (direft) return a.rank > 64 || (a.rank > 48 ? a.d_in >= 1024 : a.rank > 32 ? a.d_in >= 2048 : a.d_in >= 8192 && tiles <= 48);
+    // (above rank 64, one / two: d = 104, 180 rows 7.7 / 14.5, 128, 109 8.1 / 9.3, 256, 68 7.9 / 9.9, 384, 362 9.3 / 10.5)
+    if (direft) return a.rank > 64 ? a.d_in >= 512 : (a.rank > 48 ? a.d_in >= 1024 : a.rank > 32 ? a.d_in >= 2048 : a.d_in >= 8192 && tiles <= 48);
     if (a.rank > 112) return a.d_in > 640 || panels >= 24000;    // 512 -> 1056, 29 decode rows 8.5 / 9.7, 512 -> 608, 242 prompt rows 8.7 / 9.6; 512 -> 8192, 3 rows 10.1 / 9.4
     if (a.rank > 64) return a.d_in >= 4096 || (!singles && panels >= 100000);
-    if (a.rank > 48) return singles ? (a.d_in >= 4096 && width >= 4096) || panels >= 250000 : panels >= 80000;
+    // (decode rows: rank 56, 8192 -> 320 + 8192 + 1024, 725 of 32 adapters 35.9 / 46.1, 1416 -> 1952, 234 of 200 20.3 / 28.7; over all, one and two alike)
+    if (a.rank > 48) return !singles && panels >= 80000;
     // (hardly a shrink to repeat: 512 -> 4096, 840 prompt rows 11.3 / 12.7, 296 -> 3640, 620 7.9 / 10.4, but 304 -> 14336, 730 18.2 / 14.5)
     return a.rank > 32 && !singles && panels >= 150000 && (a.d_in > 512 || width > 8192);
 }

@@ -1,10 +1,12 @@
-"""Where the lines of the dispatch lie that choose between kernels whose sums of z are grouped differently: such a choice is the same with and without room
-for z, so it is made only where neither side of it is the slower one.  Asked from the sources' own rules on the host."""
+"""Where lines of the dispatch lie, asked from the sources' own rules on the host.  Those that choose between kernels whose sums of z are grouped differently choose
+the same with and without room for z, so they do it only where neither side is the slower one."""
+import os
 import shutil
+import subprocess
 
 import pytest
 
-from test_host_rules import ask
+from test_host_rules import ROOT, ask
 
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
 
@@ -25,3 +27,31 @@ def test_calls_above_1024_rows_that_stay_with_the_kernels_of_larger_batches(tmp_
         assert not any(small(tmp_path_factory, short + ragged))
     # and those that the small-batch kernel keeps
     assert all(small(tmp_path_factory, [(T, 4, 64, 0, rank, d, n) for T in (1025, 2000) for d, n in ((4096, 4096), (512, 14336), (1000, 2072))]))
+
+
+ANSWERS = ("small", "two", "stay", "in_place_small", "in_place_two", "h_stays", "keeps_units")
+_exe = {}
+
+
+def lines(tmp_path_factory, cases):
+    """The driver's answers for calls (T, S, N, all positions, rank, d_in, columns of the output, bytes of an element)."""
+    if "exe" not in _exe:
+        exe = tmp_path_factory.mktemp("dispatch_lines") / "driver"
+        build = subprocess.run(["hipcc", "--cuda-host-only", "-std=c++17", os.path.join(ROOT, "tests", "dispatch_lines_driver.hip"), "-o", str(exe)], capture_output=True, text=True)
+        assert build.returncode == 0, build.stderr
+        _exe["exe"] = exe
+    run = subprocess.run([str(_exe["exe"])], input="".join(" ".join(map(str, c)) + "\n" for c in cases), capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr
+    out = [dict(zip(ANSWERS, (v == "1" for v in line.split()))) for line in run.stdout.splitlines()]
+    assert len(out) == len(cases)
+    return out
+
+
+def test_the_second_launch_of_few_tiles_has_a_shrink_to_save(tmp_path_factory):
+    one = [(3000, 8, 64, 0, rank, d, n, 2) for rank, d, n in ((20, 512, 112), (32, 4096, 4096), (40, 360, 1088), (48, 1848, 512), (60, 1024, 232), (56, 256, 2048), (68, 768, 128), (128, 4096, 512))]
+    one += [(725, 725, 32, 1, 56, 8192, 9536, 2), (960, 960, 4, 1, 56, 384, 14336, 2), (234, 234, 200, 1, 64, 1416, 1952, 2)]
+    assert not any(a["two"] for a in lines(tmp_path_factory, one))
+    two = [(3000, 8, 64, 0, rank, d, n, 2) for rank, d, n in ((20, 4096, 8192), (48, 1024, 4096), (64, 4096, 1536), (68, 1024, 1024), (128, 512, 4096))] + [(900, 5, 5, 0, 64, 4096, 4096, 2)]
+    assert all(a["two"] for a in lines(tmp_path_factory, two))
+    in_place = lines(tmp_path_factory, [(180, 24, 64, 1, 68, 104, 104, 2), (362, 362, 32, 1, 68, 384, 384, 2), (286, 3, 4, 0, 128, 144, 144, 2), (300, 2, 5, 0, 128, 512, 512, 2), (300, 2, 5, 0, 96, 4096, 4096, 2)])
+    assert [a["in_place_two"] for a in in_place] == [False, False, False, True, True]
