@@ -379,7 +379,10 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     // 1602, rank 63 q+k+v 1355 -> 1282; 352 814 rows, q+k+v 5100 -> 5000.  But 8192 -> 1024 376 -> 392: next to nothing to expand, and the single
     // launch has tiles enough.
     if (a.rank > 32 && a.T > 49152 && 4 * width <= a.d_in) return false;
-    if (a.rank > 64 && a.T > 14336 && a.d_in <= 512 && width <= 512) return false;      // rank 128, 512 -> 512, one launch / two: 25 000 rows 27 / 38, 19 600 38 / 46, 4000 25 / 22
+    // Above rank 64 z is as many bytes as 256 columns of y, written once and read by every panel: that pays where the columns are many (the workgroups of the single launch, 128 rows each, leave the chip
+    // idle and repeat nothing).  Two launches / one over random calls above 4096 rows, geometric mean by columns: up to 512 0.90 (22 of 107 slower, up to 1.9: rank 96, 128 -> 128, 9800 rows 20.4 /
+    // 10.7), 513 to 1024 0.83 (11 of 48, up to 1.3; none of those of d_in >= 2048, up to 16384 rows and 64 rows a segment), 0.64, 0.54, 0.43 above.
+    if (a.rank > 64 && width <= 1024) return a.d_in >= 2048 && width > 512 && a.T <= 16384 && a.T >= 64 * S;
     if (a.rank > 16) return true;
     if (a.all_tokens && a.T < 8 * S) return false;
     if (a.rank < 4) return a.T * width >= (n_slices > 1 ? 6000000 : 12000000) && width >= 3072 && (n_slices > 1 || !rows_off_lines(a, n_slices));
@@ -397,8 +400,9 @@ bool wants_split_in_place(const ApplyArgs &a, int64_t S, const Knobs &k)
     if (!expand_ids_fit(a, S, 1) || !offsets_fit(a)) return false;
     if (k.resident == 1) return true;
     if (a.T <= 1024 || prompt_rows(a, S) < 64) return false;
-    // above rank 64, rank 96, one launch / two: 24 000 rows, d = 512 28.8 / 34, 2048 83 / 80, 4096 173 / 144; 26 600 rows, d = 1024 46 / 54; 12 000 rows, d = 512 27.0 / 25.0, 2048 79 / 51
-    if (a.rank > 64) return a.d_in >= 2048 || a.T <= 14336;
+    // above rank 64, rank 96, one launch / two: 24 000 rows, d = 512 28.8 / 34, 2048 83 / 80, 4096 173 / 144; 26 600 rows, d = 1024 46 / 54; 12 000 rows, d = 512 27.0 / 25.0, 2048 79 / 51; rank 128,
+    // d = 128, 4600 rows 11.1 / 14.2; in segments of 50 to 70 rows, 512, 8600 rows 42.5 / 47.8, 1024, 13 200 46.5 / 51.0
+    if (a.rank > 64) return a.d_in >= 2048 || (a.d_in >= 512 && a.T <= 14336 && a.T >= 72 * S);
     return a.d_in >= 4096 || (a.d_in >= 1024 && a.T <= 8192);
 }
 
