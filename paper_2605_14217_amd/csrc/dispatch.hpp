@@ -315,4 +315,31 @@ inline bool odd_streams(const ApplyArgs &a, int64_t S, bool direft, const Knobs 
     return !wide_widths_ok(a, 1) || k.variant == 3 || (direft && a.rank <= 32 && k.variant == 0 && odd_streams_in_place(a, S));
 }
 
+// The expand launch of a call whose z is in the workspace: up to rank 32 a workgroup per 32 rows x 512 columns, above per 64 rows and panel.
+constexpr int EXPAND_MB = 2;
+
+inline int64_t expand_panels(const ApplyArgs &a, int n_slices, int64_t cols)
+{
+    int64_t panels = (a.d_out + cols - 1) / cols;
+    for (int i = 1; i < n_slices; ++i) panels += (a.more[i - 1].d_out + cols - 1) / cols;
+    return panels;
+}
+
+// Above rank 32: units of 128 columns in a panel of panel_expand_kernel, which every output holds a whole number of (the widths are
+// multiples of 128 there).  Rank 65-128: one unit of factors is 35 KB of LDS.
+inline int panel_units(const ApplyArgs &a, int n_slices)
+{
+    bool two = a.rank <= 64 && (a.d_out % 256) == 0;
+    for (int i = 1; i < n_slices; ++i) two = two && (a.more[i - 1].d_out % 256) == 0;
+    return two ? 2 : 1;
+}
+
+// the kernel numbers its tiles in 32 bits
+inline bool expand_ids_fit(const ApplyArgs &a, int64_t S, int n_slices)
+{
+    const int64_t tiles = a.rank > 32 ? tile_grid(a, S, 16 * PANEL_RW) * expand_panels(a, n_slices, 128 * panel_units(a, n_slices))
+                                      : tile_grid(a, S, 16 * EXPAND_MB) * expand_panels(a, n_slices, EXPAND_WAVES * 128);
+    return tiles < ((int64_t)1 << 31);
+}
+
 }  // namespace preft

@@ -70,7 +70,7 @@ template __global__ void preft::valu_tile_kernel<5, 2, 4, true, 1, 0, false>(pre
 template __global__ void preft::valu_tile_kernel<6, 2, 4, true, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<7, 2, 4, true, 1, 0, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<8, 2, 4, true, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<2, 2, 4, 8>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<3, 4, 4, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<5, 2, 4, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<7, 2, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<2, 4, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<4, 4, 1, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<6, 2, 1, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<7, 2, 4, 8>(preft::ApplyArgs);

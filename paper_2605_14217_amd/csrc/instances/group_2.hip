@@ -41,7 +41,6 @@ template __global__ void preft::mfma_wide_layers_kernel<2, 1, 4, 1, true>(preft:
 template __global__ void preft::mfma_wide_layers_kernel<4, 1, 8, 1, false>(preft::ApplyArgs);
 template __global__ void preft::panel_expand_kernel<4, 4, 1, false, false, false>(preft::ApplyArgs, int);
 template __global__ void preft::panel_expand_kernel<4, 4, 2, false, true, true>(preft::ApplyArgs, int);
-template __global__ void preft::panel_expand_kernel<8, 4, 2, false, false, false>(preft::ApplyArgs, int);
 template __global__ void preft::small_shrink_kernel<2, false, 24, 8>(preft::ApplyArgs, int);
 template __global__ void preft::small_shrink_kernel<4, false, 0, 8>(preft::ApplyArgs, int);
 template __global__ void preft::small_tile_kernel<1, false, false, false, 8, true, 0, true>(preft::ApplyArgs, preft::SmallLaunch);
@@ -71,7 +70,8 @@ template __global__ void preft::valu_tile_kernel<5, 2, 4, true, 1, 8, false>(pre
 template __global__ void preft::valu_tile_kernel<6, 2, 4, true, 1, 8, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<7, 2, 4, true, 1, 8, false>(preft::ApplyArgs);
 template __global__ void preft::valu_tile_kernel<8, 2, 4, true, 1, 8, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<2, 4, 1, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<4, 2, 4, 8>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<5, 2, 4, 8>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<7, 2, 4, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<1, 2, 4, 8>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<2, 4, 4, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<4, 4, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<6, 2, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<8, 2, 1, 0>(preft::ApplyArgs);

@@ -263,33 +263,6 @@ void launch_wide_shape(const ApplyArgs &a, int64_t S, hipStream_t stream)
     hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 16 * MB * RW), a.n_layers), dim3(RW * CW * 64), 0, stream, a);
 }
 
-// The expand launch of a call whose z is in the workspace: a workgroup per 32 rows x 512 columns.
-constexpr int EXPAND_MB = 2;
-
-inline int64_t expand_panels(const ApplyArgs &a, int n_slices, int64_t cols)
-{
-    int64_t panels = (a.d_out + cols - 1) / cols;
-    for (int i = 1; i < n_slices; ++i) panels += (a.more[i - 1].d_out + cols - 1) / cols;
-    return panels;
-}
-
-// Rank 33-64: units of 128 columns in a panel of panel_expand_kernel, which every output holds a whole number of (the widths are
-// multiples of 128 there).
-inline int panel_units(const ApplyArgs &a, int n_slices)
-{
-    bool two = (a.d_out % 256) == 0;
-    for (int i = 1; i < n_slices; ++i) two = two && (a.more[i - 1].d_out % 256) == 0;
-    return two ? 2 : 1;
-}
-
-// the kernel numbers its tiles in 32 bits
-inline bool expand_ids_fit(const ApplyArgs &a, int64_t S, int n_slices)
-{
-    const int64_t tiles = a.rank > 32 ? tile_grid(a, S, 16 * PANEL_RW) * expand_panels(a, n_slices, 128 * panel_units(a, n_slices))
-                                      : tile_grid(a, S, 16 * EXPAND_MB) * expand_panels(a, n_slices, EXPAND_WAVES * 128);
-    return tiles < ((int64_t)1 << 31);
-}
-
 // Columns of outputs whose rows do not start on 128-byte lines: neighbouring panels of those share lines.
 int64_t columns_off_lines(const ApplyArgs &a, int n_slices)
 {
@@ -342,9 +315,11 @@ void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stre
         }
         launch_expand_kernel(kernel, a, S, n_slices, stream);
     } else {
-        const int pu = NB == 8 ? 1 : panel_units(a, n_slices);        // rank 65-128: one unit of factors is 35 KB of LDS
-        void (*kernel)(ApplyArgs, int) = pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD> : panel_expand_kernel<NB, PANEL_RW, 1, ODD>;
-        if (stay) kernel = pu == 2 ? panel_expand_kernel<NB, PANEL_RW, 2, ODD, false, false> : panel_expand_kernel<NB, PANEL_RW, 1, ODD, false, false>;
+        const int pu = panel_units(a, n_slices);
+        void (*kernel)(ApplyArgs, int) = stay ? panel_expand_kernel<NB, PANEL_RW, 1, ODD, false, false> : panel_expand_kernel<NB, PANEL_RW, 1, ODD>;
+        if constexpr (NB == 4) {
+            if (pu == 2) kernel = stay ? panel_expand_kernel<NB, PANEL_RW, 2, ODD, false, false> : panel_expand_kernel<NB, PANEL_RW, 2, ODD>;
+        }
         launch_expand_kernel(kernel, a, S, n_slices, stream, 16 * PANEL_RW, 128 * pu, 64 * PANEL_RW);
     }
 }

@@ -29,7 +29,7 @@ def test_calls_above_1024_rows_that_stay_with_the_kernels_of_larger_batches(tmp_
     assert all(small(tmp_path_factory, [(T, 4, 64, 0, rank, d, n) for T in (1025, 2000) for d, n in ((4096, 4096), (512, 14336), (1000, 2072))]))
 
 
-ANSWERS = ("small", "two", "stay", "in_place_small", "in_place_two", "h_stays", "keeps_units")
+ANSWERS = ("small", "two", "stay", "in_place_small", "in_place_two", "h_stays", "keeps_units", "ids")
 _exe = {}
 
 
@@ -55,3 +55,10 @@ def test_the_second_launch_of_few_tiles_has_a_shrink_to_save(tmp_path_factory):
     assert all(a["two"] for a in lines(tmp_path_factory, two))
     in_place = lines(tmp_path_factory, [(180, 24, 64, 1, 68, 104, 104, 2), (362, 362, 32, 1, 68, 384, 384, 2), (286, 3, 4, 0, 128, 144, 144, 2), (300, 2, 5, 0, 128, 512, 512, 2), (300, 2, 5, 0, 96, 4096, 4096, 2)])
     assert [a["in_place_two"] for a in in_place] == [False, False, False, True, True]
+
+
+def test_tiles_of_an_expand_launch_are_counted_as_they_are_numbered(tmp_path_factory):
+    """64 rows a tile above rank 32, in panels of 256 columns where the width allows it and the rank is at most 64, else of 128; fewer than 2^31 ids."""
+    T, S = 64 * 8192, 1
+    got = lines(tmp_path_factory, [(T, S, 1, 0, rank, 4096, n, 2) for rank in (64, 68, 128) for n in (1 << 24, 1 << 25, 1 << 26)])
+    assert [a["ids"] for a in got] == [True, True, False, True, False, False, True, False, False]
