@@ -67,15 +67,17 @@ inline bool h_stays(const ApplyArgs &a)
     return bytes >= ((int64_t)16 << 20) && bytes <= ((int64_t)192 << 20);
 }
 
-// In place at rank 20-32, rows wider than 8192: whether every wavefront of the 32-row tiles keeps 8 of its units in registers between the sweeps.  It costs
-// half the wavefronts of a compute unit; a tile of such rows (576 KB at 9216) does not outlast its first sweep in an XCD's L2 in any case.  All streamed / 8 kept, us: rank 32, d = 9216 /
-// 10240 / 14336, 6000 rows 61.9 / 60.6, 73 / 70, 101 / 96; 18 000 rows 225 / 181, 264 / 209, 379 / 302; 30 000 rows 329 / 306, 393 / 351, 561 / 504; 72 000 rows 706 / 692, 814 / 779;
-// 28672, 18 000 rows 752 / 683; 4 layers of 1600 rows, 10240 125 / 72; prompts of 45 rows, 14336, 12 000 rows 410 / 391; rank 20, 18 000 rows, 14336 358 / 289, but 9216, 72 000 rows 658 /
-// 670, and 4000 decode rows of 64 adapters 124 / 141 (rank 32 148 / 145).  8192 and narrower: rank 32, 12 000 rows 109 / 106, 60 000 505 / 515, 4096 54 / 56, 2048 30 / 33, rank 20, 8192 99.5 / 104.8.
+// In place at rank 20-32, rows wider than 8192: whether every wavefront of the 32-row tiles keeps 8 of its units in registers between the sweeps.  That costs
+// half the wavefronts of a compute unit (40 of its registers are spilled besides, 84 bytes a lane); a tile of such rows (576 KB at 9216) does not outlast its first sweep in an XCD's L2 in any
+// case.  All streamed / 8 kept, us, two buffers in turn, prompts of 600 rows: rank 32, d = 9216 / 10240 / 14336 / 28672, 6000 rows 62.6 / 61.8, 72.3 / 70.2, 102 / 103, 242 / 230; 12 000 rows 134 /
+// 122, 158 / 140, 224 / 201, 457 / 444; 18 000 rows 233 / 190, 271 / 216, 367 / 310, 714 / 646; 30 000 rows 344 / 321, 401 / 364, 564 / 519, 1144 / 1083; 72 000 rows 713 / 712, 808 / 782, 1128 /
+// 1083, 2408 / 2321; rank 20, 72 000 rows 645 / 645 (9216), 756 / 754; 4 layers of 1600 rows, 10240 132 / 73.  8192 and narrower: rank 32, 12 000 rows 109 / 106, 60 000 505 / 515, 4096 54 / 56,
+// 2048 30 / 33, rank 20, 8192 99.5 / 104.8.
+// Short segments leave the tiles part-empty, and the streamed form has more of them on their way: rank 20, 8320, 2500 rows in 239 prompts 122 / 170; rank 32, 12288, 2200 in 143 158 / 183, 10256, 3100 in
+// 66 113 / 118; 4 layers, rank 28, 14336, 2600 in 225 552 / 898, rank 20, 14336, 1600 in 25 144 / 152; 12 000 in 120 231 / 212.
 inline bool keeps_units(const ApplyArgs &a, int64_t S)
 {
-    if (a.d_in <= 8192) return false;
-    if (a.all_tokens && a.T < 2 * S && a.T > 2048) return false;
+    if (a.d_in <= 8192 || a.T < 72 * S) return false;
     return a.d_in >= 10240 || a.T <= 32768;
 }
 

@@ -241,3 +241,10 @@ def test_in_place_calls_that_the_cache_can_hold(rank, d, empty):
 def test_wide_rows_in_place_keep_units(rank, d):
     """Rank 20-32 on rows wider than 8192: 8 units a wavefront in registers, the bits of tiles that are streamed in both sweeps."""
     _direft(_table(rank, d, 5), 5, rank, d, [(0, True), (preft.test_flags(variant=3), True)], 0)
+
+
+@pytest.mark.parametrize("rank,d", [(20, 9224), (32, 10240), (28, 14336)])
+def test_wide_rows_of_long_prompts_keep_units(rank, d):
+    """The same where the dispatch takes that form: segments of 72 rows and more on average."""
+    tab = wl.from_lengths(np.array([700, 129, 500, 33, 161]), np.array([0, 3, -1, 2, 0]), np.array([700, 128, 500, 33, 0]))
+    _direft(tab, 5, rank, d, [(0, True), (preft.test_flags(variant=3), True)], 0)
