@@ -47,24 +47,32 @@ inline int64_t likely_tiles(const ApplyArgs &a, int64_t S)
     return extra / 16 + (extra ? prompts / 2 + 1 : 0) + likely_gathered(a, S);
 }
 
-// Whether what a call reads and writes of its activations (once each, `es` bytes an element) is little enough for the memory-side cache (256 MB) to still hold it from the
-// kernel before, and for the kernel after: then it is read without the non-temporal hint, which has it fetched from memory.  Hint / none, us, two sets of buffers in turn: fp32,
-// rank 16, 4096 -> 4096, 2304 rows (75 MB) 31.8 / 27.1, 5000 rows (165 MB) 59 / 68; rank 31, 3760 -> 600, 6000 rows (52 MB) 36.5 / 27.2; rank 20, 1000 -> 2000, 5900 rows (35 MB) 21.7 / 19.2; in place,
-// rank 64, d = 4096, 5000 rows (41 MB) 50.6 / 46.9; 4096 -> 4096, rank 64, 8400 rows (138 MB) 60.3 / 62.7, rank 16, 12 600 rows (206 MB) 62 / 72.  Below the size of the L2s together (32 MB) the
-// lines of y that were read plainly are written back at the end of the kernel: rank 48, 4096 -> 4096, 880 rows (14 MB) 13.7 / 14.9, fp32, rank 4, 1024 -> 1024, 2400 rows (20 MB) 9.9 / 11.0.
-inline bool activations_stay(const ApplyArgs &a, int64_t width, bool direft, int es)
+// Whether what a call reads and writes of its activations (once each, `es` bytes an element) is little enough, with the factors that pass by, for the memory-side cache (256 MB) to still hold it
+// from the kernel before, and for the kernel after: then it is read without the non-temporal hint, which has it fetched from memory.  y has just been written when a call adds to it, so
+// what decides is how much passes between that kernel and this one.  Hint / none, us, the same buffers again, two in turn, four in turn (from 64 MB on these have left the cache): single launches:
+// fp32, rank 16, 4096 -> 4096, 38 MB 22.4 / 21.9, 22.0 / 21.0, 21.7 / 20.7, 56 MB 25.1 / 24.2, 24.3 / 23.1, 23.9 / 23.9, 75 MB 32.6 / 29.3, 31.8 / 27.8, 32.0 / 35.8, 112 MB 37.5 / 33.8, 36.6 / 34.3, 37.1 /
+// 41.4, 187 MB 64.0 / 57.5, 64.8 / 71.5, 68.3 / 73.0; rank 20, 1000 -> 2072 (rows off lines), 70 MB 38.1 / 33.8, 38.9 / 33.2, 39.7 / 37.1; rank 31, 3760 -> 600, 70 MB 34.2 / 30.1, 36.4 / 29.7, 36.8 / 35.4.
+// Expands of two launches: rank 32, 4096 -> 4096, 56 MB 27.5 / 26.5, 27.2 / 25.9, 26.6 / 25.3, 75 MB 35.5 / 35.6, 35.1 / 35.1, 35.2 / 38.9; rank 64, 8192 -> 8192, 56 MB 30.8 / 29.4, 30.2 / 29.3,
+// 30.2 / 31.4, 75 MB 39.5 / 38.5, 39.0 / 38.1, 39.2 / 43.7.  So the single launches keep it up to where three such calls fill the cache, the expands, which gain less, up to where four do.
+// Below the size of the L2s together (32 MB) the lines of y that were read plainly are written back at the end of the kernel: rank 64, 4096 -> 4096, 28 MB 19.1 / 19.8, 19.2 / 19.5, 18.5 / 19.2; fp32, rank 4,
+// 1024 -> 1024, 23 MB 9.8 / 10.9, 11.0 / 11.6, 11.5 / 11.2, 33 MB 16.8 / 19.0, 18.1 / 18.9, 17.5 / 18.4.  In place in fp32 (the tile is read twice in either form) 47 MB 30.4 / 30.7, 75 MB 51.2 / 59.2: always the hint.
+// Factors count: 4096 decode rows of 512 adapters, rank 44, 4936 -> 896 (48 MB of activations, 260 of factors) 54.1 / 57.7.
+constexpr int64_t STAY_SINGLE = (int64_t)76 << 20, STAY_EXPAND = (int64_t)64 << 20;
+inline bool activations_stay(const ApplyArgs &a, int64_t S, int64_t width, int es, int64_t most)
 {
-    const int64_t bytes = a.T * (direft ? (int64_t)a.d_in : a.d_in + width) * es * a.n_layers;
-    return bytes >= ((int64_t)28 << 20) && bytes <= ((int64_t)76 << 20);
+    const int64_t activations = a.T * (a.d_in + width) * es, factors = likely_adapters(S, a.N) * a.rank * (a.d_in + width) * es;
+    return activations >= ((int64_t)(es == 4 ? 36 : 32) << 20) && activations + factors <= most;
 }
 
-// The same for the two launches of an in-place call: the expand reads h again where the shrink has read it, and neither has the hint.  Hint in the shrink, and in the expand
-// above 76 MB / none, us: rank 64, d = 4096, 12 000 / 18 000 / 24 000 / 30 000 / 36 000 rows (98 to 295 MB) 70.9 / 63.9, 99 / 89, 121 / 109, 157 / 155, 178 / 184; 8192, 1200 rows (20 MB) 62.6 / 57.3, 6000 90 /
-// 81, 12 000 (197 MB) 126 / 122, 13 800 161 / 166; 14336, 6000 154 / 143, 7800 (224 MB) 172 / 177; rank 48, 4096, 18 000 95 / 86; rank 96 121 / 110; but 1200 rows (10 MB) 44.6 / 47.3.
+// The same for the two launches of an in-place call: the expand reads h again where the shrink has read it, and neither has the hint.  Hint in the shrink, and in the expand from 76 MB on /
+// none, us, the same buffer again, two in turn, four in turn: rank 64, d = 4096, 14 MB 35.6 / 39.1, 37.4 / 39.3, 38.2 / 38.9; 23 MB 43.8 / 41.5, 43.9 / 41.6, 43.9 / 40.5; 47 MB 54.0 / 49.6, 53.3 / 48.4, 53.0 /
+// 48.3; 61 MB 59.7 / 54.2, 59.4 / 53.4, 60.0 / 59.2; 98 MB 78.5 / 69.1, 76.6 / 67.8, 76.0 / 79.1; 126 MB 99 / 87, 99 / 103, 98 / 112; 187 MB 125 / 112, 123 / 138, 123 / 145; 8192, 19 MB 62.1 / 60.0, 62.7 /
+// 60.4, 63.0 / 60.2, 56 MB 79.1 / 72.4, 78.6 / 71.7, 78.6 / 73.7, 122 MB 104 / 94, 105 / 105, 105 / 110; 14336, 66 MB 118 / 105, 118 / 104, 118 / 115; rank 48 alike; rank 96, 4096, 61 MB 73.3 / 69.6, 72.7 / 70.5,
+// 73.7 / 71.8, 126 MB 117 / 108, 112 / 119, 112 / 123.  h that is still in the cache gains up to 200 MB, h that is not loses from 76 MB on: so up to 64.
 inline bool h_stays(const ApplyArgs &a)
 {
     const int64_t bytes = a.T * (int64_t)a.d_in * 2;
-    return bytes >= ((int64_t)16 << 20) && bytes <= ((int64_t)192 << 20);
+    return bytes >= ((int64_t)20 << 20) && bytes <= ((int64_t)64 << 20);
 }
 
 // In place at rank 20-32, rows wider than 8192: whether every wavefront of the 32-row tiles keeps 8 of its units in registers between the sweeps.  That costs

@@ -7,25 +7,24 @@
 #include "../valu_kernel.hpp"
 
 template __global__ void preft::f32_tile_kernel<1, false, true, true, false>(preft::ApplyArgs);
-template __global__ void preft::f32_tile_kernel<1, true, true, true, true>(preft::ApplyArgs);
-template __global__ void preft::f32_tile_kernel<2, true, false, false, false>(preft::ApplyArgs);
-template __global__ void preft::f32_tile_kernel<4, false, true, false, true>(preft::ApplyArgs);
-template __global__ void preft::f32_tile_kernel<8, false, true, false, false>(preft::ApplyArgs);
-template __global__ void preft::f32_tile_layers_kernel<2, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_expand_kernel<1, 2, true, (preft::YHint)0>(preft::ApplyArgs, int);
-template __global__ void preft::mfma_tile_kernel<1, 1, 4, 0, false, 2, false, 0, false, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_kernel<1, 1, 4, 0, false, 3, false, 4, false, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_kernel<1, 1, 8, 0, false, 1, false, 2, true, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_kernel<1, 1, 8, 0, false, 3, false, 0, false, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_kernel<1, 1, 8, 8, true, 1, false, 0, false, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_kernel<2, 1, 4, 0, false, 1, false, 1, false, false>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_kernel<2, 2, 4, 0, false, 1, false, 1, false, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_kernel<4, 1, 4, 0, false, 1, false, 1, false, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_kernel<8, 1, 4, 0, false, 1, false, 0, false, true>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_layers_kernel<1, 1, 4, 8, false, 2>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_layers_kernel<1, 1, 8, 8, false, 2>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_layers_kernel<2, 2, 4, 8, true, 0>(preft::ApplyArgs);
-template __global__ void preft::mfma_tile_outputs_kernel<2, 4, 1>(preft::ApplyArgs);
+template __global__ void preft::f32_tile_kernel<2, false, false, false, true>(preft::ApplyArgs);
+template __global__ void preft::f32_tile_kernel<4, false, false, false, false>(preft::ApplyArgs);
+template __global__ void preft::f32_tile_kernel<8, false, false, false, true>(preft::ApplyArgs);
+template __global__ void preft::f32_tile_layers_kernel<2, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_expand_kernel<1, 2, true, (preft::YHint)2>(preft::ApplyArgs, int);
+template __global__ void preft::mfma_tile_kernel<1, 1, 4, 0, false, 2, false, 2, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_kernel<1, 1, 4, 0, true, 1, false, 0, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_kernel<1, 1, 8, 0, false, 1, false, 4, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_kernel<1, 1, 8, 0, false, 3, false, 2, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_kernel<1, 1, 8, 8, true, 1, false, 2, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_kernel<2, 1, 4, 0, false, 1, false, 1, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_kernel<2, 2, 4, 0, true, 1, false, 0, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_kernel<4, 1, 4, 0, true, 1, false, 0, false, true>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_kernel<8, 1, 4, 0, false, 1, false, 1, false, false>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_layers_kernel<1, 1, 4, 8, false, 4>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_layers_kernel<1, 1, 8, 8, false, 4>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_layers_kernel<4, 1, 4, 0, false, 0>(preft::ApplyArgs);
+template __global__ void preft::mfma_tile_outputs_kernel<4, 4, 0>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_kernel<1, 2, 4, 1, false, 1, false, false, false, true>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 2, false, false, false, true>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_kernel<2, 1, 4, 1, false, 3, true, false, false, true>(preft::ApplyArgs);
@@ -39,8 +38,8 @@ template __global__ void preft::mfma_wide_kernel<8, 1, 8, 1, true, 1, false, fal
 template __global__ void preft::mfma_wide_layers_kernel<1, 1, 8, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<4, 1, 4, 1, false>(preft::ApplyArgs);
 template __global__ void preft::mfma_wide_layers_kernel<8, 1, 8, 1, true>(preft::ApplyArgs);
-template __global__ void preft::panel_expand_kernel<4, 4, 2, false, false, false>(preft::ApplyArgs, int);
-template __global__ void preft::panel_expand_kernel<8, 4, 1, false, false, true>(preft::ApplyArgs, int);
+template __global__ void preft::panel_expand_kernel<4, 4, 2, false, true, false>(preft::ApplyArgs, int);
+template __global__ void preft::panel_expand_kernel<8, 4, 1, false, true, true>(preft::ApplyArgs, int);
 template __global__ void preft::small_shrink_kernel<3, false, 0, 8>(preft::ApplyArgs, int);
 template __global__ void preft::small_tile_kernel<1, false, false, false, 8, false, 3, true>(preft::ApplyArgs, preft::SmallLaunch);
 template __global__ void preft::small_tile_kernel<1, false, false, false, 8, true, 4, true>(preft::ApplyArgs, preft::SmallLaunch);
@@ -59,18 +58,18 @@ template __global__ void preft::small_tile_layers_kernel<1, false, true, 0>(pref
 template __global__ void preft::small_tile_layers_kernel<1, true, false, 8>(preft::ApplyArgs, preft::SmallLaunch);
 template __global__ void preft::small_tile_layers_kernel<2, true, false, 0>(preft::ApplyArgs, preft::SmallLaunch);
 template __global__ void preft::small_tile_layers_kernel<8, false, true, 0>(preft::ApplyArgs, preft::SmallLaunch);
-template __global__ void preft::thin_expand_kernel<1, 2>(preft::ApplyArgs, int);
-template __global__ void preft::valu_tile_kernel<1, 4, 2, true, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<1, 4, 4, true, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<2, 4, 4, false, 1, 0, true>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<3, 4, 1, false, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<3, 4, 4, false, 2, 0, true>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<4, 4, 2, false, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<5, 2, 2, true, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<6, 2, 2, true, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<7, 2, 2, true, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_kernel<8, 2, 2, true, 1, 0, false>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<2, 2, 4, 8>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<3, 4, 4, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<5, 2, 4, 0>(preft::ApplyArgs);
-template __global__ void preft::valu_tile_layers_kernel<7, 2, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::thin_expand_kernel<3, 2>(preft::ApplyArgs, int);
+template __global__ void preft::valu_tile_kernel<1, 4, 4, false, 1, 0, true>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<2, 4, 1, false, 1, 0, false>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<2, 4, 4, false, 2, 0, true>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<3, 4, 2, false, 1, 0, false>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<3, 4, 4, false, 3, 0, true>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<4, 4, 4, false, 1, 0, false>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<5, 2, 4, true, 1, 0, false>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<6, 2, 4, true, 1, 0, false>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<7, 2, 4, true, 1, 0, false>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_kernel<8, 2, 4, true, 1, 0, false>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<2, 4, 2, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<4, 4, 1, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<6, 2, 1, 0>(preft::ApplyArgs);
+template __global__ void preft::valu_tile_layers_kernel<7, 2, 4, 8>(preft::ApplyArgs);

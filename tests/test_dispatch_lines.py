@@ -69,3 +69,12 @@ def test_units_stay_in_registers_where_the_tiles_are_full(tmp_path_factory):
     short = [(2510, 239, 200, 0, 20, 8320, 8320, 2), (2588, 225, 32, 0, 28, 14336, 14336, 2), (6305, 130, 200, 0, 24, 8320, 8320, 2), (1613, 25, 64, 0, 20, 14336, 14336, 2), (900, 900, 4, 1, 32, 9216, 9216, 2)]
     assert not any(a["keeps_units"] for a in lines(tmp_path_factory, short + [(18000, 30, 64, 0, 32, 8192, 8192, 2)]))
     assert all(a["keeps_units"] for a in lines(tmp_path_factory, [(18000, 30, 64, 0, 32, 10240, 10240, 2), (12000, 120, 64, 0, 20, 14336, 14336, 2)]))
+
+
+def test_what_is_read_without_the_non_temporal_hint(tmp_path_factory):
+    """Activations between the L2s together and a quarter (fp32 and single launches: a third) of the memory-side cache, the factors of many adapters counted; in place 20 to 64 MB of h."""
+    lora = [(2300, 4, 4, 0, 16, 4096, 4096, 4), (2600, 4, 4, 0, 16, 4096, 4096, 4), (3000, 4, 4, 0, 32, 4096, 4096, 2), (4400, 4, 4, 0, 32, 4096, 4096, 2), (1900, 4, 4, 0, 32, 4096, 4096, 2),
+            (3000, 3000, 512, 1, 44, 4096, 4096, 2)]
+    assert [a["stay"] for a in lines(tmp_path_factory, lora)] == [True, False, True, False, False, False]
+    h = [(1200, 4, 4, 0, 64, 8192, 8192, 2), (1300, 4, 4, 0, 64, 8192, 8192, 2), (4000, 4, 4, 0, 64, 8192, 8192, 2), (4200, 4, 4, 0, 64, 8192, 8192, 2)]
+    assert [a["h_stays"] for a in lines(tmp_path_factory, h)] == [False, True, True, False]
