@@ -75,7 +75,7 @@ inline bool h_stays(const ApplyArgs &a)
     return bytes >= ((int64_t)20 << 20) && bytes <= ((int64_t)64 << 20);
 }
 
-// In place at rank 20-32, rows wider than 8192: whether every wavefront of the 32-row tiles keeps 8 of its units in registers between the sweeps.  That costs
+// In place at rank 20-32, rows of 9216 and more: whether every wavefront of the 32-row tiles keeps 8 of its units in registers between the sweeps.  That costs
 // half the wavefronts of a compute unit (40 of its registers are spilled besides, 84 bytes a lane); a tile of such rows (576 KB at 9216) does not outlast its first sweep in an XCD's L2 in any
 // case.  All streamed / 8 kept, us, two buffers in turn, prompts of 600 rows: rank 32, d = 9216 / 10240 / 14336 / 28672, 6000 rows 62.6 / 61.8, 72.3 / 70.2, 102 / 103, 242 / 230; 12 000 rows 134 /
 // 122, 158 / 140, 224 / 201, 457 / 444; 18 000 rows 233 / 190, 271 / 216, 367 / 310, 714 / 646; 30 000 rows 344 / 321, 401 / 364, 564 / 519, 1144 / 1083; 72 000 rows 713 / 712, 808 / 782, 1128 /
@@ -83,9 +83,11 @@ inline bool h_stays(const ApplyArgs &a)
 // 2048 30 / 33, rank 20, 8192 99.5 / 104.8.
 // Short segments leave the tiles part-empty, and the streamed form has more of them on their way: rank 20, 8320, 2500 rows in 239 prompts 122 / 170; rank 32, 12288, 2200 in 143 158 / 183, 10256, 3100 in
 // 66 113 / 118; 4 layers, rank 28, 14336, 2600 in 225 552 / 898, rank 20, 14336, 1600 in 25 144 / 152; 12 000 in 120 231 / 212.
+// And where the tiles are about as many as the compute units, the wavefronts that are missing are not made up for by another round of tiles: 7700 rows, 9216 / 10240 / 12288, rank 20 1.14 / 1.08 / 1.06 of the time of the
+// streamed form, 24 1.11 / 1.06 / 1.04, 28 1.09 / 1.04 / 1.02, 32 1.03 / 0.98 / 0.95 (5000 rows 0.97 / 0.98 / 0.97, 9300 0.91-1.01, 0.92-0.99, 0.91-0.98); 8320, 5000 to 12 000 rows 0.93-1.15.
 inline bool keeps_units(const ApplyArgs &a, int64_t S)
 {
-    if (a.d_in <= 8192 || a.T < 72 * S) return false;
+    if (a.d_in < 9216 || a.T < 72 * S || (a.d_in < 12288 && a.T > 6144 && a.T <= 8704)) return false;
     return a.d_in >= 10240 || a.T <= 32768;
 }
 

@@ -67,7 +67,7 @@ def test_tiles_of_an_expand_launch_are_counted_as_they_are_numbered(tmp_path_fac
 def test_units_stay_in_registers_where_the_tiles_are_full(tmp_path_factory):
     """In place, rank 20-32: not for segments that leave the 32-row tiles part-empty, prompts or decode rows."""
     short = [(2510, 239, 200, 0, 20, 8320, 8320, 2), (2588, 225, 32, 0, 28, 14336, 14336, 2), (6305, 130, 200, 0, 24, 8320, 8320, 2), (1613, 25, 64, 0, 20, 14336, 14336, 2), (900, 900, 4, 1, 32, 9216, 9216, 2)]
-    assert not any(a["keeps_units"] for a in lines(tmp_path_factory, short + [(18000, 30, 64, 0, 32, 8192, 8192, 2)]))
+    assert not any(a["keeps_units"] for a in lines(tmp_path_factory, short + [(18000, 30, 64, 0, 32, 9208, 9208, 2), (7700, 14, 64, 0, 24, 9216, 9216, 2)]))
     assert all(a["keeps_units"] for a in lines(tmp_path_factory, [(18000, 30, 64, 0, 32, 10240, 10240, 2), (12000, 120, 64, 0, 20, 14336, 14336, 2)]))
 
 
