@@ -223,8 +223,9 @@ inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool dire
     if (!a.all_tokens && prompt_rows(a, S) < 64) return false;            // hardly a row to do
     // Above SMALL_T rows a second launch costs 2 to 4 us, and what it saves are the shrinks that the shares of the outputs repeat.  Two launches / one over random prompts of 1025 to 6144 rows,
     // geometric mean by columns of all outputs, up to 512, 1024, 2048, 4096, more: rank 20-32 1.44, 1.23, 1.17, 1.05, 0.90; 36-48 1.18, 1.10, 0.99, 0.90, 0.71; 52-64 1.22, 1.09, 0.93, 0.74,
-    // 0.60; 68-128 1.06, 0.87, 0.77, 0.65, 0.50; next to no shrink to repeat: rank 44, 256 -> 1032, 2748 rows 11.4 / 9.2.
-    if (a.T > SMALL_T) return a.rank <= 32 ? width > 4096 : a.rank <= 64 ? width > 1024 && a.d_in * width > 640000 : width > 512;
+    // 0.60; 68-128 1.06, 0.87, 0.77, 0.65, 0.50; next to no shrink to repeat: rank 44, 256 -> 1032, 2748 rows 11.4 / 9.2.  Activations that no cache holds any more (above 64 MB) come better in the expand's
+    // order: rank 32, 4096 -> 4096, 4000 / 4600 / 5750 rows, four sets of buffers in turn 32.9 / 38.1, 35.0 / 42.8, 38.9 / 46.7.
+    if (a.T > SMALL_T) return a.rank <= 32 ? width > (a.T > 3840 ? 2048 : 4096) : a.rank <= 64 ? width > 1024 && a.d_in * width > 640000 : width > 512;
     const int64_t tiles = likely_tiles(a, S), panels = tiles * width;
     // (in place, decode rows of many adapters: rank 48, d = 3184, 209 of 376 20.8 / 23.6, 2688, 535 of 197 (184 tiles) 22.3 / 31.4, 4096, 730 of 54 (72 tiles) 25.5 / 22.9)
     if (direft && a.rank > 32 && a.rank <= 48 && a.d_in <= 4096 && singles && tiles > 128) return false;
