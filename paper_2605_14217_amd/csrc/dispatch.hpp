@@ -161,12 +161,11 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
     }
     if (a.T > SMALL_STREAM_T) return false;
     const int64_t d = a.d_in, singles = a.all_tokens && a.T < 2 * S;
-    if (a.rank <= 2 && singles && 8 * width <= d) return false;
     if (a.rank >= 4 && width <= 1024 && d <= 2048) return false;          // rank 16, 1104 -> 1024, 1080 prompt rows 5.4 / 5.7
     if (a.rank >= 4 && !singles && d > 8192 && width > 4608) return false;   // rank 11, 14336 -> 5176, 1470 prompt rows 26.7 / 42.5, rank 16, 14336 -> 5832, 1490 31 / 38 (rank 5, 14336 -> 4448, 1300 26 / 18)
     if (width > 10240 && !(a.rank < 4 && singles)) return false;          // rank 8, 912 -> 14336 + 4096 + 1512, 1240 prompt rows 28.3 / 34.0
     const int64_t elements = a.T * (d + 2 * width) + likely_adapters(S, a.N) * a.rank * (d + width);
-    const int64_t most = a.rank < 4 && singles ? 180000000 : d >= 8192 && width >= 8192 && a.T >= 8 * S ? 48000000 : 76000000;
+    const int64_t most = a.rank < 4 && singles ? 120000000 : d >= 8192 && width >= 8192 && a.T >= 8 * S ? 48000000 : 76000000;
     return elements <= most;
 }
 
@@ -178,6 +177,9 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     if (k.resident == 2 && a.rank > 16 && a.rank % 4 == 0) return true;
     if ((k.variant != 0 && k.variant != 5) || k.waves || k.rowblocks || k.resident) return false;
     if (!direft && k.colsplit) return k.colsplit > 1;
+    // Ranks 1 and 2, next to nothing to expand: the vector-ALU kernel / this, us: rank 1, 8192 -> 512, 41 rows 4.8 / 6.9, 14336 -> 1024, 19 rows 6.5 / 9.6, 7040 -> 512, 850 rows 5.5 / 6.8, 2048 -> 408, 14 rows 3.7
+    // / 4.1 (d_in from 4 to 8 times the columns, 10 calls 0.93, 8 times and more, 8 calls 1.14; below 4 times 0.77 and less); rank 2, 9016 -> 1024, 8 rows 6.6 / 7.4, 4096 -> 88, 1100 rows 8.6 / 9.9.
+    if (!direft && (a.rank == 1 ? 4 : 8) * width <= a.d_in && a.rank <= 2) return false;
     if (!direft) return a.T <= SMALL_T || (k.variant == 0 && no_long_stream(a, S, width));
     if (a.T > SMALL_T) return false;
     // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 1000
@@ -195,7 +197,11 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     if (a.all_tokens && prompt_rows(a, S) == 0 && likely_tiles(a, S) <= 32 && a.T <= 3 * likely_tiles(a, S)) return true;
     // Ranks 1-3, rows resident in a wavefront's registers / this, us: rank 1, d = 1024, 250 and 920 prompt rows 3.6 / 3.7, 4.2 / 3.9, 4096 7.6 / 7.1, 512 decode rows 8.2 /
     // 7.2, rank 3 9.7 / 8.4, 11.2 / 9.3, 11.1 / 8.6; but rank 1, d = 512, 250 rows 3.2 / 3.4.
-    if (a.rank == 1 && a.d_in <= 512) return false;
+    // rank 3, prompts of 7 rows, d = 128, 105 rows 4.3 / 5.4, 96 4.6 / 5.7.
+    if (a.rank < 4 && a.d_in <= (a.rank == 1 ? 512 : 256)) return false;
+    // More tiles than that fill the chip with the layers of a call, each of which takes the kernel of its one-layer call: 8 layers, rank 2, d = 896, 81 rows in 74 tiles 6.7 / 9.2; 4 layers, rank 1, 2048,
+    // 360 rows 7.0 / 9.0, rank 2, 3456, 300 rows in 57 prompts 14.4 / 17.0; over all one-layer calls of more 0.96.
+    if (a.rank < 4 && likely_tiles(a, S) > 24) return false;
     // and wide rows of fuller tiles than a few decode rows: rank 1, d = 4096, 150 prompt rows 6.4 / 7.2, 74 decode rows of 3 adapters 6.4 / 7.3, rank 2, 230 prompt rows 7.2 / 7.9, 396 7.4 /
     // 8.2 (482 9.5 / 8.2; 160 decode rows of 313 adapters 7.1 / 5.3)
     if (a.rank <= 2 && a.d_in > 2048 && a.T <= 448 && a.T > 5 * likely_tiles(a, S)) return false;

@@ -78,3 +78,11 @@ def test_what_is_read_without_the_non_temporal_hint(tmp_path_factory):
     assert [a["stay"] for a in lines(tmp_path_factory, lora)] == [True, False, True, False, False, False]
     h = [(1200, 4, 4, 0, 64, 8192, 8192, 2), (1300, 4, 4, 0, 64, 8192, 8192, 2), (4000, 4, 4, 0, 64, 8192, 8192, 2), (4200, 4, 4, 0, 64, 8192, 8192, 2)]
     assert [a["h_stays"] for a in lines(tmp_path_factory, h)] == [False, True, True, False]
+
+
+def test_ranks_1_to_3_that_stay_with_the_vector_alu(tmp_path_factory):
+    """Next to nothing to expand, in place narrow rows, or tiles enough to fill the chip with the layers of one call."""
+    lora = [(41, 34, 32, 0, 1, 8192, 512, 2), (850, 2, 1, 0, 1, 7040, 512, 2), (8, 1, 64, 0, 2, 9016, 1024, 2), (2000, 2000, 500, 1, 1, 4096, 512, 2), (41, 34, 32, 0, 1, 4096, 4096, 2), (41, 34, 32, 0, 3, 8192, 512, 2)]
+    assert [a["small"] for a in lines(tmp_path_factory, lora)] == [False, False, False, False, True, True]
+    h = [(81, 74, 512, 1, 2, 896, 896, 2), (360, 16, 200, 1, 1, 2048, 2048, 2), (105, 14, 512, 0, 3, 128, 128, 2), (32, 32, 8, 1, 2, 896, 896, 2), (100, 2, 8, 0, 3, 1024, 1024, 2)]
+    assert [a["in_place_small"] for a in lines(tmp_path_factory, h)] == [False, False, False, True, True]
