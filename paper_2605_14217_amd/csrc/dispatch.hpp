@@ -161,11 +161,17 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
     }
     if (a.T > SMALL_STREAM_T) return false;
     const int64_t d = a.d_in, singles = a.all_tokens && a.T < 2 * S;
-    if (a.rank >= 4 && width <= 1024 && d <= 2048) return false;          // rank 16, 1104 -> 1024, 1080 prompt rows 5.4 / 5.7
-    if (a.rank >= 4 && !singles && d > 8192 && width > 4608) return false;   // rank 11, 14336 -> 5176, 1470 prompt rows 26.7 / 42.5, rank 16, 14336 -> 5832, 1490 31 / 38 (rank 5, 14336 -> 4448, 1300 26 / 18)
+    // Narrow inputs and outputs: rank 16, 1104 -> 1024, 1080 prompt rows 5.4 / 5.7, 768 -> 1296, 3500 7.1 / 7.7, rank 12, 2304 -> 1024, 2000 in 106 prompts 10.4 / 11.6; up to 3200 rows rank 8, 2048 -> 2048, 1600
+    // / 2000 / 2800 7.4 / 8.2, 8.0 / 9.1, 9.4 / 10.3, 1024 -> 2048 6.8 / 7.2, 7.0 / 7.5, 8.2 / 9.0, rank 16, 1024 -> 2144, 3200 9.4 / 11.6 (4000 rows,
+    // 2048 -> 2048 17.1 / 14.0; ranks that are no multiple of 4, rank 5 and 9, 1600 to 2800 rows 7.2-10.0 / 6.4-10.0).
+    if (a.rank >= 4 && d <= 2304 && (width <= 1296 || (width <= 2176 && a.T <= 3200 && !singles && a.rank % 4 == 0))) return false;
+    // (rank 1, 1024 -> 1024, 1300 rows 4.8 / 5.9, rank 2, 512 -> 1024, 2300 in 241 prompts 7.1 / 10.5)
+    if (a.rank <= 2 && d <= 1024 && width <= 1024) return false;
+    if (a.rank >= 4 && !singles && d > 8192 && width > 4096) return false;   // rank 11, 14336 -> 5176, 1470 prompt rows 26.7 / 42.5, rank 16, 14336 -> 5832, 1490 31 / 38, 4224, 1720 28 / 36 (rank 5, 14336 -> 4448, 1300 26 / 18)
     if (width > 10240 && !(a.rank < 4 && singles)) return false;          // rank 8, 912 -> 14336 + 4096 + 1512, 1240 prompt rows 28.3 / 34.0
+    // (8192 -> 6144, rank 12, 1600 rows (33) 21.7 / 24.2, 2800 (57) 28.2 / 31.5)
     const int64_t elements = a.T * (d + 2 * width) + likely_adapters(S, a.N) * a.rank * (d + width);
-    const int64_t most = a.rank < 4 && singles ? 120000000 : d >= 8192 && width >= 8192 && a.T >= 8 * S ? 48000000 : 76000000;
+    const int64_t most = a.rank < 4 && singles ? 120000000 : d >= 8192 && width > 4608 && a.T >= 8 * S ? 24000000 : 76000000;
     return elements <= most;
 }
 
@@ -180,6 +186,9 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     // Ranks 1 and 2, next to nothing to expand: the vector-ALU kernel / this, us: rank 1, 8192 -> 512, 41 rows 4.8 / 6.9, 14336 -> 1024, 19 rows 6.5 / 9.6, 7040 -> 512, 850 rows 5.5 / 6.8, 2048 -> 408, 14 rows 3.7
     // / 4.1 (d_in from 4 to 8 times the columns, 10 calls 0.93, 8 times and more, 8 calls 1.14; below 4 times 0.77 and less); rank 2, 9016 -> 1024, 8 rows 6.6 / 7.4, 4096 -> 88, 1100 rows 8.6 / 9.9.
     if (!direft && (a.rank == 1 ? 4 : 8) * width <= a.d_in && a.rank <= 2) return false;
+    // A very wide output beside narrow ones: every share of these repeats the shrink as well, and the wide one's take 64 units where 32 of 8192 columns do: 4096 -> 136 + 208 + 8448, 2900 rows, rank 4 33.3 /
+    // 47.5, 16 37.4 / 52.6; decode rows, rank 2, 2048 -> 256 + 384 + 14336, 4096 73 / 85 (4096 -> 512 + 8192, rank 16 32.7 / 33.4).
+    if (!direft && a.T > SMALL_T && widest > 8192 && width > widest && 4 * (width - widest) < widest) return false;
     if (!direft) return a.T <= SMALL_T || (k.variant == 0 && no_long_stream(a, S, width));
     if (a.T > SMALL_T) return false;
     // In place the resident shapes of mfma_tile_kernel stay ahead up to rank 16 where their tile fits (rank 16, d = 4096, 1000
