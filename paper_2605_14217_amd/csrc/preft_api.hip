@@ -149,7 +149,7 @@ void launch_small_shape(ApplyArgs a, int64_t S, int n_slices, const Knobs &k, hi
         auto pick = [&](auto few_tag) {
             constexpr bool FEW = decltype(few_tag)::value;
             void (*kernel)(ApplyArgs, SmallLaunch) = small_tile_kernel<NB, false, ODD, true, SMALL_WAVES, FEW, RK>;
-            if constexpr (NB == 2 && !ODD) { if (shape.units < SMALL_WAVES) kernel = small_tile_kernel<NB, false, ODD, true, SMALL_WAVES, FEW, RK, false>; }
+            if constexpr (NB == 2 && !ODD && RK != 20 && RK != 28) { if (shape.units < SMALL_WAVES) kernel = small_tile_kernel<NB, false, ODD, true, SMALL_WAVES, FEW, RK, false>; }
             if constexpr (NB == 1) { if (!shape.deep) kernel = small_tile_kernel<NB, false, ODD, false, SMALL_WAVES, FEW, RK>; }
             if constexpr (NB > 2) { if (shape.waves == 4) kernel = small_tile_kernel<NB, false, ODD, true, 4, FEW>; }
             return kernel;
@@ -168,7 +168,9 @@ void launch_small(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k, h
         constexpr bool ODD = decltype(odd_tag)::value;
         if (a.rank <= 8)       launch_small_shape<1, DIREFT, ODD, 8>(a, S, n_slices, k, stream);
         else if (a.rank <= 16) launch_small_shape<1, DIREFT, ODD>(a, S, n_slices, k, stream);
-        else if (!ODD && a.rank <= 24) launch_small_shape<2, DIREFT, false, 24>(a, S, n_slices, k, stream);
+        else if (a.rank == 20) launch_small_shape<2, DIREFT, false, 20>(a, S, n_slices, k, stream);
+        else if (a.rank == 24) launch_small_shape<2, DIREFT, false, 24>(a, S, n_slices, k, stream);
+        else if (a.rank == 28) launch_small_shape<2, DIREFT, false, 28>(a, S, n_slices, k, stream);
         else if (a.rank <= 32) launch_small_shape<2, DIREFT, ODD>(a, S, n_slices, k, stream);
         else if (a.rank <= 64) launch_small_shape<4, DIREFT, ODD>(a, S, n_slices, k, stream);
         else                   launch_small_shape<8, DIREFT, ODD>(a, S, n_slices, k, stream);

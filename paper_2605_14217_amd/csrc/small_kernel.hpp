@@ -25,12 +25,17 @@ constexpr int SMALL_WAVES = 8;
 // rows, 7.4 / 7.6.  Without / with it, us: rank 32, 900 prompt rows 14.4 / 13.5, in place, 32 decode rows, d = 4096 13.4 / 11.4; rank 7 (which had its factors in LDS
 // already), 600 prompt rows 8.4 / 8.0, 200 decode rows 7.6 / 7.3.  (Factors straight from memory in that column order, 16 lines an instruction: in place 7.9 / 12.2, rank 48 17.7 / 36.)
 // LINES: rank 17-32 out of place, shares of 8 units and more, where every wavefront has a unit (rank 32, 4096 -> 512, 300 rows, shares of 2 units, without / with 7.9 / 8.6).
-template <int NB, bool DIREFT, bool ODD, bool LINES> constexpr bool small_direct(int NG) { return ODD ? NB == 1 : NB == 2 && (DIREFT || (LINES && NG == 4)); }
+// Not at ranks 20 and 28, whose columns are an odd number of 8-byte quarters: with / without it, us, in place, rank 28, d = 2048 / 4096 / 8192, 300 decode rows 10.5 / 9.4, 16.7 / 15.0, 28.9 / 25.8, rank 20, 32
+// rows 8.3 / 8.0, 12.4 / 11.7, 19.9 / 18.5; 900 prompt rows, 4096 -> 4096, rank 28 15.2 / 13.1, rank 20 13.8 / 13.0.
+template <int NB, bool DIREFT, bool ODD, bool LINES, int RK> constexpr bool small_direct(int NG)
+{
+    return ODD ? NB == 1 : NB == 2 && RK != 20 && RK != 28 && (DIREFT || (LINES && NG == 4));
+}
 // A wavefront's own LDS, in 16-byte vectors: a unit of activations and one of the factor in turn, later a unit's factors of the expand.
-template <int NB, bool DIREFT, bool ODD, bool LINES>
+template <int NB, bool DIREFT, bool ODD, bool LINES, int RK>
 constexpr int small_area()
 {
-    constexpr int turns = 2 * 16 * MFMA_TRS, factors = small_direct<NB, DIREFT, ODD, LINES>(4) ? (FactorLds<NB>::BYTES + 15) / 16 : 0;
+    constexpr int turns = 2 * 16 * MFMA_TRS, factors = small_direct<NB, DIREFT, ODD, LINES, RK>(4) ? (FactorLds<NB>::BYTES + 15) / 16 : 0;
     return turns > factors ? turns : factors;
 }
 
@@ -50,7 +55,7 @@ struct SmallOutput {                                          // the output of a
     int slice, slices, rank0;                                 // the shrink alone: which output of how many, and its first rank
 };
 
-// RK: 0, or the largest rank of the form: 1, 2, 3 and 4 are that rank, 8 the ranks 5 to 8, 24 the ranks 20 and 24.  An instruction brings four ranks of a unit of A:
+// RK: 0, or the largest rank of the form: 1, 2, 3 and 4 are that rank, 8 the ranks 5 to 8, 20, 24 and 28 that rank.  An instruction brings four ranks of a unit of A:
 // those that no such rank has are left out.  Ranks 1-3 are too thin for the matrix cores' expand, and z stays
 // in fp32: the sums of valu_tile_kernel, a lane's 8 columns of its rows, whose factors are RK 16-byte pieces.
 // Before / now, replayed, us: 32 decode rows of 32 adapters, a layer's six launches, rank 1 64.5 / 28.1, 3 118 / 33.5 (valu_tile_kernel: 16 rows of a tile on four wavefronts),
@@ -60,12 +65,12 @@ struct SmallOutput {                                          // the output of a
 // launch follows.
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, int NG, int RK, bool ZOUT, bool LINES>
 __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallOutput &o, const i32x4_t entry, bool gathered, int row0, int n_rows, int unit,
-                                                u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD, LINES>()], float (&red)[WAVES * NB * 4 * 64])
+                                                u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD, LINES, RK>()], float (&red)[WAVES * NB * 4 * 64])
 {
     constexpr bool ANY = ODD && NB > 1;                       // ranks above 16 that are no multiple of 4
-    constexpr bool DIRECT = !ZOUT && small_direct<NB, DIREFT, ODD, LINES>(NG), THIN = RK >= 1 && RK <= 3;
+    constexpr bool DIRECT = !ZOUT && small_direct<NB, DIREFT, ODD, LINES, RK>(NG), THIN = RK >= 1 && RK <= 3;
     constexpr int RANKS = RK ? RK : 16 * NB;
-    auto groups = [](int b) constexpr { return RANKS - 16 * b >= 16 ? 4 : (RANKS - 16 * b + 3) / 4; };     // of four ranks in block b of a unit of A: 1, 2 or 4
+    auto groups = [](int b) constexpr { return RANKS - 16 * b > 8 ? 4 : (RANKS - 16 * b + 3) / 4; };     // of four ranks in block b of a unit of A that are loaded: 1, 2 or 4
     // units of the shrink and of the expand sweep in flight (registers)
     constexpr int BATCH = ZOUT ? 2 : DEEP ? (NB == 1 ? 4 : NB <= 4 ? 2 : 1) : 2;
     // units of the expand that are asked for before the shrink's last ones are used (registers).  With that, waits for one unit at a time (sweep below) and
@@ -486,7 +491,7 @@ __device__ __forceinline__ void small_tile_rows(const ApplyArgs &p, const SmallO
 // FEW: with the form for tiles of up to four rows (in place only for steps of decode rows: its second copy of the code costs the others 0.1 us of 4.5).
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW, int RK, bool ZOUT, bool LINES>
 __device__ __forceinline__ void small_tile_one(const ApplyArgs &p, const SmallOutput &o, int unit, int n_chunk_units,
-                                               u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD, LINES>()], float (&red)[WAVES * NB * 4 * 64])
+                                               u32x4_t (&area)[WAVES][small_area<NB, DIREFT, ODD, LINES, RK>()], float (&red)[WAVES * NB * 4 * 64])
 {
     // the tile: 16 rows of a chunk, or a gathered tile (rows listed one by one)
     const bool gathered = unit >= n_chunk_units;
@@ -507,7 +512,7 @@ struct SmallLaunch { int shares0, shares1; };
 template <int NB, bool DIREFT, bool ODD, bool DEEP, int WAVES, bool FEW, int RK, bool LINES>
 __device__ __forceinline__ void small_tile_body(const ApplyArgs &p, const SmallLaunch &l)
 {
-    __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, ODD, LINES>()];
+    __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, ODD, LINES, RK>()];
     __shared__ float red[WAVES * NB * 4 * 64];
 
     // What the launch arguments say is asked for together with the header: each line of them that is touched later is a trip of its own (in
@@ -561,7 +566,7 @@ __global__ __launch_bounds__(SMALL_WAVES * 64, 2) void small_tile_layers_kernel(
 template <int NB, bool DIREFT, int RK = 0, int WAVES = SMALL_WAVES>
 __global__ __launch_bounds__(WAVES * 64, 2) void small_shrink_kernel(ApplyArgs p, int slices)
 {
-    __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, false, false>()];
+    __shared__ u32x4_t area[WAVES][small_area<NB, DIREFT, false, false, RK>()];
     __shared__ float red[WAVES * NB * 4 * 64];
     const int parts = (p.rank + 16 * NB - 1) / (16 * NB), part = blockIdx.x >> 3, sl = part / parts;
     SmallOutput o = {nullptr, 0, 0, 0, p.A_pool, nullptr, sl, slices, (part - sl * parts) * 16 * NB};

@@ -178,3 +178,22 @@ def test_small_ranks(rank, d_in, d_outs):
     assert bool(torch.isfinite(y[~mine]).all()) and not bool(torch.isfinite(y[mine]).any())
     if rank == 1:
         assert bool(torch.isinf(y[mine]).all())
+
+
+@pytest.mark.parametrize("rank", [20, 24, 28, 32])
+@pytest.mark.parametrize("d_in,d_out", [(264, 1032), (1000, 520), (4104, 2056)])
+def test_forms_of_rank_20_to_32(rank, d_in, d_out):
+    """Each rank has a form of its own (the groups of the first factor that are loaded, the way of the second): tiles of one to sixteen rows, prompts and decode rows, out of place
+    and in place, one layer and several, against the oracle."""
+    from parity_util import run_direft_case, run_direft_layers_case, run_lora_case
+    lens = np.array([1] * 26 + [17, 20, 36, 130])
+    ids = np.concatenate([np.repeat(np.arange(4), [1, 4, 5, 16]), 4 + np.arange(4)]).astype(int)
+    order = np.random.Generator(np.random.PCG64(rank + d_in)).permutation(len(lens))
+    tab = wl.from_lengths(lens[order], ids[order], np.where(lens > 1, lens, 0)[order])
+    x = wl.activations(tab.T, d_in, "bf16", device="cuda", seed=1)
+    y0 = wl.activations(tab.T, d_out, "bf16", device="cuda", seed=2)
+    for all_tokens in (True, False):
+        run_lora_case(tab, wl.lora_pool(8, rank, d_in, d_out, "bf16", device="cuda", seed=3), x, y0, "bf16", 2.0, all_tokens, pad_cols=8)
+        run_direft_case(tab, wl.direft_pool(8, rank, d_in, "bf16", device="cuda", seed=4), x, "bf16", 0.5, all_tokens, pad_cols=8)
+    run_direft_layers_case(tab, [wl.direft_pool(8, rank, d_in, "bf16", device="cuda", seed=l) for l in range(2)],
+                           [wl.activations(tab.T, d_in, "bf16", device="cuda", seed=9 + l) for l in range(2)], "bf16", 0.5, True, [True, False], pad_cols=8)
