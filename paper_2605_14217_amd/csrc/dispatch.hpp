@@ -208,9 +208,10 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     // 7.2, rank 3 9.7 / 8.4, 11.2 / 9.3, 11.1 / 8.6; but rank 1, d = 512, 250 rows 3.2 / 3.4.
     // rank 3, prompts of 7 rows, d = 128, 105 rows 4.3 / 5.4, 96 4.6 / 5.7.
     if (a.rank < 4 && a.d_in <= (a.rank == 1 ? 512 : 256)) return false;
-    // More tiles than that fill the chip with the layers of a call, each of which takes the kernel of its one-layer call: 8 layers, rank 2, d = 896, 81 rows in 74 tiles 6.7 / 9.2; 4 layers, rank 1, 2048,
-    // 360 rows 7.0 / 9.0, rank 2, 3456, 300 rows in 57 prompts 14.4 / 17.0; over all one-layer calls of more 0.96.
-    if (a.rank < 4 && likely_tiles(a, S) > 24) return false;
+    // Many part-empty tiles fill the chip with the layers of a call, each of which takes the kernel of its one-layer call: 8 layers, rank 2, d = 896, 81 rows in 74 tiles 6.7 / 9.2; 4 layers, rank 2, 3456,
+    // 300 rows in 57 prompts 14.4 / 17.0 (full ones too, but one layer of those gains: 4 layers, rank 1, 2048, 360 rows in 31 tiles 7.0 / 9.0).
+    // Narrow rows, full tiles too: 8 layers, rank 3, d = 512, 557 rows 12.8 / 17.5.
+    if (a.rank < 4 && likely_tiles(a, S) > 24 && (a.d_in <= 512 || a.T < 8 * likely_tiles(a, S))) return false;
     // and wide rows of fuller tiles than a few decode rows: rank 1, d = 4096, 150 prompt rows 6.4 / 7.2, 74 decode rows of 3 adapters 6.4 / 7.3, rank 2, 230 prompt rows 7.2 / 7.9, 396 7.4 /
     // 8.2 (482 9.5 / 8.2; 160 decode rows of 313 adapters 7.1 / 5.3)
     if (a.rank <= 2 && a.d_in > 2048 && a.T <= 448 && a.T > 5 * likely_tiles(a, S)) return false;
