@@ -247,6 +247,9 @@ inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool dire
     if (direft && a.rank > 32 && a.rank <= 48 && a.d_in <= 4096 && singles && tiles > 128) return false;
     // (above rank 64, one / two: d = 104, 180 rows 7.7 / 14.5, 128, 109 8.1 / 9.3, 256, 68 7.9 / 9.9, 384, 362 9.3 / 10.5)
     if (direft) return a.rank > 64 ? a.d_in >= 512 : (a.rank > 48 ? a.d_in >= 1024 : a.rank > 32 ? a.d_in >= 2048 : a.d_in >= 8192 && tiles <= 48);
+    // (tiles enough to fill the chip hide the single launch's shrinks: 900 decode rows of 200 / 500 adapters, one / two, 4096 -> 512, rank 68 29.0 / 33.7, 49.7 / 59.4, rank 128 43.5 / 49.4, 102 / 108, 4096 ->
+    // 4096, rank 68 53.6 / 67.0, 115 / 149, 96 72 / 86, 149 / 170, 128 107 / 111, 203 / 208; 150 of 200, rank 96, 8192 -> 2144 55 / 50; 512 of 64, 4096 -> 512 22.5 / 19.2)
+    if (a.rank > 64 && singles && tiles > 160) return false;
     if (a.rank > 112) return a.d_in > 640 || panels >= 24000;    // 512 -> 1056, 29 decode rows 8.5 / 9.7, 512 -> 608, 242 prompt rows 8.7 / 9.6; 512 -> 8192, 3 rows 10.1 / 9.4
     if (a.rank > 64) return a.d_in >= 4096 || (!singles && panels >= 100000);
     // (decode rows: rank 56, 8192 -> 320 + 8192 + 1024, 725 of 32 adapters 35.9 / 46.1, 1416 -> 1952, 234 of 200 20.3 / 28.7; over all, one and two alike)

@@ -49,9 +49,9 @@ def lines(tmp_path_factory, cases):
 
 def test_the_second_launch_of_few_tiles_has_a_shrink_to_save(tmp_path_factory):
     one = [(3000, 8, 64, 0, rank, d, n, 2) for rank, d, n in ((20, 512, 112), (32, 4096, 4096), (40, 360, 1088), (48, 1848, 512), (60, 1024, 232), (56, 256, 2048), (68, 768, 128), (128, 4096, 512))]
-    one += [(725, 725, 32, 1, 56, 8192, 9536, 2), (960, 960, 4, 1, 56, 384, 14336, 2), (234, 234, 200, 1, 64, 1416, 1952, 2)]
+    one += [(725, 725, 32, 1, 56, 8192, 9536, 2), (960, 960, 4, 1, 56, 384, 14336, 2), (234, 234, 200, 1, 64, 1416, 1952, 2), (900, 900, 500, 1, 96, 4096, 1024, 2)]
     assert not any(a["two"] for a in lines(tmp_path_factory, one))
-    two = [(3000, 8, 64, 0, rank, d, n, 2) for rank, d, n in ((20, 4096, 8192), (48, 1024, 4096), (64, 4096, 1536), (68, 1024, 1024), (128, 512, 4096))] + [(900, 5, 5, 0, 64, 4096, 4096, 2)]
+    two = [(3000, 8, 64, 0, rank, d, n, 2) for rank, d, n in ((20, 4096, 8192), (48, 1024, 4096), (64, 4096, 1536), (68, 1024, 1024), (128, 512, 4096))] + [(900, 5, 5, 0, 64, 4096, 4096, 2), (512, 512, 64, 1, 96, 4096, 1024, 2)]
     assert all(a["two"] for a in lines(tmp_path_factory, two))
     in_place = lines(tmp_path_factory, [(180, 24, 64, 1, 68, 104, 104, 2), (362, 362, 32, 1, 68, 384, 384, 2), (286, 3, 4, 0, 128, 144, 144, 2), (300, 2, 5, 0, 128, 512, 512, 2), (300, 2, 5, 0, 96, 4096, 4096, 2)])
     assert [a["in_place_two"] for a in in_place] == [False, False, False, True, True]
