@@ -253,7 +253,8 @@ inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool dire
     if (a.rank > 112) return a.d_in > 640 || panels >= 24000;    // 512 -> 1056, 29 decode rows 8.5 / 9.7, 512 -> 608, 242 prompt rows 8.7 / 9.6; 512 -> 8192, 3 rows 10.1 / 9.4
     if (a.rank > 64) return a.d_in >= 4096 || (!singles && panels >= 100000);
     // (decode rows: rank 56, 8192 -> 320 + 8192 + 1024, 725 of 32 adapters 35.9 / 46.1, 1416 -> 1952, 234 of 200 20.3 / 28.7; over all, one and two alike)
-    if (a.rank > 48) return !singles && panels >= 80000;
+    // (tiles x columns from 80 000 to 120 000: d_in 1024 0.95-1.27, 2048 0.84-1.15, 4096 0.75-0.96 of one launch's time; up to 160 000 0.57-1.04, 0.60-1.01, 0.59-0.92)
+    if (a.rank > 48) return !singles && panels >= (a.d_in > 2048 ? 80000 : 120000);
     // (hardly a shrink to repeat: 512 -> 4096, 840 prompt rows 11.3 / 12.7, 296 -> 3640, 620 7.9 / 10.4, but 304 -> 14336, 730 18.2 / 14.5)
     return a.rank > 32 && !singles && panels >= 150000 && (a.d_in > 512 || width > 8192);
 }
