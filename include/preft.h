@@ -100,7 +100,7 @@ enum {
  *   PREFT_TEST_ROWBLOCKS(b)  MFMA kernels: 16-row blocks per wavefront: 0 = automatic, 1 or 2
  *   PREFT_TEST_COLSPLIT(c)   LoRA, matrix cores: workgroups that share a tile of one output, each writing its share
  *                            of the output columns (the small-batch kernel): 0 = automatic (that kernel for
- *                            batches of up to 1024 rows and, at rank 1..16, a few thousand), 1 = the kernels of larger batches, 2..15 (fp32: 1..15).
+ *                            batches of up to 1024 rows and, of most shapes, prompts of a few thousand), 1 = the kernels of larger batches, 2..15 (fp32: 1..15).
  *                            Together with variant 4 it names the column groups of the row-split kernel
  *                            instead: 0 = automatic, 1 or 2
  *   PREFT_TEST_RESIDENT(n)   0 = automatic.  LoRA, and in place at rank 33..128: 1 = two launches (preft_workspace_bytes_z)
@@ -108,7 +108,7 @@ enum {
  *                            20..128 in multiples of 4: 2 = the small-batch kernel at any batch size, as two launches
  *                            where the workspace has room for z.  In-place
  *                            MFMA kernel at rank 20..32 (automatic: 32-row tiles, streamed in
- *                            both sweeps up to 8192 columns and as 3 above): 3 = every wavefront keeps 8 of its
+ *                            both sweeps; long prompts of wide rows as 3): 3 = every wavefront keeps 8 of its
  *                            128-column units in registers between the sweeps (half of a
  *                            32-row tile of 8192 columns) and streams the rest twice
  */
@@ -153,9 +153,9 @@ size_t preft_workspace_bytes(int32_t T, int32_t S);
  * preft_loreft_apply) of up to `rank`.  A bf16 LoRA call
  * that is handed at least this many bytes runs its two sweeps as two launches -- shrink into z, then the
  * expand in 2-D tiles -- where that is faster: on more than 1024 rows wide outputs (4096 -> 2 x 14336 at rank 16: 1.15x on 37 000 rows, 1.8x on
- * 1100), and nearly every shape above rank 16; above rank 32 smaller batches too (rank 64, 4096 -> 4096, 900 rows: half
+ * 1100), and above rank 16 most shapes that are not narrow; above rank 32 smaller batches too (rank 64, 4096 -> 4096, 900 rows: half
  * the time); not on a step of decode rows that has nothing to apply.
- * So does a bf16 in-place call above rank 32 where that is faster (d = 4096, 900 rows: rank 64 in two fifths of the time, rank 128 in a seventh),
+ * So does a bf16 in-place call above rank 32 where that is faster (d = 4096, 900 rows: rank 64 in two fifths of the time, rank 128 in a quarter),
  * and on rows of 8192 and more from rank 17 on.
  * With fewer bytes, or outside those limits,
  * the same call runs in one launch.  The result is the same bit for bit.
@@ -231,9 +231,9 @@ int preft_lora_apply(void *y, int64_t ldy, const void *x, int64_t ldx,
  * disjoint column ranges of one buffer (a fused qkv or gate-up output: same row stride, every
  * range inside one row); any other overlap, and any overlap with x, is PREFT_EINVAL.
  * The result is that of n_proj preft_lora_apply calls.  For bf16 they run as one launch at rank 1..16, above it on batches
- * of at most 1024 rows, and on larger batches at rank 17..64 when every width is a
- * multiple of 128; otherwise the call issues one launch per projection.  (Batches of at most 1024 rows read x once per workgroup, the
- * others once per launch.)
+ * of at most 1024 rows, on larger batches at rank 17..64 when every width is a
+ * multiple of 128, and on prompts of a few thousand rows where the kernel of small batches takes them; otherwise the call issues one launch per projection.  (That
+ * kernel reads x once per workgroup, the others once per launch.)
  */
 int preft_lora_apply_packed(int32_t n_proj, void *const *y, const int64_t *ldy, const int32_t *d_out,
                             const void *x, int64_t ldx, int32_t T, int32_t d_in,
@@ -270,7 +270,7 @@ int preft_direft_apply(void *h, int64_t ldh, int32_t T, int32_t d,
  * kept in a static area of device memory inside the library (PREFT_STATIC_SCRATCH_BYTES bytes,
  * which every GPU the library runs on holds until the process ends) instead of a caller workspace.
  * The rest of the area takes the place of a workspace's room for z: a call that runs as two launches
- * (bf16, rank 33..64, see preft_workspace_bytes_z) keeps z there if it fits, and otherwise runs as one.
+ * (bf16, mostly above rank 32, see preft_workspace_bytes_z) keeps z there if it fits, and otherwise runs as one.
  * The call allocates and frees nothing, on the host or the device.
  *
  * Limit: preft_workspace_bytes(T, S) <= PREFT_STATIC_SCRATCH_BYTES (every batch of up to 32 768

@@ -118,7 +118,7 @@ inline bool wide_widths_ok(const ApplyArgs &a, int cw)
     return (a.d_in % m) == 0 && (a.d_out % m) == 0;
 }
 
-// Whether the matrix-core kernels take a bf16 call: from rank 4 on (ranks 1..3 are a vector-ALU matter).
+// Whether the matrix-core kernels take a bf16 call: from rank 4 on (ranks 1..3: the small-batch kernel, whose shrink is theirs, or the vector-ALU kernel).
 inline bool mfma_takes(const ApplyArgs &a, const Knobs &k)
 {
     if (a.rank < 4) return false;
@@ -195,6 +195,8 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     // rows 11.4 and 13.1 us; d = 1000 6.4 and 5.4; rank 7, 4096: 14.6 and 11.5, 8192: 18.4 and 19.5;
     // rank 32, 4096: 24.3 and 17.3; rank 64, 8192, 1000 rows: 155 and 81)
     if (likely_tiles(a, S) > 200) return false;               // whatever n_layers: a layer's result is that of its one-layer call, bit for bit
+    // Above rank 64 (128-row tiles / this, one launch either way, d = 512 / 2048 / 4096 / 8192, 300 prompt rows, rank 68 22.8 / 10.5, 67 / 25, 124 / 43, 252 / 80, rank 128 23.7 / 14.7, 69 / 41, 131 / 75, 272 / 146;
+    // 32 decode rows, rank 128, 16-row tiles of the column-split kernel, 17.0 / 14.5, 44 / 39, 81 / 75, 149 / 141)
     if (a.rank > 64) return a.rank % 4 == 0;
     if (a.rank > 16) return true;
     // A few decode rows of an adapter each: tiles of which this kernel loads a quarter.  Rank 16, 32 rows of 32 adapters, resident / this, us: d = 4096 9.2 /

@@ -20,7 +20,7 @@
 // MFMA order every lane is an access of its own in the texture path: at rank 64, 89 740 rows of 2 x 28 672, 5290 us instead of 4270.)
 // Two row blocks per wavefront halve the factor traffic; four leave too few wavefronts in flight.
 // gate+up of the 8B layer, rank 16, 36 864 rows (4.2 GB of y), whole call: one launch 931 us, y turned through LDS 801, now 783 = 5.8 TB/s.
-// Rank 33-64: panel_expand_kernel below.
+// Above rank 32: panel_expand_kernel below.
 #pragma once
 #include "common.hpp"
 #include "mfma_kernel.hpp"
@@ -42,8 +42,8 @@ struct FactorLds {
     int r4, column;                                           // quarters of 4 factors, and bytes, of a column
     float inv;
     __device__ __forceinline__ explicit FactorLds(int r) : r4(r >> 2), column(factor_column_bytes(r)), inv(4.0f / (float)r) {}
-    // where quarter i of a contiguous [128][r] block goes.  (i + 0.5) / r4 is below 128 and at least 0.5 / 16 away from a
-    // whole number: the rounding of the product, below 1e-4, never reaches one.
+    // where quarter i of a contiguous [128][r] block goes.  (i + 0.5) / r4 is below 128 and at least 0.5 / 32 away from a
+    // whole number (rank 128; 0.5 / 16 up to rank 64): the rounding of the product, below 1e-4, never reaches one.
     __device__ __forceinline__ int quarter(int i) const
     {
         const int c = (int)(((float)i + 0.5f) * inv);
@@ -262,8 +262,8 @@ __global__ __launch_bounds__(EXPAND_WAVES * 64, 4) void mfma_expand_kernel(Apply
     }
 }
 
-// The same in tiles of 16 RW rows x 128 PU columns whose factors the RW wavefronts share through LDS (rank 33-64, widths multiples of
-// 128 PU; chunks only).  At rank 64 the factors of a wavefront's own columns would be as many bytes as its 32 rows of y; shared by
+// The same in tiles of 16 RW rows x 128 PU columns whose factors the RW wavefronts share through LDS (above rank 32; widths multiples of 128 PU
+// and chunks only, unless ANY).  At rank 64 the factors of a wavefront's own columns would be as many bytes as its 32 rows of y; shared by
 // 64 rows they are half as many.  64 x 256 where every output is a multiple of 256 wide, else 64 x 128.
 // gate+up of a 70B layer, rank 64, 89 740 rows, whole call: one launch 4845 us, two with y turned through LDS 4470, without 4165-4250, and 4060-4120
 // since the shrink launch takes tiles of 128 rows (5.7 TB/s); 8192 -> 8192 946 / 855 / 842; rank 63, 8192 -> 28 672 2586 (one launch) / 2282; 8B layer,

@@ -280,7 +280,7 @@ int64_t out_width(const ApplyArgs &a, int n_slices)
 }
 bool rows_off_lines(const ApplyArgs &a, int n_slices) { return columns_off_lines(a, n_slices) > 0; }
 
-// the shrink launch of rank 17-64 keeps byte offsets within a 64-row tile of x and within a factor in 32 bits
+// the row-split kernel's shrink launch, above rank 16, keeps byte offsets within a 64-row tile of x and within a factor in 32 bits
 inline bool offsets_fit(const ApplyArgs &a) { return a.rank <= 16 || (a.ldx <= (1 << 22) && a.d_in <= (1 << 22)); }
 
 // a workgroup of four wavefronts for every tile of `height` rows x `cols` columns
@@ -366,7 +366,7 @@ bool wants_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs &k)
     return a.T * width >= 6000000 && (width >= 3072 || !rows_off_lines(a, n_slices));
 }
 
-// The in-place call of rank 33-64 as two launches.  The single launch reads h twice as well, in 64-row tiles that sweep all columns; narrow
+// The in-place call above rank 32 as two launches of the row-split order.  The single launch reads h twice as well, in 64-row tiles that sweep all columns; narrow
 // rows find part of the second read in the caches, as long as the batch fills the chip.  Rank 64, one launch -> two, us: 89 740 rows,
 // d = 512 / 1024 / 2048 / 3072 / 4096 / 8192 / 14336: 56 -> 79, 110 -> 131, 234 -> 241, 338 -> 337, 447 -> 433, 878 -> 828, 1620 -> 1446; 23 000 rows, d = 2048
 // 61 -> 69, 3072 90 -> 95, 4096 132 -> 115; 7000 rows, 512 14.8 -> 15.8, 1024 25 -> 23, 2048 45 -> 38, 4096 (10 prompts) 89 -> 56; 2500 rows, 1024 22 -> 18,
@@ -391,7 +391,7 @@ bool column_groups_fit(const ApplyArgs &a, int n_slices)
     return fit;
 }
 
-// The shrink launch of rank 17-64: tiles of 64 rows, or, at rank 33-64 of several outputs or of the largest calls, of 128, whose eight
+// The row-split kernel's shrink launch, above rank 16: tiles of 64 rows, or, at rank 33-64 of several outputs or of the largest calls (above rank 64: see below), of 128, whose eight
 // wavefronts share a step's factors: half the factor traffic, half as many workgroups (and with three outputs the four-wavefront form spills).
 // 64 / 128 rows, whole calls, us: three outputs, 8192 -> 8192 + 2 x 1024, 89 740 rows 1270 / 1124, 4096 -> 4096 + 2 x 1024, 2500 rows 89 / 78, 9500
 // rows 119 / 108; two, 8192 -> 2 x 28672, 89 740 rows 4120 / 4067, 4096 -> 2 x 14336, 23 000 rows 525 / 519, 9500 rows 223 / 233; one,
@@ -430,7 +430,7 @@ void launch_wide_shrink(const ApplyArgs &a, int64_t S, hipStream_t stream)
     hipLaunchKernelGGL(kernel, dim3(chunk_grid(a, S, 16 * waves)), dim3(64 * waves), 0, stream, a);
 }
 
-// rank 17..64: the row-split kernel's shrink sweep of the chunks, then their expand launch
+// above rank 16: the row-split kernel's shrink sweep of the chunks, then their expand launch
 template <int NB, int SLICES, bool DIREFT = false>
 bool launch_mfma_split(const ApplyArgs &a0, int64_t S, const Knobs &k, hipStream_t stream)
 {
