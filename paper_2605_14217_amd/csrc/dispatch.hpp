@@ -157,6 +157,7 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
         if (a.rank <= 32) return a.T <= 4096 || (a.T <= SMALL_STREAM_T && (ragged || a.d_in >= 2048));
         if ((a.T < 20 * S && a.d_in <= 1024) || (a.rank > 64 && a.T > 2048 && a.T < 64 * S)) return false;
         if (ragged) return a.T <= (width <= 4096 ? 4096 : 1536);
+        if (a.rank > 64 && width > 8192 && a.T > 3072) return false;           // rank 128, 8192 -> 14336, 3500 rows without room 438 / 475 (with room 96, 121 as 64-row tiles in two launches)
         return a.T <= 4096 || (a.T <= SMALL_STREAM_T && a.d_in >= 2048 && width <= 16384 && a.rank <= 64);
     }
     if (a.T > SMALL_STREAM_T) return false;
