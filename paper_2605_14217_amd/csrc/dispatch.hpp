@@ -53,11 +53,12 @@ inline int64_t likely_tiles(const ApplyArgs &a, int64_t S)
 // fp32, rank 16, 4096 -> 4096, 38 MB 22.4 / 21.9, 22.0 / 21.0, 21.7 / 20.7, 56 MB 25.1 / 24.2, 24.3 / 23.1, 23.9 / 23.9, 75 MB 32.6 / 29.3, 31.8 / 27.8, 32.0 / 35.8, 112 MB 37.5 / 33.8, 36.6 / 34.3, 37.1 /
 // 41.4, 187 MB 64.0 / 57.5, 64.8 / 71.5, 68.3 / 73.0; rank 20, 1000 -> 2072 (rows off lines), 70 MB 38.1 / 33.8, 38.9 / 33.2, 39.7 / 37.1; rank 31, 3760 -> 600, 70 MB 34.2 / 30.1, 36.4 / 29.7, 36.8 / 35.4.
 // Expands of two launches: rank 32, 4096 -> 4096, 56 MB 27.5 / 26.5, 27.2 / 25.9, 26.6 / 25.3, 75 MB 35.5 / 35.6, 35.1 / 35.1, 35.2 / 38.9; rank 64, 8192 -> 8192, 56 MB 30.8 / 29.4, 30.2 / 29.3,
-// 30.2 / 31.4, 75 MB 39.5 / 38.5, 39.0 / 38.1, 39.2 / 43.7.  So the single launches keep it up to where three such calls fill the cache, the expands, which gain less, up to where four do.
+// 30.2 / 31.4, 75 MB 39.5 / 38.5, 39.0 / 38.1, 39.2 / 43.7.  Column-split kernel, four in turn, 71 MB, 4096 decode rows, rank 48, 488 -> 8192 41.2 / 46.3.  So fp32 goes
+// without it up to where three such calls fill the cache, bf16, which gains less, up to where four do.
 // Below the size of the L2s together (32 MB) the lines of y that were read plainly are written back at the end of the kernel: rank 64, 4096 -> 4096, 28 MB 19.1 / 19.8, 19.2 / 19.5, 18.5 / 19.2; fp32, rank 4,
 // 1024 -> 1024, 23 MB 9.8 / 10.9, 11.0 / 11.6, 11.5 / 11.2, 33 MB 16.8 / 19.0, 18.1 / 18.9, 17.5 / 18.4.  In place in fp32 (the tile is read twice in either form) 47 MB 30.4 / 30.7, 75 MB 51.2 / 59.2: always the hint.
 // Factors count: 4096 decode rows of 512 adapters, rank 44, 4936 -> 896 (48 MB of activations, 260 of factors) 54.1 / 57.7.
-constexpr int64_t STAY_SINGLE = (int64_t)76 << 20, STAY_EXPAND = (int64_t)64 << 20;
+constexpr int64_t STAY_F32 = (int64_t)76 << 20, STAY_BF16 = (int64_t)64 << 20;
 inline bool activations_stay(const ApplyArgs &a, int64_t S, int64_t width, int es, int64_t most)
 {
     const int64_t activations = a.T * (a.d_in + width) * es, factors = likely_adapters(S, a.N) * a.rank * (a.d_in + width) * es;

@@ -205,7 +205,7 @@ void launch_mfma(const ApplyArgs &a, int64_t S, hipStream_t stream)
     constexpr int R = 16 * MB;
     void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, MB, WAVES, HUNITS, DIREFT>;
     if constexpr (NB > 1 && !DIREFT) {
-        if (activations_stay(a, S, a.d_out, 2, STAY_SINGLE)) kernel = mfma_tile_kernel<NB, MB, WAVES, HUNITS, DIREFT, 1, false, 0, false, false>;
+        if (activations_stay(a, S, a.d_out, 2, STAY_BF16)) kernel = mfma_tile_kernel<NB, MB, WAVES, HUNITS, DIREFT, 1, false, 0, false, false>;
     }
     if constexpr (DIREFT) {
         if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, MB, WAVES, HUNITS>;
@@ -304,7 +304,7 @@ void launch_expand_kernel(void (*kernel)(ApplyArgs, int), ApplyArgs a, int64_t S
 template <int NB, bool ODD>
 void launch_expand(const ApplyArgs &a, int64_t S, int n_slices, hipStream_t stream)
 {
-    const bool stay = a.x == a.y ? h_stays(a) : activations_stay(a, S, out_width(a, n_slices), 2, STAY_EXPAND);
+    const bool stay = a.x == a.y ? h_stays(a) : activations_stay(a, S, out_width(a, n_slices), 2, STAY_BF16);
     if constexpr (NB <= 2) {
         void (*kernel)(ApplyArgs, int) = mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::All>;
         if (stay) kernel = mfma_expand_kernel<NB, EXPAND_MB, ODD, YHint::None>;
@@ -458,7 +458,7 @@ void launch_small_split(const ApplyArgs &a, int64_t S, int n_slices, const Knobs
         waves = small_shape(a, S, n_slices, k).waves;         // the single launch's: its sums of z are grouped by them
         if (waves == 4) shrink = nb == 4 ? small_shrink_kernel<4, false, 0, 4> : nb == 3 ? small_shrink_kernel<3, false, 0, 4> : small_shrink_kernel<2, false, 0, 4>;
     }
-    const bool stay = DIREFT ? h_stays(a) : activations_stay(a, S, out_width(a, n_slices), 2, STAY_EXPAND);
+    const bool stay = DIREFT ? h_stays(a) : activations_stay(a, S, out_width(a, n_slices), 2, STAY_BF16);
     hipLaunchKernelGGL(shrink, dim3((unsigned)(n_slices * rank_parts) * 8, slots), dim3(waves * 64), 0, stream, a, n_slices);
     if (a.rank <= 32)
         launch_expand<2, false>(a, S, n_slices, stream);
@@ -545,7 +545,7 @@ bool launch_mfma_wide(const ApplyArgs &a, int64_t S, int mb, int waves, int cw, 
 template <int NB, bool DIREFT>
 void launch_mfma_odd_stream(const ApplyArgs &a, int64_t S, int mb, hipStream_t stream)
 {
-    const bool stay = !DIREFT && activations_stay(a, S, a.d_out, 2, STAY_SINGLE);
+    const bool stay = !DIREFT && activations_stay(a, S, a.d_out, 2, STAY_BF16);
     void (*kernel)(ApplyArgs) = mfma_tile_kernel<NB, 1, 4, 0, DIREFT, 1, false, 1>;
     if constexpr (!DIREFT) { if (stay) kernel = mfma_tile_kernel<NB, 1, 4, 0, DIREFT, 1, false, 1, false, false>; }
     if constexpr (DIREFT) { if (a.h_layers) kernel = mfma_tile_layers_kernel<NB, 1, 4, 0, false, 1>; }
@@ -882,7 +882,7 @@ void launch_f32_nb(const ApplyArgs &a, int64_t S, hipStream_t stream)
         if (a.h_layers) kernel = (a.rank % 4) ? f32_tile_layers_kernel<NB, true> : f32_tile_layers_kernel<NB, false>;
         else            kernel = (a.rank % 4) ? f32_tile_kernel<NB, true, true, BY_LDS> : f32_tile_kernel<NB, true, false, false>;
     } else {
-        const bool stay = activations_stay(a, S, a.d_out, 4, STAY_SINGLE);
+        const bool stay = activations_stay(a, S, a.d_out, 4, STAY_F32);
         kernel = (a.rank % 4) ? f32_tile_kernel<NB, false, true, BY_LDS> : f32_tile_kernel<NB, false, false, false>;
         if (stay) kernel = (a.rank % 4) ? f32_tile_kernel<NB, false, true, BY_LDS, false> : f32_tile_kernel<NB, false, false, false, false>;
         // A workgroup of one or two units of 64 columns has one or two wavefronts at work on them, and LDS is only a further step on their way; at

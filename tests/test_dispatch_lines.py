@@ -72,7 +72,7 @@ def test_units_stay_in_registers_where_the_tiles_are_full(tmp_path_factory):
 
 
 def test_what_is_read_without_the_non_temporal_hint(tmp_path_factory):
-    """Activations between the L2s together and a quarter (fp32 and single launches: a third) of the memory-side cache, the factors of many adapters counted; in place 20 to 64 MB of h."""
+    """Activations between the L2s together and a quarter (fp32: a third) of the memory-side cache, the factors of many adapters counted; in place 20 to 64 MB of h."""
     lora = [(2300, 4, 4, 0, 16, 4096, 4096, 4), (2600, 4, 4, 0, 16, 4096, 4096, 4), (3000, 4, 4, 0, 32, 4096, 4096, 2), (4400, 4, 4, 0, 32, 4096, 4096, 2), (1900, 4, 4, 0, 32, 4096, 4096, 2),
             (3000, 3000, 512, 1, 44, 4096, 4096, 2)]
     assert [a["stay"] for a in lines(tmp_path_factory, lora)] == [True, False, True, False, False, False]
