@@ -172,8 +172,10 @@ inline bool no_long_stream(const ApplyArgs &a, int64_t S, int64_t width)
     if (a.rank >= 4 && !singles && d > 8192 && width > 4096) return false;   // rank 11, 14336 -> 5176, 1470 prompt rows 26.7 / 42.5, rank 16, 14336 -> 5832, 1490 31 / 38, 4224, 1720 28 / 36 (rank 5, 14336 -> 4448, 1300 26 / 18)
     if (width > 10240 && !(a.rank < 4 && singles)) return false;          // rank 8, 912 -> 14336 + 4096 + 1512, 1240 prompt rows 28.3 / 34.0
     // (8192 -> 6144, rank 12, 1600 rows (33) 21.7 / 24.2, 2800 (57) 28.2 / 31.5)
+    // (and where the activations have left the caches its order over y costs more than the expand's: four sets of buffers in turn / two, geometric mean of the time before over random calls of rank 4-16 of 40 to 56
+    // million 0.90 / 0.88, of 56 to 76 1.05 / 0.92: rank 16, 4096 -> 3072 + 184, 6000 rows (64) 36.6 / 43.3, rank 11, 112 -> 1024 + 8192, 3400 (62) 30.1 / 38.3)
     const int64_t elements = a.T * (d + 2 * width) + likely_adapters(S, a.N) * a.rank * (d + width);
-    const int64_t most = a.rank < 4 && singles ? 120000000 : d >= 8192 && width > 4608 && a.T >= 8 * S ? 24000000 : 76000000;
+    const int64_t most = a.rank < 4 && singles ? 120000000 : d >= 8192 && width > 4608 && a.T >= 8 * S ? 24000000 : 56000000;
     return elements <= most;
 }
 

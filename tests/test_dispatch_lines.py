@@ -91,6 +91,6 @@ def test_ranks_1_to_3_that_stay_with_the_vector_alu(tmp_path_factory):
 
 def test_ranks_4_to_16_above_1024_rows_that_stay_with_the_kernels_of_larger_batches(tmp_path_factory):
     """Narrow inputs and outputs, and wide inputs with wide outputs."""
-    no = [(3500, 2, 4, 0, 16, 768, 1296, 2), (2000, 106, 4, 0, 12, 2304, 1024, 2), (2800, 7, 32, 0, 8, 2048, 2048, 2), (2800, 7, 32, 0, 12, 8192, 6144, 2)]
-    yes = [(4000, 10, 32, 0, 8, 2048, 2048, 2), (2800, 7, 32, 0, 9, 2048, 2048, 2), (2800, 7, 32, 0, 12, 8192, 4096, 2), (2800, 7, 32, 0, 4, 4096, 8448, 2)]
-    assert [a["small"] for a in lines(tmp_path_factory, no + yes)] == [False] * 4 + [True] * 4
+    no = [(3500, 2, 4, 0, 16, 768, 1296, 2), (2000, 106, 4, 0, 12, 2304, 1024, 2), (2800, 7, 32, 0, 8, 2048, 2048, 2), (2800, 7, 32, 0, 12, 8192, 6144, 2), (6000, 5, 64, 0, 16, 4096, 3256, 2)]
+    yes = [(4000, 10, 32, 0, 8, 2048, 2048, 2), (2800, 7, 32, 0, 9, 2048, 2048, 2), (2800, 7, 32, 0, 12, 8192, 4096, 2), (2400, 7, 32, 0, 4, 4096, 8448, 2)]
+    assert [a["small"] for a in lines(tmp_path_factory, no + yes)] == [False] * 5 + [True] * 4
