@@ -249,13 +249,13 @@ inline bool small_in_two(const ApplyArgs &a, int64_t S, int64_t width, bool dire
     // order: rank 32, 4096 -> 4096, 4000 / 4600 / 5750 rows, four sets of buffers in turn 32.9 / 38.1, 35.0 / 42.8, 38.9 / 46.7.
     if (a.T > SMALL_T) return a.rank <= 32 ? width > (a.T > 3840 ? 2048 : 4096) : a.rank <= 64 ? width > 1024 && a.d_in * width > 640000 : width > 512;
     const int64_t tiles = likely_tiles(a, S), panels = tiles * width;
+    // (tiles enough to fill the chip hide the single launch's shrinks: 900 decode rows of 200 / 500 adapters, one / two, 4096 -> 512, rank 68 29.0 / 33.7, 49.7 / 59.4, rank 128 43.5 / 49.4, 102 / 108, 4096 ->
+    // 4096, rank 68 53.6 / 67.0, 115 / 149, 96 72 / 86, 149 / 170, 128 107 / 111, 203 / 208; 150 of 200, rank 96, 8192 -> 2144 55 / 50; 512 of 64, 4096 -> 512 22.5 / 19.2; in place, rank 96, 2880, 426 of 200 42.9 / 54.6)
+    if (a.rank > 64 && singles && tiles > 160) return false;
     // (in place, decode rows of many adapters: rank 48, d = 3184, 209 of 376 20.8 / 23.6, 2688, 535 of 197 (184 tiles) 22.3 / 31.4, 4096, 730 of 54 (72 tiles) 25.5 / 22.9)
     if (direft && a.rank > 32 && a.rank <= 48 && a.d_in <= 4096 && singles && tiles > 128) return false;
     // (above rank 64, one / two: d = 104, 180 rows 7.7 / 14.5, 128, 109 8.1 / 9.3, 256, 68 7.9 / 9.9, 384, 362 9.3 / 10.5)
     if (direft) return a.rank > 64 ? a.d_in >= 512 : (a.rank > 48 ? a.d_in >= 1024 : a.rank > 32 ? a.d_in >= 2048 : a.d_in >= 8192 && tiles <= 48);
-    // (tiles enough to fill the chip hide the single launch's shrinks: 900 decode rows of 200 / 500 adapters, one / two, 4096 -> 512, rank 68 29.0 / 33.7, 49.7 / 59.4, rank 128 43.5 / 49.4, 102 / 108, 4096 ->
-    // 4096, rank 68 53.6 / 67.0, 115 / 149, 96 72 / 86, 149 / 170, 128 107 / 111, 203 / 208; 150 of 200, rank 96, 8192 -> 2144 55 / 50; 512 of 64, 4096 -> 512 22.5 / 19.2)
-    if (a.rank > 64 && singles && tiles > 160) return false;
     if (a.rank > 112) return a.d_in > 640 || panels >= 24000;    // 512 -> 1056, 29 decode rows 8.5 / 9.7, 512 -> 608, 242 prompt rows 8.7 / 9.6; 512 -> 8192, 3 rows 10.1 / 9.4
     if (a.rank > 64) return a.d_in >= 4096 || (!singles && panels >= 100000);
     // (decode rows: rank 56, 8192 -> 320 + 8192 + 1024, 725 of 32 adapters 35.9 / 46.1, 1416 -> 1952, 234 of 200 20.3 / 28.7; over all, one and two alike)

@@ -53,8 +53,8 @@ def test_the_second_launch_of_few_tiles_has_a_shrink_to_save(tmp_path_factory):
     assert not any(a["two"] for a in lines(tmp_path_factory, one))
     two = [(3000, 8, 64, 0, rank, d, n, 2) for rank, d, n in ((20, 4096, 8192), (48, 1024, 4096), (64, 4096, 1536), (68, 1024, 1024), (128, 512, 4096))] + [(900, 5, 5, 0, 64, 4096, 4096, 2), (512, 512, 64, 1, 96, 4096, 1024, 2)]
     assert all(a["two"] for a in lines(tmp_path_factory, two))
-    in_place = lines(tmp_path_factory, [(180, 24, 64, 1, 68, 104, 104, 2), (362, 362, 32, 1, 68, 384, 384, 2), (286, 3, 4, 0, 128, 144, 144, 2), (300, 2, 5, 0, 128, 512, 512, 2), (300, 2, 5, 0, 96, 4096, 4096, 2)])
-    assert [a["in_place_two"] for a in in_place] == [False, False, False, True, True]
+    in_place = lines(tmp_path_factory, [(180, 24, 64, 1, 68, 104, 104, 2), (362, 362, 32, 1, 68, 384, 384, 2), (286, 3, 4, 0, 128, 144, 144, 2), (300, 2, 5, 0, 128, 512, 512, 2), (300, 2, 5, 0, 96, 4096, 4096, 2), (426, 426, 200, 1, 96, 2880, 2880, 2)])
+    assert [a["in_place_two"] for a in in_place] == [False, False, False, True, True, False]
 
 
 def test_tiles_of_an_expand_launch_are_counted_as_they_are_numbered(tmp_path_factory):
