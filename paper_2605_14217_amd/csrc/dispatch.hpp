@@ -190,6 +190,8 @@ inline bool takes_small(const ApplyArgs &a, int64_t S, int32_t widest, int64_t w
     // Ranks 1 and 2, next to nothing to expand: the vector-ALU kernel / this, us: rank 1, 8192 -> 512, 41 rows 4.8 / 6.9, 14336 -> 1024, 19 rows 6.5 / 9.6, 7040 -> 512, 850 rows 5.5 / 6.8, 2048 -> 408, 14 rows 3.7
     // / 4.1 (d_in from 4 to 8 times the columns, 10 calls 0.93, 8 times and more, 8 calls 1.14; below 4 times 0.77 and less); rank 2, 9016 -> 1024, 8 rows 6.6 / 7.4, 4096 -> 88, 1100 rows 8.6 / 9.9.
     if (!direft && (a.rank == 1 ? 4 : 8) * width <= a.d_in && a.rank <= 2) return false;
+    // (and many rows of narrow prompts: rank 1, 512 -> 1024, 585 rows 4.7 / 6.1, 240 -> 1024, 504 4.5 / 5.6; up to 300 rows 0.87-1.03 of the time)
+    if (!direft && a.rank == 1 && a.d_in <= 1024 && width <= 1024 && a.T > 384 && !(a.all_tokens && a.T < 2 * S)) return false;
     // A very wide output beside narrow ones: every share of these repeats the shrink as well, and the wide one's take 64 units where 32 of 8192 columns do: 4096 -> 136 + 208 + 8448, 2900 rows, rank 4 33.3 /
     // 47.5, 16 37.4 / 52.6; decode rows, rank 2, 2048 -> 256 + 384 + 14336, 4096 73 / 85 (4096 -> 512 + 8192, rank 16 32.7 / 33.4).
     if (!direft && a.T > SMALL_T && widest > 8192 && width > widest && 4 * (width - widest) < widest) return false;

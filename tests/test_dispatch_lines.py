@@ -83,8 +83,8 @@ def test_what_is_read_without_the_non_temporal_hint(tmp_path_factory):
 def test_ranks_1_to_3_that_stay_with_the_vector_alu(tmp_path_factory):
     """Next to nothing to expand, in place narrow rows, or tiles enough to fill the chip with the layers of one call."""
     lora = [(41, 34, 32, 0, 1, 8192, 512, 2), (850, 2, 1, 0, 1, 7040, 512, 2), (8, 1, 64, 0, 2, 9016, 1024, 2), (2000, 2000, 500, 1, 1, 4096, 512, 2), (1300, 38, 64, 1, 1, 1024, 1024, 2),
-            (41, 34, 32, 0, 1, 4096, 4096, 2), (41, 34, 32, 0, 3, 8192, 512, 2)]
-    assert [a["small"] for a in lines(tmp_path_factory, lora)] == [False] * 5 + [True] * 2
+            (585, 130, 512, 0, 1, 512, 1024, 2), (41, 34, 32, 0, 1, 4096, 4096, 2), (41, 34, 32, 0, 3, 8192, 512, 2)]
+    assert [a["small"] for a in lines(tmp_path_factory, lora)] == [False] * 6 + [True] * 2
     h = [(81, 74, 512, 1, 2, 896, 896, 2), (304, 57, 200, 1, 2, 3456, 3456, 2), (105, 14, 512, 0, 3, 128, 128, 2), (32, 32, 8, 1, 2, 896, 896, 2), (100, 2, 8, 0, 3, 1024, 1024, 2)]
     assert [a["in_place_small"] for a in lines(tmp_path_factory, h)] == [False, False, False, True, True]
 
